@@ -145,6 +145,16 @@ struct bsse_game {
     // pinned host
     HostOut *h_out = nullptr;
     int32_t *h_br = nullptr;
+    float *h_x = nullptr, *h_l = nullptr;   // any-shape kernel: the winner's row [m] and per-type leader payoffs [K]
+    bool hx_valid = false;                  // h_x holds the row of the result last reported
+    // Any-shape kernel: a sweep in one call leaves its result on the host only (h_out->run, h_x, h_br);
+    // the device copies (w.run, w.best_x) are brought up to date when a further chunk needs them.
+    bool host_best = false;
+    float *row_l = nullptr;                 // per-type outputs of sliced launches, type-major
+    int32_t *row_br = nullptr;
+    size_t cap_row_l = 0, cap_row_br = 0;
+    unsigned char *h_rec = nullptr;         // pinned: records of launch_finish_rows
+    size_t cap_rec = 0;
     long long n_evals = 0;
     bool fresh = true;       // the next chunk starts a new sweep
     bool result_valid = false;   // bsse_sweep_result has reported the sweep in the handle's own scratch
@@ -218,6 +228,10 @@ void free_game(bsse_game *g)
     (void)hipFree(g->centre_dev); (void)hipFree(g->stage);
     if (g->h_out) (void)hipHostFree(g->h_out);
     if (g->h_br) (void)hipHostFree(g->h_br);
+    if (g->h_x) (void)hipHostFree(g->h_x);
+    if (g->h_l) (void)hipHostFree(g->h_l);
+    if (g->h_rec) (void)hipHostFree(g->h_rec);
+    (void)hipFree(g->row_l); (void)hipFree(g->row_br);
     for (hipEvent_t e : g->ev) (void)hipEventDestroy(e);
     for (hipEvent_t e : g->ev_pool) (void)hipEventDestroy(e);
     delete g;
@@ -256,9 +270,12 @@ bsse_status ensure_gen(bsse_game *g, unsigned long long rows)
     return BSSE_OK;
 }
 
+bool on_any(const bsse_game *g) { return g->path != PATH_VALU && g->view.variant == kAnyVariant; }
+
 hipError_t launch_sweep_on(bsse_game *g, const SweepArgs &a, bool eval, hipStream_t stream)
 {
     if (g->path == PATH_VALU) return launch_sweep_valu(g->view, a, eval, stream);
+    if (on_any(g)) return launch_sweep_any(g->view, a, 1, stream);
     (void)eval;
     return launch_sweep_mfma(g->view, a, stream);
 }
@@ -270,7 +287,53 @@ hipError_t launch_sweep(bsse_game *g, const SweepArgs &a, bool eval)
 
 long long sweep_blocks(const bsse_game *g, long long count)
 {
+    if (on_any(g)) return any_num_blocks(g->view, count);
     return g->path == PATH_VALU ? valu_num_blocks(count) : mfma_num_blocks(g->view.variant, count);
+}
+
+// A block of handle-owned memory of at least `bytes`; nothing enqueued may still use the old one.
+bsse_status grow_device(bsse_game *g, void **ptr, size_t *cap, size_t bytes)
+{
+    if (bytes <= *cap) return BSSE_OK;
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    (void)hipFree(*ptr);
+    *ptr = nullptr; *cap = 0;
+    HIP_TRY(hipMalloc(ptr, bytes));
+    *cap = bytes;
+    return BSSE_OK;
+}
+
+bsse_status grow_pinned(bsse_game *g, void **ptr, size_t *cap, size_t bytes)
+{
+    if (bytes <= *cap) return BSSE_OK;
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    if (*ptr) (void)hipHostFree(*ptr);
+    *ptr = nullptr; *cap = 0;
+    if (hipHostMalloc(ptr, bytes, hipHostMallocDefault) != hipSuccess)
+        return fail(BSSE_ENOMEM, "hipHostMalloc of %zu bytes failed", bytes);
+    *cap = bytes;
+    return BSSE_OK;
+}
+
+// Per-type outputs of a sliced launch: at most this many (64 MiB of leader payoffs).
+constexpr long long ROW_SCRATCH_MAX = 1LL << 24;
+
+// Per-candidate outputs (a.V_out, a.br_out [count][K], a.l_out [count][K]; each nullable).
+bsse_status launch_eval(bsse_game *g, SweepArgs a)
+{
+    if (!on_any(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
+    a.br_sc = g->K; a.br_st = 1; a.l_sc = g->K; a.l_st = 1;
+    int slices = any_slices(g->view, a.count);
+    if (a.V_out && (a.l_out || a.count * g->K > ROW_SCRATCH_MAX)) slices = 1;
+    if (slices == 1 || !a.V_out) { HIP_TRY(launch_sweep_any(g->view, a, slices, g->stream)); return BSSE_OK; }
+    bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float));
+    if (st != BSSE_OK) return st;
+    FinishRowsArgs f{};
+    f.l = g->row_l; f.prior = g->dprior; f.count = a.count; f.K = g->K; f.m = g->m; f.V_out = a.V_out;
+    a.V_out = nullptr; a.l_out = g->row_l; a.l_sc = 1; a.l_st = a.count;
+    HIP_TRY(launch_sweep_any(g->view, a, slices, g->stream));
+    HIP_TRY(launch_finish_rows(f, g->stream));
+    return BSSE_OK;
 }
 
 bsse_status take_event(bsse_game *g, hipEvent_t *e)
@@ -418,6 +481,11 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
                 path = PATH_MFMA_F32;
             }
         }
+        // every other shape the matrix cores pay for: tiles padded as needed
+        if (path == PATH_VALU && any_supported(m, n)) {
+            variant = kAnyVariant;
+            path = bf ? PATH_MFMA_BF16 : PATH_MFMA_SPLIT;
+        }
     }
     const bool use_mfma = path != PATH_VALU;
 
@@ -446,15 +514,18 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     DeviceGuard dg(dev);
     if (!dg.ok) { free_game(g); return fail(BSSE_EDEVICE, "hipSetDevice(%d) failed", dev); }
 
-    // ---- pack on the host: optional bf16 rounding, B as given, A transposed per type
-    std::vector<float> hB(elems), hAT(elems), hA;
-    for (unsigned long long e = 0; e < elems; ++e) hB[e] = bf ? host_round_bf16(B[e]) : B[e];
-    for (int t = 0; t < K; ++t)
-        for (int i = 0; i < m; ++i)
-            for (int j = 0; j < n; ++j) {
-                const float a = A[((size_t)t * m + i) * n + j];
-                hAT[((size_t)t * n + j) * m + i] = bf ? host_round_bf16(a) : a;
-            }
+    // ---- vector path: pack on the host: optional bf16 rounding, B as given, A transposed per type
+    std::vector<float> hB, hAT;
+    if (!use_mfma) {
+        hB.resize(elems); hAT.resize(elems);
+        for (unsigned long long e = 0; e < elems; ++e) hB[e] = bf ? host_round_bf16(B[e]) : B[e];
+        for (int t = 0; t < K; ++t)
+            for (int i = 0; i < m; ++i)
+                for (int j = 0; j < n; ++j) {
+                    const float a = A[((size_t)t * m + i) * n + j];
+                    hAT[((size_t)t * n + j) * m + i] = bf ? host_round_bf16(a) : a;
+                }
+    }
 
     bsse_status st = BSSE_OK;
     auto up = [&](void **dst, const void *src, size_t bytes) -> bsse_status {
@@ -468,11 +539,32 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         return BSSE_OK;
     };
     do {
-        if ((st = up((void **)&g->dB, hB.data(), elems * 4)) != BSSE_OK) break;
-        if ((st = up((void **)&g->dAT, hAT.data(), elems * 4)) != BSSE_OK) break;
+        if (!use_mfma && (st = up((void **)&g->dB, hB.data(), elems * 4)) != BSSE_OK) break;
+        if (!use_mfma && (st = up((void **)&g->dAT, hAT.data(), elems * 4)) != BSSE_OK) break;
         if ((st = up((void **)&g->dprior, prior, (size_t)K * 4)) != BSSE_OK) break;
+        g->view.m = m; g->view.n = n; g->view.K = K;
         g->view.m_pad = m; g->view.n_pad = n;
-        if (use_mfma) {
+        if (use_mfma && variant == kAnyVariant) {
+            // packed on the device from the payoffs as given
+            g->view.any = any_geometry(m, n, K, bf ? 1 : exact ? 3 : 6);
+            size_t bb = 0, ab = 0;
+            any_pack_sizes(g->view, &bb, &ab);
+            float *rawA = nullptr, *rawB = nullptr;
+            st = up((void **)&rawA, A, elems * 4);
+            if (st == BSSE_OK) st = up((void **)&rawB, B, elems * 4);
+            hipError_t pe = hipSuccess;
+            if (st == BSSE_OK && (pe = hipMalloc(&g->dBpack, bb)) == hipSuccess && (pe = hipMalloc(&g->dATpack, ab)) == hipSuccess &&
+                (pe = launch_any_pack(g->view, rawA, rawB, g->dBpack, g->dATpack, nullptr)) == hipSuccess &&
+                (pe = hipStreamSynchronize(nullptr)) == hipSuccess)
+                pe = any_prepare(g->view);
+            (void)hipFree(rawA); (void)hipFree(rawB);
+            if (st == BSSE_OK && pe != hipSuccess)
+                st = fail(pe == hipErrorOutOfMemory ? BSSE_ENOMEM : BSSE_EDEVICE, "packing: %s", hipGetErrorString(pe));
+            if (st != BSSE_OK) break;
+            hipError_t he = hipHostMalloc((void **)&g->h_x, (size_t)m * 4, hipHostMallocDefault);
+            if (he == hipSuccess) he = hipHostMalloc((void **)&g->h_l, (size_t)K * 4, hipHostMallocDefault);
+            if (he != hipSuccess) { st = fail(BSSE_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(he)); break; }
+        } else if (use_mfma) {
             void *pb = nullptr, *pa = nullptr;
             size_t bb = 0, ab = 0;
             mfma_pack(variant, m, n, K, A, B, &pb, &bb, &pa, &ab, &g->view.m_pad, &g->view.n_pad);
@@ -538,7 +630,7 @@ extern "C" const char *bsse_path_name(const bsse_game *g)
     case PATH_VALU: return g->storage == BSSE_STORAGE_BF16 ? "valu_bf16" : "valu";
     case PATH_MFMA_F32:
     case PATH_MFMA_BF16:
-    case PATH_MFMA_SPLIT: return mfma_variant_name(g->view.variant);
+    case PATH_MFMA_SPLIT: return on_any(g) ? any_name(g->view.any) : mfma_variant_name(g->view.variant);
     }
     return "";
 }
@@ -743,6 +835,15 @@ bool on_small_kernel(const bsse_game *g)
     return g->path != PATH_VALU && mfma_is_small(g->view.variant);
 }
 
+// The value of a re-evaluated winner on the any-shape path, from its per-type leader payoffs: the
+// kernel's own sum, term by term.
+float value_of(const bsse_game *g, const float *l)
+{
+    float v = 0.0f;
+    for (int t = 0; t < g->K; ++t) v = std::fmaf(g->hprior[t], l[t], v);
+    return v;
+}
+
 // The caller's stream waits for whatever the handle's own streams still have in flight.
 bsse_status join_aux(bsse_game *g)
 {
@@ -771,6 +872,12 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     bsse_status st;
     const long long count = a.count;
     const bool small = on_small_kernel(g);
+    if (g->host_best && !g->fresh) {             // the running best so far goes back to the device
+        HIP_TRY(hipMemcpyAsync(g->w.run, &g->h_out->run, sizeof(RunningBest), hipMemcpyHostToDevice, g->stream));
+        HIP_TRY(hipMemcpyAsync(g->w.best_x, g->h_x, (size_t)g->m * sizeof(float), hipMemcpyHostToDevice, g->stream));
+        HIP_TRY(hipStreamSynchronize(g->stream));     // (the host copies are free to change)
+    }
+    g->host_best = false; g->hx_valid = false;
     long long nblocks = 0;
     hipStream_t stream = g->stream;
     if (small) {
@@ -849,6 +956,9 @@ bsse_status fold_small(bsse_game *g)
 
 bool fuses_generation(const bsse_game *g) { return on_small_kernel(g); }
 
+// Rows of the staging buffer generated candidates pass through (at most 2^26 floats).
+long long stage_rows(const bsse_game *g) { return (1LL << 26) / g->m; }
+
 bsse_status check_rows(int64_t first, int64_t count)
 {
     if (first < 0 || count < 0) return fail(BSSE_EINVAL, "first and count must be >= 0");
@@ -897,16 +1007,8 @@ extern "C" bsse_status bsse_sweep_dirichlet_chunk(bsse_game *g, uint64_t seed, i
     }
     // other shapes: the rows pass through a staging buffer of the handle (at most 2^26 floats),
     // piece by piece on the handle's stream
-    long long piece = (1LL << 26) / g->m;
-    if (piece > count) piece = count;
-    const size_t bytes = (size_t)piece * g->m * sizeof(float);
-    if (bytes > g->stage_cap) {
-        HIP_TRY(hipStreamSynchronize(g->stream));
-        (void)hipFree(g->stage);
-        g->stage = nullptr; g->stage_cap = 0;
-        HIP_TRY(hipMalloc((void **)&g->stage, bytes));
-        g->stage_cap = bytes;
-    }
+    const long long piece = count < stage_rows(g) ? count : stage_rows(g);
+    if ((st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)piece * g->m * sizeof(float))) != BSSE_OK) return st;
     for (long long base = 0; base < count; base += piece) {
         const long long rows = count - base < piece ? count - base : piece;
         HIP_TRY(launch_dirichlet(seed, first + base, rows, g->m, nullptr, 1.0f, g->stage, g->stream));
@@ -915,6 +1017,10 @@ extern "C" bsse_status bsse_sweep_dirichlet_chunk(bsse_game *g, uint64_t seed, i
         if ((st = sweep_chunk_impl(g, a)) != BSSE_OK) return st;
     }
     return BSSE_OK;
+}
+
+namespace {
+bsse_status sweep_once_any(bsse_game *g, const float *X, long long count, bsse_result *res, int32_t *best_response_out);
 }
 
 extern "C" bsse_status bsse_sweep_dirichlet(bsse_game *g, uint64_t seed, int64_t first, int64_t count,
@@ -926,8 +1032,19 @@ extern "C" bsse_status bsse_sweep_dirichlet(bsse_game *g, uint64_t seed, int64_t
     bsse_status st = check_rows(first, count);
     if (st != BSSE_OK) return st;
     if ((st = bsse_sweep_reset(g)) != BSSE_OK) return st;
+    if (on_any(g) && count > 0 && count <= stage_rows(g)) {
+        DeviceGuard dg(g->device);
+        if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
+        if ((st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)count * g->m * sizeof(float))) != BSSE_OK) return st;
+        HIP_TRY(launch_dirichlet(seed, first, count, g->m, nullptr, 1.0f, g->stage, g->stream));
+        return sweep_once_any(g, g->stage, count, res, best_response_out);
+    }
     if ((st = bsse_sweep_dirichlet_chunk(g, seed, first, count, 0)) != BSSE_OK) return st;
     return bsse_sweep_result(g, res, best_response_out);
+}
+
+namespace {
+bsse_status report_result(bsse_game *g, bsse_result *res, int32_t *best_response_out);
 }
 
 extern "C" bsse_status bsse_sweep_result(bsse_game *g, bsse_result *res, int32_t *best_response_out)
@@ -947,6 +1064,15 @@ extern "C" bsse_status bsse_sweep_result(bsse_game *g, bsse_result *res, int32_t
     if (on_small_kernel(g)) {
         bsse_status st = fold_small(g);
         if (st != BSSE_OK) return st;
+    } else if (on_any(g)) {
+        if (!g->host_best) {
+            SweepArgs a{};
+            a.X = g->w.best_x; a.count = 1;
+            a.br_out = g->h_br; a.br_sc = g->K; a.br_st = 1;
+            a.l_out = g->h_l; a.l_sc = g->K; a.l_st = 1;
+            a.row_host = g->h_x;
+            HIP_TRY(launch_sweep_any(g->view, a, any_slices(g->view, 1), g->stream));
+        }
     } else {
         SweepArgs a{};
         a.X = g->w.best_x; a.count = 1; a.index_base = 0;
@@ -955,8 +1081,20 @@ extern "C" bsse_status bsse_sweep_result(bsse_game *g, bsse_result *res, int32_t
         if (g->path != PATH_VALU && mfma_slices_types(g->view.variant)) a.l_out = g->w.win_l;
         HIP_TRY(launch_sweep(g, a, true));
     }
-    HIP_TRY(hipStreamSynchronize(g->stream));
+    if (!g->host_best) HIP_TRY(hipStreamSynchronize(g->stream));
+    return report_result(g, res, best_response_out);
+}
+
+namespace {
+
+// The result in the handle's host memory (everything that writes it has run).
+bsse_status report_result(bsse_game *g, bsse_result *res, int32_t *best_response_out)
+{
     const bool has = g->h_out->run.has != 0;
+    if (on_any(g)) {
+        if (!g->host_best && has) g->h_out->fin_v = value_of(g, g->h_l);
+        g->hx_valid = has;
+    }
     if (has && !(g->h_out->fin_v == g->h_out->run.value))
         return fail(BSSE_EDEVICE, "internal: re-evaluated winner value %.9g differs from swept value %.9g",
                     (double)g->h_out->fin_v, (double)g->h_out->run.value);
@@ -969,6 +1107,84 @@ extern "C" bsse_status bsse_sweep_result(bsse_game *g, bsse_result *res, int32_t
     return BSSE_OK;
 }
 
+// One whole sweep (already reset) of rows that stay put until it is done, on the any-shape path: two
+// launches and one wait, whatever the size.  Few rows: a type-sliced launch, and one that sums the
+// values and leaves a record per 256 rows, with that record's row and best responses, in pinned memory;
+// the host folds the records.  Many rows: the sweep, and one launch whose workgroups each fold its
+// records and evaluate their slice of the types at the winner.
+bsse_status sweep_once_any(bsse_game *g, const float *X, long long count, bsse_result *res, int32_t *best_response_out)
+{
+    const int m = g->m, K = g->K;
+    bsse_status st;
+    g->host_best = false; g->hx_valid = false;
+    const int slices = any_slices(g->view, count);
+    const long long nrec = (count + FINISH_ROWS - 1) / FINISH_ROWS;
+    const bool rows = slices > 1 && nrec <= 256 && nrec * (m + K) <= (1LL << 18) && count * K <= ROW_SCRATCH_MAX;
+    SweepArgs a{};
+    a.X = X; a.count = count; a.tie_counter = g->w.tie_counter;
+    const size_t off_x = (size_t)nrec * sizeof(FinishRec), off_br = off_x + (size_t)nrec * m * sizeof(float);
+    if (rows) {
+        if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * K * sizeof(float))) != BSSE_OK) return st;
+        if ((st = grow_device(g, (void **)&g->row_br, &g->cap_row_br, (size_t)count * K * sizeof(int32_t))) != BSSE_OK) return st;
+        if ((st = grow_pinned(g, (void **)&g->h_rec, &g->cap_rec, off_br + (size_t)nrec * K * sizeof(int32_t))) != BSSE_OK) return st;
+        a.l_out = g->row_l; a.l_sc = 1; a.l_st = count;
+        a.br_out = g->row_br; a.br_sc = 1; a.br_st = count;
+    } else {
+        if ((st = ensure_blocks(g, any_num_blocks(g->view, count))) != BSSE_OK) return st;
+        a.blk_v = g->w.blk_v; a.blk_i = g->w.blk_i;
+    }
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (g->timing) {
+        if ((st = take_event(g, &e0)) != BSSE_OK) return st;
+        if ((st = take_event(g, &e1)) != BSSE_OK) { g->ev_pool.push_back(e0); return st; }
+        HIP_TRY(hipEventRecord(e0, g->stream));
+    }
+    const hipError_t le = launch_sweep_any(g->view, a, rows ? slices : 1, g->stream);
+    if (g->timing) {
+        (void)hipEventRecord(e1, g->stream);
+        g->ev.push_back(e0); g->ev.push_back(e1);
+    }
+    HIP_TRY(le);
+    if (rows) {
+        FinishRowsArgs f{};
+        f.l = g->row_l; f.br = g->row_br; f.prior = g->dprior; f.X = X; f.count = count; f.K = K; f.m = m;
+        f.rec = reinterpret_cast<FinishRec *>(g->h_rec);
+        f.rec_x = reinterpret_cast<float *>(g->h_rec + off_x);
+        f.rec_br = reinterpret_cast<int32_t *>(g->h_rec + off_br);
+        f.ties = g->w.tie_counter;
+        HIP_TRY(launch_finish_rows(f, g->stream));
+    } else {
+        SweepArgs e{};
+        e.X = X; e.count = 1; e.index_base = 0;
+        e.fold_v = g->w.blk_v; e.fold_i = g->w.blk_i; e.fold_n = (int)any_num_blocks(g->view, count);
+        e.fold_ties = g->w.tie_counter; e.fold_run = &g->h_out->run;
+        e.row_host = g->h_x;
+        e.br_out = g->h_br; e.br_sc = K; e.br_st = 1;
+        e.l_out = g->h_l; e.l_sc = K; e.l_st = 1;
+        HIP_TRY(launch_sweep_any(g->view, e, any_slices(g->view, 1), g->stream));
+    }
+    g->fresh = false;
+    g->n_evals += count * K;
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    if (rows) {
+        const FinishRec *rec = reinterpret_cast<const FinishRec *>(g->h_rec);
+        long long b = 0;
+        for (long long r = 1; r < nrec; ++r)
+            if (rec[r].value > rec[b].value) b = r;          // records ascend in index
+        RunningBest &run = g->h_out->run;
+        run.value = rec[b].value; run.index = rec[b].index; run.has = 1; run.ties = rec[0].ties;
+        memcpy(g->h_x, g->h_rec + off_x + (size_t)b * m * sizeof(float), (size_t)m * sizeof(float));
+        memcpy(g->h_br, g->h_rec + off_br + (size_t)b * K * sizeof(int32_t), (size_t)K * sizeof(int32_t));
+        g->h_out->fin_v = run.value;
+    } else if (g->h_out->run.has) {
+        g->h_out->fin_v = value_of(g, g->h_l);
+    }
+    g->host_best = true;
+    return report_result(g, res, best_response_out);
+}
+
+}  // namespace
+
 extern "C" bsse_status bsse_sweep_best_row(bsse_game *g, float *x_out)
 {
     g_err[0] = 0;
@@ -980,9 +1196,10 @@ extern "C" bsse_status bsse_sweep_best_row(bsse_game *g, float *x_out)
         bsse_status st = fold_small(g);
         if (st != BSSE_OK) return st;
     }
-    HIP_TRY(hipStreamSynchronize(g->stream));
+    if (!g->hx_valid || g->fresh) HIP_TRY(hipStreamSynchronize(g->stream));
     if (g->fresh || !g->h_out->run.has) return fail(BSSE_ESTATE, "no candidate has been swept since the last reset");
-    HIP_TRY(hipMemcpy(x_out, g->w.best_x, (size_t)g->m * sizeof(float), hipMemcpyDeviceToHost));
+    if (g->hx_valid) memcpy(x_out, g->h_x, (size_t)g->m * sizeof(float));
+    else HIP_TRY(hipMemcpy(x_out, g->w.best_x, (size_t)g->m * sizeof(float), hipMemcpyDeviceToHost));
     return BSSE_OK;
 }
 
@@ -1000,6 +1217,16 @@ extern "C" bsse_status bsse_sweep(bsse_game *g, const float *candidates_dev, int
     }
     bsse_status st = bsse_sweep_reset(g);
     if (st != BSSE_OK) return st;
+    if (on_any(g)) {
+        const float *x = candidates_dev;
+        int64_t c = count;
+        if ((st = resolve_candidates(g, &x, &c)) != BSSE_OK) return st;
+        if (c > 0) {
+            DeviceGuard dg(g->device);
+            if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
+            return sweep_once_any(g, x, c, res, best_response_out);
+        }
+    }
     if ((st = bsse_sweep_chunk(g, candidates_dev, count, 0)) != BSSE_OK) return st;
     return bsse_sweep_result(g, res, best_response_out);
 }
@@ -1043,6 +1270,7 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
         {
             g->w = own; g->timing = timing; g->ties_dirty = ties_dirty;
             g->fresh = true; g->fold_pending = false; g->result_valid = false; g->n_evals = 0;
+            g->host_best = false; g->hx_valid = false;
         }
     } swap{ g, g->w, g->timing, g->ties_dirty };
     Work w;
@@ -1082,8 +1310,7 @@ extern "C" bsse_status bsse_eval(bsse_game *g, const float *candidates_dev, int6
     SweepArgs a{};
     a.X = candidates_dev; a.count = count; a.index_base = 0;
     a.V_out = values_dev_out; a.br_out = br_dev_out;
-    HIP_TRY(launch_sweep(g, a, true));
-    return BSSE_OK;
+    return launch_eval(g, a);
 }
 
 // ------------------------------------------------------------------------ prior batch
@@ -1161,7 +1388,7 @@ extern "C" bsse_status bsse_sweep_priors(bsse_game *g, const float *candidates_d
         SweepArgs a{};
         a.X = candidates_dev + base * m; a.count = rows; a.index_base = base;
         a.l_out = w.L; a.tie_counter = w.ties;
-        HIP_TRY(launch_sweep(g, a, true));
+        if ((st = launch_eval(g, a)) != BSSE_OK) return st;
         HIP_TRY(launch_prior_batch(w.L, rows, base, K, w.priors, P, base == 0 ? 1 : 0, w.blk_v, w.blk_i,
                                    w.run, g->stream));
     }
@@ -1170,7 +1397,7 @@ extern "C" bsse_status bsse_sweep_priors(bsse_game *g, const float *candidates_d
     {
         SweepArgs a{};
         a.X = w.rows; a.count = P; a.index_base = 0; a.br_out = w.br;
-        HIP_TRY(launch_sweep(g, a, true));
+        if ((st = launch_eval(g, a)) != BSSE_OK) return st;
     }
     // (the staging buffer is free again once the copy of the priors has run: same stream)
     HIP_TRY(hipMemcpyAsync(w.host + off_run, w.run, (size_t)P * sizeof(PriorBest), hipMemcpyDeviceToHost, g->stream));
@@ -1264,7 +1491,7 @@ extern "C" bsse_status bsse_sweep_topk(bsse_game *g, const float *candidates_dev
         const long long base = c * chunk, n = count - base < chunk ? count - base : chunk;
         SweepArgs a{};
         a.X = candidates_dev + base * m; a.count = n; a.index_base = 0; a.V_out = V.as<float>();
-        HIP_TRY(launch_sweep(g, a, true));
+        if ((st = launch_eval(g, a)) != BSSE_OK) return st;
         if ((st = reduce_to(V.as<float>(), nullptr, n, base, wv.as<float>() + c * k,
                             wi.as<long long>() + c * k)) != BSSE_OK) return st;
     }
@@ -1279,7 +1506,7 @@ extern "C" bsse_status bsse_sweep_topk(bsse_game *g, const float *candidates_dev
     {
         SweepArgs a{};
         a.X = rows.as<float>(); a.count = k; a.index_base = 0; a.br_out = br.as<int32_t>();
-        HIP_TRY(launch_sweep(g, a, true));
+        if ((st = launch_eval(g, a)) != BSSE_OK) return st;
     }
     std::vector<float> hv((size_t)k);
     std::vector<long long> hi((size_t)k);
@@ -1457,7 +1684,8 @@ extern "C" bsse_status bsse_polish(bsse_game *g, const int32_t *profile, float *
     std::vector<int32_t> brs((size_t)kPolishRows * K);
     std::vector<double> x((size_t)m);
     memcpy(prof.data(), profile ? profile : g->h_br, (size_t)K * sizeof(int32_t));
-    HIP_TRY(hipMemcpy(start.data(), g->w.best_x, (size_t)m * sizeof(float), hipMemcpyDeviceToHost));
+    if (g->hx_valid) memcpy(start.data(), g->h_x, (size_t)m * sizeof(float));
+    else HIP_TRY(hipMemcpy(start.data(), g->w.best_x, (size_t)m * sizeof(float), hipMemcpyDeviceToHost));
     double v_lp = 0.0;
     const int rc = solve_profile_lp(m, n, K, g->hA.data(), g->hB.data(), g->hprior.data(), prof.data(),
                                     x.data(), &v_lp);
@@ -1480,7 +1708,8 @@ extern "C" bsse_status bsse_polish(bsse_game *g, const int32_t *profile, float *
     SweepArgs a{};
     a.X = g->pol_rows; a.count = kPolishRows; a.index_base = 0;
     a.V_out = g->pol_v; a.br_out = g->pol_br;
-    HIP_TRY(launch_sweep(g, a, true));
+    bsse_status st = launch_eval(g, a);
+    if (st != BSSE_OK) return st;
     HIP_TRY(hipMemcpyAsync(vals.data(), g->pol_v, vals.size() * sizeof(float), hipMemcpyDeviceToHost, g->stream));
     HIP_TRY(hipMemcpyAsync(brs.data(), g->pol_br, brs.size() * sizeof(int32_t), hipMemcpyDeviceToHost, g->stream));
     HIP_TRY(hipStreamSynchronize(g->stream));
@@ -1520,7 +1749,7 @@ extern "C" bsse_status bsse_solve_realised(bsse_game *g, const float *candidates
     SweepArgs a{};
     a.X = candidates_dev; a.count = count; a.index_base = 0;
     a.V_out = V.as<float>(); a.br_out = br.as<int32_t>();
-    HIP_TRY(launch_sweep(g, a, true));
+    if ((st = launch_eval(g, a)) != BSSE_OK) return st;
     std::vector<float> hv;
     std::vector<int32_t> hb;
     std::vector<int64_t> order;

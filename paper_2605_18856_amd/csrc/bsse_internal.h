@@ -5,6 +5,23 @@
 
 namespace bsse {
 
+// Record geometry of the any-shape matrix-core kernel (see sweep_any_impl.h).  A unit is one type
+// (form 0: n > 32, form 1: n > 16) or one row tile of several types (form 8, 16: n <= 8, n <= 16).
+struct AnyGeo {
+    int terms;            // 1, 3 or 6 part products
+    int ks;               // k-steps of 16 leader actions
+    int form;
+    int tpg;              // row tiles per type (forms 0 and 1)
+    int units;
+    int tile_bytes;       // fragments of one row tile
+    int rec_bytes;        // one unit: fragments, then leader rows (or leader fragments, forms 8 and 16)
+    int lead_off;         // offset of the leader rows in a record; -1: gathered from global memory
+    int lead_stride;      // bytes from one leader row to the next in a record
+    int ups;              // units per LDS stage
+    int stt, nq;          // a unit too large for a stage: stt row tiles per stage, nq stages
+    int buf_bytes;        // one of the two stage buffers
+};
+
 // Device view of one game, passed to kernels by value.  All pointers are device memory
 // owned by the handle.
 struct GameView {
@@ -19,6 +36,7 @@ struct GameView {
     int m_pad;            // m rounded up to the MFMA k granularity
     int n_pad;            // n rounded up to the row-tile granularity (see sweep_mfma.hip)
     int variant;          // matrix-core kernel variant chosen at create (see mfma_select)
+    AnyGeo any;           // variant kAnyVariant
 };
 
 // Running best over chunks, in device memory.
@@ -78,7 +96,18 @@ struct SweepArgs {
     // every type would leave the chip idle), and a second kernel forms V_out from l_out in type
     // order (the same sum, term by term, as the unsliced kernel).
     float *l_out;
-    int slice_stages;        // LDS stages per slice (set by the launcher)
+    int slice_stages;        // LDS stages (any-shape kernel: units) per slice (set by the launcher)
+    // Any-shape kernel: l_out / br_out element (c, t) sits at c * _sc + t * _st.
+    long long l_sc, l_st, br_sc, br_st;
+    // Any-shape kernel, one row (count == 1): with fold_n > 0 the row is the winner of fold_n
+    // workgroup records of an earlier launch over the rows X; the winner and the tie counter's value
+    // (which is cleared) go to fold_run.  row_host (nullable) receives the row evaluated.
+    const float *fold_v;
+    const long long *fold_i;
+    int fold_n;
+    unsigned long long *fold_ties;
+    RunningBest *fold_run;
+    float *row_host;
     // Small-game kernel only, gen != 0: X is not read; row c is the flat-Dirichlet row
     // gen_first + c of the generator keyed (gen_k0, gen_k1), produced in registers with the
     // arithmetic of the generation kernel (sweep mode only).
@@ -125,6 +154,41 @@ int small_num_slots();
 hipError_t launch_finish_small(const GameView &g, const FinishArgs &f, hipStream_t s);
 void small_pack(int m, int n, int K, const float *A, const float *B, void **Bpack, size_t *Bbytes,
                 void **ATpack, size_t *ATbytes);
+
+// Any-shape matrix-core kernel (m <= 128; see sweep_any.hip).
+constexpr int kAnyVariant = 2000;
+bool any_supported(int m, int n);
+AnyGeo any_geometry(int m, int n, int K, int terms);
+void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes);
+// Fragments and leader rows from the payoffs as given to create (device, fp32 [K][m][n]).
+hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, hipStream_t s);
+hipError_t any_prepare(const GameView &g);
+const char *any_name(const AnyGeo &q);
+long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an unsliced launch
+// Type slices that `count` candidates should be cut into (1: none).
+int any_slices(const GameView &g, long long count);
+// slices > 1: l_out (and br_out) only; the value comes from launch_finish_rows.
+hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int slices, hipStream_t s);
+
+// Values of rows whose per-type leader payoffs l (type-major, [K][count]) a sliced launch left:
+// V[c] = sum_t prior[t] * l[t][c] in type order.  V_out: [count], nullable.  blk_v / blk_i: one record
+// per workgroup of FINISH_ROWS rows, nullable.  With rec: the same records in pinned host memory, each
+// with the row and the best responses (br type-major, [K][count]) of the workgroup's winner.
+constexpr int FINISH_ROWS = 256;
+struct FinishRec { float value; int pad; long long index; unsigned long long ties; };
+struct FinishRowsArgs {
+    const float *l, *prior, *X;
+    const int32_t *br;
+    long long count, index_base;
+    int K, m;
+    float *V_out, *blk_v;
+    long long *blk_i;
+    FinishRec *rec;
+    float *rec_x;            // [workgroups][m]
+    int32_t *rec_br;         // [workgroups][K]
+    unsigned long long *ties;   // read into record 0 and cleared
+};
+hipError_t launch_finish_rows(const FinishRowsArgs &f, hipStream_t s);
 
 // first != 0: the running best is replaced, not merged (start of a sweep).  tie_counter (the
 // chunk's count, left by the sweep kernel) is folded into run->ties and cleared.  The merged

@@ -1,0 +1,274 @@
+// Host side of the any-shape matrix-core kernel (sweep_any_impl.h), the kernel that packs payoffs for
+// it, and the kernel that turns the per-type leader payoffs of a sliced launch into values.
+#include "bsse_internal.h"
+#include "sweep_any_impl.h"
+
+namespace bsse {
+
+any_impl::any_kernel_t any_kernel_terms1(int ks, int form);
+any_impl::any_kernel_t any_kernel_terms3(int ks, int form);
+any_impl::any_kernel_t any_kernel_terms6(int ks, int form);
+
+namespace {
+
+using any_impl::THREADS;
+
+int roundup(int v, int to) { return (v + to - 1) / to * to; }
+
+any_impl::any_kernel_t kernel_for(const AnyGeo &q)
+{
+    return q.terms == 1 ? any_kernel_terms1(q.ks, q.form) : q.terms == 3 ? any_kernel_terms3(q.ks, q.form)
+                                                                         : any_kernel_terms6(q.ks, q.form);
+}
+
+// bf16 part `p` of v: every part the nearest bf16 (ties to even) of what the parts before it leave
+__device__ __forceinline__ unsigned bf16_part(float v, int p)
+{
+    for (int k = 0;; ++k) {
+        unsigned b = __float_as_uint(v);
+        b += 0x7FFFu + ((b >> 16) & 1u);
+        b &= 0xFFFF0000u;
+        if (k == p) return b >> 16;
+        v -= __uint_as_float(b);
+    }
+}
+
+// One thread per 16-byte piece of the records: eight k-slots of a fragment, or four (fp32) or eight
+// (bf16) entries of a leader row.  Runs once per game; the reads are strided by n but the payoffs fit
+// the caches.
+__global__ void __launch_bounds__(256)
+any_pack_kernel(AnyGeo q, int m, int n, int K, const float *__restrict__ A, const float *__restrict__ B,
+                uint4 *__restrict__ Bpack, size_t pieces)
+{
+    const int parts = q.terms == 6 ? 3 : 1, half = 8 * q.ks;
+    const int rec16 = q.rec_bytes / 16, frag16 = q.form >= 8 ? 2 * parts * q.ks * 64 : q.tpg * parts * q.ks * 64;
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < pieces; p += stride) {
+        const int u = (int)(p / rec16), o = (int)(p % rec16);
+        unsigned e[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
+        uint4 out = make_uint4(0u, 0u, 0u, 0u);
+        if (o < frag16) {
+            const int lane = o % 64, f = o / 64, part = f % parts, s = f / parts % q.ks, tile = f / (parts * q.ks);
+            const int hh = lane / 32, row = lane % 32;
+            int t, j;
+            const float *P = B;
+            if (q.form >= 8) {
+                // the rows a lane half receives are whole types: register r of half h2 is row 8(r/4)+4*h2+r%4
+                const int h2 = (row >> 2) & 1, r = (row >> 3) * 4 + (row & 3);
+                t = (32 / q.form) * u + (q.form == 16 ? h2 : 2 * h2 + (r >> 3));
+                j = q.form == 16 ? r : r & 7;
+                t = t < K ? t : K - 1;               // a padded type behaves like the last one, at weight zero
+                P = tile ? A : B;                    // the second tile of a record holds the leader's payoffs
+            } else {
+                t = u; j = tile * 32 + row;
+            }
+            if (j < n)
+                for (int k = 0; k < 8; ++k) {
+                    const int i = hh * half + 8 * s + k;
+                    if (i < m) e[k] = bf16_part(P[((size_t)t * m + i) * n + j], part);
+                }
+            out = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+        } else if (q.lead_off >= 0 && o >= q.lead_off / 16) {
+            const int byte = (o - q.lead_off / 16) * 16, j = byte / q.lead_stride, b0 = byte % q.lead_stride;
+            if (j < n) {
+                const int per = q.terms == 1 ? 8 : 4, i0 = b0 / (q.terms == 1 ? 2 : 4);
+                for (int k = 0; k < per; ++k) {
+                    const float v = i0 + k < m ? A[((size_t)u * m + i0 + k) * n + j] : 0.0f;
+                    e[k] = q.terms == 1 ? bf16_part(v, 0) : __float_as_uint(v);
+                }
+                out = q.terms == 1 ? make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16)
+                                   : make_uint4(e[0], e[1], e[2], e[3]);
+            }
+        }
+        Bpack[p] = out;
+    }
+}
+
+// Leader columns [K][n][16*ks], fp32 (bf16 for terms == 1), zero padded: the gather from global memory
+// and the exact routine.
+__global__ void __launch_bounds__(256)
+any_pack_lead_kernel(AnyGeo q, int m, int n, int K, const float *__restrict__ A, void *__restrict__ ATpack)
+{
+    const int mp = 16 * q.ks;
+    const size_t total = (size_t)K * n * mp, stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < total; p += stride) {
+        const int i = (int)(p % mp);
+        const size_t tj = p / mp, t = tj / n, j = tj % n;
+        const float v = i < m ? A[(t * m + i) * n + j] : 0.0f;
+        if (q.terms == 1) reinterpret_cast<unsigned short *>(ATpack)[p] = (unsigned short)bf16_part(v, 0);
+        else reinterpret_cast<float *>(ATpack)[p] = v;
+    }
+}
+
+__global__ void __launch_bounds__(FINISH_ROWS) finish_rows_kernel(FinishRowsArgs f)
+{
+    __shared__ float sv[FINISH_ROWS / 64];
+    __shared__ unsigned sc[FINISH_ROWS / 64];
+    const int tid = threadIdx.x;
+    const unsigned count = (unsigned)f.count, c = blockIdx.x * FINISH_ROWS + tid;
+    const unsigned cc = c < count ? c : count - 1u;
+    float v = 0.0f;
+    for (int t = 0; t < f.K; ++t) v = fmaf(f.prior[t], f.l[(size_t)t * count + cc], v);
+    if (!(v == v)) v = -INFINITY;
+    if (f.V_out && c < count) f.V_out[c] = v;
+    if (!f.blk_v && !f.rec) return;
+    float bv = v;
+    unsigned bc = cc;                                    // (a thread past the end repeats the last row)
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const float ov = __shfl_xor(bv, d, 64);
+        const unsigned oc = __shfl_xor(bc, d, 64);
+        if (ov > bv || (ov == bv && oc < bc)) { bv = ov; bc = oc; }
+    }
+    if ((tid & 63) == 0) { sv[tid >> 6] = bv; sc[tid >> 6] = bc; }
+    __syncthreads();
+    bv = sv[0]; bc = sc[0];
+    for (int w = 1; w < FINISH_ROWS / 64; ++w)
+        if (sv[w] > bv || (sv[w] == bv && sc[w] < bc)) { bv = sv[w]; bc = sc[w]; }
+    if (f.blk_v) {
+        if (tid == 0) { f.blk_v[blockIdx.x] = bv; f.blk_i[blockIdx.x] = f.index_base + bc; }
+        return;
+    }
+    for (int t = tid; t < f.K; t += FINISH_ROWS) f.rec_br[(size_t)blockIdx.x * f.K + t] = f.br[(size_t)t * count + bc];
+    for (int i = tid; i < f.m; i += FINISH_ROWS) f.rec_x[(size_t)blockIdx.x * f.m + i] = f.X[(size_t)bc * f.m + i];
+    if (tid == 0) {
+        FinishRec r;
+        r.value = bv; r.pad = 0; r.index = f.index_base + bc; r.ties = 0ull;
+        if (blockIdx.x == 0) { r.ties = *f.ties; *f.ties = 0ull; }
+        f.rec[blockIdx.x] = r;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_finish_rows(const FinishRowsArgs &f, hipStream_t s)
+{
+    if (f.count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(finish_rows_kernel, dim3((unsigned)((f.count + FINISH_ROWS - 1) / FINISH_ROWS)), dim3(FINISH_ROWS), 0, s, f);
+    return hipGetLastError();
+}
+
+bool any_supported(int m, int n) { return m <= 128 && (long long)m * n > 64; }
+
+AnyGeo any_geometry(int m, int n, int K, int terms)
+{
+    AnyGeo q{};
+    static const int steps[] = { 1, 2, 3, 4, 6, 8 };
+    q.terms = terms;
+    q.ks = 8;
+    for (int k : steps)
+        if (16 * k >= m) { q.ks = k; break; }
+    if (terms == 3 && q.ks != 2 && q.ks != 4) q.ks = q.ks == 1 ? 2 : q.ks == 3 ? 4 : 8;      // (fewer instantiations)
+    const int parts = terms == 6 ? 3 : 1, lbytes = terms == 1 ? 2 : 4;
+    q.tile_bytes = parts * q.ks * 1024;
+    q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : 0;
+    q.nq = 1; q.lead_off = -1;
+    // Two stage buffers per workgroup and two or three workgroups (the register allocation's two
+    // wavefronts per SIMD or better) per compute unit of 160 KiB: 26 KiB a stage.  A type that needs up
+    // to 36 KiB with its leader rows still goes in one piece (two workgroups); beyond that the row tiles
+    // come in pieces and the leader column is gathered from L2.
+    const int cap = 26 * 1024, most = 36 * 1024;
+    if (q.form >= 8) {
+        q.tpg = 1;
+        q.units = (K + 32 / q.form - 1) / (32 / q.form);
+        q.rec_bytes = 2 * q.tile_bytes;
+    } else {
+        q.tpg = (n + 31) / 32;
+        q.units = K;
+        q.lead_stride = 16 * q.ks * lbytes + 16;         // (16 bytes more: rows spread over the banks)
+        const long long whole = (long long)q.tpg * q.tile_bytes + roundup(n * q.lead_stride, 1024);
+        if (whole <= most) {
+            q.lead_off = q.tpg * q.tile_bytes;
+            q.rec_bytes = (int)whole;
+        } else {
+            q.rec_bytes = q.tpg * q.tile_bytes;
+            q.stt = cap / q.tile_bytes > 1 ? cap / q.tile_bytes & ~1 : 1;      // tiles go in pairs
+            if (q.stt > q.tpg) q.stt = q.tpg;
+            q.nq = (q.tpg + q.stt - 1) / q.stt;
+        }
+    }
+    q.ups = 1;
+    if (q.nq == 1) {
+        q.ups = cap / q.rec_bytes > 1 ? cap / q.rec_bytes : 1;
+        if (q.ups > q.units) q.ups = q.units;
+        q.stt = q.tpg;
+        q.buf_bytes = q.ups * q.rec_bytes;
+    } else {
+        q.buf_bytes = q.stt * q.tile_bytes;
+    }
+    return q;
+}
+
+const char *any_name(const AnyGeo &q) { return q.terms == 1 ? "mfma_bf16" : q.terms == 3 ? "mfma_split3" : "mfma_split6"; }
+
+void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes)
+{
+    *Bbytes = (size_t)g.any.units * g.any.rec_bytes;
+    *ATbytes = g.any.form >= 8 ? 16 : (size_t)g.K * g.n * 16 * g.any.ks * (g.any.terms == 1 ? 2 : 4);
+}
+
+hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, hipStream_t s)
+{
+    size_t bb, ab;
+    any_pack_sizes(g, &bb, &ab);
+    const size_t pieces = bb / 16;
+    size_t blocks = (pieces + 255) / 256;
+    if (blocks > 8192) blocks = 8192;
+    hipLaunchKernelGGL(any_pack_kernel, dim3((unsigned)blocks), dim3(256), 0, s, g.any, g.m, g.n, g.K, A, B,
+                       (uint4 *)Bpack, pieces);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || g.any.form >= 8) return e;
+    blocks = (ab / 4 + 255) / 256;
+    if (blocks > 8192) blocks = 8192;
+    hipLaunchKernelGGL(any_pack_lead_kernel, dim3((unsigned)blocks), dim3(256), 0, s, g.any, g.m, g.n, g.K, A, ATpack);
+    return hipGetLastError();
+}
+
+hipError_t any_prepare(const GameView &g)
+{
+    const int lds = 2 * g.any.buf_bytes;
+    if (lds <= 48 * 1024) return hipSuccess;
+    return hipFuncSetAttribute((const void *)kernel_for(g.any), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+}
+
+static long long rows_per_block(const AnyGeo &q) { return 32LL * any_impl::WAVES * any_impl::tiles_per_wave(q.terms, q.ks); }
+
+long long any_num_blocks(const GameView &g, long long count)
+{
+    // At most one resident set (two workgroups a compute unit); every workgroup then walks the same
+    // number of blocks up to one.
+    const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any), cap = 512;
+    const long long rounds = (blocks + cap - 1) / cap;
+    return rounds > 0 ? (blocks + rounds - 1) / rounds : 1;
+}
+
+int any_slices(const GameView &g, long long count)
+{
+    // Fewer blocks of candidates than compute units: cut the types until the grid is about twice that.
+    const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
+    if (blocks >= 256 || g.any.units < 2) return 1;
+    long long want = 512 / blocks;
+    if (want > g.any.units) want = g.any.units;
+    const int per = (int)((g.any.units + want - 1) / want);
+    return (g.any.units + per - 1) / per;
+}
+
+hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int slices, hipStream_t s)
+{
+    if (a.count <= 0) return hipSuccess;
+    any_impl::any_kernel_t k = kernel_for(g.any);
+    if (!k) return hipErrorNotSupported;
+    any_impl::AnyArgs args{ g, a };
+    SweepArgs &b = args.a;
+    const int units = g.any.units;
+    b.slice_stages = (units + slices - 1) / slices;
+    const int ny = (units + b.slice_stages - 1) / b.slice_stages;
+    const long long blocks = (a.count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
+    const long long nx = ny > 1 ? blocks : any_num_blocks(g, a.count);
+    if (ny > 1 && (a.V_out || a.blk_v)) return hipErrorInvalidValue;
+    if (ny > 65535 || nx > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3((unsigned)nx, (unsigned)ny), dim3(THREADS), (size_t)2 * g.any.buf_bytes, s, args);
+    return hipGetLastError();
+}
+
+}  // namespace bsse

@@ -1,0 +1,724 @@
+// Fused sweep on the bf16 matrix cores for games of any shape with m <= 128 (not installed; one
+// translation unit per TERMS instantiates it).
+//
+// The tile orientation, the partner-lane exchanges, the tie rule and the split of fp32 operands into
+// bf16 parts are those of sweep_mfma.hip; what differs is that n and K are run-time numbers.
+//   * The follower actions of a type are padded to whole row tiles.  A padded row never wins: its
+//     accumulator starts at minus infinity (the C operand of the tile's first instruction) and its
+//     payoffs are zero.
+//   * FORM 0 (n > 32) walks the row tiles of a type two at a time and keeps, per lane, the running
+//     maximum with its tile and the running element-wise maximum over the tiles; when the type is
+//     done the latter says which of the sixteen positions holds the maximum.  Nothing depends on the
+//     number of tiles, so registers do not grow with n.
+//   * FORM 1 (16 < n <= 32) is the same with one tile per type.
+//   * FORM 8 and FORM 16 (n <= 8, n <= 16) put four or two whole types into one row tile, the rows
+//     permuted so that each lane holds every action of its types: no exchange is needed to find the
+//     best response.  The leader payoffs of all the actions come off the matrix cores too and the one
+//     at the best response is picked under the masks of the arg-max compares.
+// The leader payoff of FORM 0 and 1 is an fp32 dot product (bf16 pairs in bf16 storage) with the
+// column of A at the best response, from LDS where a whole type fits a stage, else from L2.
+//
+// Rows past the end of the candidates repeat the last one: they behave like any other row (no
+// special case, no detour through the exact routine) and are left out of every output.
+//
+// Types can be sliced over blockIdx.y (few candidates: one workgroup walking all types would leave
+// the chip idle); a slice writes per-type leader payoffs and finish_rows_kernel sums them in type
+// order, so a row's value has the same bits however the launch was cut.
+#pragma once
+#include "bsse_internal.h"
+#include "mfma_device.h"
+#include <limits.h>
+
+namespace bsse {
+namespace any_impl {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef const void __attribute__((address_space(1))) *global_ptr;
+typedef void __attribute__((address_space(3))) *lds_ptr;
+
+constexpr int WAVES = 4, THREADS = WAVES * 64;
+
+// NT: 32-candidate tiles per wavefront.  Two let one fragment read serve two instructions; with
+// three parts of a long row in registers there is room for one.
+constexpr int tiles_per_wave(int terms, int ks) { return (terms == 1 || ks <= 2) ? 2 : 1; }
+// Wavefronts per SIMD that the register allocation is held to.
+constexpr int occupancy(int terms, int ks, int form) { return (ks <= 2 && form != 0) ? 3 : 2; }
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    const v2f ab = { a, b };
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(ab, v2bf));       // nearest, ties to even
+}
+__device__ __forceinline__ float bf16_lo(unsigned p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned p) { return __uint_as_float(p & 0xFFFF0000u); }
+
+__device__ __forceinline__ f32x16 mfma_bf16(const u32x4 &a, const unsigned *x, const f32x16 &c)
+{
+    const u32x4 b = { x[0], x[1], x[2], x[3] };
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Maximum of sixteen values.
+__device__ __forceinline__ float vmax16(const float *u)
+{
+    const float a = vmax3(vmax3(u[0], u[1], u[2]), u[3], u[4]), b = vmax3(vmax3(u[8], u[9], u[10]), u[11], u[12]);
+    const float c = vmax3(a, u[5], u[6]), d = vmax3(b, u[13], u[14]);
+    return vmax2(vmax3(c, u[7], d), u[15]);
+}
+
+// Eight follower payoffs u against their maximum g with the leader payoffs w beside them, from the
+// highest position down: l = w[j] wherever u[j] holds g, so that after the last block l belongs to the
+// lowest position that does.  TOP: the first block of a chain (l starts as w[7]).  n_eq += how many
+// (lane, position) pairs of the wavefront hold g.  Compare masks in scalar register pairs, counted on
+// the scalar unit.
+template <bool TOP>
+__device__ __forceinline__ void argmax8_chain(const float *u, const float *w, float g, float &l, unsigned &n_eq)
+{
+    unsigned long long m0, m1, m2, m3, m4, m5, m6, m7;
+    unsigned c, t;
+    float lv = TOP ? w[7] : l;
+#define BSSE_ACC(k) "s_bcnt1_i32_b64 %[t], %[m" #k "]\n\ts_add_u32 %[c], %[c], %[t]\n\t"
+#define BSSE_SEL(k) "v_cndmask_b32 %[l], %[l], %[w" #k "], %[m" #k "]\n\t"
+#define BSSE_CMP(k) "v_cmp_eq_f32 %[m" #k "], %[u" #k "], %[g]\n\t"
+    if constexpr (TOP) {
+        asm(BSSE_CMP(6) BSSE_CMP(5) BSSE_CMP(4) BSSE_CMP(3) BSSE_CMP(2) BSSE_CMP(1) BSSE_CMP(0) BSSE_CMP(7)
+            BSSE_SEL(6) BSSE_SEL(5) BSSE_SEL(4) BSSE_SEL(3) BSSE_SEL(2) BSSE_SEL(1) BSSE_SEL(0)
+            "s_bcnt1_i32_b64 %[c], %[m7]\n\t"
+            BSSE_ACC(6) BSSE_ACC(5) BSSE_ACC(4) BSSE_ACC(3) BSSE_ACC(2) BSSE_ACC(1) BSSE_ACC(0)
+            : [l] "+v"(lv), [c] "=&s"(c), [t] "=&s"(t), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2),
+              [m3] "=&s"(m3), [m4] "=&s"(m4), [m5] "=&s"(m5), [m6] "=&s"(m6), [m7] "=&s"(m7)
+            : [u0] "v"(u[0]), [u1] "v"(u[1]), [u2] "v"(u[2]), [u3] "v"(u[3]), [u4] "v"(u[4]), [u5] "v"(u[5]),
+              [u6] "v"(u[6]), [u7] "v"(u[7]), [w0] "v"(w[0]), [w1] "v"(w[1]), [w2] "v"(w[2]), [w3] "v"(w[3]),
+              [w4] "v"(w[4]), [w5] "v"(w[5]), [w6] "v"(w[6]), [g] "v"(g)
+            : "scc");
+    } else {
+        asm(BSSE_CMP(7) BSSE_CMP(6) BSSE_CMP(5) BSSE_CMP(4) BSSE_CMP(3) BSSE_CMP(2) BSSE_CMP(1) BSSE_CMP(0)
+            BSSE_SEL(7) BSSE_SEL(6) BSSE_SEL(5) BSSE_SEL(4) BSSE_SEL(3) BSSE_SEL(2) BSSE_SEL(1) BSSE_SEL(0)
+            "s_bcnt1_i32_b64 %[c], %[m7]\n\t"
+            BSSE_ACC(6) BSSE_ACC(5) BSSE_ACC(4) BSSE_ACC(3) BSSE_ACC(2) BSSE_ACC(1) BSSE_ACC(0)
+            : [l] "+v"(lv), [c] "=&s"(c), [t] "=&s"(t), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2),
+              [m3] "=&s"(m3), [m4] "=&s"(m4), [m5] "=&s"(m5), [m6] "=&s"(m6), [m7] "=&s"(m7)
+            : [u0] "v"(u[0]), [u1] "v"(u[1]), [u2] "v"(u[2]), [u3] "v"(u[3]), [u4] "v"(u[4]), [u5] "v"(u[5]),
+              [u6] "v"(u[6]), [u7] "v"(u[7]), [w0] "v"(w[0]), [w1] "v"(w[1]), [w2] "v"(w[2]), [w3] "v"(w[3]),
+              [w4] "v"(w[4]), [w5] "v"(w[5]), [w6] "v"(w[6]), [w7] "v"(w[7]), [g] "v"(g)
+            : "scc");
+    }
+#undef BSSE_ACC
+#undef BSSE_SEL
+#undef BSSE_CMP
+    l = lv;
+    n_eq += c;
+}
+
+// Folds `n` workgroup records (greatest value, lowest index among equals); every thread of the
+// workgroup gets the result.
+__device__ __forceinline__ void fold_records(const float *v, const long long *i, int n, float &bv, long long &bi)
+{
+    __shared__ float fv[WAVES];
+    __shared__ long long fi[WAVES];
+    bv = -INFINITY; bi = LLONG_MAX;
+    for (int b = threadIdx.x; b < n; b += THREADS) {
+        const float x = v[b];
+        const long long k = i[b];
+        if (x > bv || (x == bv && k < bi)) { bv = x; bi = k; }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const float ov = __shfl_xor(bv, d, 64);
+        const long long oi = __shfl_xor(bi, d, 64);
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    }
+    if ((threadIdx.x & 63) == 0) { fv[threadIdx.x >> 6] = bv; fi[threadIdx.x >> 6] = bi; }
+    __syncthreads();
+    bv = fv[0]; bi = fi[0];
+    for (int w = 1; w < WAVES; ++w)
+        if (fv[w] > bv || (fv[w] == bv && fi[w] < bi)) { bv = fv[w]; bi = fi[w]; }
+}
+
+// Kernel arguments.  What the inner loop needs is read from the argument; everything else (outputs,
+// records) through `late`, at the point of use: a pointer the compiler cannot see through keeps those
+// fields out of the scalar registers of the loop, where they were spilled to vector lanes.
+struct AnyArgs {
+    GameView g;
+    SweepArgs a;
+};
+typedef const AnyArgs __attribute__((address_space(4))) *late_args;
+__device__ __forceinline__ late_args late()
+{
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return (late_args)p;
+}
+
+// TERMS: 1 = operands rounded to bf16 (bf16 storage), 3 / 6 = fp32 operands as three bf16 parts
+// against payoffs that are bf16 numbers / payoffs in three parts.  KS: k-steps of 16 leader actions.
+// FORM: see the top of the file.
+template <int TERMS, int KS, int FORM>
+__global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any_kernel(AnyArgs args)
+{
+    constexpr int NT = tiles_per_wave(TERMS, KS);
+    constexpr int XP = TERMS == 1 ? 1 : 3;               // parts of a candidate component
+    constexpr int PA = TERMS == 6 ? 3 : 1;               // parts of a payoff
+    constexpr int HALF = 8 * KS;                         // leader actions per lane half
+    constexpr bool NARROW = FORM >= 8;
+    constexpr bool XF = !NARROW && TERMS != 1 && KS <= 2;   // the fp32 half row stays in registers
+    constexpr int TPT = NARROW ? 32 / FORM : 1;          // types per unit
+    constexpr bool PAIRS = FORM == 0 && TERMS == 1;      // row tiles two at a time: fewer vector instructions
+                                                         // per tile where these outweigh the matrix time
+    const AnyGeo &q = args.g.any;
+
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // two stage buffers
+    __shared__ float red_v[WAVES];
+    __shared__ unsigned red_c[WAVES];
+    __shared__ __attribute__((aligned(16))) float cinit[2][16];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, col = lane & 31;
+    const int partner_addr = 4 * (lane ^ 32);
+    const int m = args.g.m, n = args.g.n, K = args.g.K;
+    const unsigned count = (unsigned)args.a.count;       // <= 2^31 per launch
+    const unsigned char *records = reinterpret_cast<const unsigned char *>(args.g.Bpack);
+    const unsigned char *ATpack = reinterpret_cast<const unsigned char *>(args.g.ATpack);
+    const float *prior = args.g.prior;
+    const int u0 = (int)blockIdx.y * args.a.slice_stages;     // units of this slice
+    const int u1 = u0 + args.a.slice_stages < q.units ? u0 + args.a.slice_stages : q.units;
+    const bool per_type = args.a.br_out || args.a.l_out; // per-type outputs are wanted
+    if (u0 >= u1) return;                                // whole workgroup
+    const int nsu = (u1 - u0 + q.ups - 1) / q.ups;       // groups of units, nq stages each
+    constexpr unsigned PER_WG = WAVES * NT * 32;
+    const unsigned nblk = (count + PER_WG - 1) / PER_WG;
+
+    // a stage: `ups` whole units, or (nq > 1) `stt` row tiles of one unit
+    auto copy_stage = [&](int su, int qq, int buf) __attribute__((always_inline)) {
+        const unsigned char *src = records + (size_t)(u0 + su * q.ups) * q.rec_bytes;
+        int bytes;
+        if (q.nq == 1) {
+            const int nu = u1 - (u0 + su * q.ups) < q.ups ? u1 - (u0 + su * q.ups) : q.ups;
+            bytes = nu * q.rec_bytes;
+        } else {
+            src += (size_t)qq * q.stt * q.tile_bytes;
+            bytes = (q.tpg - qq * q.stt < q.stt ? q.tpg - qq * q.stt : q.stt) * q.tile_bytes;
+        }
+        unsigned char *dst = smem + buf * q.buf_bytes;
+        for (int chunk = wave; chunk < (bytes >> 10); chunk += WAVES)
+            __builtin_amdgcn_global_load_lds((global_ptr)(src + chunk * 1024 + lane * 16),
+                                             (lds_ptr)(dst + chunk * 1024), 16, 0, 0);
+    };
+    copy_stage(0, 0, 0);
+
+    // the one row of a fold launch: the winner among the records of an earlier launch
+    const float *X = args.a.X;
+    {
+        const late_args p = late();
+        if (p->a.fold_n > 0) {
+            float bv;
+            long long bi;
+            fold_records(p->a.fold_v, p->a.fold_i, p->a.fold_n, bv, bi);
+            const bool has = bi != LLONG_MAX;
+            if (has) X += (bi - p->a.index_base) * m;
+            if (blockIdx.y == 0 && tid == 0) {
+                RunningBest r;
+                r.value = has ? bv : 0.0f; r.has = has ? 1 : 0; r.index = has ? bi : -1; r.ties = *p->a.fold_ties;
+                *p->a.fold_ties = 0ull;
+                *p->a.fold_run = r;
+            }
+        }
+        if (p->a.row_host && blockIdx.y == 0)
+            for (int i = tid; i < m; i += THREADS) p->a.row_host[i] = X[i];
+    }
+
+    // C operand of the first instruction on a type's last row tile: minus infinity where the row is
+    // padding (NARROW: in every tile, the row's action being its register index modulo FORM).  In LDS,
+    // one copy per lane half, where sixteen registers are worth more than the reads.
+    if (tid < 32) {
+        const int r = tid & 15, hh = tid >> 4;
+        cinit[hh][r] = (NARROW ? r % (FORM >= 8 ? FORM : 8) : (q.tpg - 1) * 32 + acc_row_base(r) + 4 * hh) < n ? 0.0f : -INFINITY;
+    }
+    const bool padded = NARROW ? n != FORM : n != 32 * q.tpg;
+
+    unsigned x[NT][XP][KS * 4];
+    float xf[NT][XF ? HALF : 1];
+    unsigned valid32[NT];
+    const bool vec4 = (m & 3) == 0;                      // (rows are then 16-byte aligned)
+    auto load_rows = [&](unsigned first) __attribute__((always_inline)) {
+        // (laundered: the bounds masks are then formed here, not kept across the loop over blocks)
+        int m_here = m;
+        asm volatile("" : "+s"(m_here));
+        const int m = m_here;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const unsigned c = first + ct * 32 + col;
+            const float *row = X + (size_t)(c < count ? c : count - 1u) * m;
+            valid32[ct] = (unsigned)__builtin_amdgcn_ballot_w64(c < count);
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                float v[8];
+                const int i0 = h * HALF + 8 * s;
+                if (vec4) {
+#pragma unroll
+                    for (int e = 0; e < 8; e += 4) {
+                        const int i = i0 + e;
+                        const f32x4 t = *reinterpret_cast<const f32x4 *>(row + (i < m ? i : 0));
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) v[e + k] = i < m ? t[k] : 0.0f;
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int i = i0 + e;
+                        const float t = row[i < m ? i : 0];
+                        v[e] = i < m ? t : 0.0f;
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    const int k = 4 * s + e / 2;
+                    const unsigned p0 = pack_bf16(v[e], v[e + 1]);
+                    x[ct][0][k] = p0;
+                    if constexpr (XP == 3) {
+                        // (the differences are exact: x = p0 + p1 + p2)
+                        const float ra = v[e] - bf16_lo(p0), rb = v[e + 1] - bf16_hi(p0);
+                        const unsigned p1 = pack_bf16(ra, rb);
+                        x[ct][1][k] = p1;
+                        x[ct][2][k] = pack_bf16(ra - bf16_lo(p1), rb - bf16_hi(p1));
+                    }
+                    if constexpr (XF) { xf[ct][8 * s + e] = v[e]; xf[ct][8 * s + e + 1] = v[e + 1]; }
+                }
+            }
+        }
+    };
+
+    // One row tile against the wavefront's candidate tiles: fragments [k-step][part][lane].  The order
+    // of the products is fixed (small parts first within a k-step), so every way of reaching a tile
+    // gives the same bits.
+    auto tile_mfma = [&](f32x16 (&acc)[NT], auto fr, bool last) __attribute__((always_inline)) {
+        static_for<0, KS, 1>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            u32x4 f[PA];
+#pragma unroll
+            for (int p = 0; p < PA; ++p) f[p] = fr[(s * PA + p) * 64];
+            auto product = [&](int pb, int px, bool first) __attribute__((always_inline)) {
+                if (s == 0 && first) {
+                    f32x16 zero;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+                    if (last) {
+                        const f32x4 *c = reinterpret_cast<const f32x4 *>(cinit[h]);
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) {
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) acc[ct][r] = c[r / 4][r % 4];
+                            acc[ct] = mfma_bf16(f[pb], &x[ct][px][4 * s], acc[ct]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) acc[ct] = mfma_bf16(f[pb], &x[ct][px][4 * s], zero);
+                    }
+                } else {
+#pragma unroll
+                    for (int ct = 0; ct < NT; ++ct) acc[ct] = mfma_bf16(f[pb], &x[ct][px][4 * s], acc[ct]);
+                }
+            };
+            if constexpr (TERMS == 6) {
+                product(2, 0, true); product(1, 1, false); product(0, 2, false);
+                product(1, 0, false); product(0, 1, false); product(0, 0, false);
+            } else if constexpr (TERMS == 3) {
+                product(0, 2, true); product(0, 1, false); product(0, 0, false);
+            } else {
+                product(0, 0, true);
+            }
+        });
+    };
+    // The asm blocks below read accumulators, and the compiler's hazard handling does not look into
+    // inline asm: the wait states a vector read of a fresh MFMA result needs are explicit, with the
+    // accumulators as operands so that nothing that reads them can be scheduled above the wait.
+    auto settle = [&](f32x16 (&acc)[NT]) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (NT == 2) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0]), "+v"(acc[NT - 1]));
+        else asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0]));
+    };
+
+    float V[NT];
+    unsigned tie_count = 0;                              // wave-uniform
+    float best_v = -INFINITY;
+    unsigned best_c = 0xFFFFFFFFu;
+
+    // the lane's half of the candidate row against its half of leader column (t, j); two chains
+    auto half_dot = [&](int ct, auto column) __attribute__((always_inline)) {
+        float l0 = 0.0f, l1 = 0.0f;
+        if constexpr (TERMS == 1) {
+            u32x4 cr[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) cr[s] = column[s];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                const unsigned w0 = cr[s][0], w1 = cr[s][1], w2 = cr[s][2], w3 = cr[s][3];
+                asm volatile("v_dot2c_f32_bf16 %0, %2, %6\n\t"
+                             "v_dot2c_f32_bf16 %1, %3, %7\n\t"
+                             "v_dot2c_f32_bf16 %0, %4, %8\n\t"
+                             "v_dot2c_f32_bf16 %1, %5, %9"
+                             : "+v"(l0), "+v"(l1)
+                             : "v"(x[ct][0][4 * s]), "v"(x[ct][0][4 * s + 1]), "v"(x[ct][0][4 * s + 2]),
+                               "v"(x[ct][0][4 * s + 3]), "v"(w0), "v"(w1), "v"(w2), "v"(w3));
+            }
+            // (three wait states between a dot result and another kind of vector instruction)
+            asm volatile("s_nop 2" : "+v"(l0), "+v"(l1));
+        } else {
+#pragma unroll
+            for (int e = 0; e < HALF; e += 4) {
+                const u32x4 raw = column[e / 4];
+                const f32x4 r = __builtin_bit_cast(f32x4, raw);
+                float v[4];
+                if constexpr (XF) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[k] = xf[ct][e + k];
+                } else {
+                    // the component from its three parts: exact, p0 + p1 + p2 being the fp32 number
+#pragma unroll
+                    for (int k = 0; k < 4; k += 2) {
+                        const unsigned p0 = x[ct][0][(e + k) / 2], p1 = x[ct][XP - 2][(e + k) / 2], p2 = x[ct][XP - 1][(e + k) / 2];
+                        v[k] = (bf16_lo(p0) + bf16_lo(p1)) + bf16_lo(p2);
+                        v[k + 1] = (bf16_hi(p0) + bf16_hi(p1)) + bf16_hi(p2);
+                    }
+                }
+                l0 = fmaf(v[0], r[0], l0); l1 = fmaf(v[1], r[1], l1);
+                l0 = fmaf(v[2], r[2], l0); l1 = fmaf(v[3], r[3], l1);
+            }
+        }
+        return l0 + l1;
+    };
+    constexpr int LBYTES = TERMS == 1 ? 2 : 4;           // bytes of a leader payoff
+    auto lead_global = [&](int t, int j) __attribute__((always_inline)) {
+        return reinterpret_cast<const u32x4 *>(ATpack + (((size_t)t * n + j) * (2 * HALF) + h * HALF) * LBYTES);
+    };
+    auto pair_total = [&](float part) __attribute__((always_inline)) {
+        const float other = pair_other(part, partner_addr);
+        return h ? other + part : part + other;          // (lower half) + (upper half)
+    };
+
+    // Exact routine for one (candidate tile, type) of FORM 0 / 1: the type's tiles once more from the
+    // records in global memory (same instructions, same bits), the exact maximisers in ascending
+    // action order; the leader's payoff decides and then the lower action.
+    auto exact_type = [&](int ct, int t, float gmax, float &l_out, int &j_out) __attribute__((always_inline)) {
+        float lbest = 0.0f;
+        int jbest = 0, nmatch = 0;
+#pragma unroll 1
+        for (int tt = 0; tt < q.tpg; ++tt) {
+            f32x16 acc[NT];
+            tile_mfma(acc, reinterpret_cast<const u32x4 *>(records + (size_t)t * q.rec_bytes + (size_t)tt * q.tile_bytes) + lane,
+                      padded && tt == q.tpg - 1);
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const int r = 4 * q4 + rr;
+                        const int j = tt * 32 + acc_row_base(r) + 4 * hh;
+                        const unsigned long long meq = __builtin_amdgcn_ballot_w64(acc[ct][r] == gmax);
+                        const unsigned hit = (unsigned)(hh ? (meq >> 32) : meq);
+                        if (hit == 0u || j > n - 1) continue;               // wave-uniform
+                        const float l = pair_total(half_dot(ct, lead_global(t, j)));
+                        if ((hit >> col) & 1u) {
+                            if (nmatch == 0 || l > lbest) { lbest = l; jbest = j; }
+                            ++nmatch;
+                        }
+                    }
+        }
+        l_out = lbest; j_out = jbest;
+        tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2) & valid32[ct]);
+    };
+
+    int buf = 0;
+    for (unsigned blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+        const unsigned first = (blk * WAVES + wave) * (NT * 32);
+        load_rows(first);
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) V[ct] = 0.0f;
+        // state of the type in progress (FORM 0)
+        float best[NT], w[NT][16];
+        unsigned btile[NT];
+        unsigned long long dup[NT];
+
+#pragma unroll 1
+        for (int su = 0; su < nsu; ++su) {
+#pragma unroll 1
+            for (int qq = 0; qq < q.nq; ++qq) {
+                // own copies of this stage have landed; then everyone's have, and everyone is done with
+                // the other buffer, which takes the next stage
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                {
+                    int su2 = su, qq2 = qq + 1;
+                    if (qq2 == q.nq) { qq2 = 0; ++su2; }
+                    bool more = su2 < nsu;
+                    if (!more && blk + gridDim.x < nblk) { su2 = 0; more = true; }
+                    if (more) copy_stage(su2, qq2, buf ^ 1);
+                }
+                const unsigned char *sb = smem + buf * q.buf_bytes;
+                buf ^= 1;
+                const int ub = u0 + su * q.ups;
+                const int nu = u1 - ub < q.ups ? u1 - ub : q.ups;
+#pragma unroll 1
+                for (int ui = 0; ui < nu; ++ui) {
+                    const int u = ub + ui;
+                    const u32x4 *fr = reinterpret_cast<const u32x4 *>(sb + ui * q.rec_bytes) + lane;
+                    if constexpr (NARROW) {
+                        f32x16 uf[NT], wl[NT];
+                        tile_mfma(uf, fr, padded);
+                        tile_mfma(wl, fr + PA * KS * 64, false);
+                        settle(uf); settle(wl);
+                        constexpr int PT = TPT / 2;      // types per lane
+                        float gm[NT][PT], l[NT][PT];
+                        unsigned n_eq = 0;
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) {
+                            float uu[16], ww[16];
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) { uu[r] = uf[ct][r]; ww[r] = wl[ct][r]; }
+                            if constexpr (FORM == 16) {
+                                gm[ct][0] = vmax16(uu);
+                                argmax8_chain<true>(uu + 8, ww + 8, gm[ct][0], l[ct][0], n_eq);
+                                argmax8_chain<false>(uu, ww, gm[ct][0], l[ct][0], n_eq);
+                            } else {
+#pragma unroll
+                                for (int p = 0; p < PT; ++p) {
+                                    const float *v = uu + 8 * (p & 1);
+                                    gm[ct][p] = vmax2(vmax3(vmax3(vmax3(v[0], v[1], v[2]), v[3], v[4]), v[5], v[6]), v[7]);
+                                    argmax8_chain<true>(v, ww + 8 * (p & 1), gm[ct][p], l[ct][p], n_eq);
+                                }
+                            }
+                        }
+                        unsigned js[NT][PT];
+                        const bool exact = n_eq != 64u * NT * PT;          // wave-uniform
+                        if (exact || per_type) {
+                            // several maximisers in some lane (or none), or the action itself is wanted:
+                            // maximisers in ascending order, the leader's payoff decides, then the lower
+                            // action; a lane with one maximiser keeps what it had
+#pragma unroll
+                            for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+                                for (int p = 0; p < PT; ++p) {
+                                    float lbest = 0.0f;
+                                    unsigned jbest = 0;
+                                    int nm = 0;
+#pragma unroll
+                                    for (int j = 0; j < (FORM == 16 ? 16 : 8); ++j)
+                                        if (uf[ct][8 * p + j] == gm[ct][p] && j < n) {
+                                            const float lj = wl[ct][8 * p + j];
+                                            if (nm == 0 || lj > lbest) { lbest = lj; jbest = (unsigned)j; }
+                                            ++nm;
+                                        }
+                                    l[ct][p] = lbest; js[ct][p] = jbest;
+                                    const bool live = TPT * u + PT * h + p < K && ((valid32[ct] >> col) & 1u);
+                                    tie_count += __builtin_popcountll(__builtin_amdgcn_ballot_w64(live && nm >= 2));
+                                }
+                        }
+                        // the value in type order: the partner lane holds the other half's types
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) {
+                            float lo[PT];
+#pragma unroll
+                            for (int p = 0; p < PT; ++p) lo[p] = pair_other(l[ct][p], partner_addr);
+#pragma unroll
+                            for (int k = 0; k < TPT; ++k) {
+                                const int t = TPT * u + k;
+                                const float pt = t < K ? prior[t] : 0.0f;
+                                const float lk = (k / PT == h) ? l[ct][k % PT] : lo[k % PT];
+                                V[ct] = fmaf(pt, lk, V[ct]);
+                            }
+                            if (per_type) {
+                                const late_args o = late();
+                                const size_t c = first + ct * 32 + col;
+#pragma unroll
+                                for (int p = 0; p < PT; ++p) {
+                                    const int t = TPT * u + PT * h + p;
+                                    if (c < count && t < K) {
+                                        if (o->a.br_out) o->a.br_out[c * o->a.br_sc + t * o->a.br_st] = (int32_t)js[ct][p];
+                                        if (o->a.l_out) o->a.l_out[c * o->a.l_sc + t * o->a.l_st] = l[ct][p];
+                                    }
+                                }
+                            }
+                        }
+                    } else {
+                        // ---- FORM 0 / 1: one type
+                        if (qq == 0) {
+#pragma unroll
+                            for (int ct = 0; ct < NT; ++ct) {
+                                // (not minus infinity: a lane whose rows of a tile are all padding must
+                                // not count as a tie with the start value)
+                                best[ct] = -3.402823466e38f; btile[ct] = 0u; dup[ct] = 0ull;
+                                if constexpr (FORM == 0)
+#pragma unroll
+                                    for (int r = 0; r < 16; ++r) w[ct][r] = -INFINITY;
+                            }
+                        }
+                        if constexpr (FORM == 1) {
+                            f32x16 acc[NT];
+                            tile_mfma(acc, fr, padded);
+                            settle(acc);
+#pragma unroll
+                            for (int ct = 0; ct < NT; ++ct) {
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) w[ct][r] = acc[ct][r];
+                                best[ct] = vmax16(w[ct]);
+                            }
+                        } else {
+                            const int tb = qq * q.stt;
+                            const int te = tb + q.stt < q.tpg ? tb + q.stt : q.tpg;
+                            auto merge = [&](int ct, float pm, int tt) __attribute__((always_inline)) {
+                                dup[ct] |= __builtin_amdgcn_ballot_w64(pm == best[ct]);
+                                keep_greater2(pm, (unsigned)tt, best[ct], btile[ct]);
+                            };
+#pragma unroll 1
+                            for (int tt = tb; tt < te; tt += (PAIRS ? 2 : 1)) {
+                                f32x16 a0[NT], a1[PAIRS ? NT : 1];
+                                const u32x4 *f0 = fr + (size_t)(tt - tb) * (PA * KS * 64);
+                                tile_mfma(a0, f0, padded && tt == q.tpg - 1);
+                                bool two = false;
+                                if constexpr (PAIRS) if (tt + 1 < te) {
+                                    two = true;
+                                    tile_mfma(a1, f0 + PA * KS * 64, padded && tt + 1 == q.tpg - 1);
+                                    settle(a0); settle(a1);
+#pragma unroll
+                                    for (int ct = 0; ct < NT; ++ct) {
+                                        float v0[16], v1[16];
+#pragma unroll
+                                        for (int r = 0; r < 16; ++r) { v0[r] = a0[ct][r]; v1[r] = a1[ct][r]; }
+                                        merge(ct, vmax16(v0), tt);
+                                        merge(ct, vmax16(v1), tt + 1);
+#pragma unroll
+                                        for (int r = 0; r < 16; ++r) w[ct][r] = vmax3(w[ct][r], v0[r], v1[r]);
+                                    }
+                                }
+                                if (!two) {
+                                    settle(a0);
+#pragma unroll
+                                    for (int ct = 0; ct < NT; ++ct) {
+                                        float v0[16];
+#pragma unroll
+                                        for (int r = 0; r < 16; ++r) v0[r] = a0[ct][r];
+                                        merge(ct, vmax16(v0), tt);
+#pragma unroll
+                                        for (int r = 0; r < 16; ++r) w[ct][r] = vmax2(w[ct][r], v0[r]);
+                                    }
+                                }
+                            }
+                            if (qq + 1 < q.nq) continue;             // the type goes on in the next stage
+                        }
+                        // ---- epilogue of type t = u: both candidate tiles stage by stage
+                        const int t = u;
+                        const float pt = prior[t];
+                        float gm[NT];
+                        unsigned total[NT], total_other[NT];
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) gm[ct] = pair_other(best[ct], partner_addr);
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) {
+                            gm[ct] = vmax2(gm[ct], best[ct]);
+                            // bit 15 - r set iff position r holds the maximum; a unique maximiser of the
+                            // pair sits in this lane's leading tile or the columns are marked in dup
+                            const unsigned bm = bitmap16_pairs(w[ct], gm[ct]);
+                            const unsigned cnt = (unsigned)__builtin_popcount(bm);
+                            const unsigned r = ffbh(bm) - 16u;
+                            const unsigned act = (FORM == 1 ? 0u : btile[ct] << 5) | ((r & 0xCu) << 1) | (r & 3u) | (4u * h);
+                            total[ct] = cnt ? (cnt << 16) | act : 0u;
+                            total_other[ct] = (unsigned)__builtin_amdgcn_ds_bpermute(partner_addr, (int)total[ct]);
+                        }
+                        float l[NT];
+                        int js[NT];
+                        bool clean[NT];
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) {
+                            const unsigned pair = total[ct] + total_other[ct];
+                            js[ct] = (int)(pair & 0xFFFFu);
+                            unsigned long long multi = __builtin_amdgcn_ballot_w64((pair >> 16) != 1u);
+                            if constexpr (FORM == 0) multi |= dup[ct];
+                            clean[ct] = multi == 0ull;               // wave-uniform
+                            // (a wavefront that is not clean may hold any sum, and its gather is issued
+                            // all the same)
+                            js[ct] = js[ct] < n ? js[ct] : 0;
+                        }
+                        float part[NT];
+                        if (q.lead_off >= 0) {
+                            const lds_byte *lb = (const lds_byte *)sb + (unsigned)(ui * q.rec_bytes + q.lead_off + h * HALF * LBYTES);
+#pragma unroll
+                            for (int ct = 0; ct < NT; ++ct)
+                                part[ct] = half_dot(ct, (const __attribute__((address_space(3))) u32x4 *)(lb + (unsigned)(js[ct] * q.lead_stride)));
+                        } else {
+#pragma unroll
+                            for (int ct = 0; ct < NT; ++ct) part[ct] = half_dot(ct, lead_global(t, js[ct]));
+                        }
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) l[ct] = pair_total(part[ct]);
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) {
+                            if (!clean[ct]) exact_type(ct, t, gm[ct], l[ct], js[ct]);
+                            V[ct] = fmaf(pt, l[ct], V[ct]);
+                            if (per_type) {
+                                const late_args o = late();
+                                const size_t c = first + ct * 32 + col;
+                                if (h == 0 && c < count) {
+                                    if (o->a.br_out) o->a.br_out[c * o->a.br_sc + t * o->a.br_st] = js[ct];
+                                    if (o->a.l_out) o->a.l_out[c * o->a.l_sc + t * o->a.l_st] = l[ct];
+                                }
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        // ---- outputs of the block
+        float *V_out = late()->a.V_out;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const unsigned c = first + ct * 32 + col;
+            float v = V[ct];
+            if (!(v == v)) v = -INFINITY;
+            if (V_out && h == 0 && c < count) V_out[c] = v;
+            // (a lane meets its candidates in ascending order: strictly greater replaces)
+            v = c < count ? v : -INFINITY;
+            keep_greater2(v, c, best_v, best_c);
+        }
+    }
+
+    const late_args o = late();
+    if (o->a.blk_v) {
+#pragma unroll
+        for (int d = 16; d >= 1; d >>= 1) {              // both lane halves hold the same values
+            const float ov = __shfl_xor(best_v, d, 64);
+            const unsigned oc = __shfl_xor(best_c, d, 64);
+            if (ov > best_v || (ov == best_v && oc < best_c)) { best_v = ov; best_c = oc; }
+        }
+        if (lane == 0) { red_v[wave] = best_v; red_c[wave] = best_c; }
+        __syncthreads();
+        if (tid == 0) {
+            for (int k = 1; k < WAVES; ++k)
+                if (red_v[k] > best_v || (red_v[k] == best_v && red_c[k] < best_c)) { best_v = red_v[k]; best_c = red_c[k]; }
+            o->a.blk_v[blockIdx.x] = best_v;
+            o->a.blk_i[blockIdx.x] = best_c == 0xFFFFFFFFu ? LLONG_MAX : o->a.index_base + (long long)best_c;
+        }
+    }
+    if (o->a.tie_counter && lane == 0 && tie_count) atomicAdd(o->a.tie_counter, (unsigned long long)tie_count);
+}
+
+typedef void (*any_kernel_t)(AnyArgs);
+
+template <int TERMS, int KS>
+any_kernel_t any_kernel_form(int form)
+{
+    switch (form) {
+    case 0: return sweep_any_kernel<TERMS, KS, 0>;
+    case 1: return sweep_any_kernel<TERMS, KS, 1>;
+    case 8: return sweep_any_kernel<TERMS, KS, 8>;
+    case 16: return sweep_any_kernel<TERMS, KS, 16>;
+    }
+    return nullptr;
+}
+
+}  // namespace any_impl
+}  // namespace bsse
