@@ -3,6 +3,7 @@
 #include "../../include/bsse.h"
 #include "bsse_internal.h"
 
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -56,9 +57,11 @@ extern "C" const char *bsse_status_name(bsse_status s)
     } while (0)
 
 // ------------------------------------------------------------------------------ handle
+constexpr int MAX_FLAGS = 1024;
+
 struct HostOut {            // pinned, device-visible: kernels write results here directly
     RunningBest run;        // by the merge kernel of every chunk
-    float fin_v;            // by the one-row re-evaluation of the winner
+    float fin_v;            // the winner's value as its re-evaluation gave it
 };
 
 // Device scratch of the prior batch: kept by the handle and grown on demand, so that repeated
@@ -89,8 +92,7 @@ struct TopkScratch {
 };
 
 // Device scratch of the streamed sweep: one record per workgroup of a chunk, the running best, the
-// winning row, the tie counter, the per-type leader payoffs of the re-evaluated winner and (small-
-// game kernel) the workgroups' running-best slots.  Owned by the handle and grown on demand, or
+// winning row, the tie counter and (small-game kernel) the workgroups' running-best slots.  Owned by the handle and grown on demand, or
 // (`fixed`) a carving of the library's static scratch array that cannot grow.
 struct Work {
     float *blk_v = nullptr;
@@ -99,9 +101,8 @@ struct Work {
     SmallSlot *slots = nullptr;      // slot_sets sets of small_num_slots() slots
     int slot_sets = 0;
     RunningBest *run = nullptr;
-    float *best_x = nullptr;
+    float *best_x = nullptr;         // (not on the small-game kernel)
     unsigned long long *tie_counter = nullptr;
-    float *win_l = nullptr;          // [K]
     bool fixed = false;
 };
 
@@ -133,6 +134,7 @@ struct bsse_game {
     hipEvent_t aux_fork = nullptr, aux_join[2] = { nullptr, nullptr };
     bool aux_used[2] = { false, false };           // work enqueued since the last join
     unsigned chunk_seq = 0;                        // chunks of the current sweep
+    int set_used[3] = { 0, 0, 0 };                 // slots of each set that its chunks may have written
     PriorScratch pri;
     TopkScratch topk;
     // host copies of the game as given to create (fp32, unrounded): the profile LP of bsse_polish
@@ -142,11 +144,14 @@ struct bsse_game {
     float *centre_dev = nullptr;                   // [m] centre of a local candidate set
     float *pol_rows = nullptr, *pol_v = nullptr;   // device scratch of bsse_polish
     int32_t *pol_br = nullptr;
-    // pinned host
+    // pinned host memory, one block: what the kernels report
     HostOut *h_out = nullptr;
-    int32_t *h_br = nullptr;
-    float *h_x = nullptr, *h_l = nullptr;   // any-shape kernel: the winner's row [m] and per-type leader payoffs [K]
-    bool hx_valid = false;                  // h_x holds the row of the result last reported
+    unsigned *h_flag = nullptr;             // completion flags [MAX_FLAGS]
+    unsigned seq = 0;                       // of the call that last set out to wait for flags
+    int32_t *h_br = nullptr;                // the winner's best responses [K]
+    float *h_x = nullptr;                   // its row [m]
+    float *h_l = nullptr;                   // its per-type leader payoffs [K] (general and any-shape kernel)
+    bool hx_valid = false;                  // h_x holds the row of the running best and nothing is in flight
     // Any-shape kernel: a sweep in one call leaves its result on the host only (h_out->run, h_x, h_br);
     // the device copies (w.run, w.best_x) are brought up to date when a further chunk needs them.
     bool host_best = false;
@@ -216,7 +221,6 @@ void free_game(bsse_game *g)
     (void)hipFree(g->gen); (void)hipFree(g->lat_table);
     (void)hipFree(g->w.blk_v); (void)hipFree(g->w.blk_i); (void)hipFree(g->w.slots);
     (void)hipFree(g->w.run); (void)hipFree(g->w.best_x); (void)hipFree(g->w.tie_counter);
-    (void)hipFree(g->w.win_l);
     g->pri.release();
     g->topk.release();
     (void)hipFree(g->pol_rows); (void)hipFree(g->pol_v); (void)hipFree(g->pol_br);
@@ -227,9 +231,6 @@ void free_game(bsse_game *g)
     if (g->aux_fork) (void)hipEventDestroy(g->aux_fork);
     (void)hipFree(g->centre_dev); (void)hipFree(g->stage);
     if (g->h_out) (void)hipHostFree(g->h_out);
-    if (g->h_br) (void)hipHostFree(g->h_br);
-    if (g->h_x) (void)hipHostFree(g->h_x);
-    if (g->h_l) (void)hipHostFree(g->h_l);
     if (g->h_rec) (void)hipHostFree(g->h_rec);
     (void)hipFree(g->row_l); (void)hipFree(g->row_br);
     for (hipEvent_t e : g->ev) (void)hipEventDestroy(e);
@@ -311,6 +312,7 @@ bsse_status grow_pinned(bsse_game *g, void **ptr, size_t *cap, size_t bytes)
     *ptr = nullptr; *cap = 0;
     if (hipHostMalloc(ptr, bytes, hipHostMallocDefault) != hipSuccess)
         return fail(BSSE_ENOMEM, "hipHostMalloc of %zu bytes failed", bytes);
+    memset(*ptr, 0, bytes);                      // (no completion flag is set)
     *cap = bytes;
     return BSSE_OK;
 }
@@ -318,23 +320,75 @@ bsse_status grow_pinned(bsse_game *g, void **ptr, size_t *cap, size_t bytes)
 // Per-type outputs of a sliced launch: at most this many (64 MiB of leader payoffs).
 constexpr long long ROW_SCRATCH_MAX = 1LL << 24;
 
+// Paths whose launches can be cut over the types, and whether `count` rows are few enough for it.
+bool cuts_types(const bsse_game *g)
+{
+    return on_any(g) || (g->path != PATH_VALU && !mfma_is_small(g->view.variant));
+}
+bool few_rows(const bsse_game *g, long long count)
+{
+    if (!cuts_types(g) || count * g->K > ROW_SCRATCH_MAX) return false;
+    return on_any(g) ? any_slices(g->view, count) > 1 : mfma_few_rows(g->view, count);
+}
+
+// A launch cut over the types where that pays: a.l_out (and a.br_out) only.
+hipError_t launch_rows(bsse_game *g, const SweepArgs &a, hipStream_t stream)
+{
+    return on_any(g) ? launch_sweep_any(g->view, a, any_slices(g->view, a.count), stream)
+                     : launch_sweep_mfma(g->view, a, stream);
+}
+// Workgroups of such a launch of one candidate block that set a completion flag.
+int row_flags(const bsse_game *g) { return on_any(g) ? any_slices(g->view, 1) : mfma_slices(g->view, 1); }
+
 // Per-candidate outputs (a.V_out, a.br_out [count][K], a.l_out [count][K]; each nullable).
 bsse_status launch_eval(bsse_game *g, SweepArgs a)
 {
-    if (!on_any(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
+    if (!cuts_types(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
     a.br_sc = g->K; a.br_st = 1; a.l_sc = g->K; a.l_st = 1;
-    int slices = any_slices(g->view, a.count);
-    if (a.V_out && (a.l_out || a.count * g->K > ROW_SCRATCH_MAX)) slices = 1;
-    if (slices == 1 || !a.V_out) { HIP_TRY(launch_sweep_any(g->view, a, slices, g->stream)); return BSSE_OK; }
+    if (!a.V_out && (a.l_out || on_any(g))) { HIP_TRY(launch_rows(g, a, g->stream)); return BSSE_OK; }
+    if (a.l_out || !few_rows(g, a.count)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
     bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float));
     if (st != BSSE_OK) return st;
     FinishRowsArgs f{};
     f.l = g->row_l; f.prior = g->dprior; f.count = a.count; f.K = g->K; f.m = g->m; f.V_out = a.V_out;
     a.V_out = nullptr; a.l_out = g->row_l; a.l_sc = 1; a.l_st = a.count;
-    HIP_TRY(launch_sweep_any(g->view, a, slices, g->stream));
-    HIP_TRY(launch_finish_rows(f, g->stream));
+    HIP_TRY(launch_rows(g, a, g->stream));
+    if (f.V_out) HIP_TRY(launch_finish_rows(f, g->stream));
     return BSSE_OK;
 }
+
+// The completion flags of the call's last launch: a sequence number no flag holds yet.
+Done new_done(bsse_game *g)
+{
+    g->seq += 1;
+    if (g->seq == 0) g->seq = 1;                 // 0 is the state of a flag never set
+    return Done{ g->h_flag, g->seq };
+}
+
+// Waits until `n` words, `stride` bytes apart, hold the handle's sequence number.  Polling ends by
+// itself: after SPIN_US the stream is synchronised instead, which also reports a failed launch.
+constexpr long long SPIN_US = 50000;
+bsse_status wait_words(bsse_game *g, const unsigned *word, int n, size_t stride)
+{
+    const auto *p = reinterpret_cast<const unsigned char *>(word);
+    std::chrono::steady_clock::time_point t0{};
+    bool started = false, synced = false;
+    for (int i = 0; i < n; ++i) {
+        const unsigned *w = reinterpret_cast<const unsigned *>(p + (size_t)i * stride);
+        for (unsigned k = 1; __atomic_load_n(w, __ATOMIC_ACQUIRE) != g->seq; ++k) {
+            if (synced) return fail(BSSE_EDEVICE, "internal: completion flag %d was not set", i);
+            __builtin_ia32_pause();
+            if (k % 1024 != 0) continue;
+            const auto now = std::chrono::steady_clock::now();
+            if (!started) { t0 = now; started = true; }
+            if (std::chrono::duration_cast<std::chrono::microseconds>(now - t0).count() < SPIN_US) continue;
+            HIP_TRY(hipStreamSynchronize(g->stream));
+            synced = true;
+        }
+    }
+    return BSSE_OK;
+}
+bsse_status wait_flags(bsse_game *g, int n) { return wait_words(g, g->h_flag, n, sizeof(unsigned)); }
 
 bsse_status take_event(bsse_game *g, hipEvent_t *e)
 {
@@ -375,15 +429,14 @@ bsse_status drain_timing(bsse_game *g)
 namespace {
 
 constexpr long long STATIC_MAX_BLOCKS = 65536;    // workgroup records of one chunk
-constexpr int STATIC_MAX_M = 4096, STATIC_MAX_K = 65536, STATIC_MAX_SLOTS = 2048;
+constexpr int STATIC_MAX_M = 4096, STATIC_MAX_SLOTS = 2048;
 constexpr size_t ST_OFF_RUN = 0, ST_OFF_TIES = 256, ST_OFF_BESTX = 512,
-                 ST_OFF_WINL = ST_OFF_BESTX + (size_t)STATIC_MAX_M * sizeof(float),
-                 ST_OFF_BLKV = ST_OFF_WINL + (size_t)STATIC_MAX_K * sizeof(float),
+                 ST_OFF_BLKV = ST_OFF_BESTX + (size_t)STATIC_MAX_M * sizeof(float),
                  ST_OFF_BLKI = ST_OFF_BLKV + (size_t)STATIC_MAX_BLOCKS * sizeof(float),
                  ST_OFF_SLOTS = ST_OFF_BLKI + (size_t)STATIC_MAX_BLOCKS * sizeof(long long),
                  STATIC_BYTES = ST_OFF_SLOTS + (size_t)STATIC_MAX_SLOTS * sizeof(SmallSlot);
 static_assert(sizeof(RunningBest) <= 256 && sizeof(SmallSlot) == 64, "scratch layout");
-static_assert(ST_OFF_WINL % 256 == 0 && ST_OFF_BLKV % 256 == 0 && ST_OFF_BLKI % 256 == 0 &&
+static_assert(ST_OFF_BLKV % 256 == 0 && ST_OFF_BLKI % 256 == 0 &&
               ST_OFF_SLOTS % 256 == 0, "scratch parts stay 256-byte aligned");
 
 }  // namespace
@@ -561,9 +614,6 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
             if (st == BSSE_OK && pe != hipSuccess)
                 st = fail(pe == hipErrorOutOfMemory ? BSSE_ENOMEM : BSSE_EDEVICE, "packing: %s", hipGetErrorString(pe));
             if (st != BSSE_OK) break;
-            hipError_t he = hipHostMalloc((void **)&g->h_x, (size_t)m * 4, hipHostMallocDefault);
-            if (he == hipSuccess) he = hipHostMalloc((void **)&g->h_l, (size_t)K * 4, hipHostMallocDefault);
-            if (he != hipSuccess) { st = fail(BSSE_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(he)); break; }
         } else if (use_mfma) {
             void *pb = nullptr, *pa = nullptr;
             size_t bb = 0, ab = 0;
@@ -582,10 +632,17 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         if (use_mfma && mfma_is_small(variant) &&       // epoch 0 marks a slot never written
             (st = zeroed((void **)&g->w.slots, (size_t)3 * small_num_slots() * sizeof(SmallSlot))) != BSSE_OK) break;
         g->w.slot_sets = g->w.slots ? 3 : 0;
-        if ((st = zeroed((void **)&g->w.win_l, (size_t)K * 4)) != BSSE_OK) break;
-        hipError_t e = hipHostMalloc((void **)&g->h_out, sizeof(HostOut), hipHostMallocDefault);
-        if (e == hipSuccess) e = hipHostMalloc((void **)&g->h_br, (size_t)K * 4, hipHostMallocDefault);
+        const size_t off_flag = 256, off_br = off_flag + MAX_FLAGS * sizeof(unsigned), off_l = off_br + (size_t)K * 4,
+                     off_x = off_l + (size_t)K * 4, host_bytes = off_x + (size_t)m * 4;
+        static_assert(sizeof(HostOut) <= 256, "the flags start behind it");
+        hipError_t e = hipHostMalloc((void **)&g->h_out, host_bytes, hipHostMallocDefault);
         if (e != hipSuccess) { st = fail(BSSE_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e)); break; }
+        unsigned char *hb = reinterpret_cast<unsigned char *>(g->h_out);
+        memset(hb, 0, host_bytes);
+        g->h_flag = reinterpret_cast<unsigned *>(hb + off_flag);
+        g->h_br = reinterpret_cast<int32_t *>(hb + off_br);
+        g->h_l = reinterpret_cast<float *>(hb + off_l);
+        g->h_x = reinterpret_cast<float *>(hb + off_x);
     } while (0);
     if (st != BSSE_OK) { free_game(g); return st; }
 
@@ -880,6 +937,8 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     g->host_best = false; g->hx_valid = false;
     long long nblocks = 0;
     hipStream_t stream = g->stream;
+    const bool rows = !small && !g->w.fixed && few_rows(g, count);       // (the static scratch holds records only)
+    FinishRowsArgs f{};
     if (small) {
         // every workgroup keeps its own running best over the chunks: nothing but the sweep
         // kernel runs per chunk; bsse_sweep_result folds
@@ -889,6 +948,7 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
             if (g->epoch == 0) g->epoch = 1;         // 0 is the mark of a slot never written
             g->fold_first = true;
             g->chunk_seq = 0;
+            g->set_used[0] = g->set_used[1] = g->set_used[2] = 0;
             if (g->ties_dirty) HIP_TRY(launch_clear_u64(g->w.tie_counter, g->stream));   // an abandoned sweep's
         }
         int set = g->w.slot_sets - 1;                // the caller's stream (the last set)
@@ -904,12 +964,21 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
             stream = g->aux[set];
         }
         g->chunk_seq += 1;
+        g->set_used[set] = std::max(g->set_used[set], (int)sweep_blocks(g, count));
         a.small.slots = g->w.slots + (size_t)set * small_num_slots(); a.small.epoch = g->epoch;
         a.tie_counter = g->w.tie_counter;
     } else {
-        nblocks = sweep_blocks(g, count);
+        nblocks = rows ? (count + FINISH_ROWS - 1) / FINISH_ROWS : sweep_blocks(g, count);
         if ((st = ensure_blocks(g, nblocks)) != BSSE_OK) return st;
-        a.blk_v = g->w.blk_v; a.blk_i = g->w.blk_i; a.tie_counter = g->w.tie_counter;
+        a.tie_counter = g->w.tie_counter;
+        if (rows) {
+            if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * g->K * sizeof(float))) != BSSE_OK) return st;
+            a.l_out = g->row_l; a.l_sc = 1; a.l_st = count;
+            f.l = g->row_l; f.prior = g->dprior; f.count = count; f.index_base = a.index_base; f.K = g->K; f.m = g->m;
+            f.blk_v = g->w.blk_v; f.blk_i = g->w.blk_i;
+        } else {
+            a.blk_v = g->w.blk_v; a.blk_i = g->w.blk_i;
+        }
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (g->timing) {
@@ -917,7 +986,7 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
         if ((st = take_event(g, &e1)) != BSSE_OK) { g->ev_pool.push_back(e0); return st; }
         HIP_TRY(hipEventRecord(e0, stream));
     }
-    hipError_t le = launch_sweep_on(g, a, false, stream);
+    hipError_t le = rows ? launch_rows(g, a, stream) : launch_sweep_on(g, a, false, stream);
     if (g->timing) {
         (void)hipEventRecord(e1, stream);
         g->ev.push_back(e0); g->ev.push_back(e1);
@@ -926,9 +995,10 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     if (small) {
         g->fold_pending = true; g->ties_dirty = true;
     } else {
+        if (rows) HIP_TRY(launch_finish_rows(f, g->stream));
         HIP_TRY(launch_reduce_merge(g->w.blk_v, g->w.blk_i, nblocks, a.X, a.index_base, g->m,
                                     g->fresh ? 1 : 0, g->w.tie_counter, g->w.run, &g->h_out->run, g->w.best_x,
-                                    g->stream));
+                                    g->h_x, g->stream));
     }
     g->fresh = false;
     g->result_valid = false;  // until bsse_sweep_result has brought the new state to the host
@@ -937,21 +1007,23 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
 }
 
 // Small-game kernel: fold the workgroups' running bests into the handle's result (value, index,
-// row, best responses, tie count).  No-op when nothing was swept since the last fold.
+// row, best responses, tie count) and wait for it.  No-op when nothing was swept since the last fold.
 bsse_status fold_small(bsse_game *g)
 {
-    if (!on_small_kernel(g) || !g->fold_pending) return BSSE_OK;
+    if (!g->fold_pending) return BSSE_OK;
     bsse_status st = join_aux(g);
     if (st != BSSE_OK) return st;
     FinishArgs f{};
-    f.slots = g->w.slots; f.nslots = g->w.slot_sets * small_num_slots(); f.epoch = g->epoch;
+    f.slots = g->w.slots; f.epoch = g->epoch;
+    for (int q = 0; q < 3; ++q) f.used[q] = g->set_used[q];
     f.first = g->fold_first ? 1 : 0;
     f.tie_counter = g->w.tie_counter;
-    f.run = g->w.run; f.run_host = &g->h_out->run; f.best_x = g->w.best_x;
+    f.run = g->w.run; f.run_host = &g->h_out->run; f.x_host = g->h_x;
     f.win_v = &g->h_out->fin_v; f.win_br = g->h_br;
+    f.done = new_done(g);
     HIP_TRY(launch_finish_small(g->view, f, g->stream));
     g->fold_pending = false; g->fold_first = false; g->ties_dirty = false;
-    return BSSE_OK;
+    return wait_flags(g, 1);
 }
 
 bool fuses_generation(const bsse_game *g) { return on_small_kernel(g); }
@@ -1020,7 +1092,8 @@ extern "C" bsse_status bsse_sweep_dirichlet_chunk(bsse_game *g, uint64_t seed, i
 }
 
 namespace {
-bsse_status sweep_once_any(bsse_game *g, const float *X, long long count, bsse_result *res, int32_t *best_response_out);
+bool sweeps_at_once(const bsse_game *g, long long count);
+bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_result *res, int32_t *best_response_out);
 }
 
 extern "C" bsse_status bsse_sweep_dirichlet(bsse_game *g, uint64_t seed, int64_t first, int64_t count,
@@ -1032,12 +1105,12 @@ extern "C" bsse_status bsse_sweep_dirichlet(bsse_game *g, uint64_t seed, int64_t
     bsse_status st = check_rows(first, count);
     if (st != BSSE_OK) return st;
     if ((st = bsse_sweep_reset(g)) != BSSE_OK) return st;
-    if (on_any(g) && count > 0 && count <= stage_rows(g)) {
+    if (sweeps_at_once(g, count) && count <= stage_rows(g)) {
         DeviceGuard dg(g->device);
         if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
         if ((st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)count * g->m * sizeof(float))) != BSSE_OK) return st;
         HIP_TRY(launch_dirichlet(seed, first, count, g->m, nullptr, 1.0f, g->stage, g->stream));
-        return sweep_once_any(g, g->stage, count, res, best_response_out);
+        return sweep_once(g, g->stage, count, res, best_response_out);
     }
     if ((st = bsse_sweep_dirichlet_chunk(g, seed, first, count, 0)) != BSSE_OK) return st;
     return bsse_sweep_result(g, res, best_response_out);
@@ -1061,27 +1134,26 @@ extern "C" bsse_status bsse_sweep_result(bsse_game *g, bsse_result *res, int32_t
     }
     // best responses of the winner: the same kernel, one row, per-candidate outputs written
     // straight into pinned host memory (the small-game kernel carries them with its records)
+    bsse_status st = BSSE_OK;
     if (on_small_kernel(g)) {
-        bsse_status st = fold_small(g);
-        if (st != BSSE_OK) return st;
-    } else if (on_any(g)) {
-        if (!g->host_best) {
-            SweepArgs a{};
-            a.X = g->w.best_x; a.count = 1;
-            a.br_out = g->h_br; a.br_sc = g->K; a.br_st = 1;
-            a.l_out = g->h_l; a.l_sc = g->K; a.l_st = 1;
-            a.row_host = g->h_x;
-            HIP_TRY(launch_sweep_any(g->view, a, any_slices(g->view, 1), g->stream));
-        }
-    } else {
+        st = fold_small(g);
+    } else if (!g->host_best) {
         SweepArgs a{};
-        a.X = g->w.best_x; a.count = 1; a.index_base = 0;
-        a.V_out = &g->h_out->fin_v; a.br_out = g->h_br;
-        // one row against every type: the general matrix-core kernel spreads the types over the chip
-        if (g->path != PATH_VALU && mfma_slices_types(g->view.variant)) a.l_out = g->w.win_l;
-        HIP_TRY(launch_sweep(g, a, true));
+        a.X = g->w.best_x; a.count = 1;
+        a.br_out = g->h_br; a.br_sc = g->K; a.br_st = 1;
+        a.done = new_done(g);
+        if (cuts_types(g)) {
+            // one row against every type: the types are spread over the chip, and the host sums
+            a.l_out = g->h_l; a.l_sc = g->K; a.l_st = 1;
+            HIP_TRY(launch_rows(g, a, g->stream));
+            if ((st = wait_flags(g, row_flags(g))) == BSSE_OK && g->h_out->run.has) g->h_out->fin_v = value_of(g, g->h_l);
+        } else {
+            a.V_out = &g->h_out->fin_v;
+            HIP_TRY(launch_sweep(g, a, true));
+            st = wait_flags(g, 1);
+        }
     }
-    if (!g->host_best) HIP_TRY(hipStreamSynchronize(g->stream));
+    if (st != BSSE_OK) return st;
     return report_result(g, res, best_response_out);
 }
 
@@ -1091,10 +1163,7 @@ namespace {
 bsse_status report_result(bsse_game *g, bsse_result *res, int32_t *best_response_out)
 {
     const bool has = g->h_out->run.has != 0;
-    if (on_any(g)) {
-        if (!g->host_best && has) g->h_out->fin_v = value_of(g, g->h_l);
-        g->hx_valid = has;
-    }
+    g->hx_valid = has;
     if (has && !(g->h_out->fin_v == g->h_out->run.value))
         return fail(BSSE_EDEVICE, "internal: re-evaluated winner value %.9g differs from swept value %.9g",
                     (double)g->h_out->fin_v, (double)g->h_out->run.value);
@@ -1107,22 +1176,37 @@ bsse_status report_result(bsse_game *g, bsse_result *res, int32_t *best_response
     return BSSE_OK;
 }
 
-// One whole sweep (already reset) of rows that stay put until it is done, on the any-shape path: two
-// launches and one wait, whatever the size.  Few rows: a type-sliced launch, and one that sums the
+// Whether the records of a sweep of few rows, each with a row and its best responses, are few enough
+// to go to the host (256 KiB: a few microseconds over the bus).
+constexpr int MAX_HOST_RECS = 512;
+bool host_folds(const bsse_game *g, long long count)
+{
+    const long long nrec = (count + FINISH_ROWS - 1) / FINISH_ROWS;
+    return few_rows(g, count) && nrec <= MAX_HOST_RECS && nrec * (g->m + g->K) <= (1LL << 16);
+}
+
+// Whether sweep_once takes a sweep.
+bool sweeps_at_once(const bsse_game *g, long long count)
+{
+    return count > 0 && (host_folds(g, count) || (on_any(g) && !few_rows(g, count)));
+}
+
+// One whole sweep (already reset) of rows that stay put until it is done, on the any-shape path, or on
+// the general one when the rows are few: two launches and one wait, whatever the size.  Few rows: a type-sliced launch, and one that sums the
 // values and leaves a record per 256 rows, with that record's row and best responses, in pinned memory;
 // the host folds the records.  Many rows: the sweep, and one launch whose workgroups each fold its
 // records and evaluate their slice of the types at the winner.
-bsse_status sweep_once_any(bsse_game *g, const float *X, long long count, bsse_result *res, int32_t *best_response_out)
+bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_result *res, int32_t *best_response_out)
 {
     const int m = g->m, K = g->K;
     bsse_status st;
     g->host_best = false; g->hx_valid = false;
-    const int slices = any_slices(g->view, count);
     const long long nrec = (count + FINISH_ROWS - 1) / FINISH_ROWS;
-    const bool rows = slices > 1 && nrec <= 256 && nrec * (m + K) <= (1LL << 18) && count * K <= ROW_SCRATCH_MAX;
+    const bool rows = host_folds(g, count);
     SweepArgs a{};
     a.X = X; a.count = count; a.tie_counter = g->w.tie_counter;
-    const size_t off_x = (size_t)nrec * sizeof(FinishRec), off_br = off_x + (size_t)nrec * m * sizeof(float);
+    // (the records have a place of their own: nothing else is ever written where a flag is looked for)
+    const size_t off_x = (size_t)MAX_HOST_RECS * sizeof(FinishRec), off_br = off_x + (size_t)nrec * m * sizeof(float);
     if (rows) {
         if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * K * sizeof(float))) != BSSE_OK) return st;
         if ((st = grow_device(g, (void **)&g->row_br, &g->cap_row_br, (size_t)count * K * sizeof(int32_t))) != BSSE_OK) return st;
@@ -1139,7 +1223,7 @@ bsse_status sweep_once_any(bsse_game *g, const float *X, long long count, bsse_r
         if ((st = take_event(g, &e1)) != BSSE_OK) { g->ev_pool.push_back(e0); return st; }
         HIP_TRY(hipEventRecord(e0, g->stream));
     }
-    const hipError_t le = launch_sweep_any(g->view, a, rows ? slices : 1, g->stream);
+    const hipError_t le = rows ? launch_rows(g, a, g->stream) : launch_sweep_any(g->view, a, 1, g->stream);
     if (g->timing) {
         (void)hipEventRecord(e1, g->stream);
         g->ev.push_back(e0); g->ev.push_back(e1);
@@ -1152,6 +1236,7 @@ bsse_status sweep_once_any(bsse_game *g, const float *X, long long count, bsse_r
         f.rec_x = reinterpret_cast<float *>(g->h_rec + off_x);
         f.rec_br = reinterpret_cast<int32_t *>(g->h_rec + off_br);
         f.ties = g->w.tie_counter;
+        f.seq = new_done(g).seq;
         HIP_TRY(launch_finish_rows(f, g->stream));
     } else {
         SweepArgs e{};
@@ -1161,11 +1246,14 @@ bsse_status sweep_once_any(bsse_game *g, const float *X, long long count, bsse_r
         e.row_host = g->h_x;
         e.br_out = g->h_br; e.br_sc = K; e.br_st = 1;
         e.l_out = g->h_l; e.l_sc = K; e.l_st = 1;
-        HIP_TRY(launch_sweep_any(g->view, e, any_slices(g->view, 1), g->stream));
+        e.done = new_done(g);
+        HIP_TRY(launch_rows(g, e, g->stream));
     }
     g->fresh = false;
     g->n_evals += count * K;
-    HIP_TRY(hipStreamSynchronize(g->stream));
+    st = rows ? wait_words(g, &reinterpret_cast<const FinishRec *>(g->h_rec)->seq, (int)nrec, sizeof(FinishRec))
+              : wait_flags(g, row_flags(g));
+    if (st != BSSE_OK) return st;
     if (rows) {
         const FinishRec *rec = reinterpret_cast<const FinishRec *>(g->h_rec);
         long long b = 0;
@@ -1192,14 +1280,16 @@ extern "C" bsse_status bsse_sweep_best_row(bsse_game *g, float *x_out)
     if (!x_out) return fail(BSSE_EINVAL, "x_out is NULL");
     DeviceGuard dg(g->device);
     if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
-    if (!g->fresh) {
-        bsse_status st = fold_small(g);
-        if (st != BSSE_OK) return st;
+    if (g->fresh || !g->hx_valid) {
+        if (!g->fresh && on_small_kernel(g)) {
+            bsse_status st = fold_small(g);
+            if (st != BSSE_OK) return st;
+        } else {
+            HIP_TRY(hipStreamSynchronize(g->stream));
+        }
     }
-    if (!g->hx_valid || g->fresh) HIP_TRY(hipStreamSynchronize(g->stream));
     if (g->fresh || !g->h_out->run.has) return fail(BSSE_ESTATE, "no candidate has been swept since the last reset");
-    if (g->hx_valid) memcpy(x_out, g->h_x, (size_t)g->m * sizeof(float));
-    else HIP_TRY(hipMemcpy(x_out, g->w.best_x, (size_t)g->m * sizeof(float), hipMemcpyDeviceToHost));
+    memcpy(x_out, g->h_x, (size_t)g->m * sizeof(float));
     return BSSE_OK;
 }
 
@@ -1217,14 +1307,14 @@ extern "C" bsse_status bsse_sweep(bsse_game *g, const float *candidates_dev, int
     }
     bsse_status st = bsse_sweep_reset(g);
     if (st != BSSE_OK) return st;
-    if (on_any(g)) {
+    {
         const float *x = candidates_dev;
         int64_t c = count;
         if ((st = resolve_candidates(g, &x, &c)) != BSSE_OK) return st;
-        if (c > 0) {
+        if (sweeps_at_once(g, c)) {
             DeviceGuard dg(g->device);
             if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
-            return sweep_once_any(g, x, c, res, best_response_out);
+            return sweep_once(g, x, c, res, best_response_out);
         }
     }
     if ((st = bsse_sweep_chunk(g, candidates_dev, count, 0)) != BSSE_OK) return st;
@@ -1254,8 +1344,7 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
     if (small && small_num_slots() > STATIC_MAX_SLOTS)
         return fail(BSSE_EOVERFLOW, "the static scratch holds %d running-best slots, %d needed", STATIC_MAX_SLOTS,
                     small_num_slots());
-    if (g->m > STATIC_MAX_M || g->K > STATIC_MAX_K)
-        return fail(BSSE_EOVERFLOW, "the static scratch holds rows of %d and %d types", STATIC_MAX_M, STATIC_MAX_K);
+    if (g->m > STATIC_MAX_M) return fail(BSSE_EOVERFLOW, "the static scratch holds rows of %d", STATIC_MAX_M);
     DeviceGuard dg(g->device);
     if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
     unsigned char *ptr = nullptr;
@@ -1277,7 +1366,6 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
     w.run = reinterpret_cast<RunningBest *>(ptr + ST_OFF_RUN);
     w.tie_counter = reinterpret_cast<unsigned long long *>(ptr + ST_OFF_TIES);
     w.best_x = reinterpret_cast<float *>(ptr + ST_OFF_BESTX);
-    w.win_l = reinterpret_cast<float *>(ptr + ST_OFF_WINL);
     w.blk_v = reinterpret_cast<float *>(ptr + ST_OFF_BLKV);
     w.blk_i = reinterpret_cast<long long *>(ptr + ST_OFF_BLKI);
     w.blk_cap = STATIC_MAX_BLOCKS;
@@ -1678,14 +1766,12 @@ extern "C" bsse_status bsse_polish(bsse_game *g, const int32_t *profile, float *
     if (cells > (double)(1u << 28)) return fail(BSSE_EOVERFLOW, "the program's tableau (%.3g cells) is too large", cells);
     DeviceGuard dg(g->device);
     if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
-    HIP_TRY(hipStreamSynchronize(g->stream));            // the winner's row and profile are final
     std::vector<int32_t> prof((size_t)K);
     std::vector<float> start((size_t)m), rows((size_t)kPolishRows * m), vals((size_t)kPolishRows);
     std::vector<int32_t> brs((size_t)kPolishRows * K);
     std::vector<double> x((size_t)m);
     memcpy(prof.data(), profile ? profile : g->h_br, (size_t)K * sizeof(int32_t));
-    if (g->hx_valid) memcpy(start.data(), g->h_x, (size_t)m * sizeof(float));
-    else HIP_TRY(hipMemcpy(start.data(), g->w.best_x, (size_t)m * sizeof(float), hipMemcpyDeviceToHost));
+    memcpy(start.data(), g->h_x, (size_t)m * sizeof(float));     // (a reported result: nothing in flight)
     double v_lp = 0.0;
     const int rc = solve_profile_lp(m, n, K, g->hA.data(), g->hB.data(), g->hprior.data(), prof.data(),
                                     x.data(), &v_lp);

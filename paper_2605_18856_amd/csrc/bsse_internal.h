@@ -39,6 +39,13 @@ struct GameView {
     AnyGeo any;           // variant kAnyVariant
 };
 
+// Completion flags of a call in pinned host memory: workgroup b of its last launch stores `seq` into
+// flag[b] once its results are there (see done_device.h).  flag == nullptr: nobody waits.
+struct Done {
+    unsigned *flag;
+    unsigned seq;
+};
+
 // Running best over chunks, in device memory.
 struct RunningBest {
     float value;
@@ -67,16 +74,17 @@ struct SmallSweep {
 
 // Fold of the slots into the result of the sweep.
 struct FinishArgs {
-    const SmallSlot *slots;
-    int nslots;
+    const SmallSlot *slots;  // up to three sets, small_num_slots() apart
+    int used[3];             // slots of each set that a launch of this sweep may have written
     unsigned epoch;
     int first;               // != 0: first fold of this sweep (the tie count restarts)
     unsigned long long *tie_counter;
     RunningBest *run;        // device
     RunningBest *run_host;   // device-visible pinned host memory
-    float *best_x;           // [m] row of the best
+    float *x_host;           // [m] row of the best (pinned host)
     float *win_v;            // its value (pinned host)
     int32_t *win_br;         // [K] its best responses (pinned host)
+    Done done;
 };
 
 // One sweep launch.  Either (V_out, br_out) [evaluation mode: per-candidate outputs] or
@@ -92,13 +100,15 @@ struct SweepArgs {
     unsigned long long *tie_counter;  // += number of (candidate,type) evaluations with a tie
     // Evaluation mode only: l_out [count][K] receives the leader payoffs l_t[j*_t] at the best
     // responses.  In the general matrix-core kernel this selects the type-sliced instantiation:
-    // for a handful of rows the launch is split over the types as well (one workgroup walking
-    // every type would leave the chip idle), and a second kernel forms V_out from l_out in type
-    // order (the same sum, term by term, as the unsliced kernel).
+    // for few rows the launch is split over the types as well (one workgroup walking every type
+    // would leave the chip idle); the value comes from launch_finish_rows or, for one row, from the
+    // host, which sum l_out in type order (term by term the sum of the unsliced kernel).
     float *l_out;
     int slice_stages;        // LDS stages (any-shape kernel: units) per slice (set by the launcher)
-    // Any-shape kernel: l_out / br_out element (c, t) sits at c * _sc + t * _st.
+    // Any-shape kernel and sliced instantiation of the general one: l_out / br_out element (c, t) sits
+    // at c * _sc + t * _st.
     long long l_sc, l_st, br_sc, br_st;
+    Done done;               // launches of one candidate block: a flag per workgroup (by blockIdx.y)
     // Any-shape kernel, one row (count == 1): with fold_n > 0 the row is the winner of fold_n
     // workgroup records of an earlier launch over the rows X; the winner and the tie counter's value
     // (which is cleared) go to fold_run.  row_host (nullable) receives the row evaluated.
@@ -140,7 +150,10 @@ const char *mfma_variant_name(int variant);
 long long mfma_num_blocks(int variant, long long count);
 hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t s);
 hipError_t mfma_prepare(int variant, int K);   // per game, on its device, before the first launch
-bool mfma_slices_types(int variant);   // the variant honours SweepArgs::l_out
+// Type slices of a launch with l_out; whether `count` candidates are so few that a sweep or an
+// evaluation is a launch with l_out and then launch_finish_rows.
+int mfma_slices(const GameView &g, long long count);
+bool mfma_few_rows(const GameView &g, long long count);
 bool mfma_is_small(int variant);       // the small-game kernel: launch_finish_small applies
 // Host-side packing of payoffs for a variant; returns malloc'ed buffers (caller frees).
 void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B, void **Bpack,
@@ -170,12 +183,13 @@ int any_slices(const GameView &g, long long count);
 // slices > 1: l_out (and br_out) only; the value comes from launch_finish_rows.
 hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int slices, hipStream_t s);
 
-// Values of rows whose per-type leader payoffs l (type-major, [K][count]) a sliced launch left:
+// Values of rows whose per-type leader payoffs l (type-major, [K][count]) a sliced launch left
+// (here and below on the any-shape path and for the general matrix-core kernel alike):
 // V[c] = sum_t prior[t] * l[t][c] in type order.  V_out: [count], nullable.  blk_v / blk_i: one record
 // per workgroup of FINISH_ROWS rows, nullable.  With rec: the same records in pinned host memory, each
 // with the row and the best responses (br type-major, [K][count]) of the workgroup's winner.
 constexpr int FINISH_ROWS = 256;
-struct FinishRec { float value; int pad; long long index; unsigned long long ties; };
+struct FinishRec { float value; unsigned seq; long long index; unsigned long long ties; };
 struct FinishRowsArgs {
     const float *l, *prior, *X;
     const int32_t *br;
@@ -187,16 +201,17 @@ struct FinishRowsArgs {
     float *rec_x;            // [workgroups][m]
     int32_t *rec_br;         // [workgroups][K]
     unsigned long long *ties;   // read into record 0 and cleared
+    unsigned seq;            // stored into a record last (see Done)
 };
 hipError_t launch_finish_rows(const FinishRowsArgs &f, hipStream_t s);
 
 // first != 0: the running best is replaced, not merged (start of a sweep).  tie_counter (the
 // chunk's count, left by the sweep kernel) is folded into run->ties and cleared.  The merged
-// record is also written to run_host (device-visible pinned host memory).
+// record is also written to run_host and the row of a new best to x_host (pinned host memory).
 hipError_t launch_reduce_merge(const float *blk_v, const long long *blk_i, long long nblocks,
                                const float *X, long long index_base, int m, int first,
                                unsigned long long *tie_counter, RunningBest *run,
-                               RunningBest *run_host, float *best_x, hipStream_t s);
+                               RunningBest *run_host, float *best_x, float *x_host, hipStream_t s);
 
 // *p = 0 by a one-thread kernel (a fill node that is safe to capture in a graph).
 hipError_t launch_clear_u64(unsigned long long *p, hipStream_t s);

@@ -22,7 +22,7 @@ __global__ void __launch_bounds__(RT)
 reduce_merge_kernel(const float *__restrict__ blk_v, const long long *__restrict__ blk_i,
                     long long nblocks, const float *__restrict__ X, long long index_base, int m,
                     int first, unsigned long long *tie_counter, RunningBest *run,
-                    RunningBest *run_host, float *best_x)
+                    RunningBest *run_host, float *best_x, float *x_host)
 {
     __shared__ float sv[RT / 64];
     __shared__ long long si[RT / 64];
@@ -65,7 +65,10 @@ reduce_merge_kernel(const float *__restrict__ blk_v, const long long *__restrict
     __syncthreads();
     const long long row = win;
     if (row >= 0)
-        for (int i = threadIdx.x; i < m; i += RT) best_x[i] = X[row * m + i];
+        for (int i = threadIdx.x; i < m; i += RT) {
+            const float x = X[row * m + i];
+            best_x[i] = x; x_host[i] = x;
+        }
 }
 
 __global__ void clear_u64_kernel(unsigned long long *p) { *p = 0ull; }
@@ -100,11 +103,11 @@ hipError_t launch_clear_u64(unsigned long long *p, hipStream_t s)
 hipError_t launch_reduce_merge(const float *blk_v, const long long *blk_i, long long nblocks,
                                const float *X, long long index_base, int m, int first,
                                unsigned long long *tie_counter, RunningBest *run,
-                               RunningBest *run_host, float *best_x, hipStream_t s)
+                               RunningBest *run_host, float *best_x, float *x_host, hipStream_t s)
 {
     if (nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(reduce_merge_kernel, dim3(1), dim3(RT), 0, s, blk_v, blk_i, nblocks, X,
-                       index_base, m, first, tie_counter, run, run_host, best_x);
+                       index_base, m, first, tie_counter, run, run_host, best_x, x_host);
     return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 // it, and the kernel that turns the per-type leader payoffs of a sliced launch into values.
 #include "bsse_internal.h"
 #include "sweep_any_impl.h"
+#include "done_device.h"
 
 namespace bsse {
 
@@ -108,7 +109,15 @@ __global__ void __launch_bounds__(FINISH_ROWS) finish_rows_kernel(FinishRowsArgs
     const unsigned count = (unsigned)f.count, c = blockIdx.x * FINISH_ROWS + tid;
     const unsigned cc = c < count ? c : count - 1u;
     float v = 0.0f;
-    for (int t = 0; t < f.K; ++t) v = fmaf(f.prior[t], f.l[(size_t)t * count + cc], v);
+    int t0 = 0;
+    for (; t0 + 8 <= f.K; t0 += 8) {                     // eight loads in flight: the loop is bound by their latency
+        float l[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) l[k] = f.l[(size_t)(t0 + k) * count + cc];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v = fmaf(f.prior[t0 + k], l[k], v);
+    }
+    for (; t0 < f.K; ++t0) v = fmaf(f.prior[t0], f.l[(size_t)t0 * count + cc], v);
     if (!(v == v)) v = -INFINITY;
     if (f.V_out && c < count) f.V_out[c] = v;
     if (!f.blk_v && !f.rec) return;
@@ -131,12 +140,13 @@ __global__ void __launch_bounds__(FINISH_ROWS) finish_rows_kernel(FinishRowsArgs
     }
     for (int t = tid; t < f.K; t += FINISH_ROWS) f.rec_br[(size_t)blockIdx.x * f.K + t] = f.br[(size_t)t * count + bc];
     for (int i = tid; i < f.m; i += FINISH_ROWS) f.rec_x[(size_t)blockIdx.x * f.m + i] = f.X[(size_t)bc * f.m + i];
+    FinishRec &rec = f.rec[blockIdx.x];
     if (tid == 0) {
-        FinishRec r;
-        r.value = bv; r.pad = 0; r.index = f.index_base + bc; r.ties = 0ull;
-        if (blockIdx.x == 0) { r.ties = *f.ties; *f.ties = 0ull; }
-        f.rec[blockIdx.x] = r;
+        rec.value = bv; rec.index = f.index_base + bc;
+        if (blockIdx.x == 0) { rec.ties = *f.ties; *f.ties = 0ull; }
     }
+    const Done d = { &rec.seq, f.seq };
+    signal_done(d, 0);
 }
 
 }  // namespace

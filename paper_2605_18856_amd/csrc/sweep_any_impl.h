@@ -27,6 +27,7 @@
 #pragma once
 #include "bsse_internal.h"
 #include "mfma_device.h"
+#include "done_device.h"
 #include <limits.h>
 
 namespace bsse {
@@ -704,6 +705,10 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
         }
     }
     if (o->a.tie_counter && lane == 0 && tie_count) atomicAdd(o->a.tie_counter, (unsigned long long)tie_count);
+    if (o->a.done.flag) {
+        const Done d = { o->a.done.flag, o->a.done.seq };
+        signal_done(d, blockIdx.y);
+    }
 }
 
 typedef void (*any_kernel_t)(AnyArgs);

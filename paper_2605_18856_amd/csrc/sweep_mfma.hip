@@ -25,6 +25,7 @@
 // payoffs.
 #include "bsse_internal.h"
 #include "mfma_device.h"
+#include "done_device.h"
 #include <limits.h>
 #include <stdlib.h>
 #include <string.h>
@@ -371,19 +372,22 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     unsigned valid32[NT];                     // bit c set iff candidate c of the tile exists
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) {
+        // (columns past the end repeat the last row: they behave like any other and are left out of
+        // every output; as rows of zeros they tied everywhere and sent their tile through the exact
+        // routine for every type -- 54 us instead of 11 for 1000 rows of m = n = 32, K = 16)
         const long long c = wave_base + ct * 32 + col;
         const bool ok = c < a.count;
         float vb[HALF_BASE];
-        const float *row = a.X + (ok ? c : 0) * (long long)m + h * HALF_BASE;
+        const float *row = a.X + (ok ? c : a.count - 1) * (long long)m + h * HALF_BASE;
         if (m == MP_BASE && HALF_BASE % 4 == 0 && ((uintptr_t)a.X & 15) == 0) {
 #pragma unroll
             for (int e = 0; e < HALF_BASE; e += 4) {
-                f32x4 q = ok ? *(const f32x4 *)(row + e) : f32x4{ 0, 0, 0, 0 };
+                const f32x4 q = *(const f32x4 *)(row + e);
                 vb[e] = q[0]; vb[e + 1] = q[1]; vb[e + 2] = q[2]; vb[e + 3] = q[3];
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < HALF_BASE; ++e) vb[e] = (ok && h * HALF_BASE + e < m) ? row[e] : 0.0f;
+            for (int e = 0; e < HALF_BASE; ++e) vb[e] = h * HALF_BASE + e < m ? row[e] : 0.0f;
         }
         if constexpr (TERMS == 1) {
             P::pack_x(vb, x[ct]);
@@ -574,13 +578,15 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 exact_type(ct, group, ti, t, gmax[ct], l, js);
             }
             V[ct] = fmaf(pt, l, V[ct]);
-            if (a.br_out) {
-                const long long c = wave_base + ct * 32 + col;
-                if (h == 0 && c < a.count) a.br_out[c * K + t] = js;
-            }
             if constexpr (SLICED) {
                 const long long c = wave_base + ct * 32 + col;
-                if (h == 0 && c < a.count) a.l_out[c * K + t] = l;
+                if (h == 0 && c < a.count) {
+                    a.l_out[c * a.l_sc + t * a.l_st] = l;
+                    if (a.br_out) a.br_out[c * a.br_sc + t * a.br_st] = js;
+                }
+            } else if (a.br_out) {
+                const long long c = wave_base + ct * 32 + col;
+                if (h == 0 && c < a.count) a.br_out[c * K + t] = js;
             }
         }
     };
@@ -692,7 +698,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 gmax[ct] = gm;
                 jstar[ct] = (int)(pair & 0xFFFFu);
                 const unsigned multi = (unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | tile_tie;
-                clean[ct] = (multi & valid32[ct]) == 0u && valid32[ct] == 0xFFFFFFFFu;   // wave-uniform
+                clean[ct] = multi == 0u;                                // wave-uniform
             }
             leader_part(group, ti, t, pt, at_lds, gmax, jstar, clean);
         });
@@ -784,6 +790,8 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
         }
     }
     if (a.tie_counter && lane == 0 && tie_count) atomicAdd(a.tie_counter, (unsigned long long)tie_count);
+    if constexpr (SLICED)
+        if (a.done.flag) signal_done(a.done, blockIdx.y);
 }
 
 
@@ -867,18 +875,18 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
             const long long c = wave_base + (ps * NT + ct) * 32 + col;
-            const bool ok = c < a.count;
+            const bool ok = c < a.count;                     // (past the end: the last row again)
             float vb[HALF_BASE];
-            const float *row = a.X + (ok ? c : 0) * (long long)m + h * HALF_BASE;
+            const float *row = a.X + (ok ? c : a.count - 1) * (long long)m + h * HALF_BASE;
             if (m == MP && HALF_BASE % 4 == 0 && ((uintptr_t)a.X & 15) == 0) {
 #pragma unroll
                 for (int e = 0; e < HALF_BASE; e += 4) {
-                    f32x4 q = ok ? *(const f32x4 *)(row + e) : f32x4{ 0, 0, 0, 0 };
+                    const f32x4 q = *(const f32x4 *)(row + e);
                     vb[e] = q[0]; vb[e + 1] = q[1]; vb[e + 2] = q[2]; vb[e + 3] = q[3];
                 }
             } else {
 #pragma unroll
-                for (int e = 0; e < HALF_BASE; ++e) vb[e] = (ok && h * HALF_BASE + e < m) ? row[e] : 0.0f;
+                for (int e = 0; e < HALF_BASE; ++e) vb[e] = h * HALF_BASE + e < m ? row[e] : 0.0f;
             }
             P::pack_x(vb, x[ps][ct]);
             valid32[ps][ct] = (unsigned)__builtin_amdgcn_ballot_w64(ok);
@@ -1035,7 +1043,7 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
                                                     : ((unsigned)js[ct] < (unsigned)N ? (unsigned)js[ct] : 0u);
             P::gather_half(Lt + (unsigned)((jg * G.ats + h * HALF) * sizeof(T)), cr[ct]);
             const unsigned multi = (unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | tile_tie[ct];
-            clean[ct] = (multi & vp[ct]) == 0u && vp[ct] == 0xFFFFFFFFu;   // wave-uniform
+            clean[ct] = multi == 0u;                         // wave-uniform
             __builtin_amdgcn_sched_barrier(0);
         }
         // stage 4: leader payoffs (each lane its half, the partner the other) and the value
@@ -1132,20 +1140,6 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
         }
     }
     if (a.tie_counter && lane == 0 && tie_count) atomicAdd(a.tie_counter, (unsigned long long)tie_count);
-}
-
-// Second step of the type-sliced evaluation: V[c] = sum_t prior[t] * l[c][t], one lane per row,
-// accumulated in type order with the fused multiply-add of the unsliced kernel, so the value is
-// the same fp32 number.
-__global__ void finish_value_kernel(const float *__restrict__ prior, const float *__restrict__ l,
-                                    int K, long long count, float *__restrict__ V_out)
-{
-    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= count) return;
-    float v = 0.0f;
-    for (int t = 0; t < K; ++t) v = fmaf(prior[t], l[c * K + t], v);
-    if (!(v == v)) v = -INFINITY;
-    V_out[c] = v;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1247,14 +1241,43 @@ const char *mfma_variant_name(int variant)
 }
 
 bool mfma_is_small(int variant) { return variant == kSmallVariant; }
-bool mfma_slices_types(int variant) { return variant >= 0 && variant < kNumVariants; }
 
 long long mfma_num_blocks(int variant, long long count)
 {
     if (variant == kSmallVariant) return small_num_blocks(count);
     const Variant &v = kVariants[variant];
-    const long long per = (long long)v.nt * 32 * v.waves * (v.wide ? 2 : 1);     // candidates per workgroup record     // candidates per workgroup record
+    const long long per = (long long)v.nt * 32 * v.waves * (v.wide ? 2 : 1);     // candidates per workgroup record
     return (count + per - 1) / per;
+}
+
+// Stages per type slice of a sliced launch: 32 candidates per wavefront, whole groups per slice; few
+// rows are cut into about 256 slices, many rows fill the chip by themselves.
+static int stages_per_slice(const Variant &v, int K, long long count)
+{
+    const int nstages = (row_tiles_for(v, K) + v.stage_tiles - 1) / v.stage_tiles;
+    const long long per = 32LL * v.waves, blocks = (count + per - 1) / per;
+    const int slices = blocks >= 256 ? 1 : (int)(256 / blocks);
+    const int spg = v.geo.tpg > v.stage_tiles ? v.geo.tpg / v.stage_tiles : 1;       // stages per group
+    return ((nstages + slices - 1) / slices + spg - 1) / spg * spg;
+}
+
+int mfma_slices(const GameView &g, long long count)
+{
+    if (g.variant < 0 || g.variant >= kNumVariants) return 1;
+    const Variant &v = kVariants[g.variant];
+    const int nstages = (row_tiles_for(v, g.K) + v.stage_tiles - 1) / v.stage_tiles;
+    const int sps = stages_per_slice(v, g.K, count);
+    return (nstages + sps - 1) / sps;
+}
+
+// A workgroup of the unsliced kernel walks every type, whatever the number of rows: with fewer of them
+// than half the compute units, the same rows spread over types (and, on the wide kernel, over twice or
+// four times as many workgroups) finish sooner, although one candidate tile per wavefront reads every
+// fragment for 32 candidates only.
+bool mfma_few_rows(const GameView &g, long long count)
+{
+    if (g.variant < 0 || g.variant >= kNumVariants || mfma_num_blocks(g.variant, count) > 128) return false;
+    return kVariants[g.variant].wide || mfma_slices(g, count) > 1;
 }
 
 // Once per game, on the game's device: kernels whose two stage buffers exceed the default 48 KiB of
@@ -1297,21 +1320,14 @@ hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t 
             hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(v->waves * 64), lds, s, g, a, tiles);
         return hipGetLastError();
     }
-    // type-sliced evaluation: 32 candidates per wavefront, whole groups per slice; few rows are
-    // cut into about 256 slices, many rows fill the chip by themselves
+    // type-sliced evaluation
     const long long per = 32LL * v->waves, blocks = (a.count + per - 1) / per;
-    if (a.blk_v || blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    const int kSlices = blocks >= 256 ? 1 : (int)(256 / blocks);
-    const int spg = v->geo.tpg > v->stage_tiles ? v->geo.tpg / v->stage_tiles : 1;   // stages per group
+    if (a.blk_v || a.V_out || blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     SweepArgs b = a;
-    b.slice_stages = ((nstages + kSlices - 1) / kSlices + spg - 1) / spg * spg;
+    b.slice_stages = stages_per_slice(*v, g.K, a.count);
     const int slices = (nstages + b.slice_stages - 1) / b.slice_stages;
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, (unsigned)slices), dim3(v->waves * 64), lds, s, g, b,
                        tiles);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !a.V_out) return e;
-    hipLaunchKernelGGL(finish_value_kernel, dim3((unsigned)((a.count + 63) / 64)), dim3(64), 0, s,
-                       g.prior, a.l_out, g.K, a.count, a.V_out);
     return hipGetLastError();
 }
 

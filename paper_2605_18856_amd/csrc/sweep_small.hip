@@ -28,6 +28,7 @@
 #include "bsse_internal.h"
 #include "mfma_device.h"
 #include "gen_device.h"
+#include "done_device.h"
 #include <limits.h>
 #include <stdlib.h>
 #include <string.h>
@@ -44,6 +45,7 @@ constexpr int SM_M = 8, SM_N = 8;
 constexpr int SM_WAVES = 4;
 constexpr int SM_NT = 2;               // 32-candidate tiles per wavefront per iteration
 constexpr int SM_MAX_TILES = 4;
+constexpr int SM_SLOTS = 256 * 5;      // the largest grid launch_sweep_small uses
 #ifndef BSSE_SM_RING
 #define BSSE_SM_RING 2
 #endif
@@ -402,11 +404,13 @@ sweep_small_gen_kernel(GameView g, SweepArgs a)
 }
 
 // Steps 5-6 at the end of a sweep: fold the slots of the current sweep (greatest value, lowest
-// index among equals) and report the winner: value, index, tie count and row.  Its best
-// responses come from a one-row evaluation launch behind this kernel (launch_finish_small): the
-// same instruction sequence on the same row, hence the same decisions.
+// index among equals) and report the winner: value, index, tie count and row, and its best
+// responses, by evaluating the row again in the same workgroup (the same instruction sequence on the
+// same row, hence the same decisions).  One launch: a second one for the evaluation cost 9 us of a
+// 52 us call (2^20 rows, K = 4).  Bound by three dependent round trips to memory.
+template <int TILES>
 __global__ void __launch_bounds__(SM_WAVES * 64)
-small_finish_kernel(int K, FinishArgs f)
+small_finish_kernel(GameView g, FinishArgs f)
 {
     __shared__ float sv[SM_WAVES];
     __shared__ long long si[SM_WAVES];
@@ -415,14 +419,22 @@ small_finish_kernel(int K, FinishArgs f)
     float bv = -INFINITY;
     long long bi = LLONG_MAX;
     int bb = -1;
+    RunningBest r{};
+    if (tid == 0) {
+        if (!f.first) r = *f.run;
+        r.ties += *f.tie_counter;
+    }
     // (value, epoch and index are the first sixteen bytes of a slot: one load each, all of a
     // thread's loads independent of one another)
-    for (int b = tid; b < f.nslots; b += SM_WAVES * 64) {
-        const uint4 head = *reinterpret_cast<const uint4 *>(&f.slots[b]);
-        const float v = __uint_as_float(head.x);
-        const long long i = (long long)(((unsigned long long)head.w << 32) | head.z);
-        if (head.y == f.epoch && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; bb = b; }
-    }
+    for (int set = 0; set < 3; ++set)
+#pragma unroll 4
+        for (int b = tid; b < f.used[set]; b += SM_WAVES * 64) {
+            const int s = set * SM_SLOTS + b;
+            const uint4 head = *reinterpret_cast<const uint4 *>(&f.slots[s]);
+            const float v = __uint_as_float(head.x);
+            const long long i = (long long)(((unsigned long long)head.w << 32) | head.z);
+            if (head.y == f.epoch && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; bb = s; }
+        }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         const float ov = __shfl_xor(bv, d, 64);
@@ -432,21 +444,37 @@ small_finish_kernel(int K, FinishArgs f)
     }
     if (lane == 0) { sv[wave] = bv; si[wave] = bi; sb[wave] = bb; }
     __syncthreads();
-    if (tid != 0) return;
+    bv = sv[0]; bi = si[0]; bb = sb[0];
     for (int w = 1; w < SM_WAVES; ++w)
         if (sv[w] > bv || (sv[w] == bv && si[w] < bi)) { bv = sv[w]; bi = si[w]; bb = sb[w]; }
-    RunningBest r = *f.run;
-    if (f.first) r.ties = 0ull;
-    r.ties += *f.tie_counter;
-    *f.tie_counter = 0ull;                       // counted; later chunks of the sweep add to zero
-    r.has = bb >= 0 ? 1 : 0;
-    r.value = bb >= 0 ? bv : 0.0f;
-    r.index = bb >= 0 ? bi : -1;
-    *f.run = r;
-    *f.run_host = r;
-    if (bb < 0) return;
-    *f.win_v = bv;
-    for (int i = 0; i < SM_M; ++i) f.best_x[i] = f.slots[bb].x[i];
+    // with no winner the row is whatever slot 0 holds and nothing of it is reported
+    const float *x = f.slots[bb >= 0 ? bb : 0].x;
+    if (tid < SM_M) f.x_host[tid] = x[tid];
+    if (tid == 0) {
+        *f.tie_counter = 0ull;                   // counted; later chunks of the sweep add to zero
+        r.has = bb >= 0 ? 1 : 0;
+        r.value = bb >= 0 ? bv : 0.0f;
+        r.index = bb >= 0 ? bi : -1;
+        *f.run = r;
+        *f.run_host = r;
+        *f.win_v = r.value;
+    }
+    SweepArgs ev{};
+    ev.X = x; ev.count = 1; ev.br_out = f.win_br;
+    small_body<TILES, true, false>(g, ev, 0, 1);
+    if (f.done.flag) signal_done(f.done, 0);
+}
+
+typedef void (*small_finish_t)(GameView, FinishArgs);
+small_finish_t small_finish_for(int K)
+{
+    switch (K / 4) {
+    case 1: return small_finish_kernel<1>;
+    case 2: return small_finish_kernel<2>;
+    case 3: return small_finish_kernel<3>;
+    case 4: return small_finish_kernel<4>;
+    }
+    return nullptr;
 }
 
 typedef void (*small_kernel_t)(GameView, SweepArgs);
@@ -507,21 +535,13 @@ hipError_t launch_sweep_small(const GameView &g, const SweepArgs &a, hipStream_t
     return hipGetLastError();
 }
 
-int small_num_slots() { return 256 * 5; }          // the largest grid launch_sweep_small uses
+int small_num_slots() { return SM_SLOTS; }
 
 hipError_t launch_finish_small(const GameView &g, const FinishArgs &f, hipStream_t s)
 {
-    hipLaunchKernelGGL(small_finish_kernel, dim3(1), dim3(SM_WAVES * 64), 0, s, g.K, f);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // the winner's best responses: its row (left in best_x by the fold) through the evaluation
-    // form of the sweep kernel; with no winner the row is whatever the buffer holds and the
-    // responses are not reported
-    SweepArgs ev{};
-    ev.X = f.best_x; ev.count = 1; ev.br_out = f.win_br;
-    small_kernel_t k = small_kernel_for(g.K, true);
+    const small_finish_t k = small_finish_for(g.K);
     if (!k) return hipErrorNotSupported;
-    hipLaunchKernelGGL(k, dim3(1), dim3(SM_WAVES * 64), 0, s, g, ev);
+    hipLaunchKernelGGL(k, dim3(1), dim3(SM_WAVES * 64), 0, s, g, f);
     return hipGetLastError();
 }
 
