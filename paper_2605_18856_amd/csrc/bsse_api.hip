@@ -86,9 +86,16 @@ struct PriorScratch {
 
 // Device scratch of the top-k entry point: kept by the handle and grown on demand.
 struct TopkScratch {
-    void *p[9] = { nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr };
-    size_t cap[9] = { 0, 0, 0, 0, 0, 0, 0, 0, 0 };
-    void release() { for (void *q : p) (void)hipFree(q); }
+    float *V = nullptr, *rows = nullptr;
+    unsigned long long *heads = nullptr;
+    size_t cap_V = 0, cap_rows = 0, cap_heads = 0;
+    unsigned char *host = nullptr;   // pinned: the records
+    size_t cap_host = 0;
+    void release()
+    {
+        if (host) (void)hipHostFree(host);
+        (void)hipFree(V); (void)hipFree(rows); (void)hipFree(heads);
+    }
 };
 
 // Device scratch of the streamed sweep: one record per workgroup of a chunk, the running best, the
@@ -389,6 +396,33 @@ bsse_status wait_words(bsse_game *g, const unsigned *word, int n, size_t stride)
     return BSSE_OK;
 }
 bsse_status wait_flags(bsse_game *g, int n) { return wait_words(g, g->h_flag, n, sizeof(unsigned)); }
+
+// Best responses [rows][K] of a few rows into pinned memory, as the last launch of a call (`last`: it
+// sets completion flags, *flags of them; 0 when there would be too many).
+bsse_status launch_winners(bsse_game *g, const float *X, long long rows, int32_t *br, bool last, int *flags)
+{
+    SweepArgs a{};
+    a.X = X; a.count = rows;
+    a.br_out = br; a.br_sc = g->K; a.br_st = 1;
+    const long long blocks = on_any(g) ? any_row_blocks(g->view, rows)
+                             : cuts_types(g) ? mfma_row_blocks(g->view, rows) : sweep_blocks(g, rows);
+    *flags = last && blocks <= MAX_FLAGS ? (int)blocks : 0;
+    if (*flags) a.done = new_done(g);
+    if (!cuts_types(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
+    if (!on_any(g)) {                            // (the general kernel is cut only when asked for leader payoffs)
+        bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)rows * g->K * sizeof(float));
+        if (st != BSSE_OK) return st;
+        a.l_out = g->row_l; a.l_sc = g->K; a.l_st = 1;
+    }
+    HIP_TRY(launch_rows(g, a, g->stream));
+    return BSSE_OK;
+}
+bsse_status wait_winners(bsse_game *g, int flags)
+{
+    if (flags) return wait_flags(g, flags);
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    return BSSE_OK;
+}
 
 bsse_status take_event(bsse_game *g, hipEvent_t *e)
 {
@@ -1508,16 +1542,34 @@ extern "C" bsse_status bsse_sweep_priors(bsse_game *g, const float *candidates_d
 // --------------------------------------------------------------------------------- top-k
 namespace {
 
-struct DevView {                     // a block of handle-owned scratch
-    void *p = nullptr;
-    template <typename T> T *as() const { return reinterpret_cast<T *>(p); }
-};
-
 struct DevBuf {                      // device scratch of one call, released on every exit path
     void *p = nullptr;
     ~DevBuf() { (void)hipFree(p); }
     template <typename T> T *as() const { return reinterpret_cast<T *>(p); }
 };
+
+// Evaluation of `sets` sets of `count` rows each (one behind the other at X) and the k best of every
+// set: values, indices, best responses and (rows_host) rows into pinned memory.  `flags` as in
+// launch_winners.
+bsse_status enqueue_topk(bsse_game *g, const float *X, long long count, int sets, int k, long long index_base,
+                         float *val, long long *idx, int32_t *br, float *rows_host, bool last, int *flags)
+{
+    TopkScratch &w = g->topk;
+    const int m = g->m;
+    const long long total = count * sets;
+    bsse_status st;
+    if ((st = grow_device(g, (void **)&w.V, &w.cap_V, (size_t)total * sizeof(float))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.heads, &w.cap_heads, topk_heads_bytes(count, sets))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.rows, &w.cap_rows, (size_t)sets * k * m * sizeof(float))) != BSSE_OK) return st;
+    SweepArgs a{};
+    a.X = X; a.count = total; a.V_out = w.V;
+    if ((st = launch_eval(g, a)) != BSSE_OK) return st;
+    TopkArgs t{};
+    t.V = w.V; t.heads = w.heads; t.X = X; t.count = (unsigned)count; t.k = k; t.m = m; t.index_base = index_base;
+    t.val = val; t.idx = idx; t.rows = w.rows; t.rows_host = rows_host;
+    HIP_TRY(launch_topk(t, sets, g->stream));
+    return launch_winners(g, w.rows, (long long)sets * k, br, last, flags);
+}
 
 }  // namespace
 
@@ -1534,80 +1586,38 @@ extern "C" bsse_status bsse_sweep_topk(bsse_game *g, const float *candidates_dev
     if (count == 0) { *found_out = 0; return BSSE_OK; }
     DeviceGuard dg(g->device);
     if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
-    const int m = g->m, K = g->K;
+    const int K = g->K;
 
+    // chunks of at most 2^26 candidates, each with its own k best; the host merges them
     const long long chunk = count < (1LL << 26) ? count : (1LL << 26);
     const long long nchunks = (count + chunk - 1) / chunk;
-    const long long rec0 = topk_level_blocks(chunk) * k;          // records after the first level
-    // scratch of the handle, grown on demand (allocating and freeing per call costs more than the call)
-    DevView V, av, ai, bv, bi, wv, wi, rows, br;
-    {
-        DevView *views[9] = { &V, &av, &ai, &bv, &bi, &wv, &wi, &rows, &br };
-        const size_t need[9] = { (size_t)chunk * sizeof(float), (size_t)rec0 * sizeof(float),
-                                 (size_t)rec0 * sizeof(long long), (size_t)rec0 * sizeof(float),
-                                 (size_t)rec0 * sizeof(long long), (size_t)(nchunks + 1) * k * sizeof(float),
-                                 (size_t)(nchunks + 1) * k * sizeof(long long), (size_t)k * m * sizeof(float),
-                                 (size_t)k * K * sizeof(int32_t) };
-        for (int q = 0; q < 9; ++q) {
-            if (need[q] > g->topk.cap[q]) {
-                HIP_TRY(hipStreamSynchronize(g->stream));   // nothing enqueued may still use the old block
-                (void)hipFree(g->topk.p[q]);
-                g->topk.p[q] = nullptr; g->topk.cap[q] = 0;
-                HIP_TRY(hipMalloc(&g->topk.p[q], need[q]));
-                g->topk.cap[q] = need[q];
-            }
-            views[q]->p = g->topk.p[q];
-        }
-    }
-
-    // levels from `n` (value, index) records in (sv, si) down to k records, written to (dv, di)
-    auto reduce_to = [&](const float *sv, const long long *si, long long n, long long index_base,
-                         float *dv, long long *di) -> bsse_status {
-        float *pv[2] = { av.as<float>(), bv.as<float>() };
-        long long *pi[2] = { ai.as<long long>(), bi.as<long long>() };
-        int cur = 0;
-        for (;;) {
-            const long long nb = topk_level_blocks(n);
-            float *ov = nb == 1 ? dv : pv[cur];
-            long long *oi = nb == 1 ? di : pi[cur];
-            HIP_TRY(launch_topk_level(sv, si, n, index_base, k, ov, oi, g->stream));
-            if (nb == 1) return BSSE_OK;
-            sv = ov; si = oi; n = nb * k; cur ^= 1;
-        }
-    };
+    const size_t recs = (size_t)nchunks * k;
+    const size_t off_idx = 0, off_val = recs * sizeof(long long), off_br = off_val + recs * sizeof(float);
+    if ((st = grow_pinned(g, (void **)&g->topk.host, &g->topk.cap_host, off_br + recs * K * sizeof(int32_t))) != BSSE_OK) return st;
+    long long *hi = reinterpret_cast<long long *>(g->topk.host + off_idx);
+    float *hv = reinterpret_cast<float *>(g->topk.host + off_val);
+    int32_t *hb = reinterpret_cast<int32_t *>(g->topk.host + off_br);
+    int flags = 0;
+    struct Part { long long at, end; };                  // what is left of a chunk's records
+    std::vector<Part> part;
+    try { part.resize((size_t)nchunks); } catch (...) { return fail(BSSE_ENOMEM, "host allocation failed"); }
     for (long long c = 0; c < nchunks; ++c) {
         const long long base = c * chunk, n = count - base < chunk ? count - base : chunk;
-        SweepArgs a{};
-        a.X = candidates_dev + base * m; a.count = n; a.index_base = 0; a.V_out = V.as<float>();
-        if ((st = launch_eval(g, a)) != BSSE_OK) return st;
-        if ((st = reduce_to(V.as<float>(), nullptr, n, base, wv.as<float>() + c * k,
-                            wi.as<long long>() + c * k)) != BSSE_OK) return st;
+        const int kk = n < k ? (int)n : k;
+        part[(size_t)c] = { c * k, c * k + kk };
+        if ((st = enqueue_topk(g, candidates_dev + base * g->m, n, 1, kk, base, hv + c * k, hi + c * k, hb + c * k * K,
+                               nullptr, c + 1 == nchunks, &flags)) != BSSE_OK) return st;
     }
-    float *fv = wv.as<float>();
-    long long *fi = wi.as<long long>();
-    if (nchunks > 1) {
-        fv += nchunks * k; fi += nchunks * k;
-        if ((st = reduce_to(wv.as<float>(), wi.as<long long>(), nchunks * k, 0, fv, fi)) != BSSE_OK) return st;
+    if ((st = wait_winners(g, flags)) != BSSE_OK) return st;
+    const int found = count < k ? (int)count : k;
+    for (int r = 0; r < found; ++r) {
+        Part *best = nullptr;                            // (an earlier chunk's index is the lower one)
+        for (Part &p : part)
+            if (p.at < p.end && (!best || hv[p.at] > hv[best->at])) best = &p;
+        const long long e = best->at++;
+        values_out[r] = (double)hv[e]; indices_out[r] = (int64_t)hi[e];
+        if (best_response_out) memcpy(best_response_out + (size_t)r * K, hb + e * K, (size_t)K * sizeof(int32_t));
     }
-    // best responses of the survivors: their rows, evaluated once more with per-candidate outputs
-    HIP_TRY(launch_gather_indexed_rows(candidates_dev, fi, k, m, rows.as<float>(), g->stream));
-    {
-        SweepArgs a{};
-        a.X = rows.as<float>(); a.count = k; a.index_base = 0; a.br_out = br.as<int32_t>();
-        if ((st = launch_eval(g, a)) != BSSE_OK) return st;
-    }
-    std::vector<float> hv((size_t)k);
-    std::vector<long long> hi((size_t)k);
-    std::vector<int32_t> hb(best_response_out ? (size_t)k * K : 0);
-    HIP_TRY(hipMemcpyAsync(hv.data(), fv, (size_t)k * sizeof(float), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipMemcpyAsync(hi.data(), fi, (size_t)k * sizeof(long long), hipMemcpyDeviceToHost, g->stream));
-    if (best_response_out)
-        HIP_TRY(hipMemcpyAsync(hb.data(), br.p, hb.size() * sizeof(int32_t), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipStreamSynchronize(g->stream));
-    int found = 0;
-    while (found < k && hi[found] != LLONG_MAX) ++found;
-    for (int r = 0; r < found; ++r) { values_out[r] = (double)hv[r]; indices_out[r] = (int64_t)hi[r]; }
-    if (best_response_out) memcpy(best_response_out, hb.data(), (size_t)found * K * sizeof(int32_t));
     *found_out = found;
     return BSSE_OK;
 }

@@ -108,7 +108,7 @@ struct SweepArgs {
     // Any-shape kernel and sliced instantiation of the general one: l_out / br_out element (c, t) sits
     // at c * _sc + t * _st.
     long long l_sc, l_st, br_sc, br_st;
-    Done done;               // launches of one candidate block: a flag per workgroup (by blockIdx.y)
+    Done done;               // evaluation mode: a flag per workgroup (blockIdx.y * gridDim.x + blockIdx.x)
     // Any-shape kernel, one row (count == 1): with fold_n > 0 the row is the winner of fold_n
     // workgroup records of an earlier launch over the rows X; the winner and the tie counter's value
     // (which is cleared) go to fold_run.  row_host (nullable) receives the row evaluated.
@@ -153,6 +153,7 @@ hipError_t mfma_prepare(int variant, int K);   // per game, on its device, befor
 // Type slices of a launch with l_out; whether `count` candidates are so few that a sweep or an
 // evaluation is a launch with l_out and then launch_finish_rows.
 int mfma_slices(const GameView &g, long long count);
+long long mfma_row_blocks(const GameView &g, long long count);      // workgroups of such a launch
 bool mfma_few_rows(const GameView &g, long long count);
 bool mfma_is_small(int variant);       // the small-game kernel: launch_finish_small applies
 // Host-side packing of payoffs for a variant; returns malloc'ed buffers (caller frees).
@@ -180,6 +181,7 @@ const char *any_name(const AnyGeo &q);
 long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an unsliced launch
 // Type slices that `count` candidates should be cut into (1: none).
 int any_slices(const GameView &g, long long count);
+long long any_row_blocks(const GameView &g, long long count);       // workgroups of a launch cut like that
 // slices > 1: l_out (and br_out) only; the value comes from launch_finish_rows.
 hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int slices, hipStream_t s);
 
@@ -228,15 +230,22 @@ hipError_t launch_prior_batch(const float *L, long long count, long long index_b
 hipError_t launch_gather_rows(const float *X, const PriorBest *run, int P, int m, float *rows,
                               hipStream_t s);
 
-// Top-k reduction (see topk.hip): one level turns `count` (value, index) elements (idx null: the
-// index of element e is index_base + e) into k records per workgroup, best first; an index of
-// LLONG_MAX marks an empty record.  topk_level_blocks(count) workgroups.
-long long topk_level_blocks(long long count);
-hipError_t launch_topk_level(const float *vals, const long long *idx, long long count,
-                             long long index_base, int k, float *out_v, long long *out_i,
-                             hipStream_t s);
-hipError_t launch_gather_indexed_rows(const float *X, const long long *idx, int rows, int m,
-                                      float *out, hipStream_t s);
+// Top-k reduction (see topk.hip) of `sets` sets of `count` values each, one behind the other, over the
+// rows X in the same order: the k <= min(256, count) best of each set, best first.
+struct TopkArgs {
+    const float *V;
+    unsigned long long *heads;   // workspace of topk_heads_bytes (nullptr when that is 0)
+    const float *X;
+    unsigned count;
+    int k, m;
+    long long index_base;    // global index of element 0 of a set
+    float *val;              // [sets][k]
+    long long *idx;          // [sets][k]
+    float *rows;             // [sets][k][m] their rows
+    float *rows_host;        // the same once more, nullable
+};
+size_t topk_heads_bytes(long long count, int sets);
+hipError_t launch_topk(const TopkArgs &args, int sets, hipStream_t s);
 
 // Host code: the linear program of one pure follower profile (see profile_lp.hip).  Returns 0 with
 // x_out[m] (on the simplex) and *value_out, 1 when the profile is a best response nowhere, 2 when

@@ -263,6 +263,12 @@ int any_slices(const GameView &g, long long count)
     return (g.any.units + per - 1) / per;
 }
 
+long long any_row_blocks(const GameView &g, long long count)
+{
+    const int slices = any_slices(g, count);
+    return slices > 1 ? (count + rows_per_block(g.any) - 1) / rows_per_block(g.any) * slices : any_num_blocks(g, count);
+}
+
 hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int slices, hipStream_t s)
 {
     if (a.count <= 0) return hipSuccess;

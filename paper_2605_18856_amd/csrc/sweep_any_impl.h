@@ -707,7 +707,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     if (o->a.tie_counter && lane == 0 && tie_count) atomicAdd(o->a.tie_counter, (unsigned long long)tie_count);
     if (o->a.done.flag) {
         const Done d = { o->a.done.flag, o->a.done.seq };
-        signal_done(d, blockIdx.y);
+        signal_done(d, blockIdx.y * gridDim.x + blockIdx.x);
     }
 }
 

@@ -791,7 +791,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     }
     if (a.tie_counter && lane == 0 && tie_count) atomicAdd(a.tie_counter, (unsigned long long)tie_count);
     if constexpr (SLICED)
-        if (a.done.flag) signal_done(a.done, blockIdx.y);
+        if (a.done.flag) signal_done(a.done, blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 
@@ -1268,6 +1268,12 @@ int mfma_slices(const GameView &g, long long count)
     const int nstages = (row_tiles_for(v, g.K) + v.stage_tiles - 1) / v.stage_tiles;
     const int sps = stages_per_slice(v, g.K, count);
     return (nstages + sps - 1) / sps;
+}
+
+long long mfma_row_blocks(const GameView &g, long long count)
+{
+    const long long per = 32LL * kVariants[g.variant].waves;
+    return (count + per - 1) / per * mfma_slices(g, count);
 }
 
 // A workgroup of the unsliced kernel walks every type, whatever the number of rows: with fewer of them

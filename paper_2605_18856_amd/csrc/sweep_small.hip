@@ -393,6 +393,7 @@ __global__ void __launch_bounds__(SM_WAVES * 64, TILES == 1 ? 4 : 3)
 sweep_small_kernel(GameView g, SweepArgs a)
 {
     small_body<TILES, EVAL, false>(g, a, blockIdx.x, gridDim.x);
+    if (EVAL && a.done.flag) signal_done(a.done, blockIdx.x);
 }
 
 // The sweep over rows generated in registers (step 1 fused in): no candidate ever reaches memory.

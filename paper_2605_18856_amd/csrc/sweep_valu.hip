@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(WG) sweep_valu_kernel(GameView g, SweepArgs a)
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) ties += __shfl_xor(ties, d, 64);
     if (lane == 0 && ties && a.tie_counter) atomicAdd(a.tie_counter, (unsigned long long)ties);
-    if (EVAL && a.done.flag) signal_done(a.done, 0);
+    if (EVAL && a.done.flag) signal_done(a.done, blockIdx.x);
 }
 
 }  // namespace

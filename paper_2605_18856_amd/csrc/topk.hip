@@ -1,13 +1,21 @@
 // Top-k reduction over candidates: the k best (value, index) pairs in the order "greater value
 // first, lower index among equal values" -- the order whose first element is the sweep's winner.
 //
-// One kernel, applied level by level.  A workgroup takes a slice of TK_SLICE elements into
-// registers (TK_E per thread) and extracts its k best in k rounds: every thread keeps the best of
-// its elements not yet taken, a shuffle/LDS reduction finds the workgroup's best (one barrier per
-// round: the wavefronts' winners are double-buffered and every thread folds them itself), and only
-// the owning thread rescans its registers.  The k records of every workgroup form the input of the next
-// level (now with explicit indices), until one workgroup is left.  Nothing is atomic, so the
-// result does not depend on scheduling.
+// That order is the order of 64-bit keys (value as an ordered integer, then the complement of the
+// index), all of them different, so selection is by threshold: no tie needs a rule of its own and
+// nothing depends on scheduling.  Two launches:
+//   * heads: one wavefront per block of TK_BLOCK elements leaves the block's greatest key;
+//   * select: one workgroup per set.  A threshold that at least k heads reach bounds the k-th key
+//     from below, and every element that reaches it lies in one of the blocks whose head does: those
+//     blocks (about k of them) are read again, what reaches the threshold is gathered in LDS and ranked
+//     by counting.
+// Thresholds come from a histogram of 2048 bins over the range of the keys, narrowed to the bin of
+// the k-th key while too many keys reach it; the keys being different, the range runs out first.
+// Values in sorted or clustered order only cost further passes.
+//
+// Bound by latency: the passes over memory are short, and each is followed by a few barriers.  k = 64
+// of 2^20 values: heads 4 us, select 13 us; extracting k maxima one after the other in three
+// levels of workgroups took 256 us.
 #include "bsse_internal.h"
 #include <limits.h>
 
@@ -15,111 +23,249 @@ namespace bsse {
 
 namespace {
 
-constexpr int TK_THREADS = 256;
-constexpr int TK_E = 8;
-constexpr int TK_SLICE = TK_THREADS * TK_E;
+typedef unsigned long long u64;
 
-__device__ __forceinline__ bool tk_better(float v, long long i, float bv, long long bi)
+constexpr int TK_BLOCK = 256;            // elements behind one head
+constexpr int TK_T = 1024;               // threads of a select workgroup
+constexpr int TK_BINS = 2 * TK_T;
+constexpr int TK_LIST = 512;             // blocks that can be listed (>= 256, the greatest k, and some)
+constexpr int TK_CAND = 4096;            // keys LDS holds
+constexpr int TK_RANK = 512;             // keys that are ranked by counting (>= 256)
+
+// index: below 2^32.  A value that is not a number counts as minus infinity, and -0 as 0.
+__device__ __forceinline__ u64 tk_key(float v, unsigned index)
 {
-    return v > bv || (v == bv && i < bi);
+    if (!(v == v)) v = -INFINITY;
+    if (v == 0.0f) v = 0.0f;
+    const unsigned b = __float_as_uint(v);
+    const unsigned o = (b & 0x80000000u) ? ~b : b | 0x80000000u;
+    return ((u64)o << 32) | (0xFFFFFFFFu - index);
+}
+__device__ __forceinline__ float tk_value(u64 key)
+{
+    const unsigned o = (unsigned)(key >> 32);
+    return __uint_as_float((o & 0x80000000u) ? o & 0x7FFFFFFFu : ~o);
+}
+__device__ __forceinline__ unsigned tk_index(u64 key) { return 0xFFFFFFFFu - (unsigned)key; }
+
+__device__ __forceinline__ u64 tk_max(u64 a, u64 b) { return a > b ? a : b; }
+__device__ __forceinline__ u64 tk_min(u64 a, u64 b) { return a < b ? a : b; }
+
+// heads[set][nh] of the sets of `count` values at V + set * count
+__global__ void __launch_bounds__(256)
+topk_heads_kernel(const float *__restrict__ V, unsigned count, unsigned nh, u64 *__restrict__ heads)
+{
+    const unsigned lane = threadIdx.x & 63, b = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (b >= nh) return;                                 // whole wavefront
+    const float *v = V + (size_t)blockIdx.y * count;
+    u64 best = 0;
+#pragma unroll
+    for (unsigned q = 0; q < TK_BLOCK / 64; ++q) {
+        const unsigned i = b * TK_BLOCK + q * 64 + lane;
+        if (i < count) best = tk_max(best, tk_key(v[i], i));
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) best = tk_max(best, __shfl_xor(best, d, 64));
+    if (lane == 0) heads[(size_t)blockIdx.y * nh + b] = best;
 }
 
-// vals[count]; idx[count] or null (then the index of element e is index_base + e).  An index of
-// LLONG_MAX marks an empty record.  out_v / out_i: k records per workgroup, best first.
-__global__ void __launch_bounds__(TK_THREADS)
-topk_level_kernel(const float *__restrict__ vals, const long long *__restrict__ idx, long long count,
-                  long long index_base, int k, float *__restrict__ out_v, long long *__restrict__ out_i)
-{
-    // per-wavefront winners of a round, double-buffered by round parity: one barrier per round
-    __shared__ float sv[2][TK_THREADS / 64];
-    __shared__ long long si[2][TK_THREADS / 64];
+struct TkShared {
+    unsigned hist[TK_BINS];
+    u64 cand[TK_CAND];
+    unsigned list[TK_LIST];
+    unsigned wsum[TK_T / 64];
+    u64 wmin[TK_T / 64], wmax[TK_T / 64];
+    u64 lo;
+    unsigned total, above, n, nlist;
+};
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const long long base = (long long)blockIdx.x * TK_SLICE;
-    float v[TK_E];
-    long long ix[TK_E];
-    // element e of the thread sits at base + e * TK_THREADS + tid (coalesced loads)
+// Range of the keys that for_each(f) hands to f, over all threads (at least one key).
+template <typename E> __device__ __forceinline__ void tk_range(TkShared &s, E for_each, u64 &lo, u64 &hi)
+{
+    u64 mn = ~0ull, mx = 0;
+    for_each([&](u64 key) { mn = tk_min(mn, key); mx = tk_max(mx, key); });
 #pragma unroll
-    for (int e = 0; e < TK_E; ++e) {
-        const long long pos = base + (long long)e * TK_THREADS + tid;
-        const bool ok = pos < count;
-        float x = ok ? vals[pos] : -INFINITY;
-        if (!(x == x)) x = -INFINITY;
-        v[e] = x;
-        ix[e] = ok ? (idx ? idx[pos] : index_base + pos) : LLONG_MAX;
+    for (int d = 32; d >= 1; d >>= 1) {
+        mn = tk_min(mn, __shfl_xor(mn, d, 64));
+        mx = tk_max(mx, __shfl_xor(mx, d, 64));
     }
-    unsigned taken = 0u;
-    auto rescan = [&](float &bv, long long &bi, int &be) {
-        bv = -INFINITY; bi = LLONG_MAX; be = -1;
-#pragma unroll
-        for (int e = 0; e < TK_E; ++e) {
-            if ((taken >> e) & 1u) continue;
-            if (ix[e] != LLONG_MAX && (be < 0 || tk_better(v[e], ix[e], bv, bi))) { bv = v[e]; bi = ix[e]; be = e; }
-        }
-    };
-    // (an index of LLONG_MAX is "nothing": it never beats a record and any record beats it)
-    auto beats = [](float ov, long long oi, float bv, long long bi) {
-        return oi != LLONG_MAX && (bi == LLONG_MAX || tk_better(ov, oi, bv, bi));
-    };
-    float my_v; long long my_i; int my_e;
-    rescan(my_v, my_i, my_e);
-    for (int r = 0; r < k; ++r) {
-        float bv = my_v;
-        long long bi = my_i;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const float ov = __shfl_xor(bv, d, 64);
-            const long long oi = __shfl_xor(bi, d, 64);
-            if (beats(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-        }
-        const int buf = r & 1;
-        if (lane == 0) { sv[buf][wave] = bv; si[buf][wave] = bi; }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) { s.wmin[threadIdx.x >> 6] = mn; s.wmax[threadIdx.x >> 6] = mx; }
+    __syncthreads();
+    lo = s.wmin[0]; hi = s.wmax[0];
+    for (int w = 1; w < TK_T / 64; ++w) { lo = tk_min(lo, s.wmin[w]); hi = tk_max(hi, s.wmax[w]); }
+}
+
+// A threshold that at least k and at most cap (>= k) of the keys in lo..hi reach.  Every key for_each
+// hands over is at most hi, and at least k are in the range.
+template <typename E>
+__device__ __forceinline__ u64 tk_threshold(TkShared &s, E for_each, unsigned k, unsigned cap, u64 lo, u64 hi)
+{
+    const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned above = 0;                                  // keys above hi
+    for (;;) {
+        const int bits = 64 - __clzll((long long)(hi - lo)), shift = bits > 11 ? bits - 11 : 0;
+        s.hist[tid] = 0; s.hist[tid + TK_T] = 0;
         __syncthreads();
-        // every thread folds the wavefronts' winners itself: no second barrier to broadcast the result
-        bv = sv[buf][0]; bi = si[buf][0];
+        for_each([&](u64 key) { if (key >= lo && key <= hi) atomicAdd(&s.hist[(key - lo) >> shift], 1u); });
+        __syncthreads();
+        // from the top: thread t sums bins TK_BINS - 1 - 2t and the one below
+        const unsigned b = TK_BINS - 1 - 2 * tid, c1 = s.hist[b], c0 = s.hist[b - 1];
+        unsigned incl = c1 + c0;
 #pragma unroll
-        for (int w = 1; w < TK_THREADS / 64; ++w)
-            if (beats(sv[buf][w], si[buf][w], bv, bi)) { bv = sv[buf][w]; bi = si[buf][w]; }
-        if (tid == 0) {
-            out_v[(size_t)blockIdx.x * k + r] = bv;
-            out_i[(size_t)blockIdx.x * k + r] = bi;
+        for (int d = 1; d < 64; d <<= 1) {
+            const unsigned o = __shfl_up(incl, d, 64);
+            if (lane >= (unsigned)d) incl += o;
         }
-        if (bi != LLONG_MAX && my_e >= 0 && my_i == bi) {       // indices are distinct: one owner
-            taken |= 1u << my_e;
-            rescan(my_v, my_i, my_e);
+        if (lane == 63) s.wsum[wave] = incl;
+        __syncthreads();
+        for (unsigned w = 0; w < wave; ++w) incl += s.wsum[w];
+        const unsigned need = k - above, excl = incl - c1 - c0;
+        if (excl < need && need <= incl) {               // one thread
+            const bool first = excl + c1 >= need;
+            s.lo = lo + ((u64)(first ? b : b - 1) << shift);
+            s.above = above + excl + (first ? 0u : c1);
+            s.total = above + excl + c1 + (first ? 0u : c0);
         }
-        // (round r + 1 writes the other buffer; round r + 2 writes this one again, after everybody
-        // has passed the barrier of round r + 1 and so has finished reading it)
+        __syncthreads();
+        lo = s.lo;
+        if (s.total <= cap || shift == 0) return lo;
+        above = s.above;
+        hi = tk_min(hi, lo + (1ull << shift) - 1ull);
     }
 }
 
-__global__ void gather_indexed_rows_kernel(const float *__restrict__ X, const long long *__restrict__ idx,
-                                           int rows, int m, float *__restrict__ out)
+__global__ void __launch_bounds__(TK_T) topk_select_kernel(TopkArgs a)
 {
-    const int r = blockIdx.x;
-    const long long c = idx[r] == LLONG_MAX ? 0 : idx[r];
-    for (int i = threadIdx.x; i < m; i += blockDim.x) out[(size_t)r * m + i] = X[c * m + i];
+    __shared__ TkShared s;
+    const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const unsigned count = a.count, set = blockIdx.x;
+    const unsigned k = (unsigned)a.k;                    // <= count
+    const unsigned nh = (count + TK_BLOCK - 1) / TK_BLOCK;
+    const float *V = a.V + (size_t)set * count;
+
+    // ---- the blocks to look into, and a bound from below
+    u64 T = 0;
+    unsigned nlist = nh;
+    const bool listed = a.heads != nullptr && nh > k;
+    if (tid == 0) { s.n = 0; s.nlist = 0; }
+    if (listed) {
+        const u64 *heads = a.heads + (size_t)set * nh;
+        auto each_head = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll 4
+            for (unsigned i = tid; i < nh; i += TK_T) f(heads[i]);
+        };
+        u64 lo, hi;
+        tk_range(s, each_head, lo, hi);
+        T = tk_threshold(s, each_head, k, k + k / 4 + 8, lo, hi);
+        for (unsigned i = tid; i < nh; i += TK_T)
+            if (heads[i] >= T) s.list[atomicAdd(&s.nlist, 1u)] = i;
+        __syncthreads();
+        nlist = s.nlist;
+    } else {
+        __syncthreads();
+    }
+
+    // ---- what reaches the bound, into LDS
+    auto each_element = [&](auto f) __attribute__((always_inline)) {
+        for (unsigned e = wave; e < nlist; e += TK_T / 64) {
+            const unsigned first = (listed ? s.list[e] : e) * TK_BLOCK + lane;
+            float v[TK_BLOCK / 64];
+#pragma unroll
+            for (unsigned q = 0; q < TK_BLOCK / 64; ++q) v[q] = V[first + q * 64 < count ? first + q * 64 : count - 1u];
+#pragma unroll
+            for (unsigned q = 0; q < TK_BLOCK / 64; ++q)
+                if (first + q * 64 < count) f(tk_key(v[q], first + q * 64));
+        }
+    };
+    auto gather = [&]() __attribute__((always_inline)) {
+        each_element([&](u64 key) {
+            if (key < T) return;
+            const unsigned at = atomicAdd(&s.n, 1u);
+            if (at < TK_CAND) s.cand[at] = key;
+        });
+    };
+    gather();
+    __syncthreads();
+    unsigned n = s.n;
+    if (n > TK_CAND) {                                   // workgroup-uniform, here and below
+        u64 lo, hi;
+        tk_range(s, each_element, lo, hi);
+        T = tk_threshold(s, each_element, k, TK_RANK, tk_max(lo, T), hi);
+        if (tid == 0) s.n = 0;
+        __syncthreads();
+        gather();
+        __syncthreads();
+        n = s.n;
+    } else if (n > TK_RANK) {
+        auto each_cand = [&](auto f) __attribute__((always_inline)) {
+            for (unsigned i = tid; i < n; i += TK_T) f(s.cand[i]);
+        };
+        u64 lo, hi;
+        tk_range(s, each_cand, lo, hi);
+        T = tk_threshold(s, each_cand, k, TK_RANK, lo, hi);
+        u64 mine[TK_CAND / TK_T];
+#pragma unroll
+        for (unsigned q = 0; q < TK_CAND / TK_T; ++q) mine[q] = tid + q * TK_T < n ? s.cand[tid + q * TK_T] : 0ull;
+        __syncthreads();
+        if (tid == 0) s.n = 0;
+        __syncthreads();
+#pragma unroll
+        for (unsigned q = 0; q < TK_CAND / TK_T; ++q)
+            if (tid + q * TK_T < n && mine[q] >= T) s.cand[atomicAdd(&s.n, 1u)] = mine[q];
+        __syncthreads();
+        n = s.n;
+    }
+
+    // ---- in order: n <= TK_RANK keys, ranked by how many are greater
+    u64 my = 0;
+    unsigned r = 0;
+    if (tid < n) {
+        my = s.cand[tid];
+        for (unsigned i = 0; i < n; ++i) r += s.cand[i] > my ? 1u : 0u;
+    }
+    __syncthreads();
+    if (tid < n && r < k) {
+        s.list[r] = tk_index(my);
+        a.val[(size_t)set * k + r] = tk_value(my);
+        a.idx[(size_t)set * k + r] = a.index_base + (long long)tk_index(my);
+    }
+    __syncthreads();
+    const unsigned m = (unsigned)a.m;
+    const float *X = a.X + (size_t)set * count * m;
+    for (unsigned e = tid; e < k * m; e += TK_T) {
+        const unsigned row = e / m;
+        const float x = X[(size_t)s.list[row] * m + (e - row * m)];
+        a.rows[(size_t)set * k * m + e] = x;
+        if (a.rows_host) a.rows_host[(size_t)set * k * m + e] = x;
+    }
 }
 
 }  // namespace
 
-long long topk_level_blocks(long long count) { return (count + TK_SLICE - 1) / TK_SLICE; }
+// Up to here one workgroup reads all values itself sooner than a launch over the blocks ends.
+constexpr long long TK_DIRECT = 16384;
 
-hipError_t launch_topk_level(const float *vals, const long long *idx, long long count,
-                             long long index_base, int k, float *out_v, long long *out_i,
-                             hipStream_t s)
+size_t topk_heads_bytes(long long count, int sets)
 {
-    if (count <= 0 || k <= 0) return hipSuccess;
-    hipLaunchKernelGGL(topk_level_kernel, dim3((unsigned)topk_level_blocks(count)), dim3(TK_THREADS), 0,
-                       s, vals, idx, count, index_base, k, out_v, out_i);
-    return hipGetLastError();
+    return count <= TK_DIRECT ? 0 : (size_t)((count + TK_BLOCK - 1) / TK_BLOCK) * sets * sizeof(u64);
 }
 
-hipError_t launch_gather_indexed_rows(const float *X, const long long *idx, int rows, int m,
-                                      float *out, hipStream_t s)
+hipError_t launch_topk(const TopkArgs &args, int sets, hipStream_t s)
 {
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gather_indexed_rows_kernel, dim3(rows), dim3(64), 0, s, X, idx, rows, m, out);
+    if (args.count == 0 || args.k <= 0 || sets <= 0) return hipSuccess;
+    if (args.k > 256 || (unsigned)args.k > args.count) return hipErrorInvalidValue;
+    TopkArgs a = args;
+    if ((long long)a.count > TK_DIRECT) {
+        if (!a.heads) return hipErrorInvalidValue;
+        const unsigned nh = (a.count + TK_BLOCK - 1) / TK_BLOCK;
+        hipLaunchKernelGGL(topk_heads_kernel, dim3((nh + 3) / 4, (unsigned)sets), dim3(256), 0, s, a.V, a.count, nh, a.heads);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    } else {
+        a.heads = nullptr;
+    }
+    hipLaunchKernelGGL(topk_select_kernel, dim3((unsigned)sets), dim3(TK_T), 0, s, a);
     return hipGetLastError();
 }
 
