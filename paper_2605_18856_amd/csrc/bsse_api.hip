@@ -98,6 +98,25 @@ struct TopkScratch {
     }
 };
 
+// Device scratch of bsse_solve_realised, and the payoffs as given to create.
+struct RealisedScratch {
+    float *V = nullptr, *payoffs = nullptr;
+    int32_t *br = nullptr;
+    unsigned char *table = nullptr;
+    unsigned long long *list = nullptr, *sel = nullptr;
+    double *v = nullptr, *x = nullptr;
+    int *rc = nullptr;
+    size_t cap_V = 0, cap_br = 0, cap_table = 0, cap_list = 0, cap_sel = 0, cap_v = 0, cap_x = 0, cap_rc = 0;
+    unsigned char *host = nullptr;   // pinned: the best program
+    size_t cap_host = 0;
+    void release()
+    {
+        if (host) (void)hipHostFree(host);
+        (void)hipFree(V); (void)hipFree(payoffs); (void)hipFree(br); (void)hipFree(table); (void)hipFree(list);
+        (void)hipFree(sel); (void)hipFree(v); (void)hipFree(x); (void)hipFree(rc);
+    }
+};
+
 // Device scratch of the streamed sweep: one record per workgroup of a chunk, the running best, the
 // winning row, the tie counter and (small-game kernel) the workgroups' running-best slots.  Owned by the handle and grown on demand, or
 // (`fixed`) a carving of the library's static scratch array that cannot grow.
@@ -144,13 +163,17 @@ struct bsse_game {
     int set_used[3] = { 0, 0, 0 };                 // slots of each set that its chunks may have written
     PriorScratch pri;
     TopkScratch topk;
+    RealisedScratch real;
     // host copies of the game as given to create (fp32, unrounded): the profile LP of bsse_polish
     std::vector<float> hA, hB, hprior;
     float *stage = nullptr;                        // generated rows on their way into a sweep
     size_t stage_cap = 0;
-    float *centre_dev = nullptr;                   // [m] centre of a local candidate set
-    float *pol_rows = nullptr, *pol_v = nullptr;   // device scratch of bsse_polish
-    int32_t *pol_br = nullptr;
+    float *centre_dev = nullptr;                   // [.][m] centres of local candidate sets
+    size_t cap_centre = 0;
+    float *h_centre = nullptr;                     // pinned: the same on the way
+    size_t cap_h_centre = 0;
+    unsigned char *h_pol = nullptr;                // pinned: rows, values and best responses of bsse_polish
+    size_t cap_pol = 0;
     // pinned host memory, one block: what the kernels report
     HostOut *h_out = nullptr;
     unsigned *h_flag = nullptr;             // completion flags [MAX_FLAGS]
@@ -230,7 +253,8 @@ void free_game(bsse_game *g)
     (void)hipFree(g->w.run); (void)hipFree(g->w.best_x); (void)hipFree(g->w.tie_counter);
     g->pri.release();
     g->topk.release();
-    (void)hipFree(g->pol_rows); (void)hipFree(g->pol_v); (void)hipFree(g->pol_br);
+    g->real.release();
+    if (g->h_pol) (void)hipHostFree(g->h_pol);
     for (int q = 0; q < 2; ++q) {
         if (g->aux[q]) { (void)hipStreamSynchronize(g->aux[q]); (void)hipStreamDestroy(g->aux[q]); }
         if (g->aux_join[q]) (void)hipEventDestroy(g->aux_join[q]);
@@ -239,6 +263,7 @@ void free_game(bsse_game *g)
     (void)hipFree(g->centre_dev); (void)hipFree(g->stage);
     if (g->h_out) (void)hipHostFree(g->h_out);
     if (g->h_rec) (void)hipHostFree(g->h_rec);
+    if (g->h_centre) (void)hipHostFree(g->h_centre);
     (void)hipFree(g->row_l); (void)hipFree(g->row_br);
     for (hipEvent_t e : g->ev) (void)hipEventDestroy(e);
     for (hipEvent_t e : g->ev_pool) (void)hipEventDestroy(e);
@@ -398,8 +423,11 @@ bsse_status wait_words(bsse_game *g, const unsigned *word, int n, size_t stride)
 bsse_status wait_flags(bsse_game *g, int n) { return wait_words(g, g->h_flag, n, sizeof(unsigned)); }
 
 // Best responses [rows][K] of a few rows into pinned memory, as the last launch of a call (`last`: it
-// sets completion flags, *flags of them; 0 when there would be too many).
-bsse_status launch_winners(bsse_game *g, const float *X, long long rows, int32_t *br, bool last, int *flags)
+// sets completion flags, *flags of them; 0 when there would be too many).  Values too, if asked for: l
+// receives the leader payoffs [rows][K] on paths that are cut over the types (the host sums, value_of),
+// V the values on the others.
+bsse_status launch_winners(bsse_game *g, const float *X, long long rows, int32_t *br, bool last, int *flags,
+                           float *V = nullptr, float *l = nullptr)
 {
     SweepArgs a{};
     a.X = X; a.count = rows;
@@ -408,11 +436,12 @@ bsse_status launch_winners(bsse_game *g, const float *X, long long rows, int32_t
                              : cuts_types(g) ? mfma_row_blocks(g->view, rows) : sweep_blocks(g, rows);
     *flags = last && blocks <= MAX_FLAGS ? (int)blocks : 0;
     if (*flags) a.done = new_done(g);
-    if (!cuts_types(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
-    if (!on_any(g)) {                            // (the general kernel is cut only when asked for leader payoffs)
+    if (!cuts_types(g)) { a.V_out = V; HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
+    a.l_out = l; a.l_sc = g->K; a.l_st = 1;
+    if (!on_any(g) && !l) {                      // (the general kernel is cut only when asked for leader payoffs)
         bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)rows * g->K * sizeof(float));
         if (st != BSSE_OK) return st;
-        a.l_out = g->row_l; a.l_sc = g->K; a.l_st = 1;
+        a.l_out = g->row_l;
     }
     HIP_TRY(launch_rows(g, a, g->stream));
     return BSSE_OK;
@@ -754,7 +783,8 @@ bsse_status check_around(const bsse_game *g, const float *centre, float radius)
 
 bsse_status upload_centre(bsse_game *g, const float *centre)
 {
-    if (!g->centre_dev) HIP_TRY(hipMalloc((void **)&g->centre_dev, (size_t)g->m * sizeof(float)));
+    bsse_status st = grow_device(g, (void **)&g->centre_dev, &g->cap_centre, (size_t)g->m * sizeof(float));
+    if (st != BSSE_OK) return st;
     HIP_TRY(hipMemcpyAsync(g->centre_dev, centre, (size_t)g->m * sizeof(float), hipMemcpyHostToDevice, g->stream));
     HIP_TRY(hipStreamSynchronize(g->stream));          // the host array is the caller's again
     return BSSE_OK;
@@ -785,17 +815,12 @@ extern "C" bsse_status bsse_lattice_around(bsse_game *g, int N, const float *cen
 
 namespace {
 
-bsse_status lattice_impl(bsse_game *g, int N, const float *centre, float radius, int64_t *count_out)
+// The table of resolution N on the device (which is current).
+bsse_status ensure_lattice_table(bsse_game *g, int N)
 {
-    int64_t cnt = 0;
-    bsse_status st = bsse_lattice_count(g->m, N, &cnt);
-    if (st != BSSE_OK) return st;
     const int m = g->m;
     const size_t tab_elems = (size_t)(m + 1) * (N + 1);
     if (tab_elems > (1ull << 27)) return fail(BSSE_EOVERFLOW, "lattice table of %zu entries is too large", tab_elems);
-    DeviceGuard dg(g->device);
-    if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
-    if ((st = ensure_gen(g, (unsigned long long)cnt)) != BSSE_OK) return st;
     if (g->lat_table_N != N) {                    // (the table of the last resolution stays on the device)
         // W(R,q) = C(R+q-1, q-1) for q = 0..m, R = 0..N by Pascal's rule; every entry <= cnt
         std::vector<unsigned long long> tab(tab_elems, 0ull);
@@ -818,8 +843,21 @@ bsse_status lattice_impl(bsse_game *g, int N, const float *centre, float radius,
         HIP_TRY(hipStreamSynchronize(g->stream));     // `tab` is pageable and dies with this block
         g->lat_table_N = N;
     }
+    return BSSE_OK;
+}
+
+bsse_status lattice_impl(bsse_game *g, int N, const float *centre, float radius, int64_t *count_out)
+{
+    int64_t cnt = 0;
+    bsse_status st = bsse_lattice_count(g->m, N, &cnt);
+    if (st != BSSE_OK) return st;
+    const int m = g->m;
+    DeviceGuard dg(g->device);
+    if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
+    if ((st = ensure_gen(g, (unsigned long long)cnt)) != BSSE_OK) return st;
+    if ((st = ensure_lattice_table(g, N)) != BSSE_OK) return st;
     if (centre && (st = upload_centre(g, centre)) != BSSE_OK) return st;
-    HIP_TRY(launch_lattice(g->lat_table, m, N, cnt, centre ? g->centre_dev : nullptr, radius, g->gen, g->stream));
+    HIP_TRY(launch_lattice(g->lat_table, m, N, cnt, centre ? g->centre_dev : nullptr, radius, 1, g->gen, g->stream));
     g->gen_count = cnt;
     *count_out = cnt;
     return BSSE_OK;
@@ -868,7 +906,7 @@ bsse_status dirichlet_impl(bsse_game *g, uint64_t seed, int64_t first, int64_t c
         bsse_status st = upload_centre(g, centre);
         if (st != BSSE_OK) return st;
     }
-    HIP_TRY(launch_dirichlet(seed, first, count, g->m, centre ? g->centre_dev : nullptr, radius, dst, g->stream));
+    HIP_TRY(launch_dirichlet(seed, first, count, g->m, centre ? g->centre_dev : nullptr, radius, 1, dst, g->stream));
     if (!out_dev) g->gen_count = count;
     return BSSE_OK;
 }
@@ -1117,7 +1155,7 @@ extern "C" bsse_status bsse_sweep_dirichlet_chunk(bsse_game *g, uint64_t seed, i
     if ((st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)piece * g->m * sizeof(float))) != BSSE_OK) return st;
     for (long long base = 0; base < count; base += piece) {
         const long long rows = count - base < piece ? count - base : piece;
-        HIP_TRY(launch_dirichlet(seed, first + base, rows, g->m, nullptr, 1.0f, g->stage, g->stream));
+        HIP_TRY(launch_dirichlet(seed, first + base, rows, g->m, nullptr, 1.0f, 1, g->stage, g->stream));
         SweepArgs a{};
         a.X = g->stage; a.count = rows; a.index_base = index_base + base;
         if ((st = sweep_chunk_impl(g, a)) != BSSE_OK) return st;
@@ -1143,7 +1181,7 @@ extern "C" bsse_status bsse_sweep_dirichlet(bsse_game *g, uint64_t seed, int64_t
         DeviceGuard dg(g->device);
         if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
         if ((st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)count * g->m * sizeof(float))) != BSSE_OK) return st;
-        HIP_TRY(launch_dirichlet(seed, first, count, g->m, nullptr, 1.0f, g->stage, g->stream));
+        HIP_TRY(launch_dirichlet(seed, first, count, g->m, nullptr, 1.0f, 1, g->stage, g->stream));
         return sweep_once(g, g->stage, count, res, best_response_out);
     }
     if ((st = bsse_sweep_dirichlet_chunk(g, seed, first, count, 0)) != BSSE_OK) return st;
@@ -1542,12 +1580,6 @@ extern "C" bsse_status bsse_sweep_priors(bsse_game *g, const float *candidates_d
 // --------------------------------------------------------------------------------- top-k
 namespace {
 
-struct DevBuf {                      // device scratch of one call, released on every exit path
-    void *p = nullptr;
-    ~DevBuf() { (void)hipFree(p); }
-    template <typename T> T *as() const { return reinterpret_cast<T *>(p); }
-};
-
 // Evaluation of `sets` sets of `count` rows each (one behind the other at X) and the k best of every
 // set: values, indices, best responses and (rows_host) rows into pinned memory.  `flags` as in
 // launch_winners.
@@ -1644,59 +1676,132 @@ extern "C" bsse_status bsse_refine(bsse_game *g, int k, int rounds, int lattice_
     // survivors: value, row, best responses; kept sorted by (value desc, order of discovery)
     struct Survivor { double v; std::vector<float> x; std::vector<int32_t> br; };
     std::vector<Survivor> pool;
-    std::vector<double> vals((size_t)k);
-    std::vector<int64_t> idx((size_t)k);
-    std::vector<int32_t> brs((size_t)k * K);
+    // what a round finds, in the order of discovery; x and br stay where the records are
+    struct Found { double v; const float *x; const int32_t *br; };
+    std::vector<Found> found;
     long long evals = 0;
-    // the k best of the handle's current set, with their rows, into `into`
-    auto harvest = [&](std::vector<Survivor> &into) -> bsse_status {
-        int found = 0;
-        bsse_status st = bsse_sweep_topk(g, nullptr, 0, k, vals.data(), idx.data(), brs.data(), &found);
-        if (st != BSSE_OK) return st;
-        evals += (long long)g->gen_count * K;
-        for (int r = 0; r < found; ++r) {
-            Survivor sv;
-            sv.v = vals[r];
-            sv.x.resize((size_t)m);
-            sv.br.assign(brs.begin() + (size_t)r * K, brs.begin() + (size_t)(r + 1) * K);
-            HIP_TRY(hipMemcpy(sv.x.data(), g->gen + (size_t)idx[r] * m, (size_t)m * sizeof(float),
-                              hipMemcpyDeviceToHost));
-            into.push_back(std::move(sv));
-        }
-        return BSSE_OK;
-    };
-    auto keep_best = [&](std::vector<Survivor> &v) {
-        std::stable_sort(v.begin(), v.end(), [](const Survivor &a, const Survivor &b) { return a.v > b.v; });
-        // the same point may be found from two centres: keep one
+    bsse_status st;
+    // the k best distinct points of `found` become the pool
+    auto keep_best = [&]() {
+        std::stable_sort(found.begin(), found.end(), [](const Found &a, const Found &b) { return a.v > b.v; });
         std::vector<Survivor> out;
-        for (auto &sv : v) {
+        for (const Found &f : found) {
+            // the same point may be found from two centres: keep one
             bool dupl = false;
-            for (auto &o : out) if (o.x == sv.x) { dupl = true; break; }
-            if (!dupl) out.push_back(std::move(sv));
+            for (const Survivor &o : out) if (std::equal(o.x.begin(), o.x.end(), f.x)) { dupl = true; break; }
+            if (!dupl) out.push_back({ f.v, std::vector<float>(f.x, f.x + m), std::vector<int32_t>(f.br, f.br + K) });
             if ((int)out.size() == k) break;
         }
-        v.swap(out);
+        pool.swap(out);
     };
-    bsse_status st;
+    // Room for the records of `sets` sets in pinned memory, and those of `nsets` sets of `kk` appended to
+    // `found`.
+    std::vector<double> vals;
+    std::vector<int64_t> idx;
+    long long *hi = nullptr;
+    float *hv = nullptr, *hx = nullptr;
+    int32_t *hb = nullptr;
+    auto records = [&](size_t recs) -> bsse_status {
+        const size_t off_v = recs * sizeof(long long), off_b = off_v + recs * sizeof(float), off_x = off_b + recs * K * sizeof(int32_t);
+        bsse_status s = grow_pinned(g, (void **)&g->topk.host, &g->topk.cap_host, off_x + recs * m * sizeof(float));
+        hi = reinterpret_cast<long long *>(g->topk.host);
+        hv = reinterpret_cast<float *>(g->topk.host + off_v);
+        hb = reinterpret_cast<int32_t *>(g->topk.host + off_b);
+        hx = reinterpret_cast<float *>(g->topk.host + off_x);
+        return s;
+    };
+    auto append = [&](size_t recs) {
+        for (size_t r = 0; r < recs; ++r) found.push_back({ (double)hv[r], hx + r * m, hb + r * K });
+    };
+    // A set too large for one selection (2^26 rows): bsse_sweep_topk, which cuts it, and copies of the
+    // rows.  The records are copied here, for the next set overwrites the pinned ones.
+    std::vector<std::vector<float>> big_x;
+    std::vector<std::vector<int32_t>> big_br;
+    auto harvest_big = [&]() -> bsse_status {
+        vals.resize((size_t)k); idx.resize((size_t)k);
+        std::vector<int32_t> brs((size_t)k * K);
+        int n = 0;
+        bsse_status s = bsse_sweep_topk(g, nullptr, 0, k, vals.data(), idx.data(), brs.data(), &n);
+        if (s != BSSE_OK) return s;
+        std::vector<float> xs((size_t)n * m);
+        for (int r = 0; r < n; ++r)
+            HIP_TRY(hipMemcpyAsync(&xs[(size_t)r * m], g->gen + (size_t)idx[r] * m, (size_t)m * sizeof(float), hipMemcpyDeviceToHost, g->stream));
+        HIP_TRY(hipStreamSynchronize(g->stream));
+        big_x.push_back(std::move(xs)); big_br.push_back(std::move(brs));
+        for (int r = 0; r < n; ++r) found.push_back({ vals[r], big_x.back().data() + (size_t)r * m, big_br.back().data() + (size_t)r * K });
+        return BSSE_OK;
+    };
+    constexpr long long SET_MAX = 1LL << 26;             // rows one selection takes
     try {
-        if ((st = harvest(pool)) != BSSE_OK) return st;
-        keep_best(pool);
+        int flags = 0;
+        evals += (long long)g->gen_count * K;
+        if (g->gen_count > SET_MAX) {
+            if ((st = harvest_big()) != BSSE_OK) return st;
+        } else {
+            const int kk = (int)std::min<long long>(k, g->gen_count);
+            if ((st = records((size_t)kk)) != BSSE_OK) return st;
+            if ((st = enqueue_topk(g, g->gen, g->gen_count, 1, kk, 0, hv, hi, hb, hx, true, &flags)) != BSSE_OK) return st;
+            if ((st = wait_winners(g, flags)) != BSSE_OK) return st;
+            append((size_t)kk);
+        }
+        keep_best();
+        int64_t cnt = cloud_count;
+        if (lattice_N > 0) {
+            if ((st = bsse_lattice_count(m, lattice_N, &cnt)) != BSSE_OK) return st;
+            if (cnt <= SET_MAX && (st = ensure_lattice_table(g, lattice_N)) != BSSE_OK) return st;
+        }
+        // The local sets of a round do not depend on each other: as many as fit 2^26 floats (but one at
+        // least) are generated, evaluated and selected together, five launches and one wait for all of them.
+        const int kk = (int)std::min<long long>(k, cnt);
+        const long long together = std::max<long long>(1, std::min<long long>(k, (1LL << 26) / (cnt * m)));
         float rad = radius;
         for (int round = 0; round < rounds; ++round) {
-            std::vector<Survivor> next = pool;             // a centre survives unless it is beaten
-            for (size_t c = 0; c < pool.size(); ++c) {
-                if (lattice_N > 0) {
-                    int64_t cnt = 0;
-                    st = bsse_lattice_around(g, lattice_N, pool[c].x.data(), rad, &cnt);
-                } else {
-                    st = bsse_dirichlet_around(g, seed + (uint64_t)round * 1000003ull + c, 0, cloud_count,
-                                               pool[c].x.data(), rad, nullptr);
-                }
-                if (st != BSSE_OK) return st;
-                if ((st = harvest(next)) != BSSE_OK) return st;
+            found.clear(); big_x.clear(); big_br.clear();
+            for (const Survivor &s : pool) found.push_back({ s.v, s.x.data(), s.br.data() });   // a centre survives unless it is beaten
+            const uint64_t rseed = seed + (uint64_t)round * 1000003ull;
+            const size_t nc = pool.size();
+            evals += (long long)nc * cnt * K;
+            const bool big = cnt > SET_MAX;
+            // (the handle-owned set ends as the last local set, as if each had been generated there)
+            if (!big && round + 1 == rounds && (st = ensure_gen(g, (unsigned long long)cnt)) != BSSE_OK) return st;
+            if (!big) {
+                const size_t bytes = nc * m * sizeof(float);
+                if ((st = grow_device(g, (void **)&g->centre_dev, &g->cap_centre, bytes)) != BSSE_OK) return st;
+                if ((st = grow_pinned(g, (void **)&g->h_centre, &g->cap_h_centre, bytes)) != BSSE_OK) return st;
+                for (size_t c = 0; c < nc; ++c) memcpy(g->h_centre + c * m, pool[c].x.data(), (size_t)m * sizeof(float));
+                HIP_TRY(launch_copy_words(g->h_centre, g->centre_dev, nc * m, g->stream));
+                if ((st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)together * cnt * m * sizeof(float))) != BSSE_OK) return st;
+                if ((st = records((size_t)nc * kk)) != BSSE_OK) return st;
             }
-            keep_best(next);
-            pool.swap(next);
+            auto generate = [&](size_t c0, int sets, float *out) -> bsse_status {
+                if (lattice_N > 0) HIP_TRY(launch_lattice(g->lat_table, m, lattice_N, cnt, g->centre_dev + c0 * m, rad, sets, out, g->stream));
+                else HIP_TRY(launch_dirichlet(rseed + c0, 0, cnt, m, g->centre_dev + c0 * m, rad, sets, out, g->stream));
+                return BSSE_OK;
+            };
+            for (size_t c0 = 0; c0 < nc; c0 += (size_t)(big ? 1 : together)) {
+                if (big) {
+                    int64_t n = 0;
+                    st = lattice_N > 0 ? bsse_lattice_around(g, lattice_N, pool[c0].x.data(), rad, &n)
+                                       : bsse_dirichlet_around(g, rseed + c0, 0, cnt, pool[c0].x.data(), rad, nullptr);
+                    if (st == BSSE_OK) st = harvest_big();
+                    if (st != BSSE_OK) return st;
+                    continue;
+                }
+                const int sets = (int)std::min<size_t>((size_t)together, nc - c0);
+                const bool last = c0 + sets == nc;
+                if ((st = generate(c0, sets, g->stage)) != BSSE_OK) return st;
+                if (last && round + 1 == rounds) {
+                    if ((st = generate(nc - 1, 1, g->gen)) != BSSE_OK) return st;
+                    g->gen_count = cnt;
+                }
+                const size_t at = c0 * kk;
+                if ((st = enqueue_topk(g, g->stage, cnt, sets, kk, 0, hv + at, hi + at, hb + at * K, hx + at * m, last, &flags)) != BSSE_OK) return st;
+            }
+            if (!big) {
+                if ((st = wait_winners(g, flags)) != BSSE_OK) return st;
+                append(nc * kk);
+            }
+            keep_best();
             rad *= shrink;
         }
     } catch (...) { return fail(BSSE_ENOMEM, "host allocation failed"); }
@@ -1794,21 +1899,22 @@ extern "C" bsse_status bsse_polish(bsse_game *g, const int32_t *profile, float *
     for (int e = 0; e < kPolishRows; ++e)
         for (int i = 0; i < m; ++i)
             rows[(size_t)e * m + i] = (float)((1.0 - eps[e]) * x[i] + eps[e] * (double)start[i]);
-    if (!g->pol_rows) {
-        // a row stride of m floats keeps 16-byte alignment whenever m % 4 == 0, as the kernels ask
-        HIP_TRY(hipMalloc((void **)&g->pol_rows, (size_t)kPolishRows * m * sizeof(float)));
-        HIP_TRY(hipMalloc((void **)&g->pol_v, (size_t)kPolishRows * sizeof(float)));
-        HIP_TRY(hipMalloc((void **)&g->pol_br, (size_t)kPolishRows * K * sizeof(int32_t)));
-    }
-    HIP_TRY(hipMemcpyAsync(g->pol_rows, rows.data(), rows.size() * sizeof(float), hipMemcpyHostToDevice, g->stream));
-    SweepArgs a{};
-    a.X = g->pol_rows; a.count = kPolishRows; a.index_base = 0;
-    a.V_out = g->pol_v; a.br_out = g->pol_br;
-    bsse_status st = launch_eval(g, a);
+    // the kernel reads the rows from pinned memory and leaves its results there: one launch, one wait
+    const size_t off_v = rows.size() * sizeof(float), off_br = off_v + vals.size() * sizeof(float);
+    bsse_status st = grow_pinned(g, (void **)&g->h_pol, &g->cap_pol, off_br + brs.size() * sizeof(int32_t) + (size_t)kPolishRows * K * sizeof(float));
     if (st != BSSE_OK) return st;
-    HIP_TRY(hipMemcpyAsync(vals.data(), g->pol_v, vals.size() * sizeof(float), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipMemcpyAsync(brs.data(), g->pol_br, brs.size() * sizeof(int32_t), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipStreamSynchronize(g->stream));
+    float *pol_v = reinterpret_cast<float *>(g->h_pol + off_v);
+    int32_t *pol_br = reinterpret_cast<int32_t *>(g->h_pol + off_br);
+    float *pol_l = reinterpret_cast<float *>(pol_br + brs.size());
+    memcpy(g->h_pol, rows.data(), rows.size() * sizeof(float));
+    int flags = 0;
+    if ((st = launch_winners(g, reinterpret_cast<const float *>(g->h_pol), kPolishRows, pol_br, true, &flags, pol_v, pol_l)) != BSSE_OK) return st;
+    if ((st = wait_winners(g, flags)) != BSSE_OK) return st;
+    memcpy(brs.data(), pol_br, brs.size() * sizeof(int32_t));
+    for (int e = 0; e < kPolishRows; ++e) {
+        vals[e] = cuts_types(g) ? value_of(g, pol_l + (size_t)e * K) : pol_v[e];
+        if (!(vals[e] == vals[e])) vals[e] = -INFINITY;
+    }
     int best = kPolishRows - 1;                          // the sweep's own winner, unless a point beats it
     for (int e = kPolishRows - 2; e >= 0; --e)
         if (vals[e] >= vals[best]) best = e;             // equal values: the point nearest the vertex
@@ -1839,53 +1945,84 @@ extern "C" bsse_status bsse_solve_realised(bsse_game *g, const float *candidates
     if (cells > (double)(1u << 28)) return fail(BSSE_EOVERFLOW, "the program's tableau (%.3g cells) is too large", cells);
     DeviceGuard dg(g->device);
     if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
-    DevBuf V, br;
-    HIP_TRY(hipMalloc(&V.p, (size_t)count * sizeof(float)));
-    HIP_TRY(hipMalloc(&br.p, (size_t)count * K * sizeof(int32_t)));
+    RealisedScratch &w = g->real;
+    const unsigned nslots = profile_table_slots(count), most = (unsigned)std::min<int64_t>(max_profiles, count);
+    const bool on_device = lp_on_device(m, n, K);
+    const size_t table_bytes = (size_t)nslots * 12 + 16;             // keys, slots, counter
+    struct Release {                     // scratch of a large set is not kept
+        RealisedScratch &w;
+        ~Release() { if (w.cap_br + w.cap_table + w.cap_x > (size_t)1 << 30) { w.release(); w = RealisedScratch(); } }
+    } release{ w };
+    if ((st = grow_device(g, (void **)&w.V, &w.cap_V, (size_t)count * sizeof(float))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.br, &w.cap_br, (size_t)count * K * sizeof(int32_t))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.table, &w.cap_table, table_bytes)) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.list, &w.cap_list, (size_t)count * sizeof(unsigned long long))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.sel, &w.cap_sel, (size_t)most * sizeof(unsigned long long))) != BSSE_OK) return st;
+    auto *best = reinterpret_cast<unsigned long long *>(w.table);
+    auto *slots = reinterpret_cast<unsigned *>(best + nslots), *n_dev = slots + nslots;
+    HIP_TRY(launch_fill_zero(w.table, table_bytes, g->stream));
     SweepArgs a{};
     a.X = candidates_dev; a.count = count; a.index_base = 0;
-    a.V_out = V.as<float>(); a.br_out = br.as<int32_t>();
+    a.V_out = w.V; a.br_out = w.br;
     if ((st = launch_eval(g, a)) != BSSE_OK) return st;
-    std::vector<float> hv;
+    // distinct profiles, each with the best value a candidate reached under it; the most promising of
+    // them by that value
+    HIP_TRY(launch_profiles(w.V, w.br, count, K, slots, best, n_dev, w.list, most, w.sel, g->stream));
+    if (on_device) {
+        const size_t elems = (size_t)K * m * n * sizeof(float);
+        if (!w.payoffs) {                // as given to create, once per game
+            HIP_TRY(hipMalloc((void **)&w.payoffs, 2 * elems));
+            HIP_TRY(hipMemcpyAsync(w.payoffs, g->hA.data(), elems, hipMemcpyHostToDevice, g->stream));
+            HIP_TRY(hipMemcpyAsync(w.payoffs + elems / sizeof(float), g->hB.data(), elems, hipMemcpyHostToDevice, g->stream));
+        }
+        if ((st = grow_device(g, (void **)&w.v, &w.cap_v, (size_t)most * sizeof(double))) != BSSE_OK) return st;
+        if ((st = grow_device(g, (void **)&w.x, &w.cap_x, (size_t)most * m * sizeof(double))) != BSSE_OK) return st;
+        if ((st = grow_device(g, (void **)&w.rc, &w.cap_rc, (size_t)most * sizeof(int))) != BSSE_OK) return st;
+        const size_t off_x = 64, off_prof = off_x + (size_t)m * sizeof(double);
+        if ((st = grow_pinned(g, (void **)&w.host, &w.cap_host, off_prof + (size_t)K * sizeof(int32_t))) != BSSE_OK) return st;
+        static_assert(sizeof(LpBest) <= 64, "the vertex starts behind it");
+        LpArgs p{};
+        p.A = w.payoffs; p.B = w.payoffs + elems / sizeof(float); p.prior = g->dprior;
+        p.m = m; p.n_act = n; p.K = K; p.br = w.br; p.sel = w.sel; p.n = n_dev; p.most = most;
+        p.v = w.v; p.x = w.x; p.rc = w.rc;
+        auto *out = reinterpret_cast<LpBest *>(w.host);
+        auto *hx = reinterpret_cast<double *>(w.host + off_x);
+        auto *hp = reinterpret_cast<int32_t *>(w.host + off_prof);
+        HIP_TRY(launch_profile_lps(p, out, hx, hp, new_done(g), g->stream));
+        if ((st = wait_flags(g, 1)) != BSSE_OK) return st;
+        *n_profiles_out = (int)out->profiles;
+        if (out->failed) return fail(BSSE_ESTATE, "the simplex method did not converge");
+        *n_solved_out = (int)out->solved;
+        if (!out->found) return fail(BSSE_ESTATE, "no realised profile has a feasible program");
+        for (int i = 0; i < m; ++i) x_out[i] = (float)hx[i];
+        *value_out = out->value;
+        if (profile_out) memcpy(profile_out, hp, (size_t)K * sizeof(int32_t));
+        return BSSE_OK;
+    }
+    // programs too large for one workgroup's LDS: one after the other on the host
+    unsigned n_prof = 0;
+    std::vector<unsigned long long> sel;
     std::vector<int32_t> hb;
-    std::vector<int64_t> order;
-    try {
-        hv.resize((size_t)count); hb.resize((size_t)count * K); order.resize((size_t)count);
-    } catch (...) { return fail(BSSE_ENOMEM, "host allocation failed"); }
-    HIP_TRY(hipMemcpyAsync(hv.data(), V.p, hv.size() * sizeof(float), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipMemcpyAsync(hb.data(), br.p, hb.size() * sizeof(int32_t), hipMemcpyDeviceToHost, g->stream));
+    HIP_TRY(hipMemcpyAsync(&n_prof, n_dev, sizeof(n_prof), hipMemcpyDeviceToHost, g->stream));
     HIP_TRY(hipStreamSynchronize(g->stream));
-    // distinct profiles, each with the best value a candidate reached under it: sort the candidates
-    // by profile (then value descending) and take the head of every run
-    for (int64_t c = 0; c < count; ++c) order[(size_t)c] = c;
-    auto prof_less = [&](int64_t x, int64_t y) {
-        const int cmp = memcmp(&hb[(size_t)x * K], &hb[(size_t)y * K], (size_t)K * sizeof(int32_t));
-        if (cmp != 0) return cmp < 0;
-        if (hv[(size_t)x] != hv[(size_t)y]) return hv[(size_t)x] > hv[(size_t)y];
-        return x < y;
-    };
-    std::sort(order.begin(), order.end(), prof_less);
-    std::vector<int64_t> heads;
-    for (int64_t i = 0; i < count; ++i)
-        if (i == 0 || memcmp(&hb[(size_t)order[(size_t)i] * K], &hb[(size_t)order[(size_t)i - 1] * K],
-                             (size_t)K * sizeof(int32_t)) != 0)
-            heads.push_back(order[(size_t)i]);
-    // most promising first: by the best swept value under the profile
-    std::sort(heads.begin(), heads.end(), [&](int64_t x, int64_t y) {
-        return hv[(size_t)x] != hv[(size_t)y] ? hv[(size_t)x] > hv[(size_t)y] : x < y;
-    });
-    *n_profiles_out = (int)(heads.size() > 0x7FFFFFFF ? 0x7FFFFFFF : heads.size());
-    const size_t todo = heads.size() < (size_t)max_profiles ? heads.size() : (size_t)max_profiles;
+    const size_t todo = std::min(n_prof, most);
+    try { sel.resize(todo); hb.resize((size_t)count * K); } catch (...) { return fail(BSSE_ENOMEM, "host allocation failed"); }
+    HIP_TRY(hipMemcpyAsync(sel.data(), w.sel, todo * sizeof(sel[0]), hipMemcpyDeviceToHost, g->stream));
+    HIP_TRY(hipMemcpyAsync(hb.data(), w.br, hb.size() * sizeof(int32_t), hipMemcpyDeviceToHost, g->stream));
+    HIP_TRY(hipStreamSynchronize(g->stream));
+    std::sort(sel.begin(), sel.end(), [](unsigned long long x, unsigned long long y) { return x > y; });
+    *n_profiles_out = (int)n_prof;
     std::vector<double> x((size_t)m), xbest((size_t)m);
     double vbest = 0.0;
     int64_t cbest = -1;
     for (size_t i = 0; i < todo; ++i) {
         double v = 0.0;
+        const int64_t c = 0xFFFFFFFFu - (unsigned)sel[i];            // the candidate in the key
         const int rc = solve_profile_lp(m, n, K, g->hA.data(), g->hB.data(), g->hprior.data(),
-                                        &hb[(size_t)heads[i] * K], x.data(), &v);
+                                        &hb[(size_t)c * K], x.data(), &v);
         if (rc == 2) return fail(BSSE_ESTATE, "the simplex method did not converge");
         if (rc == 1) continue;        // realised under rounded operands only (bf16 storage)
-        if (cbest < 0 || v > vbest) { vbest = v; cbest = heads[i]; xbest = x; }
+        if (cbest < 0 || v > vbest) { vbest = v; cbest = c; xbest = x; }
     }
     *n_solved_out = (int)todo;
     if (cbest < 0) return fail(BSSE_ESTATE, "no realised profile has a feasible program");

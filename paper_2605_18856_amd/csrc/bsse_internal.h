@@ -215,6 +215,8 @@ hipError_t launch_reduce_merge(const float *blk_v, const long long *blk_i, long 
                                unsigned long long *tie_counter, RunningBest *run,
                                RunningBest *run_host, float *best_x, float *x_host, hipStream_t s);
 
+// dst = src (device-visible pinned host memory) by a kernel: a few words cost less than a copy command.
+hipError_t launch_copy_words(const void *src, void *dst, size_t words, hipStream_t s);
 // *p = 0 by a one-thread kernel (a fill node that is safe to capture in a graph).
 hipError_t launch_clear_u64(unsigned long long *p, hipStream_t s);
 // Zero `bytes` (a multiple of 16) at the 16-byte aligned device address p, by a kernel.
@@ -247,6 +249,26 @@ struct TopkArgs {
 size_t topk_heads_bytes(long long count, int sets);
 hipError_t launch_topk(const TopkArgs &args, int sets, hipStream_t s);
 
+// Profiles that candidates realise, and their programs on the device (see realised.hip).  A profile is
+// named by the key (topk_device.h) of its best candidate.
+struct LpArgs {
+    const float *A, *B, *prior;  // payoffs as given to create, [K][m][n]
+    int m, n_act, K;
+    const int32_t *br;           // [count][K]
+    const unsigned long long *sel;   // the profiles to solve
+    const unsigned *n;           // distinct profiles; min(*n, most) are in sel
+    unsigned most;
+    double *v, *x;               // [most] optimum, [most][m] vertex
+    int *rc;                     // [most] as solve_profile_lp returns
+};
+struct LpBest { double value; unsigned profiles, solved; int found, failed; };
+unsigned profile_table_slots(long long count);
+hipError_t launch_profiles(const float *V, const int32_t *br, long long count, int K, unsigned *slots,
+                           unsigned long long *best, unsigned *n, unsigned long long *list, unsigned most,
+                           unsigned long long *sel, hipStream_t s);
+bool lp_on_device(int m, int n, int K);
+hipError_t launch_profile_lps(const LpArgs &a, LpBest *out, double *x_host, int32_t *profile_host, const Done &done, hipStream_t s);
+
 // Host code: the linear program of one pure follower profile (see profile_lp.hip).  Returns 0 with
 // x_out[m] (on the simplex) and *value_out, 1 when the profile is a best response nowhere, 2 when
 // the simplex method hit its iteration limit.  May throw std::bad_alloc.
@@ -255,9 +277,10 @@ int solve_profile_lp(int m, int n, int K, const float *A, const float *B, const 
 
 // centre (device [m], nullable) and radius: the generated set shrunk towards the centre, each
 // component fl(fl(radius * t) + fl(fl(1 - radius) * centre[i])); centre == nullptr: the plain set.
+// sets > 1: that many sets one behind the other, set s around row s of centre and with seed + s.
 hipError_t launch_lattice(const unsigned long long *table, int m, int N, long long count,
-                          const float *centre, float radius, float *out, hipStream_t s);
+                          const float *centre, float radius, int sets, float *out, hipStream_t s);
 hipError_t launch_dirichlet(uint64_t seed, long long first, long long count, int m,
-                            const float *centre, float radius, float *out, hipStream_t s);
+                            const float *centre, float radius, int sets, float *out, hipStream_t s);
 
 }  // namespace bsse

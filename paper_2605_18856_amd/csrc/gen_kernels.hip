@@ -6,6 +6,9 @@
 
 namespace bsse {
 
+// Several sets in one launch (blockIdx.y): set s lies behind the others, around centre row s, with seed
+// + s.
+//
 // Local sets: with a centre c (device, m floats) the generated point t is replaced by
 // fl(fl(radius * t) + fl(omr * c)), omr = fl(1 - radius): the set shrunk by `radius` towards c.
 // Separately rounded products and sum (no contraction), so the definition is three fp32 operations.
@@ -29,6 +32,8 @@ __global__ void __launch_bounds__(256)
 lattice_kernel(const unsigned long long *__restrict__ table, int m, int N, long long count,
                const float *__restrict__ centre, float radius, float omr, float *__restrict__ out)
 {
+    out += (size_t)blockIdx.y * count * m;
+    if (centre) centre += blockIdx.y * m;
     const float fN = (float)N;
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x; r < count; r += stride) {
@@ -53,12 +58,12 @@ lattice_kernel(const unsigned long long *__restrict__ table, int m, int N, long 
 }
 
 hipError_t launch_lattice(const unsigned long long *table, int m, int N, long long count,
-                          const float *centre, float radius, float *out, hipStream_t s)
+                          const float *centre, float radius, int sets, float *out, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
     long long blocks = (count + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(lattice_kernel, dim3((unsigned)blocks), dim3(256), 0, s, table, m, N, count,
+    hipLaunchKernelGGL(lattice_kernel, dim3((unsigned)blocks, (unsigned)sets), dim3(256), 0, s, table, m, N, count,
                        centre, radius, 1.0f - radius, out);
     return hipGetLastError();
 }
@@ -67,10 +72,14 @@ hipError_t launch_lattice(const unsigned long long *table, int m, int N, long lo
 // wavefront writes 1 KiB contiguously.  Requires m % 4 == 0 and m/4 a power of two <= 64, so
 // that a row's threads sit in one wavefront and the row sum is a butterfly over them.
 __global__ void __launch_bounds__(256)
-dirichlet_quad_kernel(unsigned k0, unsigned k1, long long first, long long count, int m,
+dirichlet_quad_kernel(unsigned long long seed, long long first, long long count, int m,
                       int log2_nb, const float *__restrict__ centre, float radius, float omr,
                       float *__restrict__ out)
 {
+    seed += blockIdx.y;
+    out += (size_t)blockIdx.y * count * m;
+    if (centre) centre += blockIdx.y * m;
+    const unsigned k0 = (unsigned)seed, k1 = (unsigned)(seed >> 32);
     const int nb = 1 << log2_nb;
     const long long quads = count << log2_nb;
     const long long stride = (long long)gridDim.x * blockDim.x;
@@ -103,10 +112,14 @@ dirichlet_quad_kernel(unsigned k0, unsigned k1, long long first, long long count
 // (the quad kernel needs a 16-byte aligned output; this one does not).
 template <bool TREE>
 __global__ void __launch_bounds__(256)
-dirichlet_row_kernel(unsigned k0, unsigned k1, long long first, long long count, int m,
+dirichlet_row_kernel(unsigned long long seed, long long first, long long count, int m,
                      const float *__restrict__ centre, float radius, float omr, float *__restrict__ out)
 {
 #pragma clang fp contract(off)
+    seed += blockIdx.y;
+    out += (size_t)blockIdx.y * count * m;
+    if (centre) centre += blockIdx.y * m;
+    const unsigned k0 = (unsigned)seed, k1 = (unsigned)(seed >> 32);
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x; r < count; r += stride) {
         const long long row = first + r;
@@ -146,10 +159,9 @@ dirichlet_row_kernel(unsigned k0, unsigned k1, long long first, long long count,
 }
 
 hipError_t launch_dirichlet(uint64_t seed, long long first, long long count, int m,
-                            const float *centre, float radius, float *out, hipStream_t s)
+                            const float *centre, float radius, int sets, float *out, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
-    const unsigned k0 = (unsigned)(seed & 0xFFFFFFFFull), k1 = (unsigned)(seed >> 32);
     int nb = m / 4, log2_nb = 0;
     while ((1 << log2_nb) < nb) ++log2_nb;
     const bool quad_shape = (m % 4 == 0) && nb >= 1 && (1 << log2_nb) == nb && nb <= 64;
@@ -157,16 +169,16 @@ hipError_t launch_dirichlet(uint64_t seed, long long first, long long count, int
         const long long quads = count * nb;
         long long blocks = (quads + 255) / 256;
         if (blocks > 256 * 32) blocks = 256 * 32;
-        hipLaunchKernelGGL(dirichlet_quad_kernel, dim3((unsigned)blocks), dim3(256), 0, s, k0, k1,
+        hipLaunchKernelGGL(dirichlet_quad_kernel, dim3((unsigned)blocks, (unsigned)sets), dim3(256), 0, s, seed,
                            first, count, m, log2_nb, centre, radius, 1.0f - radius, out);
     } else {
         long long blocks = (count + 255) / 256;
         if (blocks > 256 * 32) blocks = 256 * 32;
         if (quad_shape)
-            hipLaunchKernelGGL(dirichlet_row_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, s, k0, k1,
+            hipLaunchKernelGGL(dirichlet_row_kernel<true>, dim3((unsigned)blocks, (unsigned)sets), dim3(256), 0, s, seed,
                                first, count, m, centre, radius, 1.0f - radius, out);
         else
-            hipLaunchKernelGGL(dirichlet_row_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, s, k0, k1,
+            hipLaunchKernelGGL(dirichlet_row_kernel<false>, dim3((unsigned)blocks, (unsigned)sets), dim3(256), 0, s, seed,
                                first, count, m, centre, radius, 1.0f - radius, out);
     }
     return hipGetLastError();

@@ -1,0 +1,358 @@
+// Follower profiles that a set of candidates realises, and the linear program of each on the device
+// (see profile_lp.hip for the program, the simplex method on its dual and the starting basis).
+//
+// Profiles: an open-addressing table in device memory.  A slot names one candidate of its profile (rows
+// of best responses are compared, so that no two profiles can be mistaken for one another) and collects
+// the key -- value, then lowest index -- of the profile's best candidate.  A thread that finds its key
+// beaten already leaves without an atomic: popular profiles would otherwise queue at one address.
+//
+// Programs: one workgroup each, the tableau in LDS; a thread owns columns, so that the update of a pivot
+// needs no exchange.  The arithmetic, operation by operation (no contraction), and the choice of every
+// pivot are those of solve_profile_lp: same vertex, same bits.  Bound by the chain entering column ->
+// ratio test -> pivot row -> update, about a microsecond a pivot; 200 programs of 16 x 78 cells run at
+// once in the time of the longest instead of one after the other on the host.
+#include "bsse_internal.h"
+#include "done_device.h"
+#include "topk_device.h"
+
+namespace bsse {
+
+namespace {
+
+typedef unsigned long long u64;
+
+__global__ void __launch_bounds__(256)
+profile_insert_kernel(const float *__restrict__ V, const int32_t *__restrict__ br, unsigned count, int K,
+                      unsigned *slots, u64 *best, unsigned mask)
+{
+    const unsigned c = blockIdx.x * 256u + threadIdx.x;
+    if (c >= count) return;
+    const int32_t *row = br + (size_t)c * K;
+    unsigned h = 0x811C9DC5u;
+    for (int t = 0; t < K; ++t) { h ^= (unsigned)row[t]; h *= 0x9E3779B1u; h ^= h >> 15; }
+    h &= mask;
+    for (;; h = (h + 1u) & mask) {                       // ends: the table has twice as many slots as candidates
+        unsigned o = __hip_atomic_load(&slots[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (o == 0u) o = atomicCAS(&slots[h], 0u, c + 1u);
+        if (o == 0u) break;
+        const int32_t *other = br + (size_t)(o - 1u) * K;
+        int t = 0;
+        while (t < K && other[t] == row[t]) ++t;
+        if (t == K) break;
+    }
+    const u64 key = tk_key(V[c], c);
+    if (__hip_atomic_load(&best[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < key) atomicMax(&best[h], key);
+}
+
+__global__ void __launch_bounds__(256)
+profile_list_kernel(const u64 *__restrict__ best, unsigned nslots, u64 *__restrict__ list, unsigned *n)
+{
+    __shared__ unsigned wave_n[4], at;
+    const unsigned i = blockIdx.x * 256u + threadIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const u64 key = i < nslots ? best[i] : 0ull;
+    const u64 live = __ballot(key != 0ull);
+    if (lane == 0) wave_n[wave] = (unsigned)__popcll(live);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned total = wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3];
+        at = total ? atomicAdd(n, total) : 0u;
+    }
+    __syncthreads();
+    unsigned pos = at;
+    for (unsigned w = 0; w < wave; ++w) pos += wave_n[w];
+    if (key) list[pos + (unsigned)__popcll(live & ((1ull << lane) - 1ull))] = key;
+}
+
+// The `most` best of the n profiles (all of them if there are no more), in any order.
+__global__ void __launch_bounds__(TK_T)
+profile_select_kernel(const u64 *__restrict__ list, const unsigned *__restrict__ n_ptr, unsigned most, u64 *__restrict__ sel)
+{
+    __shared__ TkShared s;
+    const unsigned n = *n_ptr;
+    auto each = [&](auto f) __attribute__((always_inline)) {
+#pragma unroll 4
+        for (unsigned i = threadIdx.x; i < n; i += TK_T) f(list[i]);
+    };
+    u64 T = 0;
+    if (threadIdx.x == 0) s.n = 0;
+    if (n > most) {
+        u64 lo, hi;
+        tk_range(s, each, lo, hi);
+        T = tk_threshold(s, each, most, most, lo, hi);
+    }
+    __syncthreads();
+    each([&](u64 key) { if (key >= T) sel[atomicAdd(&s.n, 1u)] = key; });
+}
+
+// ------------------------------------------------------------------------------- programs
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
+{
+    const u64 b = (u64)__double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((u64)(unsigned)hi << 32) | (unsigned)lo));
+}
+// Minimum over the wavefront, in every lane (a value that is not a number never is).
+__device__ __forceinline__ double wave_min(double v)
+{
+    v = fmin(v, dpp_f64<0xB1>(v));       // lanes 1 apart, 2 apart, half row, row, 16 lanes, 32 lanes
+    v = fmin(v, dpp_f64<0x4E>(v));
+    v = fmin(v, dpp_f64<0x141>(v));
+    v = fmin(v, dpp_f64<0x140>(v));
+    v = fmin(v, dpp_f64<0x142>(v));
+    v = fmin(v, dpp_f64<0x143>(v));
+    const u64 b = (u64)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, 63), hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+}
+template <int T> __device__ __forceinline__ double block_min(double v, double *red)
+{
+    v = wave_min(v);
+    if constexpr (T > 64) {
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+        __syncthreads();
+        v = red[0];
+        for (int w = 1; w < T / 64; ++w) v = fmin(v, red[w]);
+    }
+    return v;
+}
+
+// T threads; see solve_profile_lp for what every step is.
+template <int T>
+__global__ void __launch_bounds__(T) profile_lp_kernel(LpArgs a)
+{
+#pragma clang fp contract(off)
+    extern __shared__ __attribute__((aligned(16))) double lp[];
+    __shared__ double red[T / 64];
+    const int tid = threadIdx.x;
+    const unsigned p = blockIdx.x;
+    const unsigned n_sel = *a.n < a.most ? *a.n : a.most;
+    if (p >= n_sel) return;
+    const int m = a.m, n = a.n_act, K = a.K, R = K * (n - 1), ncol = 2 + R + m, col_s = 2 + R;
+    double *tab = lp, *d = tab + (size_t)m * ncol, *rhs = d + ncol, *c = rhs + m, *fcol = c + m, *ratio = fcol + m;
+    int *basic = reinterpret_cast<int *>(ratio + m);
+    const int32_t *profile = a.br + (size_t)tk_index(a.sel[p]) * K;
+
+    // ---- objective and payoff differences
+    for (int i = tid; i < m; i += T) {
+        double v = 0.0;
+        for (int t = 0; t < K; ++t) v += (double)a.prior[t] * (double)a.A[((size_t)t * m + i) * n + profile[t]];
+        c[i] = v;
+    }
+    double big = 0.0;                                    // minus the greatest difference
+    for (int j = tid; j < ncol; j += T) {
+        if (j < 2 || j >= col_s) {
+            for (int i = 0; i < m; ++i) tab[(size_t)i * ncol + j] = j == 0 ? 1.0 : j == 1 ? -1.0 : j == col_s + i ? -1.0 : 0.0;
+            continue;
+        }
+        const int t = (j - 2) / (n - 1), r = (j - 2) % (n - 1), pt = profile[t], act = r < pt ? r : r + 1;
+        const float *Bt = a.B + (size_t)t * m * n;
+        for (int i = 0; i < m; ++i) {
+            const double g = (double)Bt[(size_t)i * n + pt] - (double)Bt[(size_t)i * n + act];
+            tab[(size_t)i * ncol + j] = -g;
+            big = fmin(big, -fabs(g));
+        }
+    }
+    const double scale = fmax(1.0, -block_min<T>(big, red));
+    __syncthreads();
+    double cmin = c[0];
+    int k = 0;
+    for (int i = 1; i < m; ++i) {
+        cmin = c[i] < cmin ? c[i] : cmin;
+        if (c[i] > c[k]) k = i;
+    }
+    const double shift = 1.0 - cmin;
+    const double rk = c[k] + shift;
+    for (int i = tid; i < m; i += T) {
+        rhs[i] = i == k ? rk : rk - (c[i] + shift);
+        basic[i] = i == k ? 0 : col_s + i;
+    }
+    for (int j = tid; j < ncol; j += T) {
+        const double pk = tab[(size_t)k * ncol + j];
+        for (int i = 0; i < m; ++i)
+            if (i != k) tab[(size_t)i * ncol + j] = pk - tab[(size_t)i * ncol + j];
+        d[j] = (j == 0 ? 1.0 : j == 1 ? -1.0 : 0.0) - pk;
+    }
+    double z = rk;
+
+    const double tol = 1e-11 * scale;
+    const int max_iter = 200 * (m + R) + 1000;
+    int stall = 0, rc = 2;
+    for (int it = 0; it < max_iter; ++it) {
+        __syncthreads();                                 // the update of the pivot before
+        // entering column
+        double mn = INFINITY;
+        for (int j = tid; j < ncol; j += T) mn = fmin(mn, d[j]);
+        mn = block_min<T>(mn, red);
+        if (!(mn < -tol)) {                              // optimal
+            double s = 0.0;
+            for (int i = 0; i < m; ++i) { const double v = d[col_s + i]; s += v > 0.0 ? v : 0.0; }
+            if (s > 0.0) {
+                for (int i = tid; i < m; i += T) {
+                    const double v = d[col_s + i];
+                    a.x[(size_t)p * m + i] = (v > 0.0 ? v : 0.0) / s;
+                }
+                rc = 0;
+            }
+            break;
+        }
+        double first = INFINITY;                         // lowest column that qualifies
+        for (int j = tid; j < ncol; j += T)
+            if (stall < 40 ? d[j] == mn : d[j] < -tol) { first = (double)j; break; }
+        const int e = (int)block_min<T>(first, red);
+        // leaving row: least ratio, lowest basic variable among near-equal ones
+        double least = INFINITY;
+        for (int i = tid; i < m; i += T) {
+            const double v = tab[(size_t)i * ncol + e];
+            fcol[i] = v;
+            const double q = v > tol ? rhs[i] / v : INFINITY;
+            ratio[i] = q;
+            least = fmin(least, q);
+        }
+        least = block_min<T>(least, red);
+        __syncthreads();
+        if (least == INFINITY) { rc = 1; break; }        // dual unbounded
+        int l = -1;
+        {
+            // (a row apart from every other by ten times the tolerance below wins whatever the order)
+            const double near = least + 1e-12 * (1.0 + fabs(least));
+            int hits = 0;
+            for (int i = 0; i < m; ++i)
+                if (ratio[i] <= near) { l = i; ++hits; }
+            if (hits > 1) {
+                l = -1;
+                double best_ratio = 0.0;
+                for (int i = 0; i < m; ++i) {
+                    if (!(fcol[i] > tol)) continue;
+                    const double q = ratio[i];
+                    if (l < 0 || q < best_ratio - 1e-13 * (1.0 + fabs(best_ratio)) ||
+                        (q <= best_ratio + 1e-13 * (1.0 + fabs(best_ratio)) && basic[i] < basic[l])) {
+                        l = i; best_ratio = q;
+                    }
+                }
+            }
+        }
+        // pivot on (l, e): every thread its columns
+        const double piv = fcol[l], fd = d[e], rl = rhs[l] / piv;
+        __syncthreads();
+        for (int j = tid; j < ncol; j += T) {
+            double q = tab[(size_t)l * ncol + j] / piv;
+            if (j == e) q = 1.0;
+            tab[(size_t)l * ncol + j] = q;
+#pragma unroll 4
+            for (int i = 0; i < m; ++i) {
+                const double f = fcol[i];
+                if (i == l || f == 0.0) continue;
+                const double v = f * q;
+                tab[(size_t)i * ncol + j] = j == e ? 0.0 : tab[(size_t)i * ncol + j] - v;
+            }
+            const double v = fd * q;
+            d[j] = j == e ? 0.0 : d[j] - v;
+        }
+        for (int i = tid; i < m; i += T) {
+            const double f = fcol[i];
+            if (i == l) { rhs[i] = rl; basic[i] = e; continue; }
+            if (f == 0.0) continue;
+            const double v = f * rl;
+            double r = rhs[i] - v;
+            if (r < 0.0 && r > -1e-9 * (1.0 + fabs(rl))) r = 0.0;
+            rhs[i] = r;
+        }
+        const double zv = fd * rl, z_new = z + zv;
+        stall = (z - z_new > 1e-14 * (1.0 + fabs(z))) ? 0 : stall + 1;
+        z = z_new;
+    }
+    if (tid == 0) { a.v[p] = z - shift; a.rc[p] = rc; }
+}
+
+// The best program (greatest optimum, then the most promising profile) to pinned host memory.
+__global__ void __launch_bounds__(256) profile_pick_kernel(LpArgs a, LpBest *out, double *x_host, int32_t *profile_host, Done done)
+{
+    __shared__ double sv[4];
+    __shared__ u64 sk[4];
+    __shared__ int sp[4], sbad[4];
+    const int tid = threadIdx.x;
+    const unsigned n = *a.n < a.most ? *a.n : a.most;
+    double bv = -INFINITY;
+    u64 bk = 0;
+    int bp = -1, bad = 0;
+    auto take = [&](double v, u64 key, int p) {
+        if (p >= 0 && (bp < 0 || v > bv || (v == bv && key > bk))) { bv = v; bk = key; bp = p; }
+    };
+    for (unsigned p = tid; p < n; p += 256) {
+        const int rc = a.rc[p];
+        bad |= rc == 2;
+        if (rc == 0) take(a.v[p], a.sel[p], (int)p);
+    }
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) {
+        take(__shfl_xor(bv, s, 64), __shfl_xor(bk, s, 64), __shfl_xor(bp, s, 64));
+        bad |= __shfl_xor(bad, s, 64);
+    }
+    if ((tid & 63) == 0) { sv[tid >> 6] = bv; sk[tid >> 6] = bk; sp[tid >> 6] = bp; sbad[tid >> 6] = bad; }
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) { take(sv[w], sk[w], sp[w]); bad |= sbad[w]; }
+    if (bp >= 0) {
+        for (int i = tid; i < a.m; i += 256) x_host[i] = a.x[(size_t)bp * a.m + i];
+        for (int t = tid; t < a.K; t += 256) profile_host[t] = a.br[(size_t)tk_index(bk) * a.K + t];
+    }
+    if (tid == 0) {
+        LpBest r;
+        r.value = bv; r.profiles = *a.n; r.solved = n; r.found = bp >= 0 ? 1 : 0; r.failed = bad;
+        *out = r;
+    }
+    signal_done(done, 0);
+}
+
+}  // namespace
+
+unsigned profile_table_slots(long long count)
+{
+    unsigned s = 256;
+    while ((long long)s < 2 * count) s <<= 1;            // (count <= 2^27)
+    return s;
+}
+
+// slots, best and n (which the caller has cleared) -> list (up to `count` keys) and n, then sel (up to
+// `most` of them).
+hipError_t launch_profiles(const float *V, const int32_t *br, long long count, int K, unsigned *slots,
+                           unsigned long long *best, unsigned *n, unsigned long long *list, unsigned most,
+                           unsigned long long *sel, hipStream_t s)
+{
+    const unsigned nslots = profile_table_slots(count);
+    hipLaunchKernelGGL(profile_insert_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, V, br, (unsigned)count, K,
+                       slots, best, nslots - 1u);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(profile_list_kernel, dim3(nslots / 256), dim3(256), 0, s, best, nslots, list, n);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(profile_select_kernel, dim3(1), dim3(TK_T), 0, s, list, n, most, sel);
+    return hipGetLastError();
+}
+
+static size_t lp_lds(int m, int n, int K)
+{
+    const size_t ncol = 2 + (size_t)K * (n - 1) + m;
+    return ((size_t)m * ncol + ncol + 4 * (size_t)m) * sizeof(double) + (size_t)m * sizeof(int);
+}
+
+// A tableau that LDS holds beside the kernel's own words.
+bool lp_on_device(int m, int n, int K) { return n > 1 && (double)m * (2.0 + (double)K * (n - 1) + m) < 20000.0 && lp_lds(m, n, K) <= 150 * 1024; }
+
+hipError_t launch_profile_lps(const LpArgs &a, LpBest *out, double *x_host, int32_t *profile_host, const Done &done, hipStream_t s)
+{
+    const size_t lds = lp_lds(a.m, a.n_act, a.K);
+    // one wavefront needs no barriers; a larger tableau is worth four
+    const bool one = (size_t)a.m * (2 + (size_t)a.K * (a.n_act - 1) + a.m) <= 4096;
+    const void *k = one ? (const void *)profile_lp_kernel<64> : (const void *)profile_lp_kernel<256>;
+    hipError_t e;
+    if (lds > 48 * 1024 && (e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess) return e;
+    if (one) hipLaunchKernelGGL(profile_lp_kernel<64>, dim3(a.most), dim3(64), lds, s, a);
+    else hipLaunchKernelGGL(profile_lp_kernel<256>, dim3(a.most), dim3(256), lds, s, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(profile_pick_kernel, dim3(1), dim3(256), 0, s, a, out, x_host, profile_host, done);
+    return hipGetLastError();
+}
+
+}  // namespace bsse

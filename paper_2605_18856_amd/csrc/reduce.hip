@@ -80,7 +80,22 @@ __global__ void __launch_bounds__(256) fill_zero_kernel(uint4 *p, size_t n16)
         p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+__global__ void __launch_bounds__(256) copy_words_kernel(const unsigned *src, unsigned *dst, size_t n)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = src[i];
+}
+
 }  // namespace
+
+hipError_t launch_copy_words(const void *src, void *dst, size_t words, hipStream_t s)
+{
+    if (words == 0) return hipSuccess;
+    size_t blocks = (words + 255) / 256;
+    if (blocks > 1024) blocks = 1024;
+    hipLaunchKernelGGL(copy_words_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const unsigned *)src, (unsigned *)dst, words);
+    return hipGetLastError();
+}
 
 // bytes must be a multiple of 16 and p 16-byte aligned
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s)
