@@ -41,6 +41,9 @@ class bsse_result(ctypes.Structure):
                 ("n_evals", ctypes.c_int64), ("n_tie_evals", ctypes.c_int64)]
 
 
+_RESULT_DTYPE = np.dtype([("best_value", "f8"), ("best_index", "i8"), ("n_evals", "i8"), ("n_tie_evals", "i8")])
+
+
 class BsseError(RuntimeError):
     def __init__(self, status, message):
         super().__init__(f"{status_name(status)}: {message}")
@@ -136,12 +139,12 @@ def _dev_ptr(t, dtype_name, min_elems):
     if t is None:
         return None
     import torch
-    want = {"float32": torch.float32, "int32": torch.int32}[dtype_name]
+    want = torch.float32 if dtype_name == "float32" else torch.int32
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == want and t.is_contiguous()):
         raise TypeError(f"expected a contiguous CUDA {dtype_name} tensor")
     if t.numel() < min_elems:
         raise ValueError(f"tensor holds {t.numel()} elements, {min_elems} needed")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 @dataclass
@@ -159,6 +162,12 @@ class Game:
     def __init__(self, handle, m, n, K):
         self._h = handle
         self.m, self.n, self.K = m, n, K
+        # what a sweep fills: kept, with its addresses, because making them costs more than a small sweep's
+        # launch (numpy takes a microsecond to name an array's address)
+        self._res = bsse_result()
+        self._res_p = ctypes.byref(self._res)
+        self._br_buf, self._x_buf = (ctypes.c_int32 * K)(), (ctypes.c_float * m)()
+        self._br, self._x = np.frombuffer(self._br_buf, np.int32), np.frombuffer(self._x_buf, np.float32)
 
     @property
     def handle(self):
@@ -286,9 +295,10 @@ def candidates_to_host(g: Game) -> np.ndarray:
     return t.clone().cpu().numpy()
 
 
-def _outcome(g, res, br):
-    has = res.best_index >= 0
-    return SweepOutcome(res.best_value, res.best_index, br.copy() if has else None,
+def _outcome(g):
+    res = g._res
+    index = res.best_index
+    return SweepOutcome(res.best_value, index, g._br.copy() if index >= 0 else None,
                         res.n_evals, res.n_tie_evals)
 
 
@@ -298,22 +308,16 @@ def bsse_sweep(g: Game, candidates=None, count: Optional[int] = None) -> SweepOu
         count = candidates.numel() // g.m
     if count is None:
         count = 0
-    res = bsse_result()
-    br = np.full(g.K, -1, dtype=np.int32)
-    _check(lib().bsse_sweep(g.handle, _dev_ptr(candidates, "float32", count * g.m), count,
-                            ctypes.byref(res), br.ctypes.data))
-    return _outcome(g, res, br)
+    _check(lib().bsse_sweep(g.handle, _dev_ptr(candidates, "float32", count * g.m), count, g._res_p, g._br_buf))
+    return _outcome(g)
 
 
 def bsse_sweep_static(g: Game, candidates, count: Optional[int] = None) -> SweepOutcome:
     """bsse_sweep through the entry point that allocates nothing (explicit candidates only)."""
     if count is None:
         count = candidates.numel() // g.m
-    res = bsse_result()
-    br = np.full(g.K, -1, dtype=np.int32)
-    _check(lib().bsse_sweep_static(g.handle, _dev_ptr(candidates, "float32", count * g.m), count,
-                                   ctypes.byref(res), br.ctypes.data))
-    return _outcome(g, res, br)
+    _check(lib().bsse_sweep_static(g.handle, _dev_ptr(candidates, "float32", count * g.m), count, g._res_p, g._br_buf))
+    return _outcome(g)
 
 
 def bsse_sweep_priors(g: Game, priors, candidates=None, count: Optional[int] = None):
@@ -326,12 +330,15 @@ def bsse_sweep_priors(g: Game, priors, candidates=None, count: Optional[int] = N
         count = candidates.numel() // g.m
     if count is None:
         count = 0
-    res = (bsse_result * max(P, 1))()
-    br = np.full((max(P, 1), g.K), -1, dtype=np.int32)
+    res = np.empty(max(P, 1), dtype=_RESULT_DTYPE)
+    br = np.empty((max(P, 1), g.K), dtype=np.int32)
     _check(lib().bsse_sweep_priors(g.handle, _dev_ptr(candidates, "float32", count * g.m), count,
-                                   pri.ctypes.data, P, ctypes.cast(res, ctypes.c_void_p),
-                                   br.ctypes.data))
-    return [_outcome(g, res[p], br[p]) for p in range(P)]
+                                   pri.ctypes.data, P, res.ctypes.data, br.ctypes.data))
+    # (column by column: a hundred results picked out of ctypes records take longer than the sweep)
+    index = res["best_index"].tolist()
+    rows = list(br) if min(index) >= 0 else [b if i >= 0 else None for b, i in zip(br, index)]
+    return list(map(SweepOutcome, res["best_value"].tolist(), index, rows, res["n_evals"].tolist(),
+                    res["n_tie_evals"].tolist()))
 
 
 def bsse_sweep_topk(g: Game, k: int, candidates=None, count: Optional[int] = None):
@@ -342,14 +349,14 @@ def bsse_sweep_topk(g: Game, k: int, candidates=None, count: Optional[int] = Non
     if count is None:
         count = 0
     kk = max(int(k), 1)
-    v = np.zeros(kk, dtype=np.float64)
-    idx = np.full(kk, -1, dtype=np.int64)
-    br = np.full((kk, g.K), -1, dtype=np.int32)
+    v = np.empty(kk, dtype=np.float64)
+    idx = np.empty(kk, dtype=np.int64)
+    br = np.empty((kk, g.K), dtype=np.int32)
     found = ctypes.c_int(0)
     _check(lib().bsse_sweep_topk(g.handle, _dev_ptr(candidates, "float32", count * g.m), count, int(k),
                                  v.ctypes.data, idx.ctypes.data, br.ctypes.data, ctypes.byref(found)))
     f = found.value
-    return v[:f].copy(), idx[:f].copy(), br[:f].copy()
+    return (v, idx, br) if f == kk else (v[:f].copy(), idx[:f].copy(), br[:f].copy())
 
 
 def bsse_solve_realised(g: Game, candidates=None, count: Optional[int] = None, max_profiles: int = 1 << 20):
@@ -427,16 +434,13 @@ def bsse_sweep_chunk(g: Game, candidates, count: int, index_base: int):
 
 
 def bsse_sweep_best_row(g: Game) -> np.ndarray:
-    x = np.empty(g.m, dtype=np.float32)
-    _check(lib().bsse_sweep_best_row(g.handle, x.ctypes.data))
-    return x
+    _check(lib().bsse_sweep_best_row(g.handle, g._x_buf))
+    return g._x.copy()
 
 
 def bsse_sweep_dirichlet(g: Game, seed: int, first: int, count: int) -> SweepOutcome:
-    res = bsse_result()
-    br = np.full(g.K, -1, dtype=np.int32)
-    _check(lib().bsse_sweep_dirichlet(g.handle, seed, first, count, ctypes.byref(res), br.ctypes.data))
-    return _outcome(g, res, br)
+    _check(lib().bsse_sweep_dirichlet(g.handle, seed, first, count, g._res_p, g._br_buf))
+    return _outcome(g)
 
 
 def bsse_sweep_dirichlet_chunk(g: Game, seed: int, first: int, count: int, index_base: int):
@@ -444,10 +448,8 @@ def bsse_sweep_dirichlet_chunk(g: Game, seed: int, first: int, count: int, index
 
 
 def bsse_sweep_result(g: Game) -> SweepOutcome:
-    res = bsse_result()
-    br = np.full(g.K, -1, dtype=np.int32)
-    _check(lib().bsse_sweep_result(g.handle, ctypes.byref(res), br.ctypes.data))
-    return _outcome(g, res, br)
+    _check(lib().bsse_sweep_result(g.handle, g._res_p, g._br_buf))
+    return _outcome(g)
 
 
 def bsse_eval(g: Game, candidates, count: int, values_out=None, br_out=None):

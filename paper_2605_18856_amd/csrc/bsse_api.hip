@@ -68,19 +68,14 @@ struct HostOut {            // pinned, device-visible: kernels write results her
 // calls do not allocate.
 struct PriorScratch {
     float *L = nullptr, *priors = nullptr, *blk_v = nullptr, *rows = nullptr;
-    long long *blk_i = nullptr;
     bsse::PriorBest *run = nullptr;
-    int32_t *br = nullptr;
-    unsigned long long *ties = nullptr;
-    size_t cap_L = 0, cap_priors = 0, cap_blk_v = 0, cap_rows = 0, cap_blk_i = 0, cap_run = 0,
-           cap_br = 0, cap_ties = 0;
+    size_t cap_L = 0, cap_priors = 0, cap_blk_v = 0, cap_rows = 0, cap_run = 0;
     unsigned char *host = nullptr;   // pinned staging: priors on the way in, results on the way out
     size_t cap_host = 0;
     void release()
     {
         if (host) (void)hipHostFree(host);
-        (void)hipFree(L); (void)hipFree(priors); (void)hipFree(blk_v); (void)hipFree(rows);
-        (void)hipFree(blk_i); (void)hipFree(run); (void)hipFree(br); (void)hipFree(ties);
+        (void)hipFree(L); (void)hipFree(priors); (void)hipFree(blk_v); (void)hipFree(rows); (void)hipFree(run);
     }
 };
 
@@ -372,11 +367,11 @@ hipError_t launch_rows(bsse_game *g, const SweepArgs &a, hipStream_t stream)
 // Workgroups of such a launch of one candidate block that set a completion flag.
 int row_flags(const bsse_game *g) { return on_any(g) ? any_slices(g->view, 1) : mfma_slices(g->view, 1); }
 
-// Per-candidate outputs (a.V_out, a.br_out [count][K], a.l_out [count][K]; each nullable).
+// Per-candidate outputs (a.V_out, a.br_out [count][K], a.l_out with the caller's strides; each nullable).
 bsse_status launch_eval(bsse_game *g, SweepArgs a)
 {
+    a.br_sc = g->K; a.br_st = 1;
     if (!cuts_types(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
-    a.br_sc = g->K; a.br_st = 1; a.l_sc = g->K; a.l_st = 1;
     if (!a.V_out && (a.l_out || on_any(g))) { HIP_TRY(launch_rows(g, a, g->stream)); return BSSE_OK; }
     if (a.l_out || !few_rows(g, a.count)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
     bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float));
@@ -1508,72 +1503,55 @@ extern "C" bsse_status bsse_sweep_priors(bsse_game *g, const float *candidates_d
     long long chunk = (1LL << 28) / K;
     if (chunk < 4096) chunk = 4096;
     if (chunk > count) chunk = count;
-    const int nblocks = prior_batch_blocks(chunk, P);
+    const long long ld = (chunk + 3) & ~3LL;
+    const int ldp = prior_batch_ld(P);
     PriorScratch &w = g->pri;
-    auto grow = [&](void **ptr, size_t *cap, size_t bytes) -> bsse_status {
-        if (bytes <= *cap) return BSSE_OK;
-        HIP_TRY(hipStreamSynchronize(g->stream));      // nothing enqueued may still use the old block
-        (void)hipFree(*ptr);
-        *ptr = nullptr; *cap = 0;
-        HIP_TRY(hipMalloc(ptr, bytes));
-        *cap = bytes;
-        return BSSE_OK;
-    };
-    if ((st = grow((void **)&w.L, &w.cap_L, (size_t)chunk * K * sizeof(float))) != BSSE_OK) return st;
-    if ((st = grow((void **)&w.priors, &w.cap_priors, (size_t)P * K * sizeof(float))) != BSSE_OK) return st;
-    if ((st = grow((void **)&w.blk_v, &w.cap_blk_v, (size_t)nblocks * P * sizeof(float))) != BSSE_OK) return st;
-    if ((st = grow((void **)&w.blk_i, &w.cap_blk_i, (size_t)nblocks * P * sizeof(long long))) != BSSE_OK) return st;
-    if ((st = grow((void **)&w.run, &w.cap_run, (size_t)P * sizeof(PriorBest))) != BSSE_OK) return st;
-    if ((st = grow((void **)&w.rows, &w.cap_rows, (size_t)P * m * sizeof(float))) != BSSE_OK) return st;
-    if ((st = grow((void **)&w.br, &w.cap_br, (size_t)P * K * sizeof(int32_t))) != BSSE_OK) return st;
-    if ((st = grow((void **)&w.ties, &w.cap_ties, sizeof(unsigned long long))) != BSSE_OK) return st;
-    // pinned staging, so that the copies below are asynchronous and the call waits once, at the end
-    const size_t in_bytes = (size_t)P * K * sizeof(float);
-    const size_t off_run = 0, off_br = (size_t)P * sizeof(PriorBest), off_ties = off_br + (size_t)P * K * sizeof(int32_t);
-    const size_t out_bytes = off_ties + sizeof(unsigned long long);
-    const size_t host_bytes = in_bytes > out_bytes ? in_bytes : out_bytes;
-    if (host_bytes > w.cap_host) {
-        HIP_TRY(hipStreamSynchronize(g->stream));
-        if (w.host) (void)hipHostFree(w.host);
-        w.host = nullptr; w.cap_host = 0;
-        if (hipHostMalloc((void **)&w.host, host_bytes, hipHostMallocDefault) != hipSuccess)
-            return fail(BSSE_ENOMEM, "hipHostMalloc of %zu bytes failed", host_bytes);
-        w.cap_host = host_bytes;
+    // transposed priors, then the tie counter (zero), in one block each in pinned and in device memory
+    const size_t in_words = ((size_t)K * ldp + 1) / 2 * 2, in_bytes = in_words * 4 + sizeof(unsigned long long);
+    if ((st = grow_device(g, (void **)&w.L, &w.cap_L, (size_t)ld * K * sizeof(float))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.priors, &w.cap_priors, in_bytes)) != BSSE_OK) return st;
+    // (a last, shorter chunk is cut no finer than the others: one record per 1024 candidates at most)
+    if ((st = grow_device(g, (void **)&w.blk_v, &w.cap_blk_v, (size_t)1024 * P * sizeof(float))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.run, &w.cap_run, (size_t)P * sizeof(PriorBest))) != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&w.rows, &w.cap_rows, (size_t)P * m * sizeof(float))) != BSSE_OK) return st;
+    const size_t off_run = (in_bytes + 15) / 16 * 16, off_ties = off_run + (size_t)P * sizeof(PriorBest), off_br = off_ties + 16;
+    if ((st = grow_pinned(g, (void **)&w.host, &w.cap_host, off_br + (size_t)P * K * sizeof(int32_t))) != BSSE_OK) return st;
+    float *priT = reinterpret_cast<float *>(w.host);
+    for (int t = 0; t < K; ++t) {
+        for (int p = 0; p < P; ++p) priT[(size_t)t * ldp + p] = priors[(size_t)p * K + t];
+        for (int p = P; p < ldp; ++p) priT[(size_t)t * ldp + p] = 0.0f;
     }
-    memcpy(w.host, priors, in_bytes);
-    HIP_TRY(hipMemcpyAsync(w.priors, w.host, in_bytes, hipMemcpyHostToDevice, g->stream));
-    HIP_TRY(launch_clear_u64(w.ties, g->stream));                // a counter of its own
+    memset(w.host + in_words * 4, 0, sizeof(unsigned long long));
+    HIP_TRY(launch_copy_words(w.host, w.priors, in_bytes / 4, g->stream));
+    auto *ties_dev = reinterpret_cast<unsigned long long *>(w.priors + in_words);
+    auto *run = reinterpret_cast<PriorBest *>(w.host + off_run);
+    auto *ties = reinterpret_cast<unsigned long long *>(w.host + off_ties);
+    auto *br = reinterpret_cast<int32_t *>(w.host + off_br);
     for (long long base = 0; base < count; base += chunk) {
         const long long rows = count - base < chunk ? count - base : chunk;
         SweepArgs a{};
         a.X = candidates_dev + base * m; a.count = rows; a.index_base = base;
-        a.l_out = w.L; a.tie_counter = w.ties;
+        a.l_out = w.L; a.l_sc = 1; a.l_st = ld; a.tie_counter = ties_dev;
         if ((st = launch_eval(g, a)) != BSSE_OK) return st;
-        HIP_TRY(launch_prior_batch(w.L, rows, base, K, w.priors, P, base == 0 ? 1 : 0, w.blk_v, w.blk_i,
-                                   w.run, g->stream));
+        PriorFoldArgs f{};
+        f.L = w.L; f.count = (unsigned)rows; f.ld = (unsigned)ld; f.K = K; f.priT = w.priors; f.index_base = base;
+        f.first = base == 0 ? 1 : 0; f.run = w.run; f.m = m;
+        if (base + rows == count) {
+            f.rows = w.rows; f.X = candidates_dev; f.run_host = run; f.ties = ties_dev; f.ties_host = ties;
+        }
+        HIP_TRY(launch_prior_batch(f, P, w.blk_v, g->stream));
     }
     // best responses of the P winners: their rows, evaluated once more with per-candidate outputs
-    HIP_TRY(launch_gather_rows(candidates_dev, w.run, P, m, w.rows, g->stream));
-    {
-        SweepArgs a{};
-        a.X = w.rows; a.count = P; a.index_base = 0; a.br_out = w.br;
-        if ((st = launch_eval(g, a)) != BSSE_OK) return st;
-    }
-    // (the staging buffer is free again once the copy of the priors has run: same stream)
-    HIP_TRY(hipMemcpyAsync(w.host + off_run, w.run, (size_t)P * sizeof(PriorBest), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipMemcpyAsync(w.host + off_br, w.br, (size_t)P * K * sizeof(int32_t), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipMemcpyAsync(w.host + off_ties, w.ties, sizeof(unsigned long long), hipMemcpyDeviceToHost, g->stream));
-    HIP_TRY(hipStreamSynchronize(g->stream));
-    const PriorBest *run = reinterpret_cast<const PriorBest *>(w.host + off_run);
-    unsigned long long ties = 0;
-    memcpy(&ties, w.host + off_ties, sizeof(ties));
+    int flags = 0;
+    if ((st = launch_winners(g, w.rows, P, br, true, &flags)) != BSSE_OK) return st;
+    if ((st = wait_winners(g, flags)) != BSSE_OK) return st;
     for (int p = 0; p < P; ++p) {
         res[p].best_value = run[p].has ? (double)run[p].value : 0.0;
         res[p].best_index = run[p].has ? (int64_t)run[p].index : -1;
         res[p].n_evals = (int64_t)count * K;
-        res[p].n_tie_evals = (int64_t)ties;
+        res[p].n_tie_evals = (int64_t)*ties;
     }
-    if (best_response_out) memcpy(best_response_out, w.host + off_br, (size_t)P * K * sizeof(int32_t));
+    if (best_response_out) memcpy(best_response_out, br, (size_t)P * K * sizeof(int32_t));
     return BSSE_OK;
 }
 

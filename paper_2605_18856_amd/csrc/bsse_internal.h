@@ -105,8 +105,8 @@ struct SweepArgs {
     // host, which sum l_out in type order (term by term the sum of the unsliced kernel).
     float *l_out;
     int slice_stages;        // LDS stages (any-shape kernel: units) per slice (set by the launcher)
-    // Any-shape kernel and sliced instantiation of the general one: l_out / br_out element (c, t) sits
-    // at c * _sc + t * _st.
+    // l_out / br_out element (c, t) sits at c * _sc + t * _st (unsliced general and wide kernel: br_out
+    // at c * K + t).
     long long l_sc, l_st, br_sc, br_st;
     Done done;               // evaluation mode: a flag per workgroup (blockIdx.y * gridDim.x + blockIdx.x)
     // Any-shape kernel, one row (count == 1): with fold_n > 0 the row is the winner of fold_n
@@ -222,15 +222,31 @@ hipError_t launch_clear_u64(unsigned long long *p, hipStream_t s);
 // Zero `bytes` (a multiple of 16) at the 16-byte aligned device address p, by a kernel.
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 
-// Prior batch (see prior_batch.hip): V_p[c] = sum_t priors[p][t] * L[c][t] and the arg-max over c
-// for each of P priors, merged into run[P] (first != 0: replaced).  blk_v / blk_i: workspace of
-// prior_batch_blocks(count, P) * P records.
+// Prior batch (see prior_batch.hip): V_p[c] = sum_t priT[t][p] * L[t][c] and the arg-max over c for each
+// of P priors, merged into run[P].
+struct PriorFoldArgs {
+    const float *L;          // [K][ld], 16-byte aligned, readable up to the next multiple of four of count
+    unsigned count, ld;      // ld: a multiple of four
+    int K;
+    const float *priT;       // [K][prior_batch_ld(P)], zero from P on
+    long long index_base;
+    int first;               // != 0: run is replaced, not merged
+    PriorBest *run;          // [P]
+    float *rows;             // last launch of a batch (else nullptr): [P][m] rows of the running bests,
+    const float *X;          // out of these,
+    int m;
+    PriorBest *run_host;     // the running bests once more,
+    const unsigned long long *ties;
+    unsigned long long *ties_host;   // and the tie count
+    // set by the launcher
+    const float *blk_v;      // [P][nblocks]
+    unsigned slice, nblocks;
+    int ldp;
+};
 int prior_batch_blocks(long long count, int P);
-hipError_t launch_prior_batch(const float *L, long long count, long long index_base, int K,
-                              const float *priors_dev, int P, int first, float *blk_v,
-                              long long *blk_i, PriorBest *run, hipStream_t s);
-hipError_t launch_gather_rows(const float *X, const PriorBest *run, int P, int m, float *rows,
-                              hipStream_t s);
+int prior_batch_ld(int P);
+// blk_v: workspace of prior_batch_blocks(a.count, P) * P records.
+hipError_t launch_prior_batch(PriorFoldArgs a, int P, float *blk_v, hipStream_t s);
 
 // Top-k reduction (see topk.hip) of `sets` sets of `count` values each, one behind the other, over the
 // rows X in the same order: the k <= min(256, count) best of each set, best first.

@@ -1,253 +1,218 @@
 // Prior-robustness batch: the sweep for P priors at once.
 //
 // A follower's best response does not depend on the prior, so the leader payoffs at the best
-// responses, L[c][t] = l_t[j*_t(x_c)], are computed once by the sweep kernels (evaluation mode
-// with the per-type output) and every prior p only needs
-//     V_p[c] = sum_t P[p][t] * L[c][t]        (fp32 fused multiply-adds, t ascending)
-// and an arg-max over c (greatest value, lowest index).  Here priors sit on the lanes: lane
-// (p, s) carries prior p of the current group of up to 64 priors and candidate stream s, keeps a
-// running best over its candidates, and the streams, wavefronts and workgroups are folded at the
-// end, so the per-candidate cost is K multiply-adds per 64 priors.  The rows of L reach the
-// lanes through LDS (coalesced copy of a tile, then broadcast reads).
+// responses, L[t][c] = l_t[j*_t(x_c)], are computed once by the sweep kernels (evaluation mode
+// with the per-type output, type-major) and every prior p only needs
+//     V_p[c] = sum_t P[p][t] * L[t][c]        (fp32 fused multiply-adds, t ascending)
+// and an arg-max over c (greatest value, lowest index).
+//
+// Candidates sit on the lanes, four consecutive ones in each, and PB_G priors are worked on at once: the
+// payoffs come in as one 16-byte load per type and lane, the priors through scalar loads, and a step of
+// t is 4 PB_G independent multiply-adds.  Nothing goes through LDS.  Only the greatest value is kept (two
+// three-operand maxima per four candidates); the fold finds the lowest workgroup that reached it and
+// looks its candidate up again, among the PB_SLICE that workgroup had.  Bound by the vector unit:
+// 2^20 candidates, K = 4, 101 priors: 22 us of the 12 that the multiply-adds alone take at one per lane
+// and four cycles; with priors on the lanes and rows broadcast from LDS it was 52.
 #include "bsse_internal.h"
+#include "mfma_device.h"
 #include <limits.h>
 
 namespace bsse {
 
 namespace {
 
-constexpr int PB_WAVES = 4;
+constexpr int PB_T = 256;
+constexpr int PB_G = 16;                 // priors per workgroup
+constexpr int PB_STEP = 4 * PB_T;        // candidates per step of a workgroup
 
-__device__ __forceinline__ bool pb_better(float v, long long i, float bv, long long bi)
+// priT: [K][P rounded up to PB_G].  blk_v: [P][gridDim.x] greatest values.  `slice` candidates per
+// workgroup (a multiple of PB_STEP); L rows `ld` apart (a multiple of four, the rows 16-byte aligned).
+// KT: K when it is 4 (the priors then stay in scalar registers), else 0.
+template <int KT>
+__global__ void __launch_bounds__(PB_T, 4)
+prior_batch_kernel(const float *__restrict__ L, unsigned count, unsigned ld, int K_, const float *__restrict__ priT, int P,
+                   unsigned slice, float *__restrict__ blk_v)
 {
-    return v > bv || (v == bv && i < bi);
-}
-
-// blk_v / blk_i: [gridDim.x][P] records.  pri_lds != 0: the group's priors are staged in LDS as
-// [t][64]; otherwise they are read from global memory.
-__global__ void __launch_bounds__(PB_WAVES * 64)
-prior_batch_kernel(const float *__restrict__ L, long long count, long long index_base, int K,
-                   const float *__restrict__ priors, int P, int log2_pp, int pri_lds, int tile_rows,
-                   float *__restrict__ blk_v, long long *__restrict__ blk_i)
-{
-    extern __shared__ __attribute__((aligned(16))) float pri[];   // [K][64] when pri_lds, then a tile of rows
-    __shared__ float sv[PB_WAVES][64];
-    __shared__ long long si[PB_WAVES][64];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int pp = 1 << log2_pp;                         // priors per wavefront (power of two <= 64)
-    const int streams = 64 >> log2_pp;                   // candidate streams per wavefront
-    const int pl = lane & (pp - 1), s = lane >> log2_pp;
-    const long long wave_id = (long long)blockIdx.x * PB_WAVES + wave;
-    const long long step = (long long)gridDim.x * PB_WAVES * streams;
-
-    for (int p0 = 0; p0 < P; p0 += pp) {
-        const int p = p0 + pl;
-        const bool live = p < P;
-        if (pri_lds) {
-            __syncthreads();                             // the previous group's readers are done
-            for (int e = tid; e < K * 64; e += PB_WAVES * 64) {
-                const int t = e >> 6, q = e & 63;
-                pri[e] = (q < pp && p0 + q < P) ? priors[(size_t)(p0 + q) * K + t] : 0.0f;
+    __shared__ float sv[PB_T / 64][PB_G];
+    const int K = KT ? KT : K_;
+    const unsigned tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int p0 = (int)blockIdx.y * PB_G, ldp = (P + PB_G - 1) / PB_G * PB_G;
+    const unsigned first = blockIdx.x * slice, end = first + slice < count ? first + slice : count;
+    float best[PB_G];
+#pragma unroll
+    for (int p = 0; p < PB_G; ++p) best[p] = -INFINITY;
+    for (unsigned c = first + 4 * tid; c < end; c += PB_STEP) {
+        float v[PB_G][4];
+        const float *col = L + c;
+        const float *pr = priT + p0;
+        {
+            const float4 l = *reinterpret_cast<const float4 *>(col);
+#pragma unroll
+            for (int p = 0; p < PB_G; ++p) {
+                const float w = pr[p];
+                v[p][0] = w * l.x; v[p][1] = w * l.y; v[p][2] = w * l.z; v[p][3] = w * l.w;
             }
-            __syncthreads();
         }
-        float bv = -INFINITY;
-        long long bi = LLONG_MAX;
-        if (pri_lds && (K & 3) == 0) {
-            // Rows go through LDS: the workgroup copies a tile of `tile_rows` rows with coalesced
-            // 16-byte loads (every lane a different piece), and the wavefronts then read each row
-            // as a broadcast from LDS, which costs the vector unit nothing.  (Loading the row a
-            // wavefront works on straight from memory makes all 64 lanes fetch the same 16 bytes;
-            // few such loads are in flight and the kernel sat waiting for memory.)
-            float *rows = pri + K * 64;
-            const int K4 = K >> 2;
-            const long long ntiles = (count + tile_rows - 1) / tile_rows;
-            int bo = -1;                                 // row of the lane's best so far (count <= 2^31)
-            float q[16];                                 // the lane's prior, when K <= 16
+        auto types = [&](int t) __attribute__((always_inline)) {
+            const float4 l = *reinterpret_cast<const float4 *>(col + (size_t)t * ld);
 #pragma unroll
-            for (int t = 0; t < 16; ++t) q[t] = t < K ? pri[t * 64 + pl] : 0.0f;
-            for (long long tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-                const long long r0 = tile * tile_rows;
-                const int nr = (int)(count - r0 < tile_rows ? count - r0 : tile_rows);
-                __syncthreads();                         // the previous tile's readers are done
-                {
-                    const float4 *src = reinterpret_cast<const float4 *>(L + r0 * K);
-                    float4 *dst = reinterpret_cast<float4 *>(rows);
-                    for (int e = tid; e < nr * K4; e += PB_WAVES * 64) dst[e] = src[e];
-                }
-                __syncthreads();
-                // wavefront `wave`, stream s takes rows wave*streams + s, + PB_WAVES*streams, ...
-                // (a NaN value never passes "v > best", so it needs no special case here)
-                const int rstep = PB_WAVES * streams;
-                int r = wave * streams + s;
-                if (K4 <= 4) {
-                    // the lane's prior in registers; four rows per trip
-                    auto value = [&](int rr) __attribute__((always_inline)) {
-                        const float4 *row = reinterpret_cast<const float4 *>(rows + (size_t)rr * K);
-                        float v = 0.0f;
-#pragma unroll
-                        for (int t4 = 0; t4 < 4; ++t4) {
-                            if (t4 >= K4) break;
-                            const float4 l = row[t4];
-                            v = fmaf(q[4 * t4], l.x, v); v = fmaf(q[4 * t4 + 1], l.y, v);
-                            v = fmaf(q[4 * t4 + 2], l.z, v); v = fmaf(q[4 * t4 + 3], l.w, v);
-                        }
-                        return v;
-                    };
-                    for (; r + 3 * rstep < nr; r += 4 * rstep) {
-                        const float v0 = value(r), v1 = value(r + rstep), v2 = value(r + 2 * rstep),
-                                    v3 = value(r + 3 * rstep);
-                        if (v0 > bv) { bv = v0; bo = (int)r0 + r; }
-                        if (v1 > bv) { bv = v1; bo = (int)r0 + r + rstep; }
-                        if (v2 > bv) { bv = v2; bo = (int)r0 + r + 2 * rstep; }
-                        if (v3 > bv) { bv = v3; bo = (int)r0 + r + 3 * rstep; }
-                    }
-                    for (; r < nr; r += rstep) {
-                        const float v = value(r);
-                        if (v > bv) { bv = v; bo = (int)r0 + r; }
-                    }
-                } else {
-                    for (; r < nr; r += rstep) {
-                        const float4 *row = reinterpret_cast<const float4 *>(rows + (size_t)r * K);
-                        float v = 0.0f;
-                        for (int t4 = 0; t4 < K4; ++t4) {
-                            const float4 l = row[t4];
-                            v = fmaf(pri[(4 * t4) * 64 + pl], l.x, v);
-                            v = fmaf(pri[(4 * t4 + 1) * 64 + pl], l.y, v);
-                            v = fmaf(pri[(4 * t4 + 2) * 64 + pl], l.z, v);
-                            v = fmaf(pri[(4 * t4 + 3) * 64 + pl], l.w, v);
-                        }
-                        if (v > bv) { bv = v; bo = (int)r0 + r; }
-                    }
-                }
+            for (int p = 0; p < PB_G; ++p) {
+                const float w = pr[t * ldp + p];
+                v[p][0] = fmaf(w, l.x, v[p][0]); v[p][1] = fmaf(w, l.y, v[p][1]);
+                v[p][2] = fmaf(w, l.z, v[p][2]); v[p][3] = fmaf(w, l.w, v[p][3]);
             }
-            if (live && bo >= 0) bi = index_base + bo;
-            if (!live) bv = -INFINITY;
+        };
+        if constexpr (KT != 0) {
+#pragma unroll
+            for (int t = 1; t < KT; ++t) types(t);
         } else {
-            const long long c_first = wave_id * streams + s;
-            for (long long c = c_first; c < count; c += step) {
-                const float *row = L + c * K;
-                float v = 0.0f;
-                if (pri_lds) {
-                    for (int t = 0; t < K; ++t) v = fmaf(pri[t * 64 + pl], row[t], v);
-                } else if (live) {
-                    const float *pr = priors + (size_t)p * K;
-                    for (int t = 0; t < K; ++t) v = fmaf(pr[t], row[t], v);
-                }
-                if (!(v == v)) v = -INFINITY;
-                if (live && v > bv) { bv = v; bi = index_base + c; }   // a lane's candidates ascend
-            }
+#pragma unroll 2
+            for (int t = 1; t < K; ++t) types(t);
         }
-        // fold the streams of the wavefront, then the wavefronts
-        for (int d = pp; d < 64; d <<= 1) {
-            const float ov = __shfl_xor(bv, d, 64);
-            const long long oi = __shfl_xor(bi, d, 64);
-            if (pb_better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        if (c + 3 >= count) {                            // (what lies behind the last candidate of a row of L)
+#pragma unroll
+            for (int p = 0; p < PB_G; ++p)
+#pragma unroll
+                for (unsigned q = 1; q < 4; ++q) v[p][q] = c + q < count ? v[p][q] : -INFINITY;
         }
-        sv[wave][lane] = bv; si[wave][lane] = bi;
-        __syncthreads();
-        if (wave == 0 && lane < pp && live) {
-            for (int w = 1; w < PB_WAVES; ++w)
-                if (pb_better(sv[w][lane], si[w][lane], bv, bi)) { bv = sv[w][lane]; bi = si[w][lane]; }
-            blk_v[(size_t)blockIdx.x * P + p] = bv;
-            blk_i[(size_t)blockIdx.x * P + p] = bi;
+        // (a maximum never is a value that is not a number)
+#pragma unroll
+        for (int p = 0; p < PB_G; ++p) best[p] = vmax3(vmax3(best[p], v[p][0], v[p][1]), v[p][2], v[p][3]);
+    }
+    // The wavefront's maxima of all priors together: in each of the first four steps a lane gives away the
+    // half of its priors that its partner keeps (17 exchanges instead of 6 per prior); lane l ends with
+    // prior l / 4.
+    static_assert(PB_G == 16, "sixteen priors over sixteen groups of four lanes");
+#pragma unroll
+    for (int h = PB_G / 2; h >= 1; h >>= 1) {
+        const bool upper = (lane & (4u * h)) != 0u;
+#pragma unroll
+        for (int p = 0; p < h; ++p) {
+            const float keep = upper ? best[p + h] : best[p], give = upper ? best[p] : best[p + h];
+            best[p] = vmax2(keep, __shfl_xor(give, 4 * h, 64));
         }
-        __syncthreads();
+    }
+    best[0] = vmax2(best[0], __shfl_xor(best[0], 2, 64));
+    best[0] = vmax2(best[0], __shfl_xor(best[0], 1, 64));
+    if ((lane & 3) == 0) sv[wave][lane >> 2] = best[0];
+    __syncthreads();
+    if (tid < PB_G && p0 + (int)tid < P) {
+        float b = sv[0][tid];
+#pragma unroll
+        for (int w = 1; w < PB_T / 64; ++w) b = vmax2(b, sv[w][tid]);
+        blk_v[(size_t)(p0 + tid) * gridDim.x + blockIdx.x] = b;
     }
 }
 
-// One workgroup per prior folds the records of all workgroups and merges into the running best
-// of that prior (greater value, then lower index).
-__global__ void __launch_bounds__(256)
-prior_fold_kernel(const float *__restrict__ blk_v, const long long *__restrict__ blk_i, int nblocks,
-                  int P, int first, PriorBest *__restrict__ run)
+// One workgroup per prior: the greatest value of its records, the lowest workgroup that reached it, and
+// the lowest candidate of that workgroup that has it (the same sum once more); merged into the running
+// best of the prior (greater value, then lower index; first != 0: replaced).  With rows: also the
+// row of the running best (row 0 if there is none), and everything to pinned host memory.
+__global__ void __launch_bounds__(PB_T) prior_fold_kernel(PriorFoldArgs a)
 {
-    __shared__ float sv[4];
-    __shared__ long long si[4];
-    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float sv[PB_T / 64];
+    __shared__ unsigned sb[PB_T / 64];
+    __shared__ long long win;
+    const unsigned p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     float bv = -INFINITY;
-    long long bi = LLONG_MAX;
-    for (int b = tid; b < nblocks; b += 256) {
-        const float v = blk_v[(size_t)b * P + p];
-        const long long i = blk_i[(size_t)b * P + p];
-        if (pb_better(v, i, bv, bi)) { bv = v; bi = i; }
+    unsigned bb = 0xFFFFFFFFu;
+    for (unsigned b = tid; b < a.nblocks; b += PB_T) {
+        const float v = a.blk_v[(size_t)p * a.nblocks + b];
+        if (v > bv) { bv = v; bb = b; }
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         const float ov = __shfl_xor(bv, d, 64);
-        const long long oi = __shfl_xor(bi, d, 64);
-        if (pb_better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+        const unsigned ob = __shfl_xor(bb, d, 64);
+        if (ov > bv || (ov == bv && ob < bb)) { bv = ov; bb = ob; }
     }
-    if (lane == 0) { sv[wave] = bv; si[wave] = bi; }
+    if (lane == 0) { sv[wave] = bv; sb[wave] = bb; }
+    __syncthreads();
+    bv = sv[0]; bb = sb[0];
+#pragma unroll
+    for (int w = 1; w < PB_T / 64; ++w)
+        if (sv[w] > bv || (sv[w] == bv && sb[w] < bb)) { bv = sv[w]; bb = sb[w]; }
+    // the candidate: no workgroup, none
+    unsigned bc = 0xFFFFFFFFu;
+    if (bb != 0xFFFFFFFFu) {
+        const unsigned first = bb * a.slice, end = first + a.slice < a.count ? first + a.slice : a.count;
+        for (unsigned c = first + 4 * tid; c < end; c += PB_STEP) {
+            float v[4] = { 0.0f, 0.0f, 0.0f, 0.0f };
+#pragma unroll 4
+            for (int t = 0; t < a.K; ++t) {
+                const float4 l = *reinterpret_cast<const float4 *>(a.L + (size_t)t * a.ld + c);
+                const float w = a.priT[(size_t)t * a.ldp + p];
+                v[0] = fmaf(w, l.x, v[0]); v[1] = fmaf(w, l.y, v[1]); v[2] = fmaf(w, l.z, v[2]); v[3] = fmaf(w, l.w, v[3]);
+            }
+#pragma unroll
+            for (int q = 3; q >= 0; --q)
+                if (v[q] == bv && c + q < a.count && c + q < bc) bc = c + q;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const unsigned oc = __shfl_xor(bc, d, 64);
+        bc = oc < bc ? oc : bc;
+    }
+    if (lane == 0) sb[wave] = bc;
     __syncthreads();
     if (tid == 0) {
-        for (int w = 1; w < 4; ++w)
-            if (pb_better(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
-        PriorBest r = run[p];
-        if (first) { r.value = 0.0f; r.has = 0; r.index = -1; }
-        if (bi != LLONG_MAX && (!r.has || bv > r.value || (bv == r.value && bi < r.index))) {
-            r.value = bv; r.index = bi; r.has = 1;
+        for (int w = 1; w < PB_T / 64; ++w) bc = sb[w] < bc ? sb[w] : bc;
+        PriorBest r = a.run[p];
+        if (a.first) { r.value = 0.0f; r.has = 0; r.index = -1; }
+        if (bc != 0xFFFFFFFFu && (!r.has || bv > r.value || (bv == r.value && a.index_base + bc < r.index))) {
+            r.value = bv; r.index = a.index_base + bc; r.has = 1;
         }
-        run[p] = r;
+        a.run[p] = r;
+        if (a.rows) {
+            a.run_host[p] = r;
+            if (p == 0) *a.ties_host = *a.ties;
+        }
+        win = r.has ? r.index : 0;
     }
+    if (!a.rows) return;
+    __syncthreads();
+    for (int i = tid; i < a.m; i += PB_T) a.rows[(size_t)p * a.m + i] = a.X[win * a.m + i];
 }
 
-// rows[p][0..m) = X[index of prior p's winner] (row 0 when a prior has none)
-__global__ void gather_rows_kernel(const float *__restrict__ X, const PriorBest *__restrict__ run,
-                                   int P, int m, float *__restrict__ rows)
+// Candidates per workgroup.  Every workgroup ends with PB_G wavefront reductions, about as much work as
+// three steps at K = 4: four steps where that still leaves a grid of twice the resident set
+// (256 compute units, four workgroups each), down to one for fewer candidates; more for many, so that
+// the fold has no more than 1024 records per prior.
+unsigned pb_slice(long long count, int P)
 {
-    const int p = blockIdx.x;
-    const long long c = run[p].has ? run[p].index : 0;
-    for (int i = threadIdx.x; i < m; i += blockDim.x) rows[(size_t)p * m + i] = X[c * m + i];
+    const long long groups = (P + PB_G - 1) / PB_G;
+    long long steps = count * groups / (2048LL * PB_STEP);
+    if (steps < 1) steps = 1;
+    if (steps > 4) steps = 4;
+    const long long least = (count + 1024LL * PB_STEP - 1) / (1024LL * PB_STEP);
+    if (steps < least) steps = least;
+    return (unsigned)(steps * PB_STEP);
 }
 
 }  // namespace
 
 int prior_batch_blocks(long long count, int P)
 {
-    int pp = 1;
-    while (pp < P && pp < 64) pp <<= 1;
-    const long long per_wg = (long long)PB_WAVES * (64 / pp);
-    long long need = (count + per_wg - 1) / per_wg;
-    // a few passes per lane amortise the fold; never more than one resident set
-    need = (need + 7) / 8;
-    if (need < 1) need = 1;
-    return (int)(need < 1024 ? need : 1024);
+    const long long slice = pb_slice(count, P);
+    return (int)((count + slice - 1) / slice);
 }
+int prior_batch_ld(int P) { return (P + PB_G - 1) / PB_G * PB_G; }
 
-hipError_t launch_prior_batch(const float *L, long long count, long long index_base, int K,
-                              const float *priors_dev, int P, int first, float *blk_v,
-                              long long *blk_i, PriorBest *run, hipStream_t s)
+hipError_t launch_prior_batch(PriorFoldArgs a, int P, float *blk_v, hipStream_t s)
 {
-    if (count <= 0 || P <= 0) return hipSuccess;
-    int log2_pp = 0;
-    while ((1 << log2_pp) < P && log2_pp < 6) ++log2_pp;
-    const int blocks = prior_batch_blocks(count, P);
-    const size_t lds_pri = (size_t)K * 64 * sizeof(float);
-    const int pri_lds = lds_pri <= 96 * 1024 ? 1 : 0;
-    // a tile of rows of about 8 KiB: small enough that the tiles outnumber the workgroups
-    int tile_rows = 2048 / K;
-    if (tile_rows < 4) tile_rows = 4;
-    const size_t lds = pri_lds ? lds_pri + (size_t)tile_rows * K * sizeof(float) : 0;
-    if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)prior_batch_kernel,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(prior_batch_kernel, dim3(blocks), dim3(PB_WAVES * 64), lds, s, L,
-                       count, index_base, K, priors_dev, P, log2_pp, pri_lds, tile_rows, blk_v, blk_i);
+    if (a.count == 0 || P <= 0) return hipSuccess;
+    if (a.ld % 4 != 0 || a.ld < a.count || ((uintptr_t)a.L & 15) != 0) return hipErrorInvalidValue;
+    a.slice = pb_slice(a.count, P);
+    a.nblocks = (unsigned)prior_batch_blocks(a.count, P);
+    a.ldp = prior_batch_ld(P);
+    a.blk_v = blk_v;
+    hipLaunchKernelGGL((a.K == 4 ? prior_batch_kernel<4> : prior_batch_kernel<0>), dim3(a.nblocks, (unsigned)(a.ldp / PB_G)), dim3(PB_T), 0, s, a.L, a.count, a.ld, a.K,
+                       a.priT, P, a.slice, blk_v);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(prior_fold_kernel, dim3(P), dim3(256), 0, s, blk_v, blk_i, blocks, P, first, run);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather_rows(const float *X, const PriorBest *run, int P, int m, float *rows,
-                              hipStream_t s)
-{
-    if (P <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(P), dim3(64), 0, s, X, run, P, m, rows);
+    hipLaunchKernelGGL(prior_fold_kernel, dim3(P), dim3(PB_T), 0, s, a);
     return hipGetLastError();
 }
 

@@ -78,7 +78,6 @@ __device__ __forceinline__ void small_body(const GameView &g, const SweepArgs &a
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, col = lane & 31;
-    const int K = g.K;
     const unsigned count = (unsigned)a.count;            // <= 2^31 per launch
 
     const unsigned per_iter = SM_NT * 32;
@@ -275,8 +274,8 @@ __device__ __forceinline__ void small_body(const GameView &g, const SweepArgs &a
                     vhalf[ct] = fmaf(prior[T][tl], l[ct][tl], vhalf[ct]);
                     if (EVAL) {
                         const unsigned c = first + ct * 32 + col;
-                        if (a.br_out && c < count) a.br_out[(size_t)c * K + 4 * T + 2 * h + tl] = (int32_t)idx[ct][tl];
-                        if (a.l_out && c < count) a.l_out[(size_t)c * K + 4 * T + 2 * h + tl] = l[ct][tl];
+                        if (a.br_out && c < count) a.br_out[c * a.br_sc + (4 * T + 2 * h + tl) * a.br_st] = (int32_t)idx[ct][tl];
+                        if (a.l_out && c < count) a.l_out[c * a.l_sc + (4 * T + 2 * h + tl) * a.l_st] = l[ct][tl];
                     }
                 }
         }
@@ -461,7 +460,7 @@ small_finish_kernel(GameView g, FinishArgs f)
         *f.win_v = r.value;
     }
     SweepArgs ev{};
-    ev.X = x; ev.count = 1; ev.br_out = f.win_br;
+    ev.X = x; ev.count = 1; ev.br_out = f.win_br; ev.br_sc = g.K; ev.br_st = 1;
     small_body<TILES, true, false>(g, ev, 0, 1);
     if (f.done.flag) signal_done(f.done, 0);
 }

@@ -110,8 +110,8 @@ __global__ void __launch_bounds__(WG) sweep_valu_kernel(GameView g, SweepArgs a)
         if (best_u == -INFINITY) tied = false;     // non-finite input: unspecified, not counted
         V = fmaf(g.prior[t], best_l, V);
         ties += tied ? 1u : 0u;
-        if (EVAL && valid && a.br_out) a.br_out[c * K + t] = best_j;
-        if (EVAL && valid && a.l_out) a.l_out[c * K + t] = best_l;
+        if (EVAL && valid && a.br_out) a.br_out[c * a.br_sc + t * a.br_st] = best_j;
+        if (EVAL && valid && a.l_out) a.l_out[c * a.l_sc + t * a.l_st] = best_l;
     }
     if (!(V == V)) V = -INFINITY;                  // NaN never wins
 
