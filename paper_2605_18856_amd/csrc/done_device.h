@@ -14,7 +14,10 @@ namespace bsse {
 // By every thread of the workgroup, when all of its results have been written.
 __device__ __forceinline__ void signal_done(const Done &d, unsigned slot)
 {
-    __threadfence_system();              // each thread's own results first
+    // Every wavefront's stores have left it; then one write-back of the caches and the flag.  (A system
+    // fence in every wavefront instead is a write-back each: 45 us instead of 27 for 256 workgroups of
+    // eight.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_store(d.flag + slot, d.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }

@@ -311,7 +311,6 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     constexpr int REP = TERMS == 3 ? 3 : 1;             // matrix instructions per fragment read
     constexpr int KF = KS / REP;                        // fragment k-steps per row tile
     constexpr int TILE_FRAGS = KF * 64;                 // fragments per row tile
-    static_assert(PF == 0 || REP == 1, "the chunked fragment read-ahead takes one instruction per fragment");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ float red_v[WAVES];
@@ -387,7 +386,11 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < HALF_BASE; ++e) vb[e] = h * HALF_BASE + e < m ? row[e] : 0.0f;
+            for (int e = 0; e < HALF_BASE; ++e) {            // (no branch: the first element stands in past m)
+                const bool in = h * HALF_BASE + e < m;
+                const float t = row[in ? e : -h * HALF_BASE];
+                vb[e] = in ? t : 0.0f;
+            }
         }
         if constexpr (TERMS == 1) {
             P::pack_x(vb, x[ct]);
@@ -510,7 +513,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     };
     // MFMAs of NTILES consecutive row tiles (fragments in LDS at `base`; tt0 = index of the first
     // one within the group) against all NT candidate tiles.  The fragment reads are software-
-    // pipelined in chunks of PF k-steps where that was measured to pay (the wide bf16 game): the
+    // pipelined in chunks of PF k-steps where that was measured to pay: the
     // reads of chunk q+1 are issued before the MFMAs of chunk q, so the LDS latency runs under the
     // matrix pipe instead of in front of it.
     auto mfma_run = [&](const frag *base, auto ntiles_c, auto tt0_c) __attribute__((always_inline)) {
@@ -529,9 +532,9 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 }
             return;
         }
-        static_assert(PF == 0 || KS % (PF ? PF : 1) == 0, "fragment chunk must divide the k-steps of a tile");
+        static_assert(PF == 0 || KF % (PF ? PF : 1) == 0, "fragment chunk must divide the k-steps of a tile");
         constexpr int C = PF ? PF : 1;
-        constexpr int NCH = NTILES * KS / C;
+        constexpr int NCH = NTILES * KF / C;
         frag fb[2][C];
         const frag *lane_base = base + lane;
 #pragma unroll
@@ -543,15 +546,18 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 for (int e = 0; e < C; ++e) {
                     constexpr int f0 = (q + 1) * C;
                     const int f = f0 + e;                                    // flat (tile, k-step)
-                    fb[(q + 1) & 1][e] = lane_base[(size_t)(f / KS) * TILE_FRAGS + (size_t)(f % KS) * 64];
+                    fb[(q + 1) & 1][e] = lane_base[(size_t)(f / KF) * TILE_FRAGS + (size_t)(f % KF) * 64];
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
             static_for<0, C, 1>([&](auto ec) {
                 constexpr int f = q * C + decltype(ec)::value;
-                constexpr int tt = TT0 + f / KS, ks = f % KS;
+                constexpr int tt = TT0 + f / KF, ks = f % KF;
 #pragma unroll
-                for (int ct = 0; ct < NT; ++ct) acc[ct][tt] = x_mfma(fb[q & 1][decltype(ec)::value], x[ct], ks, acc[ct][tt]);
+                for (int p = 0; p < REP; ++p)
+#pragma unroll
+                    for (int ct = 0; ct < NT; ++ct)
+                        acc[ct][tt] = x_mfma(fb[q & 1][decltype(ec)::value], x[ct], p * KF + ks, acc[ct][tt]);
             });
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -641,38 +647,36 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                         for (int k = 1; k + 1 < TPG; k += 2) pm = vmax3(pm, pmt[k], pmt[k + 1]);
                         pm = vmax2(pm, pmt[TPG - 1]);
                         gm = pair_max(pm);
-                        // Only a tile whose maximum is the pair's maximum can hold a maximiser.
-                        // Two such tiles in one lane are a tie (exact routine); otherwise the
-                        // tile's sixteen registers are selected (a tournament of conditional
-                        // moves, (TPG-1)*16 of them) and the compare pass runs on those alone:
-                        // (TPG-1)*16 + 32 instructions instead of TPG*32.
-                        bool e[TPG];
-                        unsigned tile[TPG];
+                        // The position from the element-wise maxima over the tiles (TPG / 2 three-operand
+                        // maxima per position), the tile from the tiles' own maxima.  Two tiles of one
+                        // lane with the pair's maximum are a tie (exact routine), as are two positions.
+                        // (Selecting the leading tile's sixteen values with conditional moves took
+                        // (TPG - 1) * 16 of them, those under vcc several times slower than the rest.)
+                        float w[16];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            w[r] = u[0][r];
+#pragma unroll
+                            for (int k = 1; k + 1 < TPG; k += 2) w[r] = vmax3(w[r], u[k][r], u[k + 1][r]);
+                            w[r] = vmax2(w[r], u[TPG - 1][r]);
+                        }
+                        unsigned tile = 0u;
                         unsigned long long seen = 0ull, dup = 0ull;
 #pragma unroll
                         for (int k = 0; k < TPG; ++k) {
-                            e[k] = pmt[k] == gm;
-                            tile[k] = (unsigned)k;
-                            const unsigned long long mk = __builtin_amdgcn_ballot_w64(e[k]);
+                            const bool e = pmt[k] == gm;
+                            const unsigned long long mk = __builtin_amdgcn_ballot_w64(e);
                             dup |= seen & mk;
                             seen |= mk;
+                            if (k) tile = e ? (unsigned)(32 * k) : tile;
                         }
                         tile_tie |= (unsigned)(dup | (dup >> 32));
-#pragma unroll
-                        for (int nn = TPG; nn > 1; nn >>= 1)
-#pragma unroll
-                            for (int j = 0; j < nn / 2; ++j) {
-#pragma unroll
-                                for (int r = 0; r < 16; ++r) u[j][r] = e[2 * j + 1] ? u[2 * j + 1][r] : u[2 * j][r];
-                                tile[j] = e[2 * j + 1] ? tile[2 * j + 1] : tile[2 * j];
-                                e[j] = e[2 * j] || e[2 * j + 1];
-                            }
-                        // compare pass as a bitmap: bit 15 - r set iff register r is a maximiser
-                        const unsigned w = bitmap16_split(u[0], gm);
-                        const unsigned cnt = (unsigned)__builtin_popcount(w);
-                        const unsigned r = ffbh(w) - 16u;
+                        // compare pass as a bitmap: bit 15 - r set iff position r holds the maximum
+                        const unsigned bm = bitmap16_pairs(w, gm);
+                        const unsigned cnt = (unsigned)__builtin_popcount(bm);
+                        const unsigned r = ffbh(bm) - 16u;
                         // action = 32 * tile + row(register) + 4h
-                        const unsigned act = (tile[0] << 5) | ((r & 0xCu) << 1) | (r & 3u) | (4u * h);
+                        const unsigned act = tile | ((r & 0xCu) << 1) | (r & 3u) | (4u * h);
                         total = cnt ? (cnt << 16) | act : 0u;
                     }
                 } else {
@@ -886,7 +890,11 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
                 }
             } else {
 #pragma unroll
-                for (int e = 0; e < HALF_BASE; ++e) vb[e] = h * HALF_BASE + e < m ? row[e] : 0.0f;
+                for (int e = 0; e < HALF_BASE; ++e) {
+                    const bool in = h * HALF_BASE + e < m;
+                    const float t = row[in ? e : -h * HALF_BASE];
+                    vb[e] = in ? t : 0.0f;
+                }
             }
             P::pack_x(vb, x[ps][ct]);
             valid32[ps][ct] = (unsigned)__builtin_amdgcn_ballot_w64(ok);
@@ -1187,7 +1195,9 @@ const Variant kVariants[] = {
     BSSE_VARIANT(__bf16, 2, 6, 32, 32, 2, 4, 1, 3, true, 0, "mfma_split6"),
     BSSE_VARIANT(__bf16, 2, 3, 32, 32, 4, 4, 4, 2, true, 0, "mfma_split3"),
     BSSE_VARIANT(__bf16, 2, 6, 32, 64, 2, 4, 2, 2, true, 0, "mfma_split6"),
-    BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 0, "mfma_split3"),
+    // (one fragment ahead: the next one's LDS read runs under three matrix instructions; 131072 rows of
+    // K = 256: 4290 -> 4190 us; two ahead spill)
+    BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 1, "mfma_split3"),
 };
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 constexpr int kSmallVariant = 1000;          // the small-game kernel (sweep_small.hip)
