@@ -298,10 +298,12 @@ bsse_status ensure_gen(bsse_game *g, unsigned long long rows)
     return BSSE_OK;
 }
 
+bool on_tiny(const bsse_game *g) { return g->path == PATH_VALU && g->view.variant == kTinyVariant; }
 bool on_any(const bsse_game *g) { return g->path != PATH_VALU && g->view.variant == kAnyVariant; }
 
 hipError_t launch_sweep_on(bsse_game *g, const SweepArgs &a, bool eval, hipStream_t stream)
 {
+    if (on_tiny(g)) return launch_sweep_tiny(g->view, a, eval, 1, TinyRecs{}, stream);
     if (g->path == PATH_VALU) return launch_sweep_valu(g->view, a, eval, stream);
     if (on_any(g)) return launch_sweep_any(g->view, a, 1, stream);
     (void)eval;
@@ -316,6 +318,7 @@ hipError_t launch_sweep(bsse_game *g, const SweepArgs &a, bool eval)
 long long sweep_blocks(const bsse_game *g, long long count)
 {
     if (on_any(g)) return any_num_blocks(g->view, count);
+    if (on_tiny(g)) return tiny_num_blocks(count);
     return g->path == PATH_VALU ? valu_num_blocks(count) : mfma_num_blocks(g->view.variant, count);
 }
 
@@ -350,29 +353,34 @@ constexpr long long ROW_SCRATCH_MAX = 1LL << 24;
 // Paths whose launches can be cut over the types, and whether `count` rows are few enough for it.
 bool cuts_types(const bsse_game *g)
 {
-    return on_any(g) || (g->path != PATH_VALU && !mfma_is_small(g->view.variant));
+    return on_any(g) || on_tiny(g) || (g->path != PATH_VALU && !mfma_is_small(g->view.variant));
 }
 bool few_rows(const bsse_game *g, long long count)
 {
     if (!cuts_types(g) || count * g->K > ROW_SCRATCH_MAX) return false;
-    return on_any(g) ? any_slices(g->view, count) > 1 : mfma_few_rows(g->view, count);
+    return on_any(g) ? any_slices(g->view, count) > 1
+           : on_tiny(g) ? tiny_slices(g->view, count) > 1 : mfma_few_rows(g->view, count);
 }
 
 // A launch cut over the types where that pays: a.l_out (and a.br_out) only.
 hipError_t launch_rows(bsse_game *g, const SweepArgs &a, hipStream_t stream)
 {
-    return on_any(g) ? launch_sweep_any(g->view, a, any_slices(g->view, a.count), stream)
-                     : launch_sweep_mfma(g->view, a, stream);
+    if (on_any(g)) return launch_sweep_any(g->view, a, any_slices(g->view, a.count), stream);
+    if (on_tiny(g)) return launch_sweep_tiny(g->view, a, true, tiny_slices(g->view, a.count), TinyRecs{}, stream);
+    return launch_sweep_mfma(g->view, a, stream);
 }
-// Workgroups of such a launch of one candidate block that set a completion flag.
-int row_flags(const bsse_game *g) { return on_any(g) ? any_slices(g->view, 1) : mfma_slices(g->view, 1); }
+// Workgroups of such a launch, each with a completion flag.
+long long row_blocks(const bsse_game *g, long long count)
+{
+    return on_any(g) ? any_row_blocks(g->view, count) : on_tiny(g) ? tiny_row_blocks(g->view, count) : mfma_row_blocks(g->view, count);
+}
 
 // Per-candidate outputs (a.V_out, a.br_out [count][K], a.l_out with the caller's strides; each nullable).
 bsse_status launch_eval(bsse_game *g, SweepArgs a)
 {
     a.br_sc = g->K; a.br_st = 1;
     if (!cuts_types(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
-    if (!a.V_out && (a.l_out || on_any(g))) { HIP_TRY(launch_rows(g, a, g->stream)); return BSSE_OK; }
+    if (!a.V_out && (a.l_out || on_any(g) || on_tiny(g))) { HIP_TRY(launch_rows(g, a, g->stream)); return BSSE_OK; }
     if (a.l_out || !few_rows(g, a.count)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
     bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float));
     if (st != BSSE_OK) return st;
@@ -427,13 +435,12 @@ bsse_status launch_winners(bsse_game *g, const float *X, long long rows, int32_t
     SweepArgs a{};
     a.X = X; a.count = rows;
     a.br_out = br; a.br_sc = g->K; a.br_st = 1;
-    const long long blocks = on_any(g) ? any_row_blocks(g->view, rows)
-                             : cuts_types(g) ? mfma_row_blocks(g->view, rows) : sweep_blocks(g, rows);
+    const long long blocks = cuts_types(g) ? row_blocks(g, rows) : sweep_blocks(g, rows);
     *flags = last && blocks <= MAX_FLAGS ? (int)blocks : 0;
     if (*flags) a.done = new_done(g);
     if (!cuts_types(g)) { a.V_out = V; HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
     a.l_out = l; a.l_sc = g->K; a.l_st = 1;
-    if (!on_any(g) && !l) {                      // (the general kernel is cut only when asked for leader payoffs)
+    if (!on_any(g) && !on_tiny(g) && !l) {       // (the general kernel is cut only when asked for leader payoffs)
         bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)rows * g->K * sizeof(float));
         if (st != BSSE_OK) return st;
         a.l_out = g->row_l;
@@ -626,8 +633,20 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     if (!dg.ok) { free_game(g); return fail(BSSE_EDEVICE, "hipSetDevice(%d) failed", dev); }
 
     // ---- vector path: pack on the host: optional bf16 rounding, B as given, A transposed per type
+    // (short rows: both transposed, padded with zeros)
     std::vector<float> hB, hAT;
-    if (!use_mfma) {
+    const int tiny = use_mfma ? 0 : tiny_pad(m);
+    if (tiny) {
+        g->view.variant = kTinyVariant;
+        hB.assign((size_t)K * n * tiny, 0.0f); hAT.assign((size_t)K * n * tiny, 0.0f);
+        for (int t = 0; t < K; ++t)
+            for (int i = 0; i < m; ++i)
+                for (int j = 0; j < n; ++j) {
+                    const size_t from = ((size_t)t * m + i) * n + j, to = ((size_t)t * n + j) * tiny + i;
+                    hB[to] = bf ? host_round_bf16(B[from]) : B[from];
+                    hAT[to] = bf ? host_round_bf16(A[from]) : A[from];
+                }
+    } else if (!use_mfma) {
         hB.resize(elems); hAT.resize(elems);
         for (unsigned long long e = 0; e < elems; ++e) hB[e] = bf ? host_round_bf16(B[e]) : B[e];
         for (int t = 0; t < K; ++t)
@@ -650,11 +669,11 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         return BSSE_OK;
     };
     do {
-        if (!use_mfma && (st = up((void **)&g->dB, hB.data(), elems * 4)) != BSSE_OK) break;
-        if (!use_mfma && (st = up((void **)&g->dAT, hAT.data(), elems * 4)) != BSSE_OK) break;
+        if (!use_mfma && (st = up((void **)&g->dB, hB.data(), hB.size() * 4)) != BSSE_OK) break;
+        if (!use_mfma && (st = up((void **)&g->dAT, hAT.data(), hAT.size() * 4)) != BSSE_OK) break;
         if ((st = up((void **)&g->dprior, prior, (size_t)K * 4)) != BSSE_OK) break;
         g->view.m = m; g->view.n = n; g->view.K = K;
-        g->view.m_pad = m; g->view.n_pad = n;
+        g->view.m_pad = tiny ? tiny : m; g->view.n_pad = n;
         if (use_mfma && variant == kAnyVariant) {
             // packed on the device from the payoffs as given
             g->view.any = any_geometry(m, n, K, bf ? 1 : exact ? 3 : 6);
@@ -965,7 +984,7 @@ float value_of(const bsse_game *g, const float *l)
 {
     float v = 0.0f;
     for (int t = 0; t < g->K; ++t) v = std::fmaf(g->hprior[t], l[t], v);
-    return v;
+    return v == v ? v : -INFINITY;               // (as the kernels report it)
 }
 
 // The caller's stream waits for whatever the handle's own streams still have in flight.
@@ -1213,7 +1232,7 @@ extern "C" bsse_status bsse_sweep_result(bsse_game *g, bsse_result *res, int32_t
             // one row against every type: the types are spread over the chip, and the host sums
             a.l_out = g->h_l; a.l_sc = g->K; a.l_st = 1;
             HIP_TRY(launch_rows(g, a, g->stream));
-            if ((st = wait_flags(g, row_flags(g))) == BSSE_OK && g->h_out->run.has) g->h_out->fin_v = value_of(g, g->h_l);
+            if ((st = wait_flags(g, (int)row_blocks(g, 1))) == BSSE_OK && g->h_out->run.has) g->h_out->fin_v = value_of(g, g->h_l);
         } else {
             a.V_out = &g->h_out->fin_v;
             HIP_TRY(launch_sweep(g, a, true));
@@ -1245,21 +1264,28 @@ bsse_status report_result(bsse_game *g, bsse_result *res, int32_t *best_response
 
 // Whether the records of a sweep of few rows, each with a row and its best responses, are few enough
 // to go to the host (256 KiB: a few microseconds over the bus).
-constexpr int MAX_HOST_RECS = 512;
+constexpr int MAX_HOST_RECS = 2048;
 bool host_folds(const bsse_game *g, long long count)
 {
     const long long nrec = (count + FINISH_ROWS - 1) / FINISH_ROWS;
     return few_rows(g, count) && nrec <= MAX_HOST_RECS && nrec * (g->m + g->K) <= (1LL << 16);
 }
+// The same for the one launch of the short-row kernel.
+bool one_launch(const bsse_game *g, long long count)
+{
+    const long long nrec = tiny_num_blocks(count);
+    return on_tiny(g) && !few_rows(g, count) && nrec <= MAX_HOST_RECS && nrec * (g->m + g->K) <= (1LL << 16);
+}
 
 // Whether sweep_once takes a sweep.
 bool sweeps_at_once(const bsse_game *g, long long count)
 {
-    return count > 0 && (host_folds(g, count) || (on_any(g) && !few_rows(g, count)));
+    return count > 0 && (host_folds(g, count) || one_launch(g, count) || (on_any(g) && !few_rows(g, count)));
 }
 
 // One whole sweep (already reset) of rows that stay put until it is done, on the any-shape path, or on
-// the general one when the rows are few: two launches and one wait, whatever the size.  Few rows: a type-sliced launch, and one that sums the
+// the general one when the rows are few: two launches and one wait, whatever the size; on the short-row
+// kernel one launch.  Few rows: a type-sliced launch, and one that sums the
 // values and leaves a record per 256 rows, with that record's row and best responses, in pinned memory;
 // the host folds the records.  Many rows: the sweep, and one launch whose workgroups each fold its
 // records and evaluate their slice of the types at the winner.
@@ -1268,16 +1294,22 @@ bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_resul
     const int m = g->m, K = g->K;
     bsse_status st;
     g->host_best = false; g->hx_valid = false;
-    const long long nrec = (count + FINISH_ROWS - 1) / FINISH_ROWS;
-    const bool rows = host_folds(g, count);
+    const bool rows = host_folds(g, count), single = !rows && one_launch(g, count), recs = rows || single;
+    const long long nrec = single ? tiny_num_blocks(count) : (count + FINISH_ROWS - 1) / FINISH_ROWS;
+    const long long used = recs ? nrec : 0;
     SweepArgs a{};
     a.X = X; a.count = count; a.tie_counter = g->w.tie_counter;
     // (the records have a place of their own: nothing else is ever written where a flag is looked for)
-    const size_t off_x = (size_t)MAX_HOST_RECS * sizeof(FinishRec), off_br = off_x + (size_t)nrec * m * sizeof(float);
-    if (rows) {
+    const size_t off_x = (size_t)MAX_HOST_RECS * sizeof(FinishRec), off_br = off_x + (size_t)used * m * sizeof(float);
+    if (recs && (st = grow_pinned(g, (void **)&g->h_rec, &g->cap_rec, off_br + (size_t)nrec * K * sizeof(int32_t))) != BSSE_OK) return st;
+    auto *rec = reinterpret_cast<FinishRec *>(g->h_rec);
+    auto *rec_x = reinterpret_cast<float *>(g->h_rec + off_x);
+    auto *rec_br = reinterpret_cast<int32_t *>(g->h_rec + off_br);
+    if (single) {
+        a.tie_counter = nullptr;                     // (in the records)
+    } else if (rows) {
         if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * K * sizeof(float))) != BSSE_OK) return st;
         if ((st = grow_device(g, (void **)&g->row_br, &g->cap_row_br, (size_t)count * K * sizeof(int32_t))) != BSSE_OK) return st;
-        if ((st = grow_pinned(g, (void **)&g->h_rec, &g->cap_rec, off_br + (size_t)nrec * K * sizeof(int32_t))) != BSSE_OK) return st;
         a.l_out = g->row_l; a.l_sc = 1; a.l_st = count;
         a.br_out = g->row_br; a.br_sc = 1; a.br_st = count;
     } else {
@@ -1290,7 +1322,9 @@ bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_resul
         if ((st = take_event(g, &e1)) != BSSE_OK) { g->ev_pool.push_back(e0); return st; }
         HIP_TRY(hipEventRecord(e0, g->stream));
     }
-    const hipError_t le = rows ? launch_rows(g, a, g->stream) : launch_sweep_any(g->view, a, 1, g->stream);
+    const TinyRecs tr{ rec, rec_x, rec_br, single ? new_done(g).seq : 0u };
+    const hipError_t le = rows ? launch_rows(g, a, g->stream)
+                          : single ? launch_sweep_tiny(g->view, a, false, 1, tr, g->stream) : launch_sweep_any(g->view, a, 1, g->stream);
     if (g->timing) {
         (void)hipEventRecord(e1, g->stream);
         g->ev.push_back(e0); g->ev.push_back(e1);
@@ -1299,13 +1333,11 @@ bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_resul
     if (rows) {
         FinishRowsArgs f{};
         f.l = g->row_l; f.br = g->row_br; f.prior = g->dprior; f.X = X; f.count = count; f.K = K; f.m = m;
-        f.rec = reinterpret_cast<FinishRec *>(g->h_rec);
-        f.rec_x = reinterpret_cast<float *>(g->h_rec + off_x);
-        f.rec_br = reinterpret_cast<int32_t *>(g->h_rec + off_br);
+        f.rec = rec; f.rec_x = rec_x; f.rec_br = rec_br;
         f.ties = g->w.tie_counter;
         f.seq = new_done(g).seq;
         HIP_TRY(launch_finish_rows(f, g->stream));
-    } else {
+    } else if (!single) {
         SweepArgs e{};
         e.X = X; e.count = 1; e.index_base = 0;
         e.fold_v = g->w.blk_v; e.fold_i = g->w.blk_i; e.fold_n = (int)any_num_blocks(g->view, count);
@@ -1318,18 +1350,20 @@ bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_resul
     }
     g->fresh = false;
     g->n_evals += count * K;
-    st = rows ? wait_words(g, &reinterpret_cast<const FinishRec *>(g->h_rec)->seq, (int)nrec, sizeof(FinishRec))
-              : wait_flags(g, row_flags(g));
+    st = recs ? wait_words(g, &rec->seq, (int)nrec, sizeof(FinishRec))
+              : wait_flags(g, (int)row_blocks(g, 1));
     if (st != BSSE_OK) return st;
-    if (rows) {
-        const FinishRec *rec = reinterpret_cast<const FinishRec *>(g->h_rec);
+    if (recs) {
         long long b = 0;
-        for (long long r = 1; r < nrec; ++r)
-            if (rec[r].value > rec[b].value) b = r;          // records ascend in index
+        unsigned long long ties = rec[0].ties;
+        for (long long r = 1; r < nrec; ++r) {
+            if (rec[r].value > rec[b].value || (rec[r].value == rec[b].value && rec[r].index < rec[b].index)) b = r;
+            if (single) ties += rec[r].ties;
+        }
         RunningBest &run = g->h_out->run;
-        run.value = rec[b].value; run.index = rec[b].index; run.has = 1; run.ties = rec[0].ties;
-        memcpy(g->h_x, g->h_rec + off_x + (size_t)b * m * sizeof(float), (size_t)m * sizeof(float));
-        memcpy(g->h_br, g->h_rec + off_br + (size_t)b * K * sizeof(int32_t), (size_t)K * sizeof(int32_t));
+        run.value = rec[b].value; run.index = rec[b].index; run.has = 1; run.ties = ties;
+        memcpy(g->h_x, rec_x + (size_t)b * m, (size_t)m * sizeof(float));
+        memcpy(g->h_br, rec_br + (size_t)b * K, (size_t)K * sizeof(int32_t));
         g->h_out->fin_v = run.value;
     } else if (g->h_out->run.has) {
         g->h_out->fin_v = value_of(g, g->h_l);
@@ -1404,10 +1438,11 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
         if (st != BSSE_OK) return st;
     }
     const bool small = on_small_kernel(g);
-    if (!small && sweep_blocks(g, count) > STATIC_MAX_BLOCKS)
+    // (every vector-path game has the documented limit, also where the short-row kernel needs fewer records)
+    const long long records = g->path == PATH_VALU ? valu_num_blocks(count) : sweep_blocks(g, count);
+    if (!small && records > STATIC_MAX_BLOCKS)
         return fail(BSSE_EOVERFLOW, "%lld candidates need %lld workgroup records; the static scratch holds %lld "
-                    "(sweep in pieces, or use bsse_sweep)", (long long)count, sweep_blocks(g, count),
-                    STATIC_MAX_BLOCKS);
+                    "(sweep in pieces, or use bsse_sweep)", (long long)count, records, STATIC_MAX_BLOCKS);
     if (small && small_num_slots() > STATIC_MAX_SLOTS)
         return fail(BSSE_EOVERFLOW, "the static scratch holds %d running-best slots, %d needed", STATIC_MAX_SLOTS,
                     small_num_slots());
@@ -1891,7 +1926,6 @@ extern "C" bsse_status bsse_polish(bsse_game *g, const int32_t *profile, float *
     memcpy(brs.data(), pol_br, brs.size() * sizeof(int32_t));
     for (int e = 0; e < kPolishRows; ++e) {
         vals[e] = cuts_types(g) ? value_of(g, pol_l + (size_t)e * K) : pol_v[e];
-        if (!(vals[e] == vals[e])) vals[e] = -INFINITY;
     }
     int best = kPolishRows - 1;                          // the sweep's own winner, unless a point beats it
     for (int e = kPolishRows - 2; e >= 0; --e)

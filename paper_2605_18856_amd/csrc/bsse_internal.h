@@ -141,6 +141,23 @@ enum PathKind { PATH_VALU = 1, PATH_MFMA_F32 = 2, PATH_MFMA_BF16 = 3, PATH_MFMA_
 long long valu_num_blocks(long long count);
 hipError_t launch_sweep_valu(const GameView &g, const SweepArgs &a, bool eval, hipStream_t s);
 
+// Short rows on the vector unit (see sweep_tiny.hip): m <= 24, payoffs [K][n][tiny_pad(m)] in g.B and
+// g.AT, g.m_pad = tiny_pad(m).
+constexpr int kTinyVariant = 3000;
+// One launch that leaves the workgroups' winners in pinned host memory (sweep mode without blk_v).
+struct TinyRecs {
+    struct FinishRec *rec;   // [workgroups]
+    float *rec_x;            // [workgroups][m]
+    int32_t *rec_br;         // [workgroups][K]
+    unsigned seq;            // stored into a record last (see Done)
+};
+int tiny_pad(int m);                   // 0: not for this kernel
+long long tiny_num_blocks(long long count);
+int tiny_slices(const GameView &g, long long count);
+long long tiny_row_blocks(const GameView &g, long long count);
+// slices > 1 (evaluation mode): l_out and br_out only.
+hipError_t launch_sweep_tiny(const GameView &g, const SweepArgs &a, bool eval, int slices, const TinyRecs &r, hipStream_t s);
+
 // Matrix-core variants.  mode: 0 = fp32 MFMA on fp32 payoffs, 1 = bf16 MFMA on bf16-rounded
 // operands, 2 = bf16 MFMA on fp32 operands split into bf16 parts.  `exact` = every payoff is
 // exactly representable in bf16 (lets mode 2 use three terms instead of six).  Returns a

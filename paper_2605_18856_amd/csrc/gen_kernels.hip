@@ -28,12 +28,21 @@ __device__ __forceinline__ float around(float t, const float *centre, int i, flo
 //     S(v) = sum_{v'<v} W(rem-v', q) = W(rem, q+1) - W(rem-v, q+1)
 // (hockey-stick identity), which is increasing in v, so the part is the largest v with
 // S(v) <= rank, found by bisection.
+// LDS: the table fits 32 KiB and is read from there (the bisections are chains of dependent reads).
+template <bool LDS>
 __global__ void __launch_bounds__(256)
-lattice_kernel(const unsigned long long *__restrict__ table, int m, int N, long long count,
+lattice_kernel(const unsigned long long *__restrict__ table_global, int m, int N, long long count,
                const float *__restrict__ centre, float radius, float omr, float *__restrict__ out)
 {
     out += (size_t)blockIdx.y * count * m;
     if (centre) centre += blockIdx.y * m;
+    extern __shared__ unsigned long long lattice_lds[];
+    const unsigned long long *table = table_global;
+    if constexpr (LDS) {
+        for (int e = threadIdx.x; e < (m + 1) * (N + 1); e += 256) lattice_lds[e] = table_global[e];
+        __syncthreads();
+        table = lattice_lds;
+    }
     const float fN = (float)N;
     const long long stride = (long long)gridDim.x * blockDim.x;
     for (long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x; r < count; r += stride) {
@@ -63,7 +72,9 @@ hipError_t launch_lattice(const unsigned long long *table, int m, int N, long lo
     if (count <= 0) return hipSuccess;
     long long blocks = (count + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(lattice_kernel, dim3((unsigned)blocks, (unsigned)sets), dim3(256), 0, s, table, m, N, count,
+    const size_t bytes = (size_t)(m + 1) * (N + 1) * sizeof(unsigned long long);
+    const bool lds = bytes <= 32 * 1024;
+    hipLaunchKernelGGL((lds ? lattice_kernel<true> : lattice_kernel<false>), dim3((unsigned)blocks, (unsigned)sets), dim3(256), lds ? bytes : 0, s, table, m, N, count,
                        centre, radius, 1.0f - radius, out);
     return hipGetLastError();
 }
