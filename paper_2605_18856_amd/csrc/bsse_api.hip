@@ -574,6 +574,9 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     bool exact = true;                       // every payoff is a bf16 number
     for (unsigned long long e = 0; e < elems && exact; ++e)
         exact = host_round_bf16(A[e]) == A[e] && host_round_bf16(B[e]) == B[e];
+    // The three bf16 parts of a number are exact while the smallest of them is not subnormal and the
+    // greatest does not round up to infinity.
+    const auto in_parts = [](float v) { v = std::fabs(v); return v == 0.0f || (v >= 0x1p-100f && v <= 0x1p120f); };
     int variant = -1;
     PathKind path = PATH_VALU;
     if (opt->path == BSSE_PATH_MFMA_SPLIT) {
@@ -599,8 +602,11 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
                 path = PATH_MFMA_F32;
             }
         }
-        // every other shape the matrix cores pay for: tiles padded as needed
-        if (path == PATH_VALU && any_supported(m, n)) {
+        // every other shape the matrix cores pay for, tiles padded as needed; payoffs near the ends of
+        // the fp32 range stay on the vector unit
+        bool ordinary = path == PATH_VALU && any_supported(m, n);
+        for (unsigned long long e = 0; e < elems && ordinary; ++e) ordinary = in_parts(A[e]) && in_parts(B[e]);
+        if (ordinary) {
             variant = kAnyVariant;
             path = bf ? PATH_MFMA_BF16 : PATH_MFMA_SPLIT;
         }
@@ -1765,25 +1771,27 @@ extern "C" bsse_status bsse_refine(bsse_game *g, int k, int rounds, int lattice_
         }
         // The local sets of a round do not depend on each other: as many as fit 2^26 floats (but one at
         // least) are generated, evaluated and selected together, five launches and one wait for all of them.
+        const bool big = cnt > SET_MAX;                      // (any number the caller gave)
         const int kk = (int)std::min<long long>(k, cnt);
-        const long long together = std::max<long long>(1, std::min<long long>(k, (1LL << 26) / (cnt * m)));
+        const long long together = big ? 1 : std::max<long long>(1, std::min<long long>(k, (1LL << 26) / (cnt * m)));
+        // A set that goes alone is generated in the handle-owned buffer: no second one of its size.
+        const bool staged = together > 1;
         float rad = radius;
         for (int round = 0; round < rounds; ++round) {
             found.clear(); big_x.clear(); big_br.clear();
             for (const Survivor &s : pool) found.push_back({ s.v, s.x.data(), s.br.data() });   // a centre survives unless it is beaten
             const uint64_t rseed = seed + (uint64_t)round * 1000003ull;
             const size_t nc = pool.size();
-            evals += (long long)nc * cnt * K;
-            const bool big = cnt > SET_MAX;
             // (the handle-owned set ends as the last local set, as if each had been generated there)
-            if (!big && round + 1 == rounds && (st = ensure_gen(g, (unsigned long long)cnt)) != BSSE_OK) return st;
+            if (!big && (!staged || round + 1 == rounds) && (st = ensure_gen(g, (unsigned long long)cnt)) != BSSE_OK) return st;
             if (!big) {
+                evals += (long long)nc * cnt * K;
                 const size_t bytes = nc * m * sizeof(float);
                 if ((st = grow_device(g, (void **)&g->centre_dev, &g->cap_centre, bytes)) != BSSE_OK) return st;
                 if ((st = grow_pinned(g, (void **)&g->h_centre, &g->cap_h_centre, bytes)) != BSSE_OK) return st;
                 for (size_t c = 0; c < nc; ++c) memcpy(g->h_centre + c * m, pool[c].x.data(), (size_t)m * sizeof(float));
                 HIP_TRY(launch_copy_words(g->h_centre, g->centre_dev, nc * m, g->stream));
-                if ((st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)together * cnt * m * sizeof(float))) != BSSE_OK) return st;
+                if (staged && (st = grow_device(g, (void **)&g->stage, &g->stage_cap, (size_t)together * cnt * m * sizeof(float))) != BSSE_OK) return st;
                 if ((st = records((size_t)nc * kk)) != BSSE_OK) return st;
             }
             auto generate = [&](size_t c0, int sets, float *out) -> bsse_status {
@@ -1798,17 +1806,16 @@ extern "C" bsse_status bsse_refine(bsse_game *g, int k, int rounds, int lattice_
                                        : bsse_dirichlet_around(g, rseed + c0, 0, cnt, pool[c0].x.data(), rad, nullptr);
                     if (st == BSSE_OK) st = harvest_big();
                     if (st != BSSE_OK) return st;
+                    evals += (long long)cnt * K;
                     continue;
                 }
                 const int sets = (int)std::min<size_t>((size_t)together, nc - c0);
                 const bool last = c0 + sets == nc;
-                if ((st = generate(c0, sets, g->stage)) != BSSE_OK) return st;
-                if (last && round + 1 == rounds) {
-                    if ((st = generate(nc - 1, 1, g->gen)) != BSSE_OK) return st;
-                    g->gen_count = cnt;
-                }
+                if ((st = generate(c0, sets, staged ? g->stage : g->gen)) != BSSE_OK) return st;
+                if (staged && last && round + 1 == rounds && (st = generate(nc - 1, 1, g->gen)) != BSSE_OK) return st;
+                if (!staged || (last && round + 1 == rounds)) g->gen_count = cnt;
                 const size_t at = c0 * kk;
-                if ((st = enqueue_topk(g, g->stage, cnt, sets, kk, 0, hv + at, hi + at, hb + at * K, hx + at * m, last, &flags)) != BSSE_OK) return st;
+                if ((st = enqueue_topk(g, staged ? g->stage : g->gen, cnt, sets, kk, 0, hv + at, hi + at, hb + at * K, hx + at * m, last, &flags)) != BSSE_OK) return st;
             }
             if (!big) {
                 if ((st = wait_winners(g, flags)) != BSSE_OK) return st;
@@ -1958,8 +1965,14 @@ extern "C" bsse_status bsse_solve_realised(bsse_game *g, const float *candidates
     DeviceGuard dg(g->device);
     if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
     RealisedScratch &w = g->real;
-    const unsigned nslots = profile_table_slots(count), most = (unsigned)std::min<int64_t>(max_profiles, count);
-    const bool on_device = lp_on_device(m, n, K);
+    // (no more profiles than rows, nor than n to the K)
+    int64_t most64 = std::min<int64_t>(max_profiles, count), profiles = 1;
+    for (int t = 0; t < K && profiles < most64; ++t) profiles *= n;          // (both factors below 2^28: no overflow)
+    most64 = std::min(most64, n == 1 ? (int64_t)1 : profiles);
+    const unsigned nslots = profile_table_slots(count), most = (unsigned)most64;
+    // One workgroup and one vertex of doubles in memory per program: beyond four million the host keeps
+    // one of each.
+    const bool on_device = lp_on_device(m, n, K) && most <= (1u << 22);
     const size_t table_bytes = (size_t)nslots * 12 + 16;             // keys, slots, counter
     struct Release {                     // scratch of a large set is not kept
         RealisedScratch &w;
