@@ -2,6 +2,7 @@
 // it, and the kernel that turns the per-type leader payoffs of a sliced launch into values.
 #include "bsse_internal.h"
 #include "sweep_any_impl.h"
+#include <algorithm>
 #include "done_device.h"
 
 namespace bsse {
@@ -245,22 +246,41 @@ static long long rows_per_block(const AnyGeo &q) { return 32LL * any_impl::WAVES
 
 long long any_num_blocks(const GameView &g, long long count)
 {
-    // At most one resident set (two workgroups a compute unit); every workgroup then walks the same
-    // number of blocks up to one.
-    const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any), cap = 512;
-    const long long rounds = (blocks + cap - 1) / cap;
-    return rounds > 0 ? (blocks + rounds - 1) / rounds : 1;
+    // At most one resident set (two workgroups a compute unit), and always the whole of it: with the
+    // grid cut to the workgroups that share the blocks evenly, some compute units held one workgroup
+    // and the others two (m = 16, n = 40, K = 30 bf16: 140000 rows 106 -> 96 us, 270000 rows 151 -> 134;
+    // m = 20, n = 12, K = 12: 400000 rows 78 -> 71).
+    const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
+    return blocks < 1 ? 1 : blocks < 512 ? blocks : 512;
 }
 
 int any_slices(const GameView &g, long long count)
 {
-    // Fewer blocks of candidates than compute units: cut the types until the grid is about twice that.
-    const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
-    if (blocks >= 256 || g.any.units < 2) return 1;
-    long long want = 512 / blocks;
-    if (want > g.any.units) want = g.any.units;
-    const int per = (int)((g.any.units + want - 1) / want);
-    return (g.any.units + per - 1) / per;
+    const AnyGeo &q = g.any;
+    const long long blocks = (count + rows_per_block(q) - 1) / rows_per_block(q);
+    if (q.units < 2) return 1;
+    auto cut = [&](long long want) { const long long per = (q.units + want - 1) / want; return (int)((q.units + per - 1) / per); };
+    // Far fewer blocks of candidates than compute units, or packed types (the per-type outputs of a cut
+    // launch are most of their cost): cut until the grid is about twice the compute units.
+    if (blocks < 128 || (q.form >= 8 && blocks < 256)) return cut(std::min<long long>(512 / blocks, q.units));
+    if (q.form >= 8 || (count + FINISH_ROWS - 1) / FINISH_ROWS * (g.m + g.K) > (1LL << 16)) return 1;
+    // Otherwise a compute unit holds two workgroups, and the slowest one decides: 274 blocks leave 18
+    // units with two and the rest half idle.  In units of the time two workgroups together take for all
+    // types, a launch takes what its fullest unit takes -- pairs, and 0.62 for a last one by itself --
+    // and a cut one its outputs and repeated row loads on top, less in proportion the more a type has to
+    // do.  m = 50, n = 100, K = 24 bf16: 70001 rows (274 blocks) 100 us uncut, 85 in five slices; 85000
+    // rows 101 and 93 (three); 100003 rows 102 uncut, 110 in five.  m = 60, n = 100, K = 12: 66000 rows
+    // 132 and 107; m = 30, n = 50, K = 20: 66000 rows 74 and 67, 100003 rows 76 uncut, 87 in five.
+    const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg, extra = (double)blocks / 256 * std::min(1.0, 50.0 / work);
+    auto cost = [&](int slices) {
+        const int per = (q.units + slices - 1) / slices;
+        const long long n = (blocks * slices + 255) / 256;
+        return (n / 2 + (n % 2 ? 0.62 : 0.0)) * per / q.units + (slices > 1 ? (0.15 + 0.02 * slices) * extra : 0.0);
+    };
+    int best = 1;
+    for (int want = 2; want <= 8 && want <= q.units; ++want)
+        if (const int slices = cut(want); cost(slices) < 0.97 * cost(best)) best = slices;
+    return best;
 }
 
 long long any_row_blocks(const GameView &g, long long count)
