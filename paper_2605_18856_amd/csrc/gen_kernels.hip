@@ -3,6 +3,7 @@
 // output, no reads beyond a small table.
 #include "bsse_internal.h"
 #include "gen_device.h"
+#include <algorithm>
 
 namespace bsse {
 
@@ -116,6 +117,55 @@ dirichlet_quad_kernel(unsigned long long seed, long long first, long long count,
     }
 }
 
+// Rows of 9 to 256 components that the quad kernel does not take, any alignment: the workgroup's rows are
+// made in LDS quad by quad (one generator call each, in the layout of the output), a thread per row adds
+// its components in ascending order, and the scaled block is written out in one contiguous piece.  Bits
+// as dirichlet_row_kernel<false>, which made every component twice and stored each row's next to the
+// other rows' only every m numbers: 2^21 rows of m = 27 248 -> 84 us, 30000 rows of m = 250 68 -> 18.
+// (2^20 rows of m = 5: 14-15 us by that kernel, 17 by this one, which has three barriers a block.)
+constexpr int DB_T = 256, DB_WORDS = 8192;      // threads; LDS words of rows: four or five workgroups a compute unit
+static int dirichlet_block_rows(int m) { return std::min(DB_T, DB_WORDS / m); }
+__global__ void __launch_bounds__(DB_T)
+dirichlet_block_kernel(unsigned long long seed, long long first, long long count, int m, int rows_per_block,
+                       const float *__restrict__ centre, float radius, float omr, float *__restrict__ out)
+{
+#pragma clang fp contract(off)
+    __shared__ float comp[DB_WORDS], inv[DB_T];
+    seed += blockIdx.y;
+    out += (size_t)blockIdx.y * count * m;
+    if (centre) centre += blockIdx.y * m;
+    const unsigned k0 = (unsigned)seed, k1 = (unsigned)(seed >> 32);
+    const unsigned tid = threadIdx.x, nb = ((unsigned)m + 3) / 4, um = (unsigned)m;
+    // quotients by nb and m of numbers below 2^13: exact (nb >= 3) with the rounded-up reciprocals of 32 bits
+    const unsigned rec_nb = 0xFFFFFFFFu / nb + 1u, rec_m = 0xFFFFFFFFu / um + 1u;
+    const float even = 1.0f / (float)m;
+    for (long long r0 = (long long)blockIdx.x * rows_per_block; r0 < count; r0 += (long long)gridDim.x * rows_per_block) {
+        const unsigned rows = (unsigned)(count - r0 < rows_per_block ? count - r0 : rows_per_block);
+        for (unsigned q = tid; q < rows * nb; q += DB_T) {
+            const unsigned r = __umulhi(q, rec_nb), b = q - r * nb;
+            float g[4];
+            dirichlet_quad_raw(first + r0 + r, b, k0, k1, g[0], g[1], g[2], g[3]);
+#pragma unroll
+            for (unsigned e = 0; e < 4; ++e)
+                if (4 * b + e < um) comp[r * um + 4 * b + e] = g[e];
+        }
+        __syncthreads();
+        if (tid < rows) {
+            float sum = 0.0f;
+            for (unsigned i = 0; i < um; ++i) sum += comp[tid * um + i];
+            inv[tid] = sum > 0.0f ? 1.0f / sum : 0.0f;                   // correctly rounded
+        }
+        __syncthreads();
+        float *dst = out + r0 * m;
+        for (unsigned e = tid; e < rows * um; e += DB_T) {
+            const unsigned r = __umulhi(e, rec_m), i = e - r * um;
+            const float s = inv[r];
+            dst[e] = around(s > 0.0f ? comp[e] * s : even, centre, (int)i, radius, omr);
+        }
+        __syncthreads();
+    }
+}
+
 // Any m, any alignment: one thread per row, two passes over the generator (sum, then normalise).
 // TREE (m a multiple of four with m/4 a power of two <= 64, the shapes the quad kernel takes): the
 // row sum is formed in the quad kernel's order -- each quad as (g0 + g1) + (g2 + g3), then the
@@ -185,7 +235,12 @@ hipError_t launch_dirichlet(uint64_t seed, long long first, long long count, int
     } else {
         long long blocks = (count + 255) / 256;
         if (blocks > 256 * 32) blocks = 256 * 32;
-        if (quad_shape)
+        if (!quad_shape && m > 8 && m <= 256) {
+            const int rows = dirichlet_block_rows(m);
+            const long long pieces = (count + rows - 1) / rows;
+            hipLaunchKernelGGL(dirichlet_block_kernel, dim3((unsigned)std::min<long long>(pieces, 256 * 32), (unsigned)sets), dim3(DB_T), 0, s,
+                               seed, first, count, m, rows, centre, radius, 1.0f - radius, out);
+        } else if (quad_shape)
             hipLaunchKernelGGL(dirichlet_row_kernel<true>, dim3((unsigned)blocks, (unsigned)sets), dim3(256), 0, s, seed,
                                first, count, m, centre, radius, 1.0f - radius, out);
         else
