@@ -384,9 +384,13 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 const f32x4 q = *(const f32x4 *)(row + e);
                 vb[e] = q[0]; vb[e + 1] = q[1]; vb[e + 2] = q[2]; vb[e + 3] = q[3];
             }
+        } else if constexpr (TERMS != 3) {
+            load_half_row<HALF_BASE>(row - h * HALF_BASE, h, m, vb);
         } else {
+            // (component by component: at the register limit, m = 100, n = 256, K = 100, 65536 rows take
+            // 908 us like this and 916 in pieces)
 #pragma unroll
-            for (int e = 0; e < HALF_BASE; ++e) {            // (no branch: the first element stands in past m)
+            for (int e = 0; e < HALF_BASE; ++e) {
                 const bool in = h * HALF_BASE + e < m;
                 const float t = row[in ? e : -h * HALF_BASE];
                 vb[e] = in ? t : 0.0f;
@@ -815,7 +819,8 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 // maximiser is one tile and one position, anything else goes to the exact routine.  Arithmetic,
 // operand order, packing and the exact-tie routine are those of sweep_mfma_kernel: the same bits
 // per candidate.
-template <typename T, int MP, int N, int WAVES, int PF>
+// FULL: rows of MP components; shorter ones have a kernel of their own.
+template <typename T, int MP, int N, int WAVES, int PF, bool FULL>
 __global__ void __launch_bounds__(WAVES * 64, 2)
 sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
 {
@@ -882,19 +887,14 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
             const bool ok = c < a.count;                     // (past the end: the last row again)
             float vb[HALF_BASE];
             const float *row = a.X + (ok ? c : a.count - 1) * (long long)m + h * HALF_BASE;
-            if (m == MP && HALF_BASE % 4 == 0 && ((uintptr_t)a.X & 15) == 0) {
+            if constexpr (FULL) {                            // (rows are then 16-byte aligned)
 #pragma unroll
                 for (int e = 0; e < HALF_BASE; e += 4) {
                     const f32x4 q = *(const f32x4 *)(row + e);
                     vb[e] = q[0]; vb[e + 1] = q[1]; vb[e + 2] = q[2]; vb[e + 3] = q[3];
                 }
             } else {
-#pragma unroll
-                for (int e = 0; e < HALF_BASE; ++e) {
-                    const bool in = h * HALF_BASE + e < m;
-                    const float t = row[in ? e : -h * HALF_BASE];
-                    vb[e] = in ? t : 0.0f;
-                }
+                load_half_row<HALF_BASE>(row - h * HALF_BASE, h, m, vb);
             }
             P::pack_x(vb, x[ps][ct]);
             valid32[ps][ct] = (unsigned)__builtin_amdgcn_ballot_w64(ok);
@@ -1161,7 +1161,8 @@ struct Variant {
     void (*sliced)(GameView, SweepArgs, int);     // one candidate tile per wavefront, types sliced
     Geometry geo;
     const char *name;
-    void (*wide)(GameView, SweepArgs, int);       // sweep_wide_kernel for this packing, or null
+    void (*wide)(GameView, SweepArgs, int);       // sweep_wide_kernel for this packing and rows of m_pad components, or null
+    void (*wide_part)(GameView, SweepArgs, int);  // the same for shorter rows
     int wide_lds;                                 // its dynamic LDS bytes
 };
 
@@ -1169,14 +1170,14 @@ struct Variant {
     { MODE, TERMSv, MPB, Nv, NTv, Wv, STv, ATL,                                                      \
       sweep_mfma_kernel<T, MPB * TERMSv, Nv, NTv, Wv, STv, OCCv, ATL, TERMSv, false, PFv>,           \
       sweep_mfma_kernel<T, MPB * TERMSv, Nv, 1, Wv, STv, 1, ATL, TERMSv, true, PFv>,                 \
-      make_geometry((int)sizeof(T), MPB * TERMSv, Nv, STv, Wv, ATL, TERMSv), NAME, nullptr, 0 }
+      make_geometry((int)sizeof(T), MPB * TERMSv, Nv, STv, Wv, ATL, TERMSv), NAME, nullptr, nullptr, 0 }
 // A packing that sweep_wide_kernel also takes (one type per stage, leader rows in LDS, NT = 2)
 #define BSSE_VARIANT_WIDE(T, MODE, MPB, Nv, Wv, PFv, NAME)                                           \
     { MODE, 1, MPB, Nv, 2, Wv, Nv / 32, true,                                                        \
       nullptr,                                                                                       \
       sweep_mfma_kernel<T, MPB, Nv, 1, Wv, Nv / 32, 1, true, 1, true, PFv>,                          \
       make_geometry((int)sizeof(T), MPB, Nv, Nv / 32, Wv, true), NAME,                               \
-      sweep_wide_kernel<T, MPB, Nv, Wv, PFv>, wide_lds_bytes((int)sizeof(T), MPB, Nv, Wv) }
+      sweep_wide_kernel<T, MPB, Nv, Wv, PFv, true>, sweep_wide_kernel<T, MPB, Nv, Wv, PFv, false>, wide_lds_bytes((int)sizeof(T), MPB, Nv, Wv) }
 
 const Variant kVariants[] = {
     // fp32 MFMA (the last number before the name: k-steps per fragment read-ahead chunk, 0 = the
@@ -1307,8 +1308,8 @@ hipError_t mfma_prepare(int variant, int K)
     const int nstages = (tiles + v->stage_tiles - 1) / v->stage_tiles;
     const size_t lds = (size_t)v->geo.rec_bytes * (nstages > 1 ? 2 : 1);
     if (v->wide && v->wide_lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)v->wide, hipFuncAttributeMaxDynamicSharedMemorySize, v->wide_lds);
-        if (e != hipSuccess) return e;
+        for (const void *k : { (const void *)v->wide, (const void *)v->wide_part })
+            if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, v->wide_lds); e != hipSuccess) return e;
     }
     if (lds <= 48 * 1024) return hipSuccess;
     hipError_t e = hipSuccess;
@@ -1331,7 +1332,7 @@ hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t 
     if (!a.l_out) {
         const long long blocks = mfma_num_blocks(g.variant, a.count);
         if (v->wide)       // (every wavefront sweeps two pairs of candidate tiles)
-            hipLaunchKernelGGL(v->wide, dim3((unsigned)blocks), dim3(v->waves * 64), (size_t)v->wide_lds, s, g, a, tiles);
+            hipLaunchKernelGGL((g.m == v->mp_base ? v->wide : v->wide_part), dim3((unsigned)blocks), dim3(v->waves * 64), (size_t)v->wide_lds, s, g, a, tiles);
         else
             hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(v->waves * 64), lds, s, g, a, tiles);
         return hipGetLastError();
