@@ -375,13 +375,24 @@ long long row_blocks(const bsse_game *g, long long count)
     return on_any(g) ? any_row_blocks(g->view, count) : on_tiny(g) ? tiny_row_blocks(g->view, count) : mfma_row_blocks(g->view, count);
 }
 
+// Whether the handle's stream is being captured.  Asynchronous calls then go without the per-type scratch
+// (uncut): it cannot be allocated there, and a graph must not keep a pointer that a later call outgrows.
+bool recording(const bsse_game *g)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(g->stream, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+}
+
 // Per-candidate outputs (a.V_out, a.br_out [count][K], a.l_out with the caller's strides; each nullable).
 bsse_status launch_eval(bsse_game *g, SweepArgs a)
 {
     a.br_sc = g->K; a.br_st = 1;
     if (!cuts_types(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
     if (!a.V_out && (a.l_out || on_any(g) || on_tiny(g))) { HIP_TRY(launch_rows(g, a, g->stream)); return BSSE_OK; }
-    if (a.l_out || !few_rows(g, a.count)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
+    if (a.l_out || !few_rows(g, a.count) || recording(g)) {
+        HIP_TRY(launch_sweep(g, a, true));
+        return BSSE_OK;
+    }
     bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float));
     if (st != BSSE_OK) return st;
     FinishRowsArgs f{};
@@ -1022,14 +1033,15 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     const long long count = a.count;
     const bool small = on_small_kernel(g);
     if (g->host_best && !g->fresh) {             // the running best so far goes back to the device
-        HIP_TRY(hipMemcpyAsync(g->w.run, &g->h_out->run, sizeof(RunningBest), hipMemcpyHostToDevice, g->stream));
-        HIP_TRY(hipMemcpyAsync(g->w.best_x, g->h_x, (size_t)g->m * sizeof(float), hipMemcpyHostToDevice, g->stream));
-        HIP_TRY(hipStreamSynchronize(g->stream));     // (the host copies are free to change)
+        // (the host copies change in stream order only: by this chunk's merge, or once a later call has waited)
+        static_assert(sizeof(RunningBest) % 4 == 0, "copied in words");
+        HIP_TRY(launch_copy_words(&g->h_out->run, g->w.run, sizeof(RunningBest) / 4, g->stream));
+        HIP_TRY(launch_copy_words(g->h_x, g->w.best_x, (size_t)g->m, g->stream));
     }
     g->host_best = false; g->hx_valid = false;
     long long nblocks = 0;
     hipStream_t stream = g->stream;
-    const bool rows = !small && !g->w.fixed && few_rows(g, count);       // (the static scratch holds records only)
+    const bool rows = !small && !g->w.fixed && few_rows(g, count) && !recording(g);     // (the static scratch holds records only)
     FinishRowsArgs f{};
     if (small) {
         // every workgroup keeps its own running best over the chunks: nothing but the sweep
