@@ -8,6 +8,9 @@ namespace bsse {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// A number that is none, as an inline constant (the usual bit pattern costs a register).
+#define kNotANumber __uint_as_float(0xFFFFFFFFu)
+
 // Row of a 32x32 MFMA accumulator tile held in register r of a lane, without the lane-half
 // term 4*(lane/32): lane l holds column l%32 and rows 8*(r/4) + 4*(l/32) + r%4.
 __device__ __host__ constexpr int acc_row_base(int r) { return 8 * (r / 4) + (r % 4); }

@@ -425,8 +425,12 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 
     // Exact routine for one (candidate tile, type) of FORM 0 / 1: the type's tiles once more from the
     // records in global memory (same instructions, same bits), the exact maximisers in ascending
-    // action order; the leader's payoff decides and then the lower action.
-    auto exact_type = [&](int ct, int t, float gmax, float &l_out, int &j_out) __attribute__((always_inline)) {
+    // action order; the leader's payoff decides and then the lower action.  Sums of minus infinity, and sums
+    // that are not numbers, count as the least finite number here: where a row has no others, all of its
+    // actions are maximisers and its leader payoffs say what the row is worth.
+    auto exact_type = [&](int ct, int t, float gm, float &l_out, int &j_out) __attribute__((always_inline)) {
+        constexpr float LEAST = -3.402823466e38f;
+        const float gmax = fmaxf(gm, LEAST);
         float lbest = 0.0f;
         int jbest = 0, nmatch = 0;
 #pragma unroll 1
@@ -442,7 +446,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                     for (int rr = 0; rr < 4; ++rr) {
                         const int r = 4 * q4 + rr;
                         const int j = tt * 32 + acc_row_base(r) + 4 * hh;
-                        const unsigned long long meq = __builtin_amdgcn_ballot_w64(acc[ct][r] == gmax);
+                        const unsigned long long meq = __builtin_amdgcn_ballot_w64(fmaxf(acc[ct][r], LEAST) == gmax);
                         const unsigned hit = (unsigned)(hh ? (meq >> 32) : meq);
                         if (hit == 0u || j > n - 1) continue;               // wave-uniform
                         const float l = pair_total(half_dot(ct, lead_global(t, j)));
@@ -453,7 +457,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                     }
         }
         l_out = lbest; j_out = jbest;
-        tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2) & valid32[ct]);
+        tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && gmax > LEAST) & valid32[ct]);
     };
 
     int buf = 0;
@@ -526,7 +530,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                             for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
                                 for (int p = 0; p < PT; ++p) {
-                                    float lbest = 0.0f;
+                                    float lbest = kNotANumber;      // (no sum is a number)
                                     unsigned jbest = 0;
                                     int nm = 0;
 #pragma unroll
@@ -537,7 +541,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                                             ++nm;
                                         }
                                     l[ct][p] = lbest; js[ct][p] = jbest;
-                                    const bool live = TPT * u + PT * h + p < K && ((valid32[ct] >> col) & 1u);
+                                    const bool live = TPT * u + PT * h + p < K && ((valid32[ct] >> col) & 1u) && gm[ct][p] > -INFINITY;
                                     tie_count += __builtin_popcountll(__builtin_amdgcn_ballot_w64(live && nm >= 2));
                                 }
                         }
@@ -550,9 +554,9 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 #pragma unroll
                             for (int k = 0; k < TPT; ++k) {
                                 const int t = TPT * u + k;
-                                const float pt = t < K ? prior[t] : 0.0f;
+                                if (t >= K) break;       // (uniform; a padded type's payoff may be infinite)
                                 const float lk = (k / PT == h) ? l[ct][k % PT] : lo[k % PT];
-                                V[ct] = fmaf(pt, lk, V[ct]);
+                                V[ct] = fmaf(prior[t], lk, V[ct]);
                             }
                             if (per_type) {
                                 const late_args o = late();
@@ -711,6 +715,10 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 
     const late_args o = late();
     if (o->a.blk_v) {
+        if (best_c == 0xFFFFFFFFu) {                     // no value above minus infinity: the first row, as on the other paths
+            const unsigned c = (blockIdx.x * WAVES + wave) * (NT * 32) + col;
+            best_c = c < count ? c : 0xFFFFFFFFu;
+        }
 #pragma unroll
         for (int d = 16; d >= 1; d >>= 1) {              // both lane halves hold the same values
             const float ov = __shfl_xor(best_v, d, 64);

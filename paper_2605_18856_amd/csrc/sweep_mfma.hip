@@ -458,7 +458,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     // decide and then the lower action.
     auto exact_type = [&](int ct, int group, int ti, int t, float gmax, float &l_out,
                           int &j_out) __attribute__((always_inline)) {
-        float lbest = 0.0f;
+        float lbest = kNotANumber;               // (no maximiser: no sum is a number)
         int jbest = 0, nmatch = 0;
         const unsigned char *ATt = ATpack + (size_t)t * N * MP * sizeof(T);
 #pragma unroll 1
@@ -911,7 +911,7 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
     // more from the packed records in global memory (same instructions, same bits), the exact
     // maximisers in ascending action order, the leader's payoff decides and then the lower action.
     auto exact_type = [&](const xreg *xc, unsigned valid, int t, float gmax, float &l_out, int &j_out) __attribute__((always_inline)) {
-        float lbest = 0.0f;
+        float lbest = kNotANumber;               // (no maximiser: no sum is a number)
         int jbest = 0, nmatch = 0;
         const unsigned char *ATt = ATpack + (size_t)t * N * MP * sizeof(T);
 #pragma unroll 1

@@ -253,7 +253,7 @@ __device__ __forceinline__ void small_body(const GameView &g, const SweepArgs &a
                     static_for<0, 2, 1>([&](auto tlc) {
                         constexpr int tl = decltype(tlc)::value;
                         const bool ok = first + ct * 32 + col < count;
-                        float lbest = 0.0f;
+                        float lbest = kNotANumber;       // (no maximiser: no sum is a number)
                         unsigned jbest = 0;
                         int nm = 0;
 #pragma unroll
