@@ -44,7 +44,11 @@ constexpr int WAVES = 4, THREADS = WAVES * 64;
 // three parts of a long row in registers there is room for one.
 constexpr int tiles_per_wave(int terms, int ks) { return (terms == 1 || ks <= 2) ? 2 : 1; }
 // Wavefronts per SIMD that the register allocation is held to.
-constexpr int occupancy(int terms, int ks, int form) { return (ks <= 2 && form != 0) ? 3 : 2; }
+constexpr int occupancy(int terms, int ks, int form)
+{
+    if (terms == 6 && ks == 3) return form >= 8 ? 4 : 3;        // (a few registers over the limit when left free)
+    return ks <= 2 && form != 0 ? 3 : 2;
+}
 
 __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 {
@@ -167,6 +171,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     constexpr bool NARROW = FORM >= 8;
     constexpr bool XF = !NARROW && TERMS != 1 && KS <= 2;   // the fp32 half row stays in registers
     constexpr int TPT = NARROW ? 32 / FORM : 1;          // types per unit
+    constexpr bool UNSCALE = XP == 3 && !XF;             // leader payoffs come from the split row: see load_rows
     constexpr bool PAIRS = FORM == 0 && TERMS == 1;      // row tiles two at a time: fewer vector instructions
                                                          // per tile where these outweigh the matrix time
     const AnyGeo &q = args.g.any;
@@ -243,6 +248,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 
     unsigned x[NT][XP][KS * 4];
     float xf[NT][XF ? HALF : 1];
+    float unscale[UNSCALE ? NT : 1];
     unsigned valid32[NT];
     // Rows of 16-byte multiples and others alike are read sixteen bytes a lane (the hardware asks for
     // four-byte alignment only); where a piece would reach past its row it is read ending with the row
@@ -250,6 +256,10 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     // component, k-step after k-step, the rows of m = 50 cost 128 requests of 64 lines each and eight
     // round trips per wavefront: 70001 rows, n = 100, K = 24 bf16: 105 -> 103 us, and 93 -> 85 in five
     // slices, each of which reads the rows again.)
+    // The parts of a component are exact from 2^-109 (they may be subnormal bf16 numbers) to the greatest
+    // number (the first part does not round up to infinity).  A row whose greatest component is below
+    // 2^-60 is split 2^64 times greater: its follower payoffs are compared with each other alone, and a
+    // leader payoff that comes off the split row is scaled back.
     const bool vec4 = (m & 3) == 0;                      // no piece reaches past its row
     typedef f32x4 f32x4_dword __attribute__((aligned(4)));
     auto load_rows = [&](unsigned first) __attribute__((always_inline)) {
@@ -297,11 +307,24 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
             valid32[ct] = (unsigned)__builtin_amdgcn_ballot_w64(first + ct * 32 + col < count);
+            float scale = 1.0f;
+            if constexpr (XP == 3) {
+                float most = 0.0f;                       // (what `raw` holds past the row is of the row)
+#pragma unroll
+                for (int e = 0; e < HALF; ++e) most = fmaxf(most, fabsf(raw[ct][e]));
+                most = fmaxf(most, pair_other(most, partner_addr));
+                scale = most < 0x1p-60f ? 0x1p64f : 1.0f;
+                if constexpr (UNSCALE) unscale[ct] = most < 0x1p-60f ? 0x1p-64f : 1.0f;
+            }
 #pragma unroll
             for (int e = 0; e < HALF; e += 2) {
                 const int i = h * HALF + e, k = e / 2;
-                const float va = i < m ? raw[ct][e] : 0.0f, vb = i + 1 < m ? raw[ct][e + 1] : 0.0f;
-                const unsigned p0 = pack_bf16(va, vb);
+                float va = i < m ? raw[ct][e] : 0.0f, vb = i + 1 < m ? raw[ct][e + 1] : 0.0f;
+                if constexpr (XF) { xf[ct][e] = va; xf[ct][e + 1] = vb; }
+                if constexpr (XP == 3) { va *= scale; vb *= scale; }
+                constexpr float MOST = 0x1.FEp127f;      // the greatest bf16 number
+                const unsigned p0 = XP == 3 ? pack_bf16(__builtin_amdgcn_fmed3f(va, -MOST, MOST), __builtin_amdgcn_fmed3f(vb, -MOST, MOST))
+                                            : pack_bf16(va, vb);
                 x[ct][0][k] = p0;
                 if constexpr (XP == 3) {
                     // (the differences are exact: x = p0 + p1 + p2)
@@ -310,7 +333,6 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                     x[ct][1][k] = p1;
                     x[ct][2][k] = pack_bf16(ra - bf16_lo(p1), rb - bf16_hi(p1));
                 }
-                if constexpr (XF) { xf[ct][e] = va; xf[ct][e + 1] = vb; }
             }
         }
     };
@@ -400,12 +422,12 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 #pragma unroll
                     for (int k = 0; k < 4; ++k) v[k] = xf[ct][e + k];
                 } else {
-                    // the component from its three parts: exact, p0 + p1 + p2 being the fp32 number
+                    // the component from its three parts, exact: p1 + p2 is what p0 left of it
 #pragma unroll
                     for (int k = 0; k < 4; k += 2) {
                         const unsigned p0 = x[ct][0][(e + k) / 2], p1 = x[ct][XP - 2][(e + k) / 2], p2 = x[ct][XP - 1][(e + k) / 2];
-                        v[k] = (bf16_lo(p0) + bf16_lo(p1)) + bf16_lo(p2);
-                        v[k + 1] = (bf16_hi(p0) + bf16_hi(p1)) + bf16_hi(p2);
+                        v[k] = bf16_lo(p0) + (bf16_lo(p1) + bf16_lo(p2));
+                        v[k + 1] = bf16_hi(p0) + (bf16_hi(p1) + bf16_hi(p2));
                     }
                 }
                 l0 = fmaf(v[0], r[0], l0); l1 = fmaf(v[1], r[1], l1);
@@ -418,9 +440,10 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     auto lead_global = [&](int t, int j) __attribute__((always_inline)) {
         return reinterpret_cast<const u32x4 *>(ATpack + (((size_t)t * n + j) * (2 * HALF) + h * HALF) * LBYTES);
     };
-    auto pair_total = [&](float part) __attribute__((always_inline)) {
+    auto pair_total = [&](int ct, float part) __attribute__((always_inline)) {
         const float other = pair_other(part, partner_addr);
-        return h ? other + part : part + other;          // (lower half) + (upper half)
+        const float l = h ? other + part : part + other; // (lower half) + (upper half)
+        return UNSCALE ? l * unscale[UNSCALE ? ct : 0] : l;
     };
 
     // Exact routine for one (candidate tile, type) of FORM 0 / 1: the type's tiles once more from the
@@ -449,7 +472,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                         const unsigned long long meq = __builtin_amdgcn_ballot_w64(fmaxf(acc[ct][r], LEAST) == gmax);
                         const unsigned hit = (unsigned)(hh ? (meq >> 32) : meq);
                         if (hit == 0u || j > n - 1) continue;               // wave-uniform
-                        const float l = pair_total(half_dot(ct, lead_global(t, j)));
+                        const float l = pair_total(ct, half_dot(ct, lead_global(t, j)));
                         if ((hit >> col) & 1u) {
                             if (nmatch == 0 || l > lbest) { lbest = l; jbest = j; }
                             ++nmatch;
@@ -549,6 +572,9 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
                             float lo[PT];
+                            if constexpr (UNSCALE)
+#pragma unroll
+                                for (int p = 0; p < PT; ++p) l[ct][p] *= unscale[UNSCALE ? ct : 0];
 #pragma unroll
                             for (int p = 0; p < PT; ++p) lo[p] = pair_other(l[ct][p], partner_addr);
 #pragma unroll
@@ -681,7 +707,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                             for (int ct = 0; ct < NT; ++ct) part[ct] = half_dot(ct, lead_global(t, js[ct]));
                         }
 #pragma unroll
-                        for (int ct = 0; ct < NT; ++ct) l[ct] = pair_total(part[ct]);
+                        for (int ct = 0; ct < NT; ++ct) l[ct] = pair_total(ct, part[ct]);
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
                             if (!clean[ct]) exact_type(ct, t, gm[ct], l[ct], js[ct]);
