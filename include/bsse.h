@@ -184,7 +184,13 @@ bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_dev, int64_t
  *                     in; it does not wait for the device; the winning row is copied into
  *                     the handle, so the chunk buffer may be reused once the stream has
  *                     passed it;
- *   bsse_sweep_result waits for the stream and reports like bsse_sweep. */
+ *   bsse_sweep_result waits for the stream and reports like bsse_sweep.
+ * bsse_sweep_chunk may be recorded into a HIP graph, on a handle that has swept a chunk of that size
+ * (BSSE_ESTATE if its scratch would have to grow), and so may bsse_eval.  A replay does what the call would:
+ * it sweeps the rows that the buffer then holds and merges their best into the running best, or, recorded
+ * as the first chunk after bsse_sweep_reset, starts the sweep over with them.  The handle may be used freely
+ * between replays on its stream; n_evals counts calls, not replays, and a reset is consumed by the next
+ * call, not by a replay. */
 bsse_status bsse_sweep_reset(bsse_game *g);
 bsse_status bsse_sweep_chunk(bsse_game *g, const float *candidates_dev, int64_t count,
                              int64_t index_base);

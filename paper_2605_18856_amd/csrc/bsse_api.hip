@@ -60,8 +60,9 @@ extern "C" const char *bsse_status_name(bsse_status s)
 constexpr int MAX_FLAGS = 1024;
 
 struct HostOut {            // pinned, device-visible: kernels write results here directly
-    RunningBest run;        // by the merge kernel of every chunk
+    RunningBest run;        // the running best itself: read and rewritten by every merge, on the device or (one-call sweeps) here
     float fin_v;            // the winner's value as its re-evaluation gave it
+    unsigned epoch;         // small-game kernel: of the current sweep, once a chunk has been recorded into a graph
 };
 
 // Device scratch of the prior batch: kept by the handle and grown on demand, so that repeated
@@ -112,9 +113,11 @@ struct RealisedScratch {
     }
 };
 
-// Device scratch of the streamed sweep: one record per workgroup of a chunk, the running best, the
-// winning row, the tie counter and (small-game kernel) the workgroups' running-best slots.  Owned by the handle and grown on demand, or
-// (`fixed`) a carving of the library's static scratch array that cannot grow.
+// Scratch of the streamed sweep: one record per workgroup of a chunk, the running best, the winning row,
+// the tie counter and (small-game kernel) the workgroups' running-best slots.  Owned by the handle and
+// grown on demand, or (`fixed`) a carving of the library's static scratch array that cannot grow.  The
+// handle's own running best and winning row are the pinned ones (HostOut::run, h_x) and have no second
+// copy: a graph of recorded chunks may merge into them at any time, unseen by the host.
 struct Work {
     float *blk_v = nullptr;
     long long *blk_i = nullptr;
@@ -122,7 +125,7 @@ struct Work {
     SmallSlot *slots = nullptr;      // slot_sets sets of small_num_slots() slots
     int slot_sets = 0;
     RunningBest *run = nullptr;
-    float *best_x = nullptr;         // (not on the small-game kernel)
+    float *best_x = nullptr;
     unsigned long long *tie_counter = nullptr;
     bool fixed = false;
 };
@@ -144,6 +147,9 @@ struct bsse_game {
     Work w;                      // the scratch in use
     // small-game kernel: per-workgroup running bests of the current sweep, folded on demand
     unsigned epoch = 0;          // of the current sweep (slots of other epochs are stale)
+    // A chunk has been recorded into a graph, whose replays the host does not see: from then on the
+    // epoch lives in h_out->epoch, where kernels of the stream advance and read it.
+    bool recorded = false;
     bool fold_pending = false;   // chunks swept since the last fold
     bool fold_first = true;      // the next fold is the first of its sweep
     bool ties_dirty = false;     // the device tie counter may be non-zero
@@ -176,10 +182,8 @@ struct bsse_game {
     int32_t *h_br = nullptr;                // the winner's best responses [K]
     float *h_x = nullptr;                   // its row [m]
     float *h_l = nullptr;                   // its per-type leader payoffs [K] (general and any-shape kernel)
-    bool hx_valid = false;                  // h_x holds the row of the running best and nothing is in flight
-    // Any-shape kernel: a sweep in one call leaves its result on the host only (h_out->run, h_x, h_br);
-    // the device copies (w.run, w.best_x) are brought up to date when a further chunk needs them.
-    bool host_best = false;
+    std::vector<float> won_x;               // row and best responses of the result last reported
+    std::vector<int32_t> won_br;
     float *row_l = nullptr;                 // per-type outputs of sliced launches, type-major
     int32_t *row_br = nullptr;
     size_t cap_row_l = 0, cap_row_br = 0;
@@ -245,7 +249,7 @@ void free_game(bsse_game *g)
     (void)hipFree(g->dBpack); (void)hipFree(g->dATpack);
     (void)hipFree(g->gen); (void)hipFree(g->lat_table);
     (void)hipFree(g->w.blk_v); (void)hipFree(g->w.blk_i); (void)hipFree(g->w.slots);
-    (void)hipFree(g->w.run); (void)hipFree(g->w.best_x); (void)hipFree(g->w.tie_counter);
+    (void)hipFree(g->w.tie_counter);
     g->pri.release();
     g->topk.release();
     g->real.release();
@@ -265,12 +269,23 @@ void free_game(bsse_game *g)
     delete g;
 }
 
+// Whether the handle's stream is being captured.  Asynchronous calls then go without the per-type scratch
+// (uncut): it cannot be allocated there.
+bool recording(const bsse_game *g)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(g->stream, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
+}
+
 bsse_status ensure_blocks(bsse_game *g, long long nblocks)
 {
     if (nblocks <= g->w.blk_cap) return BSSE_OK;
     if (g->w.fixed)
         return fail(BSSE_EOVERFLOW, "%lld workgroup records exceed the %lld the static scratch holds",
                     nblocks, g->w.blk_cap);
+    if (recording(g))
+        return fail(BSSE_ESTATE, "%lld workgroup records are needed and nothing can be allocated while the stream is captured: "
+                    "sweep a chunk of this size before", nblocks);
     // the stream may still be reading the old workspace
     HIP_TRY(hipStreamSynchronize(g->stream));
     (void)hipFree(g->w.blk_v); (void)hipFree(g->w.blk_i);
@@ -373,14 +388,6 @@ hipError_t launch_rows(bsse_game *g, const SweepArgs &a, hipStream_t stream)
 long long row_blocks(const bsse_game *g, long long count)
 {
     return on_any(g) ? any_row_blocks(g->view, count) : on_tiny(g) ? tiny_row_blocks(g->view, count) : mfma_row_blocks(g->view, count);
-}
-
-// Whether the handle's stream is being captured.  Asynchronous calls then go without the per-type scratch
-// (uncut): it cannot be allocated there, and a graph must not keep a pointer that a later call outgrows.
-bool recording(const bsse_game *g)
-{
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(g->stream, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
 }
 
 // Per-candidate outputs (a.V_out, a.br_out [count][K], a.l_out with the caller's strides; each nullable).
@@ -643,6 +650,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     g->path = path;
     try {
         g->hA.assign(A, A + elems); g->hB.assign(B, B + elems); g->hprior.assign(prior, prior + K);
+        g->won_x.resize((size_t)m); g->won_br.resize((size_t)K);
     } catch (...) { delete g; return fail(BSSE_ENOMEM, "host allocation failed"); }
     g->view.variant = variant;
 
@@ -720,14 +728,12 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
             hipError_t pe = mfma_prepare(variant, K);
             if (pe != hipSuccess) { st = fail(BSSE_EDEVICE, "mfma_prepare: %s", hipGetErrorString(pe)); break; }
         }
-        if ((st = zeroed((void **)&g->w.run, sizeof(RunningBest))) != BSSE_OK) break;
-        if ((st = zeroed((void **)&g->w.best_x, (size_t)m * 4)) != BSSE_OK) break;
         if ((st = zeroed((void **)&g->w.tie_counter, 8)) != BSSE_OK) break;
         if (use_mfma && mfma_is_small(variant) &&       // epoch 0 marks a slot never written
             (st = zeroed((void **)&g->w.slots, (size_t)3 * small_num_slots() * sizeof(SmallSlot))) != BSSE_OK) break;
         g->w.slot_sets = g->w.slots ? 3 : 0;
         const size_t off_flag = 256, off_br = off_flag + MAX_FLAGS * sizeof(unsigned), off_l = off_br + (size_t)K * 4,
-                     off_x = off_l + (size_t)K * 4, host_bytes = off_x + (size_t)m * 4;
+                     off_x = (off_l + (size_t)K * 4 + 63) / 64 * 64, host_bytes = off_x + (size_t)m * 4;     // (an aligned row)
         static_assert(sizeof(HostOut) <= 256, "the flags start behind it");
         hipError_t e = hipHostMalloc((void **)&g->h_out, host_bytes, hipHostMallocDefault);
         if (e != hipSuccess) { st = fail(BSSE_ENOMEM, "hipHostMalloc: %s", hipGetErrorString(e)); break; }
@@ -737,6 +743,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         g->h_br = reinterpret_cast<int32_t *>(hb + off_br);
         g->h_l = reinterpret_cast<float *>(hb + off_l);
         g->h_x = reinterpret_cast<float *>(hb + off_x);
+        g->w.run = &g->h_out->run; g->w.best_x = g->h_x;
     } while (0);
     if (st != BSSE_OK) { free_game(g); return st; }
 
@@ -1032,31 +1039,30 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     bsse_status st;
     const long long count = a.count;
     const bool small = on_small_kernel(g);
-    if (g->host_best && !g->fresh) {             // the running best so far goes back to the device
-        // (the host copies change in stream order only: by this chunk's merge, or once a later call has waited)
-        static_assert(sizeof(RunningBest) % 4 == 0, "copied in words");
-        HIP_TRY(launch_copy_words(&g->h_out->run, g->w.run, sizeof(RunningBest) / 4, g->stream));
-        HIP_TRY(launch_copy_words(g->h_x, g->w.best_x, (size_t)g->m, g->stream));
-    }
-    g->host_best = false; g->hx_valid = false;
     long long nblocks = 0;
     hipStream_t stream = g->stream;
-    const bool rows = !small && !g->w.fixed && few_rows(g, count) && !recording(g);     // (the static scratch holds records only)
+    const bool record = recording(g);
+    const bool rows = !small && !g->w.fixed && few_rows(g, count) && !record;     // (the static scratch holds records only)
     FinishRowsArgs f{};
     if (small) {
         // every workgroup keeps its own running best over the chunks: nothing but the sweep
         // kernel runs per chunk; bsse_sweep_result folds
+        if (record && !g->recorded) { g->h_out->epoch = g->epoch; g->recorded = true; }
         if (g->fresh) {
             if ((st = join_aux(g)) != BSSE_OK) return st;        // an abandoned sweep may still be running
             g->epoch += 1;
             if (g->epoch == 0) g->epoch = 1;         // 0 is the mark of a slot never written
-            g->fold_first = true;
+            g->fold_first = !g->recorded;
             g->chunk_seq = 0;
-            g->set_used[0] = g->set_used[1] = g->set_used[2] = 0;
-            if (g->ties_dirty) HIP_TRY(launch_clear_u64(g->w.tie_counter, g->stream));   // an abandoned sweep's
+            if (g->recorded) {                       // (and a replay may still write any slot that a recorded chunk writes)
+                HIP_TRY(launch_new_epoch(&g->h_out->epoch, g->w.tie_counter, g->w.run, g->stream));
+            } else {
+                g->set_used[0] = g->set_used[1] = g->set_used[2] = 0;
+                if (g->ties_dirty) HIP_TRY(launch_clear_u64(g->w.tie_counter, g->stream));   // an abandoned sweep's
+            }
         }
         int set = g->w.slot_sets - 1;                // the caller's stream (the last set)
-        if (a.gen && g->chunk_seq > 0 && g->w.slot_sets == 3) {
+        if (a.gen && g->chunk_seq > 0 && g->w.slot_sets == 3 && !record) {
             // (the first chunk stays on the caller's stream, so a one-chunk sweep pays for no events)
             if ((st = ensure_aux(g)) != BSSE_OK) return st;
             set = (int)(g->chunk_seq & 1u);
@@ -1070,10 +1076,12 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
         g->chunk_seq += 1;
         g->set_used[set] = std::max(g->set_used[set], (int)sweep_blocks(g, count));
         a.small.slots = g->w.slots + (size_t)set * small_num_slots(); a.small.epoch = g->epoch;
+        a.small.epoch_now = g->recorded ? &g->h_out->epoch : nullptr;
         a.tie_counter = g->w.tie_counter;
     } else {
         nblocks = rows ? (count + FINISH_ROWS - 1) / FINISH_ROWS : sweep_blocks(g, count);
-        if ((st = ensure_blocks(g, nblocks)) != BSSE_OK) return st;
+        // (enough for the same chunk uncut, as it is recorded)
+        if ((st = ensure_blocks(g, rows ? std::max(nblocks, sweep_blocks(g, count)) : nblocks)) != BSSE_OK) return st;
         a.tie_counter = g->w.tie_counter;
         if (rows) {
             if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * g->K * sizeof(float))) != BSSE_OK) return st;
@@ -1110,15 +1118,23 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     return BSSE_OK;
 }
 
+// Waits for the handle's stream by a one-thread kernel whose flag is polled.
+bsse_status wait_stream(bsse_game *g)
+{
+    HIP_TRY(launch_signal(new_done(g), g->stream));
+    return wait_flags(g, 1);
+}
+
 // Small-game kernel: fold the workgroups' running bests into the handle's result (value, index,
-// row, best responses, tie count) and wait for it.  No-op when nothing was swept since the last fold.
+// row, best responses, tie count) and wait for it; for the stream alone when nothing can have been swept
+// since the last fold.
 bsse_status fold_small(bsse_game *g)
 {
-    if (!g->fold_pending) return BSSE_OK;
+    if (!g->fold_pending && !g->recorded) return wait_stream(g);
     bsse_status st = join_aux(g);
     if (st != BSSE_OK) return st;
     FinishArgs f{};
-    f.slots = g->w.slots; f.epoch = g->epoch;
+    f.slots = g->w.slots; f.epoch = g->epoch; f.epoch_now = g->recorded ? &g->h_out->epoch : nullptr;
     for (int q = 0; q < 3; ++q) f.used[q] = g->set_used[q];
     f.first = g->fold_first ? 1 : 0;
     f.tie_counter = g->w.tie_counter;
@@ -1241,7 +1257,7 @@ extern "C" bsse_status bsse_sweep_result(bsse_game *g, bsse_result *res, int32_t
     bsse_status st = BSSE_OK;
     if (on_small_kernel(g)) {
         st = fold_small(g);
-    } else if (!g->host_best) {
+    } else {
         SweepArgs a{};
         a.X = g->w.best_x; a.count = 1;
         a.br_out = g->h_br; a.br_sc = g->K; a.br_st = 1;
@@ -1267,7 +1283,6 @@ namespace {
 bsse_status report_result(bsse_game *g, bsse_result *res, int32_t *best_response_out)
 {
     const bool has = g->h_out->run.has != 0;
-    g->hx_valid = has;
     if (has && !(g->h_out->fin_v == g->h_out->run.value))
         return fail(BSSE_EDEVICE, "internal: re-evaluated winner value %.9g differs from swept value %.9g",
                     (double)g->h_out->fin_v, (double)g->h_out->run.value);
@@ -1277,6 +1292,10 @@ bsse_status report_result(bsse_game *g, bsse_result *res, int32_t *best_response
     res->n_tie_evals = (int64_t)g->h_out->run.ties;
     if (has && best_response_out) memcpy(best_response_out, g->h_br, (size_t)g->K * 4);
     g->result_valid = has && !g->w.fixed;
+    if (g->result_valid) {
+        memcpy(g->won_x.data(), g->h_x, (size_t)g->m * sizeof(float));
+        memcpy(g->won_br.data(), g->h_br, (size_t)g->K * sizeof(int32_t));
+    }
     return BSSE_OK;
 }
 
@@ -1311,7 +1330,6 @@ bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_resul
 {
     const int m = g->m, K = g->K;
     bsse_status st;
-    g->host_best = false; g->hx_valid = false;
     const bool rows = host_folds(g, count), single = !rows && one_launch(g, count), recs = rows || single;
     const long long nrec = single ? tiny_num_blocks(count) : (count + FINISH_ROWS - 1) / FINISH_ROWS;
     const long long used = recs ? nrec : 0;
@@ -1386,7 +1404,6 @@ bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_resul
     } else if (g->h_out->run.has) {
         g->h_out->fin_v = value_of(g, g->h_l);
     }
-    g->host_best = true;
     return report_result(g, res, best_response_out);
 }
 
@@ -1399,14 +1416,9 @@ extern "C" bsse_status bsse_sweep_best_row(bsse_game *g, float *x_out)
     if (!x_out) return fail(BSSE_EINVAL, "x_out is NULL");
     DeviceGuard dg(g->device);
     if (!dg.ok) return fail(BSSE_EDEVICE, "hipSetDevice failed");
-    if (g->fresh || !g->hx_valid) {
-        if (!g->fresh && on_small_kernel(g)) {
-            bsse_status st = fold_small(g);
-            if (st != BSSE_OK) return st;
-        } else {
-            HIP_TRY(hipStreamSynchronize(g->stream));
-        }
-    }
+    // (a graph of recorded chunks, or other work of the caller, may still be on the stream)
+    bsse_status st = !g->fresh && on_small_kernel(g) ? fold_small(g) : wait_stream(g);
+    if (st != BSSE_OK) return st;
     if (g->fresh || !g->h_out->run.has) return fail(BSSE_ESTATE, "no candidate has been swept since the last reset");
     memcpy(x_out, g->h_x, (size_t)g->m * sizeof(float));
     return BSSE_OK;
@@ -1474,14 +1486,15 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
     // the handle works on the static scratch for the length of this call; its own sweep state
     // is what bsse_sweep leaves behind as well: reset
     struct Swap {
-        bsse_game *g; Work own; bool timing, ties_dirty;
+        bsse_game *g; Work own; bool timing, ties_dirty; int used[3];
         ~Swap()
         {
             g->w = own; g->timing = timing; g->ties_dirty = ties_dirty;
+            for (int q = 0; q < 3; ++q) g->set_used[q] = used[q];
             g->fresh = true; g->fold_pending = false; g->result_valid = false; g->n_evals = 0;
-            g->host_best = false; g->hx_valid = false;
         }
-    } swap{ g, g->w, g->timing, g->ties_dirty };
+    } swap{ g, g->w, g->timing, g->ties_dirty, { g->set_used[0], g->set_used[1], g->set_used[2] } };
+    for (int &u : g->set_used) u = 0;          // (the array holds one set of slots)
     Work w;
     w.run = reinterpret_cast<RunningBest *>(ptr + ST_OFF_RUN);
     w.tie_counter = reinterpret_cast<unsigned long long *>(ptr + ST_OFF_TIES);
@@ -1917,8 +1930,8 @@ extern "C" bsse_status bsse_polish(bsse_game *g, const int32_t *profile, float *
     std::vector<float> start((size_t)m), rows((size_t)kPolishRows * m), vals((size_t)kPolishRows);
     std::vector<int32_t> brs((size_t)kPolishRows * K);
     std::vector<double> x((size_t)m);
-    memcpy(prof.data(), profile ? profile : g->h_br, (size_t)K * sizeof(int32_t));
-    memcpy(start.data(), g->h_x, (size_t)m * sizeof(float));     // (a reported result: nothing in flight)
+    memcpy(prof.data(), profile ? profile : g->won_br.data(), (size_t)K * sizeof(int32_t));
+    memcpy(start.data(), g->won_x.data(), (size_t)m * sizeof(float));
     double v_lp = 0.0;
     const int rc = solve_profile_lp(m, n, K, g->hA.data(), g->hB.data(), g->hprior.data(), prof.data(),
                                     x.data(), &v_lp);

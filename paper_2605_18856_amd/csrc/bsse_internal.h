@@ -70,6 +70,7 @@ struct SmallSlot {
 struct SmallSweep {
     SmallSlot *slots;        // [small_num_slots()]; nullptr outside the small-game sweep
     unsigned epoch;
+    const unsigned *epoch_now;   // where the epoch is read instead (a launch that a graph may replay), or nullptr
 };
 
 // Fold of the slots into the result of the sweep.
@@ -77,6 +78,7 @@ struct FinishArgs {
     const SmallSlot *slots;  // up to three sets, small_num_slots() apart
     int used[3];             // slots of each set that a launch of this sweep may have written
     unsigned epoch;
+    const unsigned *epoch_now;
     int first;               // != 0: first fold of this sweep (the tie count restarts)
     unsigned long long *tie_counter;
     RunningBest *run;        // device
@@ -226,7 +228,8 @@ hipError_t launch_finish_rows(const FinishRowsArgs &f, hipStream_t s);
 
 // first != 0: the running best is replaced, not merged (start of a sweep).  tie_counter (the
 // chunk's count, left by the sweep kernel) is folded into run->ties and cleared.  The merged
-// record is also written to run_host and the row of a new best to x_host (pinned host memory).
+// record is also written to run_host and the row of a new best to x_host (pinned host memory; for a
+// handle's own sweep run and best_x are these).
 hipError_t launch_reduce_merge(const float *blk_v, const long long *blk_i, long long nblocks,
                                const float *X, long long index_base, int m, int first,
                                unsigned long long *tie_counter, RunningBest *run,
@@ -236,6 +239,10 @@ hipError_t launch_reduce_merge(const float *blk_v, const long long *blk_i, long 
 hipError_t launch_copy_words(const void *src, void *dst, size_t words, hipStream_t s);
 // *p = 0 by a one-thread kernel (a fill node that is safe to capture in a graph).
 hipError_t launch_clear_u64(unsigned long long *p, hipStream_t s);
+// A new sweep on the small-game kernel, in stream order: the next epoch, no ties counted.
+hipError_t launch_new_epoch(unsigned *epoch, unsigned long long *tie_counter, RunningBest *run, hipStream_t s);
+// Nothing but the completion flag 0.
+hipError_t launch_signal(const Done &d, hipStream_t s);
 // Zero `bytes` (a multiple of 16) at the 16-byte aligned device address p, by a kernel.
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 

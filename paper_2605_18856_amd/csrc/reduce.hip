@@ -5,6 +5,7 @@
 // lower global index), so the result does not depend on the order of the chunks either.  When the running best changes, the
 // winning candidate row is copied into the handle so the chunk buffer can be recycled.
 #include "bsse_internal.h"
+#include "done_device.h"
 #include <limits.h>
 
 namespace bsse {
@@ -28,6 +29,14 @@ reduce_merge_kernel(const float *__restrict__ blk_v, const long long *__restrict
     __shared__ long long si[RT / 64];
     __shared__ long long win;          // chunk-local row to copy, or -1
 
+    // (requested first: the running best of a handle's own sweep is in host memory, and its way here is
+    // that of the records)
+    RunningBest r{};
+    unsigned long long ties = 0;
+    if (threadIdx.x == 0) {
+        if (!first) r = *run;
+        ties = *tie_counter;
+    }
     float bv = -INFINITY;
     long long bi = LLONG_MAX;
     for (long long b = threadIdx.x; b < nblocks; b += RT) {
@@ -48,7 +57,6 @@ reduce_merge_kernel(const float *__restrict__ blk_v, const long long *__restrict
         for (int w = 1; w < RT / 64; ++w)
             if (better(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
         long long w_row = -1;
-        RunningBest r = *run;
         if (first) { r.value = 0.0f; r.has = 0; r.index = -1; r.ties = 0ull; }
         if (bi != LLONG_MAX && (!r.has || bv > r.value || (bv == r.value && bi < r.index))) {
             r.value = bv;
@@ -56,7 +64,7 @@ reduce_merge_kernel(const float *__restrict__ blk_v, const long long *__restrict
             r.has = 1;
             w_row = bi - index_base;
         }
-        r.ties += *tie_counter;
+        r.ties += ties;
         *tie_counter = 0ull;                 // the next chunk starts from zero
         *run = r;
         *run_host = r;
@@ -72,6 +80,16 @@ reduce_merge_kernel(const float *__restrict__ blk_v, const long long *__restrict
 }
 
 __global__ void clear_u64_kernel(unsigned long long *p) { *p = 0ull; }
+
+__global__ void new_epoch_kernel(unsigned *epoch, unsigned long long *tie_counter, RunningBest *run)
+{
+    const unsigned e = *epoch + 1u;
+    *epoch = e ? e : 1u;                     // 0 is the mark of a slot never written
+    *tie_counter = 0ull;
+    run->ties = 0ull;
+}
+
+__global__ void signal_kernel(Done d) { signal_done(d, 0); }
 
 __global__ void __launch_bounds__(256) fill_zero_kernel(uint4 *p, size_t n16)
 {
@@ -112,6 +130,18 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s)
 hipError_t launch_clear_u64(unsigned long long *p, hipStream_t s)
 {
     hipLaunchKernelGGL(clear_u64_kernel, dim3(1), dim3(1), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_new_epoch(unsigned *epoch, unsigned long long *tie_counter, RunningBest *run, hipStream_t s)
+{
+    hipLaunchKernelGGL(new_epoch_kernel, dim3(1), dim3(1), 0, s, epoch, tie_counter, run);
+    return hipGetLastError();
+}
+
+hipError_t launch_signal(const Done &d, hipStream_t s)
+{
+    hipLaunchKernelGGL(signal_kernel, dim3(1), dim3(1), 0, s, d);
     return hipGetLastError();
 }
 

@@ -362,10 +362,11 @@ __device__ __forceinline__ void small_body(const GameView &g, const SweepArgs &a
             // that one row again.
             SmallSlot *slot = a.small.slots + block;
             const long long gi = a.index_base + (long long)best_c;
+            const unsigned epoch = a.small.epoch_now ? *a.small.epoch_now : a.small.epoch;
             if (best_c != 0xFFFFFFFFu &&
-                (slot->epoch != a.small.epoch || best_v > slot->value ||
+                (slot->epoch != epoch || best_v > slot->value ||
                  (best_v == slot->value && gi < slot->index))) {
-                slot->value = best_v; slot->epoch = a.small.epoch; slot->index = gi;
+                slot->value = best_v; slot->epoch = epoch; slot->index = gi;
                 if (GEN) {
                     float q[SM_M];
                     const long long row = a.gen_first + (long long)best_c;
@@ -420,6 +421,7 @@ small_finish_kernel(GameView g, FinishArgs f)
     long long bi = LLONG_MAX;
     int bb = -1;
     RunningBest r{};
+    const unsigned epoch = f.epoch_now ? *f.epoch_now : f.epoch;
     if (tid == 0) {
         if (!f.first) r = *f.run;
         r.ties += *f.tie_counter;
@@ -433,7 +435,7 @@ small_finish_kernel(GameView g, FinishArgs f)
             const uint4 head = *reinterpret_cast<const uint4 *>(&f.slots[s]);
             const float v = __uint_as_float(head.x);
             const long long i = (long long)(((unsigned long long)head.w << 32) | head.z);
-            if (head.y == f.epoch && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; bb = s; }
+            if (head.y == epoch && (v > bv || (v == bv && i < bi))) { bv = v; bi = i; bb = s; }
         }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
