@@ -150,6 +150,9 @@ struct bsse_game {
     // A chunk has been recorded into a graph, whose replays the host does not see: from then on the
     // epoch lives in h_out->epoch, where kernels of the stream advance and read it.
     bool recorded = false;
+    // Memory of the handle that recorded calls name (`kept`), and what of it has been replaced since: freed
+    // with the handle, for a graph may be replayed as long as that lives.
+    std::vector<void *> kept, retired;
     bool fold_pending = false;   // chunks swept since the last fold
     bool fold_first = true;      // the next fold is the first of its sweep
     bool ties_dirty = false;     // the device tie counter may be non-zero
@@ -264,6 +267,7 @@ void free_game(bsse_game *g)
     if (g->h_rec) (void)hipHostFree(g->h_rec);
     if (g->h_centre) (void)hipHostFree(g->h_centre);
     (void)hipFree(g->row_l); (void)hipFree(g->row_br);
+    for (void *q : g->retired) (void)hipFree(q);
     for (hipEvent_t e : g->ev) (void)hipEventDestroy(e);
     for (hipEvent_t e : g->ev_pool) (void)hipEventDestroy(e);
     delete g;
@@ -277,6 +281,33 @@ bool recording(const bsse_game *g)
     return hipStreamIsCapturing(g->stream, &c) != hipSuccess || c != hipStreamCaptureStatusNone;
 }
 
+// A call that names `ptr` is being recorded: it stays.
+bsse_status keep(bsse_game *g, void *ptr)
+{
+    if (!ptr || std::find(g->kept.begin(), g->kept.end(), ptr) != g->kept.end()) return BSSE_OK;
+    try {
+        g->kept.reserve(g->kept.size() + 1);
+        g->retired.reserve(g->retired.size() + g->kept.size() + 1);      // (drop does not allocate)
+    } catch (...) { return fail(BSSE_ENOMEM, "host allocation failed"); }
+    g->kept.push_back(ptr);
+    return BSSE_OK;
+}
+bool is_kept(const bsse_game *g, void *ptr) { return std::find(g->kept.begin(), g->kept.end(), ptr) != g->kept.end(); }
+// Device memory that the handle has no more use for and nothing enqueued still uses.
+void drop(bsse_game *g, void *ptr)
+{
+    const auto at = std::find(g->kept.begin(), g->kept.end(), ptr);
+    if (at == g->kept.end()) { (void)hipFree(ptr); return; }
+    g->kept.erase(at);
+    g->retired.push_back(ptr);
+}
+// The same for a buffer of candidates that may lie in the handle's generated set.
+bsse_status keep_rows(bsse_game *g, const float *X)
+{
+    const auto *p = reinterpret_cast<const unsigned char *>(X), *gen = reinterpret_cast<const unsigned char *>(g->gen);
+    return g->gen && p >= gen && p < gen + g->gen_cap ? keep(g, g->gen) : BSSE_OK;
+}
+
 bsse_status ensure_blocks(bsse_game *g, long long nblocks)
 {
     if (nblocks <= g->w.blk_cap) return BSSE_OK;
@@ -288,7 +319,7 @@ bsse_status ensure_blocks(bsse_game *g, long long nblocks)
                     "sweep a chunk of this size before", nblocks);
     // the stream may still be reading the old workspace
     HIP_TRY(hipStreamSynchronize(g->stream));
-    (void)hipFree(g->w.blk_v); (void)hipFree(g->w.blk_i);
+    drop(g, g->w.blk_v); drop(g, g->w.blk_i);
     g->w.blk_v = nullptr; g->w.blk_i = nullptr; g->w.blk_cap = 0;
     HIP_TRY(hipMalloc((void **)&g->w.blk_v, (size_t)nblocks * sizeof(float)));
     HIP_TRY(hipMalloc((void **)&g->w.blk_i, (size_t)nblocks * sizeof(long long)));
@@ -301,7 +332,7 @@ bsse_status ensure_gen(bsse_game *g, unsigned long long rows)
     const unsigned long long bytes = rows * (unsigned long long)g->m * sizeof(float);
     if (bytes <= g->gen_cap) return BSSE_OK;
     HIP_TRY(hipStreamSynchronize(g->stream));
-    (void)hipFree(g->gen);
+    drop(g, g->gen);
     g->gen = nullptr; g->gen_cap = 0; g->gen_count = -1;
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
@@ -342,7 +373,7 @@ bsse_status grow_device(bsse_game *g, void **ptr, size_t *cap, size_t bytes)
 {
     if (bytes <= *cap) return BSSE_OK;
     HIP_TRY(hipStreamSynchronize(g->stream));
-    (void)hipFree(*ptr);
+    drop(g, *ptr);
     *ptr = nullptr; *cap = 0;
     HIP_TRY(hipMalloc(ptr, bytes));
     *cap = bytes;
@@ -394,14 +425,16 @@ long long row_blocks(const bsse_game *g, long long count)
 bsse_status launch_eval(bsse_game *g, SweepArgs a)
 {
     a.br_sc = g->K; a.br_st = 1;
+    const bool record = recording(g);
+    bsse_status st;
+    if (record && (st = keep_rows(g, a.X)) != BSSE_OK) return st;
     if (!cuts_types(g)) { HIP_TRY(launch_sweep(g, a, true)); return BSSE_OK; }
     if (!a.V_out && (a.l_out || on_any(g) || on_tiny(g))) { HIP_TRY(launch_rows(g, a, g->stream)); return BSSE_OK; }
-    if (a.l_out || !few_rows(g, a.count) || recording(g)) {
+    if (a.l_out || !few_rows(g, a.count) || record) {
         HIP_TRY(launch_sweep(g, a, true));
         return BSSE_OK;
     }
-    bsse_status st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float));
-    if (st != BSSE_OK) return st;
+    if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float))) != BSSE_OK) return st;
     FinishRowsArgs f{};
     f.l = g->row_l; f.prior = g->dprior; f.count = a.count; f.K = g->K; f.m = g->m; f.V_out = a.V_out;
     a.V_out = nullptr; a.l_out = g->row_l; a.l_sc = 1; a.l_st = a.count;
@@ -870,9 +903,9 @@ bsse_status ensure_lattice_table(bsse_game *g, int N)
                 tab[(size_t)q * (N + 1) + R] = v;
             }
         g->lat_table_N = -1;
-        if (tab_elems * 8 > g->lat_table_cap) {
+        if (tab_elems * 8 > g->lat_table_cap || is_kept(g, g->lat_table)) {
             HIP_TRY(hipStreamSynchronize(g->stream));
-            (void)hipFree(g->lat_table);
+            drop(g, g->lat_table);
             g->lat_table = nullptr; g->lat_table_cap = 0;
             HIP_TRY(hipMalloc((void **)&g->lat_table, tab_elems * 8));
             g->lat_table_cap = tab_elems * 8;
@@ -895,6 +928,7 @@ bsse_status lattice_impl(bsse_game *g, int N, const float *centre, float radius,
     if ((st = ensure_gen(g, (unsigned long long)cnt)) != BSSE_OK) return st;
     if ((st = ensure_lattice_table(g, N)) != BSSE_OK) return st;
     if (centre && (st = upload_centre(g, centre)) != BSSE_OK) return st;
+    if (recording(g) && ((st = keep(g, g->gen)) != BSSE_OK || (st = keep(g, g->lat_table)) != BSSE_OK)) return st;
     HIP_TRY(launch_lattice(g->lat_table, m, N, cnt, centre ? g->centre_dev : nullptr, radius, 1, g->gen, g->stream));
     g->gen_count = cnt;
     *count_out = cnt;
@@ -939,6 +973,7 @@ bsse_status dirichlet_impl(bsse_game *g, uint64_t seed, int64_t first, int64_t c
         bsse_status st = ensure_gen(g, (unsigned long long)count);
         if (st != BSSE_OK) return st;
         dst = g->gen;
+        if (recording(g) && (st = keep(g, dst)) != BSSE_OK) return st;
     }
     if (centre) {
         bsse_status st = upload_centre(g, centre);
@@ -1043,6 +1078,7 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     hipStream_t stream = g->stream;
     const bool record = recording(g);
     const bool rows = !small && !g->w.fixed && few_rows(g, count) && !record;     // (the static scratch holds records only)
+    if (record && a.X && (st = a.X == g->stage ? keep(g, g->stage) : keep_rows(g, a.X)) != BSSE_OK) return st;
     FinishRowsArgs f{};
     if (small) {
         // every workgroup keeps its own running best over the chunks: nothing but the sweep
@@ -1082,6 +1118,7 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
         nblocks = rows ? (count + FINISH_ROWS - 1) / FINISH_ROWS : sweep_blocks(g, count);
         // (enough for the same chunk uncut, as it is recorded)
         if ((st = ensure_blocks(g, rows ? std::max(nblocks, sweep_blocks(g, count)) : nblocks)) != BSSE_OK) return st;
+        if (record && ((st = keep(g, g->w.blk_v)) != BSSE_OK || (st = keep(g, g->w.blk_i)) != BSSE_OK)) return st;
         a.tie_counter = g->w.tie_counter;
         if (rows) {
             if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * g->K * sizeof(float))) != BSSE_OK) return st;

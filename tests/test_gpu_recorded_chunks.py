@@ -141,3 +141,63 @@ def test_recording_alone_changes_nothing(recorder):
     r.replay(graph, A)                                   # (polishing works on the result last reported)
     assert polished.value >= float(r.V[B].max()) and np.array_equal(bsse.bsse_polish(g).x, polished.x)
     r.check(bsse.bsse_sweep_result(g), (B, 0), (A, N))
+
+
+@_games
+def test_scratch_is_outgrown(recorder):
+    """Larger chunks and generated sets after the recording: what the graph names stays as it was."""
+    import torch
+    r, g = recorder, recorder.g
+    A, B = 0, 1
+    bsse.bsse_sweep_chunk(g, r.sets[A], N, 0)
+    graphs = [r.record(N)]
+    big = torch.cat(list(r.sets) * 20)
+    for copies in (4, 20, 80):
+        bsse.bsse_sweep_reset(g)
+        bsse.bsse_sweep_chunk(g, big[:copies * N], copies * N, 0)
+        bsse.bsse_sweep_result(g)
+        graphs.append(r.record(N))
+    for graph in graphs:
+        bsse.bsse_sweep(g, r.sets[A], N)
+        r.replay(graph, B)
+        r.check(bsse.bsse_sweep_result(g), (A, 0), (B, N))
+    # rows of the handle, then a set of another size
+    bsse.bsse_dirichlet(g, 5, 0, N)
+    rows = bsse.candidates_to_host(g)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=r.stream):
+        bsse.bsse_sweep_chunk(g, None, 0, N)
+    bsse.bsse_dirichlet(g, 6, 0, 40 * N)
+    with torch.cuda.stream(r.stream):
+        torch.full((40 * N, g.m), 7.0, device="cuda")    # (memory that was freed would hold these)
+    bsse.bsse_sweep(g, r.sets[A], 1)
+    with torch.cuda.stream(r.stream):
+        graph.replay()
+    out = bsse.bsse_sweep_result(g)
+    first = bsse.bsse_sweep(g, r.sets[A], 1)
+    second = bsse.bsse_sweep(g, torch.from_numpy(rows).cuda(), N)
+    assert out.best_value == max(first.best_value, second.best_value)
+    if second.best_value > first.best_value:
+        assert out.best_index == N + second.best_index and np.array_equal(out.best_response, second.best_response)
+
+
+@pytest.mark.parametrize("shape", [(150, 9, 3), (30, 50, 6), (32, 32, 16)], ids=lambda s: "m%dn%dK%d" % s)
+def test_recording_needs_scratch(shape):
+    import torch
+    m, n, K = shape
+    game = workloads.small_game(m, n, K, 3)
+    with _make(game) as g:
+        X = torch.from_numpy(workloads.host_candidates(m, N, 1)).cuda()
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        bsse.bsse_set_stream(g, stream.cuda_stream)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            X.add_(0.0)
+            with pytest.raises(bsse.BsseError) as err:
+                bsse.bsse_sweep_chunk(g, X, N, 0)
+        assert err.value.status == bsse.BSSE_ESTATE
+        graph.replay()                                   # (the capture itself is as good as before)
+        torch.cuda.synchronize()
+        bsse.bsse_set_stream(g, None)
