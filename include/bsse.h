@@ -225,7 +225,8 @@ bsse_status bsse_sweep_dirichlet_chunk(bsse_game *g, uint64_t seed, int64_t firs
 
 /* Per-candidate outputs of the same kernels (steps 2-4 without the arg-max), for
  * checking: values_dev_out = device [count] fp32, br_dev_out = device [count][K] int32;
- * either may be NULL.  Enqueued on the handle's stream; does not wait. */
+ * either may be NULL.  Enqueued on the handle's stream; does not wait (scratch for a few rows is
+ * allocated on first use and when a later call needs more, and kept until bsse_destroy). */
 bsse_status bsse_eval(bsse_game *g, const float *candidates_dev, int64_t count,
                       float *values_dev_out, int32_t *br_dev_out);
 

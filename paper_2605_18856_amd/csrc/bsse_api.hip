@@ -285,21 +285,33 @@ bool recording(const bsse_game *g)
 bsse_status keep(bsse_game *g, void *ptr)
 {
     if (!ptr || std::find(g->kept.begin(), g->kept.end(), ptr) != g->kept.end()) return BSSE_OK;
-    try {
-        g->kept.reserve(g->kept.size() + 1);
-        g->retired.reserve(g->retired.size() + g->kept.size() + 1);      // (drop does not allocate)
-    } catch (...) { return fail(BSSE_ENOMEM, "host allocation failed"); }
-    g->kept.push_back(ptr);
+    try { g->kept.push_back(ptr); } catch (...) { return fail(BSSE_ENOMEM, "host allocation failed"); }
     return BSSE_OK;
 }
 bool is_kept(const bsse_game *g, void *ptr) { return std::find(g->kept.begin(), g->kept.end(), ptr) != g->kept.end(); }
-// Device memory that the handle has no more use for and nothing enqueued still uses.
+// Device memory that the handle has no more use for but that enqueued work or a graph may still use.  (No
+// room to note it: it is never freed.)
+void retire(bsse_game *g, void *ptr) noexcept
+{
+    g->kept.erase(std::remove(g->kept.begin(), g->kept.end(), ptr), g->kept.end());
+    try { if (ptr) g->retired.push_back(ptr); } catch (...) { }
+}
+// The same where nothing enqueued still uses it.
 void drop(bsse_game *g, void *ptr)
 {
-    const auto at = std::find(g->kept.begin(), g->kept.end(), ptr);
-    if (at == g->kept.end()) { (void)hipFree(ptr); return; }
-    g->kept.erase(at);
-    g->retired.push_back(ptr);
+    if (is_kept(g, ptr)) retire(g, ptr); else (void)hipFree(ptr);
+}
+// A larger block for an asynchronous call, which must not wait: at least twice the old one, so that what is
+// retired stays below what is used.
+bsse_status grow_async(bsse_game *g, void **ptr, size_t *cap, size_t bytes)
+{
+    if (bytes <= *cap) return BSSE_OK;
+    bytes = std::max(bytes, 2 * *cap);
+    void *p = nullptr;
+    HIP_TRY(hipMalloc(&p, bytes));
+    retire(g, *ptr);
+    *ptr = p; *cap = bytes;
+    return BSSE_OK;
 }
 // The same for a buffer of candidates that may lie in the handle's generated set.
 bsse_status keep_rows(bsse_game *g, const float *X)
@@ -317,14 +329,12 @@ bsse_status ensure_blocks(bsse_game *g, long long nblocks)
     if (recording(g))
         return fail(BSSE_ESTATE, "%lld workgroup records are needed and nothing can be allocated while the stream is captured: "
                     "sweep a chunk of this size before", nblocks);
-    // the stream may still be reading the old workspace
-    HIP_TRY(hipStreamSynchronize(g->stream));
-    drop(g, g->w.blk_v); drop(g, g->w.blk_i);
-    g->w.blk_v = nullptr; g->w.blk_i = nullptr; g->w.blk_cap = 0;
-    HIP_TRY(hipMalloc((void **)&g->w.blk_v, (size_t)nblocks * sizeof(float)));
-    HIP_TRY(hipMalloc((void **)&g->w.blk_i, (size_t)nblocks * sizeof(long long)));
-    g->w.blk_cap = nblocks;
-    return BSSE_OK;
+    size_t cap_v = (size_t)g->w.blk_cap * sizeof(float), cap_i = (size_t)g->w.blk_cap * sizeof(long long);
+    g->w.blk_cap = 0;
+    bsse_status st = grow_async(g, (void **)&g->w.blk_v, &cap_v, (size_t)nblocks * sizeof(float));
+    if (st == BSSE_OK) st = grow_async(g, (void **)&g->w.blk_i, &cap_i, (size_t)nblocks * sizeof(long long));
+    if (st == BSSE_OK) g->w.blk_cap = (long long)std::min(cap_v / sizeof(float), cap_i / sizeof(long long));
+    return st;
 }
 
 bsse_status ensure_gen(bsse_game *g, unsigned long long rows)
@@ -434,7 +444,7 @@ bsse_status launch_eval(bsse_game *g, SweepArgs a)
         HIP_TRY(launch_sweep(g, a, true));
         return BSSE_OK;
     }
-    if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float))) != BSSE_OK) return st;
+    if ((st = grow_async(g, (void **)&g->row_l, &g->cap_row_l, (size_t)a.count * g->K * sizeof(float))) != BSSE_OK) return st;
     FinishRowsArgs f{};
     f.l = g->row_l; f.prior = g->dprior; f.count = a.count; f.K = g->K; f.m = g->m; f.V_out = a.V_out;
     a.V_out = nullptr; a.l_out = g->row_l; a.l_sc = 1; a.l_st = a.count;
@@ -1121,7 +1131,7 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
         if (record && ((st = keep(g, g->w.blk_v)) != BSSE_OK || (st = keep(g, g->w.blk_i)) != BSSE_OK)) return st;
         a.tie_counter = g->w.tie_counter;
         if (rows) {
-            if ((st = grow_device(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * g->K * sizeof(float))) != BSSE_OK) return st;
+            if ((st = grow_async(g, (void **)&g->row_l, &g->cap_row_l, (size_t)count * g->K * sizeof(float))) != BSSE_OK) return st;
             a.l_out = g->row_l; a.l_sc = 1; a.l_st = count;
             f.l = g->row_l; f.prior = g->dprior; f.count = count; f.index_base = a.index_base; f.K = g->K; f.m = g->m;
             f.blk_v = g->w.blk_v; f.blk_i = g->w.blk_i;
