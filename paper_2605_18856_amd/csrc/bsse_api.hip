@@ -1623,8 +1623,10 @@ extern "C" bsse_status bsse_sweep_priors(bsse_game *g, const float *candidates_d
     const size_t in_words = ((size_t)K * ldp + 1) / 2 * 2, in_bytes = in_words * 4 + sizeof(unsigned long long);
     if ((st = grow_device(g, (void **)&w.L, &w.cap_L, (size_t)ld * K * sizeof(float))) != BSSE_OK) return st;
     if ((st = grow_device(g, (void **)&w.priors, &w.cap_priors, in_bytes)) != BSSE_OK) return st;
-    // (a last, shorter chunk is cut no finer than the others: one record per 1024 candidates at most)
-    if ((st = grow_device(g, (void **)&w.blk_v, &w.cap_blk_v, (size_t)1024 * P * sizeof(float))) != BSSE_OK) return st;
+    // (a last, shorter chunk is cut finer where it has few steps: whichever has more records)
+    const long long last = count - (count - 1) / chunk * chunk;
+    const size_t records = (size_t)std::max(prior_batch_blocks(chunk, P), prior_batch_blocks(last, P)) * P;
+    if ((st = grow_device(g, (void **)&w.blk_v, &w.cap_blk_v, records * sizeof(float))) != BSSE_OK) return st;
     if ((st = grow_device(g, (void **)&w.run, &w.cap_run, (size_t)P * sizeof(PriorBest))) != BSSE_OK) return st;
     if ((st = grow_device(g, (void **)&w.rows, &w.cap_rows, (size_t)P * m * sizeof(float))) != BSSE_OK) return st;
     const size_t off_run = (in_bytes + 15) / 16 * 16, off_ties = off_run + (size_t)P * sizeof(PriorBest), off_br = off_ties + 16;
