@@ -2070,9 +2070,16 @@ extern "C" bsse_status bsse_solve_realised(bsse_game *g, const float *candidates
     if (on_device) {
         const size_t elems = (size_t)K * m * n * sizeof(float);
         if (!w.payoffs) {                // as given to create, once per game
-            HIP_TRY(hipMalloc((void **)&w.payoffs, 2 * elems));
-            HIP_TRY(hipMemcpyAsync(w.payoffs, g->hA.data(), elems, hipMemcpyHostToDevice, g->stream));
-            HIP_TRY(hipMemcpyAsync(w.payoffs + elems / sizeof(float), g->hB.data(), elems, hipMemcpyHostToDevice, g->stream));
+            float *p = nullptr;
+            HIP_TRY(hipMalloc((void **)&p, 2 * elems));
+            hipError_t e = hipMemcpyAsync(p, g->hA.data(), elems, hipMemcpyHostToDevice, g->stream);
+            if (e == hipSuccess) e = hipMemcpyAsync(p + elems / sizeof(float), g->hB.data(), elems, hipMemcpyHostToDevice, g->stream);
+            if (e != hipSuccess) {
+                (void)hipStreamSynchronize(g->stream);
+                (void)hipFree(p);
+                return fail(BSSE_EDEVICE, "payoffs: %s", hipGetErrorString(e));
+            }
+            w.payoffs = p;               // (only once it is on its way)
         }
         if ((st = grow_device(g, (void **)&w.v, &w.cap_v, (size_t)most * sizeof(double))) != BSSE_OK) return st;
         if ((st = grow_device(g, (void **)&w.x, &w.cap_x, (size_t)most * m * sizeof(double))) != BSSE_OK) return st;
