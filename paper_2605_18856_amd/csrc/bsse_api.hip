@@ -768,7 +768,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
             if (st == BSSE_OK) st = up(&g->dATpack, pa, ab);
             free(pb); free(pa);
             if (st != BSSE_OK) break;
-            hipError_t pe = mfma_prepare(variant, K);
+            hipError_t pe = mfma_prepare(variant);
             if (pe != hipSuccess) { st = fail(BSSE_EDEVICE, "mfma_prepare: %s", hipGetErrorString(pe)); break; }
         }
         if ((st = zeroed((void **)&g->w.tie_counter, 8)) != BSSE_OK) break;

@@ -168,7 +168,7 @@ int mfma_select(int m, int n, int K, int mode, bool exact);
 const char *mfma_variant_name(int variant);
 long long mfma_num_blocks(int variant, long long count);
 hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t s);
-hipError_t mfma_prepare(int variant, int K);   // per game, on its device, before the first launch
+hipError_t mfma_prepare(int variant);   // per game, on its device, before the first launch
 // Type slices of a launch with l_out; whether `count` candidates are so few that a sweep or an
 // evaluation is a launch with l_out and then launch_finish_rows.
 int mfma_slices(const GameView &g, long long count);

@@ -565,7 +565,8 @@ static size_t lp_lds(int m, int n, int K)
 }
 
 // A tableau that LDS holds beside the kernel's own words.
-bool lp_on_device(int m, int n, int K) { return n > 1 && (double)m * (2.0 + (double)K * (n - 1) + m) < 20000.0 && lp_lds(m, n, K) <= 150 * 1024; }
+constexpr int LP_LDS_MOST = 150 * 1024;
+bool lp_on_device(int m, int n, int K) { return n > 1 && (double)m * (2.0 + (double)K * (n - 1) + m) < 20000.0 && lp_lds(m, n, K) <= LP_LDS_MOST; }
 
 hipError_t launch_profile_lps(const LpArgs &a, LpBest *out, double *x_host, int32_t *profile_host, const Done &done, hipStream_t s)
 {
@@ -582,7 +583,7 @@ hipError_t launch_profile_lps(const LpArgs &a, LpBest *out, double *x_host, int3
         hipLaunchKernelGGL(k, dim3(a.most), dim3(64), 0, s, a);
     } else {
         const void *k = one ? (const void *)profile_lp_kernel<64> : (const void *)profile_lp_kernel<256>;
-        if (lds > 48 * 1024 && (e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) != hipSuccess) return e;
+        if (lds > 48 * 1024 && (e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, LP_LDS_MOST)) != hipSuccess) return e;
         if (one) hipLaunchKernelGGL(profile_lp_kernel<64>, dim3(a.most), dim3(64), lds, s, a);
         else hipLaunchKernelGGL(profile_lp_kernel<256>, dim3(a.most), dim3(256), lds, s, a);
     }

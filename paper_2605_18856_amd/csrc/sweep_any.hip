@@ -237,9 +237,10 @@ hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, vo
 
 hipError_t any_prepare(const GameView &g)
 {
-    const int lds = 2 * g.any.buf_bytes;
-    if (lds <= 48 * 1024) return hipSuccess;
-    return hipFuncSetAttribute((const void *)kernel_for(g.any), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (2 * g.any.buf_bytes <= 48 * 1024) return hipSuccess;
+    // (the most that any game takes on this kernel: the limit is the kernel's, not the game's)
+    const int most = 2 * std::max(36 * 1024, 2 * g.any.tile_bytes);
+    return hipFuncSetAttribute((const void *)kernel_for(g.any), hipFuncAttributeMaxDynamicSharedMemorySize, most);
 }
 
 static long long rows_per_block(const AnyGeo &q) { return 32LL * any_impl::WAVES * any_impl::tiles_per_wave(q.terms, q.ks); }

@@ -1299,14 +1299,13 @@ bool mfma_few_rows(const GameView &g, long long count)
 
 // Once per game, on the game's device: kernels whose two stage buffers exceed the default 48 KiB of
 // dynamic LDS get their limit raised here, not at every launch.
-hipError_t mfma_prepare(int variant, int K)
+hipError_t mfma_prepare(int variant)
 {
     if (variant == kSmallVariant) return hipSuccess;
     if (variant < 0 || variant >= kNumVariants) return hipErrorNotSupported;
     const Variant *v = &kVariants[variant];
-    const int tiles = row_tiles_for(*v, K);
-    const int nstages = (tiles + v->stage_tiles - 1) / v->stage_tiles;
-    const size_t lds = (size_t)v->geo.rec_bytes * (nstages > 1 ? 2 : 1);
+    // (the most that any number of types takes on this kernel: the limit is the kernel's, not the game's)
+    const size_t lds = (size_t)v->geo.rec_bytes * 2;
     if (v->wide && v->wide_lds > 48 * 1024) {
         for (const void *k : { (const void *)v->wide, (const void *)v->wide_part })
             if (hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, v->wide_lds); e != hipSuccess) return e;
