@@ -34,7 +34,7 @@
  *     any row of an aligned buffer qualifies), borrowed for the duration of the call (until
  *     the stream has run the enqueued work, for the asynchronous calls).  Rows are NOT checked to lie on
  *     the simplex: the sweep is defined for any finite x.  Non-finite candidates give
- *     an unspecified result (never a fault).
+ *     an unspecified result (never a fault); a value that is not a number is reported as minus infinity.
  *   - Every function returns a bsse_status.  Arguments are validated before any HIP
  *     call, so argument errors are reported on a machine without a GPU.  On error no
  *     output argument is written.  bsse_last_error() gives a thread-local message.
@@ -78,7 +78,9 @@ typedef struct {
                     products hi*hi, hi*mid, mid*hi, hi*lo, mid*mid, lo*hi are accumulated in
                     fp32 (three products when every payoff is itself a bf16 number); the
                     omitted products are below 2^-24 of the terms, so the result is within
-                    fp32 rounding of the fp32 dot product.  AUTO picks, in this order, the
+                    fp32 rounding of the fp32 dot product.  (Components x with 2^-109 <= |x| <= 3.39e38
+                    are split exactly; on shapes without a kernel of their own, larger ones and rows that
+                    are smaller as a whole are too.)  AUTO picks, in this order, the
                     small-game kernel, MFMA_SPLIT, MFMA, VALU, by what the shape supports.
                     Games with m = n = 8 and K in {4, 8, 12, 16} (fp32 storage) run on the
                     small-game kernel under AUTO and MFMA alike: bf16 matrix cores on split

@@ -10,7 +10,7 @@
 // payoffs come in as one 16-byte load per type and lane, the priors through scalar loads, and a step of
 // t is 4 PB_G independent multiply-adds.  Nothing goes through LDS.  Only the greatest value is kept (two
 // three-operand maxima per four candidates); the fold finds the lowest workgroup that reached it and
-// looks its candidate up again, among the PB_SLICE that workgroup had.  Bound by the vector unit:
+// looks its candidate up again, among those that workgroup had.  Bound by the vector unit:
 // 2^20 candidates, K = 4, 101 priors: 22 us of the 12 that the multiply-adds alone take at one per lane
 // and four cycles; with priors on the lanes and rows broadcast from LDS it was 52.
 #include "bsse_internal.h"

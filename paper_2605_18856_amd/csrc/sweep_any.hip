@@ -269,9 +269,10 @@ int any_slices(const GameView &g, long long count)
     // units with two and the rest half idle.  In units of the time two workgroups together take for all
     // types, a launch takes what its fullest unit takes -- pairs, and 0.62 for a last one by itself --
     // and a cut one its outputs and repeated row loads on top, less in proportion the more a type has to
-    // do.  m = 50, n = 100, K = 24 bf16: 70001 rows (274 blocks) 100 us uncut, 85 in five slices; 85000
-    // rows 101 and 93 (three); 100003 rows 102 uncut, 110 in five.  m = 60, n = 100, K = 12: 66000 rows
-    // 132 and 107; m = 30, n = 50, K = 20: 66000 rows 74 and 67, 100003 rows 76 uncut, 87 in five.
+    // do.  m = 50, n = 100, K = 24 bf16: 70001 rows (274 blocks) 100 us uncut, 91 in the three slices
+    // taken (five, which score the same within 0.2 %, 84); 85000 rows 101 and 94 (three; five 100); 100003
+    // rows 104 uncut, 109 in five.  m = 60, n = 100, K = 12: 66000 rows 132 and 107 (six); m = 30, n = 50,
+    // K = 20: 66000 rows 74 and 67 (five), 100003 rows 75 uncut, 88 in five.
     const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg, extra = (double)blocks / 256 * std::min(1.0, 50.0 / work);
     auto cost = [&](int slices) {
         const int per = (q.units + slices - 1) / slices;

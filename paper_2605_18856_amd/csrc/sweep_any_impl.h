@@ -254,8 +254,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     // four-byte alignment only); where a piece would reach past its row it is read ending with the row
     // and shifted.  All of a wavefront's pieces are requested before the first is used.  (Component by
     // component, k-step after k-step, the rows of m = 50 cost 128 requests of 64 lines each and eight
-    // round trips per wavefront: 70001 rows, n = 100, K = 24 bf16: 105 -> 103 us, and 93 -> 85 in five
-    // slices, each of which reads the rows again.)
+    // round trips per wavefront: 70001 rows, n = 100, K = 24 bf16, uncut: 105 -> 103 us; cut in five, each
+    // slice reading the rows again: 93 -> 85.)
     // The parts of a component are exact from 2^-109 (they may be subnormal bf16 numbers) to the greatest
     // number (the first part does not round up to infinity).  A row whose greatest component is below
     // 2^-60 is split 2^64 times greater: its follower payoffs are compared with each other alone, and a
