@@ -1,7 +1,7 @@
 """Seeded synthetic games and candidate sets (numpy only).
 
 This module draws inputs; it holds none of the sweep's arithmetic and loads no
-native code.  Both the GPU library's callers and the CPU checker take their
+native code.  Both the GPU library's callers and the CPU oracle take their
 inputs from here so that they see the same bits.
 
 The five games follow the benchmark configurations this repository is measured
