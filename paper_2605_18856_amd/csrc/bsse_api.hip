@@ -693,6 +693,8 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     g->path = path;
     try {
         g->hA.assign(A, A + elems); g->hB.assign(B, B + elems); g->hprior.assign(prior, prior + K);
+        g->hprior.resize((size_t)2 * K, 0.0f);          // (the filter's margins behind it)
+        if (use_mfma) filter_margins(variant, m, n, K, B, g->hprior.data() + K);
         g->won_x.resize((size_t)m); g->won_br.resize((size_t)K);
     } catch (...) { delete g; return fail(BSSE_ENOMEM, "host allocation failed"); }
     g->view.variant = variant;
@@ -739,7 +741,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     do {
         if (!use_mfma && (st = up((void **)&g->dB, hB.data(), hB.size() * 4)) != BSSE_OK) break;
         if (!use_mfma && (st = up((void **)&g->dAT, hAT.data(), hAT.size() * 4)) != BSSE_OK) break;
-        if ((st = up((void **)&g->dprior, prior, (size_t)K * 4)) != BSSE_OK) break;
+        if ((st = up((void **)&g->dprior, g->hprior.data(), g->hprior.size() * 4)) != BSSE_OK) break;
         g->view.m = m; g->view.n = n; g->view.K = K;
         g->view.m_pad = tiny ? tiny : m; g->view.n_pad = n;
         if (use_mfma && variant == kAnyVariant) {

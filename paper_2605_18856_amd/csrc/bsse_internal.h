@@ -29,7 +29,7 @@ struct GameView {
     int x_bf16;           // 1: round each candidate component to bf16 before use
     const float *B;       // [K][m][n]  follower payoffs, row-major (VALU path)
     const float *AT;      // [K][n][m]  leader payoffs, one follower action's column contiguous
-    const float *prior;   // [K]
+    const float *prior;   // [K], then [K] margins of the split kernels' filter (see filter_margins)
     // MFMA paths (null when the shape has no MFMA packing)
     const void *Bpack;    // follower payoffs in MFMA A-operand fragment order
     const void *ATpack;   // leader payoffs [K][n][m_pad] in the contraction's k order
@@ -178,6 +178,9 @@ bool mfma_is_small(int variant);       // the small-game kernel: launch_finish_s
 // Host-side packing of payoffs for a variant; returns malloc'ed buffers (caller frees).
 void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B, void **Bpack,
                size_t *Bbytes, void **ATpack, size_t *ATbytes, int *m_pad, int *n_pad);
+
+// Margins [K] of the filter of variants with split operands; others leave `margin` as it is.
+void filter_margins(int variant, int m, int n, int K, const float *B, float *margin);
 
 // Small-game matrix-core kernel (n = 8, m = 8, K in {4, 8, 12, 16}, fp32); part of the MFMA path.
 bool small_supported(int m, int n, int K, int storage);

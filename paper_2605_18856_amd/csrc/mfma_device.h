@@ -31,6 +31,9 @@ __device__ __forceinline__ float vmax2(float a, float b)
     return d;
 }
 
+// Per-type numbers that every lane reads, through the scalar data cache.  (A plain load is a vector one
+// behind inline asm that clobbers memory, and waiting for it waits for the stage copies in flight.)
+typedef const float __attribute__((address_space(4))) *uniform_floats;
 typedef __attribute__((address_space(3))) float lds_float;
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
@@ -71,7 +74,8 @@ template <int I, int End, int Step, class F> __device__ __forceinline__ void sta
 }
 
 // Four steps of the "which register holds the maximum" pass:
-//     sum += sum_k (u_k == gmax ? c_k : 0),   k = 0..3
+//     sum += sum_k (u_k >= gmax ? c_k : 0),   k = 0..3
+// (gmax: the maximum, or the maximum less a margin)
 // where c_k = (action of register k) + 2^16, so that after all registers sum & 0xFFFF is the
 // maximising action and sum >> 16 the number of maximisers (the action is only meaningful
 // when that number is one; callers send every other case through an exact routine).
@@ -86,10 +90,10 @@ __device__ __forceinline__ void match4(float u0, float u1, float u2, float u3, f
 {
     unsigned t0, t1, t2, t3;
     unsigned long long m0, m1, m2;
-    asm("v_cmp_eq_f32 %[m0], %[u0], %[g]\n\t"
-        "v_cmp_eq_f32 %[m1], %[u1], %[g]\n\t"
-        "v_cmp_eq_f32 %[m2], %[u2], %[g]\n\t"
-        "v_cmp_eq_f32 vcc, %[u3], %[g]\n\t"
+    asm("v_cmp_ge_f32 %[m0], %[u0], %[g]\n\t"
+        "v_cmp_ge_f32 %[m1], %[u1], %[g]\n\t"
+        "v_cmp_ge_f32 %[m2], %[u2], %[g]\n\t"
+        "v_cmp_ge_f32 vcc, %[u3], %[g]\n\t"
         "v_cndmask_b32 %[t0], 0, %[c0], %[m0]\n\t"
         "v_cndmask_b32 %[t1], 0, %[c1], %[m1]\n\t"
         "v_cndmask_b32 %[t2], 0, %[c2], %[m2]\n\t"
@@ -278,19 +282,19 @@ __device__ __forceinline__ void match8(const float *u, float gmax, const unsigne
 {
     unsigned t0, t1, t2, t3;
     unsigned long long m0, m1, m2;
-    asm("v_cmp_eq_f32 %[m0], %[u0], %[g]\n\t"
-        "v_cmp_eq_f32 %[m1], %[u1], %[g]\n\t"
-        "v_cmp_eq_f32 %[m2], %[u2], %[g]\n\t"
-        "v_cmp_eq_f32 vcc, %[u3], %[g]\n\t"
+    asm("v_cmp_ge_f32 %[m0], %[u0], %[g]\n\t"
+        "v_cmp_ge_f32 %[m1], %[u1], %[g]\n\t"
+        "v_cmp_ge_f32 %[m2], %[u2], %[g]\n\t"
+        "v_cmp_ge_f32 vcc, %[u3], %[g]\n\t"
         "v_cndmask_b32 %[t0], 0, %[c0], %[m0]\n\t"
         "v_cndmask_b32 %[t1], 0, %[c1], %[m1]\n\t"
         "v_cndmask_b32 %[t2], 0, %[c2], %[m2]\n\t"
         "v_cndmask_b32 %[t3], 0, %[c3], vcc\n\t"
         "v_add3_u32 %[s], %[s], %[t0], %[t1]\n\t"
-        "v_cmp_eq_f32 %[m0], %[u4], %[g]\n\t"
-        "v_cmp_eq_f32 %[m1], %[u5], %[g]\n\t"
-        "v_cmp_eq_f32 %[m2], %[u6], %[g]\n\t"
-        "v_cmp_eq_f32 vcc, %[u7], %[g]\n\t"
+        "v_cmp_ge_f32 %[m0], %[u4], %[g]\n\t"
+        "v_cmp_ge_f32 %[m1], %[u5], %[g]\n\t"
+        "v_cmp_ge_f32 %[m2], %[u6], %[g]\n\t"
+        "v_cmp_ge_f32 vcc, %[u7], %[g]\n\t"
         "v_add3_u32 %[s], %[s], %[t2], %[t3]\n\t"
         "v_cndmask_b32 %[t0], 0, %[c4], %[m0]\n\t"
         "v_cndmask_b32 %[t1], 0, %[c5], %[m1]\n\t"
@@ -307,17 +311,17 @@ __device__ __forceinline__ void match8(const float *u, float gmax, const unsigne
         : "vcc");
 }
 // Compare pass as a bitmap: sixteen values against the maximum, bits = (bits << 16) | e with
-// bit 15 - r of e set iff u[r] == gmax.  One compare and one add-with-carry (bits + bits + carry)
+// bit 15 - r of e set iff u[r] >= gmax.  One compare and one add-with-carry (bits + bits + carry)
 // per value; the four compares of a group precede the four adds that read their masks, which
 // also keeps the two wait states a vector read of a vector-written scalar register needs.
 __device__ __forceinline__ void bitmap16(const float *u, float gmax, unsigned &bits)
 {
     unsigned long long m0, m1, m2;
 #define BSSE_BM4(a, b, c, d)                                                    \
-        "v_cmp_eq_f32 %[m0], %[u" #a "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m1], %[u" #b "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m2], %[u" #c "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 vcc, %[u" #d "], %[g]\n\t"                                \
+        "v_cmp_ge_f32 %[m0], %[u" #a "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m1], %[u" #b "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m2], %[u" #c "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 vcc, %[u" #d "], %[g]\n\t"                                \
         "v_addc_co_u32_e64 %[b], %[m0], %[b], %[b], %[m0]\n\t"                  \
         "v_addc_co_u32_e64 %[b], %[m1], %[b], %[b], %[m1]\n\t"                  \
         "v_addc_co_u32_e64 %[b], %[m2], %[b], %[b], %[m2]\n\t"                  \
@@ -339,14 +343,14 @@ __device__ __forceinline__ void bitmap16x2(const float *ua, float ga, unsigned &
 {
     unsigned long long m0, m1, m2, m3, m4, m5, m6;
 #define BSSE_BM4X2(a, b, c, d)                                                  \
-        "v_cmp_eq_f32 %[m0], %[ua" #a "], %[ga]\n\t"                            \
-        "v_cmp_eq_f32 %[m1], %[ub" #a "], %[gb]\n\t"                            \
-        "v_cmp_eq_f32 %[m2], %[ua" #b "], %[ga]\n\t"                            \
-        "v_cmp_eq_f32 %[m3], %[ub" #b "], %[gb]\n\t"                            \
-        "v_cmp_eq_f32 %[m4], %[ua" #c "], %[ga]\n\t"                            \
-        "v_cmp_eq_f32 %[m5], %[ub" #c "], %[gb]\n\t"                            \
-        "v_cmp_eq_f32 %[m6], %[ua" #d "], %[ga]\n\t"                            \
-        "v_cmp_eq_f32 vcc, %[ub" #d "], %[gb]\n\t"                              \
+        "v_cmp_ge_f32 %[m0], %[ua" #a "], %[ga]\n\t"                            \
+        "v_cmp_ge_f32 %[m1], %[ub" #a "], %[gb]\n\t"                            \
+        "v_cmp_ge_f32 %[m2], %[ua" #b "], %[ga]\n\t"                            \
+        "v_cmp_ge_f32 %[m3], %[ub" #b "], %[gb]\n\t"                            \
+        "v_cmp_ge_f32 %[m4], %[ua" #c "], %[ga]\n\t"                            \
+        "v_cmp_ge_f32 %[m5], %[ub" #c "], %[gb]\n\t"                            \
+        "v_cmp_ge_f32 %[m6], %[ua" #d "], %[ga]\n\t"                            \
+        "v_cmp_ge_f32 vcc, %[ub" #d "], %[gb]\n\t"                              \
         "v_addc_co_u32_e64 %[ba], %[m0], %[ba], %[ba], %[m0]\n\t"               \
         "v_addc_co_u32_e64 %[bb], %[m1], %[bb], %[bb], %[m1]\n\t"               \
         "v_addc_co_u32_e64 %[ba], %[m2], %[ba], %[ba], %[m2]\n\t"               \
@@ -455,7 +459,7 @@ __device__ __forceinline__ void vmax2x16(float *w, const float *a, const float *
 #undef BSSE_W4
 }
 // Sixteen values as two interleaved streams of eight (u[0..7] and u[8..15]) against one maximum:
-// returns the 16-bit map with bit 15 - r set iff u[r] == gmax.  Every compare mask in a scalar register
+// returns the 16-bit map with bit 15 - r set iff u[r] >= gmax.  Every compare mask in a scalar register
 // pair (a vector instruction that takes its mask or carry from vcc issues several times slower on this
 // part than one that takes it from a scalar pair).
 __device__ __forceinline__ unsigned bitmap16_pairs(const float *u, float gmax)
@@ -463,14 +467,14 @@ __device__ __forceinline__ unsigned bitmap16_pairs(const float *u, float gmax)
     unsigned ba = 0u, bb = 0u;
     unsigned long long m0, m1, m2, m3, m4, m5, m6, m7;
 #define BSSE_BM4S(a, b, c, d, e, f, g, h)                                       \
-        "v_cmp_eq_f32 %[m0], %[u" #a "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m1], %[u" #e "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m2], %[u" #b "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m3], %[u" #f "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m4], %[u" #c "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m5], %[u" #g "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m6], %[u" #d "], %[g]\n\t"                              \
-        "v_cmp_eq_f32 %[m7], %[u" #h "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m0], %[u" #a "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m1], %[u" #e "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m2], %[u" #b "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m3], %[u" #f "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m4], %[u" #c "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m5], %[u" #g "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m6], %[u" #d "], %[g]\n\t"                              \
+        "v_cmp_ge_f32 %[m7], %[u" #h "], %[g]\n\t"                              \
         "v_addc_co_u32_e64 %[ba], %[m0], %[ba], %[ba], %[m0]\n\t"               \
         "v_addc_co_u32_e64 %[bb], %[m1], %[bb], %[bb], %[m1]\n\t"               \
         "v_addc_co_u32_e64 %[ba], %[m2], %[ba], %[ba], %[m2]\n\t"               \

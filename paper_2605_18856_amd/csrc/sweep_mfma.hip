@@ -29,6 +29,7 @@
 #include <limits.h>
 #include <stdlib.h>
 #include <string.h>
+#include <math.h>
 
 namespace bsse {
 
@@ -266,6 +267,10 @@ __host__ __device__ constexpr int wide_lds_bytes(int esz, int mp, int n, int wav
 typedef const void __attribute__((address_space(1))) *global_ptr;
 typedef void __attribute__((address_space(3))) *lds_ptr;
 
+// What the filter of the split kernels scales a row's later parts by before it takes their norms, and the
+// least norm and margin it works with (see filter_margins).
+constexpr float kScale1 = 0x1p9f, kScale2 = 0x1p18f, kLeastNorm = 0x1p-30f, kLeastMargin = 0x1p-90f;
+
 // ------------------------------------------------------------------------------------------
 // T: float | __bf16.  MP: padded m.  N: follower actions (8, 16 or a multiple of 32).
 // NT: 32-candidate tiles per wavefront.  WAVES: wavefronts per workgroup.
@@ -291,7 +296,7 @@ typedef void __attribute__((address_space(3))) *lds_ptr;
 // sequence does not depend on NT, OCC or SLICED, so every instantiation of a packing gives the
 // same bits for the same row.
 template <typename T, int MP, int N, int NT, int WAVES, int STAGE_TILES, int OCC, bool AT_LDS, int TERMS,
-          bool SLICED, int PF>
+          bool SLICED, int PF, bool CUT>
 __global__ void __launch_bounds__(WAVES * 64, OCC)
 sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 {
@@ -308,9 +313,20 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     static_assert(N == 8 || N == 16 || N % 32 == 0, "unsupported action count");
     static_assert(STAGE_TILES % TPG == 0 || TPG % STAGE_TILES == 0, "stage/group mismatch");
     static_assert(!AT_LDS || STAGE_TILES >= TPG, "leader rows in LDS need whole types per stage");
-    constexpr int REP = TERMS == 3 ? 3 : 1;             // matrix instructions per fragment read
+    constexpr int REP = TERMS == 3 ? 3 : 1;             // part products per stored fragment
     constexpr int KF = KS / REP;                        // fragment k-steps per row tile
     constexpr int TILE_FRAGS = KF * 64;                 // fragments per row tile
+    // CUT (split operands): the products that decide nearly every arg-max are summed first, (p0,B0) (p0,B1)
+    // (p1,B0) of six and p0 and p1 of three; then the small others (of three in a sum of their own, which
+    // is added: the margin is a third).  FILTER: those are left out where the maximum stands clear of the
+    // next value by more than they can change (see filter_margins).  A few rows on six products wait for
+    // latencies, not for matrix instructions: nothing is left out there.  Matrix and vector time add up in
+    // these kernels, and the products were half of it: m = n = 32, K = 16, 2^20 rows 215 -> 171 us, n = 64
+    // 376 -> 284; m = 128, n = 256, K = 256, 131072 rows 4120 -> 3200, of which 1 % for the rows that are
+    // not clear (0.8 % of the tiles).
+    constexpr bool FILTER = CUT && !(SLICED && TERMS == 6);
+    constexpr int MAIN_KF = FILTER && TERMS == 6 ? KF / 2 : KF, MAIN_REP = FILTER && TERMS == 3 ? 2 : REP;
+    static_assert(!CUT || (TERMS > 1 && STAGE_TILES >= TPG && N >= 32), "split operands, whole types per stage");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ float red_v[WAVES];
@@ -368,6 +384,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     };
     xreg x[NT][XS];
     float xf[NT][LEAD_F32 ? HALF_BASE : 1];
+    float norm[FILTER ? NT : 1];              // of the row, and of what its later parts can weigh
     unsigned valid32[NT];                     // bit c set iff candidate c of the tile exists
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) {
@@ -415,6 +432,21 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 #pragma unroll
             for (int e = 0; e < 3 * HALF_BASE; e += 2)
                 x[ct][e / 2] = bf16_bits_rne(v[e]) | (bf16_bits_rne(v[e + 1]) << 16);
+            if constexpr (FILTER) {
+                float sq[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    sq[q] = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < XB; ++e) {
+                        const bf16x2 pv = __builtin_bit_cast(bf16x2, x[ct][q * XB + e]);
+                        sq[q] = __builtin_amdgcn_fdot2_f32_bf16(pv, pv, sq[q], false);
+                    }
+                }
+                const float first = TERMS == 6 ? pair_sum(sq[0]) : 0.25f * pair_sum(sq[0]);
+                const float second = TERMS == 6 ? kScale1 * kScale1 * pair_sum(sq[1]) : 0.0f;
+                norm[ct] = fmaxf(__builtin_amdgcn_sqrtf(fmaxf(first, fmaxf(second, kScale2 * kScale2 * pair_sum(sq[2])))), kLeastNorm);
+            }
             if constexpr (LEAD_F32) {
 #pragma unroll
                 for (int e = 0; e < HALF_BASE; ++e) xf[ct][e] = vb[e];
@@ -427,6 +459,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) V[ct] = 0.0f;
     unsigned tie_count = 0;                   // wave-uniform
+    const uniform_floats prior = (uniform_floats)g.prior;
     // per-register constants of the compare pass: the action a register stands for within its
     // row tile and type (lane half included) plus 2^16
     unsigned creg[16];
@@ -452,11 +485,31 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
         }
         return l0 + l1;
     };
+    // CUT: one row tile, whose fragments are at `tile`, against one candidate tile, small products and all.
+    auto rest_of = [&](const xreg *xc, const frag *tile, f32x16 r) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = TERMS == 6 ? KF / 2 : 0; s < KF; ++s) r = x_mfma(tile[s * 64 + lane], xc, TERMS == 3 ? 2 * KF + s : s, r);
+        return r;
+    };
+    auto whole_tile = [&](const xreg *xc, const frag *tile) __attribute__((always_inline)) {
+        f32x16 sum;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sum[e] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < MAIN_KF; ++s) {
+            const frag af = tile[s * 64 + lane];
+#pragma unroll
+            for (int q = 0; q < MAIN_REP; ++q) sum = x_mfma(af, xc, q * KF + s, sum);
+        }
+        if constexpr (FILTER && TERMS == 3) sum += rest_of(xc, tile, f32x16{});
+        else if constexpr (FILTER) sum = rest_of(xc, tile, sum);
+        return sum;
+    };
     // Exact routine for one (candidate tile, type): recomputes the type's tiles one at a time
     // from the packed records in global memory (same instruction sequence, hence the same
     // bits), visits the exact maximisers in ascending action order, lets the leader's payoff
-    // decide and then the lower action.
-    auto exact_type = [&](int ct, int group, int ti, int t, float gmax, float &l_out,
+    // decide and then the lower action, in the candidate columns of the mask `columns`.
+    auto exact_type = [&](int ct, unsigned columns, int group, int ti, int t, float gmax, float &l_out,
                           int &j_out) __attribute__((always_inline)) {
         float lbest = kNotANumber;               // (no maximiser: no sum is a number)
         int jbest = 0, nmatch = 0;
@@ -464,17 +517,8 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 #pragma unroll 1
         for (int tt = 0; tt < TPG; ++tt) {
             const int gt = group * TPG + tt;
-            const frag *afrags = reinterpret_cast<const frag *>(
-                records + (size_t)(gt / STAGE_TILES) * G.rec_bytes + (size_t)(gt % STAGE_TILES) * G.tile_bytes);
-            f32x16 acc1;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc1[r] = 0.0f;
-#pragma unroll
-            for (int s = 0; s < KF; ++s) {
-                const frag af = afrags[s * 64 + lane];
-#pragma unroll
-                for (int q = 0; q < REP; ++q) acc1 = x_mfma(af, x[ct], q * KF + s, acc1);
-            }
+            const f32x16 acc1 = whole_tile(x[ct], reinterpret_cast<const frag *>(
+                records + (size_t)(gt / STAGE_TILES) * G.rec_bytes + (size_t)(gt % STAGE_TILES) * G.tile_bytes));
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -486,7 +530,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                         if (N < 32 && rb / N != ti) continue;
                         const int j = (N >= 32 ? tt * 32 + rb : rb % N) + 4 * hh;
                         const unsigned long long meq = __builtin_amdgcn_ballot_w64(acc1[r] == gmax);
-                        const unsigned hit = (unsigned)(hh ? (meq >> 32) : meq) & valid32[ct];
+                        const unsigned hit = (unsigned)(hh ? (meq >> 32) : meq) & columns;
                         if (hit == 0u) continue;                       // wave-uniform
                         float lh;
                         if constexpr (LEAD_F32)
@@ -501,7 +545,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                         }
                     }
         }
-        l_out = lbest; j_out = jbest;
+        if (!FILTER || ((columns >> col) & 1u)) { l_out = lbest; j_out = jbest; }
         tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2));
     };
 
@@ -526,10 +570,10 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 #pragma unroll
             for (int tt = 0; tt < NTILES; ++tt)
 #pragma unroll
-                for (int ks = 0; ks < KF; ++ks) {
+                for (int ks = 0; ks < MAIN_KF; ++ks) {
                     const frag af = base[(size_t)tt * TILE_FRAGS + (size_t)ks * 64 + lane];
 #pragma unroll
-                    for (int q = 0; q < REP; ++q)
+                    for (int q = 0; q < MAIN_REP; ++q)
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct)
                             acc[ct][TT0 + tt] = x_mfma(af, x[ct], q * KF + ks, acc[ct][TT0 + tt]);
@@ -558,7 +602,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 constexpr int f = q * C + decltype(ec)::value;
                 constexpr int tt = TT0 + f / KF, ks = f % KF;
 #pragma unroll
-                for (int p = 0; p < REP; ++p)
+                for (int p = 0; p < MAIN_REP; ++p)
 #pragma unroll
                     for (int ct = 0; ct < NT; ++ct)
                         acc[ct][tt] = x_mfma(fb[q & 1][decltype(ec)::value], x[ct], p * KF + ks, acc[ct][tt]);
@@ -566,15 +610,55 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
             __builtin_amdgcn_sched_barrier(0);
         });
     };
+    // FILTER: the maximum of the whole sums for the candidate columns `multi` of a tile, where several values
+    // are within the margin of the greatest.  `need`: the row tiles that hold such a value in one of these
+    // columns (no other can hold their maximum).  Returns the columns where it is no unique one (ties).
+    auto settle = [&](int ct, unsigned multi, unsigned need, auto tiles_of_group, float &gmax, int &jstar) __attribute__((always_inline)) {
+        float best = -INFINITY, w[16];
+        unsigned btile = 0u;
+        unsigned long long dup = 0ull;
+        auto tile_sums = [&](int tt, float (&u)[16]) __attribute__((always_inline)) {
+            f32x16 sum = whole_tile(x[ct], tiles_of_group + (size_t)tt * TILE_FRAGS);
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 15" : "+v"(sum));
+#pragma unroll
+            for (int r = 0; r < 16; ++r) u[r] = sum[r];
+        };
+        if constexpr (TPG == 1) {
+            tile_sums(0, w);
+            best = vmax_chain16(best, w);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) w[r] = -INFINITY;
+#pragma unroll 1
+            for (int tt = 0; tt < TPG; ++tt) {
+                if (!(need >> tt & 1u)) continue;
+                float u[16];
+                tile_sums(tt, u);
+                const float pm = vmax_chain16(-INFINITY, u);
+                dup |= __builtin_amdgcn_ballot_w64(pm == best);
+                keep_greater2(pm, (unsigned)(32 * tt), best, btile);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) w[r] = vmax2(w[r], u[r]);
+            }
+        }
+        const float gm = pair_max(best);
+        const unsigned bm = bitmap16_pairs(w, gm), cnt = (unsigned)__builtin_popcount(bm), r = ffbh(bm) - 16u;
+        const unsigned total = cnt ? (cnt << 16) | btile | ((r & 0xCu) << 1) | (r & 3u) | (4u * h) : 0u;
+        const unsigned pair = pair_add_u32(total);
+        if ((multi >> col) & 1u) { gmax = gm; jstar = (int)(pair & 0xFFFFu) & (N - 1); }
+        return multi & ((unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | (unsigned)(dup | (dup >> 32)));
+    };
     // second half of a type's epilogue: leader payoff at the best response (fast path: one row
     // gather and a dot product; otherwise the exact routine), value accumulation, outputs
+    // (ties: the candidate columns without a unique maximiser, per tile)
     auto leader_part = [&](int group, int ti, int t, float pt, const lds_byte *at_lds, const float *gmax,
-                           const int *jstar, const bool *clean) __attribute__((always_inline)) {
+                           const int *jstar, const unsigned *ties) __attribute__((always_inline)) {
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
             float l;
             int js = jstar[ct];
-            if (clean[ct]) {
+            if (FILTER || ties[ct] == 0u) {
                 float part;
                 if constexpr (LEAD_F32)
                     part = leader_half_f32(xf[ct], (const __attribute__((address_space(3))) f32x4 *)(
@@ -584,9 +668,8 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 else
                     part = leader_half(x[ct], ATpack + (((size_t)t * N + js) * MP + h * HALF) * sizeof(T));
                 l = pair_sum(part);
-            } else {
-                exact_type(ct, group, ti, t, gmax[ct], l, js);
             }
+            if (ties[ct] != 0u) exact_type(ct, (FILTER ? ties[ct] : 0xFFFFFFFFu) & valid32[ct], group, ti, t, gmax[ct], l, js);
             V[ct] = fmaf(pt, l, V[ct]);
             if constexpr (SLICED) {
                 const long long c = wave_base + ct * 32 + col;
@@ -600,8 +683,9 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
             }
         }
     };
-    // per-type epilogue of a finished group; at_lds = LDS rows of the group's first type
-    auto epilogue = [&](int group, const lds_byte *at_lds) __attribute__((always_inline)) {
+    // per-type epilogue of a finished group; at_lds = LDS rows of the group's first type; rest = its row
+    // tiles, for products that were left out
+    auto epilogue = [&](int group, const lds_byte *at_lds, auto rest) __attribute__((always_inline)) {
         // The asm blocks below read the accumulators, and the compiler's hazard handling does not
         // look into inline asm: the wait states a vector read of a fresh MFMA result needs (passes
         // + 3: 11 for the 8-pass bf16 MFMA, 19 for the 16-pass fp32 one) are put here explicitly.
@@ -612,14 +696,18 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
             constexpr int ti = decltype(tic)::value;
             const int t = group * TYPES + ti;
             if (t >= K) return;                                         // padded type rows
-            const float pt = g.prior[t];
+            const float pt = prior[t], reach = FILTER ? prior[K + t] : 0.0f;
             float gmax[NT];
             int jstar[NT];
-            bool clean[NT];
+            unsigned ties[NT];
 #pragma unroll
             for (int ct = 0; ct < NT; ++ct) {
+                // Values from `floor` on count as maximisers.  While products are missing that is the maximum
+                // less what they can change: where one value stands alone it is the maximum of the whole
+                // sums too.
+                const float room = FILTER ? -norm[FILTER ? ct : 0] * reach : 0.0f;
                 // lane maximum over this type's registers
-                float pm = -INFINITY;
+                float pm = -INFINITY, pmt[TPG];
                 unsigned total = 0u, tile_tie = 0u;       // tile_tie: wave-uniform column mask
                 float gm;
                 if constexpr (N >= 32) {
@@ -633,13 +721,13 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                     if constexpr (TPG == 1) {
                         pm = vmax_chain16(pm, u[0]);
                         gm = pair_max(pm);
-                        match8(u[0], gm, creg, total);
-                        match8(u[0] + 8, gm, creg + 8, total);
+                        const float floor = FILTER ? gm + room : gm;
+                        match8(u[0], floor, creg, total);
+                        match8(u[0] + 8, floor, creg + 8, total);
                     } else {
                         // Lane maximum per row tile (tile tt goes with tile tt + TPG/2: two
                         // independent instruction streams), then over the tiles.
                         constexpr int HT = TPG / 2;
-                        float pmt[TPG];
 #pragma unroll
                         for (int k = 0; k < TPG; ++k) pmt[k] = -INFINITY;
                         static_for<0, HT, 1>([&](auto ttc) {
@@ -651,6 +739,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                         for (int k = 1; k + 1 < TPG; k += 2) pm = vmax3(pm, pmt[k], pmt[k + 1]);
                         pm = vmax2(pm, pmt[TPG - 1]);
                         gm = pair_max(pm);
+                        const float floor = FILTER ? gm + room : gm;
                         // The position from the element-wise maxima over the tiles (TPG / 2 three-operand
                         // maxima per position), the tile from the tiles' own maxima.  Two tiles of one
                         // lane with the pair's maximum are a tie (exact routine), as are two positions.
@@ -668,7 +757,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                         unsigned long long seen = 0ull, dup = 0ull;
 #pragma unroll
                         for (int k = 0; k < TPG; ++k) {
-                            const bool e = pmt[k] == gm;
+                            const bool e = pmt[k] >= floor;
                             const unsigned long long mk = __builtin_amdgcn_ballot_w64(e);
                             dup |= seen & mk;
                             seen |= mk;
@@ -676,7 +765,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                         }
                         tile_tie |= (unsigned)(dup | (dup >> 32));
                         // compare pass as a bitmap: bit 15 - r set iff position r holds the maximum
-                        const unsigned bm = bitmap16_pairs(w, gm);
+                        const unsigned bm = bitmap16_pairs(w, floor);
                         const unsigned cnt = (unsigned)__builtin_popcount(bm);
                         const unsigned r = ffbh(bm) - 16u;
                         // action = 32 * tile + row(register) + 4h
@@ -694,21 +783,38 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                     }
                     if (np == 1) pm = vmax2(pm, pend[0]);
                     gm = pair_max(pm);
+                    const float floor = FILTER ? gm + room : gm;
                     // compare pass over the type's registers of the tile
                     static_for<0, 4, 1>([&](auto qc) {
                         constexpr int r = 4 * decltype(qc)::value;
                         if constexpr (acc_row_base(r) / N == ti)
                             match4(acc[ct][0][r], acc[ct][0][r + 1], acc[ct][0][r + 2], acc[ct][0][r + 3],
-                                   gm, creg[r], creg[r + 1], creg[r + 2], creg[r + 3], total);
+                                   floor, creg[r], creg[r + 1], creg[r + 2], creg[r + 3], total);
                     });
                 }
                 const unsigned pair = pair_add_u32(total);
                 gmax[ct] = gm;
                 jstar[ct] = (int)(pair & 0xFFFFu);
-                const unsigned multi = (unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | tile_tie;
-                clean[ct] = multi == 0u;                                // wave-uniform
+                if constexpr (FILTER) jstar[ct] &= N - 1;       // (any sum where the wavefront's row is not settled)
+                const unsigned multi = (unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | tile_tie;      // columns
+                ties[ct] = multi;
+                if constexpr (FILTER)
+                    if (multi != 0u) {
+                        unsigned need = 1u;
+                        if constexpr (TPG > 1) {
+                            need = 0u;
+                            const float floor = gm + room;
+#pragma unroll
+                            for (int k = 0; k < TPG; ++k) {
+                                const unsigned long long mk = __builtin_amdgcn_ballot_w64(pmt[k] >= floor);
+                                if (((unsigned)(mk | (mk >> 32)) & multi) != 0u) need |= 1u << k;
+                            }
+                            if (need == 0u) need = (1u << TPG) - 1u;      // (sums that are infinite or no numbers)
+                        }
+                        ties[ct] = settle(ct, multi, need, rest, gmax[ct], jstar[ct]);
+                    }
             }
-            leader_part(group, ti, t, pt, at_lds, gmax, jstar, clean);
+            leader_part(group, ti, t, pt, at_lds, gmax, jstar, ties);
         });
     };
 
@@ -735,10 +841,12 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 #pragma unroll 1
             for (int gi = 0; gi < ng; ++gi) {
                 zero_acc();
-                mfma_run(tiles + (size_t)(gi * TPG) * TILE_FRAGS, std::integral_constant<int, TPG>{},
-                         std::integral_constant<int, 0>{});
+                const frag *gt = tiles + (size_t)(gi * TPG) * TILE_FRAGS;
+                mfma_run(gt, std::integral_constant<int, TPG>{}, std::integral_constant<int, 0>{});
                 if (ROLES && late && gi == ng - 1) stage_sync();
-                epilogue(g0 + gi, (const lds_byte *)buf + (unsigned)(STAGE_TILES * G.tile_bytes + gi * TYPES * N * G.ats * sizeof(T)));
+                // (with two roles the stage's buffer may be overwritten by now)
+                const lds_byte *at = (const lds_byte *)buf + (unsigned)(STAGE_TILES * G.tile_bytes + gi * TYPES * N * G.ats * sizeof(T));
+                epilogue(g0 + gi, at, ROLES ? reinterpret_cast<const frag *>(records + (size_t)st * G.rec_bytes) + (size_t)(gi * TPG) * TILE_FRAGS : gt);
             }
             if (!(ROLES && late) || ng <= 0) stage_sync();      // (every wavefront: one barrier per stage)
         }
@@ -755,7 +863,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 const frag *tiles = reinterpret_cast<const frag *>(smem + (st & 1) * G.rec_bytes);
                 mfma_run(tiles, std::integral_constant<int, STAGE_TILES>{},
                          std::integral_constant<int, ss * STAGE_TILES>{});
-                if constexpr (ss == SPG - 1) epilogue(gr, nullptr);
+                if constexpr (ss == SPG - 1) epilogue(gr, nullptr, tiles);
                 stage_sync();
                 ++st;
             });
@@ -1157,6 +1265,7 @@ struct Variant {
     int terms;                   // 1, or the number of part products of the split (3 or 6)
     int mp_base, n, nt, waves, stage_tiles;
     bool at_lds;
+    bool cut;                    // part products are left out where they decide nothing
     void (*kernel)(GameView, SweepArgs, int);     // null when `wide` sweeps this packing
     void (*sliced)(GameView, SweepArgs, int);     // one candidate tile per wavefront, types sliced
     Geometry geo;
@@ -1166,39 +1275,41 @@ struct Variant {
     int wide_lds;                                 // its dynamic LDS bytes
 };
 
-#define BSSE_VARIANT(T, MODE, TERMSv, MPB, Nv, NTv, Wv, STv, OCCv, ATL, PFv, NAME)                   \
-    { MODE, TERMSv, MPB, Nv, NTv, Wv, STv, ATL,                                                      \
-      sweep_mfma_kernel<T, MPB * TERMSv, Nv, NTv, Wv, STv, OCCv, ATL, TERMSv, false, PFv>,           \
-      sweep_mfma_kernel<T, MPB * TERMSv, Nv, 1, Wv, STv, 1, ATL, TERMSv, true, PFv>,                 \
+#define BSSE_VARIANT(T, MODE, TERMSv, MPB, Nv, NTv, Wv, STv, OCCv, ATL, PFv, CUTv, NAME)             \
+    { MODE, TERMSv, MPB, Nv, NTv, Wv, STv, ATL, CUTv,                                                \
+      sweep_mfma_kernel<T, MPB * TERMSv, Nv, NTv, Wv, STv, OCCv, ATL, TERMSv, false, PFv, CUTv>,     \
+      sweep_mfma_kernel<T, MPB * TERMSv, Nv, 1, Wv, STv, 1, ATL, TERMSv, true, PFv, CUTv>,           \
       make_geometry((int)sizeof(T), MPB * TERMSv, Nv, STv, Wv, ATL, TERMSv), NAME, nullptr, nullptr, 0 }
 // A packing that sweep_wide_kernel also takes (one type per stage, leader rows in LDS, NT = 2)
 #define BSSE_VARIANT_WIDE(T, MODE, MPB, Nv, Wv, PFv, NAME)                                           \
-    { MODE, 1, MPB, Nv, 2, Wv, Nv / 32, true,                                                        \
+    { MODE, 1, MPB, Nv, 2, Wv, Nv / 32, true, false,                                                 \
       nullptr,                                                                                       \
-      sweep_mfma_kernel<T, MPB, Nv, 1, Wv, Nv / 32, 1, true, 1, true, PFv>,                          \
+      sweep_mfma_kernel<T, MPB, Nv, 1, Wv, Nv / 32, 1, true, 1, true, PFv, false>,                   \
       make_geometry((int)sizeof(T), MPB, Nv, Nv / 32, Wv, true), NAME,                               \
       sweep_wide_kernel<T, MPB, Nv, Wv, PFv, true>, sweep_wide_kernel<T, MPB, Nv, Wv, PFv, false>, wide_lds_bytes((int)sizeof(T), MPB, Nv, Wv) }
 
 const Variant kVariants[] = {
-    // fp32 MFMA (the last number before the name: k-steps per fragment read-ahead chunk, 0 = the
-    // fragment reads are left where they are used)
-    BSSE_VARIANT(float, 0, 1, 8, 8, 4, 4, 1, 2, true, 0, "mfma_f32"),
-    BSSE_VARIANT(float, 0, 1, 16, 16, 4, 4, 2, 2, true, 0, "mfma_f32"),
-    BSSE_VARIANT(float, 0, 1, 32, 32, 4, 4, 4, 2, true, 0, "mfma_f32"),
-    BSSE_VARIANT(float, 0, 1, 32, 64, 2, 4, 4, 2, true, 0, "mfma_f32"),
-    BSSE_VARIANT(float, 0, 1, 128, 256, 1, 4, 2, 2, false, 0, "mfma_f32"),
+    // fp32 MFMA (the last number: k-steps per fragment read-ahead chunk, 0 = the fragment reads are left
+    // where they are used; the last flag: small part products are left out where they decide nothing.  The
+    // other split shapes keep them: n = 16 has few to leave out (100 -> 106 us for 2^20 rows of m = 16,
+    // K = 16), and four candidate tiles a wavefront have no registers for it (n = 32, three products: 189
+    // -> 298 us))
+    BSSE_VARIANT(float, 0, 1, 8, 8, 4, 4, 1, 2, true, 0, false, "mfma_f32"),
+    BSSE_VARIANT(float, 0, 1, 16, 16, 4, 4, 2, 2, true, 0, false, "mfma_f32"),
+    BSSE_VARIANT(float, 0, 1, 32, 32, 4, 4, 4, 2, true, 0, false, "mfma_f32"),
+    BSSE_VARIANT(float, 0, 1, 32, 64, 2, 4, 4, 2, true, 0, false, "mfma_f32"),
+    BSSE_VARIANT(float, 0, 1, 128, 256, 1, 4, 2, 2, false, 0, false, "mfma_f32"),
     // bf16 MFMA, operands rounded to bf16
-    BSSE_VARIANT(__bf16, 1, 1, 16, 32, 4, 4, 2, 2, true, 0, "mfma_bf16"),
-    BSSE_VARIANT(__bf16, 1, 1, 32, 16, 4, 4, 2, 2, false, 0, "mfma_bf16"),
+    BSSE_VARIANT(__bf16, 1, 1, 16, 32, 4, 4, 2, 2, true, 0, false, "mfma_bf16"),
+    BSSE_VARIANT(__bf16, 1, 1, 32, 16, 4, 4, 2, 2, false, 0, false, "mfma_bf16"),
     BSSE_VARIANT_WIDE(__bf16, 1, 64, 128, 8, 4, "mfma_bf16"),
     // bf16 MFMA on fp32 operands split into bf16 parts
-    BSSE_VARIANT(__bf16, 2, 6, 16, 16, 2, 4, 2, 2, true, 0, "mfma_split6"),
-    BSSE_VARIANT(__bf16, 2, 6, 32, 32, 2, 4, 1, 3, true, 0, "mfma_split6"),
-    BSSE_VARIANT(__bf16, 2, 3, 32, 32, 4, 4, 4, 2, true, 0, "mfma_split3"),
-    BSSE_VARIANT(__bf16, 2, 6, 32, 64, 2, 4, 2, 2, true, 0, "mfma_split6"),
-    // (one fragment ahead: the next one's LDS read runs under three matrix instructions; 131072 rows of
-    // K = 256: 4290 -> 4190 us; two ahead spill)
-    BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 1, "mfma_split3"),
+    BSSE_VARIANT(__bf16, 2, 6, 16, 16, 2, 4, 2, 2, true, 0, false, "mfma_split6"),
+    BSSE_VARIANT(__bf16, 2, 6, 32, 32, 2, 4, 1, 3, true, 0, true, "mfma_split6"),
+    BSSE_VARIANT(__bf16, 2, 3, 32, 32, 4, 4, 4, 2, true, 0, false, "mfma_split3"),
+    BSSE_VARIANT(__bf16, 2, 6, 32, 64, 2, 4, 2, 2, true, 0, true, "mfma_split6"),
+    // (one fragment ahead: the next one's LDS read runs under two matrix instructions; two ahead spill)
+    BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 1, true, "mfma_split3"),
 };
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 constexpr int kSmallVariant = 1000;          // the small-game kernel (sweep_small.hip)
@@ -1345,6 +1456,58 @@ hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t 
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, (unsigned)slices), dim3(v->waves * 64), lds, s, g, b,
                        tiles);
     return hipGetLastError();
+}
+
+// The filter's margins: per type t a number a_t such that in a row of norm r (as the kernels compute it) the
+// products they leave out change no difference of two follower payoffs by r * a_t or more.
+//
+// Left out of six are (p0,B2) (p1,B1) (p2,B0) with p, B the parts of row and payoffs, of three p2 alone.
+// By Cauchy and Schwarz |sum_i p_i B_ij| <= |p|_2 |B_j|_2.  For six, r bounds |p0|_2,
+// 2^9 |p1|_2 and 2^18 |p2|_2, which are about equal for rows of ordinary numbers; for three, |p0|_2 / 2 and
+// 2^18 |p2|_2, and the payoffs count from the middle of their range over the actions, which no difference
+// notices.  A matrix instruction drops what is below 2^-26 of the greatest of its seventeen terms, once
+// each, and rounds once (measured with terms set for it), 2^-21.5 of its sum together: 2^-21 of
+// |x|_2 |B_j|_2 is taken for each that goes on with the sum of the others (six).  A sum of its own (three)
+// comes to 2^-16 of that, and its addition rounds to 2^-24: 2^-23 is taken.  Both payoffs of a difference
+// move: twice all that, and 2 % for the roundings of r, of a_t and of the threshold.  Rows and payoffs so
+// small that parts underflow meet the two least values.
+void filter_margins(int variant, int m, int n, int K, const float *B, float *margin)
+{
+    if (variant < 0 || variant >= kNumVariants || !kVariants[variant].cut) return;
+    const Variant &v = kVariants[variant];
+    const int parts = v.terms == 6 ? 3 : 1;
+    constexpr int MOST_N = 256;                              // of the variants
+    for (int t = 0; t < K; ++t) {
+        // squared norms of the actions' columns: parts 0, 1, 2, and centred
+        double sum[4][MOST_N] = {};
+        for (int i = 0; i < m; ++i) {
+            const float *row = B + ((size_t)t * m + i) * n;
+            if (parts == 1) {
+                float lo = row[0], hi = row[0];
+                for (int j = 1; j < n; ++j) { lo = row[j] < lo ? row[j] : lo; hi = row[j] > hi ? row[j] : hi; }
+                const double mid = 0.5 * ((double)lo + hi);
+                for (int j = 0; j < n; ++j) {
+                    const double b = row[j], c = b - mid;
+                    sum[0][j] += b * b; sum[3][j] += c * c;
+                }
+            } else {
+                for (int j = 0; j < n; ++j) {
+                    float part[3];
+                    bf16_parts(row[j], part);
+                    for (int q = 0; q < 3; ++q) sum[q][j] += (double)part[q] * part[q];
+                }
+            }
+        }
+        double norm[4] = { 0, 0, 0, 0 };
+        for (int q = 0; q < 4; ++q) {
+            for (int j = 0; j < n; ++j) norm[q] = norm[q] > sum[q][j] ? norm[q] : sum[q][j];
+            norm[q] = sqrt(norm[q]);
+        }
+        const double left_out = parts == 1 ? norm[3] / kScale2 : norm[2] + norm[1] / kScale1 + norm[0] / kScale2;
+                const double rounding = norm[0] * (parts == 1 ? 2 * 0x1p-23 : v.mp_base / 16 * 3 * 0x1p-21);
+        const double a = 2 * 1.02 * (left_out + 1.01 * rounding);       // (|x|_2 is within 2^-8 of |p0|_2)
+        margin[t] = (float)(a > kLeastMargin ? (a < 0x1p127 ? a : 0x1p127) : kLeastMargin);
+    }
 }
 
 // Host packing.
