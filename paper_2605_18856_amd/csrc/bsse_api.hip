@@ -414,14 +414,14 @@ bool cuts_types(const bsse_game *g)
 bool few_rows(const bsse_game *g, long long count)
 {
     if (!cuts_types(g) || count * g->K > ROW_SCRATCH_MAX) return false;
-    return on_any(g) ? any_slices(g->view, count) > 1
+    return on_any(g) ? any_shares(g->view, count) > 1
            : on_tiny(g) ? tiny_slices(g->view, count) > 1 : mfma_few_rows(g->view, count);
 }
 
 // A launch cut over the types where that pays: a.l_out (and a.br_out) only.
 hipError_t launch_rows(bsse_game *g, const SweepArgs &a, hipStream_t stream)
 {
-    if (on_any(g)) return launch_sweep_any(g->view, a, any_slices(g->view, a.count), stream);
+    if (on_any(g)) return launch_sweep_any(g->view, a, any_shares(g->view, a.count), stream);
     if (on_tiny(g)) return launch_sweep_tiny(g->view, a, true, tiny_slices(g->view, a.count), TinyRecs{}, stream);
     return launch_sweep_mfma(g->view, a, stream);
 }

@@ -106,7 +106,8 @@ struct SweepArgs {
     // would leave the chip idle); the value comes from launch_finish_rows or, for one row, from the
     // host, which sum l_out in type order (term by term the sum of the unsliced kernel).
     float *l_out;
-    int slice_stages;        // LDS stages (any-shape kernel: units) per slice (set by the launcher)
+    int slice_stages;        // LDS stages per slice; any-shape kernel: (block, unit) pairs per workgroup, rounded
+                             // down, 0 uncut (set by the launcher)
     // l_out / br_out element (c, t) sits at c * _sc + t * _st (unsliced general and wide kernel: br_out
     // at c * K + t).
     long long l_sc, l_st, br_sc, br_st;
@@ -201,11 +202,11 @@ hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, vo
 hipError_t any_prepare(const GameView &g);
 const char *any_name(const AnyGeo &q);
 long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an unsliced launch
-// Type slices that `count` candidates should be cut into (1: none).
-int any_slices(const GameView &g, long long count);
+// Workgroups that share a launch over `count` candidates cut over the types (1: it is not to be cut).
+int any_shares(const GameView &g, long long count);
 long long any_row_blocks(const GameView &g, long long count);       // workgroups of a launch cut like that
-// slices > 1: l_out (and br_out) only; the value comes from launch_finish_rows.
-hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int slices, hipStream_t s);
+// shares > 1: l_out (and br_out) only; the value comes from launch_finish_rows.
+hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int shares, hipStream_t s);
 
 // Values of rows whose per-type leader payoffs l (type-major, [K][count]) a sliced launch left
 // (here and below on the any-shape path and for the general matrix-core kernel alike):

@@ -243,6 +243,9 @@ hipError_t any_prepare(const GameView &g)
     return hipFuncSetAttribute((const void *)kernel_for(g.any), hipFuncAttributeMaxDynamicSharedMemorySize, most);
 }
 
+// Two workgroups on each compute unit.
+constexpr long long RESIDENT = 512;
+
 static long long rows_per_block(const AnyGeo &q) { return 32LL * any_impl::WAVES * any_impl::tiles_per_wave(q.terms, q.ks); }
 
 long long any_num_blocks(const GameView &g, long long count)
@@ -252,60 +255,54 @@ long long any_num_blocks(const GameView &g, long long count)
     // and the others two (m = 16, n = 40, K = 30 bf16: 140000 rows 106 -> 96 us, 270000 rows 151 -> 134;
     // m = 20, n = 12, K = 12: 400000 rows 78 -> 71).
     const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
-    return blocks < 1 ? 1 : blocks < 512 ? blocks : 512;
+    return blocks < 1 ? 1 : blocks < RESIDENT ? blocks : RESIDENT;
 }
 
-int any_slices(const GameView &g, long long count)
+// Workgroups of a launch cut over the types, 1 when it is not to be cut.
+int any_shares(const GameView &g, long long count)
 {
     const AnyGeo &q = g.any;
-    const long long blocks = (count + rows_per_block(q) - 1) / rows_per_block(q);
+    const long long blocks = (count + rows_per_block(q) - 1) / rows_per_block(q), pairs = blocks * q.units;
     if (q.units < 2) return 1;
-    auto cut = [&](long long want) { const long long per = (q.units + want - 1) / want; return (int)((q.units + per - 1) / per); };
+    const int shares = (int)std::min<long long>(pairs, RESIDENT);
     // Far fewer blocks of candidates than compute units, or packed types (the per-type outputs of a cut
-    // launch are most of their cost): cut until the grid is about twice the compute units.
-    if (blocks < 128 || (q.form >= 8 && blocks < 256)) return cut(std::min<long long>(512 / blocks, q.units));
+    // launch are most of their cost).
+    if (blocks < 128 || (q.form >= 8 && blocks < 256)) return shares;
     if (q.form >= 8 || (count + FINISH_ROWS - 1) / FINISH_ROWS * (g.m + g.K) > (1LL << 16)) return 1;
-    // Otherwise a compute unit holds two workgroups, and the slowest one decides: 274 blocks leave 18
-    // units with two and the rest half idle.  In units of the time two workgroups together take for all
-    // types, a launch takes what its fullest unit takes -- pairs, and 0.62 for a last one by itself --
-    // and a cut one its outputs and repeated row loads on top, less in proportion the more a type has to
-    // do.  m = 50, n = 100, K = 24 bf16: 70001 rows (274 blocks) 100 us uncut, 91 in the three slices
-    // taken (five, which score the same within 0.2 %, 84); 85000 rows 101 and 94 (three; five 100); 100003
-    // rows 104 uncut, 109 in five.  m = 60, n = 100, K = 12: 66000 rows 132 and 107 (six); m = 30, n = 50,
-    // K = 20: 66000 rows 74 and 67 (five), 100003 rows 75 uncut, 88 in five.
-    const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg, extra = (double)blocks / 256 * std::min(1.0, 50.0 / work);
-    auto cost = [&](int slices) {
-        const int per = (q.units + slices - 1) / slices;
-        const long long n = (blocks * slices + 255) / 256;
-        return (n / 2 + (n % 2 ? 0.62 : 0.0)) * per / q.units + (slices > 1 ? (0.15 + 0.02 * slices) * extra : 0.0);
-    };
-    int best = 1;
-    for (int want = 2; want <= 8 && want <= q.units; ++want)
-        if (const int slices = cut(want); cost(slices) < 0.97 * cost(best)) best = slices;
-    return best;
+    // Otherwise what decides is how full the compute units are.  In units of the time a compute unit takes for
+    // two blocks and all types side by side: uncut, the fullest one takes as many as it has blocks for, and
+    // 0.8 (0.6) for a first (a later) one by itself; cut, all take the same, a tenth more for the outputs,
+    // and 12 us for another launch that sums them (the unit is about 0.08 us per type and unit of `work`).
+    // Uncut and cut, us: m = 50, n = 100, K = 24 bf16, 50000 rows (196 blocks) 91 and 60, 70001 rows 100 and
+    // 75, 131072 rows 110 and 122, 160000 rows 176 and 147; m = 30, n = 50, K = 20, 60000 rows 69 and 53,
+    // 100003 rows 75 and 76; m = 16, n = 40, K = 30 bf16, 140000 rows 93 and 84, 270000 rows 130 and 143;
+    // m = 20, n = 20, K = 8, 100000 rows 32 and 36; m = 128, n = 255, K = 4, 30000 rows 88 and 64.
+    const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg;
+    const long long most = (blocks + 255) / 256;
+    const double uncut = most / 2 + (most % 2 ? (most == 1 ? 0.8 : 0.6) : 0.0);
+    const double cut = 12.0 / (0.08 * work * q.units) + 1.1 * blocks / RESIDENT;
+    return cut < 0.95 * uncut ? shares : 1;
 }
 
 long long any_row_blocks(const GameView &g, long long count)
 {
-    const int slices = any_slices(g, count);
-    return slices > 1 ? (count + rows_per_block(g.any) - 1) / rows_per_block(g.any) * slices : any_num_blocks(g, count);
+    const int shares = any_shares(g, count);
+    return shares > 1 ? shares : any_num_blocks(g, count);
 }
 
-hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int slices, hipStream_t s)
+hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int shares, hipStream_t s)
 {
     if (a.count <= 0) return hipSuccess;
     any_impl::any_kernel_t k = kernel_for(g.any);
     if (!k) return hipErrorNotSupported;
     any_impl::AnyArgs args{ g, a };
-    SweepArgs &b = args.a;
-    const int units = g.any.units;
-    b.slice_stages = (units + slices - 1) / slices;
-    const int ny = (units + b.slice_stages - 1) / b.slice_stages;
     const long long blocks = (a.count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
-    const long long nx = ny > 1 ? blocks : any_num_blocks(g, a.count);
-    if (ny > 1 && (a.V_out || a.blk_v)) return hipErrorInvalidValue;
-    if (ny > 65535 || nx > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3((unsigned)nx, (unsigned)ny), dim3(THREADS), (size_t)2 * g.any.buf_bytes, s, args);
+    const long long pairs = blocks * g.any.units;
+    if (shares > 1 && (a.V_out || a.blk_v || shares > pairs || pairs > 0x7FFFFFFFLL)) return hipErrorInvalidValue;
+    args.a.slice_stages = shares > 1 ? (int)(pairs / shares) : 0;
+    const long long nx = shares > 1 ? shares : any_num_blocks(g, a.count);
+    if (nx > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3((unsigned)nx), dim3(THREADS), (size_t)2 * g.any.buf_bytes, s, args);
     return hipGetLastError();
 }
 

@@ -21,9 +21,10 @@
 // Rows past the end of the candidates repeat the last one: they behave like any other row (no
 // special case, no detour through the exact routine) and are left out of every output.
 //
-// Types can be sliced over blockIdx.y (few candidates: one workgroup walking all types would leave
-// the chip idle); a slice writes per-type leader payoffs and finish_rows_kernel sums them in type
-// order, so a row's value has the same bits however the launch was cut.
+// A launch can be cut over the types (few candidates: workgroups walking all types would leave the chip
+// idle): every workgroup then takes an equal share of the (block of candidates, unit) pairs, in order, and
+// writes per-type leader payoffs; finish_rows_kernel sums them in type order, so a row's value has the
+// same bits however the launch was cut.
 #pragma once
 #include "bsse_internal.h"
 #include "mfma_device.h"
@@ -151,6 +152,7 @@ struct AnyArgs {
     SweepArgs a;
 };
 typedef const AnyArgs __attribute__((address_space(4))) *late_args;
+struct TypeOutput { unsigned c; int t; bool live; int32_t br; float l; };
 __device__ __forceinline__ late_args late()
 {
     auto p = __builtin_amdgcn_kernarg_segment_ptr();
@@ -189,21 +191,33 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     const unsigned count = (unsigned)args.a.count;       // <= 2^31 per launch
     const unsigned char *records = reinterpret_cast<const unsigned char *>(args.g.Bpack);
     const unsigned char *ATpack = reinterpret_cast<const unsigned char *>(args.g.ATpack);
-    const float *prior = args.g.prior;
-    const int u0 = (int)blockIdx.y * args.a.slice_stages;     // units of this slice
-    const int u1 = u0 + args.a.slice_stages < q.units ? u0 + args.a.slice_stages : q.units;
+    const uniform_floats prior = (uniform_floats)args.g.prior;
     const bool per_type = args.a.br_out || args.a.l_out; // per-type outputs are wanted
-    if (u0 >= u1) return;                                // whole workgroup
-    const int nsu = (u1 - u0 + q.ups - 1) / q.ups;       // groups of units, nq stages each
     constexpr unsigned PER_WG = WAVES * NT * 32;
     const unsigned nblk = (count + PER_WG - 1) / PER_WG;
+    // Units [u0, u1) of block blk are worked on, `left` of them in all from there on.  Uncut: all units of
+    // every gridDim.x-th block.  Cut: the workgroup's share of the pairs (block, unit); the first ones take
+    // one more where the shares are not whole.  (There are at least as many pairs as workgroups.)
+    unsigned blk = blockIdx.x, step = gridDim.x;
+    int u0 = 0, left;
+    if (const int share = args.a.slice_stages) {
+        const int more = (int)nblk * q.units - share * (int)gridDim.x, w = (int)blockIdx.x;
+        const int from = w * share + (w < more ? w : more);
+        left = share + (w < more ? 1 : 0);
+        blk = (unsigned)(from / q.units);
+        u0 = from - (int)blk * q.units;
+        step = 1u;
+    } else {
+        left = (int)((nblk - 1u - blk) / step + 1u) * q.units;
+    }
+    int u1 = u0 + left < q.units ? u0 + left : q.units;
 
-    // a stage: `ups` whole units, or (nq > 1) `stt` row tiles of one unit
-    auto copy_stage = [&](int su, int qq, int buf) __attribute__((always_inline)) {
-        const unsigned char *src = records + (size_t)(u0 + su * q.ups) * q.rec_bytes;
+    // a stage: `ups` whole units from `first` on (short of `end`), or (nq > 1) `stt` row tiles of one unit
+    auto copy_stage = [&](int first, int end, int qq, int buf) __attribute__((always_inline)) {
+        const unsigned char *src = records + (size_t)first * q.rec_bytes;
         int bytes;
         if (q.nq == 1) {
-            const int nu = u1 - (u0 + su * q.ups) < q.ups ? u1 - (u0 + su * q.ups) : q.ups;
+            const int nu = end - first < q.ups ? end - first : q.ups;
             bytes = nu * q.rec_bytes;
         } else {
             src += (size_t)qq * q.stt * q.tile_bytes;
@@ -214,7 +228,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
             __builtin_amdgcn_global_load_lds((global_ptr)(src + chunk * 1024 + lane * 16),
                                              (lds_ptr)(dst + chunk * 1024), 16, 0, 0);
     };
-    copy_stage(0, 0, 0);
+    copy_stage(u0, u1, 0, 0);
 
     // the one row of a fold launch: the winner among the records of an earlier launch
     const float *X = args.a.X;
@@ -226,14 +240,14 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
             fold_records(p->a.fold_v, p->a.fold_i, p->a.fold_n, bv, bi);
             const bool has = bi != LLONG_MAX;
             if (has) X += (bi - p->a.index_base) * m;
-            if (blockIdx.y == 0 && tid == 0) {
+            if (blockIdx.x == 0 && tid == 0) {
                 RunningBest r;
                 r.value = has ? bv : 0.0f; r.has = has ? 1 : 0; r.index = has ? bi : -1; r.ties = *p->a.fold_ties;
                 *p->a.fold_ties = 0ull;
                 *p->a.fold_run = r;
             }
         }
-        if (p->a.row_host && blockIdx.y == 0)
+        if (p->a.row_host && blockIdx.x == 0)
             for (int i = tid; i < m; i += THREADS) p->a.row_host[i] = X[i];
     }
 
@@ -446,6 +460,22 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
         return UNSCALE ? l * unscale[UNSCALE ? ct : 0] : l;
     };
 
+    // Per-type outputs of type t of candidate c.  Everything the stores need is read at once: pointers and
+    // strides one after another, each behind its own wait, held a wavefront up eight times a type (m = 50,
+    // n = 100, K = 24 bf16, 70001 rows: 77.3 -> 74.5 us).
+    auto put_type = [&](auto n_outputs, auto output) __attribute__((always_inline)) {
+        const late_args o = late();
+        int32_t *const br_out = o->a.br_out;
+        float *const l_out = o->a.l_out;
+        const long long l_sc = o->a.l_sc, l_st = o->a.l_st, br_sc = o->a.br_sc, br_st = o->a.br_st;
+#pragma unroll
+        for (int k = 0; k < decltype(n_outputs)::value; ++k) {
+            const TypeOutput v = output(k);
+            if (v.live && br_out) br_out[(size_t)v.c * br_sc + v.t * br_st] = v.br;
+            if (v.live && l_out) l_out[(size_t)v.c * l_sc + v.t * l_st] = v.l;
+        }
+    };
+
     // Exact routine for one (candidate tile, type) of FORM 0 / 1: the type's tiles once more from the
     // records in global memory (same instructions, same bits), the exact maximisers in ascending
     // action order; the leader's payoff decides and then the lower action.  Sums of minus infinity, and sums
@@ -484,7 +514,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     };
 
     int buf = 0;
-    for (unsigned blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+    for (;;) {
+        const int nsu = (u1 - u0 + q.ups - 1) / q.ups;   // groups of units, nq stages each
         const unsigned first = (blk * WAVES + wave) * (NT * 32);
         load_rows(first);
 #pragma unroll
@@ -505,9 +536,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                 {
                     int su2 = su, qq2 = qq + 1;
                     if (qq2 == q.nq) { qq2 = 0; ++su2; }
-                    bool more = su2 < nsu;
-                    if (!more && blk + gridDim.x < nblk) { su2 = 0; more = true; }
-                    if (more) copy_stage(su2, qq2, buf ^ 1);
+                    if (su2 < nsu) copy_stage(u0 + su2 * q.ups, u1, qq2, buf ^ 1);
+                    else if (const int rest = left - (u1 - u0)) copy_stage(0, rest < q.units ? rest : q.units, 0, buf ^ 1);
                 }
                 const unsigned char *sb = smem + buf * q.buf_bytes;
                 buf ^= 1;
@@ -584,19 +614,13 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                                 const float lk = (k / PT == h) ? l[ct][k % PT] : lo[k % PT];
                                 V[ct] = fmaf(prior[t], lk, V[ct]);
                             }
-                            if (per_type) {
-                                const late_args o = late();
-                                const size_t c = first + ct * 32 + col;
-#pragma unroll
-                                for (int p = 0; p < PT; ++p) {
-                                    const int t = TPT * u + PT * h + p;
-                                    if (c < count && t < K) {
-                                        if (o->a.br_out) o->a.br_out[c * o->a.br_sc + t * o->a.br_st] = (int32_t)js[ct][p];
-                                        if (o->a.l_out) o->a.l_out[c * o->a.l_sc + t * o->a.l_st] = l[ct][p];
-                                    }
-                                }
-                            }
                         }
+                        if (per_type)
+                            put_type(std::integral_constant<int, NT * PT>{}, [&](int k) __attribute__((always_inline)) {
+                                const int ct = k / PT, p = k % PT, t = TPT * u + PT * h + p;
+                                const unsigned c = first + ct * 32 + col;
+                                return TypeOutput{ c, t, c < count && t < K, (int32_t)js[ct][p], l[ct][p] };
+                            });
                     } else {
                         // ---- FORM 0 / 1: one type
                         if (qq == 0) {
@@ -712,15 +736,12 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                         for (int ct = 0; ct < NT; ++ct) {
                             if (!clean[ct]) exact_type(ct, t, gm[ct], l[ct], js[ct]);
                             V[ct] = fmaf(pt, l[ct], V[ct]);
-                            if (per_type) {
-                                const late_args o = late();
-                                const size_t c = first + ct * 32 + col;
-                                if (h == 0 && c < count) {
-                                    if (o->a.br_out) o->a.br_out[c * o->a.br_sc + t * o->a.br_st] = js[ct];
-                                    if (o->a.l_out) o->a.l_out[c * o->a.l_sc + t * o->a.l_st] = l[ct];
-                                }
-                            }
                         }
+                        if (per_type)
+                            put_type(std::integral_constant<int, NT>{}, [&](int ct) __attribute__((always_inline)) {
+                                const unsigned c = first + ct * 32 + col;
+                                return TypeOutput{ c, t, h == 0 && c < count, js[ct], l[ct] };
+                            });
                     }
                 }
             }
@@ -737,6 +758,9 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
             v = c < count ? v : -INFINITY;
             keep_greater2(v, c, best_v, best_c);
         }
+        left -= u1 - u0;
+        if (left == 0) break;
+        blk += step; u0 = 0; u1 = left < q.units ? left : q.units;
     }
 
     const late_args o = late();
@@ -763,7 +787,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     if (o->a.tie_counter && lane == 0 && tie_count) atomicAdd(o->a.tie_counter, (unsigned long long)tie_count);
     if (o->a.done.flag) {
         const Done d = { o->a.done.flag, o->a.done.seq };
-        signal_done(d, blockIdx.y * gridDim.x + blockIdx.x);
+        signal_done(d, blockIdx.x);
     }
 }
 
