@@ -809,7 +809,12 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                                 const unsigned long long mk = __builtin_amdgcn_ballot_w64(pmt[k] >= floor);
                                 if (((unsigned)(mk | (mk >> 32)) & multi) != 0u) need |= 1u << k;
                             }
-                            if (need == 0u) need = (1u << TPG) - 1u;      // (sums that are infinite or no numbers)
+                            // (columns whose sums are infinite or no numbers have no such value: all the tiles)
+                            bool any = false;
+#pragma unroll
+                            for (int k = 0; k < TPG; ++k) any |= pmt[k] >= floor;
+                            const unsigned long long some = __builtin_amdgcn_ballot_w64(any);
+                            if ((multi & ~(unsigned)(some | (some >> 32))) != 0u) need = (1u << TPG) - 1u;
                         }
                         ties[ct] = settle(ct, multi, need, rest, gmax[ct], jstar[ct]);
                     }

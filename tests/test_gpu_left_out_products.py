@@ -86,3 +86,22 @@ def test_few_and_many_rows_agree(shape):
         for part in (slice(0, 33), slice(20000, 21000), slice(66000, 66001)):
             _, v, b = _run_eval(g, X[part])
             assert np.array_equal(v, V[part]) and np.array_equal(b, br[part])
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=IDS)
+def test_infinite_sums_beside_near_ties(shape):
+    """Rows whose sums are infinite have the same best responses among rows that are near a tie as by
+    themselves (2^127 in one component: infinite where a payoff is 2 or more)."""
+    m, n, K, kind = shape
+    game = _paired_columns(workloads.small_game(m, n, K, 90 + m + n, kind))
+    if kind == "uniform":
+        game.B = (2.5 * game.B).astype(np.float32)
+    X = _near_equal_rows(m, 66001, 91)
+    big = np.zeros((66001, m), np.float32)
+    big[np.arange(66001), 4 + np.arange(66001) % (m - 4)] = 2.0 ** 127
+    among = np.arange(66001) % 7 == 3
+    X[among] = big[among]
+    with _make(game) as g:
+        _, _, alone = _run_eval(g, big)
+        _, _, br = _run_eval(g, X)
+    assert np.array_equal(br[among], alone[among])
