@@ -275,114 +275,6 @@ __device__ __forceinline__ void keep_greater(float v, unsigned c, unsigned p, fl
         : [v] "v"(v), [c] "v"(c), [p] "v"(p));
 }
 
-// The same for eight values in one asm block, and the running maximum over sixteen values in
-// one block: the compiler pads every boundary between two asm statements with a no-op, so
-// fewer, larger blocks save issue slots in the epilogue.
-__device__ __forceinline__ void match8(const float *u, float gmax, const unsigned *c, unsigned &sum)
-{
-    unsigned t0, t1, t2, t3;
-    unsigned long long m0, m1, m2;
-    asm("v_cmp_ge_f32 %[m0], %[u0], %[g]\n\t"
-        "v_cmp_ge_f32 %[m1], %[u1], %[g]\n\t"
-        "v_cmp_ge_f32 %[m2], %[u2], %[g]\n\t"
-        "v_cmp_ge_f32 vcc, %[u3], %[g]\n\t"
-        "v_cndmask_b32 %[t0], 0, %[c0], %[m0]\n\t"
-        "v_cndmask_b32 %[t1], 0, %[c1], %[m1]\n\t"
-        "v_cndmask_b32 %[t2], 0, %[c2], %[m2]\n\t"
-        "v_cndmask_b32 %[t3], 0, %[c3], vcc\n\t"
-        "v_add3_u32 %[s], %[s], %[t0], %[t1]\n\t"
-        "v_cmp_ge_f32 %[m0], %[u4], %[g]\n\t"
-        "v_cmp_ge_f32 %[m1], %[u5], %[g]\n\t"
-        "v_cmp_ge_f32 %[m2], %[u6], %[g]\n\t"
-        "v_cmp_ge_f32 vcc, %[u7], %[g]\n\t"
-        "v_add3_u32 %[s], %[s], %[t2], %[t3]\n\t"
-        "v_cndmask_b32 %[t0], 0, %[c4], %[m0]\n\t"
-        "v_cndmask_b32 %[t1], 0, %[c5], %[m1]\n\t"
-        "v_cndmask_b32 %[t2], 0, %[c6], %[m2]\n\t"
-        "v_cndmask_b32 %[t3], 0, %[c7], vcc\n\t"
-        "v_add3_u32 %[s], %[s], %[t0], %[t1]\n\t"
-        "v_add3_u32 %[s], %[s], %[t2], %[t3]"
-        : [s] "+v"(sum), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3),
-          [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2)
-        : [u0] "v"(u[0]), [u1] "v"(u[1]), [u2] "v"(u[2]), [u3] "v"(u[3]), [u4] "v"(u[4]),
-          [u5] "v"(u[5]), [u6] "v"(u[6]), [u7] "v"(u[7]), [g] "v"(gmax), [c0] "v"(c[0]),
-          [c1] "v"(c[1]), [c2] "v"(c[2]), [c3] "v"(c[3]), [c4] "v"(c[4]), [c5] "v"(c[5]),
-          [c6] "v"(c[6]), [c7] "v"(c[7])
-        : "vcc");
-}
-// Compare pass as a bitmap: sixteen values against the maximum, bits = (bits << 16) | e with
-// bit 15 - r of e set iff u[r] >= gmax.  One compare and one add-with-carry (bits + bits + carry)
-// per value; the four compares of a group precede the four adds that read their masks, which
-// also keeps the two wait states a vector read of a vector-written scalar register needs.
-__device__ __forceinline__ void bitmap16(const float *u, float gmax, unsigned &bits)
-{
-    unsigned long long m0, m1, m2;
-#define BSSE_BM4(a, b, c, d)                                                    \
-        "v_cmp_ge_f32 %[m0], %[u" #a "], %[g]\n\t"                              \
-        "v_cmp_ge_f32 %[m1], %[u" #b "], %[g]\n\t"                              \
-        "v_cmp_ge_f32 %[m2], %[u" #c "], %[g]\n\t"                              \
-        "v_cmp_ge_f32 vcc, %[u" #d "], %[g]\n\t"                                \
-        "v_addc_co_u32_e64 %[b], %[m0], %[b], %[b], %[m0]\n\t"                  \
-        "v_addc_co_u32_e64 %[b], %[m1], %[b], %[b], %[m1]\n\t"                  \
-        "v_addc_co_u32_e64 %[b], %[m2], %[b], %[b], %[m2]\n\t"                  \
-        "v_addc_co_u32_e32 %[b], vcc, %[b], %[b], vcc\n\t"
-    asm(BSSE_BM4(0, 1, 2, 3) BSSE_BM4(4, 5, 6, 7) BSSE_BM4(8, 9, 10, 11) BSSE_BM4(12, 13, 14, 15)
-        : [b] "+v"(bits), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2)
-        : [u0] "v"(u[0]), [u1] "v"(u[1]), [u2] "v"(u[2]), [u3] "v"(u[3]), [u4] "v"(u[4]),
-          [u5] "v"(u[5]), [u6] "v"(u[6]), [u7] "v"(u[7]), [u8] "v"(u[8]), [u9] "v"(u[9]),
-          [u10] "v"(u[10]), [u11] "v"(u[11]), [u12] "v"(u[12]), [u13] "v"(u[13]), [u14] "v"(u[14]),
-          [u15] "v"(u[15]), [g] "v"(gmax)
-        : "vcc");
-#undef BSSE_BM4
-}
-// Two independent streams interleaved instruction by instruction: a wavefront that is alone in
-// its epilogue (its neighbour on the SIMD being busy with MFMAs) issues dependent vector
-// instructions at about half rate, independent ones at nearly full rate.
-__device__ __forceinline__ void bitmap16x2(const float *ua, float ga, unsigned &ba, const float *ub,
-                                           float gb, unsigned &bb)
-{
-    unsigned long long m0, m1, m2, m3, m4, m5, m6;
-#define BSSE_BM4X2(a, b, c, d)                                                  \
-        "v_cmp_ge_f32 %[m0], %[ua" #a "], %[ga]\n\t"                            \
-        "v_cmp_ge_f32 %[m1], %[ub" #a "], %[gb]\n\t"                            \
-        "v_cmp_ge_f32 %[m2], %[ua" #b "], %[ga]\n\t"                            \
-        "v_cmp_ge_f32 %[m3], %[ub" #b "], %[gb]\n\t"                            \
-        "v_cmp_ge_f32 %[m4], %[ua" #c "], %[ga]\n\t"                            \
-        "v_cmp_ge_f32 %[m5], %[ub" #c "], %[gb]\n\t"                            \
-        "v_cmp_ge_f32 %[m6], %[ua" #d "], %[ga]\n\t"                            \
-        "v_cmp_ge_f32 vcc, %[ub" #d "], %[gb]\n\t"                              \
-        "v_addc_co_u32_e64 %[ba], %[m0], %[ba], %[ba], %[m0]\n\t"               \
-        "v_addc_co_u32_e64 %[bb], %[m1], %[bb], %[bb], %[m1]\n\t"               \
-        "v_addc_co_u32_e64 %[ba], %[m2], %[ba], %[ba], %[m2]\n\t"               \
-        "v_addc_co_u32_e64 %[bb], %[m3], %[bb], %[bb], %[m3]\n\t"               \
-        "v_addc_co_u32_e64 %[ba], %[m4], %[ba], %[ba], %[m4]\n\t"               \
-        "v_addc_co_u32_e64 %[bb], %[m5], %[bb], %[bb], %[m5]\n\t"               \
-        "v_addc_co_u32_e64 %[ba], %[m6], %[ba], %[ba], %[m6]\n\t"               \
-        "v_addc_co_u32_e32 %[bb], vcc, %[bb], %[bb], vcc\n\t"
-#define BSSE_U4(x, a, b, c, d) [x##a] "v"(x[a]), [x##b] "v"(x[b]), [x##c] "v"(x[c]), [x##d] "v"(x[d])
-    asm(BSSE_BM4X2(0, 1, 2, 3) BSSE_BM4X2(4, 5, 6, 7) BSSE_BM4X2(8, 9, 10, 11) BSSE_BM4X2(12, 13, 14, 15)
-        : [ba] "+v"(ba), [bb] "+v"(bb), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3),
-          [m4] "=&s"(m4), [m5] "=&s"(m5), [m6] "=&s"(m6)
-        : BSSE_U4(ua, 0, 1, 2, 3), BSSE_U4(ua, 4, 5, 6, 7), BSSE_U4(ua, 8, 9, 10, 11),
-          BSSE_U4(ua, 12, 13, 14, 15), BSSE_U4(ub, 0, 1, 2, 3), BSSE_U4(ub, 4, 5, 6, 7),
-          BSSE_U4(ub, 8, 9, 10, 11), BSSE_U4(ub, 12, 13, 14, 15), [ga] "v"(ga), [gb] "v"(gb)
-        : "vcc");
-#undef BSSE_BM4X2
-}
-__device__ __forceinline__ void vmax_chain16x2(float &pa, const float *ua, float &pb, const float *ub)
-{
-#define BSSE_MX(a, b)                                                           \
-        "v_max3_f32 %[pa], %[pa], %[ua" #a "], %[ua" #b "]\n\t"                  \
-        "v_max3_f32 %[pb], %[pb], %[ub" #a "], %[ub" #b "]\n\t"
-    asm(BSSE_MX(0, 1) BSSE_MX(2, 3) BSSE_MX(4, 5) BSSE_MX(6, 7) BSSE_MX(8, 9) BSSE_MX(10, 11)
-        BSSE_MX(12, 13) BSSE_MX(14, 15)
-        : [pa] "+v"(pa), [pb] "+v"(pb)
-        : BSSE_U4(ua, 0, 1, 2, 3), BSSE_U4(ua, 4, 5, 6, 7), BSSE_U4(ua, 8, 9, 10, 11),
-          BSSE_U4(ua, 12, 13, 14, 15), BSSE_U4(ub, 0, 1, 2, 3), BSSE_U4(ub, 4, 5, 6, 7),
-          BSSE_U4(ub, 8, 9, 10, 11), BSSE_U4(ub, 12, 13, 14, 15));
-#undef BSSE_MX
-#undef BSSE_U4
-}
 // number of leading zero bits; 0xFFFFFFFF for zero
 __device__ __forceinline__ unsigned ffbh(unsigned x)
 {
@@ -390,6 +282,15 @@ __device__ __forceinline__ unsigned ffbh(unsigned x)
     asm("v_ffbh_u32 %0, %1" : "=v"(r) : "v"(x));
     return r;
 }
+// number of trailing zero bits; 0xFFFFFFFF for zero
+__device__ __forceinline__ unsigned ffbl(unsigned x)
+{
+    unsigned r;
+    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+// Maximum of sixteen on top of p, in one block: the compiler pads every boundary between two asm
+// statements with a no-op, so fewer, larger blocks save issue slots in the epilogue.
 __device__ __forceinline__ float vmax_chain16(float p, const float *u)
 {
     asm("v_max3_f32 %0, %0, %1, %2\n\t"
@@ -407,57 +308,204 @@ __device__ __forceinline__ float vmax_chain16(float p, const float *u)
 }
 
 
-// ---- helpers of the wide-game epilogue ---------------------------------------------------
-// Maximum of sixteen values, two independent streams interleaved (no initial value needed: the
-// first instruction of a stream takes three of its values).
-__device__ __forceinline__ void vmax16x2_first(float &pa, const float *ua, float &pb, const float *ub)
+// ---- the arg-max over whole row tiles ----------------------------------------------------
+// A lane's TPG * 16 sums of one type (value r of row tile tt: action 32 tt + 8 (r / 4) + 4 h + r % 4) are
+// taken as a grid of ROWS x COLS, action = 2 COLS * row + (position of the column): the maximum of every grid
+// row and of every column, then a map with one bit for each of them that reaches the threshold.  One value
+// alone there sets one row bit and one column bit; any second one, in the lane or in its partner (whose
+// column bits lie elsewhere), sets a third, so a candidate has its unique maximiser exactly when the map of
+// both lanes has two bits, and the places of its highest and lowest bit are the action.
+// Vector instructions are what bounds these epilogues (each costs about 4.9 cycles beside the matrix
+// instructions, whatever its kind): for four row tiles 64 + 4 for the maxima, 32 for sixteen values against
+// the threshold and 8 for the map's bits.  Maxima per tile (32) and per position over the tiles (32), with
+// four compares and selects for the tile, sixteen values against the threshold and a lane-wise count,
+// took 13 more: m = 64, n = 128, K = 64 bf16, 2^22 rows 4.90 -> 4.75 ms; m = 128, n = 256, K = 256, 131072
+// rows 3.29 -> 3.19 ms; one row tile (16 maxima and 8 compares in place of 8 and 16): m = 16, n = 32, K = 16
+// bf16, 2^20 rows 104 -> 92 us.
+template <int TPG> struct ArgGrid {
+    static constexpr int ROWS = TPG == 1 ? 4 : 2 * TPG, COLS = TPG == 1 ? 4 : 8;
+};
+// Maximum of sixteen values, two independent streams interleaved: a wavefront that is alone in its epilogue
+// (its neighbour on the SIMD being busy with matrix instructions) issues dependent vector instructions at
+// about half rate.
+__device__ __forceinline__ void vmax16x2(float &pa, const float *ua, float &pb, const float *ub)
 {
 #define BSSE_U4(x, a, b, c, d) [x##a] "v"(x[a]), [x##b] "v"(x[b]), [x##c] "v"(x[c]), [x##d] "v"(x[d])
 #define BSSE_MX(a, b)                                                           \
         "v_max3_f32 %[pa], %[pa], %[ua" #a "], %[ua" #b "]\n\t"                  \
         "v_max3_f32 %[pb], %[pb], %[ub" #a "], %[ub" #b "]\n\t"
-    asm("v_max3_f32 %[pa], %[ua0], %[ua1], %[ua2]\n\t"
+#define BSSE_MX_FIRST                                                           \
+        "v_max3_f32 %[pa], %[ua0], %[ua1], %[ua2]\n\t"                          \
         "v_max3_f32 %[pb], %[ub0], %[ub1], %[ub2]\n\t"
-        BSSE_MX(3, 4) BSSE_MX(5, 6) BSSE_MX(7, 8) BSSE_MX(9, 10) BSSE_MX(11, 12) BSSE_MX(13, 14)
+    asm(BSSE_MX_FIRST BSSE_MX(3, 4) BSSE_MX(5, 6) BSSE_MX(7, 8) BSSE_MX(9, 10) BSSE_MX(11, 12) BSSE_MX(13, 14)
         "v_max_f32 %[pa], %[pa], %[ua15]\n\t"
         "v_max_f32 %[pb], %[pb], %[ub15]"
         : [pa] "=&v"(pa), [pb] "=&v"(pb)
         : BSSE_U4(ua, 0, 1, 2, 3), BSSE_U4(ua, 4, 5, 6, 7), BSSE_U4(ua, 8, 9, 10, 11),
           BSSE_U4(ua, 12, 13, 14, 15), BSSE_U4(ub, 0, 1, 2, 3), BSSE_U4(ub, 4, 5, 6, 7),
           BSSE_U4(ub, 8, 9, 10, 11), BSSE_U4(ub, 12, 13, 14, 15));
+}
+// The same for eight values.
+__device__ __forceinline__ void vmax8x2(float &pa, const float *ua, float &pb, const float *ub)
+{
+    asm(BSSE_MX_FIRST BSSE_MX(3, 4) BSSE_MX(5, 6)
+        "v_max_f32 %[pa], %[pa], %[ua7]\n\t"
+        "v_max_f32 %[pb], %[pb], %[ub7]"
+        : [pa] "=&v"(pa), [pb] "=&v"(pb)
+        : BSSE_U4(ua, 0, 1, 2, 3), BSSE_U4(ua, 4, 5, 6, 7), BSSE_U4(ub, 0, 1, 2, 3), BSSE_U4(ub, 4, 5, 6, 7));
+#undef BSSE_MX_FIRST
 #undef BSSE_MX
+}
+// w[i] = max(a[i], b[i], c[i], d[i]), i = 0..3
+__device__ __forceinline__ void vmax4x4(float *w, const float *a, const float *b, const float *c, const float *d)
+{
+    asm("v_max3_f32 %[w0], %[a0], %[b0], %[c0]\n\t"
+        "v_max3_f32 %[w1], %[a1], %[b1], %[c1]\n\t"
+        "v_max3_f32 %[w2], %[a2], %[b2], %[c2]\n\t"
+        "v_max3_f32 %[w3], %[a3], %[b3], %[c3]\n\t"
+        "v_max_f32 %[w0], %[w0], %[d0]\n\t"
+        "v_max_f32 %[w1], %[w1], %[d1]\n\t"
+        "v_max_f32 %[w2], %[w2], %[d2]\n\t"
+        "v_max_f32 %[w3], %[w3], %[d3]"
+        : [w0] "=&v"(w[0]), [w1] "=&v"(w[1]), [w2] "=&v"(w[2]), [w3] "=&v"(w[3])
+        : BSSE_U4(a, 0, 1, 2, 3), BSSE_U4(b, 0, 1, 2, 3), BSSE_U4(c, 0, 1, 2, 3), BSSE_U4(d, 0, 1, 2, 3));
 #undef BSSE_U4
 }
-// Element-wise maximum over four vectors of sixteen: w[r] = max(a[r], b[r], c[r], d[r]).
-__device__ __forceinline__ void vmax4x16(float *w, const float *a, const float *b, const float *c, const float *d)
+// Maxima of the grid's rows, and of its columns.
+template <int TPG> __device__ __forceinline__ void grid_rows(const float (&u)[TPG][16], float *R)
 {
-#define BSSE_W4(x, i) [x##0] "v"(x[i]), [x##1] "v"(x[i + 1]), [x##2] "v"(x[i + 2]), [x##3] "v"(x[i + 3])
+    if constexpr (TPG == 1) {
+        float s[4][4];
 #pragma unroll
-    for (int i = 0; i < 16; i += 4)
-        asm("v_max3_f32 %[w0], %[a0], %[b0], %[c0]\n\t"
-            "v_max3_f32 %[w1], %[a1], %[b1], %[c1]\n\t"
-            "v_max3_f32 %[w2], %[a2], %[b2], %[c2]\n\t"
-            "v_max3_f32 %[w3], %[a3], %[b3], %[c3]\n\t"
-            "v_max_f32 %[w0], %[w0], %[d0]\n\t"
-            "v_max_f32 %[w1], %[w1], %[d1]\n\t"
-            "v_max_f32 %[w2], %[w2], %[d2]\n\t"
-            "v_max_f32 %[w3], %[w3], %[d3]"
-            : [w0] "=&v"(w[i]), [w1] "=&v"(w[i + 1]), [w2] "=&v"(w[i + 2]), [w3] "=&v"(w[i + 3])
-            : BSSE_W4(a, i), BSSE_W4(b, i), BSSE_W4(c, i), BSSE_W4(d, i));
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e][q] = u[0][4 * q + e];
+        vmax4x4(R, s[0], s[1], s[2], s[3]);
+    } else {
+#pragma unroll
+        for (int t = 0; t < TPG; ++t) vmax8x2(R[2 * t], u[t], R[2 * t + 1], u[t] + 8);
+    }
 }
-// w[r] = max(a[r], b[r])
-__device__ __forceinline__ void vmax2x16(float *w, const float *a, const float *b)
+template <int TPG> __device__ __forceinline__ void grid_columns(const float (&u)[TPG][16], float *C)
 {
+    if constexpr (TPG == 1) {
+        vmax4x4(C, u[0], u[0] + 4, u[0] + 8, u[0] + 12);
+    } else if constexpr (TPG == 2) {
+        vmax4x4(C, u[0], u[0] + 8, u[1], u[1] + 8);
+        vmax4x4(C + 4, u[0] + 4, u[0] + 12, u[1] + 4, u[1] + 12);
+    } else {
+        float s[8][2 * TPG];
 #pragma unroll
-    for (int i = 0; i < 16; i += 4)
-        asm("v_max_f32 %[w0], %[a0], %[b0]\n\t"
-            "v_max_f32 %[w1], %[a1], %[b1]\n\t"
-            "v_max_f32 %[w2], %[a2], %[b2]\n\t"
-            "v_max_f32 %[w3], %[a3], %[b3]"
-            : [w0] "=&v"(w[i]), [w1] "=&v"(w[i + 1]), [w2] "=&v"(w[i + 2]), [w3] "=&v"(w[i + 3])
-            : BSSE_W4(a, i), BSSE_W4(b, i));
-#undef BSSE_W4
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int k = 0; k < 2 * TPG; ++k) s[c][k] = u[k / 2][8 * (k % 2) + c];
+#pragma unroll
+        for (int c = 0; c < 8; c += 2) {
+            if constexpr (TPG == 4) vmax8x2(C[c], s[c], C[c + 1], s[c + 1]);
+            else vmax16x2(C[c], s[c], C[c + 1], s[c + 1]);
+        }
+    }
 }
+// Both sets; returns the lane's maximum (from the smaller set).  COLS_FIRST: the eight column maxima before
+// the rows', which for eight row tiles saves the registers that are spilled otherwise (m = 128, n = 256, 2000
+// rows cut over K = 100 types: 51.0 us, rows first 53.0) but is slower in long launches (65536 rows of m = 100:
+// 685 us, rows first 672).
+template <int TPG, bool COLS_FIRST = false>
+__device__ __forceinline__ float grid_maxima(const float (&u)[TPG][16], float *R, float *C)
+{
+    if constexpr (COLS_FIRST) grid_columns<TPG>(u, C);
+    grid_rows<TPG>(u, R);
+    if constexpr (!COLS_FIRST) grid_columns<TPG>(u, C);
+    if constexpr (TPG <= 2) return vmax2(vmax3(R[0], R[1], R[2]), R[3]);
+    float most;
+    asm("v_max3_f32 %0, %1, %2, %3\n\t"
+        "v_max3_f32 %0, %0, %4, %5\n\t"
+        "v_max3_f32 %0, %0, %6, %7\n\t"
+        "v_max_f32 %0, %0, %8"
+        : "=&v"(most)
+        : "v"(C[0]), "v"(C[1]), "v"(C[2]), "v"(C[3]), "v"(C[4]), "v"(C[5]), "v"(C[6]), "v"(C[7]));
+    return most;
+}
+// Two bit streams of four values each against a threshold, the first value in the highest bit; a stream
+// that goes on shifts what it has by four.  One compare and one add-with-carry (bits + bits + carry) a
+// value, a select for the first of a stream; the eight compares precede the eight that read their masks,
+// which also keeps the two wait states between a vector write of a scalar register and a vector read of it.
+// Every mask in a scalar register pair (a vector instruction that takes its mask or carry from vcc issues
+// several times slower on this part than one that takes it from a scalar pair).
+template <bool GO_ON_A, bool GO_ON_B>
+__device__ __forceinline__ void bits4x2(unsigned &a, float a0, float a1, float a2, float a3, unsigned &b, float b0,
+                                        float b1, float b2, float b3, float g)
+{
+    unsigned long long m0, m1, m2, m3, m4, m5, m6, m7;
+#define BSSE_ADDC(b, m) "v_addc_co_u32_e64 %[" #b "], %[" #m "], %[" #b "], %[" #b "], %[" #m "]\n\t"
+#define BSSE_FIRST(b, m) "v_cndmask_b32_e64 %[" #b "], 0, 1, %[" #m "]\n\t"
+#define BSSE_BITS(A, IN_A, B, IN_B)                                             \
+    asm("v_cmp_ge_f32 %[m0], %[a0], %[g]\n\t"                                   \
+        "v_cmp_ge_f32 %[m4], %[b0], %[g]\n\t"                                   \
+        "v_cmp_ge_f32 %[m1], %[a1], %[g]\n\t"                                   \
+        "v_cmp_ge_f32 %[m5], %[b1], %[g]\n\t"                                   \
+        "v_cmp_ge_f32 %[m2], %[a2], %[g]\n\t"                                   \
+        "v_cmp_ge_f32 %[m6], %[b2], %[g]\n\t"                                   \
+        "v_cmp_ge_f32 %[m3], %[a3], %[g]\n\t"                                   \
+        "v_cmp_ge_f32 %[m7], %[b3], %[g]\n\t"                                   \
+        A(a, m0) B(b, m4) BSSE_ADDC(a, m1) BSSE_ADDC(b, m5) BSSE_ADDC(a, m2) BSSE_ADDC(b, m6) BSSE_ADDC(a, m3)    \
+        BSSE_ADDC(b, m7)                                                        \
+        : [a] IN_A(a), [b] IN_B(b), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3),                \
+          [m4] "=&s"(m4), [m5] "=&s"(m5), [m6] "=&s"(m6), [m7] "=&s"(m7)        \
+        : [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3), [b0] "v"(b0), [b1] "v"(b1), [b2] "v"(b2),        \
+          [b3] "v"(b3), [g] "v"(g))
+    if constexpr (GO_ON_A && GO_ON_B) BSSE_BITS(BSSE_ADDC, "+v", BSSE_ADDC, "+v");
+    else if constexpr (GO_ON_A) BSSE_BITS(BSSE_ADDC, "+v", BSSE_FIRST, "=&v");
+    else BSSE_BITS(BSSE_FIRST, "=&v", BSSE_FIRST, "=&v");
+#undef BSSE_BITS
+}
+// One such stream.
+__device__ __forceinline__ unsigned bits4(float a0, float a1, float a2, float a3, float g)
+{
+    unsigned a;
+    unsigned long long m0, m1, m2, m3;
+    asm("v_cmp_ge_f32 %[m0], %[a0], %[g]\n\t"
+        "v_cmp_ge_f32 %[m1], %[a1], %[g]\n\t"
+        "v_cmp_ge_f32 %[m2], %[a2], %[g]\n\t"
+        "v_cmp_ge_f32 %[m3], %[a3], %[g]\n\t"
+        BSSE_FIRST(a, m0) BSSE_ADDC(a, m1) BSSE_ADDC(a, m2) BSSE_ADDC(a, m3)
+        : [a] "=&v"(a), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2), [m3] "=&s"(m3)
+        : [a0] "v"(a0), [a1] "v"(a1), [a2] "v"(a2), [a3] "v"(a3), [g] "v"(g));
+    return a;
+#undef BSSE_FIRST
+#undef BSSE_ADDC
+}
+// The lane's map: grid row k at bit 31 - k, column 4 i + e at bit 8 i + e + 4 h (h4 = 4 h: the lane's half).
+template <int TPG>
+__device__ __forceinline__ unsigned grid_map(const float *R, const float *C, float floor, unsigned h4)
+{
+    unsigned r, c;
+    if constexpr (TPG == 1) {
+        bits4x2<false, false>(r, R[0], R[1], R[2], R[3], c, C[3], C[2], C[1], C[0], floor);
+    } else {
+        unsigned c1, c0;
+        if constexpr (TPG == 2) {
+            bits4x2<false, false>(r, R[0], R[1], R[2], R[3], c1, C[7], C[6], C[5], C[4], floor);
+            c0 = bits4(C[3], C[2], C[1], C[0], floor);
+        } else {
+            bits4x2<false, false>(r, R[0], R[1], R[2], R[3], c1, C[7], C[6], C[5], C[4], floor);
+            bits4x2<true, false>(r, R[4], R[5], R[6], R[7], c0, C[3], C[2], C[1], C[0], floor);
+            if constexpr (TPG == 8) {
+                unsigned r0 = r, r1;
+                bits4x2<true, false>(r0, R[8], R[9], R[10], R[11], r1, R[12], R[13], R[14], R[15], floor);
+                r = (r0 << 4) | r1;
+            }
+        }
+        c = (c1 << 8) | c0;
+    }
+    return (r << (32 - ArgGrid<TPG>::ROWS)) | (c << h4);
+}
+// The action of a map of both lanes with two bits (the callers mask it where it may have others).
+template <int TPG> __device__ __forceinline__ unsigned grid_action(unsigned map)
+{
+    return (ffbh(map) << (TPG == 1 ? 3 : 4)) | ffbl(map);
+}
+
 // Sixteen values as two interleaved streams of eight (u[0..7] and u[8..15]) against one maximum:
 // returns the 16-bit map with bit 15 - r set iff u[r] >= gmax.  Every compare mask in a scalar register
 // pair (a vector instruction that takes its mask or carry from vcc issues several times slower on this
@@ -494,6 +542,12 @@ __device__ __forceinline__ unsigned bitmap16_pairs(const float *u, float gmax)
     return (ba << 8) | bb;
 }
 
+// (a | b) over the two lanes of a candidate
+__device__ __forceinline__ unsigned pair_or(unsigned v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return r[0] | r[1];
+}
 // (a + b) over the two lanes of a candidate, same value in both (integers)
 __device__ __forceinline__ unsigned pair_add_u32(unsigned v)
 {

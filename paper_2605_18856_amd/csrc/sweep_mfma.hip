@@ -462,7 +462,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     const uniform_floats prior = (uniform_floats)g.prior;
     // per-register constants of the compare pass: the action a register stands for within its
     // row tile and type (lane half included) plus 2^16
-    unsigned creg[16];
+    [[maybe_unused]] unsigned creg[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r)
         creg[r] = (unsigned)((N >= 32 ? acc_row_base(r) : acc_row_base(r) % N) + 4 * h) + 65536u;
@@ -706,74 +706,25 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 // less what they can change: where one value stands alone it is the maximum of the whole
                 // sums too.
                 const float room = FILTER ? -norm[FILTER ? ct : 0] * reach : 0.0f;
-                // lane maximum over this type's registers
-                float pm = -INFINITY, pmt[TPG];
-                unsigned total = 0u, tile_tie = 0u;       // tile_tie: wave-uniform column mask
+                typedef ArgGrid<TPG> Grid;
                 float gm;
+                unsigned map = 0u, multi;                 // multi: columns where no value stands alone
                 if constexpr (N >= 32) {
-                    // whole row tiles belong to the type: one asm block per 16 registers for the
-                    // maximum and one for the compare pass
+                    // whole row tiles belong to the type
                     float u[TPG][16];
 #pragma unroll
                     for (int tt = 0; tt < TPG; ++tt)
 #pragma unroll
                         for (int r = 0; r < 16; ++r) u[tt][r] = acc[ct][tt][r];
-                    if constexpr (TPG == 1) {
-                        pm = vmax_chain16(pm, u[0]);
-                        gm = pair_max(pm);
-                        const float floor = FILTER ? gm + room : gm;
-                        match8(u[0], floor, creg, total);
-                        match8(u[0] + 8, floor, creg + 8, total);
-                    } else {
-                        // Lane maximum per row tile (tile tt goes with tile tt + TPG/2: two
-                        // independent instruction streams), then over the tiles.
-                        constexpr int HT = TPG / 2;
-#pragma unroll
-                        for (int k = 0; k < TPG; ++k) pmt[k] = -INFINITY;
-                        static_for<0, HT, 1>([&](auto ttc) {
-                            constexpr int tt = decltype(ttc)::value;
-                            vmax_chain16x2(pmt[tt], u[tt], pmt[tt + HT], u[tt + HT]);
-                        });
-                        pm = pmt[0];
-#pragma unroll
-                        for (int k = 1; k + 1 < TPG; k += 2) pm = vmax3(pm, pmt[k], pmt[k + 1]);
-                        pm = vmax2(pm, pmt[TPG - 1]);
-                        gm = pair_max(pm);
-                        const float floor = FILTER ? gm + room : gm;
-                        // The position from the element-wise maxima over the tiles (TPG / 2 three-operand
-                        // maxima per position), the tile from the tiles' own maxima.  Two tiles of one
-                        // lane with the pair's maximum are a tie (exact routine), as are two positions.
-                        // (Selecting the leading tile's sixteen values with conditional moves took
-                        // (TPG - 1) * 16 of them, those under vcc several times slower than the rest.)
-                        float w[16];
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            w[r] = u[0][r];
-#pragma unroll
-                            for (int k = 1; k + 1 < TPG; k += 2) w[r] = vmax3(w[r], u[k][r], u[k + 1][r]);
-                            w[r] = vmax2(w[r], u[TPG - 1][r]);
-                        }
-                        unsigned tile = 0u;
-                        unsigned long long seen = 0ull, dup = 0ull;
-#pragma unroll
-                        for (int k = 0; k < TPG; ++k) {
-                            const bool e = pmt[k] >= floor;
-                            const unsigned long long mk = __builtin_amdgcn_ballot_w64(e);
-                            dup |= seen & mk;
-                            seen |= mk;
-                            if (k) tile = e ? (unsigned)(32 * k) : tile;
-                        }
-                        tile_tie |= (unsigned)(dup | (dup >> 32));
-                        // compare pass as a bitmap: bit 15 - r set iff position r holds the maximum
-                        const unsigned bm = bitmap16_pairs(w, floor);
-                        const unsigned cnt = (unsigned)__builtin_popcount(bm);
-                        const unsigned r = ffbh(bm) - 16u;
-                        // action = 32 * tile + row(register) + 4h
-                        const unsigned act = tile | ((r & 0xCu) << 1) | (r & 3u) | (4u * h);
-                        total = cnt ? (cnt << 16) | act : 0u;
-                    }
+                    float R[Grid::ROWS], C[Grid::COLS];
+                    gm = pair_max(grid_maxima<TPG, SLICED>(u, R, C));
+                    map = pair_or(grid_map<TPG>(R, C, FILTER ? gm + room : gm, 4u * h));
+                    jstar[ct] = (int)(grid_action<TPG>(map) & (N - 1));       // (any action where the row is not settled)
+                    multi = (unsigned)__builtin_amdgcn_ballot_w64(__builtin_popcount(map) != 2);
                 } else {
-                    float pend[2];
+                    // lane maximum over this type's registers
+                    float pm = -INFINITY, pend[2];
+                    unsigned total = 0u;
                     int np = 0;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
@@ -791,30 +742,24 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                             match4(acc[ct][0][r], acc[ct][0][r + 1], acc[ct][0][r + 2], acc[ct][0][r + 3],
                                    floor, creg[r], creg[r + 1], creg[r + 2], creg[r + 3], total);
                     });
+                    const unsigned pair = pair_add_u32(total);
+                    jstar[ct] = (int)(pair & 0xFFFFu);
+                    multi = (unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u);
                 }
-                const unsigned pair = pair_add_u32(total);
                 gmax[ct] = gm;
-                jstar[ct] = (int)(pair & 0xFFFFu);
-                if constexpr (FILTER) jstar[ct] &= N - 1;       // (any sum where the wavefront's row is not settled)
-                const unsigned multi = (unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | tile_tie;      // columns
                 ties[ct] = multi;
                 if constexpr (FILTER)
                     if (multi != 0u) {
                         unsigned need = 1u;
                         if constexpr (TPG > 1) {
+                            // the tiles with a value from the threshold on, two grid rows each (columns without
+                            // one, whose sums are infinite or no numbers, take them all)
                             need = 0u;
-                            const float floor = gm + room;
+                            const unsigned rows = (multi >> col) & 1u ? map >> (32 - Grid::ROWS) : 0u;
 #pragma unroll
-                            for (int k = 0; k < TPG; ++k) {
-                                const unsigned long long mk = __builtin_amdgcn_ballot_w64(pmt[k] >= floor);
-                                if (((unsigned)(mk | (mk >> 32)) & multi) != 0u) need |= 1u << k;
-                            }
-                            // (columns whose sums are infinite or no numbers have no such value: all the tiles)
-                            bool any = false;
-#pragma unroll
-                            for (int k = 0; k < TPG; ++k) any |= pmt[k] >= floor;
-                            const unsigned long long some = __builtin_amdgcn_ballot_w64(any);
-                            if ((multi & ~(unsigned)(some | (some >> 32))) != 0u) need = (1u << TPG) - 1u;
+                            for (int k = 0; k < TPG; ++k)
+                                if (__builtin_amdgcn_ballot_w64((rows >> (2 * (TPG - 1 - k)) & 3u) != 0u) != 0ull) need |= 1u << k;
+                            if ((multi & (unsigned)__builtin_amdgcn_ballot_w64(rows == 0u)) != 0u) need = (1u << TPG) - 1u;
                         }
                         ties[ct] = settle(ct, multi, need, rest, gmax[ct], jstar[ct]);
                     }
@@ -1100,9 +1045,9 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
         // explicit.
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_nop 15");
-        // stage 1: per-tile lane maxima and element-wise maxima across the row tiles; the lane
-        // maximum goes to the partner lane
-        float pmt[NT][TPG], w[NT][16], pm[NT], pm_other[NT];
+        // stage 1: the maxima of the grid's rows and columns; the lane maximum goes to the partner lane
+        typedef ArgGrid<TPG> Grid;
+        float R[NT][Grid::ROWS], C[NT][Grid::COLS], pm[NT], pm_other[NT];
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
             float u[TPG][16];
@@ -1110,44 +1055,18 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
             for (int tt = 0; tt < TPG; ++tt)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) u[tt][r] = acc[ct][tt][r];
-            vmax16x2_first(pmt[ct][0], u[0], pmt[ct][TPG / 2], u[TPG / 2]);
-            if constexpr (TPG == 4) {
-                vmax16x2_first(pmt[ct][1], u[1], pmt[ct][3], u[3]);
-                vmax4x16(w[ct], u[0], u[1], u[2], u[3]);
-            } else {
-                vmax2x16(w[ct], u[0], u[1]);
-            }
-            float p = TPG == 4 ? vmax3(pmt[ct][0], pmt[ct][1], pmt[ct][2]) : pmt[ct][0];
-            pm[ct] = vmax2(p, pmt[ct][TPG - 1]);
+            pm[ct] = grid_maxima<TPG>(u, R[ct], C[ct]);
             pm_other[ct] = pair_other(pm[ct], partner_addr);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // stage 2: the pair's maximum; the tile (exactly one per lane, or the columns are marked);
-        // the position as a 16-bit map (bit 15 - r set iff position r holds the maximum); then
-        // (action | number of maximisers << 16), zero in a lane without one, goes to the partner
+        // stage 2: the pair's maximum; the map of the rows and columns that hold it goes to the partner
         float gm[NT];
-        unsigned total[NT], total_other[NT], tile_tie[NT];
+        unsigned map[NT], map_other[NT];
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
             gm[ct] = vmax2(pm[ct], pm_other[ct]);
-            unsigned tile = 0u;
-            unsigned long long seen = 0ull, dup = 0ull;
-#pragma unroll
-            for (int k = 0; k < TPG; ++k) {
-                const bool e = pmt[ct][k] == gm[ct];
-                const unsigned long long mk = __builtin_amdgcn_ballot_w64(e);
-                dup |= seen & mk;
-                seen |= mk;
-                if (k) tile = e ? (unsigned)(32 * k) : tile;
-            }
-            tile_tie[ct] = (unsigned)(dup | (dup >> 32));
-            const unsigned bm = bitmap16_pairs(w[ct], gm[ct]);
-            const unsigned cnt = (unsigned)__builtin_popcount(bm);
-            const unsigned r = ffbh(bm) - 16u;
-            // action = 32 * tile + row(register) + 4h
-            const unsigned act = tile | ((r & 0xCu) << 1) | (r & 3u) | (4u * h);
-            total[ct] = cnt ? (cnt << 16) | act : 0u;
-            total_other[ct] = (unsigned)__builtin_amdgcn_ds_bpermute(partner_addr, (int)total[ct]);
+            map[ct] = grid_map<TPG>(R[ct], C[ct], gm[ct], 4u * h);
+            map_other[ct] = (unsigned)__builtin_amdgcn_ds_bpermute(partner_addr, (int)map[ct]);
             __builtin_amdgcn_sched_barrier(0);
         }
         // stage 3: the action, the gather of its leader column, and whether the tile is clean
@@ -1156,15 +1075,13 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
         typename P::colregs cr[NT];
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) {
-            const unsigned pair = total[ct] + total_other[ct];
-            // (masked: a wavefront that is not clean may hold any sum here, and the gather is issued
+            const unsigned both = map[ct] | map_other[ct];
+            // (masked: a wavefront that is not clean may hold any bits here, and the gather is issued
             // before that is known)
-            js[ct] = (int)(pair & 0xFFFFu);
-            const unsigned jg = (N & (N - 1)) == 0 ? (unsigned)js[ct] & (unsigned)(N - 1)
-                                                    : ((unsigned)js[ct] < (unsigned)N ? (unsigned)js[ct] : 0u);
+            const unsigned jg = grid_action<TPG>(both) & (unsigned)(N - 1);
+            js[ct] = (int)jg;
             P::gather_half(Lt + (unsigned)((jg * G.ats + h * HALF) * sizeof(T)), cr[ct]);
-            const unsigned multi = (unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | tile_tie[ct];
-            clean[ct] = multi == 0u;                         // wave-uniform
+            clean[ct] = __builtin_amdgcn_ballot_w64(__builtin_popcount(both) != 2) == 0ull;      // wave-uniform
             __builtin_amdgcn_sched_barrier(0);
         }
         // stage 4: leader payoffs (each lane its half, the partner the other) and the value
@@ -1209,7 +1126,7 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (t + 1 < K) copy_stage(t + 1, (t + 1) & 1);
-        const float pt = g.prior[t];
+        const float pt = ((uniform_floats)g.prior)[t];
         const frag *Ft = (t & 1) ? F1 : F0;
         const lds_byte *Lt = L0 + (unsigned)((t & 1) * LROW_BYTES);
         read_chunk(Ft, std::integral_constant<int, 0>{}, fb[0]);
