@@ -261,6 +261,31 @@ __device__ __forceinline__ void keep_greater2(float v, unsigned c, float &bv, un
         : [v] "v"(v), [c] "v"(c));
 }
 
+// (bv, bc, br[]) <- (v, c, r[]) in the lanes where v > bv; the mask in a scalar register pair.
+template <int N> __device__ __forceinline__ void keep_greater_rows(float v, unsigned c, const float *r, float &bv, unsigned &bc, float *br)
+{
+    static_assert(N == 2 || N == 4, "rows of one or two row tiles");
+    unsigned long long m;
+#define BSSE_KEEP                                                               \
+        "v_cmp_gt_f32 %[m], %[v], %[bv]\n\t"                                    \
+        "s_nop 1\n\t"                                                           \
+        "v_cndmask_b32 %[bv], %[bv], %[v], %[m]\n\t"                            \
+        "v_cndmask_b32 %[bc], %[bc], %[c], %[m]\n\t"                            \
+        "v_cndmask_b32 %[b0], %[b0], %[r0], %[m]\n\t"                           \
+        "v_cndmask_b32 %[b1], %[b1], %[r1], %[m]\n\t"
+    if constexpr (N == 2)
+        asm(BSSE_KEEP
+            : [bv] "+v"(bv), [bc] "+v"(bc), [b0] "+v"(br[0]), [b1] "+v"(br[1]), [m] "=&s"(m)
+            : [v] "v"(v), [c] "v"(c), [r0] "v"(r[0]), [r1] "v"(r[1]));
+    else
+        asm(BSSE_KEEP
+            "v_cndmask_b32 %[b2], %[b2], %[r2], %[m]\n\t"
+            "v_cndmask_b32 %[b3], %[b3], %[r3], %[m]"
+            : [bv] "+v"(bv), [bc] "+v"(bc), [b0] "+v"(br[0]), [b1] "+v"(br[1]), [b2] "+v"(br[2]), [b3] "+v"(br[3]), [m] "=&s"(m)
+            : [v] "v"(v), [c] "v"(c), [r0] "v"(r[0]), [r1] "v"(r[1]), [r2] "v"(r[2]), [r3] "v"(r[3]));
+#undef BSSE_KEEP
+}
+
 // (bv, bc, bp) <- (v, c, p) in the lanes where v > bv; the mask in a scalar register pair.
 __device__ __forceinline__ void keep_greater(float v, unsigned c, unsigned p, float &bv, unsigned &bc,
                                              unsigned &bp)

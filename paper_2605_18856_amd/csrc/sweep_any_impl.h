@@ -67,6 +67,35 @@ __device__ __forceinline__ f32x16 mfma_bf16(const u32x4 &a, const unsigned *x, c
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// c[i] = max(c[i], a[i], b[i]), i = 0..7
+__device__ __forceinline__ void vmax_into8(float *c, const float *a, const float *b)
+{
+#define BSSE_STEP(i) "v_max3_f32 %[c" #i "], %[c" #i "], %[a" #i "], %[b" #i "]\n\t"
+#define BSSE_INOUT(i) [c##i] "+v"(c[i])
+#define BSSE_IN(i) [a##i] "v"(a[i]), [b##i] "v"(b[i])
+    asm(BSSE_STEP(0) BSSE_STEP(1) BSSE_STEP(2) BSSE_STEP(3) BSSE_STEP(4) BSSE_STEP(5) BSSE_STEP(6) BSSE_STEP(7)
+        : BSSE_INOUT(0), BSSE_INOUT(1), BSSE_INOUT(2), BSSE_INOUT(3), BSSE_INOUT(4), BSSE_INOUT(5), BSSE_INOUT(6), BSSE_INOUT(7)
+        : BSSE_IN(0), BSSE_IN(1), BSSE_IN(2), BSSE_IN(3), BSSE_IN(4), BSSE_IN(5), BSSE_IN(6), BSSE_IN(7));
+#undef BSSE_STEP
+#undef BSSE_INOUT
+#undef BSSE_IN
+}
+// The map of a type of several row tiles (grid_map's, over the columns of all its tiles and the rows of the
+// one or two that lead): bits 16 to 27 stay free for the number of the leading tile.
+constexpr unsigned kUnitTiles = 0xFFFu;
+template <int ROWS> __device__ __forceinline__ unsigned unit_map(const float *R, const float *C, float floor, unsigned h4)
+{
+    unsigned r, c1, c0;
+    if constexpr (ROWS == 4) {
+        bits4x2<false, false>(r, R[0], R[1], R[2], R[3], c1, C[7], C[6], C[5], C[4], floor);
+        c0 = bits4(C[3], C[2], C[1], C[0], floor);
+    } else {
+        bits4x2<false, false>(c1, C[7], C[6], C[5], C[4], c0, C[3], C[2], C[1], C[0], floor);
+        r = (R[0] >= floor ? 2u : 0u) + (R[1] >= floor ? 1u : 0u);
+    }
+    return (r << (32 - ROWS)) | (((c1 << 8) | c0) << h4);
+}
+
 // Maximum of sixteen values.
 __device__ __forceinline__ float vmax16(const float *u)
 {
@@ -521,7 +550,12 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 #pragma unroll
         for (int ct = 0; ct < NT; ++ct) V[ct] = 0.0f;
         // state of the type in progress (FORM 0)
-        float best[NT], w[NT][16];
+        // (a unit is one row tile, or two at a time: its grid rows as far as they hold the best value so far,
+        // and the columns over all units)
+        constexpr int UNIT = PAIRS ? 2 : 1;
+        typedef ArgGrid<FORM == 1 ? 1 : 2> Grid;
+        constexpr int ROWS = FORM == 1 ? Grid::ROWS : 2 * UNIT;
+        float best[NT], R[NT][ROWS], C[NT][Grid::COLS];
         unsigned btile[NT];
         unsigned long long dup[NT];
 
@@ -629,9 +663,12 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                                 // (not minus infinity: a lane whose rows of a tile are all padding must
                                 // not count as a tie with the start value)
                                 best[ct] = -3.402823466e38f; btile[ct] = 0u; dup[ct] = 0ull;
-                                if constexpr (FORM == 0)
+                                if constexpr (FORM == 0) {
 #pragma unroll
-                                    for (int r = 0; r < 16; ++r) w[ct][r] = -INFINITY;
+                                    for (int r = 0; r < ROWS; ++r) R[ct][r] = -INFINITY;
+#pragma unroll
+                                    for (int c = 0; c < Grid::COLS; ++c) C[ct][c] = -INFINITY;
+                                }
                             }
                         }
                         if constexpr (FORM == 1) {
@@ -640,19 +677,21 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                             settle(acc);
 #pragma unroll
                             for (int ct = 0; ct < NT; ++ct) {
+                                float v[1][16];
 #pragma unroll
-                                for (int r = 0; r < 16; ++r) w[ct][r] = acc[ct][r];
-                                best[ct] = vmax16(w[ct]);
+                                for (int r = 0; r < 16; ++r) v[0][r] = acc[ct][r];
+                                best[ct] = grid_maxima<1>(v, R[ct], C[ct]);
                             }
                         } else {
                             const int tb = qq * q.stt;
                             const int te = tb + q.stt < q.tpg ? tb + q.stt : q.tpg;
-                            auto merge = [&](int ct, float pm, int tt) __attribute__((always_inline)) {
+                            auto merge = [&](int ct, const float *r, int tt) __attribute__((always_inline)) {
+                                const float pm = ROWS == 2 ? vmax2(r[0], r[1]) : vmax2(vmax3(r[0], r[1], r[ROWS - 2]), r[ROWS - 1]);
                                 dup[ct] |= __builtin_amdgcn_ballot_w64(pm == best[ct]);
-                                keep_greater2(pm, (unsigned)tt, best[ct], btile[ct]);
+                                keep_greater_rows<ROWS>(pm, (unsigned)tt, r, best[ct], btile[ct], R[ct]);
                             };
 #pragma unroll 1
-                            for (int tt = tb; tt < te; tt += (PAIRS ? 2 : 1)) {
+                            for (int tt = tb; tt < te; tt += UNIT) {
                                 f32x16 a0[NT], a1[PAIRS ? NT : 1];
                                 const u32x4 *f0 = fr + (size_t)(tt - tb) * (PA * KS * 64);
                                 tile_mfma(a0, f0, padded && tt == q.tpg - 1);
@@ -666,10 +705,12 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                                         float v0[16], v1[16];
 #pragma unroll
                                         for (int r = 0; r < 16; ++r) { v0[r] = a0[ct][r]; v1[r] = a1[ct][r]; }
-                                        merge(ct, vmax16(v0), tt);
-                                        merge(ct, vmax16(v1), tt + 1);
-#pragma unroll
-                                        for (int r = 0; r < 16; ++r) w[ct][r] = vmax3(w[ct][r], v0[r], v1[r]);
+                                        float r[4];
+                                        vmax8x2(r[0], v0, r[1], v0 + 8);
+                                        vmax8x2(r[2], v1, r[3], v1 + 8);
+                                        vmax_into8(C[ct], v0, v0 + 8);
+                                        vmax_into8(C[ct], v1, v1 + 8);
+                                        merge(ct, r, tt);
                                     }
                                 }
                                 if (!two) {
@@ -679,9 +720,11 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                                         float v0[16];
 #pragma unroll
                                         for (int r = 0; r < 16; ++r) v0[r] = a0[ct][r];
-                                        merge(ct, vmax16(v0), tt);
-#pragma unroll
-                                        for (int r = 0; r < 16; ++r) w[ct][r] = vmax2(w[ct][r], v0[r]);
+                                        float r[ROWS];
+                                        vmax8x2(r[0], v0, r[1], v0 + 8);
+                                        if constexpr (PAIRS) r[2] = r[3] = -INFINITY;
+                                        vmax_into8(C[ct], v0, v0 + 8);
+                                        merge(ct, r, tt);
                                     }
                                 }
                             }
@@ -691,34 +734,36 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
                         const int t = u;
                         const float pt = prior[t];
                         float gm[NT];
-                        unsigned total[NT], total_other[NT];
+                        unsigned map[NT], map_other[NT];
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) gm[ct] = pair_other(best[ct], partner_addr);
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
                             gm[ct] = vmax2(gm[ct], best[ct]);
-                            // bit 15 - r set iff position r holds the maximum; a unique maximiser of the
-                            // pair sits in this lane's leading tile or the columns are marked in dup
-                            const unsigned bm = bitmap16_pairs(w[ct], gm[ct]);
-                            const unsigned cnt = (unsigned)__builtin_popcount(bm);
-                            const unsigned r = ffbh(bm) - 16u;
-                            const unsigned act = (FORM == 1 ? 0u : btile[ct] << 5) | ((r & 0xCu) << 1) | (r & 3u) | (4u * h);
-                            total[ct] = cnt ? (cnt << 16) | act : 0u;
-                            total_other[ct] = (unsigned)__builtin_amdgcn_ds_bpermute(partner_addr, (int)total[ct]);
+                            // FORM 0: a unique maximiser of the pair sits in this lane's leading unit, whose
+                            // first tile goes with the bits, or the columns are marked in dup
+                            if constexpr (FORM == 1) {
+                                map[ct] = grid_map<1>(R[ct], C[ct], gm[ct], 4u * h);
+                            } else {
+                                map[ct] = unit_map<ROWS>(R[ct], C[ct], gm[ct], 4u * h);
+                                map[ct] = map[ct] ? map[ct] | (btile[ct] << 16) : 0u;
+                            }
+                            map_other[ct] = (unsigned)__builtin_amdgcn_ds_bpermute(partner_addr, (int)map[ct]);
                         }
                         float l[NT];
                         int js[NT];
                         bool clean[NT];
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
-                            const unsigned pair = total[ct] + total_other[ct];
-                            js[ct] = (int)(pair & 0xFFFFu);
-                            unsigned long long multi = __builtin_amdgcn_ballot_w64((pair >> 16) != 1u);
+                            const unsigned both = map[ct] | map_other[ct];
+                            constexpr unsigned BITS = FORM == 1 ? 0xFFFFFFFFu : ~(kUnitTiles << 16);
+                            unsigned long long multi = __builtin_amdgcn_ballot_w64(__builtin_popcount(both & BITS) != 2);
                             if constexpr (FORM == 0) multi |= dup[ct];
                             clean[ct] = multi == 0ull;               // wave-uniform
-                            // (a wavefront that is not clean may hold any sum, and its gather is issued
+                            // (a wavefront that is not clean may hold any bits, and its gather is issued
                             // all the same)
-                            js[ct] = js[ct] < n ? js[ct] : 0;
+                            const unsigned j = FORM == 1 ? grid_action<1>(both) : grid_action<2>(both) + 32u * ((both >> 16) & kUnitTiles);
+                            js[ct] = j < (unsigned)n ? (int)j : 0;
                         }
                         float part[NT];
                         if (q.lead_off >= 0) {

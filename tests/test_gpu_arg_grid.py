@@ -8,9 +8,12 @@ from tests.test_gpu_parity import _make, _run_eval
 
 pytestmark = pytest.mark.gpu
 
-# (m, n, payoffs, storage): one, two, four and eight row tiles a type, rows of full length and shorter ones
+# (m, n, payoffs, storage): one, two, four and eight row tiles a type, rows of full length and shorter ones;
+# then numbers of actions that are no whole row tiles, odd and even numbers of them
 SHAPES = [(32, 32, "normal", "f32"), (30, 32, "int", "f32"), (16, 32, "normal", "bf16"), (32, 64, "normal", "f32"),
-          (64, 128, "normal", "bf16"), (50, 128, "normal", "bf16"), (128, 256, "int", "f32")]
+          (64, 128, "normal", "bf16"), (50, 128, "normal", "bf16"), (128, 256, "int", "f32"),
+          (20, 20, "normal", "f32"), (9, 31, "normal", "bf16"), (30, 50, "normal", "f32"), (40, 33, "int", "f32"),
+          (50, 100, "normal", "bf16"), (100, 200, "int", "f32"), (16, 65, "normal", "bf16"), (8, 129, "normal", "f32")]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "m%dn%d%s_%s" % s)
