@@ -20,6 +20,8 @@ struct AnyGeo {
     int ups;              // units per LDS stage
     int stt, nq;          // a unit too large for a stage: stt row tiles per stage, nq stages
     int buf_bytes;        // one of the two stage buffers
+    int resident;         // workgroups that a compute unit holds
+    int resident_cut;     // the same of the kernel for launches cut over the types
 };
 
 // Device view of one game, passed to kernels by value.  All pointers are device memory
@@ -201,7 +203,7 @@ void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes);
 hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, hipStream_t s);
 hipError_t any_prepare(const GameView &g);
 const char *any_name(const AnyGeo &q);
-long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an unsliced launch
+long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an uncut launch
 // Workgroups that share a launch over `count` candidates cut over the types (1: it is not to be cut).
 int any_shares(const GameView &g, long long count);
 long long any_row_blocks(const GameView &g, long long count);       // workgroups of a launch cut like that

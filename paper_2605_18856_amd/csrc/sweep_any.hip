@@ -3,13 +3,14 @@
 #include "bsse_internal.h"
 #include "sweep_any_impl.h"
 #include <algorithm>
+#include <cmath>
 #include "done_device.h"
 
 namespace bsse {
 
-any_impl::any_kernel_t any_kernel_terms1(int ks, int form);
-any_impl::any_kernel_t any_kernel_terms3(int ks, int form);
-any_impl::any_kernel_t any_kernel_terms6(int ks, int form);
+any_impl::any_kernel_t any_kernel_terms1(int ks, int form, bool many);
+any_impl::any_kernel_t any_kernel_terms3(int ks, int form, bool many);
+any_impl::any_kernel_t any_kernel_terms6(int ks, int form, bool many);
 
 namespace {
 
@@ -17,10 +18,11 @@ using any_impl::THREADS;
 
 int roundup(int v, int to) { return (v + to - 1) / to * to; }
 
-any_impl::any_kernel_t kernel_for(const AnyGeo &q)
+any_impl::any_kernel_t kernel_for(const AnyGeo &q, bool many)
 {
-    return q.terms == 1 ? any_kernel_terms1(q.ks, q.form) : q.terms == 3 ? any_kernel_terms3(q.ks, q.form)
-                                                                         : any_kernel_terms6(q.ks, q.form);
+    return q.terms == 1   ? any_kernel_terms1(q.ks, q.form, many)
+           : q.terms == 3 ? any_kernel_terms3(q.ks, q.form, many)
+                          : any_kernel_terms6(q.ks, q.form, many);
 }
 
 // bf16 part `p` of v: every part the nearest bf16 (ties to even) of what the parts before it leave
@@ -174,11 +176,12 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     q.tile_bytes = parts * q.ks * 1024;
     q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : 0;
     q.nq = 1; q.lead_off = -1;
-    // Two stage buffers per workgroup and two or three workgroups (the register allocation's two
-    // wavefronts per SIMD or better) per compute unit of 160 KiB: 26 KiB a stage.  A type that needs up
-    // to 36 KiB with its leader rows still goes in one piece (two workgroups); beyond that the row tiles
-    // come in pieces and the leader column is gathered from L2.
-    const int cap = 26 * 1024, most = 36 * 1024;
+    // Two stage buffers per workgroup, and as many workgroups on a compute unit of 160 KiB as the registers
+    // allow: 26 KiB a stage for two or three, 19 for four.  A type that needs up to 36 KiB with its leader
+    // rows still goes in one piece (two workgroups); beyond that the row tiles come in pieces and the leader
+    // column is gathered from L2.
+    const int waves = any_impl::occupancy(terms, q.ks, q.form, true);
+    const int cap = (waves >= 4 ? 19 : 26) * 1024, most = waves >= 3 ? cap : 36 * 1024;
     if (q.form >= 8) {
         q.tpg = 1;
         q.units = (K + 32 / q.form - 1) / (32 / q.form);
@@ -207,6 +210,8 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     } else {
         q.buf_bytes = q.stt * q.tile_bytes;
     }
+    q.resident = std::max(2, std::min(waves, 160 * 1024 / (2 * q.buf_bytes + 1024)));
+    q.resident_cut = std::min(q.resident, any_impl::occupancy(terms, q.ks, q.form, false));
     return q;
 }
 
@@ -240,22 +245,30 @@ hipError_t any_prepare(const GameView &g)
     if (2 * g.any.buf_bytes <= 48 * 1024) return hipSuccess;
     // (the most that any game takes on this kernel: the limit is the kernel's, not the game's)
     const int most = 2 * std::max(36 * 1024, 2 * g.any.tile_bytes);
-    return hipFuncSetAttribute((const void *)kernel_for(g.any), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    for (bool many : { false, true })
+        if (hipError_t e = hipFuncSetAttribute((const void *)kernel_for(g.any, many), hipFuncAttributeMaxDynamicSharedMemorySize, most))
+            return e;
+    return hipSuccess;
 }
 
-// Two workgroups on each compute unit.
-constexpr long long RESIDENT = 512;
+constexpr int CUS = 256;
 
 static long long rows_per_block(const AnyGeo &q) { return 32LL * any_impl::WAVES * any_impl::tiles_per_wave(q.terms, q.ks); }
 
+// Time that `side` workgroups of a compute unit take for a block each, two being one.
+static double round_time(long long side) { return side <= 0 ? 0.0 : side == 1 ? 0.8 : side <= 3 ? 0.4 + 0.3 * side : 1.65; }
+
 long long any_num_blocks(const GameView &g, long long count)
 {
-    // At most one resident set (two workgroups a compute unit), and always the whole of it: with the
-    // grid cut to the workgroups that share the blocks evenly, some compute units held one workgroup
-    // and the others two (m = 16, n = 40, K = 30 bf16: 140000 rows 106 -> 96 us, 270000 rows 151 -> 134;
-    // m = 20, n = 12, K = 12: 400000 rows 78 -> 71).
+    // At most one resident set, and always the whole of it: with the grid cut to the workgroups that share
+    // the blocks evenly, some compute units held one workgroup and the others two (m = 16, n = 40, K = 30
+    // bf16: 140000 rows 106 -> 96 us, 270000 rows 151 -> 134; m = 20, n = 12, K = 12: 400000 rows 78 -> 71).
+    // All the workgroups that the registers allow, not two a compute unit (three or four, us): the same 140000
+    // rows 81 -> 70, 1000000 rows 348 -> 281; m = 12, n = 100, K = 30, 100000 rows 101 -> 89; m = 40, n = 80,
+    // K = 50, 100000 rows 310 -> 261; m = 20, n = 20, K = 8, 270000 rows 51 -> 45; m = 9, n = 15, K = 20 bf16,
+    // 1000000 rows 96 -> 74; nothing of eleven shapes and eight sizes slower by more than 2 %.
     const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
-    return blocks < 1 ? 1 : blocks < RESIDENT ? blocks : RESIDENT;
+    return blocks < 1 ? 1 : std::min<long long>(blocks, CUS * g.any.resident);
 }
 
 // Workgroups of a launch cut over the types, 1 when it is not to be cut.
@@ -264,23 +277,33 @@ int any_shares(const GameView &g, long long count)
     const AnyGeo &q = g.any;
     const long long blocks = (count + rows_per_block(q) - 1) / rows_per_block(q), pairs = blocks * q.units;
     if (q.units < 2) return 1;
-    const int shares = (int)std::min<long long>(pairs, RESIDENT);
+    const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg;
+    // Workgroups side by side: the time of a share, which begins with a block's rows (all that are resident,
+    // two a compute unit, us: m = 60, n = 30, K = 20 bf16, 30000 rows 33 and 31; m = 16, n = 40, K = 30 bf16,
+    // 20000 rows 26 and 28; m = 60, n = 100, K = 20, three products, 10000 rows 40 and 43).
+    auto share_time = [&](int r) {
+        const double each = (double)pairs / (CUS * r);
+        return (0.5 * (each + std::ceil(each)) + (4.0 + 6.0 * q.ks) / work) * round_time(r);
+    };
+    int side = 1;
+    for (int r = 2; r <= q.resident_cut; ++r)
+        if (share_time(r) < share_time(side)) side = r;
+    const int shares = (int)std::min<long long>(pairs, CUS * side);
     // Far fewer blocks of candidates than compute units, or packed types (the per-type outputs of a cut
     // launch are most of their cost).
     if (blocks < 128 || (q.form >= 8 && blocks < 256)) return shares;
     if (q.form >= 8 || (count + FINISH_ROWS - 1) / FINISH_ROWS * (g.m + g.K) > (1LL << 16)) return 1;
     // Otherwise what decides is how full the compute units are.  In units of the time a compute unit takes for
-    // two blocks and all types side by side: uncut, the fullest one takes as many as it has blocks for, and
-    // 0.8 (0.6) for a first (a later) one by itself; cut, all take the same, a tenth more for the outputs,
+    // two blocks and all types side by side: uncut, the fullest one takes as many rounds as it has blocks for,
+    // and 0.8 (0.6) for a first (a later) one by itself; cut, all take the same, a tenth more for the outputs,
     // and 12 us for another launch that sums them (the unit is about 0.08 us per type and unit of `work`).
     // Uncut and cut, us: m = 50, n = 100, K = 24 bf16, 50000 rows (196 blocks) 91 and 60, 70001 rows 100 and
     // 75, 131072 rows 110 and 122, 160000 rows 176 and 147; m = 30, n = 50, K = 20, 60000 rows 69 and 53,
     // 100003 rows 75 and 76; m = 16, n = 40, K = 30 bf16, 140000 rows 93 and 84, 270000 rows 130 and 143;
     // m = 20, n = 20, K = 8, 100000 rows 32 and 36; m = 128, n = 255, K = 4, 30000 rows 88 and 64.
-    const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg;
-    const long long most = (blocks + 255) / 256;
-    const double uncut = most / 2 + (most % 2 ? (most == 1 ? 0.8 : 0.6) : 0.0);
-    const double cut = 12.0 / (0.08 * work * q.units) + 1.1 * blocks / RESIDENT;
+    const long long all = CUS * q.resident, rest = (blocks % all + CUS - 1) / CUS;
+    const double uncut = blocks / all * round_time(q.resident) + (blocks >= all && rest == 1 ? 0.6 : round_time(rest));
+    const double cut = 12.0 / (0.08 * work * q.units) + 1.1 * round_time(side) * blocks / (CUS * side);
     return cut < 0.95 * uncut ? shares : 1;
 }
 
@@ -293,7 +316,7 @@ long long any_row_blocks(const GameView &g, long long count)
 hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int shares, hipStream_t s)
 {
     if (a.count <= 0) return hipSuccess;
-    any_impl::any_kernel_t k = kernel_for(g.any);
+    any_impl::any_kernel_t k = kernel_for(g.any, shares <= 1 && any_num_blocks(g, a.count) > 2 * CUS);
     if (!k) return hipErrorNotSupported;
     any_impl::AnyArgs args{ g, a };
     const long long blocks = (a.count + rows_per_block(g.any) - 1) / rows_per_block(g.any);

@@ -43,12 +43,21 @@ constexpr int WAVES = 4, THREADS = WAVES * 64;
 
 // NT: 32-candidate tiles per wavefront.  Two let one fragment read serve two instructions; with
 // three parts of a long row in registers there is room for one.
-constexpr int tiles_per_wave(int terms, int ks) { return (terms == 1 || ks <= 2) ? 2 : 1; }
-// Wavefronts per SIMD that the register allocation is held to.
-constexpr int occupancy(int terms, int ks, int form)
+constexpr int tiles_per_wave(int terms, int ks) { return ks <= (terms == 1 ? 4 : 2) ? 2 : 1; }
+// Wavefronts per SIMD that the register allocation is held to; with one wavefront of every workgroup on each
+// SIMD also the workgroups that a compute unit holds.  These kernels are bound by vector instructions, and a
+// SIMD issues more of them the more wavefronts it chooses from (one, an instruction in 8 cycles; two, in 5.7;
+// four, in 4.9): as many as fit without spilling in the loop over the types (us, 1000000 rows: m = 45,
+// n = 100, K = 24 bf16 587 with two and 442 with three; m = 60, n = 100, K = 20, three products 1039 and 830).
+// `many`: for launches of more than two workgroups a compute unit.  Splits with two k-steps spill 15 and 25
+// registers at a block's start with three (m = 30, n = 50, K = 20: 1000 rows 19.8 us with two, 21.1 with
+// three; 270000 rows 165 and 157).
+constexpr bool spills(int terms, int ks, int form) { return form == 0 && terms != 1 && ks == 2; }
+constexpr int occupancy(int terms, int ks, int form, bool many)
 {
-    if (terms == 6 && ks == 3) return form >= 8 ? 4 : 3;        // (a few registers over the limit when left free)
-    return ks <= 2 && form != 0 ? 3 : 2;
+    if (form == 0) return (terms == 1 || ks <= 4) && (many || !spills(terms, ks, form)) ? 3 : 2;
+    if (form == 1) return terms == 1 ? (ks <= 4 ? 4 : 3) : ks == 1 ? 4 : ks <= 4 ? 3 : 2;
+    return terms == 1 ? (ks <= 2 ? 4 : 3) : ks == 3 ? 4 : ks <= 4 ? 3 : 2;
 }
 
 __device__ __forceinline__ unsigned pack_bf16(float a, float b)
@@ -192,8 +201,8 @@ __device__ __forceinline__ late_args late()
 // TERMS: 1 = operands rounded to bf16 (bf16 storage), 3 / 6 = fp32 operands as three bf16 parts
 // against payoffs that are bf16 numbers / payoffs in three parts.  KS: k-steps of 16 leader actions.
 // FORM: see the top of the file.
-template <int TERMS, int KS, int FORM>
-__global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any_kernel(AnyArgs args)
+template <int TERMS, int KS, int FORM, bool MANY>
+__global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) sweep_any_kernel(AnyArgs args)
 {
     constexpr int NT = tiles_per_wave(TERMS, KS);
     constexpr int XP = TERMS == 1 ? 1 : 3;               // parts of a candidate component
@@ -203,7 +212,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
     constexpr bool XF = !NARROW && TERMS != 1 && KS <= 2;   // the fp32 half row stays in registers
     constexpr int TPT = NARROW ? 32 / FORM : 1;          // types per unit
     constexpr bool UNSCALE = XP == 3 && !XF;             // leader payoffs come from the split row: see load_rows
-    constexpr bool PAIRS = FORM == 0 && TERMS == 1;      // row tiles two at a time: fewer vector instructions
+    constexpr bool PAIRS = FORM == 0 && TERMS == 1 && KS <= 2;      // row tiles two at a time: fewer vector instructions
                                                          // per tile where these outweigh the matrix time
     const AnyGeo &q = args.g.any;
 
@@ -839,13 +848,13 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM)) sweep_any
 typedef void (*any_kernel_t)(AnyArgs);
 
 template <int TERMS, int KS>
-any_kernel_t any_kernel_form(int form)
+any_kernel_t any_kernel_form(int form, bool many)
 {
     switch (form) {
-    case 0: return sweep_any_kernel<TERMS, KS, 0>;
-    case 1: return sweep_any_kernel<TERMS, KS, 1>;
-    case 8: return sweep_any_kernel<TERMS, KS, 8>;
-    case 16: return sweep_any_kernel<TERMS, KS, 16>;
+    case 0: return many ? sweep_any_kernel<TERMS, KS, 0, true> : sweep_any_kernel<TERMS, KS, 0, !spills(TERMS, KS, 0)>;
+    case 1: return sweep_any_kernel<TERMS, KS, 1, true>;
+    case 8: return sweep_any_kernel<TERMS, KS, 8, true>;
+    case 16: return sweep_any_kernel<TERMS, KS, 16, true>;
     }
     return nullptr;
 }

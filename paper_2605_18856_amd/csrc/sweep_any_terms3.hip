@@ -4,12 +4,12 @@
 
 namespace bsse {
 
-any_impl::any_kernel_t any_kernel_terms3(int ks, int form)
+any_impl::any_kernel_t any_kernel_terms3(int ks, int form, bool many)
 {
     switch (ks) {
-    case 2: return any_impl::any_kernel_form<3, 2>(form);
-    case 4: return any_impl::any_kernel_form<3, 4>(form);
-    case 8: return any_impl::any_kernel_form<3, 8>(form);
+    case 2: return any_impl::any_kernel_form<3, 2>(form, many);
+    case 4: return any_impl::any_kernel_form<3, 4>(form, many);
+    case 8: return any_impl::any_kernel_form<3, 8>(form, many);
     }
     return nullptr;
 }

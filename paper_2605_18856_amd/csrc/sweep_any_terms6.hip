@@ -3,15 +3,15 @@
 
 namespace bsse {
 
-any_impl::any_kernel_t any_kernel_terms6(int ks, int form)
+any_impl::any_kernel_t any_kernel_terms6(int ks, int form, bool many)
 {
     switch (ks) {
-    case 1: return any_impl::any_kernel_form<6, 1>(form);
-    case 2: return any_impl::any_kernel_form<6, 2>(form);
-    case 3: return any_impl::any_kernel_form<6, 3>(form);
-    case 4: return any_impl::any_kernel_form<6, 4>(form);
-    case 6: return any_impl::any_kernel_form<6, 6>(form);
-    case 8: return any_impl::any_kernel_form<6, 8>(form);
+    case 1: return any_impl::any_kernel_form<6, 1>(form, many);
+    case 2: return any_impl::any_kernel_form<6, 2>(form, many);
+    case 3: return any_impl::any_kernel_form<6, 3>(form, many);
+    case 4: return any_impl::any_kernel_form<6, 4>(form, many);
+    case 6: return any_impl::any_kernel_form<6, 6>(form, many);
+    case 8: return any_impl::any_kernel_form<6, 8>(form, many);
     }
     return nullptr;
 }

@@ -34,3 +34,13 @@ def test_every_row_whatever_its_share(shape):
         for first, last in ((0, 1), (255, 258), (12000, 12400), (30000, 45000), (50000, 50001)):
             _, v, b = _run_eval(g, X[first:last])
             assert np.array_equal(v, V[first:last]) and np.array_equal(b, br[first:last])
+
+
+@pytest.mark.parametrize("shape", [(30, 50, 2, "normal", "f32"), (20, 40, 3, "int", "f32"), (16, 40, 3, "uniform", "bf16"),
+                                   (24, 20, 4, "normal", "f32"), (90, 33, 1, "uniform", "bf16")],
+                         ids=lambda s: "m%dn%dK%d%s_%s" % s)
+@pytest.mark.parametrize("count", [131072, 131073, 196609, 262401])
+def test_more_blocks_than_two_a_compute_unit(shape, count):
+    m, n, K, kind, storage = shape
+    game = workloads.small_game(m, n, K, 97 + m + n, kind=kind, storage=storage)
+    _full_check(game, workloads.host_candidates(m, count, 98), bsse.BSSE_PATH_AUTO, "mfma")
