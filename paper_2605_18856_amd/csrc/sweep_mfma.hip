@@ -24,6 +24,7 @@
 // (bit-identical) and walks the exact maximisers in ascending action order comparing leader
 // payoffs.
 #include "bsse_internal.h"
+#include <algorithm>
 #include "mfma_device.h"
 #include "done_device.h"
 #include <limits.h>
@@ -1212,23 +1213,27 @@ struct Variant {
 
 const Variant kVariants[] = {
     // fp32 MFMA (the last number: k-steps per fragment read-ahead chunk, 0 = the fragment reads are left
-    // where they are used; the last flag: small part products are left out where they decide nothing.  The
-    // other split shapes keep them: n = 16 has few to leave out (100 -> 106 us for 2^20 rows of m = 16,
-    // K = 16), and four candidate tiles a wavefront have no registers for it (n = 32, three products: 189
-    // -> 298 us))
+    // where they are used; the last flag: small part products are left out where they decide nothing.  n = 16
+    // with six products keeps them: there are few to leave out (100 -> 106 us for 2^20 rows of m = 16, K = 16))
     BSSE_VARIANT(float, 0, 1, 8, 8, 4, 4, 1, 2, true, 0, false, "mfma_f32"),
     BSSE_VARIANT(float, 0, 1, 16, 16, 4, 4, 2, 2, true, 0, false, "mfma_f32"),
     BSSE_VARIANT(float, 0, 1, 32, 32, 4, 4, 4, 2, true, 0, false, "mfma_f32"),
     BSSE_VARIANT(float, 0, 1, 32, 64, 2, 4, 4, 2, true, 0, false, "mfma_f32"),
     BSSE_VARIANT(float, 0, 1, 128, 256, 1, 4, 2, 2, false, 0, false, "mfma_f32"),
     // bf16 MFMA, operands rounded to bf16
-    BSSE_VARIANT(__bf16, 1, 1, 16, 32, 4, 4, 2, 2, true, 0, false, "mfma_bf16"),
-    BSSE_VARIANT(__bf16, 1, 1, 32, 16, 4, 4, 2, 2, false, 0, false, "mfma_bf16"),
+    // Candidate tiles a wavefront and wavefronts a SIMD: these kernels issue vector instructions most of the
+    // time, and more wavefronts issue more of them, as long as registers and two stages in LDS allow it
+    // (2^20 rows, K = 16, us: m = 16, n = 32 bf16, four tiles 91, two 85, one 92; m = 32, n = 16, four 118,
+    // two 111, one 103; three products, two tiles a wavefront and one row tile a stage, four wavefronts a SIMD
+    // 145, three 186, four tiles and two wavefronts 184; six products with n = 32 spill with four wavefronts,
+    // 200, and with one tile wait for LDS, 199; 170 as they are)
+    BSSE_VARIANT(__bf16, 1, 1, 16, 32, 2, 4, 2, 4, true, 0, false, "mfma_bf16"),
+    BSSE_VARIANT(__bf16, 1, 1, 32, 16, 1, 4, 2, 4, false, 0, false, "mfma_bf16"),
     BSSE_VARIANT_WIDE(__bf16, 1, 64, 128, 8, 4, "mfma_bf16"),
     // bf16 MFMA on fp32 operands split into bf16 parts
     BSSE_VARIANT(__bf16, 2, 6, 16, 16, 2, 4, 2, 2, true, 0, false, "mfma_split6"),
     BSSE_VARIANT(__bf16, 2, 6, 32, 32, 2, 4, 1, 3, true, 0, true, "mfma_split6"),
-    BSSE_VARIANT(__bf16, 2, 3, 32, 32, 4, 4, 4, 2, true, 0, false, "mfma_split3"),
+    BSSE_VARIANT(__bf16, 2, 3, 32, 32, 2, 4, 1, 4, true, 0, true, "mfma_split3"),
     BSSE_VARIANT(__bf16, 2, 6, 32, 64, 2, 4, 2, 2, true, 0, true, "mfma_split6"),
     // (one fragment ahead: the next one's LDS read runs under two matrix instructions; two ahead spill)
     BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 1, true, "mfma_split3"),
@@ -1294,13 +1299,31 @@ long long mfma_num_blocks(int variant, long long count)
     return (count + per - 1) / per;
 }
 
-// Stages per type slice of a sliced launch: 32 candidates per wavefront, whole groups per slice; few
-// rows are cut into about 256 slices, many rows fill the chip by themselves.
+// Kernels of eight wavefronts fill a compute unit with one workgroup: the time of `blocks` blocks of rows and
+// all types, cut into `slices`, in types of one candidate tile a wavefront.  A slice begins with its rows
+// (two types' time).
+static long long cut_time(long long blocks, int K, int slices)
+{
+    return (blocks * slices + 255) / 256 * ((K + slices - 1) / slices + 2);
+}
+
+// Stages per type slice of a sliced launch: 32 candidates per wavefront, whole groups per slice.
+// Workgroups of four wavefronts: few rows are cut into about 1024 slices, four a compute unit (two thirds
+// to one half of the time of 256: m = n = 32, K = 16, 10000 rows 21 -> 19 us; three products, 30000 rows
+// 27 us with 512 and 24 with 1024).  Of eight: the number with the least time (m = 128, n = 256, K = 100,
+// 40000 rows 593 -> 468 us; cut finer than rounds of 256 workgroups ask for, 1000 rows 37 -> 43).
 static int stages_per_slice(const Variant &v, int K, long long count)
 {
     const int nstages = (row_tiles_for(v, K) + v.stage_tiles - 1) / v.stage_tiles;
     const long long per = 32LL * v.waves, blocks = (count + per - 1) / per;
-    const int slices = blocks >= 256 ? 1 : (int)(256 / blocks);
+    int slices = 1;
+    if (v.waves < 8) {
+        slices = blocks >= 1024 ? 1 : (int)(1024 / blocks);
+    } else if (blocks < 4096) {
+        slices = blocks >= 256 ? 1 : (int)std::min<long long>(256 / blocks, K);          // one round
+        for (int s = slices + 1; s <= K && s <= 16; ++s)
+            if (cut_time(blocks, K, s) < cut_time(blocks, K, slices)) slices = s;
+    }
     const int spg = v.geo.tpg > v.stage_tiles ? v.geo.tpg / v.stage_tiles : 1;       // stages per group
     return ((nstages + slices - 1) / slices + spg - 1) / spg * spg;
 }
@@ -1320,14 +1343,27 @@ long long mfma_row_blocks(const GameView &g, long long count)
     return (count + per - 1) / per * mfma_slices(g, count);
 }
 
-// A workgroup of the unsliced kernel walks every type, whatever the number of rows: with fewer of them
-// than half the compute units, the same rows spread over types (and, on the wide kernel, over twice or
-// four times as many workgroups) finish sooner, although one candidate tile per wavefront reads every
-// fragment for 32 candidates only.
+// A workgroup of the unsliced kernel walks every type, whatever the number of rows: where they do not fill
+// the chip, the same rows spread over types finish sooner, although one candidate tile per wavefront reads
+// every fragment for 32 candidates only.  Workgroups of four wavefronts: up to 512 of them with one candidate
+// tile each (40000 rows, us, whole and cut: m = n = 32, K = 16 39 and 30; n = 64 48 and 36; three products
+// 40 and 25; m = 16, n = 32 bf16 29 and 21; m = n = 16 30 and 23; 100000 rows 43 and 52).  Of eight: fewer whole
+// workgroups than half the compute units, or where that is less time: the wide kernel takes its four candidate
+// tiles in that of 2.5 here, and a type takes about n (0.0104 + 3.3e-5 terms m) us (us, whole or uncut in
+// slices, and now: m = 64, n = 128, K = 64 bf16, 66000 rows 204 and 152; m = 128, n = 256, K = 100, 66000 rows
+// 1187 and 829, 140000 rows 1859 and 1528).
 bool mfma_few_rows(const GameView &g, long long count)
 {
-    if (g.variant < 0 || g.variant >= kNumVariants || mfma_num_blocks(g.variant, count) > 128) return false;
-    return kVariants[g.variant].wide || mfma_slices(g, count) > 1;
+    if (g.variant < 0 || g.variant >= kNumVariants) return false;
+    const Variant &v = kVariants[g.variant];
+    const long long per = 32LL * v.waves, blocks = (count + per - 1) / per, whole = mfma_num_blocks(g.variant, count);
+    if (v.waves < 8) return blocks <= 512 && mfma_slices(g, count) > 1;
+    if (blocks >= 4096) return false;
+    const int slices = mfma_slices(g, count);
+    if (whole <= 128 && (v.wide || slices > 1)) return true;
+    const double type = v.n * (0.0104 + 3.3e-5 * v.terms * v.mp_base);
+    const double outputs = (12.0 + 2e-6 * (double)count * g.K) / type;
+    return (double)cut_time(blocks, g.K, slices) + outputs < 0.95 * (v.wide ? 2.5 : 1.0) * (double)((whole + 255) / 256 * g.K);
 }
 
 // Once per game, on the game's device: kernels whose two stage buffers exceed the default 48 KiB of
