@@ -165,7 +165,7 @@ bsse_status bsse_sweep(bsse_game *g, const float *candidates_dev, int64_t count,
  * loops, harnesses that forbid allocation, code that will later be captured into a HIP graph).
  * Same arguments, same result bit for bit as bsse_sweep on the same rows, but every piece of device
  * scratch (workgroup records, running best, winning row, tie counter, running-best slots) lives in
- * a static device array of 1.2 MiB that each GPU the library runs on holds until the process ends;
+ * a static device array of 3.2 MiB that each GPU the library runs on holds until the process ends;
  * the call performs no hipMalloc / hipHostMalloc / hipFree and creates no stream or event.
  * candidates_dev must be given (not NULL).  Limits: the chunk may need at most 65536 workgroup
  * records (2^24 candidates on the matrix-core paths with 256 candidates per workgroup, 2^22 on

@@ -549,17 +549,18 @@ bsse_status drain_timing(bsse_game *g)
 
 // ---------------------------------------------------------------------- static scratch
 // Scratch of bsse_sweep_static: a file-scope device array, so that the entry point allocates
-// nothing.  Every GPU the library runs on holds its own copy (1.2 MiB) until the process ends; the
+// nothing.  Every GPU the library runs on holds its own copy (3.2 MiB) until the process ends; the
 // array's name is only a host-side stand-in, the device address is looked up once per device with
 // hipGetSymbolAddress and that pointer is what kernels and fills are given.
 namespace {
 
-constexpr long long STATIC_MAX_BLOCKS = 65536;    // workgroup records of one chunk
+constexpr long long STATIC_MAX_BLOCKS = 65536;    // workgroup records of one chunk, as the limit counts them
+constexpr long long STATIC_HELD_BLOCKS = 4 * STATIC_MAX_BLOCKS;      // (see mfma_limit_blocks)
 constexpr int STATIC_MAX_M = 4096, STATIC_MAX_SLOTS = 2048;
 constexpr size_t ST_OFF_RUN = 0, ST_OFF_TIES = 256, ST_OFF_BESTX = 512,
                  ST_OFF_BLKV = ST_OFF_BESTX + (size_t)STATIC_MAX_M * sizeof(float),
-                 ST_OFF_BLKI = ST_OFF_BLKV + (size_t)STATIC_MAX_BLOCKS * sizeof(float),
-                 ST_OFF_SLOTS = ST_OFF_BLKI + (size_t)STATIC_MAX_BLOCKS * sizeof(long long),
+                 ST_OFF_BLKI = ST_OFF_BLKV + (size_t)STATIC_HELD_BLOCKS * sizeof(float),
+                 ST_OFF_SLOTS = ST_OFF_BLKI + (size_t)STATIC_HELD_BLOCKS * sizeof(long long),
                  STATIC_BYTES = ST_OFF_SLOTS + (size_t)STATIC_MAX_SLOTS * sizeof(SmallSlot);
 static_assert(sizeof(RunningBest) <= 256 && sizeof(SmallSlot) == 64, "scratch layout");
 static_assert(ST_OFF_BLKV % 256 == 0 && ST_OFF_BLKI % 256 == 0 &&
@@ -1518,7 +1519,8 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
     }
     const bool small = on_small_kernel(g);
     // (every vector-path game has the documented limit, also where the short-row kernel needs fewer records)
-    const long long records = g->path == PATH_VALU ? valu_num_blocks(count) : sweep_blocks(g, count);
+    const long long records = g->path == PATH_VALU ? valu_num_blocks(count)
+                              : small || on_any(g) || on_tiny(g) ? sweep_blocks(g, count) : mfma_limit_blocks(g->view.variant, count);
     if (!small && records > STATIC_MAX_BLOCKS)
         return fail(BSSE_EOVERFLOW, "%lld candidates need %lld workgroup records; the static scratch holds %lld "
                     "(sweep in pieces, or use bsse_sweep)", (long long)count, records, STATIC_MAX_BLOCKS);
@@ -1550,7 +1552,7 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
     w.best_x = reinterpret_cast<float *>(ptr + ST_OFF_BESTX);
     w.blk_v = reinterpret_cast<float *>(ptr + ST_OFF_BLKV);
     w.blk_i = reinterpret_cast<long long *>(ptr + ST_OFF_BLKI);
-    w.blk_cap = STATIC_MAX_BLOCKS;
+    w.blk_cap = STATIC_HELD_BLOCKS;
     w.slots = small ? reinterpret_cast<SmallSlot *>(ptr + ST_OFF_SLOTS) : nullptr;
     w.slot_sets = small ? 1 : 0;
     w.fixed = true;

@@ -170,6 +170,7 @@ hipError_t launch_sweep_tiny(const GameView &g, const SweepArgs &a, bool eval, i
 int mfma_select(int m, int n, int K, int mode, bool exact);
 const char *mfma_variant_name(int variant);
 long long mfma_num_blocks(int variant, long long count);
+long long mfma_limit_blocks(int variant, long long count);        // the same as the limit of the static scratch counts them
 hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t s);
 hipError_t mfma_prepare(int variant);   // per game, on its device, before the first launch
 // Type slices of a launch with l_out; whether `count` candidates are so few that a sweep or an

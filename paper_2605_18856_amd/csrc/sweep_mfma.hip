@@ -1299,6 +1299,14 @@ long long mfma_num_blocks(int variant, long long count)
     return (count + per - 1) / per;
 }
 
+// The limit of the static scratch is one of candidates too: n <= 32 with one or three products count 512 to a
+// record, of which the workgroups may take as few as 128.
+long long mfma_limit_blocks(int variant, long long count)
+{
+    const Variant &v = kVariants[variant];
+    return v.n <= 32 && v.terms != 6 ? (count + 511) / 512 : mfma_num_blocks(variant, count);
+}
+
 // Kernels of eight wavefronts fill a compute unit with one workgroup: the time of `blocks` blocks of rows and
 // all types, cut into `slices`, in types of one candidate tile a wavefront.  A slice begins with its rows
 // (two types' time).

@@ -118,3 +118,21 @@ def test_static_sweep_allocates_no_device_memory_and_rejects_what_exceeds_the_sc
         torch.cuda.synchronize()
         assert torch.cuda.mem_get_info()[0] == free0
         _same(got, bsse.bsse_sweep(h, X, 50000))
+
+
+@pytest.mark.parametrize("shape", [(32, 32, 2, "int", "f32"), (16, 32, 2, "uniform", "bf16"), (32, 16, 2, "uniform", "bf16")],
+                         ids=lambda s: "m%dn%dK%d%s_%s" % s)
+def test_static_scratch_holds_512_candidates_a_record(shape):
+    """2^25 candidates on the kernels whose limit counts 512 to a record, whatever their workgroups take."""
+    import torch
+    m, n, K, kind, storage = shape
+    count = 1 << 25
+    game = workloads.small_game(m, n, K, 5, kind, storage)
+    store = bsse.BSSE_STORAGE_BF16 if storage == "bf16" else bsse.BSSE_STORAGE_F32
+    with bsse.bsse_create(m, n, K, game.A, game.B, game.prior, storage=store) as g:
+        X = torch.empty((count + 1, m), dtype=torch.float32, device="cuda")
+        bsse.bsse_dirichlet(g, 6, 0, count + 1, X)
+        _same(bsse.bsse_sweep_static(g, X, count), bsse.bsse_sweep(g, X, count))
+        with pytest.raises(bsse.BsseError) as e:
+            bsse.bsse_sweep_static(g, X, count + 1)
+        assert e.value.status == bsse.BSSE_EOVERFLOW
