@@ -235,6 +235,10 @@ template <int MP> struct Path<__bf16, MP> {
 // that one flat asynchronous copy (global_load_lds) brings everything a stage needs into LDS.
 // Leader rows in LDS are padded by 16 bytes so that gathers of different rows spread over
 // banks.  The record size is rounded to what one sweep of all wavefronts copies (1 KiB each).
+// terms == 6: the six products take the payoffs' parts 0 1 0 2 1 0, and a tile holds the three once (mp / 2
+// slots): half the stage copies, and four fragment reads instead of six for the products that are always
+// summed.  2^20 rows, K = 16, us: m = n = 32 175 -> 165, n = 64 291 -> 268,
+// m = n = 16 101 -> 93.
 struct Geometry {
     int tile_bytes, tpg, types, ts, ats, at_bytes, rec_bytes;
 };
@@ -247,7 +251,7 @@ __host__ __device__ constexpr Geometry make_geometry(int esz, int mp, int n, int
                                                      int waves, bool at_lds, int terms = 1)
 {
     Geometry q{};
-    q.tile_bytes = 32 * (terms == 3 ? mp / 3 : mp) * esz;
+    q.tile_bytes = 32 * (terms == 3 ? mp / 3 : terms == 6 ? mp / 2 : mp) * esz;
     q.tpg = n >= 32 ? n / 32 : 1;
     q.types = n >= 32 ? 1 : 32 / n;
     q.ts = stage_tiles >= q.tpg ? (stage_tiles / q.tpg) * q.types : 0;     // whole types per stage
@@ -316,7 +320,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     static_assert(!AT_LDS || STAGE_TILES >= TPG, "leader rows in LDS need whole types per stage");
     constexpr int REP = TERMS == 3 ? 3 : 1;             // part products per stored fragment
     constexpr int KF = KS / REP;                        // fragment k-steps per row tile
-    constexpr int TILE_FRAGS = KF * 64;                 // fragments per row tile
+    constexpr int TILE_FRAGS = (TERMS == 6 ? KF / 2 : KF) * 64;         // fragments per row tile
     // CUT (split operands): the products that decide nearly every arg-max are summed first, (p0,B0) (p0,B1)
     // (p1,B0) of six and p0 and p1 of three; then the small others (of three in a sum of their own, which
     // is added: the margin is a third).  FILTER: those are left out where the maximum stands clear of the
@@ -382,6 +386,11 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
         } else {
             return P::mfma(fr, xc, s, c);
         }
+    };
+    // stored fragment of k-step s (of a tile)
+    auto stored = [](int s) __attribute__((always_inline)) {
+        constexpr int bsel6[6] = { 0, 1, 0, 2, 1, 0 };
+        return (TERMS == 6 ? bsel6[s / SPT] * SPT + s % SPT : s) * 64;
     };
     xreg x[NT][XS];
     float xf[NT][LEAD_F32 ? HALF_BASE : 1];
@@ -489,7 +498,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     // CUT: one row tile, whose fragments are at `tile`, against one candidate tile, small products and all.
     auto rest_of = [&](const xreg *xc, const frag *tile, f32x16 r) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = TERMS == 6 ? KF / 2 : 0; s < KF; ++s) r = x_mfma(tile[s * 64 + lane], xc, TERMS == 3 ? 2 * KF + s : s, r);
+        for (int s = TERMS == 6 ? KF / 2 : 0; s < KF; ++s) r = x_mfma(tile[stored(s) + lane], xc, TERMS == 3 ? 2 * KF + s : s, r);
         return r;
     };
     auto whole_tile = [&](const xreg *xc, const frag *tile) __attribute__((always_inline)) {
@@ -498,7 +507,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
         for (int e = 0; e < 16; ++e) sum[e] = 0.0f;
 #pragma unroll
         for (int s = 0; s < MAIN_KF; ++s) {
-            const frag af = tile[s * 64 + lane];
+            const frag af = tile[stored(s) + lane];
 #pragma unroll
             for (int q = 0; q < MAIN_REP; ++q) sum = x_mfma(af, xc, q * KF + s, sum);
         }
@@ -572,7 +581,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
             for (int tt = 0; tt < NTILES; ++tt)
 #pragma unroll
                 for (int ks = 0; ks < MAIN_KF; ++ks) {
-                    const frag af = base[(size_t)tt * TILE_FRAGS + (size_t)ks * 64 + lane];
+                    const frag af = base[(size_t)tt * TILE_FRAGS + stored(ks) + lane];
 #pragma unroll
                     for (int q = 0; q < MAIN_REP; ++q)
 #pragma unroll
@@ -581,6 +590,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
                 }
             return;
         }
+        static_assert(PF == 0 || TERMS != 6, "fragments are read ahead in the order of the k-steps");
         static_assert(PF == 0 || KF % (PF ? PF : 1) == 0, "fragment chunk must divide the k-steps of a tile");
         constexpr int C = PF ? PF : 1;
         constexpr int NCH = NTILES * KF / C;
@@ -1481,7 +1491,8 @@ void filter_margins(int variant, int m, int n, int K, const float *B, float *mar
 // slots h*MP/2 .. (h+1)*MP/2; within a half, slot = term * mp_base/2 + (i - h*mp_base/2) for the
 // leader actions i of that half, and the value stored at (term, i) is part q(term) of the payoff:
 // the payoff itself when terms == 1, parts (0,1,0,2,1,0) for six terms, (0,0,0) for three (whose
-// fragments hold the first block only: the kernel uses each for all three terms).
+// fragments hold the first block only: the kernel uses each for all three terms; those of six terms hold
+// parts 0, 1 and 2 once).
 // Bpack = stage records (see Geometry): per stage, STAGE_TILES row tiles, each laid out as
 // [k-step][lane 0..63][fragment], where lane = 32*h + rowInTile supplies the slots
 // h*MP/2 + (elements per lane)*s + e of (type, action) row 32*tile + rowInTile; then, when the
@@ -1506,7 +1517,7 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
     const int MP = v->mp_base * v->terms, half = MP / 2, half_base = v->mp_base / 2;
     const bool bf = v->mode != 0;
     const int epl = bf ? 8 : 1;                            // k-slots per lane per MFMA
-    const int ks = half / epl / (v->terms == 3 ? 3 : 1);   // fragment k-steps per tile (one block of three-term rows)
+    const int ks = half / epl / (v->terms == 3 ? 3 : v->terms == 6 ? 2 : 1);         // stored fragments per tile and lane
     const int tiles = row_tiles_for(*v, K);
     const int nstages = (tiles + v->stage_tiles - 1) / v->stage_tiles;
     const size_t esz = bf ? 2 : 4;
@@ -1529,14 +1540,14 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
         }
     };
     // value stored at slot `li` (within lane half hh) of payoff matrix M (type t, action j)
-    auto slot_value = [&](const float *M, int t, int j, int hh, int li) -> float {
+    auto slot_value = [&](const float *M, int t, int j, int hh, int li, bool fragment) -> float {
         const int term = li / half_base, i = hh * half_base + li % half_base;
         if (t >= K || i >= m) return 0.0f;
         const float val = M[((size_t)t * m + i) * n + j];
         if (v->terms == 1) return val;
         float part[3];
         bf16_parts(val, part);
-        return part[v->terms == 3 ? 0 : bsel6[term]];
+        return part[v->terms == 3 ? 0 : fragment ? term : bsel6[term]];
     };
     for (int tile = 0; tile < tiles; ++tile) {
         unsigned char *tb = pb + (size_t)(tile / v->stage_tiles) * G.rec_bytes +
@@ -1546,7 +1557,7 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
                 const int hh = lane / 32, row = tile * 32 + lane % 32;
                 const int t = row / n, j = row % n;
                 for (int e = 0; e < epl; ++e)
-                    put(tb, ((size_t)s * 64 + lane) * epl + e, slot_value(B, t, j, hh, epl * s + e));
+                    put(tb, ((size_t)s * 64 + lane) * epl + e, slot_value(B, t, j, hh, epl * s + e, true));
             }
     }
     if (v->at_lds)
@@ -1563,7 +1574,7 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
                     }
                     for (int hh = 0; hh < 2; ++hh)
                         for (int li = 0; li < half; ++li)
-                            put(ab, ((size_t)q * n + j) * G.ats + hh * half + li, slot_value(A, t, j, hh, li));
+                            put(ab, ((size_t)q * n + j) * G.ats + hh * half + li, slot_value(A, t, j, hh, li, false));
                 }
             }
         }
@@ -1576,7 +1587,7 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
             }
             for (int hh = 0; hh < 2; ++hh)
                 for (int li = 0; li < half; ++li)
-                    put(pa, ((size_t)t * n + j) * MP + hh * half + li, slot_value(A, t, j, hh, li));
+                    put(pa, ((size_t)t * n + j) * MP + hh * half + li, slot_value(A, t, j, hh, li, false));
         }
     *Bpack = pb; *ATpack = pa;
 }
