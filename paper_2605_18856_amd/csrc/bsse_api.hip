@@ -695,7 +695,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     try {
         g->hA.assign(A, A + elems); g->hB.assign(B, B + elems); g->hprior.assign(prior, prior + K);
         g->hprior.resize((size_t)2 * K, 0.0f);          // (the filter's margins behind it)
-        if (use_mfma) filter_margins(variant, m, n, K, B, g->hprior.data() + K);
+        if (use_mfma) variant = mfma_filter(variant, m, n, K, B, g->hprior.data() + K);
         g->won_x.resize((size_t)m); g->won_br.resize((size_t)K);
     } catch (...) { delete g; return fail(BSSE_ENOMEM, "host allocation failed"); }
     g->view.variant = variant;

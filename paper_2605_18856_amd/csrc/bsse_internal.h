@@ -183,8 +183,9 @@ bool mfma_is_small(int variant);       // the small-game kernel: launch_finish_s
 void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B, void **Bpack,
                size_t *Bbytes, void **ATpack, size_t *ATbytes, int *m_pad, int *n_pad);
 
-// Margins [K] of the filter of variants with split operands; others leave `margin` as it is.
-void filter_margins(int variant, int m, int n, int K, const float *B, float *margin);
+// Margins [K] of the filter of variants with split operands (others leave `margin` as it is).  Returns the variant
+// that sweeps this game: the one without a filter where that is the faster one.
+int mfma_filter(int variant, int m, int n, int K, const float *B, float *margin);
 
 // Small-game matrix-core kernel (n = 8, m = 8, K in {4, 8, 12, 16}, fp32); part of the MFMA path.
 bool small_supported(int m, int n, int K, int storage);

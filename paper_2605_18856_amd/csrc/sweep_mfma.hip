@@ -301,7 +301,7 @@ constexpr float kScale1 = 0x1p9f, kScale2 = 0x1p18f, kLeastNorm = 0x1p-30f, kLea
 // sequence does not depend on NT, OCC or SLICED, so every instantiation of a packing gives the
 // same bits for the same row.
 template <typename T, int MP, int N, int NT, int WAVES, int STAGE_TILES, int OCC, bool AT_LDS, int TERMS,
-          bool SLICED, int PF, bool CUT>
+          bool SLICED, int PF, bool FILTER>
 __global__ void __launch_bounds__(WAVES * 64, OCC)
 sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 {
@@ -321,17 +321,15 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     constexpr int REP = TERMS == 3 ? 3 : 1;             // part products per stored fragment
     constexpr int KF = KS / REP;                        // fragment k-steps per row tile
     constexpr int TILE_FRAGS = (TERMS == 6 ? KF / 2 : KF) * 64;         // fragments per row tile
-    // CUT (split operands): the products that decide nearly every arg-max are summed first, (p0,B0) (p0,B1)
+    // FILTER (split operands): the products that decide nearly every arg-max are summed first, (p0,B0) (p0,B1)
     // (p1,B0) of six and p0 and p1 of three; then the small others (of three in a sum of their own, which
-    // is added: the margin is a third).  FILTER: those are left out where the maximum stands clear of the
-    // next value by more than they can change (see filter_margins).  A few rows on six products wait for
-    // latencies, not for matrix instructions: nothing is left out there.  Matrix and vector time add up in
+    // is added: the margin is a third), which are left out where the maximum stands clear of the
+    // next value by more than they can change (see filter_margins).  Matrix and vector time add up in
     // these kernels, and the products were half of it: m = n = 32, K = 16, 2^20 rows 215 -> 171 us, n = 64
     // 376 -> 284; m = 128, n = 256, K = 256, 131072 rows 4120 -> 3200, of which 1 % for the rows that are
     // not clear (0.8 % of the tiles).
-    constexpr bool FILTER = CUT && !(SLICED && TERMS == 6);
     constexpr int MAIN_KF = FILTER && TERMS == 6 ? KF / 2 : KF, MAIN_REP = FILTER && TERMS == 3 ? 2 : REP;
-    static_assert(!CUT || (TERMS > 1 && STAGE_TILES >= TPG && N >= 32), "split operands, whole types per stage");
+    static_assert(!FILTER || (TERMS > 1 && STAGE_TILES >= TPG && N >= 32), "split operands, whole types per stage");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ float red_v[WAVES];
@@ -495,7 +493,7 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
         }
         return l0 + l1;
     };
-    // CUT: one row tile, whose fragments are at `tile`, against one candidate tile, small products and all.
+    // One row tile, whose fragments are at `tile`, against one candidate tile, small products and all.
     auto rest_of = [&](const xreg *xc, const frag *tile, f32x16 r) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = TERMS == 6 ? KF / 2 : 0; s < KF; ++s) r = x_mfma(tile[stored(s) + lane], xc, TERMS == 3 ? 2 * KF + s : s, r);
@@ -1198,7 +1196,7 @@ struct Variant {
     int terms;                   // 1, or the number of part products of the split (3 or 6)
     int mp_base, n, nt, waves, stage_tiles;
     bool at_lds;
-    bool cut;                    // part products are left out where they decide nothing
+    bool cut;                    // part products are left out where they decide nothing (see mfma_filter)
     void (*kernel)(GameView, SweepArgs, int);     // null when `wide` sweeps this packing
     void (*sliced)(GameView, SweepArgs, int);     // one candidate tile per wavefront, types sliced
     Geometry geo;
@@ -1208,10 +1206,11 @@ struct Variant {
     int wide_lds;                                 // its dynamic LDS bytes
 };
 
+// (A few rows on six products wait for latencies, not for matrix instructions: they leave nothing out.)
 #define BSSE_VARIANT(T, MODE, TERMSv, MPB, Nv, NTv, Wv, STv, OCCv, ATL, PFv, CUTv, NAME)             \
     { MODE, TERMSv, MPB, Nv, NTv, Wv, STv, ATL, CUTv,                                                \
       sweep_mfma_kernel<T, MPB * TERMSv, Nv, NTv, Wv, STv, OCCv, ATL, TERMSv, false, PFv, CUTv>,     \
-      sweep_mfma_kernel<T, MPB * TERMSv, Nv, 1, Wv, STv, 1, ATL, TERMSv, true, PFv, CUTv>,           \
+      sweep_mfma_kernel<T, MPB * TERMSv, Nv, 1, Wv, STv, 1, ATL, TERMSv, true, PFv, CUTv && TERMSv != 6>, \
       make_geometry((int)sizeof(T), MPB * TERMSv, Nv, STv, Wv, ATL, TERMSv), NAME, nullptr, nullptr, 0 }
 // A packing that sweep_wide_kernel also takes (one type per stage, leader rows in LDS, NT = 2)
 #define BSSE_VARIANT_WIDE(T, MODE, MPB, Nv, Wv, PFv, NAME)                                           \
@@ -1245,6 +1244,9 @@ const Variant kVariants[] = {
     BSSE_VARIANT(__bf16, 2, 6, 32, 32, 2, 4, 1, 3, true, 0, true, "mfma_split6"),
     BSSE_VARIANT(__bf16, 2, 3, 32, 32, 2, 4, 1, 4, true, 0, true, "mfma_split3"),
     BSSE_VARIANT(__bf16, 2, 6, 32, 64, 2, 4, 2, 2, true, 0, true, "mfma_split6"),
+    // (for games where the small products decide too often; behind those that leave them out)
+    BSSE_VARIANT(__bf16, 2, 6, 32, 32, 2, 4, 1, 3, true, 0, false, "mfma_split6"),
+    BSSE_VARIANT(__bf16, 2, 6, 32, 64, 2, 4, 2, 2, true, 0, false, "mfma_split6"),
     // (one fragment ahead: the next one's LDS read runs under two matrix instructions; two ahead spill)
     BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 1, true, "mfma_split3"),
 };
@@ -1447,10 +1449,8 @@ hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t 
 // comes to 2^-16 of that, and its addition rounds to 2^-24: 2^-23 is taken.  Both payoffs of a difference
 // move: twice all that, and 2 % for the roundings of r, of a_t and of the threshold.  Rows and payoffs so
 // small that parts underflow meet the two least values.
-void filter_margins(int variant, int m, int n, int K, const float *B, float *margin)
+static void filter_margins(const Variant &v, int m, int n, int K, const float *B, float *margin)
 {
-    if (variant < 0 || variant >= kNumVariants || !kVariants[variant].cut) return;
-    const Variant &v = kVariants[variant];
     const int parts = v.terms == 6 ? 3 : 1;
     constexpr int MOST_N = 256;                              // of the variants
     for (int t = 0; t < K; ++t) {
@@ -1480,10 +1480,77 @@ void filter_margins(int variant, int m, int n, int K, const float *B, float *mar
             norm[q] = sqrt(norm[q]);
         }
         const double left_out = parts == 1 ? norm[3] / kScale2 : norm[2] + norm[1] / kScale1 + norm[0] / kScale2;
-                const double rounding = norm[0] * (parts == 1 ? 2 * 0x1p-23 : v.mp_base / 16 * 3 * 0x1p-21);
+        const double rounding = norm[0] * (parts == 1 ? 2 * 0x1p-23 : v.mp_base / 16 * 3 * 0x1p-21);
         const double a = 2 * 1.02 * (left_out + 1.01 * rounding);       // (|x|_2 is within 2^-8 of |p0|_2)
         margin[t] = (float)(a > kLeastMargin ? (a < 0x1p127 ? a : 0x1p127) : kLeastMargin);
     }
+}
+
+// The share of (candidate tile, type) pairs that a filter with these margins sums twice and that would not
+// have been for a tie of equal columns, which every kernel does (and the filter's exact routine looks at the
+// tied candidates only): from the gaps between the greatest two payoffs in 64 pairs of up to eight types and
+// rows of the flat Dirichlet distribution.  A gap is below the margin a sixteenth as often as below sixteen
+// margins, of which 64 pairs show enough.
+static double twice_summed(int m, int n, int K, const float *B, const float *margin)
+{
+    constexpr int PAIRS = 64, MOST_M = 32, MOST_N = 64;
+    const int types = K < 8 ? K : 8, rows = PAIRS / types;
+    float x[PAIRS][MOST_M], norm[PAIRS];
+    uint64_t state = 0;
+    for (int r = 0; r < rows; ++r) {
+        float sum = 0.0f, square = 0.0f;
+        for (int i = 0; i < m; ++i) {
+            uint64_t z = state += 0x9E3779B97F4A7C15ull;                // splitmix64
+            z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+            z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+            x[r][i] = -logf(((float)((z ^ (z >> 31)) >> 41) + 0.5f) * 0x1p-23f);
+            sum += x[r][i]; square += x[r][i] * x[r][i];
+        }
+        for (int i = 0; i < m; ++i) x[r][i] /= sum;
+        norm[r] = sqrtf(square) / sum;
+    }
+    double share = 0.0;
+    for (int q = 0; q < types; ++q) {
+        const int t = (int)((long long)q * K / types);
+        int near = 0, tied = 0;
+        for (int r = 0; r < rows; ++r) {
+            float u[MOST_N] = {}, first = -INFINITY, second = -INFINITY;
+            for (int i = 0; i < m; ++i) {
+                const float *row = B + ((size_t)t * m + i) * n;
+                for (int j = 0; j < n; ++j) u[j] += x[r][i] * row[j];
+            }
+            for (int j = 0; j < n; ++j) {
+                second = u[j] > first ? first : u[j] > second ? u[j] : second;
+                first = u[j] > first ? u[j] : first;
+            }
+            tied += first == second;
+            near += first > second && first - second < 16.0f * norm[r] * margin[t];
+        }
+        const double clear = 1.0 - (double)tied / rows;
+        share += (pow(clear, 32.0) - pow(std::max(0.0, clear - near / 16.0 / rows), 32.0)) / types;
+    }
+    return share;
+}
+
+// The margins grow with the payoffs, the gaps with what tells them apart: payoffs with a large part in common
+// make the filter sum most tiles twice, at the pace of one chain.  From about a quarter of them on, six
+// products sum everything at once (m = n = 32 and n = 64, K = 16, 2^20 rows, normal payoffs plus 0, 10, 30,
+// 100 and 1000, us, filter and whole sums: 182 and 213, 190 and 210, 207 and 210, 259 and 211, 303 and 225; 265
+// and 360, 322 and 356, 378 and 356, 486 and 365, 588 and 385; share 0.01, 0.11, 0.27, 0.65, 1).  Three products
+// have no other variant: payoffs that are bf16 numbers differ by 2^-8 of their size if they differ (whole
+// numbers 248..255 in place of 0..7: 143 -> 150 us, and 443 -> 507 for m = 128, n = 256, where all products at
+// once took 203 and 623).
+int mfma_filter(int variant, int m, int n, int K, const float *B, float *margin)
+{
+    if (variant < 0 || variant >= kNumVariants || !kVariants[variant].cut) return variant;
+    const Variant &v = kVariants[variant];
+    filter_margins(v, m, n, K, B, margin);
+    for (int i = 0; i < kNumVariants; ++i) {
+        const Variant &w = kVariants[i];
+        if (w.mode == v.mode && w.terms == v.terms && w.mp_base == v.mp_base && w.n == v.n && !w.cut)
+            return twice_summed(m, n, K, B, margin) > 0.25 ? i : variant;
+    }
+    return variant;
 }
 
 // Host packing.
