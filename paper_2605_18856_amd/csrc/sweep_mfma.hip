@@ -699,8 +699,14 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
         // look into inline asm: the wait states a vector read of a fresh MFMA result needs (passes
         // + 3: 11 for the 8-pass bf16 MFMA, 19 for the 16-pass fp32 one) are put here explicitly.
         __builtin_amdgcn_sched_barrier(0);
+        // The statements behind it tie the accumulators to the wait: asm that is not volatile moves above
+        // one that names nothing it reads.
         asm volatile("s_nop 15");
         if constexpr (std::is_same<T, float>::value) asm volatile("s_nop 3");
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int tt = 0; tt < TPG; ++tt) asm volatile("" : "+v"(acc[ct][tt]));
         static_for<0, TYPES, 1>([&](auto tic) {
             constexpr int ti = decltype(tic)::value;
             const int t = group * TYPES + ti;
@@ -1051,9 +1057,13 @@ sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
                         float *Vp, long long cbase) __attribute__((always_inline)) {
         // The asm blocks read the accumulators, and the compiler's hazard handling does not look into
         // inline asm: the wait states a vector read of a fresh MFMA result needs (passes + 3 = 11) are
-        // explicit.
+        // explicit, and the accumulators are tied to them.
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_nop 15");
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+            for (int tt = 0; tt < TPG; ++tt) asm volatile("" : "+v"(acc[ct][tt]));
         // stage 1: the maxima of the grid's rows and columns; the lane maximum goes to the partner lane
         typedef ArgGrid<TPG> Grid;
         float R[NT][Grid::ROWS], C[NT][Grid::COLS], pm[NT], pm_other[NT];
