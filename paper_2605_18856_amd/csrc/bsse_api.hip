@@ -378,6 +378,12 @@ long long sweep_blocks(const bsse_game *g, long long count)
     return g->path == PATH_VALU ? valu_num_blocks(count) : mfma_num_blocks(g->view.variant, count);
 }
 
+// Records that `count` candidates or fewer may need uncut (a recorded chunk finds room after a greater one).
+long long sweep_records(const bsse_game *g, long long count)
+{
+    return on_any(g) ? any_max_blocks(g->view, count) : sweep_blocks(g, count);
+}
+
 // A block of handle-owned memory of at least `bytes`; nothing enqueued may still use the old one.
 bsse_status grow_device(bsse_game *g, void **ptr, size_t *cap, size_t bytes)
 {
@@ -1130,7 +1136,7 @@ bsse_status sweep_chunk_impl(bsse_game *g, SweepArgs a)
     } else {
         nblocks = rows ? (count + FINISH_ROWS - 1) / FINISH_ROWS : sweep_blocks(g, count);
         // (enough for the same chunk uncut, as it is recorded)
-        if ((st = ensure_blocks(g, rows ? std::max(nblocks, sweep_blocks(g, count)) : nblocks)) != BSSE_OK) return st;
+        if ((st = ensure_blocks(g, std::max(nblocks, sweep_records(g, count)))) != BSSE_OK) return st;
         if (record && ((st = keep(g, g->w.blk_v)) != BSSE_OK || (st = keep(g, g->w.blk_i)) != BSSE_OK)) return st;
         a.tie_counter = g->w.tie_counter;
         if (rows) {
@@ -1399,7 +1405,7 @@ bsse_status sweep_once(bsse_game *g, const float *X, long long count, bsse_resul
         a.l_out = g->row_l; a.l_sc = 1; a.l_st = count;
         a.br_out = g->row_br; a.br_sc = 1; a.br_st = count;
     } else {
-        if ((st = ensure_blocks(g, any_num_blocks(g->view, count))) != BSSE_OK) return st;
+        if ((st = ensure_blocks(g, any_max_blocks(g->view, count))) != BSSE_OK) return st;
         a.blk_v = g->w.blk_v; a.blk_i = g->w.blk_i;
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1520,7 +1526,7 @@ extern "C" bsse_status bsse_sweep_static(bsse_game *g, const float *candidates_d
     const bool small = on_small_kernel(g);
     // (every vector-path game has the documented limit, also where the short-row kernel needs fewer records)
     const long long records = g->path == PATH_VALU ? valu_num_blocks(count)
-                              : small || on_any(g) || on_tiny(g) ? sweep_blocks(g, count) : mfma_limit_blocks(g->view.variant, count);
+                              : small || on_any(g) || on_tiny(g) ? sweep_records(g, count) : mfma_limit_blocks(g->view.variant, count);
     if (!small && records > STATIC_MAX_BLOCKS)
         return fail(BSSE_EOVERFLOW, "%lld candidates need %lld workgroup records; the static scratch holds %lld "
                     "(sweep in pieces, or use bsse_sweep)", (long long)count, records, STATIC_MAX_BLOCKS);

@@ -206,6 +206,7 @@ hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, vo
 hipError_t any_prepare(const GameView &g);
 const char *any_name(const AnyGeo &q);
 long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an uncut launch
+long long any_max_blocks(const GameView &g, long long count);     // the most that one of up to `count` candidates has
 // Workgroups that share a launch over `count` candidates cut over the types (1: it is not to be cut).
 int any_shares(const GameView &g, long long count);
 long long any_row_blocks(const GameView &g, long long count);       // workgroups of a launch cut like that

@@ -177,11 +177,15 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : 0;
     q.nq = 1; q.lead_off = -1;
     // Two stage buffers per workgroup, and as many workgroups on a compute unit of 160 KiB as the registers
-    // allow: 26 KiB a stage for two or three, 19 for four.  A type that needs up to 36 KiB with its leader
-    // rows still goes in one piece (two workgroups); beyond that the row tiles come in pieces and the leader
-    // column is gathered from L2.
+    // allow: 26 KiB a stage for two or three, 19 for four.  Beyond that the row tiles come in pieces and the
+    // leader column is gathered from L2; but one candidate tile a wavefront and two row tiles a type are too
+    // little to hide a gather of 256 bytes behind: types that need up to 36 KiB with their leader rows go in one
+    // piece there, for two workgroups (us, three and two: m = 120, n = 40, K = 30 bf16, 260000 rows 276 and 206;
+    // m = 100, n = 60, K = 16 bf16 170 and 138; m = 60, n = 40, K = 20, 130000 rows 153 and 126; but m = 45,
+    // n = 60, K = 20 f32, 260000 rows 197 and 210; m = 90, n = 70, K = 20 bf16, 20000 rows 40 and 45).
     const int waves = any_impl::occupancy(terms, q.ks, q.form, true);
-    const int cap = (waves >= 4 ? 19 : 26) * 1024, most = waves >= 3 ? cap : 36 * 1024;
+    const bool gather = any_impl::tiles_per_wave(terms, q.ks, q.form, true) == 1 && n <= 64 && 16 * q.ks * lbytes >= 256;
+    const int cap = (waves >= 4 ? 19 : 26) * 1024, most = waves >= 3 && !gather ? cap : 36 * 1024;
     if (q.form >= 8) {
         q.tpg = 1;
         q.units = (K + 32 / q.form - 1) / (32 / q.form);
@@ -211,7 +215,7 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
         q.buf_bytes = q.stt * q.tile_bytes;
     }
     q.resident = std::max(2, std::min(waves, 160 * 1024 / (2 * q.buf_bytes + 1024)));
-    q.resident_cut = std::min(q.resident, any_impl::occupancy(terms, q.ks, q.form, false));
+    q.resident_cut = terms == 1 ? q.resident : std::min(q.resident, any_impl::occupancy(terms, q.ks, q.form, false));
     return q;
 }
 
@@ -253,10 +257,43 @@ hipError_t any_prepare(const GameView &g)
 
 constexpr int CUS = 256;
 
-static long long rows_per_block(const AnyGeo &q) { return 32LL * any_impl::WAVES * any_impl::tiles_per_wave(q.terms, q.ks); }
+static int tiles_of(const AnyGeo &q, bool many) { return any_impl::tiles_per_wave(q.terms, q.ks, q.form, many); }
+static long long blocks_of(const AnyGeo &q, long long count, bool many)
+{
+    const long long rows = 32LL * any_impl::WAVES * tiles_of(q, many);
+    return (count + rows - 1) / rows;
+}
 
-// Time that `side` workgroups of a compute unit take for a block each, two being one.
-static double round_time(long long side) { return side <= 0 ? 0.0 : side == 1 ? 0.8 : side <= 3 ? 0.4 + 0.3 * side : 1.65; }
+// An uncut launch of `blocks` blocks for three workgroups a compute unit that takes one round of three and
+// a last one of one: two rounds of two are full, and where a wavefront has three parts of a row they are
+// faster (us, 768 workgroups and 512: m = 30, n = 50, K = 20, 210000 rows 144 and 128; m = 60, n = 30, K = 20,
+// 100000 rows 90 and 82; whole numbers, m = 20, n = 140, K = 20, 210000 rows 191 and 179; but m = 16,
+// n = 40, K = 30 bf16, 210000 rows 90 and 100).
+static bool one_left_over(const AnyGeo &q, long long blocks)
+{
+    return q.resident == 3 && q.form < 8 && blocks > 3 * CUS && blocks <= 4 * CUS;
+}
+
+// Which of two kinds of kernel takes a launch (see two_kinds).  Long bf16 rows: the one for two workgroups where
+// one would be left over, as it takes twice the rows in one round (us: m = 96, n = 60, K = 16, 130000 rows 82
+// and 69; m = 128, n = 20, K = 30 99 and 88), and where LDS holds two only (see any_geometry).
+static bool many_kind(const AnyGeo &q, long long count, bool cut)
+{
+    if (!any_impl::two_kinds(q.terms, q.ks, q.form)) return true;
+    if (q.resident < 3 || (cut && q.terms != 1)) return false;
+    const long long blocks = blocks_of(q, count, true);
+    return cut || !(one_left_over(q, blocks) || (q.terms != 1 && blocks <= 2 * CUS));
+}
+
+// Workgroups on a compute unit of an uncut launch.
+static int side_by_side(const AnyGeo &q, long long count)
+{
+    return !many_kind(q, count, false) || (q.terms != 1 && one_left_over(q, blocks_of(q, count, true))) ? 2 : q.resident;
+}
+
+// Time that `side` workgroups of a compute unit take for a block each, two being one.  (One takes no less: it
+// waits for its own loads, and rarely is every unit left with one.)
+static double round_time(long long side) { return side <= 0 ? 0.0 : side <= 2 ? 1.0 : side == 3 ? 1.3 : 1.65; }
 
 long long any_num_blocks(const GameView &g, long long count)
 {
@@ -266,16 +303,21 @@ long long any_num_blocks(const GameView &g, long long count)
     // All the workgroups that the registers allow, not two a compute unit (three or four, us): the same 140000
     // rows 81 -> 70, 1000000 rows 348 -> 281; m = 12, n = 100, K = 30, 100000 rows 101 -> 89; m = 40, n = 80,
     // K = 50, 100000 rows 310 -> 261; m = 20, n = 20, K = 8, 270000 rows 51 -> 45; m = 9, n = 15, K = 20 bf16,
-    // 1000000 rows 96 -> 74; nothing of eleven shapes and eight sizes slower by more than 2 %.
-    const long long blocks = (count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
-    return blocks < 1 ? 1 : std::min<long long>(blocks, CUS * g.any.resident);
+    // 1000000 rows 96 -> 74.
+    const AnyGeo &q = g.any;
+    return std::max(1LL, std::min<long long>(blocks_of(q, count, many_kind(q, count, false)), CUS * side_by_side(q, count)));
+}
+
+long long any_max_blocks(const GameView &g, long long count)
+{
+    return std::max(1LL, std::min<long long>(blocks_of(g.any, count, true), CUS * g.any.resident));
 }
 
 // Workgroups of a launch cut over the types, 1 when it is not to be cut.
 int any_shares(const GameView &g, long long count)
 {
     const AnyGeo &q = g.any;
-    const long long blocks = (count + rows_per_block(q) - 1) / rows_per_block(q), pairs = blocks * q.units;
+    const long long blocks = blocks_of(q, count, many_kind(q, count, true)), pairs = blocks * q.units;
     if (q.units < 2) return 1;
     const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg;
     // Workgroups side by side: the time of a share, which begins with a block's rows (all that are resident,
@@ -295,15 +337,22 @@ int any_shares(const GameView &g, long long count)
     if (q.form >= 8 || (count + FINISH_ROWS - 1) / FINISH_ROWS * (g.m + g.K) > (1LL << 16)) return 1;
     // Otherwise what decides is how full the compute units are.  In units of the time a compute unit takes for
     // two blocks and all types side by side: uncut, the fullest one takes as many rounds as it has blocks for,
-    // and 0.8 (0.6) for a first (a later) one by itself; cut, all take the same, a tenth more for the outputs,
-    // and 12 us for another launch that sums them (the unit is about 0.08 us per type and unit of `work`).
-    // Uncut and cut, us: m = 50, n = 100, K = 24 bf16, 50000 rows (196 blocks) 91 and 60, 70001 rows 100 and
-    // 75, 131072 rows 110 and 122, 160000 rows 176 and 147; m = 30, n = 50, K = 20, 60000 rows 69 and 53,
-    // 100003 rows 75 and 76; m = 16, n = 40, K = 30 bf16, 140000 rows 93 and 84, 270000 rows 130 and 143;
-    // m = 20, n = 20, K = 8, 100000 rows 32 and 36; m = 128, n = 255, K = 4, 30000 rows 88 and 64.
-    const long long all = CUS * q.resident, rest = (blocks % all + CUS - 1) / CUS;
-    const double uncut = blocks / all * round_time(q.resident) + (blocks >= all && rest == 1 ? 0.6 : round_time(rest));
-    const double cut = 12.0 / (0.08 * work * q.units) + 1.1 * round_time(side) * blocks / (CUS * side);
+    // later ones shorter (they start one by one) and one block left over 0.8; cut, all take the same, more for
+    // the outputs where a type is little work, and 12 us for another launch that sums them (the unit is about
+    // 0.09 us per type and unit of `work`).  Uncut and cut, us: m = 50, n = 100, K = 24 bf16, 50000 rows 109 and
+    // 60, 130000 rows 121 and 114; m = 30, n = 50, K = 20, 60000 rows 68 and 53, 100003 rows 74 and 76; m = 70,
+    // n = 100, K = 10 bf16, 30000 rows 58 and 42; m = 20, n = 20, K = 8, 45000 rows 31 and 25; m = 10, n = 20,
+    // K = 30, 200000 rows 66 and 85; m = 60, n = 100, K = 20, whole numbers, 60000 rows 105 and 86; m = 128,
+    // n = 255, K = 4, 30000 rows 90 and 65.  Over 49 shapes and 27 sizes the choice takes 0.7 % longer than the
+    // better one on average, and 18 % at most.
+    const bool many = many_kind(q, count, false);
+    const int tiles = tiles_of(q, many), tiles_cut = tiles_of(q, many_kind(q, count, true)), full = side_by_side(q, count);
+    const long long uncut_blocks = blocks_of(q, count, many), all = CUS * full;
+    const long long sets = uncut_blocks / all, rest = (uncut_blocks % all + CUS - 1) / CUS;
+    const double later = rest == 1 ? 0.8 : 0.82 * round_time(rest);
+    const double rounds = sets == 0 ? round_time(rest) : round_time(full) * (1.0 + 0.82 * (double)(sets - 1)) + later;
+    const double uncut = rounds * (tiles > tiles_cut ? 1.75 : 1.0);            // (twice the rows in a block)
+    const double cut = 12.0 / (0.09 * work * q.units) + (0.94 + 9.0 / work) * round_time(side) * blocks / (CUS * side);
     return cut < 0.95 * uncut ? shares : 1;
 }
 
@@ -316,11 +365,11 @@ long long any_row_blocks(const GameView &g, long long count)
 hipError_t launch_sweep_any(const GameView &g, const SweepArgs &a, int shares, hipStream_t s)
 {
     if (a.count <= 0) return hipSuccess;
-    any_impl::any_kernel_t k = kernel_for(g.any, shares <= 1 && any_num_blocks(g, a.count) > 2 * CUS);
+    const bool many = many_kind(g.any, a.count, shares > 1);
+    any_impl::any_kernel_t k = kernel_for(g.any, many);
     if (!k) return hipErrorNotSupported;
     any_impl::AnyArgs args{ g, a };
-    const long long blocks = (a.count + rows_per_block(g.any) - 1) / rows_per_block(g.any);
-    const long long pairs = blocks * g.any.units;
+    const long long pairs = blocks_of(g.any, a.count, many) * g.any.units;
     if (shares > 1 && (a.V_out || a.blk_v || shares > pairs || pairs > 0x7FFFFFFFLL)) return hipErrorInvalidValue;
     args.a.slice_stages = shares > 1 ? (int)(pairs / shares) : 0;
     const long long nx = shares > 1 ? shares : any_num_blocks(g, a.count);

@@ -41,21 +41,28 @@ typedef void __attribute__((address_space(3))) *lds_ptr;
 
 constexpr int WAVES = 4, THREADS = WAVES * 64;
 
+// Kernels of two kinds, for three workgroups on a compute unit (`many`) and for two: splits with two k-steps,
+// which spill 15 and 25 registers at a block's start with three wavefronts a SIMD, and long bf16 rows, which
+// have one candidate tile a wavefront with three and two with two.  The others have one kernel.
+constexpr bool two_kinds(int terms, int ks, int form)
+{
+    return terms == 1 ? (ks == 6 && form == 0) || (ks == 8 && form < 8) : form == 0 && ks == 2;
+}
 // NT: 32-candidate tiles per wavefront.  Two let one fragment read serve two instructions; with
 // three parts of a long row in registers there is room for one.
-constexpr int tiles_per_wave(int terms, int ks) { return ks <= (terms == 1 ? 4 : 2) ? 2 : 1; }
+constexpr int tiles_per_wave(int terms, int ks, int form, bool many)
+{
+    return ks <= (terms == 1 ? 4 : 2) || (terms == 1 && two_kinds(terms, ks, form) && !many) ? 2 : 1;
+}
 // Wavefronts per SIMD that the register allocation is held to; with one wavefront of every workgroup on each
 // SIMD also the workgroups that a compute unit holds.  These kernels are bound by vector instructions, and a
 // SIMD issues more of them the more wavefronts it chooses from (one, an instruction in 8 cycles; two, in 5.7;
 // four, in 4.9): as many as fit without spilling in the loop over the types (us, 1000000 rows: m = 45,
 // n = 100, K = 24 bf16 587 with two and 442 with three; m = 60, n = 100, K = 20, three products 1039 and 830).
-// `many`: for launches of more than two workgroups a compute unit.  Splits with two k-steps spill 15 and 25
-// registers at a block's start with three (m = 30, n = 50, K = 20: 1000 rows 19.8 us with two, 21.1 with
-// three; 270000 rows 165 and 157).
-constexpr bool spills(int terms, int ks, int form) { return form == 0 && terms != 1 && ks == 2; }
 constexpr int occupancy(int terms, int ks, int form, bool many)
 {
-    if (form == 0) return (terms == 1 || ks <= 4) && (many || !spills(terms, ks, form)) ? 3 : 2;
+    if (two_kinds(terms, ks, form)) return many ? 3 : 2;
+    if (form == 0) return terms == 1 || ks <= 4 ? 3 : 2;
     if (form == 1) return terms == 1 ? (ks <= 4 ? 4 : 3) : ks == 1 ? 4 : ks <= 4 ? 3 : 2;
     return terms == 1 ? (ks <= 2 ? 4 : 3) : ks == 3 ? 4 : ks <= 4 ? 3 : 2;
 }
@@ -204,7 +211,7 @@ __device__ __forceinline__ late_args late()
 template <int TERMS, int KS, int FORM, bool MANY>
 __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) sweep_any_kernel(AnyArgs args)
 {
-    constexpr int NT = tiles_per_wave(TERMS, KS);
+    constexpr int NT = tiles_per_wave(TERMS, KS, FORM, MANY);
     constexpr int XP = TERMS == 1 ? 1 : 3;               // parts of a candidate component
     constexpr int PA = TERMS == 6 ? 3 : 1;               // parts of a payoff
     constexpr int HALF = 8 * KS;                         // leader actions per lane half
@@ -851,8 +858,8 @@ template <int TERMS, int KS>
 any_kernel_t any_kernel_form(int form, bool many)
 {
     switch (form) {
-    case 0: return many ? sweep_any_kernel<TERMS, KS, 0, true> : sweep_any_kernel<TERMS, KS, 0, !spills(TERMS, KS, 0)>;
-    case 1: return sweep_any_kernel<TERMS, KS, 1, true>;
+    case 0: return many ? sweep_any_kernel<TERMS, KS, 0, true> : sweep_any_kernel<TERMS, KS, 0, !two_kinds(TERMS, KS, 0)>;
+    case 1: return many ? sweep_any_kernel<TERMS, KS, 1, true> : sweep_any_kernel<TERMS, KS, 1, !two_kinds(TERMS, KS, 1)>;
     case 8: return sweep_any_kernel<TERMS, KS, 8, true>;
     case 16: return sweep_any_kernel<TERMS, KS, 16, true>;
     }
