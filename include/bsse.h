@@ -168,9 +168,10 @@ bsse_status bsse_sweep(bsse_game *g, const float *candidates_dev, int64_t count,
  * a static device array of 3.2 MiB that each GPU the library runs on holds until the process ends;
  * the call performs no hipMalloc / hipHostMalloc / hipFree and creates no stream or event.
  * candidates_dev must be given (not NULL).  Limits: the chunk may need at most 65536 workgroup
- * records (2^24 candidates on the matrix-core paths with 256 candidates per workgroup, 2^22 on
- * the plain vector path; the small-game kernel has no such limit); more is BSSE_EOVERFLOW, with
- * nothing enqueued.  All calls on one GPU share that GPU's array: calls that overlap in time on
+ * records: 2^22 candidates on the plain vector path; on the matrix-core paths 2^24, but 2^25 where
+ * n <= 32 with bf16 storage or BSSE_PATH_MFMA, and where n = 32 with payoffs that are bf16 numbers, and
+ * 2^26 for bf16 storage with n = 128 and m <= 64; the small-game kernel and shapes without a kernel of
+ * their own have no such limit.  More is BSSE_EOVERFLOW, with nothing enqueued.  All calls on one GPU share that GPU's array: calls that overlap in time on
  * one GPU (two handles, two streams, two threads) race on it and must be serialised by the
  * caller.  Kernel timing (bsse_set_timing) does not cover this call.  Like bsse_sweep it resets
  * the handle's streamed sweep; afterwards there is no result to polish (bsse_polish: BSSE_ESTATE). */

@@ -45,11 +45,6 @@ __device__ __forceinline__ float pair_max(float v)
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return vmax2(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-__device__ __forceinline__ int pair_min(int v)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
-    return min((int)r[0], (int)r[1]);
-}
 // The partner lane's value, through the LDS crossbar (no LDS memory is touched): this keeps
 // the exchange off the vector ALU, where a swap costs two copies, the swap and a select.
 // partner_addr = 4 * (lane ^ 32).
@@ -140,55 +135,6 @@ __device__ __forceinline__ void split_parts(const f32x4 &x, unsigned (&p12)[4], 
     rest(p12[2], r[0], r[1], q[0], q[1]); rest(p12[3], r[2], r[3], q[2], q[3]);
     p31[0] = pack(q[0], q[1]); p31[1] = pack(q[2], q[3]);
     p31[2] = p12[0]; p31[3] = p12[1];
-}
-
-// Eight values and their maximum g: idx = the lowest position that holds g, n_eq = how many
-// (lane, position) pairs of the wavefront hold g (64 exactly when every lane has one maximiser).
-// Every compare mask lives in a scalar register pair (a select fed by vcc issues several times
-// slower on this part), the position is a chain of selects between inline constants from the
-// highest position down, and the count is taken on the scalar unit.  Each select stands at least
-// two instructions behind its compare.
-__device__ __forceinline__ void argmax8(float u0, float u1, float u2, float u3, float u4, float u5,
-                                        float u6, float u7, float g, unsigned &idx, unsigned &n_eq)
-{
-    unsigned long long m0, m1, m2, m3, m4, m5, m6, m7;
-    unsigned i, c, t;
-    asm("v_cmp_eq_f32 %[m6], %[u6], %[g]\n\t"
-        "v_cmp_eq_f32 %[m5], %[u5], %[g]\n\t"
-        "v_cmp_eq_f32 %[m4], %[u4], %[g]\n\t"
-        "v_cmp_eq_f32 %[m3], %[u3], %[g]\n\t"
-        "v_cmp_eq_f32 %[m2], %[u2], %[g]\n\t"
-        "v_cmp_eq_f32 %[m1], %[u1], %[g]\n\t"
-        "v_cmp_eq_f32 %[m0], %[u0], %[g]\n\t"
-        "v_cmp_eq_f32 %[m7], %[u7], %[g]\n\t"
-        "v_cndmask_b32 %[i], 7, 6, %[m6]\n\t"
-        "v_cndmask_b32 %[i], %[i], 5, %[m5]\n\t"
-        "v_cndmask_b32 %[i], %[i], 4, %[m4]\n\t"
-        "v_cndmask_b32 %[i], %[i], 3, %[m3]\n\t"
-        "v_cndmask_b32 %[i], %[i], 2, %[m2]\n\t"
-        "v_cndmask_b32 %[i], %[i], 1, %[m1]\n\t"
-        "v_cndmask_b32 %[i], %[i], 0, %[m0]\n\t"
-        "s_bcnt1_i32_b64 %[c], %[m0]\n\t"
-        "s_bcnt1_i32_b64 %[t], %[m1]\n\t"
-        "s_add_u32 %[c], %[c], %[t]\n\t"
-        "s_bcnt1_i32_b64 %[t], %[m2]\n\t"
-        "s_add_u32 %[c], %[c], %[t]\n\t"
-        "s_bcnt1_i32_b64 %[t], %[m3]\n\t"
-        "s_add_u32 %[c], %[c], %[t]\n\t"
-        "s_bcnt1_i32_b64 %[t], %[m4]\n\t"
-        "s_add_u32 %[c], %[c], %[t]\n\t"
-        "s_bcnt1_i32_b64 %[t], %[m5]\n\t"
-        "s_add_u32 %[c], %[c], %[t]\n\t"
-        "s_bcnt1_i32_b64 %[t], %[m6]\n\t"
-        "s_add_u32 %[c], %[c], %[t]\n\t"
-        "s_bcnt1_i32_b64 %[t], %[m7]\n\t"
-        "s_add_u32 %[c], %[c], %[t]"
-        : [i] "=&v"(i), [c] "=&s"(c), [t] "=&s"(t), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2),
-          [m3] "=&s"(m3), [m4] "=&s"(m4), [m5] "=&s"(m5), [m6] "=&s"(m6), [m7] "=&s"(m7)
-        : [u0] "v"(u0), [u1] "v"(u1), [u2] "v"(u2), [u3] "v"(u3), [u4] "v"(u4), [u5] "v"(u5),
-          [u6] "v"(u6), [u7] "v"(u7), [g] "v"(g)
-        : "scc");
-    idx = i; n_eq = c;
 }
 
 // Eight follower payoffs u with their maximum g, and the eight leader payoffs w beside them:
@@ -284,20 +230,6 @@ template <int N> __device__ __forceinline__ void keep_greater_rows(float v, unsi
             : [bv] "+v"(bv), [bc] "+v"(bc), [b0] "+v"(br[0]), [b1] "+v"(br[1]), [b2] "+v"(br[2]), [b3] "+v"(br[3]), [m] "=&s"(m)
             : [v] "v"(v), [c] "v"(c), [r0] "v"(r[0]), [r1] "v"(r[1]), [r2] "v"(r[2]), [r3] "v"(r[3]));
 #undef BSSE_KEEP
-}
-
-// (bv, bc, bp) <- (v, c, p) in the lanes where v > bv; the mask in a scalar register pair.
-__device__ __forceinline__ void keep_greater(float v, unsigned c, unsigned p, float &bv, unsigned &bc,
-                                             unsigned &bp)
-{
-    unsigned long long m;
-    asm("v_cmp_gt_f32 %[m], %[v], %[bv]\n\t"
-        "s_nop 1\n\t"
-        "v_cndmask_b32 %[bv], %[bv], %[v], %[m]\n\t"
-        "v_cndmask_b32 %[bc], %[bc], %[c], %[m]\n\t"
-        "v_cndmask_b32 %[bp], %[bp], %[p], %[m]"
-        : [bv] "+v"(bv), [bc] "+v"(bc), [bp] "+v"(bp), [m] "=&s"(m)
-        : [v] "v"(v), [c] "v"(c), [p] "v"(p));
 }
 
 // number of leading zero bits; 0xFFFFFFFF for zero

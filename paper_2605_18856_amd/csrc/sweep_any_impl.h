@@ -6,11 +6,12 @@
 //   * The follower actions of a type are padded to whole row tiles.  A padded row never wins: its
 //     accumulator starts at minus infinity (the C operand of the tile's first instruction) and its
 //     payoffs are zero.
-//   * FORM 0 (n > 32) walks the row tiles of a type two at a time and keeps, per lane, the running
-//     maximum with its tile and the running element-wise maximum over the tiles; when the type is
-//     done the latter says which of the sixteen positions holds the maximum.  Nothing depends on the
-//     number of tiles, so registers do not grow with n.
-//   * FORM 1 (16 < n <= 32) is the same with one tile per type.
+//   * FORM 0 (n > 32) walks the row tiles of a type, one or two at a time (PAIRS), and keeps, per lane,
+//     the eight column maxima of the tiles' grid over all of them and, for the tile or pair that holds
+//     the running maximum, its number and its two or four row maxima; when the type is done a bit for
+//     each that reaches the maximum names the action (unit_map).  Nothing depends on the number of
+//     tiles, so registers do not grow with n.
+//   * FORM 1 (16 < n <= 32) has one tile per type, a grid of four by four.
 //   * FORM 8 and FORM 16 (n <= 8, n <= 16) put four or two whole types into one row tile, the rows
 //     permuted so that each lane holds every action of its types: no exchange is needed to find the
 //     best response.  The leader payoffs of all the actions come off the matrix cores too and the one

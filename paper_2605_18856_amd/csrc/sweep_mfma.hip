@@ -17,12 +17,12 @@
 // per-lane fragment order, so staging a row tile into LDS is a flat copy and the operand
 // reads are conflict-free.
 //
-// Ties.  The accumulators of a whole type stay in registers; the arg-max is a max3 chain, one
-// exchange with the partner lane, then a compare pass whose sum carries both the maximising
-// action and the number of maximisers.  Anything other than one maximiser per candidate sends
-// the wavefront through an exact routine for that type, which recomputes the same MFMA tiles
-// (bit-identical) and walks the exact maximisers in ascending action order comparing leader
-// payoffs.
+// Ties.  The accumulators of a whole type stay in registers.  With n >= 32 the arg-max comes from the maxima
+// of the rows and columns of a grid of them (ArgGrid), with fewer actions from a max3 chain, one exchange
+// with the partner lane and a compare pass whose sum carries the maximising action and the number of
+// maximisers.  Anything other than one maximiser per candidate sends the wavefront through an exact
+// routine for that type, which recomputes the same MFMA tiles (bit-identical) and walks the exact
+// maximisers in ascending action order comparing leader payoffs.
 #include "bsse_internal.h"
 #include <algorithm>
 #include "mfma_device.h"
@@ -285,12 +285,14 @@ constexpr float kScale1 = 0x1p9f, kScale2 = 0x1p18f, kLeastNorm = 0x1p-30f, kLea
 //
 // A "group" is the set of row tiles that holds whole types: N/32 tiles of one type when
 // N >= 32, one tile of 32/N types otherwise.  The accumulators of a whole group stay in
-// registers (N/2 per lane and candidate tile when N >= 32), so the arg-max is two passes
-// over registers: a max3 chain for the lane's maximum, one exchange with the partner lane
-// for the pair's maximum, then a compare pass that adds (action + 2^16) for every register
-// equal to the maximum: the sum carries the maximising action and the number of maximisers.
-// Anything other than one maximiser per candidate means an exact tie somewhere in the tile
-// and sends the wavefront through the exact routine for that type.
+// registers (N/2 per lane and candidate tile when N >= 32), so the arg-max is passes over
+// registers.  N >= 32: the maxima of a grid's rows and columns, one exchange with the partner
+// lane for the pair's maximum, then a bit for each row and column that reaches it, both lanes'
+// (grid_map).  N < 32: a max3 chain and the exchange, then a compare pass that adds
+// (action + 2^16) for every register equal to the maximum: the sum carries the maximising action
+// and the number of maximisers.  Anything other than one maximiser per candidate means an exact
+// tie somewhere in the tile (FILTER: or values too near each other, which settle sums whole
+// first) and sends the wavefront through the exact routine for that type.
 //
 // Stages are double-buffered: the copy of stage s+1 is issued (asynchronously, straight into
 // LDS) before the work on stage s and awaited after it, one workgroup barrier per stage.
@@ -887,12 +889,12 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
 // and the copies issued one type ago have landed, so a copy has a whole type to arrive.
 // Epilogue: both candidate tiles of a pair advance together, stage by stage, so that every
 // exchange with the partner lane (through the LDS crossbar) and every gather is in flight while
-// the other tile's vector work is issued: per-tile lane maxima (which row tile holds the maximum)
-// and element-wise maxima across the row tiles (which register position holds it); a unique
-// maximiser is one tile and one position, anything else goes to the exact routine.  Arithmetic,
-// operand order, packing and the exact-tie routine are those of sweep_mfma_kernel: the same bits
-// per candidate.
-// FULL: rows of MP components; shorter ones have a kernel of their own.
+// the other tile's vector work is issued: the maxima of the grid's rows and columns, the map of
+// those that hold the pair's maximum, the leader column at its two bits; anything but two bits
+// goes to the exact routine.  Arithmetic, operand order, packing and the exact-tie routine are
+// those of sweep_mfma_kernel: the same bits per candidate.
+// FULL: rows of MP components; shorter ones have a kernel of their own (two registers of it are
+// spilled where it loads its rows, none in the loop over the types).
 template <typename T, int MP, int N, int WAVES, int PF, bool FULL>
 __global__ void __launch_bounds__(WAVES * 64, 2)
 sweep_wide_kernel(GameView g, SweepArgs a, int row_tiles)
@@ -1257,7 +1259,8 @@ const Variant kVariants[] = {
     // (for games where the small products decide too often; behind those that leave them out)
     BSSE_VARIANT(__bf16, 2, 6, 32, 32, 2, 4, 1, 3, true, 0, false, "mfma_split6"),
     BSSE_VARIANT(__bf16, 2, 6, 32, 64, 2, 4, 2, 2, true, 0, false, "mfma_split6"),
-    // (one fragment ahead: the next one's LDS read runs under two matrix instructions; two ahead spill)
+    // (one fragment ahead: the next one's LDS read runs under two matrix instructions; two ahead spill.  Six
+    // registers are spilled as it is, three read back per type, and four of m = n = 32 with three products)
     BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 1, true, "mfma_split3"),
 };
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
@@ -1377,11 +1380,14 @@ long long mfma_row_blocks(const GameView &g, long long count)
 // the chip, the same rows spread over types finish sooner, although one candidate tile per wavefront reads
 // every fragment for 32 candidates only.  Workgroups of four wavefronts: up to 512 of them with one candidate
 // tile each (40000 rows, us, whole and cut: m = n = 32, K = 16 39 and 30; n = 64 48 and 36; three products
-// 40 and 25; m = 16, n = 32 bf16 29 and 21; m = n = 16 30 and 23; 100000 rows 43 and 52).  Of eight: fewer whole
-// workgroups than half the compute units, or where that is less time: the wide kernel takes its four candidate
-// tiles in that of 2.5 here, and a type takes about n (0.0104 + 3.3e-5 terms m) us (us, whole or uncut in
-// slices, and now: m = 64, n = 128, K = 64 bf16, 66000 rows 204 and 152; m = 128, n = 256, K = 100, 66000 rows
-// 1187 and 829, 140000 rows 1859 and 1528).
+// 40 and 25; m = 16, n = 32 bf16 29 and 21; m = n = 16 30 and 23; 100000 rows 43 and 52).  With K = 2 to 128 and
+// 1000 to 200000 rows that is within 4 % of the better one, but for n = 64 and K = 64 or more (50000 rows, K = 64
+// 110 and 123, K = 128 198 and 226).  Of eight: fewer whole workgroups than half the compute units, or where
+// that is less time: the wide kernel takes its four candidate tiles in that of 2.5 here, and a type takes about
+// n (0.0104 + 3.3e-5 terms m) us, a fit to times with the small products left out, in which `terms` counts
+// them (us, whole or uncut in slices, and now: m = 64, n = 128, K = 64 bf16, 66000 rows 204 and 152; m = 128,
+// n = 256, K = 100, 66000 rows 1187 and 829, 140000 rows 1859 and 1528; with fewer types the fit asks too much of
+// the cut: K = 16, 40000 rows 132 whole, as it goes, and 106).
 bool mfma_few_rows(const GameView &g, long long count)
 {
     if (g.variant < 0 || g.variant >= kNumVariants) return false;
