@@ -43,7 +43,8 @@ def test_few_and_many_rows_and_ties_agree(m, n):
 @pytest.mark.parametrize("n, most", [(32, 1.45), (64, 1.75)])
 def test_time(n, most):
     """All products at once cost 1.2 (n = 32) and 1.45 (n = 64) of leaving the small ones out; leaving them out
-    and summing most tiles again 1.67 and 2.2.  One type of sixteen with an offset changes nothing."""
+    and summing most tiles again 1.67 and 2.2.  One type of sixteen with an offset leaves the game its filter: a
+    sixteenth of that, 1.1 at most."""
     def best_time(offset, types=slice(None)):
         with _make(_offset_game(32, n, 16, offset, types)) as g:
             X = _torch().empty((1 << 20, 32), dtype=_torch().float32, device="cuda")
@@ -56,4 +57,4 @@ def test_time(n, most):
             return min(times)
     plain = best_time(0)
     assert best_time(1000) < most * plain
-    assert best_time(1000, slice(0, 1)) < 1.15 * plain
+    assert best_time(1000, slice(0, 1)) < 1.3 * plain
