@@ -698,10 +698,12 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     if (!g) return fail(BSSE_ENOMEM, "host allocation failed");
     g->m = m; g->n = n; g->K = K; g->storage = opt->storage; g->device = dev;
     g->path = path;
+    bool half = false;
     try {
         g->hA.assign(A, A + elems); g->hB.assign(B, B + elems); g->hprior.assign(prior, prior + K);
         g->hprior.resize((size_t)2 * K, 0.0f);          // (the filter's margins behind it)
         if (use_mfma) variant = mfma_filter(variant, m, n, K, B, g->hprior.data() + K);
+        half = variant == kAnyVariant && !bf && !exact && any_half_suits(m, n, K, B);
         g->won_x.resize((size_t)m); g->won_br.resize((size_t)K);
     } catch (...) { delete g; return fail(BSSE_ENOMEM, "host allocation failed"); }
     g->view.variant = variant;
@@ -753,18 +755,19 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         g->view.m_pad = tiny ? tiny : m; g->view.n_pad = n;
         if (use_mfma && variant == kAnyVariant) {
             // packed on the device from the payoffs as given
-            g->view.any = any_geometry(m, n, K, bf ? 1 : exact ? 3 : 6);
+            g->view.any = any_geometry(m, n, K, bf ? 1 : exact ? 3 : half ? 2 : 6);
             size_t bb = 0, ab = 0;
             any_pack_sizes(g->view, &bb, &ab);
-            float *rawA = nullptr, *rawB = nullptr;
+            float *rawA = nullptr, *rawB = nullptr, *scale = nullptr;
             st = up((void **)&rawA, A, elems * 4);
             if (st == BSSE_OK) st = up((void **)&rawB, B, elems * 4);
             hipError_t pe = hipSuccess;
-            if (st == BSSE_OK && (pe = hipMalloc(&g->dBpack, bb)) == hipSuccess && (pe = hipMalloc(&g->dATpack, ab)) == hipSuccess &&
-                (pe = launch_any_pack(g->view, rawA, rawB, g->dBpack, g->dATpack, nullptr)) == hipSuccess &&
+            if (st == BSSE_OK && half) pe = hipMalloc((void **)&scale, (size_t)K * 4);
+            if (st == BSSE_OK && pe == hipSuccess && (pe = hipMalloc(&g->dBpack, bb)) == hipSuccess && (pe = hipMalloc(&g->dATpack, ab)) == hipSuccess &&
+                (pe = launch_any_pack(g->view, rawA, rawB, g->dBpack, g->dATpack, g->dprior + K, scale, nullptr)) == hipSuccess &&
                 (pe = hipStreamSynchronize(nullptr)) == hipSuccess)
                 pe = any_prepare(g->view);
-            (void)hipFree(rawA); (void)hipFree(rawB);
+            (void)hipFree(rawA); (void)hipFree(rawB); (void)hipFree(scale);
             if (st == BSSE_OK && pe != hipSuccess)
                 st = fail(pe == hipErrorOutOfMemory ? BSSE_ENOMEM : BSSE_EDEVICE, "packing: %s", hipGetErrorString(pe));
             if (st != BSSE_OK) break;

@@ -2,13 +2,14 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <functional>
 
 namespace bsse {
 
 // Record geometry of the any-shape matrix-core kernel (see sweep_any_impl.h).  A unit is one type
 // (form 0: n > 32, form 1: n > 16) or one row tile of several types (form 8, 16: n <= 8, n <= 16).
 struct AnyGeo {
-    int terms;            // 1, 3 or 6 part products
+    int terms;            // 1, 3 or 6 part products of bf16 parts; 2: three of half-precision parts
     int ks;               // k-steps of 16 leader actions
     int form;
     int tpg;              // row tiles per type (forms 0 and 1)
@@ -22,6 +23,7 @@ struct AnyGeo {
     int buf_bytes;        // one of the two stage buffers
     int resident;         // workgroups that a compute unit holds
     int resident_cut;     // the same of the kernel for launches cut over the types
+    size_t exact_off;     // terms 2: offset in Bpack of the payoffs' bf16 parts, [type][row tile][k-step][part][lane]
 };
 
 // Device view of one game, passed to kernels by value.  All pointers are device memory
@@ -187,6 +189,10 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
 // that sweeps this game: the one without a filter where that is the faster one.
 int mfma_filter(int variant, int m, int n, int K, const float *B, float *margin);
 
+// The share of (candidate tile, type) pairs that a filter with margin(t) sums twice, from `pairs` (8 to 64) pairs of
+// types and rows (see sweep_mfma.hip).
+double twice_summed(int m, int n, int K, const float *B, const std::function<float(int)> &margin, int pairs);
+
 // Small-game matrix-core kernel (n = 8, m = 8, K in {4, 8, 12, 16}, fp32); part of the MFMA path.
 bool small_supported(int m, int n, int K, int storage);
 long long small_num_blocks(long long count);
@@ -202,7 +208,11 @@ bool any_supported(int m, int n);
 AnyGeo any_geometry(int m, int n, int K, int terms);
 void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes);
 // Fragments and leader rows from the payoffs as given to create (device, fp32 [K][m][n]).
-hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, hipStream_t s);
+// terms 2: also the filter's margins, into margin [K], and the payoffs' scales [K] (scratch).
+hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, float *margin,
+                           float *scale, hipStream_t s);
+// Whether an fp32 game of this shape is swept in half-precision parts (terms 2).
+bool any_half_suits(int m, int n, int K, const float *B);
 hipError_t any_prepare(const GameView &g);
 const char *any_name(const AnyGeo &q);
 long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an uncut launch

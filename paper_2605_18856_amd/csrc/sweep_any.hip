@@ -4,6 +4,7 @@
 #include "sweep_any_impl.h"
 #include <algorithm>
 #include <cmath>
+#include <vector>
 #include "done_device.h"
 
 namespace bsse {
@@ -11,16 +12,28 @@ namespace bsse {
 any_impl::any_kernel_t any_kernel_terms1(int ks, int form, bool many);
 any_impl::any_kernel_t any_kernel_terms3(int ks, int form, bool many);
 any_impl::any_kernel_t any_kernel_terms6(int ks, int form, bool many);
+any_impl::any_kernel_t any_kernel_half(int ks, int form);
 
 namespace {
 
 using any_impl::THREADS;
 
 int roundup(int v, int to) { return (v + to - 1) / to * to; }
+int payoff_parts(int terms) { return terms == 6 ? 3 : terms == 2 ? 2 : 1; }
+int products(const AnyGeo &q) { return q.terms != 2 ? q.terms : q.ks == 3 ? 4 : 3; }
+
+// Two half-precision parts leave up to 2^-25 of a number whose second part is subnormal: of components and payoffs
+// below 2^-16 of the greatest of their row or type, which is scaled to 2^14 to 2^15.  In a difference of two sums that is
+// 2^-24 sqrt(m) (|x|_2 + |B_j|_2) at most, and with both norms at least 2^14 no more than this times |x|_2 |B_j|_2.
+// 2 % for the roundings of norms and threshold.
+float half_margin(int ks) { return (float)(1.02 * 0x1p-37 * std::sqrt(16.0 * ks)); }
+// Payoffs from here on may have infinite sums, which the filter's scaled ones would not show.
+constexpr float kHalfMost = 0x1p60f;
 
 any_impl::any_kernel_t kernel_for(const AnyGeo &q, bool many)
 {
     return q.terms == 1   ? any_kernel_terms1(q.ks, q.form, many)
+           : q.terms == 2 ? any_kernel_half(q.ks, q.form)
            : q.terms == 3 ? any_kernel_terms3(q.ks, q.form, many)
                           : any_kernel_terms6(q.ks, q.form, many);
 }
@@ -37,17 +50,71 @@ __device__ __forceinline__ unsigned bf16_part(float v, int p)
     }
 }
 
+// terms 2, one workgroup per type: the power of two that brings the greatest payoff to 2^14, and the margin of
+// the sums' filter.
+__global__ void __launch_bounds__(256)
+any_margin_kernel(int m, int n, float relative, const float *__restrict__ B, float *__restrict__ scale, float *__restrict__ margin)
+{
+    __shared__ float part[2][4];
+    const int t = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const float *Bt = B + (size_t)t * m * n;
+    auto greatest = [&](float v, int which) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) v = fmaxf(v, __shfl_xor(v, d, 64));
+        if (lane == 0) part[which][wave] = v;
+        __syncthreads();
+        return fmaxf(fmaxf(part[which][0], part[which][1]), fmaxf(part[which][2], part[which][3]));
+    };
+    float most = 0.0f;
+    for (int e = tid; e < m * n; e += 256) most = fmaxf(most, fabsf(Bt[e]));
+    most = greatest(most, 0);
+    const float s = most > 0.0f ? ldexpf(1.0f, 14 - ilogbf(most)) : 1.0f;
+    float norm = 0.0f;
+    for (int j = tid; j < n; j += 256) {
+        float sum = 0.0f;
+        for (int i = 0; i < m; ++i) {
+            const float b = Bt[(size_t)i * n + j] * s;
+            sum = fmaf(b, b, sum);
+        }
+        norm = fmaxf(norm, sum);
+    }
+    norm = greatest(norm, 1);
+    if (tid == 0) {
+        scale[t] = s;
+        margin[t] = most < kHalfMost ? relative * sqrtf(norm) : INFINITY;
+    }
+}
+
 // One thread per 16-byte piece of the records: eight k-slots of a fragment, or four (fp32) or eight
 // (bf16) entries of a leader row.  Runs once per game; the reads are strided by n but the payoffs fit
 // the caches.
+__device__ __forceinline__ unsigned half_part(float v, int p)
+{
+    const _Float16 first = (_Float16)v, part = p ? (_Float16)(v - (float)first) : first;
+    return __builtin_bit_cast(unsigned short, part);
+}
 __global__ void __launch_bounds__(256)
 any_pack_kernel(AnyGeo q, int m, int n, int K, const float *__restrict__ A, const float *__restrict__ B,
-                uint4 *__restrict__ Bpack, size_t pieces)
+                const float *__restrict__ scale, uint4 *__restrict__ Bpack, size_t pieces)
 {
-    const int parts = q.terms == 6 ? 3 : 1, half = 8 * q.ks;
+    const int parts = q.terms == 6 ? 3 : q.terms == 2 ? 2 : 1, half = 8 * q.ks;
     const int rec16 = q.rec_bytes / 16, frag16 = q.form >= 8 ? 2 * parts * q.ks * 64 : q.tpg * parts * q.ks * 64;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < pieces; p += stride) {
+        if (q.terms == 2 && p >= q.exact_off / 16) {      // terms 2: the bf16 parts behind the records
+            const size_t o = p - q.exact_off / 16;
+            const int lane = (int)(o % 64), part = (int)(o / 64 % 3), s = (int)(o / 192 % q.ks);
+            const size_t gt = o / (192 * q.ks);
+            const int t = (int)(gt / q.tpg), j = (int)(gt % q.tpg) * 32 + lane % 32;
+            unsigned e[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
+            if (j < n)
+                for (int k = 0; k < 8; ++k) {
+                    const int i = lane / 32 * half + 8 * s + k;
+                    if (i < m) e[k] = bf16_part(B[((size_t)t * m + i) * n + j], part);
+                }
+            Bpack[p] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+            continue;
+        }
         const int u = (int)(p / rec16), o = (int)(p % rec16);
         unsigned e[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
         uint4 out = make_uint4(0u, 0u, 0u, 0u);
@@ -69,7 +136,9 @@ any_pack_kernel(AnyGeo q, int m, int n, int K, const float *__restrict__ A, cons
             if (j < n)
                 for (int k = 0; k < 8; ++k) {
                     const int i = hh * half + 8 * s + k;
-                    if (i < m) e[k] = bf16_part(P[((size_t)t * m + i) * n + j], part);
+                    if (i >= m) continue;
+                    const float v = P[((size_t)t * m + i) * n + j];
+                    e[k] = q.terms == 2 ? half_part(v * scale[t], part) : bf16_part(v, part);
                 }
             out = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
         } else if (q.lead_off >= 0 && o >= q.lead_off / 16) {
@@ -161,6 +230,44 @@ hipError_t launch_finish_rows(const FinishRowsArgs &f, hipStream_t s)
     return hipGetLastError();
 }
 
+// The margin of one type, as any_margin_kernel forms it, in the payoffs' own units.
+static float half_margin_of(int m, int n, int ks, const float *B)
+{
+    std::vector<double> sum((size_t)n, 0.0);
+    float most = 0.0f;
+    for (int i = 0; i < m; ++i)
+        for (int j = 0; j < n; ++j) {
+            const float b = B[(size_t)i * n + j];
+            sum[j] += (double)b * b;
+            most = std::max(most, std::fabs(b));
+        }
+    return most < kHalfMost ? (float)(half_margin(ks) * std::sqrt(*std::max_element(sum.begin(), sum.end()))) : INFINITY;
+}
+
+// Two half-precision parts hold 22 bits of a number or more, and fewer products of them come closer to the true sum
+// than six of bf16 parts, because fewer matrix instructions round: with the small products first only the last
+// k-steps do at the sum's size.  Root mean square and greatest error against 64 bits, in 2^-24 of the sum of the
+// absolute terms, six products and these (flat rows, normal payoffs): m = 33 0.41 and 3.6, four products 0.39 and
+// 2.4 (three 0.45); m = 49 0.43 and 3.7, three products 0.39 and 2.6; m = 64 0.40 and 3.6, 0.35 and 2.1; m = 128
+// 0.43 and 4.0, 0.28 and 1.8; payoffs in 0..1 m = 48 1.21 and 5.5, 0.72 and 3.0; m = 128 2.10 and 9.3, 1.01 and 4.7.
+// Up to 32 leader actions what the parts leave counts for more (m = 24 0.34 and 2.8, four products 0.43 and 2.8).
+// What the parts lose outright, and ties, go back to six products (half_margin, exact_columns).
+// Sixteen follower actions or fewer take their leader payoffs off the matrix cores, which nothing watches.
+// Payoffs of very different sizes (forbidden actions at -10^6) put many values within the margin, and whole numbers
+// beyond 2^22 have ties that 22 bits may not show: six products.
+bool any_half_suits(int m, int n, int K, const float *B)
+{
+    if (m <= 32 || n <= 16 || !any_supported(m, n)) return false;
+    bool whole = true, large = false;
+    for (size_t e = 0; e < (size_t)K * m * n && whole; ++e) {
+        whole = std::rint(B[e]) == B[e];
+        large |= std::fabs(B[e]) > 0x1p22f;
+    }
+    if (whole && large) return false;
+    const int ks = any_geometry(m, n, K, 2).ks;
+    return twice_summed(m, n, K, B, [=](int t) { return half_margin_of(m, n, ks, B + (size_t)t * m * n); }, 16) <= 0.25;
+}
+
 bool any_supported(int m, int n) { return m <= 128 && (long long)m * n > 64; }
 
 AnyGeo any_geometry(int m, int n, int K, int terms)
@@ -172,7 +279,7 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     for (int k : steps)
         if (16 * k >= m) { q.ks = k; break; }
     if (terms == 3 && q.ks != 2 && q.ks != 4) q.ks = q.ks == 1 ? 2 : q.ks == 3 ? 4 : 8;      // (fewer instantiations)
-    const int parts = terms == 6 ? 3 : 1, lbytes = terms == 1 ? 2 : 4;
+    const int parts = payoff_parts(terms), lbytes = terms == 1 ? 2 : 4;
     q.tile_bytes = parts * q.ks * 1024;
     q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : 0;
     q.nq = 1; q.lead_off = -1;
@@ -214,6 +321,7 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     } else {
         q.buf_bytes = q.stt * q.tile_bytes;
     }
+    if (terms == 2) q.exact_off = (size_t)q.units * q.rec_bytes;
     q.resident = std::max(2, std::min(waves, 160 * 1024 / (2 * q.buf_bytes + 1024)));
     q.resident_cut = terms == 1 ? q.resident : std::min(q.resident, any_impl::occupancy(terms, q.ks, q.form, false));
     return q;
@@ -223,18 +331,24 @@ const char *any_name(const AnyGeo &q) { return q.terms == 1 ? "mfma_bf16" : q.te
 
 void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes)
 {
-    *Bbytes = (size_t)g.any.units * g.any.rec_bytes;
+    *Bbytes = (size_t)g.any.units * g.any.rec_bytes + (g.any.terms == 2 ? (size_t)g.K * g.any.tpg * 3 * g.any.ks * 1024 : 0);
     *ATbytes = g.any.form >= 8 ? 16 : (size_t)g.K * g.n * 16 * g.any.ks * (g.any.terms == 1 ? 2 : 4);
 }
 
-hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, hipStream_t s)
+hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, float *margin,
+                           float *scale, hipStream_t s)
 {
     size_t bb, ab;
+    if (g.any.terms == 2) {
+        hipLaunchKernelGGL(any_margin_kernel, dim3((unsigned)g.K), dim3(256), 0, s, g.m, g.n, half_margin(g.any.ks), B,
+                           scale, margin);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    }
     any_pack_sizes(g, &bb, &ab);
     const size_t pieces = bb / 16;
     size_t blocks = (pieces + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(any_pack_kernel, dim3((unsigned)blocks), dim3(256), 0, s, g.any, g.m, g.n, g.K, A, B,
+    hipLaunchKernelGGL(any_pack_kernel, dim3((unsigned)blocks), dim3(256), 0, s, g.any, g.m, g.n, g.K, A, B, scale,
                        (uint4 *)Bpack, pieces);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || g.any.form >= 8) return e;
@@ -319,7 +433,7 @@ int any_shares(const GameView &g, long long count)
     const AnyGeo &q = g.any;
     const long long blocks = blocks_of(q, count, many_kind(q, count, true)), pairs = blocks * q.units;
     if (q.units < 2) return 1;
-    const double work = 20.0 + 1.5 * q.terms * q.ks * q.tpg;
+    const double work = 20.0 + 1.5 * products(q) * q.ks * q.tpg;
     // Workgroups side by side: the time of a share, which begins with a block's rows (all that are resident,
     // two a compute unit, us: m = 60, n = 30, K = 20 bf16, 30000 rows 33 and 31; m = 16, n = 40, K = 30 bf16,
     // 20000 rows 26 and 28; m = 60, n = 100, K = 20, three products, 10000 rows 40 and 43).

@@ -36,6 +36,7 @@ namespace bsse {
 namespace any_impl {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef const void __attribute__((address_space(1))) *global_ptr;
 typedef void __attribute__((address_space(3))) *lds_ptr;
@@ -47,7 +48,7 @@ constexpr int WAVES = 4, THREADS = WAVES * 64;
 // have one candidate tile a wavefront with three and two with two.  The others have one kernel.
 constexpr bool two_kinds(int terms, int ks, int form)
 {
-    return terms == 1 ? (ks == 6 && form == 0) || (ks == 8 && form < 8) : form == 0 && ks == 2;
+    return terms == 1 ? (ks == 6 && form == 0) || (ks == 8 && form < 8) : terms != 2 && form == 0 && ks == 2;
 }
 // NT: 32-candidate tiles per wavefront.  Two let one fragment read serve two instructions; with
 // three parts of a long row in registers there is room for one.
@@ -63,6 +64,7 @@ constexpr int tiles_per_wave(int terms, int ks, int form, bool many)
 constexpr int occupancy(int terms, int ks, int form, bool many)
 {
     if (two_kinds(terms, ks, form)) return many ? 3 : 2;
+    if (terms == 2) return ks <= 4 ? 3 : 2;
     if (form == 0) return terms == 1 || ks <= 4 ? 3 : 2;
     if (form == 1) return terms == 1 ? (ks <= 4 ? 4 : 3) : ks == 1 ? 4 : ks <= 4 ? 3 : 2;
     return terms == 1 ? (ks <= 2 ? 4 : 3) : ks == 3 ? 4 : ks <= 4 ? 3 : 2;
@@ -78,6 +80,25 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 __device__ __forceinline__ float bf16_lo(unsigned p) { return __uint_as_float(p << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned p) { return __uint_as_float(p & 0xFFFF0000u); }
 
+// the nearest half-precision numbers, ties to even
+__device__ __forceinline__ unsigned pack_half(float a, float b)
+{
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+    const v2f ab = { a, b };
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(ab, v2h));
+}
+__device__ __forceinline__ float half_of(unsigned p, int k)
+{
+    typedef _Float16 v2h __attribute__((ext_vector_type(2)));
+    return (float)__builtin_bit_cast(v2h, p)[k];
+}
+
+__device__ __forceinline__ f32x16 mfma_half(const u32x4 &a, const unsigned *x, const f32x16 &c)
+{
+    const u32x4 b = { x[0], x[1], x[2], x[3] };
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
 __device__ __forceinline__ f32x16 mfma_bf16(const u32x4 &a, const unsigned *x, const f32x16 &c)
 {
     const u32x4 b = { x[0], x[1], x[2], x[3] };
@@ -207,17 +228,20 @@ __device__ __forceinline__ late_args late()
 }
 
 // TERMS: 1 = operands rounded to bf16 (bf16 storage), 3 / 6 = fp32 operands as three bf16 parts
-// against payoffs that are bf16 numbers / payoffs in three parts.  KS: k-steps of 16 leader actions.
+// against payoffs that are bf16 numbers / payoffs in three parts; 2 = fp32 operands as two half-precision
+// parts each, three or four products of them (see any_half_suits).  KS: k-steps of 16 leader actions.
 // FORM: see the top of the file.
 template <int TERMS, int KS, int FORM, bool MANY>
 __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) sweep_any_kernel(AnyArgs args)
 {
     constexpr int NT = tiles_per_wave(TERMS, KS, FORM, MANY);
-    constexpr int XP = TERMS == 1 ? 1 : 3;               // parts of a candidate component
-    constexpr int PA = TERMS == 6 ? 3 : 1;               // parts of a payoff
+    constexpr bool FILTER = TERMS == 2;                  // values too near each other are summed in bf16 parts
+    constexpr int XP = TERMS == 1 ? 1 : FILTER ? 2 : 3;  // parts of a candidate component
+    constexpr int PA = TERMS == 6 ? 3 : FILTER ? 2 : 1;  // parts of a payoff
     constexpr int HALF = 8 * KS;                         // leader actions per lane half
     constexpr bool NARROW = FORM >= 8;
-    constexpr bool XF = !NARROW && TERMS != 1 && KS <= 2;   // the fp32 half row stays in registers
+    static_assert(!(FILTER && NARROW), "leader payoffs off the matrix cores take all six products");
+    constexpr bool XF = FILTER || (!NARROW && TERMS != 1 && KS <= 2);   // the fp32 half row stays in registers
     constexpr int TPT = NARROW ? 32 / FORM : 1;          // types per unit
     constexpr bool UNSCALE = XP == 3 && !XF;             // leader payoffs come from the split row: see load_rows
     constexpr bool PAIRS = FORM == 0 && TERMS == 1 && KS <= 2;      // row tiles two at a time: fewer vector instructions
@@ -309,6 +333,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
     unsigned x[NT][XP][KS * 4];
     float xf[NT][XF ? HALF : 1];
     float unscale[UNSCALE ? NT : 1];
+    float norm[FILTER ? NT : 1];                         // of the row as it is split; infinite where the filter does not apply
     unsigned valid32[NT];
     // Rows of 16-byte multiples and others alike are read sixteen bytes a lane (the hardware asks for
     // four-byte alignment only); where a piece would reach past its row it is read ending with the row
@@ -368,6 +393,18 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         for (int ct = 0; ct < NT; ++ct) {
             valid32[ct] = (unsigned)__builtin_amdgcn_ballot_w64(first + ct * 32 + col < count);
             float scale = 1.0f;
+            if constexpr (FILTER) {
+                // the greatest component comes to 2^14 or more: what the parts leave of smaller ones is below
+                // 2^-39 of it.  Rows near the ends of fp32 (and rows of zeros) are not for the filter.
+                float most = 0.0f;
+#pragma unroll
+                for (int e = 0; e < HALF; ++e) most = fmaxf(most, fabsf(raw[ct][e]));
+                most = fmaxf(most, pair_other(most, partner_addr));
+                const unsigned e = __float_as_uint(most) >> 23;
+                const bool fits = e >= 67u && e < 187u;              // 2^-60 to 2^60
+                scale = __uint_as_float((fits ? 268u - e : 127u) << 23);
+                norm[ct] = fits ? 0.0f : INFINITY;
+            }
             if constexpr (XP == 3) {
                 float most = 0.0f;                       // (what `raw` holds past the row is of the row)
 #pragma unroll
@@ -382,6 +419,14 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                 float va = i < m ? raw[ct][e] : 0.0f, vb = i + 1 < m ? raw[ct][e + 1] : 0.0f;
                 if constexpr (XF) { xf[ct][e] = va; xf[ct][e + 1] = vb; }
                 if constexpr (XP == 3) { va *= scale; vb *= scale; }
+                if constexpr (FILTER) {
+                    va *= scale; vb *= scale;
+                    norm[ct] = fmaf(va, va, fmaf(vb, vb, norm[ct]));
+                    const unsigned p = pack_half(va, vb);
+                    x[ct][0][k] = p;
+                    x[ct][XP - 1][k] = pack_half(va - half_of(p, 0), vb - half_of(p, 1));
+                    continue;
+                }
                 constexpr float MOST = 0x1.FEp127f;      // the greatest bf16 number
                 const unsigned p0 = XP == 3 ? pack_bf16(__builtin_amdgcn_fmed3f(va, -MOST, MOST), __builtin_amdgcn_fmed3f(vb, -MOST, MOST))
                                             : pack_bf16(va, vb);
@@ -390,17 +435,52 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                     // (the differences are exact: x = p0 + p1 + p2)
                     const float ra = va - bf16_lo(p0), rb = vb - bf16_hi(p0);
                     const unsigned p1 = pack_bf16(ra, rb);
-                    x[ct][1][k] = p1;
-                    x[ct][2][k] = pack_bf16(ra - bf16_lo(p1), rb - bf16_hi(p1));
+                    x[ct][XP - 2][k] = p1;
+                    x[ct][XP - 1][k] = pack_bf16(ra - bf16_lo(p1), rb - bf16_hi(p1));
                 }
             }
+            if constexpr (FILTER) norm[ct] = __builtin_amdgcn_sqrtf(norm[ct] + pair_other(norm[ct], partner_addr));
         }
     };
 
     // One row tile against the wavefront's candidate tiles: fragments [k-step][part][lane].  The order
     // of the products is fixed (small parts first within a k-step), so every way of reaching a tile
     // gives the same bits.
+    // The C operand of a tile's first instruction.
+    auto start_of = [&](f32x16 &c, bool last) __attribute__((always_inline)) {
+        if (last) {
+            const f32x4 *p = reinterpret_cast<const f32x4 *>(cinit[h]);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c[r] = p[r / 4][r % 4];
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c[r] = 0.0f;
+        }
+    };
     auto tile_mfma = [&](f32x16 (&acc)[NT], auto fr, bool last) __attribute__((always_inline)) {
+        if constexpr (FILTER) {
+            // Small products first, beside which nothing is rounded that counts; the fragments of the great ones stay
+            // in registers meanwhile.  (See any_half_suits for the number of products.)
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) start_of(acc[ct], last);
+            u32x4 f0[KS];
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                f0[s] = fr[s * PA * 64];
+                const u32x4 f1 = fr[(s * PA + 1) * 64];
+#pragma unroll
+                for (int ct = 0; ct < NT; ++ct) {
+                    if constexpr (KS == 3) acc[ct] = mfma_half(f1, &x[ct][XP - 1][4 * s], acc[ct]);
+                    acc[ct] = mfma_half(f0[s], &x[ct][XP - 1][4 * s], acc[ct]);
+                    acc[ct] = mfma_half(f1, &x[ct][0][4 * s], acc[ct]);
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int ct = 0; ct < NT; ++ct) acc[ct] = mfma_half(f0[s], &x[ct][0][4 * s], acc[ct]);
+            return;
+        }
         static_for<0, KS, 1>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
             u32x4 f[PA];
@@ -559,6 +639,73 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && gmax > LEAST) & valid32[ct]);
     };
 
+    // The same for the candidate columns of the mask `columns`, with the maximum still to be found: all six
+    // products of bf16 parts, the payoffs' from records of their own in global memory and the row's made here.
+    // Tile by tile; a greater sum than any so far starts the maximisers anew.
+    auto exact_columns = [&](int ct, unsigned columns, int t, float &l_out, int &j_out) __attribute__((always_inline)) {
+        constexpr float LEAST = -3.402823466e38f;
+        float cur = LEAST, lbest = 0.0f, most = 0.0f;
+        int jbest = 0, nmatch = 0;
+#pragma unroll
+        for (int e = 0; e < (XF ? HALF : 0); ++e) most = fmaxf(most, fabsf(xf[ct][e]));
+        most = fmaxf(most, pair_other(most, partner_addr));
+        const float scale = most < 0x1p-60f ? 0x1p64f : 1.0f;
+#pragma unroll 1
+        for (int tt = 0; tt < q.tpg; ++tt) {
+            const u32x4 *fr = reinterpret_cast<const u32x4 *>(records + q.exact_off + ((size_t)t * q.tpg + tt) * (3 * KS * 1024)) + lane;
+            f32x16 acc;
+            start_of(acc, padded && tt == q.tpg - 1);
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                u32x4 f[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) f[p] = fr[(s * 3 + p) * 64];
+                unsigned px[3][4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    constexpr float MOST = 0x1.FEp127f;
+                    float va = xf[ct][XF ? 8 * s + 2 * k : 0], vb = xf[ct][XF ? 8 * s + 2 * k + 1 : 0];
+                    // (laundered: parts formed outside the loops would take the registers of the main path)
+                    asm volatile("" : "+v"(va), "+v"(vb));
+                    va *= scale; vb *= scale;
+                    px[0][k] = pack_bf16(__builtin_amdgcn_fmed3f(va, -MOST, MOST), __builtin_amdgcn_fmed3f(vb, -MOST, MOST));
+                    const float ra = va - bf16_lo(px[0][k]), rb = vb - bf16_hi(px[0][k]);
+                    px[1][k] = pack_bf16(ra, rb);
+                    px[2][k] = pack_bf16(ra - bf16_lo(px[1][k]), rb - bf16_hi(px[1][k]));
+                }
+                acc = mfma_bf16(f[2], px[0], acc); acc = mfma_bf16(f[1], px[1], acc); acc = mfma_bf16(f[0], px[2], acc);
+                acc = mfma_bf16(f[1], px[0], acc); acc = mfma_bf16(f[0], px[1], acc); acc = mfma_bf16(f[0], px[0], acc);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc));
+            float v[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] = acc[r];
+            float pm = vmax16(v);
+            pm = fmaxf(fmaxf(pm, LEAST), pair_other(fmaxf(pm, LEAST), partner_addr));
+            if (pm > cur) { cur = pm; nmatch = 0; }
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+                for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) {
+                        const int r = 4 * q4 + rr;
+                        const int j = tt * 32 + acc_row_base(r) + 4 * hh;
+                        const unsigned long long meq = __builtin_amdgcn_ballot_w64(fmaxf(acc[r], LEAST) == cur);
+                        const unsigned hit = (unsigned)(hh ? (meq >> 32) : meq) & columns;
+                        if (hit == 0u || j > n - 1) continue;               // wave-uniform
+                        const float l = pair_total(ct, half_dot(ct, lead_global(t, j)));
+                        if ((hit >> col) & 1u) {
+                            if (nmatch == 0 || l > lbest) { lbest = l; jbest = j; }
+                            ++nmatch;
+                        }
+                    }
+        }
+        if ((columns >> col) & 1u) { l_out = lbest; j_out = jbest; }
+        tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && cur > LEAST) & columns & valid32[ct]);
+    };
+
     int buf = 0;
     for (;;) {
         const int nsu = (u1 - u0 + q.ups - 1) / q.ups;   // groups of units, nq stages each
@@ -574,7 +721,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         constexpr int ROWS = FORM == 1 ? Grid::ROWS : 2 * UNIT;
         float best[NT], R[NT][ROWS], C[NT][Grid::COLS];
         unsigned btile[NT];
-        unsigned long long dup[NT];
+        [[maybe_unused]] unsigned long long dup[NT];
+        [[maybe_unused]] float second[NT];               // FILTER: the greatest maximum of a unit beside the leading one's
 
 #pragma unroll 1
         for (int su = 0; su < nsu; ++su) {
@@ -679,7 +827,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             for (int ct = 0; ct < NT; ++ct) {
                                 // (not minus infinity: a lane whose rows of a tile are all padding must
                                 // not count as a tie with the start value)
-                                best[ct] = -3.402823466e38f; btile[ct] = 0u; dup[ct] = 0ull;
+                                best[ct] = second[ct] = -3.402823466e38f; btile[ct] = 0u; dup[ct] = 0ull;
                                 if constexpr (FORM == 0) {
 #pragma unroll
                                     for (int r = 0; r < ROWS; ++r) R[ct][r] = -INFINITY;
@@ -704,7 +852,9 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             const int te = tb + q.stt < q.tpg ? tb + q.stt : q.tpg;
                             auto merge = [&](int ct, const float *r, int tt) __attribute__((always_inline)) {
                                 const float pm = ROWS == 2 ? vmax2(r[0], r[1]) : vmax2(vmax3(r[0], r[1], r[ROWS - 2]), r[ROWS - 1]);
-                                dup[ct] |= __builtin_amdgcn_ballot_w64(pm == best[ct]);
+                                // (second <= best: the middle one is what the greater of the two leaves)
+                                if constexpr (FILTER) second[ct] = __builtin_amdgcn_fmed3f(pm, best[ct], second[ct]);
+                                else dup[ct] |= __builtin_amdgcn_ballot_w64(pm == best[ct]);
                                 keep_greater_rows<ROWS>(pm, (unsigned)tt, r, best[ct], btile[ct], R[ct]);
                             };
 #pragma unroll 1
@@ -749,20 +899,23 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         }
                         // ---- epilogue of type t = u: both candidate tiles stage by stage
                         const int t = u;
-                        const float pt = prior[t];
-                        float gm[NT];
+                        const float pt = prior[t], reach = FILTER ? prior[K + t] : 0.0f;
+                        float gm[NT], floor[NT];
                         unsigned map[NT], map_other[NT];
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) gm[ct] = pair_other(best[ct], partner_addr);
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
                             gm[ct] = vmax2(gm[ct], best[ct]);
+                            // Values from `floor` on count as maximisers: with products missing that is what they
+                            // and the roundings can change below the maximum.
+                            floor[ct] = FILTER ? fmaf(-norm[FILTER ? ct : 0], reach, gm[ct]) : gm[ct];
                             // FORM 0: a unique maximiser of the pair sits in this lane's leading unit, whose
                             // first tile goes with the bits, or the columns are marked in dup
                             if constexpr (FORM == 1) {
-                                map[ct] = grid_map<1>(R[ct], C[ct], gm[ct], 4u * h);
+                                map[ct] = grid_map<1>(R[ct], C[ct], floor[ct], 4u * h);
                             } else {
-                                map[ct] = unit_map<ROWS>(R[ct], C[ct], gm[ct], 4u * h);
+                                map[ct] = unit_map<ROWS>(R[ct], C[ct], floor[ct], 4u * h);
                                 map[ct] = map[ct] ? map[ct] | (btile[ct] << 16) : 0u;
                             }
                             map_other[ct] = (unsigned)__builtin_amdgcn_ds_bpermute(partner_addr, (int)map[ct]);
@@ -770,12 +923,14 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         float l[NT];
                         int js[NT];
                         bool clean[NT];
+                        [[maybe_unused]] unsigned columns[NT];       // FILTER: those without a value that stands clear
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
                             const unsigned both = map[ct] | map_other[ct];
                             constexpr unsigned BITS = FORM == 1 ? 0xFFFFFFFFu : ~(kUnitTiles << 16);
                             unsigned long long multi = __builtin_amdgcn_ballot_w64(__builtin_popcount(both & BITS) != 2);
-                            if constexpr (FORM == 0) multi |= dup[ct];
+                            if constexpr (FORM == 0) multi |= FILTER ? __builtin_amdgcn_ballot_w64(second[ct] >= floor[ct]) : dup[ct];
+                            columns[ct] = (unsigned)(multi | (multi >> 32));
                             clean[ct] = multi == 0ull;               // wave-uniform
                             // (a wavefront that is not clean may hold any bits, and its gather is issued
                             // all the same)
@@ -796,7 +951,10 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         for (int ct = 0; ct < NT; ++ct) l[ct] = pair_total(ct, part[ct]);
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
-                            if (!clean[ct]) exact_type(ct, t, gm[ct], l[ct], js[ct]);
+                            if (!clean[ct]) {
+                                if constexpr (FILTER) exact_columns(ct, columns[ct], t, l[ct], js[ct]);
+                                else exact_type(ct, t, gm[ct], l[ct], js[ct]);
+                            }
                             V[ct] = fmaf(pt, l[ct], V[ct]);
                         }
                         if (per_type)
@@ -854,6 +1012,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
 }
 
 typedef void (*any_kernel_t)(AnyArgs);
+
+template <int KS> any_kernel_t any_kernel_half_form(int form) { return form == 0 ? sweep_any_kernel<2, KS, 0, true> : sweep_any_kernel<2, KS, 1, true>; }
 
 template <int TERMS, int KS>
 any_kernel_t any_kernel_form(int form, bool many)

@@ -25,6 +25,7 @@
 // maximisers in ascending action order comparing leader payoffs.
 #include "bsse_internal.h"
 #include <algorithm>
+#include <vector>
 #include "mfma_device.h"
 #include "done_device.h"
 #include <limits.h>
@@ -1507,14 +1508,17 @@ static void filter_margins(const Variant &v, int m, int n, int K, const float *B
 // tied candidates only): from the gaps between the greatest two payoffs in 64 pairs of up to eight types and
 // rows of the flat Dirichlet distribution.  A gap is below the margin a sixteenth as often as below sixteen
 // margins, of which 64 pairs show enough.
-static double twice_summed(int m, int n, int K, const float *B, const float *margin)
+double twice_summed(int m, int n, int K, const float *B, const std::function<float(int)> &margin, int pairs)
 {
-    constexpr int PAIRS = 64, MOST_M = 32, MOST_N = 64;
-    const int types = K < 8 ? K : 8, rows = PAIRS / types;
-    float x[PAIRS][MOST_M], norm[PAIRS];
+    constexpr int PAIRS = 64;                                           // at most
+    const int types = K < 8 ? K : 8, rows = pairs / types;
+    float norm[PAIRS];
+    std::vector<float> rows_of_x((size_t)rows * m), u(n);
+    float *x[PAIRS];
     uint64_t state = 0;
     for (int r = 0; r < rows; ++r) {
         float sum = 0.0f, square = 0.0f;
+        x[r] = rows_of_x.data() + (size_t)r * m;
         for (int i = 0; i < m; ++i) {
             uint64_t z = state += 0x9E3779B97F4A7C15ull;                // splitmix64
             z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
@@ -1528,9 +1532,11 @@ static double twice_summed(int m, int n, int K, const float *B, const float *mar
     double share = 0.0;
     for (int q = 0; q < types; ++q) {
         const int t = (int)((long long)q * K / types);
+        const float room = margin(t);
         int near = 0, tied = 0;
         for (int r = 0; r < rows; ++r) {
-            float u[MOST_N] = {}, first = -INFINITY, second = -INFINITY;
+            float first = -INFINITY, second = -INFINITY;
+            std::fill(u.begin(), u.end(), 0.0f);
             for (int i = 0; i < m; ++i) {
                 const float *row = B + ((size_t)t * m + i) * n;
                 for (int j = 0; j < n; ++j) u[j] += x[r][i] * row[j];
@@ -1540,7 +1546,7 @@ static double twice_summed(int m, int n, int K, const float *B, const float *mar
                 first = u[j] > first ? u[j] : first;
             }
             tied += first == second;
-            near += first > second && first - second < 16.0f * norm[r] * margin[t];
+            near += first > second && first - second < 16.0f * norm[r] * room;
         }
         const double clear = 1.0 - (double)tied / rows;
         share += (pow(clear, 32.0) - pow(std::max(0.0, clear - near / 16.0 / rows), 32.0)) / types;
@@ -1564,7 +1570,7 @@ int mfma_filter(int variant, int m, int n, int K, const float *B, float *margin)
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &w = kVariants[i];
         if (w.mode == v.mode && w.terms == v.terms && w.mp_base == v.mp_base && w.n == v.n && !w.cut)
-            return twice_summed(m, n, K, B, margin) > 0.25 ? i : variant;
+            return twice_summed(m, n, K, B, [=](int t) { return margin[t]; }, 64) > 0.25 ? i : variant;
     }
     return variant;
 }
