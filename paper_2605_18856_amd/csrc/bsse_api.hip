@@ -702,7 +702,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
     try {
         g->hA.assign(A, A + elems); g->hB.assign(B, B + elems); g->hprior.assign(prior, prior + K);
         g->hprior.resize((size_t)2 * K, 0.0f);          // (the filter's margins behind it)
-        if (use_mfma) variant = mfma_filter(variant, m, n, K, B, g->hprior.data() + K);
+        if (use_mfma) variant = mfma_filter(variant, m, n, K, A, B, g->hprior.data() + K);
         half = variant == kAnyVariant && !bf && !exact && any_half_suits(m, n, K, B);
         g->won_x.resize((size_t)m); g->won_br.resize((size_t)K);
     } catch (...) { delete g; return fail(BSSE_ENOMEM, "host allocation failed"); }

@@ -187,7 +187,16 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
 
 // Margins [K] of the filter of variants with split operands (others leave `margin` as it is).  Returns the variant
 // that sweeps this game: the one without a filter where that is the faster one.
-int mfma_filter(int variant, int m, int n, int K, const float *B, float *margin);
+int mfma_filter(int variant, int m, int n, int K, const float *A, const float *B, float *margin);
+
+// Small whole-number payoffs, n = 256, on the six-bit matrix instruction (see sweep_fp6.hip): a variant of the general
+// matrix-core kernel's table.  fp6_pack: Bpack [K][fp6_record_bytes()] and ATpack [K][n][128], both zeroed.
+typedef void (*sweep_fn_t)(GameView, SweepArgs, int);
+sweep_fn_t fp6_kernel(bool sliced);
+int fp6_record_bytes();
+bool fp6_suits(int m, int n, int K, const float *A, const float *B);
+void fp6_pack(int m, int K, const float *A, const float *B, unsigned char *Bpack, unsigned short *ATpack);
+void fp6_margins(int m, int K, const float *B, float *margin);
 
 // The share of (candidate tile, type) pairs that a filter with margin(t) sums twice, from `pairs` (8 to 64) pairs of
 // types and rows (see sweep_mfma.hip).

@@ -363,6 +363,19 @@ template <int TPG> __device__ __forceinline__ void grid_columns(const float (&u)
         }
     }
 }
+// c[i] = max(c[i], a[i], b[i]), i = 0..7
+__device__ __forceinline__ void vmax_into8(float *c, const float *a, const float *b)
+{
+#define BSSE_STEP(i) "v_max3_f32 %[c" #i "], %[c" #i "], %[a" #i "], %[b" #i "]\n\t"
+#define BSSE_INOUT(i) [c##i] "+v"(c[i])
+#define BSSE_IN(i) [a##i] "v"(a[i]), [b##i] "v"(b[i])
+    asm(BSSE_STEP(0) BSSE_STEP(1) BSSE_STEP(2) BSSE_STEP(3) BSSE_STEP(4) BSSE_STEP(5) BSSE_STEP(6) BSSE_STEP(7)
+        : BSSE_INOUT(0), BSSE_INOUT(1), BSSE_INOUT(2), BSSE_INOUT(3), BSSE_INOUT(4), BSSE_INOUT(5), BSSE_INOUT(6), BSSE_INOUT(7)
+        : BSSE_IN(0), BSSE_IN(1), BSSE_IN(2), BSSE_IN(3), BSSE_IN(4), BSSE_IN(5), BSSE_IN(6), BSSE_IN(7));
+#undef BSSE_STEP
+#undef BSSE_INOUT
+#undef BSSE_IN
+}
 // Both sets; returns the lane's maximum (from the smaller set).  COLS_FIRST: the eight column maxima before
 // the rows', which for eight row tiles saves the registers that are spilled otherwise (m = 128, n = 256, 2000
 // rows cut over K = 100 types: 51.0 us, rows first 53.0) but is slower in long launches (65536 rows of m = 100:

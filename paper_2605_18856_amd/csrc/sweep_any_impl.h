@@ -105,19 +105,6 @@ __device__ __forceinline__ f32x16 mfma_bf16(const u32x4 &a, const unsigned *x, c
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// c[i] = max(c[i], a[i], b[i]), i = 0..7
-__device__ __forceinline__ void vmax_into8(float *c, const float *a, const float *b)
-{
-#define BSSE_STEP(i) "v_max3_f32 %[c" #i "], %[c" #i "], %[a" #i "], %[b" #i "]\n\t"
-#define BSSE_INOUT(i) [c##i] "+v"(c[i])
-#define BSSE_IN(i) [a##i] "v"(a[i]), [b##i] "v"(b[i])
-    asm(BSSE_STEP(0) BSSE_STEP(1) BSSE_STEP(2) BSSE_STEP(3) BSSE_STEP(4) BSSE_STEP(5) BSSE_STEP(6) BSSE_STEP(7)
-        : BSSE_INOUT(0), BSSE_INOUT(1), BSSE_INOUT(2), BSSE_INOUT(3), BSSE_INOUT(4), BSSE_INOUT(5), BSSE_INOUT(6), BSSE_INOUT(7)
-        : BSSE_IN(0), BSSE_IN(1), BSSE_IN(2), BSSE_IN(3), BSSE_IN(4), BSSE_IN(5), BSSE_IN(6), BSSE_IN(7));
-#undef BSSE_STEP
-#undef BSSE_INOUT
-#undef BSSE_IN
-}
 // The map of a type of several row tiles (grid_map's, over the columns of all its tiles and the rows of the
 // one or two that lead): bits 16 to 27 stay free for the number of the leading tile.
 constexpr unsigned kUnitTiles = 0xFFFu;

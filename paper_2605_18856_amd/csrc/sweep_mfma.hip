@@ -1250,6 +1250,8 @@ struct Variant {
     void (*wide)(GameView, SweepArgs, int);       // sweep_wide_kernel for this packing and rows of m_pad components, or null
     void (*wide_part)(GameView, SweepArgs, int);  // the same for shorter rows
     int wide_lds;                                 // its dynamic LDS bytes
+    int side;                                     // workgroups a compute unit holds where that is one or two, else 0
+    bool fp6;                                     // sweep_fp6.hip
 };
 
 // (A few rows on six products wait for latencies, not for matrix instructions: they leave nothing out.)
@@ -1257,14 +1259,22 @@ struct Variant {
     { MODE, TERMSv, MPB, Nv, NTv, Wv, STv, ATL, CUTv,                                                \
       sweep_mfma_kernel<T, MPB * TERMSv, Nv, NTv, Wv, STv, OCCv, ATL, TERMSv, false, PFv, CUTv>,     \
       sweep_mfma_kernel<T, MPB * TERMSv, Nv, 1, Wv, STv, 1, ATL, TERMSv, true, PFv, CUTv && TERMSv != 6>, \
-      make_geometry((int)sizeof(T), MPB * TERMSv, Nv, STv, Wv, ATL, TERMSv), NAME, nullptr, nullptr, 0 }
+      make_geometry((int)sizeof(T), MPB * TERMSv, Nv, STv, Wv, ATL, TERMSv), NAME, nullptr, nullptr, 0, Wv == 8 ? 1 : 0, false }
 // A packing that sweep_wide_kernel also takes (one type per stage, leader rows in LDS, NT = 2)
 #define BSSE_VARIANT_WIDE(T, MODE, MPB, Nv, Wv, PFv, NAME)                                           \
     { MODE, 1, MPB, Nv, 2, Wv, Nv / 32, true, false,                                                 \
       nullptr,                                                                                       \
       sweep_mfma_kernel<T, MPB, Nv, 1, Wv, Nv / 32, 1, true, 1, true, PFv, false>,                   \
       make_geometry((int)sizeof(T), MPB, Nv, Nv / 32, Wv, true), NAME,                               \
-      sweep_wide_kernel<T, MPB, Nv, Wv, PFv, true>, sweep_wide_kernel<T, MPB, Nv, Wv, PFv, false>, wide_lds_bytes((int)sizeof(T), MPB, Nv, Wv) }
+      sweep_wide_kernel<T, MPB, Nv, Wv, PFv, true>, sweep_wide_kernel<T, MPB, Nv, Wv, PFv, false>, wide_lds_bytes((int)sizeof(T), MPB, Nv, Wv), 1, false }
+
+// The six-bit kernel for the games of (<=128, 256) with three products: a type per stage, two workgroups a compute unit.
+Variant fp6_variant()
+{
+    Geometry q{};
+    q.tpg = 8; q.types = q.ts = 1; q.rec_bytes = fp6_record_bytes();
+    return { 2, 3, 128, 256, 1, 4, 8, false, true, fp6_kernel(false), fp6_kernel(true), q, "mfma_split3", nullptr, nullptr, 0, 2, true };
+}
 
 const Variant kVariants[] = {
     // fp32 MFMA (the last number: k-steps per fragment read-ahead chunk, 0 = the fragment reads are left
@@ -1296,6 +1306,8 @@ const Variant kVariants[] = {
     // (one fragment ahead: the next one's LDS read runs under two matrix instructions; two ahead spill.  Six
     // registers are spilled as it is, three read back per type, and four of m = n = 32 with three products)
     BSSE_VARIANT(__bf16, 2, 3, 128, 256, 1, 8, 8, 2, false, 1, true, "mfma_split3"),
+    // the same games with small whole-number payoffs (fp6_suits)
+    fp6_variant(),
 };
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 constexpr int kSmallVariant = 1000;          // the small-game kernel (sweep_small.hip)
@@ -1332,7 +1344,7 @@ int mfma_select(int m, int n, int K, int mode, bool exact)
     int best = -1;
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &v = kVariants[i];
-        if (v.mode != mode || v.n != n || v.mp_base < m) continue;
+        if (v.fp6 || v.mode != mode || v.n != n || v.mp_base < m) continue;
         if (v.terms == 3 && !exact) continue;
         // smallest padded m wins; among equals, fewer terms
         if (best < 0 || v.mp_base < kVariants[best].mp_base ||
@@ -1359,19 +1371,20 @@ long long mfma_num_blocks(int variant, long long count)
 }
 
 // The limit of the static scratch is one of candidates too: n <= 32 with one or three products count 512 to a
-// record, of which the workgroups may take as few as 128.
+// record, of which the workgroups may take as few as 128, and the six-bit kernel 256, of which they take 128.
 long long mfma_limit_blocks(int variant, long long count)
 {
     const Variant &v = kVariants[variant];
+    if (v.fp6) return (count + 255) / 256;
     return v.n <= 32 && v.terms != 6 ? (count + 511) / 512 : mfma_num_blocks(variant, count);
 }
 
 // Kernels of eight wavefronts fill a compute unit with one workgroup: the time of `blocks` blocks of rows and
 // all types, cut into `slices`, in types of one candidate tile a wavefront.  A slice begins with its rows
 // (two types' time).
-static long long cut_time(long long blocks, int K, int slices)
+static long long cut_time(long long blocks, int K, int slices, int side)
 {
-    return (blocks * slices + 255) / 256 * ((K + slices - 1) / slices + 2);
+    return (blocks * slices + 256 * side - 1) / (256 * side) * ((K + slices - 1) / slices + 2);
 }
 
 // Stages per type slice of a sliced launch: 32 candidates per wavefront, whole groups per slice.
@@ -1384,12 +1397,13 @@ static int stages_per_slice(const Variant &v, int K, long long count)
     const int nstages = (row_tiles_for(v, K) + v.stage_tiles - 1) / v.stage_tiles;
     const long long per = 32LL * v.waves, blocks = (count + per - 1) / per;
     int slices = 1;
-    if (v.waves < 8) {
+    if (!v.side) {
         slices = blocks >= 1024 ? 1 : (int)(1024 / blocks);
-    } else if (blocks < 4096) {
-        slices = blocks >= 256 ? 1 : (int)std::min<long long>(256 / blocks, K);          // one round
+    } else if (blocks < 4096 * v.side) {
+        const int all = 256 * v.side;
+        slices = blocks >= all ? 1 : (int)std::min<long long>(all / blocks, K);          // one round
         for (int s = slices + 1; s <= K && s <= 16; ++s)
-            if (cut_time(blocks, K, s) < cut_time(blocks, K, slices)) slices = s;
+            if (cut_time(blocks, K, s, v.side) < cut_time(blocks, K, slices, v.side)) slices = s;
     }
     const int spg = v.geo.tpg > v.stage_tiles ? v.geo.tpg / v.stage_tiles : 1;       // stages per group
     return ((nstages + slices - 1) / slices + spg - 1) / spg * spg;
@@ -1427,13 +1441,14 @@ bool mfma_few_rows(const GameView &g, long long count)
     if (g.variant < 0 || g.variant >= kNumVariants) return false;
     const Variant &v = kVariants[g.variant];
     const long long per = 32LL * v.waves, blocks = (count + per - 1) / per, whole = mfma_num_blocks(g.variant, count);
-    if (v.waves < 8) return blocks <= 512 && mfma_slices(g, count) > 1;
-    if (blocks >= 4096) return false;
+    if (!v.side) return blocks <= 512 && mfma_slices(g, count) > 1;
+    if (blocks >= 4096 * v.side) return false;
     const int slices = mfma_slices(g, count);
-    if (whole <= 128 && (v.wide || slices > 1)) return true;
+    if (whole <= 128 * v.side && (v.wide || slices > 1)) return true;
     const double type = v.n * (0.0104 + 3.3e-5 * v.terms * v.mp_base);
     const double outputs = (12.0 + 2e-6 * (double)count * g.K) / type;
-    return (double)cut_time(blocks, g.K, slices) + outputs < 0.95 * (v.wide ? 2.5 : 1.0) * (double)((whole + 255) / 256 * g.K);
+    const long long all = 256 * v.side;
+    return (double)cut_time(blocks, g.K, slices, v.side) + outputs < 0.95 * (v.wide ? 2.5 : 1.0) * (double)((whole + all - 1) / all * g.K);
 }
 
 // Once per game, on the game's device: kernels whose two stage buffers exceed the default 48 KiB of
@@ -1595,10 +1610,15 @@ double twice_summed(int m, int n, int K, const float *B, const std::function<flo
 // have no other variant: payoffs that are bf16 numbers differ by 2^-8 of their size if they differ (whole
 // numbers 248..255 in place of 0..7: 143 -> 150 us, and 443 -> 507 for m = 128, n = 256, where all products at
 // once took 203 and 623).
-int mfma_filter(int variant, int m, int n, int K, const float *B, float *margin)
+int mfma_filter(int variant, int m, int n, int K, const float *A, const float *B, float *margin)
 {
     if (variant < 0 || variant >= kNumVariants || !kVariants[variant].cut) return variant;
     const Variant &v = kVariants[variant];
+    if (v.terms == 3 && v.n == 256 && fp6_suits(m, n, K, A, B)) {
+        fp6_margins(m, K, B, margin);
+        for (int i = 0; i < kNumVariants; ++i)
+            if (kVariants[i].fp6) return i;
+    }
     filter_margins(v, m, n, K, B, margin);
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &w = kVariants[i];
@@ -1645,6 +1665,12 @@ void mfma_pack(int variant, int m, int n, int K, const float *A, const float *B,
     const size_t esz = bf ? 2 : 4;
     static const int bsel6[6] = { 0, 1, 0, 2, 1, 0 };
     *m_pad = v->mp_base; *n_pad = n;
+    if (v->fp6) {
+        *Bbytes = (size_t)K * G.rec_bytes; *ATbytes = (size_t)K * n * v->mp_base * 2;
+        *Bpack = calloc(*Bbytes, 1); *ATpack = calloc(*ATbytes, 1);
+        if (*Bpack && *ATpack) fp6_pack(m, K, A, B, (unsigned char *)*Bpack, (unsigned short *)*ATpack);
+        return;
+    }
     *Bbytes = (size_t)nstages * G.rec_bytes;
     const bool lead_f32 = v->terms == 6 && v->at_lds;       // leader rows as plain fp32
     *ATbytes = lead_f32 ? (size_t)K * n * v->mp_base * sizeof(float) : (size_t)K * n * MP * esz;
