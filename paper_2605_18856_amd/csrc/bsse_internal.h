@@ -7,12 +7,12 @@
 namespace bsse {
 
 // Record geometry of the any-shape matrix-core kernel (see sweep_any_impl.h).  A unit is one type
-// (form 0: n > 32, form 1: n > 16) or one row tile of several types (form 8, 16: n <= 8, n <= 16).
+// (form 0: n > 64, form 1: 16 < n <= 32, form 2: up to 64) or one row tile of several types (form 8, 16: n <= 8, n <= 16).
 struct AnyGeo {
     int terms;            // 1, 3 or 6 part products of bf16 parts; 2: three of half-precision parts
     int ks;               // k-steps of 16 leader actions
     int form;
-    int tpg;              // row tiles per type (forms 0 and 1)
+    int tpg;              // row tiles per type (forms 0, 1 and 2)
     int units;
     int tile_bytes;       // fragments of one row tile
     int rec_bytes;        // one unit: fragments, then leader rows (or leader fragments, forms 8 and 16)
@@ -23,7 +23,7 @@ struct AnyGeo {
     int buf_bytes;        // one of the two stage buffers
     int resident;         // workgroups that a compute unit holds
     int resident_cut;     // the same of the kernel for launches cut over the types
-    size_t exact_off;     // terms 2: offset in Bpack of the payoffs' bf16 parts, [type][row tile][k-step][part][lane]
+    size_t exact_off;     // terms 2: offset in Bpack of the payoffs as given, [type][action][16 * ks], zero padded
 };
 
 // Device view of one game, passed to kernels by value.  All pointers are device memory
@@ -200,7 +200,7 @@ void fp6_margins(int m, int K, const float *B, float *margin);
 
 // The share of (candidate tile, type) pairs that a filter with margin(t) sums twice, from `pairs` (8 to 64) pairs of
 // types and rows (see sweep_mfma.hip).
-double twice_summed(int m, int n, int K, const float *B, const std::function<float(int)> &margin, int pairs);
+double twice_summed(int m, int n, int K, const float *B, const std::function<float(int)> &margin, int pairs, bool ties);
 
 // Small-game matrix-core kernel (n = 8, m = 8, K in {4, 8, 12, 16}, fp32); part of the MFMA path.
 bool small_supported(int m, int n, int K, int storage);

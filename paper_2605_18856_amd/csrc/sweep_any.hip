@@ -12,7 +12,7 @@ namespace bsse {
 any_impl::any_kernel_t any_kernel_terms1(int ks, int form, bool many);
 any_impl::any_kernel_t any_kernel_terms3(int ks, int form, bool many);
 any_impl::any_kernel_t any_kernel_terms6(int ks, int form, bool many);
-any_impl::any_kernel_t any_kernel_half(int ks, int form);
+any_impl::any_kernel_t any_kernel_half(int ks, int form, bool many);
 
 namespace {
 
@@ -33,7 +33,7 @@ constexpr float kHalfMost = 0x1p60f;
 any_impl::any_kernel_t kernel_for(const AnyGeo &q, bool many)
 {
     return q.terms == 1   ? any_kernel_terms1(q.ks, q.form, many)
-           : q.terms == 2 ? any_kernel_half(q.ks, q.form)
+           : q.terms == 2 ? any_kernel_half(q.ks, q.form, many)
            : q.terms == 3 ? any_kernel_terms3(q.ks, q.form, many)
                           : any_kernel_terms6(q.ks, q.form, many);
 }
@@ -101,18 +101,14 @@ any_pack_kernel(AnyGeo q, int m, int n, int K, const float *__restrict__ A, cons
     const int rec16 = q.rec_bytes / 16, frag16 = q.form >= 8 ? 2 * parts * q.ks * 64 : q.tpg * parts * q.ks * 64;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < pieces; p += stride) {
-        if (q.terms == 2 && p >= q.exact_off / 16) {      // terms 2: the bf16 parts behind the records
-            const size_t o = p - q.exact_off / 16;
-            const int lane = (int)(o % 64), part = (int)(o / 64 % 3), s = (int)(o / 192 % q.ks);
-            const size_t gt = o / (192 * q.ks);
-            const int t = (int)(gt / q.tpg), j = (int)(gt % q.tpg) * 32 + lane % 32;
-            unsigned e[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
-            if (j < n)
-                for (int k = 0; k < 8; ++k) {
-                    const int i = lane / 32 * half + 8 * s + k;
-                    if (i < m) e[k] = bf16_part(B[((size_t)t * m + i) * n + j], part);
-                }
-            Bpack[p] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+        if (q.terms == 2 && p >= q.exact_off / 16) {      // terms 2: the payoffs themselves behind the records
+            const size_t o = p - q.exact_off / 16, tj = o / (4 * q.ks), t = tj / n, j = tj % n;
+            float v[4];
+            for (int k = 0; k < 4; ++k) {
+                const int i = (int)(o % (4 * q.ks)) * 4 + k;
+                v[k] = i < m ? B[(t * m + i) * n + j] : 0.0f;
+            }
+            Bpack[p] = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
             continue;
         }
         const int u = (int)(p / rec16), o = (int)(p % rec16);
@@ -251,10 +247,11 @@ static float half_margin_of(int m, int n, int ks, const float *B)
 // 2.4 (three 0.45); m = 49 0.43 and 3.7, three products 0.39 and 2.6; m = 64 0.40 and 3.6, 0.35 and 2.1; m = 128
 // 0.43 and 4.0, 0.28 and 1.8; payoffs in 0..1 m = 48 1.21 and 5.5, 0.72 and 3.0; m = 128 2.10 and 9.3, 1.01 and 4.7.
 // Up to 32 leader actions what the parts leave counts for more (m = 24 0.34 and 2.8, four products 0.43 and 2.8).
-// What the parts lose outright, and ties, go back to six products (half_margin, exact_columns).
+// Where what the parts lose outright could decide, and for ties, sums in 64 bits do (half_margin, exact_actions).
 // Sixteen follower actions or fewer take their leader payoffs off the matrix cores, which nothing watches.
 // Payoffs of very different sizes (forbidden actions at -10^6) put many values within the margin, and whole numbers
-// beyond 2^22 have ties that 22 bits may not show: six products.
+// beyond 2^22 have ties that 22 bits may not show: six products, and so in
+// games with equal columns, which tie everywhere.
 bool any_half_suits(int m, int n, int K, const float *B)
 {
     if (m <= 32 || n <= 16 || !any_supported(m, n)) return false;
@@ -265,7 +262,7 @@ bool any_half_suits(int m, int n, int K, const float *B)
     }
     if (whole && large) return false;
     const int ks = any_geometry(m, n, K, 2).ks;
-    return twice_summed(m, n, K, B, [=](int t) { return half_margin_of(m, n, ks, B + (size_t)t * m * n); }, 16) <= 0.25;
+    return twice_summed(m, n, K, B, [=](int t) { return half_margin_of(m, n, ks, B + (size_t)t * m * n); }, 16, true) <= 0.25;
 }
 
 bool any_supported(int m, int n) { return m <= 128 && (long long)m * n > 64; }
@@ -281,7 +278,7 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     if (terms == 3 && q.ks != 2 && q.ks != 4) q.ks = q.ks == 1 ? 2 : q.ks == 3 ? 4 : 8;      // (fewer instantiations)
     const int parts = payoff_parts(terms), lbytes = terms == 1 ? 2 : 4;
     q.tile_bytes = parts * q.ks * 1024;
-    q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : 0;
+    q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : n <= 64 && any_impl::two_tiles(terms, q.ks) ? 2 : 0;
     q.nq = 1; q.lead_off = -1;
     // Two stage buffers per workgroup, and as many workgroups on a compute unit of 160 KiB as the registers
     // allow: 26 KiB a stage for two or three, 19 for four.  Beyond that the row tiles come in pieces and the
@@ -308,7 +305,7 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
         } else {
             q.rec_bytes = q.tpg * q.tile_bytes;
             q.stt = cap / q.tile_bytes > 1 ? cap / q.tile_bytes & ~1 : 1;      // tiles go in pairs
-            if (q.stt > q.tpg) q.stt = q.tpg;
+            if (q.stt > q.tpg || q.form == 2) q.stt = q.tpg;       // (two tiles of 16 KiB at most)
             q.nq = (q.tpg + q.stt - 1) / q.stt;
         }
     }
@@ -331,7 +328,7 @@ const char *any_name(const AnyGeo &q) { return q.terms == 1 ? "mfma_bf16" : q.te
 
 void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes)
 {
-    *Bbytes = (size_t)g.any.units * g.any.rec_bytes + (g.any.terms == 2 ? (size_t)g.K * g.any.tpg * 3 * g.any.ks * 1024 : 0);
+    *Bbytes = (size_t)g.any.units * g.any.rec_bytes + (g.any.terms == 2 ? (size_t)g.K * g.n * 16 * g.any.ks * 4 : 0);
     *ATbytes = g.any.form >= 8 ? 16 : (size_t)g.K * g.n * 16 * g.any.ks * (g.any.terms == 1 ? 2 : 4);
 }
 

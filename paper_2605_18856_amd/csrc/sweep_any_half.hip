@@ -9,13 +9,13 @@
 
 namespace bsse {
 
-any_impl::any_kernel_t any_kernel_half(int ks, int form)
+any_impl::any_kernel_t any_kernel_half(int ks, int form, bool many)
 {
     switch (ks) {
-    case 3: return any_impl::any_kernel_half_form<3>(form);
-    case 4: return any_impl::any_kernel_half_form<4>(form);
-    case 6: return any_impl::any_kernel_half_form<6>(form);
-    case 8: return any_impl::any_kernel_half_form<8>(form);
+    case 3: return any_impl::any_kernel_half_form<3>(form, many);
+    case 4: return any_impl::any_kernel_half_form<4>(form, many);
+    case 6: return any_impl::any_kernel_half_form<6>(form, many);
+    case 8: return any_impl::any_kernel_half_form<8>(form, many);
     }
     return nullptr;
 }

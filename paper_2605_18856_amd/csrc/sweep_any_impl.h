@@ -11,12 +11,13 @@
 //     the running maximum, its number and its two or four row maxima; when the type is done a bit for
 //     each that reaches the maximum names the action (unit_map).  Nothing depends on the number of
 //     tiles, so registers do not grow with n.
-//   * FORM 1 (16 < n <= 32) has one tile per type, a grid of four by four.
+//   * FORM 1 (16 < n <= 32) has one tile per type, a grid of four by four; FORM 2 (32 < n <= 64) two, side by
+//     side in registers, with nothing to carry from tile to tile.
 //   * FORM 8 and FORM 16 (n <= 8, n <= 16) put four or two whole types into one row tile, the rows
 //     permuted so that each lane holds every action of its types: no exchange is needed to find the
 //     best response.  The leader payoffs of all the actions come off the matrix cores too and the one
 //     at the best response is picked under the masks of the arg-max compares.
-// The leader payoff of FORM 0 and 1 is an fp32 dot product (bf16 pairs in bf16 storage) with the
+// The leader payoff of FORM 0, 1 and 2 is an fp32 dot product (bf16 pairs in bf16 storage) with the
 // column of A at the best response, from LDS where a whole type fits a stage, else from L2.
 //
 // Rows past the end of the candidates repeat the last one: they behave like any other row (no
@@ -48,8 +49,10 @@ constexpr int WAVES = 4, THREADS = WAVES * 64;
 // have one candidate tile a wavefront with three and two with two.  The others have one kernel.
 constexpr bool two_kinds(int terms, int ks, int form)
 {
-    return terms == 1 ? (ks == 6 && form == 0) || (ks == 8 && form < 8) : terms != 2 && form == 0 && ks == 2;
+    return terms == 1 ? (ks == 6 && form == 0) || (ks == 8 && form < 8) : (form == 0 || form == 2) && ks == 2;
 }
+// Whether types of two row tiles keep both in registers and in one stage (FORM 2).
+constexpr bool two_tiles(int terms, int ks) { return terms != 6 || ks <= 4; }
 // NT: 32-candidate tiles per wavefront.  Two let one fragment read serve two instructions; with
 // three parts of a long row in registers there is room for one.
 constexpr int tiles_per_wave(int terms, int ks, int form, bool many)
@@ -64,8 +67,9 @@ constexpr int tiles_per_wave(int terms, int ks, int form, bool many)
 constexpr int occupancy(int terms, int ks, int form, bool many)
 {
     if (two_kinds(terms, ks, form)) return many ? 3 : 2;
-    if (terms == 2) return ks <= 4 ? 3 : 2;
-    if (form == 0) return terms == 1 || ks <= 4 ? 3 : 2;
+    if (terms == 2) return ks == 1 && form == 1 ? 4 : ks <= 4 ? 3 : 2;
+    if (form == 2 && terms == 1) return ks <= 2 ? 4 : 3;
+    if (form == 0 || form == 2) return terms == 1 || ks <= 4 ? 3 : 2;
     if (form == 1) return terms == 1 ? (ks <= 4 ? 4 : 3) : ks == 1 ? 4 : ks <= 4 ? 3 : 2;
     return terms == 1 ? (ks <= 2 ? 4 : 3) : ks == 3 ? 4 : ks <= 4 ? 3 : 2;
 }
@@ -229,7 +233,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
     constexpr bool NARROW = FORM >= 8;
     static_assert(!(FILTER && NARROW), "leader payoffs off the matrix cores take all six products");
     constexpr bool XF = FILTER || (!NARROW && TERMS != 1 && KS <= 2);   // the fp32 half row stays in registers
-    constexpr int TPT = NARROW ? 32 / FORM : 1;          // types per unit
+    constexpr int WHOLE = FORM == 1 || FORM == 2 ? FORM : 0;            // row tiles of a type, where all are held at once
+    constexpr int TPT = NARROW ? 32 / (NARROW ? FORM : 32) : 1;          // types per unit
     constexpr bool UNSCALE = XP == 3 && !XF;             // leader payoffs come from the split row: see load_rows
     constexpr bool PAIRS = FORM == 0 && TERMS == 1 && KS <= 2;      // row tiles two at a time: fewer vector instructions
                                                          // per tile where these outweigh the matrix time
@@ -444,28 +449,32 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
             for (int r = 0; r < 16; ++r) c[r] = 0.0f;
         }
     };
+    // FILTER: small products first, beside which nothing is rounded that counts; the fragments of the great ones stay
+    // in registers meanwhile (see any_half_suits for the number of products).  Candidate tiles [CT, CT + NTS).
+    auto half_tiles = [&](auto ct0, auto nts, f32x16 *acc, auto fr, bool last) __attribute__((always_inline)) {
+        constexpr int CT = decltype(ct0)::value, NTS = decltype(nts)::value;
+#pragma unroll
+        for (int ct = 0; ct < NTS; ++ct) start_of(acc[ct], last);
+        u32x4 f0[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            f0[s] = fr[s * PA * 64];
+            const u32x4 f1 = fr[(s * PA + PA - 1) * 64];
+#pragma unroll
+            for (int ct = 0; ct < NTS; ++ct) {
+                if constexpr (KS == 3) acc[ct] = mfma_half(f1, &x[CT + ct][XP - 1][4 * s], acc[ct]);
+                acc[ct] = mfma_half(f0[s], &x[CT + ct][XP - 1][4 * s], acc[ct]);
+                acc[ct] = mfma_half(f1, &x[CT + ct][0][4 * s], acc[ct]);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int ct = 0; ct < NTS; ++ct) acc[ct] = mfma_half(f0[s], &x[CT + ct][0][4 * s], acc[ct]);
+    };
     auto tile_mfma = [&](f32x16 (&acc)[NT], auto fr, bool last) __attribute__((always_inline)) {
         if constexpr (FILTER) {
-            // Small products first, beside which nothing is rounded that counts; the fragments of the great ones stay
-            // in registers meanwhile.  (See any_half_suits for the number of products.)
-#pragma unroll
-            for (int ct = 0; ct < NT; ++ct) start_of(acc[ct], last);
-            u32x4 f0[KS];
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                f0[s] = fr[s * PA * 64];
-                const u32x4 f1 = fr[(s * PA + 1) * 64];
-#pragma unroll
-                for (int ct = 0; ct < NT; ++ct) {
-                    if constexpr (KS == 3) acc[ct] = mfma_half(f1, &x[ct][XP - 1][4 * s], acc[ct]);
-                    acc[ct] = mfma_half(f0[s], &x[ct][XP - 1][4 * s], acc[ct]);
-                    acc[ct] = mfma_half(f1, &x[ct][0][4 * s], acc[ct]);
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < KS; ++s)
-#pragma unroll
-                for (int ct = 0; ct < NT; ++ct) acc[ct] = mfma_half(f0[s], &x[ct][0][4 * s], acc[ct]);
+            half_tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, NT>{}, acc, fr, last);
             return;
         }
         static_for<0, KS, 1>([&](auto sc) {
@@ -589,7 +598,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         }
     };
 
-    // Exact routine for one (candidate tile, type) of FORM 0 / 1: the type's tiles once more from the
+    // Exact routine for one (candidate tile, type) of FORM 0, 1, 2: the type's tiles once more from the
     // records in global memory (same instructions, same bits), the exact maximisers in ascending
     // action order; the leader's payoff decides and then the lower action.  Sums of minus infinity, and sums
     // that are not numbers, count as the least finite number here: where a row has no others, all of its
@@ -626,71 +635,62 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && gmax > LEAST) & valid32[ct]);
     };
 
-    // The same for the candidate columns of the mask `columns`, with the maximum still to be found: all six
-    // products of bf16 parts, the payoffs' from records of their own in global memory and the row's made here.
-    // Tile by tile; a greater sum than any so far starts the maximisers anew.
-    auto exact_columns = [&](int ct, unsigned columns, int t, float &l_out, int &j_out) __attribute__((always_inline)) {
+    // FILTER: the best responses of the candidate columns `columns`, where values are too near the maximum for the
+    // three products, by the same rule.  These once more say which actions they are (from `floor` on, in any of the
+    // columns); their sums are taken in 64 bits and rounded once, so no further from the true ones than any sum in
+    // 32.  A column's answer does not depend on the others.  Few wavefronts come here, but a short launch ends with the
+    // last of them, and all of it is cold: little code and few loads (5 us; six products of bf16 parts over all tiles
+    // and a leader's dot product for each of a tile's rows took 13).
+    auto exact_actions = [&](auto ctc, unsigned columns, int t, float gm, float floor, const u32x4 *fr, int &j_out) __attribute__((always_inline)) {
+        constexpr int ct = decltype(ctc)::value;
         constexpr float LEAST = -3.402823466e38f;
-        float cur = LEAST, lbest = 0.0f, most = 0.0f;
+        const bool mine = (columns >> col) & 1u;
+        if (!(gm > LEAST)) floor = -INFINITY;            // (nothing but minus infinity and no numbers: every action)
+        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + q.exact_off) + (size_t)t * n * (HALF / 2);
+        float cur = LEAST;
         int jbest = 0, nmatch = 0;
-#pragma unroll
-        for (int e = 0; e < (XF ? HALF : 0); ++e) most = fmaxf(most, fabsf(xf[ct][e]));
-        most = fmaxf(most, pair_other(most, partner_addr));
-        const float scale = most < 0x1p-60f ? 0x1p64f : 1.0f;
 #pragma unroll 1
         for (int tt = 0; tt < q.tpg; ++tt) {
-            const u32x4 *fr = reinterpret_cast<const u32x4 *>(records + q.exact_off + ((size_t)t * q.tpg + tt) * (3 * KS * 1024)) + lane;
             f32x16 acc;
-            start_of(acc, padded && tt == q.tpg - 1);
-#pragma unroll
-            for (int s = 0; s < KS; ++s) {
-                u32x4 f[3];
-#pragma unroll
-                for (int p = 0; p < 3; ++p) f[p] = fr[(s * 3 + p) * 64];
-                unsigned px[3][4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    constexpr float MOST = 0x1.FEp127f;
-                    float va = xf[ct][XF ? 8 * s + 2 * k : 0], vb = xf[ct][XF ? 8 * s + 2 * k + 1 : 0];
-                    // (laundered: parts formed outside the loops would take the registers of the main path)
-                    asm volatile("" : "+v"(va), "+v"(vb));
-                    va *= scale; vb *= scale;
-                    px[0][k] = pack_bf16(__builtin_amdgcn_fmed3f(va, -MOST, MOST), __builtin_amdgcn_fmed3f(vb, -MOST, MOST));
-                    const float ra = va - bf16_lo(px[0][k]), rb = vb - bf16_hi(px[0][k]);
-                    px[1][k] = pack_bf16(ra, rb);
-                    px[2][k] = pack_bf16(ra - bf16_lo(px[1][k]), rb - bf16_hi(px[1][k]));
-                }
-                acc = mfma_bf16(f[2], px[0], acc); acc = mfma_bf16(f[1], px[1], acc); acc = mfma_bf16(f[0], px[2], acc);
-                acc = mfma_bf16(f[1], px[0], acc); acc = mfma_bf16(f[0], px[1], acc); acc = mfma_bf16(f[0], px[0], acc);
-            }
+            half_tiles(ctc, std::integral_constant<int, 1>{}, &acc, fr + (size_t)tt * (PA * KS * 64), padded && tt == q.tpg - 1);
             __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc));
-            float v[16];
+            unsigned near = 0u;                          // a bit for each row of the tile, as rows are numbered
 #pragma unroll
-            for (int r = 0; r < 16; ++r) v[r] = acc[r];
-            float pm = vmax16(v);
-            pm = fmaxf(fmaxf(pm, LEAST), pair_other(fmaxf(pm, LEAST), partner_addr));
-            if (pm > cur) { cur = pm; nmatch = 0; }
+            for (int r = 0; r < 16; ++r) near |= acc[r] < floor ? 0u : 1u << acc_row_base(r);
+            near = mine ? near << (4 * h) : 0u;
+            if (__builtin_amdgcn_ballot_w64(near != 0u) == 0ull) continue;
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
+            for (int d = 32; d >= 1; d >>= 1) near |= (unsigned)__shfl_xor((int)near, d, 64);
+            if (n - tt * 32 < 32) near &= (1u << (n - tt * 32)) - 1u;
+#pragma unroll 1
+            for (unsigned rest = (unsigned)__builtin_amdgcn_readfirstlane((int)near); rest != 0u; rest &= rest - 1u) {
+                const int j = tt * 32 + __builtin_ctz(rest);
+                const f32x4 *b = payoffs + (size_t)j * (HALF / 2);
+                b += h * (HALF / 4);
+                double sum = 0.0;
 #pragma unroll
-                for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        const int r = 4 * q4 + rr;
-                        const int j = tt * 32 + acc_row_base(r) + 4 * hh;
-                        const unsigned long long meq = __builtin_amdgcn_ballot_w64(fmaxf(acc[r], LEAST) == cur);
-                        const unsigned hit = (unsigned)(hh ? (meq >> 32) : meq) & columns;
-                        if (hit == 0u || j > n - 1) continue;               // wave-uniform
-                        const float l = pair_total(ct, half_dot(ct, lead_global(t, j)));
-                        if ((hit >> col) & 1u) {
-                            if (nmatch == 0 || l > lbest) { lbest = l; jbest = j; }
-                            ++nmatch;
-                        }
-                    }
+                for (int e = 0; e < HALF; ++e) {
+                    // (laundered, and eight at a time: numbers in 64 bits kept across the loop, or all payoffs at once, would
+                    // take the main path's registers)
+                    if (e % 8 == 0) __builtin_amdgcn_sched_barrier(0);
+                    float xe = xf[ct][XF ? e : 0];
+                    asm volatile("" : "+v"(xe));
+                    sum = fma((double)xe, (double)b[e / 4][e % 4], sum);
+                }
+                const float u = fmaxf((float)(sum + __shfl_xor(sum, 32, 64)), LEAST);      // (the same in both lanes)
+                if (u > cur) { cur = u; nmatch = 0; }
+                const bool again = u == cur && nmatch > 0;
+                bool better = u == cur && nmatch == 0;
+                if (__builtin_amdgcn_ballot_w64(again && mine) != 0ull) {
+                    const float l0 = pair_total(ct, half_dot(ct, lead_global(t, jbest))), l1 = pair_total(ct, half_dot(ct, lead_global(t, j)));
+                    better = better || (again && l1 > l0);
+                }
+                if (u == cur) ++nmatch;
+                if (better) jbest = j;
+            }
         }
-        if ((columns >> col) & 1u) { l_out = lbest; j_out = jbest; }
-        tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && cur > LEAST) & columns & valid32[ct]);
+        if (mine) j_out = jbest;
+        tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && cur > LEAST) & columns);
     };
 
     int buf = 0;
@@ -704,8 +704,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         // (a unit is one row tile, or two at a time: its grid rows as far as they hold the best value so far,
         // and the columns over all units)
         constexpr int UNIT = PAIRS ? 2 : 1;
-        typedef ArgGrid<FORM == 1 ? 1 : 2> Grid;
-        constexpr int ROWS = FORM == 1 ? Grid::ROWS : 2 * UNIT;
+        typedef ArgGrid<WHOLE ? WHOLE : 2> Grid;
+        constexpr int ROWS = WHOLE ? Grid::ROWS : 2 * UNIT;
         float best[NT], R[NT][ROWS], C[NT][Grid::COLS];
         unsigned btile[NT];
         [[maybe_unused]] unsigned long long dup[NT];
@@ -808,7 +808,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                                 return TypeOutput{ c, t, c < count && t < K, (int32_t)js[ct][p], l[ct][p] };
                             });
                     } else {
-                        // ---- FORM 0 / 1: one type
+                        // ---- FORM 0, 1, 2: one type
                         if (qq == 0) {
 #pragma unroll
                             for (int ct = 0; ct < NT; ++ct) {
@@ -823,16 +823,20 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                                 }
                             }
                         }
-                        if constexpr (FORM == 1) {
-                            f32x16 acc[NT];
-                            tile_mfma(acc, fr, padded);
-                            settle(acc);
+                        if constexpr (WHOLE > 0) {
+                            f32x16 acc[WHOLE][NT];
+#pragma unroll
+                            for (int tt = 0; tt < WHOLE; ++tt) tile_mfma(acc[tt], fr + tt * (PA * KS * 64), padded && tt == WHOLE - 1);
+#pragma unroll
+                            for (int tt = 0; tt < WHOLE; ++tt) settle(acc[tt]);
 #pragma unroll
                             for (int ct = 0; ct < NT; ++ct) {
-                                float v[1][16];
+                                float v[WHOLE][16];
 #pragma unroll
-                                for (int r = 0; r < 16; ++r) v[0][r] = acc[ct][r];
-                                best[ct] = grid_maxima<1>(v, R[ct], C[ct]);
+                                for (int tt = 0; tt < WHOLE; ++tt)
+#pragma unroll
+                                    for (int r = 0; r < 16; ++r) v[tt][r] = acc[tt][ct][r];
+                                best[ct] = grid_maxima<WHOLE>(v, R[ct], C[ct]);
                             }
                         } else {
                             const int tb = qq * q.stt;
@@ -899,8 +903,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             floor[ct] = FILTER ? fmaf(-norm[FILTER ? ct : 0], reach, gm[ct]) : gm[ct];
                             // FORM 0: a unique maximiser of the pair sits in this lane's leading unit, whose
                             // first tile goes with the bits, or the columns are marked in dup
-                            if constexpr (FORM == 1) {
-                                map[ct] = grid_map<1>(R[ct], C[ct], floor[ct], 4u * h);
+                            if constexpr (WHOLE > 0) {
+                                map[ct] = grid_map<WHOLE>(R[ct], C[ct], floor[ct], 4u * h);
                             } else {
                                 map[ct] = unit_map<ROWS>(R[ct], C[ct], floor[ct], 4u * h);
                                 map[ct] = map[ct] ? map[ct] | (btile[ct] << 16) : 0u;
@@ -914,16 +918,24 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
                             const unsigned both = map[ct] | map_other[ct];
-                            constexpr unsigned BITS = FORM == 1 ? 0xFFFFFFFFu : ~(kUnitTiles << 16);
+                            constexpr unsigned BITS = WHOLE ? 0xFFFFFFFFu : ~(kUnitTiles << 16);
                             unsigned long long multi = __builtin_amdgcn_ballot_w64(__builtin_popcount(both & BITS) != 2);
                             if constexpr (FORM == 0) multi |= FILTER ? __builtin_amdgcn_ballot_w64(second[ct] >= floor[ct]) : dup[ct];
-                            columns[ct] = (unsigned)(multi | (multi >> 32));
+                            columns[ct] = (unsigned)(multi | (multi >> 32)) & valid32[ct];
                             clean[ct] = multi == 0ull;               // wave-uniform
                             // (a wavefront that is not clean may hold any bits, and its gather is issued
                             // all the same)
-                            const unsigned j = FORM == 1 ? grid_action<1>(both) : grid_action<2>(both) + 32u * ((both >> 16) & kUnitTiles);
+                            const unsigned j = WHOLE ? grid_action<WHOLE ? WHOLE : 1>(both) : grid_action<2>(both) + 32u * ((both >> 16) & kUnitTiles);
                             js[ct] = j < (unsigned)n ? (int)j : 0;
                         }
+                        if constexpr (FILTER)
+                            static_for<0, NT, 1>([&](auto ctc) __attribute__((always_inline)) {
+                                constexpr int ct = decltype(ctc)::value;
+                                if (columns[ct] != 0u)
+                                    exact_actions(ctc, columns[ct], t, gm[ct], floor[ct],
+                                                  q.nq == 1 ? fr : reinterpret_cast<const u32x4 *>(records + (size_t)t * q.rec_bytes) + lane,
+                                                  js[ct]);
+                            });
                         float part[NT];
                         if (q.lead_off >= 0) {
                             const lds_byte *lb = (const lds_byte *)sb + (unsigned)(ui * q.rec_bytes + q.lead_off + h * HALF * LBYTES);
@@ -938,10 +950,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         for (int ct = 0; ct < NT; ++ct) l[ct] = pair_total(ct, part[ct]);
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
-                            if (!clean[ct]) {
-                                if constexpr (FILTER) exact_columns(ct, columns[ct], t, l[ct], js[ct]);
-                                else exact_type(ct, t, gm[ct], l[ct], js[ct]);
-                            }
+                            if constexpr (!FILTER)
+                                if (!clean[ct]) exact_type(ct, t, gm[ct], l[ct], js[ct]);
                             V[ct] = fmaf(pt, l[ct], V[ct]);
                         }
                         if (per_type)
@@ -1000,7 +1010,12 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
 
 typedef void (*any_kernel_t)(AnyArgs);
 
-template <int KS> any_kernel_t any_kernel_half_form(int form) { return form == 0 ? sweep_any_kernel<2, KS, 0, true> : sweep_any_kernel<2, KS, 1, true>; }
+template <int KS> any_kernel_t any_kernel_half_form(int form, bool many)
+{
+    if (form == 1) return sweep_any_kernel<2, KS, 1, true>;
+    if (form == 2) return many ? sweep_any_kernel<2, KS, 2, true> : sweep_any_kernel<2, KS, 2, !two_kinds(2, KS, 2)>;
+    return many ? sweep_any_kernel<2, KS, 0, true> : sweep_any_kernel<2, KS, 0, !two_kinds(2, KS, 0)>;
+}
 
 template <int TERMS, int KS>
 any_kernel_t any_kernel_form(int form, bool many)
@@ -1008,6 +1023,9 @@ any_kernel_t any_kernel_form(int form, bool many)
     switch (form) {
     case 0: return many ? sweep_any_kernel<TERMS, KS, 0, true> : sweep_any_kernel<TERMS, KS, 0, !two_kinds(TERMS, KS, 0)>;
     case 1: return many ? sweep_any_kernel<TERMS, KS, 1, true> : sweep_any_kernel<TERMS, KS, 1, !two_kinds(TERMS, KS, 1)>;
+    case 2:
+        if constexpr (two_tiles(TERMS, KS)) return many ? sweep_any_kernel<TERMS, KS, 2, true> : sweep_any_kernel<TERMS, KS, 2, !two_kinds(TERMS, KS, 2)>;
+        break;
     case 8: return sweep_any_kernel<TERMS, KS, 8, true>;
     case 16: return sweep_any_kernel<TERMS, KS, 16, true>;
     }

@@ -1553,10 +1553,11 @@ static void filter_margins(const Variant &v, int m, int n, int K, const float *B
 
 // The share of (candidate tile, type) pairs that a filter with these margins sums twice and that would not
 // have been for a tie of equal columns, which every kernel does (and the filter's exact routine looks at the
-// tied candidates only): from the gaps between the greatest two payoffs in 64 pairs of up to eight types and
+// tied candidates only; `ties`: these count too): from the gaps between the greatest two payoffs in 64 pairs of up to eight types and
 // rows of the flat Dirichlet distribution.  A gap is below the margin a sixteenth as often as below sixteen
 // margins, of which 64 pairs show enough.
-double twice_summed(int m, int n, int K, const float *B, const std::function<float(int)> &margin, int pairs)
+double twice_summed(int m, int n, int K, const float *B, const std::function<float(int)> &margin, int pairs,
+                    bool ties)
 {
     constexpr int PAIRS = 64;                                           // at most
     const int types = K < 8 ? K : 8, rows = pairs / types;
@@ -1596,7 +1597,8 @@ double twice_summed(int m, int n, int K, const float *B, const std::function<flo
             tied += first == second;
             near += first > second && first - second < 16.0f * norm[r] * room;
         }
-        const double clear = 1.0 - (double)tied / rows;
+        const double clear = ties ? 1.0 : 1.0 - (double)tied / rows;
+        if (ties) near += 16 * tied;
         share += (pow(clear, 32.0) - pow(std::max(0.0, clear - near / 16.0 / rows), 32.0)) / types;
     }
     return share;
@@ -1623,7 +1625,7 @@ int mfma_filter(int variant, int m, int n, int K, const float *A, const float *B
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant &w = kVariants[i];
         if (w.mode == v.mode && w.terms == v.terms && w.mp_base == v.mp_base && w.n == v.n && !w.cut)
-            return twice_summed(m, n, K, B, [=](int t) { return margin[t]; }, 64) > 0.25 ? i : variant;
+            return twice_summed(m, n, K, B, [=](int t) { return margin[t]; }, 64, false) > 0.25 ? i : variant;
     }
     return variant;
 }
