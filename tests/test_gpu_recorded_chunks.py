@@ -152,6 +152,7 @@ def test_scratch_is_outgrown(recorder):
     bsse.bsse_sweep_chunk(g, r.sets[A], N, 0)
     graphs = [r.record(N)]
     big = torch.cat(list(r.sets) * 20)
+    torch.cuda.synchronize()                             # (the rows are made on another stream than the handle's)
     for copies in (4, 20, 80):
         bsse.bsse_sweep_reset(g)
         bsse.bsse_sweep_chunk(g, big[:copies * N], copies * N, 0)
