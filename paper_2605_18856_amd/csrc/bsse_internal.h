@@ -7,12 +7,12 @@
 namespace bsse {
 
 // Record geometry of the any-shape matrix-core kernel (see sweep_any_impl.h).  A unit is one type
-// (form 0: n > 64, form 1: 16 < n <= 32, form 2: up to 64) or one row tile of several types (form 8, 16: n <= 8, n <= 16).
+// (forms 1, 2, 3, 4: that many row tiles, n > 16; form 0: any number) or one row tile of several types (form 8, 16: n <= 8, n <= 16).
 struct AnyGeo {
     int terms;            // 1, 3 or 6 part products of bf16 parts; 2: three of half-precision parts
     int ks;               // k-steps of 16 leader actions
     int form;
-    int tpg;              // row tiles per type (forms 0, 1 and 2)
+    int tpg;              // row tiles per type (forms 0 to 4)
     int units;
     int tile_bytes;       // fragments of one row tile
     int rec_bytes;        // one unit: fragments, then leader rows (or leader fragments, forms 8 and 16)

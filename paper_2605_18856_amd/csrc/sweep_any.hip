@@ -278,7 +278,9 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     if (terms == 3 && q.ks != 2 && q.ks != 4) q.ks = q.ks == 1 ? 2 : q.ks == 3 ? 4 : 8;      // (fewer instantiations)
     const int parts = payoff_parts(terms), lbytes = terms == 1 ? 2 : 4;
     q.tile_bytes = parts * q.ks * 1024;
-    q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : n <= 64 && any_impl::two_tiles(terms, q.ks) ? 2 : 0;
+    q.form = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 1 : n <= 64 && any_impl::two_tiles(terms, q.ks) ? 2
+             : n <= 96 && n > 64 && any_impl::three_tiles(terms, q.ks) ? 3
+             : n <= 128 && n > 96 && any_impl::four_tiles(terms, q.ks) ? 4 : 0;
     q.nq = 1; q.lead_off = -1;
     // Two stage buffers per workgroup, and as many workgroups on a compute unit of 160 KiB as the registers
     // allow: 26 KiB a stage for two or three, 19 for four.  Beyond that the row tiles come in pieces and the
@@ -305,7 +307,7 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
         } else {
             q.rec_bytes = q.tpg * q.tile_bytes;
             q.stt = cap / q.tile_bytes > 1 ? cap / q.tile_bytes & ~1 : 1;      // tiles go in pairs
-            if (q.stt > q.tpg || q.form == 2) q.stt = q.tpg;       // (two tiles of 16 KiB at most)
+            if (q.stt > q.tpg || (q.form >= 2 && q.form <= 4)) q.stt = q.tpg;       // (32 KiB at most)
             q.nq = (q.tpg + q.stt - 1) / q.stt;
         }
     }

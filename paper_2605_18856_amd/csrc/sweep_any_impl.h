@@ -6,18 +6,18 @@
 //   * The follower actions of a type are padded to whole row tiles.  A padded row never wins: its
 //     accumulator starts at minus infinity (the C operand of the tile's first instruction) and its
 //     payoffs are zero.
-//   * FORM 0 (n > 32) walks the row tiles of a type, one or two at a time (PAIRS), and keeps, per lane,
+//   * FORM 0 (n > 128, and where no other suits) walks the row tiles of a type, one or two at a time (PAIRS), and keeps, per lane,
 //     the eight column maxima of the tiles' grid over all of them and, for the tile or pair that holds
 //     the running maximum, its number and its two or four row maxima; when the type is done a bit for
 //     each that reaches the maximum names the action (unit_map).  Nothing depends on the number of
 //     tiles, so registers do not grow with n.
-//   * FORM 1 (16 < n <= 32) has one tile per type, a grid of four by four; FORM 2 (32 < n <= 64) two, side by
-//     side in registers, with nothing to carry from tile to tile.
+//   * FORM 1 (16 < n <= 32) has one tile per type, a grid of four by four; FORM 2, 3 and 4 (n up to 64, 96
+//     and 128) have two, three and four, side by side in registers.
 //   * FORM 8 and FORM 16 (n <= 8, n <= 16) put four or two whole types into one row tile, the rows
 //     permuted so that each lane holds every action of its types: no exchange is needed to find the
 //     best response.  The leader payoffs of all the actions come off the matrix cores too and the one
 //     at the best response is picked under the masks of the arg-max compares.
-// The leader payoff of FORM 0, 1 and 2 is an fp32 dot product (bf16 pairs in bf16 storage) with the
+// The leader payoff of FORM 0 to 4 is an fp32 dot product (bf16 pairs in bf16 storage) with the
 // column of A at the best response, from LDS where a whole type fits a stage, else from L2.
 //
 // Rows past the end of the candidates repeat the last one: they behave like any other row (no
@@ -49,14 +49,23 @@ constexpr int WAVES = 4, THREADS = WAVES * 64;
 // have one candidate tile a wavefront with three and two with two.  The others have one kernel.
 constexpr bool two_kinds(int terms, int ks, int form)
 {
-    return terms == 1 ? (ks == 6 && form == 0) || (ks == 8 && form < 8) : (form == 0 || form == 2) && ks == 2;
+    return terms == 1 ? (ks == 6 && form == 0) || (ks == 8 && form < 3) : (form == 0 || form == 2) && ks == 2;
 }
-// Whether types of two row tiles keep both in registers and in one stage (FORM 2).
+// Whether types of two, three or four row tiles keep them all in registers and in one stage (FORM 2, 3, 4): one wait
+// for the matrix unit and one grid arg-max a type, and nothing carried from tile to tile.  Where it takes a wavefront
+// one candidate tile in place of two, what it gives depends on the room that is left (1000000 rows, us, tile by tile
+// and at once: m = 30, n = 50, K = 20 bf16 233 and 180; m = 60, n = 40, K = 20 651 and 584; m = 12, n = 90, K = 30
+// bf16 393 and 297; m = 50, n = 100, K = 24 bf16, 600000 rows 386 and 330; m = 60, n = 66, K = 40, whole numbers,
+// 300000 rows 474 and 407).  Not where it was slower: m = 55, n = 85, K = 24 bf16, 600000 rows 276 and 287; m = 45,
+// n = 100, K = 20, 100003 rows 119 and 123, whole numbers 125 and 134; m = 30, n = 70, K = 20 618 and 639.
 constexpr bool two_tiles(int terms, int ks) { return terms != 6 || ks <= 4; }
+constexpr bool three_tiles(int terms, int ks) { return terms == 2 ? ks <= 4 : terms == 1 ? ks != 4 : terms == 3; }
+constexpr bool four_tiles(int terms, int ks) { return terms == 1 || (terms == 3 && ks <= 2); }
 // NT: 32-candidate tiles per wavefront.  Two let one fragment read serve two instructions; with
 // three parts of a long row in registers there is room for one.
 constexpr int tiles_per_wave(int terms, int ks, int form, bool many)
 {
+    if (form == 3 || form == 4) return 1;
     return ks <= (terms == 1 ? 4 : 2) || (terms == 1 && two_kinds(terms, ks, form) && !many) ? 2 : 1;
 }
 // Wavefronts per SIMD that the register allocation is held to; with one wavefront of every workgroup on each
@@ -67,6 +76,7 @@ constexpr int tiles_per_wave(int terms, int ks, int form, bool many)
 constexpr int occupancy(int terms, int ks, int form, bool many)
 {
     if (two_kinds(terms, ks, form)) return many ? 3 : 2;
+    if (form == 3 || form == 4) return terms == 1 ? (ks <= 4 ? 4 : 3) : ks <= 2 ? 3 : 2;
     if (terms == 2) return ks == 1 && form == 1 ? 4 : ks <= 4 ? 3 : 2;
     if (form == 2 && terms == 1) return ks <= 2 ? 4 : 3;
     if (form == 0 || form == 2) return terms == 1 || ks <= 4 ? 3 : 2;
@@ -233,7 +243,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
     constexpr bool NARROW = FORM >= 8;
     static_assert(!(FILTER && NARROW), "leader payoffs off the matrix cores take all six products");
     constexpr bool XF = FILTER || (!NARROW && TERMS != 1 && KS <= 2);   // the fp32 half row stays in registers
-    constexpr int WHOLE = FORM == 1 || FORM == 2 ? FORM : 0;            // row tiles of a type, where all are held at once
+    static_assert((FORM != 3 && FORM != 4) || NT == 1, "one wait names up to four accumulators");
+    constexpr int WHOLE = FORM < 8 ? FORM : 0;           // row tiles of a type, where all are held at once
     constexpr int TPT = NARROW ? 32 / (NARROW ? FORM : 32) : 1;          // types per unit
     constexpr bool UNSCALE = XP == 3 && !XF;             // leader payoffs come from the split row: see load_rows
     constexpr bool PAIRS = FORM == 0 && TERMS == 1 && KS <= 2;      // row tiles two at a time: fewer vector instructions
@@ -598,7 +609,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         }
     };
 
-    // Exact routine for one (candidate tile, type) of FORM 0, 1, 2: the type's tiles once more from the
+    // Exact routine for one (candidate tile, type) of FORM 0 to 4: the type's tiles once more from the
     // records in global memory (same instructions, same bits), the exact maximisers in ascending
     // action order; the leader's payoff decides and then the lower action.  Sums of minus infinity, and sums
     // that are not numbers, count as the least finite number here: where a row has no others, all of its
@@ -704,7 +715,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         // (a unit is one row tile, or two at a time: its grid rows as far as they hold the best value so far,
         // and the columns over all units)
         constexpr int UNIT = PAIRS ? 2 : 1;
-        typedef ArgGrid<WHOLE ? WHOLE : 2> Grid;
+        typedef ArgGrid<WHOLE == 3 ? 4 : WHOLE ? WHOLE : 2> Grid;
         constexpr int ROWS = WHOLE ? Grid::ROWS : 2 * UNIT;
         float best[NT], R[NT][ROWS], C[NT][Grid::COLS];
         unsigned btile[NT];
@@ -808,7 +819,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                                 return TypeOutput{ c, t, c < count && t < K, (int32_t)js[ct][p], l[ct][p] };
                             });
                     } else {
-                        // ---- FORM 0, 1, 2: one type
+                        // ---- FORM 0 to 4: one type
                         if (qq == 0) {
 #pragma unroll
                             for (int ct = 0; ct < NT; ++ct) {
@@ -826,9 +837,22 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         if constexpr (WHOLE > 0) {
                             f32x16 acc[WHOLE][NT];
 #pragma unroll
-                            for (int tt = 0; tt < WHOLE; ++tt) tile_mfma(acc[tt], fr + tt * (PA * KS * 64), padded && tt == WHOLE - 1);
-#pragma unroll
-                            for (int tt = 0; tt < WHOLE; ++tt) settle(acc[tt]);
+                            for (int tt = 0; tt < WHOLE; ++tt) {
+                                tile_mfma(acc[tt], fr + tt * (PA * KS * 64), padded && tt == WHOLE - 1);
+                            }
+                            if constexpr (WHOLE == 1) {
+                                settle(acc[0]);
+                            } else {                     // (one wait for all of them)
+                                constexpr int LAST = WHOLE - 1;
+                                __builtin_amdgcn_sched_barrier(0);
+                                if constexpr (WHOLE * NT == 2) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[LAST][0]));
+                                else if constexpr (NT == 2)
+                                    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[0][NT - 1]), "+v"(acc[LAST][0]), "+v"(acc[LAST][NT - 1]));
+                                else if constexpr (WHOLE == 3)
+                                    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[LAST][0]));
+                                else
+                                    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[LAST - 1][0]), "+v"(acc[LAST][0]));
+                            }
 #pragma unroll
                             for (int ct = 0; ct < NT; ++ct) {
                                 float v[WHOLE][16];
@@ -836,7 +860,16 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                                 for (int tt = 0; tt < WHOLE; ++tt)
 #pragma unroll
                                     for (int r = 0; r < 16; ++r) v[tt][r] = acc[tt][ct][r];
-                                best[ct] = grid_maxima<WHOLE>(v, R[ct], C[ct]);
+                                if constexpr (WHOLE == 3) {      // a grid of four row tiles, one of them empty
+                                    grid_rows<3>(v, R[ct]);
+                                    R[ct][ROWS - 2] = R[ct][ROWS - 1] = -INFINITY;
+                                    vmax4x4(C[ct], v[0], v[0] + 8, v[1], v[1] + 8);
+                                    vmax4x4(C[ct] + 4, v[0] + 4, v[0] + 12, v[1] + 4, v[1] + 12);
+                                    vmax_into8(C[ct], v[WHOLE - 1], v[WHOLE - 1] + 8);
+                                    best[ct] = vmax2(vmax3(R[ct][0], R[ct][1], R[ct][2]), vmax3(R[ct][3], R[ct][ROWS - 4], R[ct][ROWS - 3]));
+                                } else {
+                                    best[ct] = grid_maxima<WHOLE>(v, R[ct], C[ct]);
+                                }
                             }
                         } else {
                             const int tb = qq * q.stt;
@@ -904,7 +937,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             // FORM 0: a unique maximiser of the pair sits in this lane's leading unit, whose
                             // first tile goes with the bits, or the columns are marked in dup
                             if constexpr (WHOLE > 0) {
-                                map[ct] = grid_map<WHOLE>(R[ct], C[ct], floor[ct], 4u * h);
+                                map[ct] = grid_map<WHOLE == 3 ? 4 : WHOLE>(R[ct], C[ct], floor[ct], 4u * h);
                             } else {
                                 map[ct] = unit_map<ROWS>(R[ct], C[ct], floor[ct], 4u * h);
                                 map[ct] = map[ct] ? map[ct] | (btile[ct] << 16) : 0u;
@@ -925,7 +958,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             clean[ct] = multi == 0ull;               // wave-uniform
                             // (a wavefront that is not clean may hold any bits, and its gather is issued
                             // all the same)
-                            const unsigned j = WHOLE ? grid_action<WHOLE ? WHOLE : 1>(both) : grid_action<2>(both) + 32u * ((both >> 16) & kUnitTiles);
+                            const unsigned j = WHOLE ? grid_action<WHOLE == 3 ? 4 : WHOLE ? WHOLE : 1>(both) : grid_action<2>(both) + 32u * ((both >> 16) & kUnitTiles);
                             js[ct] = j < (unsigned)n ? (int)j : 0;
                         }
                         if constexpr (FILTER)
@@ -1013,6 +1046,8 @@ typedef void (*any_kernel_t)(AnyArgs);
 template <int KS> any_kernel_t any_kernel_half_form(int form, bool many)
 {
     if (form == 1) return sweep_any_kernel<2, KS, 1, true>;
+    if constexpr (three_tiles(2, KS))
+        if (form == 3) return sweep_any_kernel<2, KS, 3, true>;
     if (form == 2) return many ? sweep_any_kernel<2, KS, 2, true> : sweep_any_kernel<2, KS, 2, !two_kinds(2, KS, 2)>;
     return many ? sweep_any_kernel<2, KS, 0, true> : sweep_any_kernel<2, KS, 0, !two_kinds(2, KS, 0)>;
 }
@@ -1025,6 +1060,12 @@ any_kernel_t any_kernel_form(int form, bool many)
     case 1: return many ? sweep_any_kernel<TERMS, KS, 1, true> : sweep_any_kernel<TERMS, KS, 1, !two_kinds(TERMS, KS, 1)>;
     case 2:
         if constexpr (two_tiles(TERMS, KS)) return many ? sweep_any_kernel<TERMS, KS, 2, true> : sweep_any_kernel<TERMS, KS, 2, !two_kinds(TERMS, KS, 2)>;
+        break;
+    case 4:
+        if constexpr (four_tiles(TERMS, KS)) return sweep_any_kernel<TERMS, KS, 4, true>;
+        break;
+    case 3:
+        if constexpr (three_tiles(TERMS, KS)) return sweep_any_kernel<TERMS, KS, 3, true>;
         break;
     case 8: return sweep_any_kernel<TERMS, KS, 8, true>;
     case 16: return sweep_any_kernel<TERMS, KS, 16, true>;

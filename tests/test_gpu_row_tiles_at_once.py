@@ -1,4 +1,4 @@
-"""Types of two row tiles on the any-shape kernel (32 < n <= 64), which hold both in registers: the edges of n and of the
+"""Types of two to four row tiles on the any-shape kernel (32 < n <= 128), held in registers all at once: the edges of n and of the
 k-steps for every kind of operand, ties, and the sums in 64 bits that decide where half-precision parts cannot."""
 import numpy as np
 import pytest
@@ -12,8 +12,8 @@ PATHS = {"normal": "mfma_split6", "int": "mfma_split3", "bf16": "mfma_bf16"}
 
 
 @pytest.mark.parametrize("kind", ["normal", "int", "bf16"])
-@pytest.mark.parametrize("m", [2, 15, 17, 31, 33, 48, 49, 64, 65, 96, 97, 128])
-@pytest.mark.parametrize("n", [33, 48, 63, 64])
+@pytest.mark.parametrize("m", [3, 16, 17, 32, 33, 48, 49, 64, 65, 96, 97, 128])
+@pytest.mark.parametrize("n", [33, 63, 64, 65, 96, 97, 127, 128])
 def test_edges(m, n, kind):
     if m * n <= 64 or (n == 64 and m <= 32 and kind != "bf16"):
         pytest.skip("another kernel's shape")
