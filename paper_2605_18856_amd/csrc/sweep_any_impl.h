@@ -84,6 +84,15 @@ constexpr int occupancy(int terms, int ks, int form, bool many)
     return terms == 1 ? (ks <= 2 ? 4 : 3) : ks == 3 ? 4 : ks <= 4 ? 3 : 2;
 }
 
+// K-steps whose fragments are requested ahead of the one that is multiplied, as many as the registers hold (0: the
+// compiler's order; half-precision parts have their own).
+constexpr int fragments_ahead(int terms, int ks, int form, bool many)
+{
+    if (form == 0 || form >= 8 || terms == 2) return 0;
+    if (terms == 1) return form != 4 ? 3 : ks == 3 ? 0 : ks == 6 ? 1 : 3;
+    return (two_kinds(terms, ks, form) && many) || (terms == 6 && ks == 4) ? 0 : 1;
+}
+
 __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 {
     typedef float v2f __attribute__((ext_vector_type(2)));
@@ -525,6 +534,44 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
             }
         });
     };
+    // All row tiles of a type at once (FORM 1 to 4), in the same order.  The fragments of AHEAD k-steps are under way
+    // while one is multiplied, in the order written: left to the compiler, which saves registers, every matrix
+    // instruction waited for a read of LDS issued just before it (us: m = 50, n = 100, K = 24 bf16, 300000 rows 182 and
+    // 173, 70001 rows 71.5 and 69.8; m = 90, n = 80, K = 10 bf16 118 and 112; m = 60, n = 40, K = 20, whole numbers,
+    // 1000000 rows 435 and 424; up to 32 actions and with six products it makes no difference).
+    constexpr int AHEAD = fragments_ahead(TERMS, KS, FORM, MANY);
+    auto whole_mfma = [&](f32x16 (&acc)[WHOLE ? WHOLE : 1][NT], auto fr) __attribute__((always_inline)) {
+        constexpr int STEPS = WHOLE * KS, RING = AHEAD + 1;
+        u32x4 f[RING][PA];
+        auto read = [&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            if constexpr (i < STEPS)
+#pragma unroll
+                for (int p = 0; p < PA; ++p) f[i % RING][p] = fr[(i * PA + p) * 64];
+        };
+        static_for<0, AHEAD, 1>([&](auto ic) { read(ic); });
+        static_for<0, STEPS, 1>([&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value, tt = i / KS, s = i % KS;
+            read(std::integral_constant<int, i + AHEAD>{});
+            if constexpr (s == 0)
+#pragma unroll
+                for (int ct = 0; ct < NT; ++ct) start_of(acc[tt][ct], tt == WHOLE - 1);
+            __builtin_amdgcn_sched_barrier(0);
+            auto product = [&](int pb, int px) __attribute__((always_inline)) {
+#pragma unroll
+                for (int ct = 0; ct < NT; ++ct) acc[tt][ct] = mfma_bf16(f[i % RING][pb], &x[ct][px][4 * s], acc[tt][ct]);
+            };
+            if constexpr (TERMS == 6) {
+                product(PA - 1, 0); product(1 % PA, 1 % XP); product(0, XP - 1);
+                product(1 % PA, 0); product(0, 1 % XP); product(0, 0);
+            } else if constexpr (TERMS == 3) {
+                product(0, XP - 1); product(0, 1 % XP); product(0, 0);
+            } else {
+                product(0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
     // The asm blocks below read accumulators, and the compiler's hazard handling does not look into
     // inline asm: the wait states a vector read of a fresh MFMA result needs are explicit, with the
     // accumulators as operands so that nothing that reads them can be scheduled above the wait.
@@ -836,9 +883,11 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         }
                         if constexpr (WHOLE > 0) {
                             f32x16 acc[WHOLE][NT];
+                            if constexpr (AHEAD == 0) {
 #pragma unroll
-                            for (int tt = 0; tt < WHOLE; ++tt) {
-                                tile_mfma(acc[tt], fr + tt * (PA * KS * 64), padded && tt == WHOLE - 1);
+                                for (int tt = 0; tt < WHOLE; ++tt) tile_mfma(acc[tt], fr + tt * (PA * KS * 64), padded && tt == WHOLE - 1);
+                            } else {
+                                whole_mfma(acc, fr);
                             }
                             if constexpr (WHOLE == 1) {
                                 settle(acc[0]);
