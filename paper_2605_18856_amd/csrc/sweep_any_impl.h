@@ -93,6 +93,14 @@ constexpr int fragments_ahead(int terms, int ks, int form, bool many)
     return (two_kinds(terms, ks, form) && many) || (terms == 6 && ks == 4) ? 0 : 1;
 }
 
+// The same within one row tile (FORM 0; us: m = 90, n = 150, K = 6 bf16, 300000 rows 130 and 122, 5000 rows 34.0 and
+// 32.5; m = 50, n = 200, K = 12 bf16, 70001 rows 69 and 66; six products have enough to do meanwhile).
+constexpr int tile_ahead(int terms, int ks, bool many)
+{
+    if (terms == 1) return ks < 4 ? ks - 1 : 3;
+    return terms == 3 && (ks == 4 || (ks == 2 && !many)) ? 1 : 0;
+}
+
 __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 {
     typedef float v2f __attribute__((ext_vector_type(2)));
@@ -497,11 +505,20 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
             half_tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, NT>{}, acc, fr, last);
             return;
         }
+        constexpr int HERE = NARROW || WHOLE > 0 ? 0 : tile_ahead(TERMS, KS, MANY);
+        u32x4 ring[HERE + 1][PA];
+        auto read = [&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            if constexpr (i < KS)
+#pragma unroll
+                for (int p = 0; p < PA; ++p) ring[i % (HERE + 1)][p] = fr[(i * PA + p) * 64];
+        };
+        static_for<0, HERE, 1>([&](auto ic) { read(ic); });
         static_for<0, KS, 1>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
-            u32x4 f[PA];
-#pragma unroll
-            for (int p = 0; p < PA; ++p) f[p] = fr[(s * PA + p) * 64];
+            read(std::integral_constant<int, s + HERE>{});
+            if constexpr (HERE > 0) __builtin_amdgcn_sched_barrier(0);
+            u32x4 (&f)[PA] = ring[s % (HERE + 1)];
             auto product = [&](int pb, int px, bool first) __attribute__((always_inline)) {
                 if (s == 0 && first) {
                     f32x16 zero;
@@ -532,6 +549,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
             } else {
                 product(0, 0, true);
             }
+            if constexpr (HERE > 0) __builtin_amdgcn_sched_barrier(0);
         });
     };
     // All row tiles of a type at once (FORM 1 to 4), in the same order.  The fragments of AHEAD k-steps are under way
