@@ -355,6 +355,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
     float unscale[UNSCALE ? NT : 1];
     float norm[FILTER ? NT : 1];                         // of the row as it is split; infinite where the filter does not apply
     unsigned valid32[NT];
+    [[maybe_unused]] unsigned zero32[NT];                // FILTER: valid rows of zeros
     // Rows of 16-byte multiples and others alike are read sixteen bytes a lane (the hardware asks for
     // four-byte alignment only); where a piece would reach past its row it is read ending with the row
     // and shifted.  All of a wavefront's pieces are requested before the first is used.  (Component by
@@ -424,6 +425,11 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                 const bool fits = e >= 67u && e < 187u;              // 2^-60 to 2^60
                 scale = __uint_as_float((fits ? 268u - e : 127u) << 23);
                 norm[ct] = fits ? 0.0f : INFINITY;
+                bool zero = true;                        // (not from `most`, which passes over what is no number)
+#pragma unroll
+                for (int k = 0; k < HALF; ++k) zero = zero && !(h * HALF + k < m && raw[ct][k] != 0.0f);
+                const unsigned long long zeros = __builtin_amdgcn_ballot_w64(zero);
+                zero32[ct] = (unsigned)zeros & (unsigned)(zeros >> 32) & valid32[ct];
             }
             if constexpr (XP == 3) {
                 float most = 0.0f;                       // (what `raw` holds past the row is of the row)
@@ -1022,6 +1028,11 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             unsigned long long multi = __builtin_amdgcn_ballot_w64(__builtin_popcount(both & BITS) != 2);
                             if constexpr (FORM == 0) multi |= FILTER ? __builtin_amdgcn_ballot_w64(second[ct] >= floor[ct]) : dup[ct];
                             columns[ct] = (unsigned)(multi | (multi >> 32)) & valid32[ct];
+                            if constexpr (FILTER) {
+                                // rows of zeros: all actions tie and are worth the same, and the map says the first
+                                columns[ct] &= ~zero32[ct];
+                                tie_count += __builtin_popcount(zero32[ct]);
+                            }
                             clean[ct] = multi == 0ull;               // wave-uniform
                             // (a wavefront that is not clean may hold any bits, and its gather is issued
                             // all the same)
