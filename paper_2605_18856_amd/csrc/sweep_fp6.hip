@@ -265,12 +265,14 @@ sweep_fp6_kernel(GameView g, SweepArgs a, int row_tiles)
         if ((multi >> col) & 1u) { gmax = gm; jstar = (int)(pair & 0xFFFFu) & (N - 1); }
         return multi & ((unsigned)__builtin_amdgcn_ballot_w64((pair >> 16) != 1u) | (unsigned)(dup | (dup >> 32)));
     };
-    // The maximisers of the whole sums in ascending order: the leader's payoff decides, then the lower action.
-    auto exact_type = [&](unsigned columns, int t, float gmax, float &l_out, int &j_out) __attribute__((always_inline)) {
+    // The maximisers of the whole sums, all of them in the row tiles `need`, in ascending order: the leader's payoff
+    // decides, then the lower action.
+    auto exact_type = [&](unsigned columns, unsigned need, int t, float gmax, float &l_out, int &j_out) __attribute__((always_inline)) {
         float lbest = kNotANumber;                       // (no maximiser: no sum is a number)
         int jbest = 0, nmatch = 0;
 #pragma unroll 1
         for (int tt = 0; tt < TPG; ++tt) {
+            if (!(need >> tt & 1u)) continue;
             const f32x16 sum = whole_tile(t, tt);
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -402,7 +404,7 @@ sweep_fp6_kernel(GameView g, SweepArgs a, int row_tiles)
                 if (__builtin_amdgcn_ballot_w64((rows >> (2 * (TPG - 1 - k)) & 3u) != 0u) != 0ull) need |= 1u << k;
             if ((multi & (unsigned)__builtin_amdgcn_ballot_w64(rows == 0u)) != 0u) need = (1u << TPG) - 1u;
             exact = settle(multi, need, t, gmax, js) & valid32;
-            if (exact != 0u) exact_type(exact, t, gmax, l_exact, js);
+            if (exact != 0u) exact_type(exact, need, t, gmax, l_exact, js);
         }
         const u32x4 *from = column_of(t, js);
 #pragma unroll
