@@ -31,8 +31,8 @@ PEAK_TFLOPS = {"mfma_f32": 157.3, "mfma_bf16": 2500.0, "valu": 78.6, "valu_bf16"
                # that peak with ALGORITHMIC flops (the kernel executes 2x / 3x as many, the
                # small-game kernel 6x)
                "mfma_split3": 2500.0, "mfma_split6": 2500.0, "mfma_small_split6": 2500.0}
-# (the part products that are always summed; the others, where they may decide, add 0.3 and 2.5 % to the
-# matrix instructions of configs 5 and 3)
+# (the part products that are always summed; the others, where they may decide, add 2.5 % to the matrix
+# instructions of config 3.  Config 5's small whole numbers run on the six-bit matrix instruction instead)
 EXECUTED_FLOP_FACTOR = {"mfma_split3": 2.0, "mfma_split6": 3.0, "mfma_small_split6": 6.0}
 
 # HBM bytes per launch of the fused sweep kernel, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
@@ -43,15 +43,15 @@ TRAFFIC_BYTES = {
     "config2": (155.9 * 2.0 + 29.0) * 1024.0,          # rows generated in registers: slots and payoffs only
     "config3": (1049780.0 * 2.0 + 4097.3) * 1024.0,
     "config4": (673209.0 * 2.0 + 267.9) * 1024.0,
-    "config5": (1870280.0 * 2.0 + 48254.6) * 1024.0,
+    "config5": (1968690.0 * 2.0 + 610.8) * 1024.0,
 }
 
 # Matrix and vector instructions a wavefront alternates between in the fused sweep kernel of a
 # workload, from the rocprofv3 counters in profiles/ (SQ_INSTS_MFMA and SQ_INSTS_VALU minus it, per
 # wavefront and block of one type, rounded to the measurement's granularity of 24): config 4, one
-# pass of two candidate tiles: 32 and 2 x 140; config 5, one tile: 128 and 321.  Both keep two
-# wavefronts on a SIMD, as the loop does that measures the ceiling; config 3 keeps three.
-MIXES = {"config4": (32, 288), "config5": (128, 312)}
+# pass of two candidate tiles: 32 and 2 x 140.  It keeps two wavefronts on a SIMD, as the loop does that
+# measures the ceiling; config 3 keeps three, and config 5 does not run on the loop's bf16 instruction.
+MIXES = {"config4": (32, 288)}
 
 # workload -> (config number, candidates per step, candidates per chunk (= per launch), note)
 WORKLOADS = {
