@@ -413,7 +413,8 @@ long long any_num_blocks(const GameView &g, long long count)
     // At most one resident set, and always the whole of it: with the grid cut to the workgroups that share
     // the blocks evenly, some compute units held one workgroup and the others two (m = 16, n = 40, K = 30
     // bf16: 140000 rows 106 -> 96 us, 270000 rows 151 -> 134; m = 20, n = 12, K = 12: 400000 rows 78 -> 71).
-    // All the workgroups that the registers allow, not two a compute unit (three or four, us): the same 140000
+    // All the workgroups that the registers allow, not two a compute unit (three or four, row tiles one
+    // by one, us): the same 140000
     // rows 81 -> 70, 1000000 rows 348 -> 281; m = 12, n = 100, K = 30, 100000 rows 101 -> 89; m = 40, n = 80,
     // K = 50, 100000 rows 310 -> 261; m = 20, n = 20, K = 8, 270000 rows 51 -> 45; m = 9, n = 15, K = 20 bf16,
     // 1000000 rows 96 -> 74.
@@ -452,12 +453,13 @@ int any_shares(const GameView &g, long long count)
     // two blocks and all types side by side: uncut, the fullest one takes as many rounds as it has blocks for,
     // later ones shorter (they start one by one) and one block left over 0.8; cut, all take the same, more for
     // the outputs where a type is little work, and 12 us for another launch that sums them (the unit is about
-    // 0.09 us per type and unit of `work`).  Uncut and cut, us: m = 50, n = 100, K = 24 bf16, 50000 rows 109 and
-    // 60, 130000 rows 121 and 114; m = 30, n = 50, K = 20, 60000 rows 68 and 53, 100003 rows 74 and 76; m = 70,
-    // n = 100, K = 10 bf16, 30000 rows 58 and 42; m = 20, n = 20, K = 8, 45000 rows 31 and 25; m = 10, n = 20,
-    // K = 30, 200000 rows 66 and 85; m = 60, n = 100, K = 20, whole numbers, 60000 rows 105 and 86; m = 128,
-    // n = 255, K = 4, 30000 rows 90 and 65.  Over 49 shapes and 27 sizes the choice takes 0.7 % longer than the
-    // better one on average, and 18 % at most.
+    // 0.09 us per type and unit of `work`).  Uncut and cut, us: m = 50, n = 100, K = 24 bf16, 50000 rows 62 and
+    // 52, 200000 rows 129 and 146; m = 30, n = 50, K = 20, 50000 rows 60 and 48, 100003 rows 67 and 72; m = 30,
+    // n = 70, K = 20, whole numbers, 35000 rows 45 and 35, 140000 rows 82 and 87; m = 90, n = 100, K = 10, 70001
+    // rows 121 and 94; m = 24, n = 24, K = 20, 50000 rows 48 and 38, 140000 rows 59 and 66; m = 12, n = 90, K = 30
+    // bf16, 140000 rows 65 and 82.  Over 12 shapes of two to seven row tiles and 7 sizes from 20000 to 200000 rows the
+    // choice takes 1 % longer than the better one on average, and 17 % at most (m = 45, n = 60, K = 20 bf16, 200000
+    // rows 86, uncut 73).
     const bool many = many_kind(q, count, false);
     const int tiles = tiles_of(q, many), tiles_cut = tiles_of(q, many_kind(q, count, true)), full = side_by_side(q, count);
     const long long uncut_blocks = blocks_of(q, count, many), all = CUS * full;

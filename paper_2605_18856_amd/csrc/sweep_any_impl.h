@@ -71,7 +71,7 @@ constexpr int tiles_per_wave(int terms, int ks, int form, bool many)
 // Wavefronts per SIMD that the register allocation is held to; with one wavefront of every workgroup on each
 // SIMD also the workgroups that a compute unit holds.  These kernels are bound by vector instructions, and a
 // SIMD issues more of them the more wavefronts it chooses from (one, an instruction in 8 cycles; two, in 5.7;
-// four, in 4.9): as many as fit without spilling in the loop over the types (us, 1000000 rows: m = 45,
+// four, in 4.9): as many as fit without spilling in the loop over the types (row tiles one by one, us, 1000000 rows: m = 45,
 // n = 100, K = 24 bf16 587 with two and 442 with three; m = 60, n = 100, K = 20, three products 1039 and 830).
 constexpr int occupancy(int terms, int ks, int form, bool many)
 {
