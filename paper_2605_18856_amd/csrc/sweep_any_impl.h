@@ -85,10 +85,10 @@ constexpr int occupancy(int terms, int ks, int form, bool many)
 }
 
 // K-steps whose fragments are requested ahead of the one that is multiplied, as many as the registers hold (0: the
-// compiler's order; half-precision parts have their own).
+// compiler's order, as good with one row tile; half-precision parts have their own).
 constexpr int fragments_ahead(int terms, int ks, int form, bool many)
 {
-    if (form == 0 || form >= 8 || terms == 2) return 0;
+    if (form < 2 || form >= 8 || terms == 2) return 0;
     if (terms == 1) return form != 4 ? 3 : ks == 3 ? 0 : ks == 6 ? 1 : 3;
     return (two_kinds(terms, ks, form) && many) || (terms == 6 && ks == 4) ? 0 : 1;
 }
@@ -512,19 +512,26 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
             return;
         }
         constexpr int HERE = NARROW || WHOLE > 0 ? 0 : tile_ahead(TERMS, KS, MANY);
-        u32x4 ring[HERE + 1][PA];
+        [[maybe_unused]] u32x4 ring[HERE + 1][PA];
         auto read = [&](auto ic) __attribute__((always_inline)) {
             constexpr int i = decltype(ic)::value;
             if constexpr (i < KS)
 #pragma unroll
                 for (int p = 0; p < PA; ++p) ring[i % (HERE + 1)][p] = fr[(i * PA + p) * 64];
         };
-        static_for<0, HERE, 1>([&](auto ic) { read(ic); });
+        if constexpr (HERE > 0) static_for<0, HERE, 1>([&](auto ic) { read(ic); });
         static_for<0, KS, 1>([&](auto sc) {
             constexpr int s = decltype(sc)::value;
-            read(std::integral_constant<int, s + HERE>{});
-            if constexpr (HERE > 0) __builtin_amdgcn_sched_barrier(0);
-            u32x4 (&f)[PA] = ring[s % (HERE + 1)];
+            u32x4 f[PA];
+            if constexpr (HERE > 0) {
+                read(std::integral_constant<int, s + HERE>{});
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int p = 0; p < PA; ++p) f[p] = ring[s % (HERE + 1)][p];
+            } else {
+#pragma unroll
+                for (int p = 0; p < PA; ++p) f[p] = fr[(s * PA + p) * 64];
+            }
             auto product = [&](int pb, int px, bool first) __attribute__((always_inline)) {
                 if (s == 0 && first) {
                     f32x16 zero;
@@ -905,7 +912,18 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                                 }
                             }
                         }
-                        if constexpr (WHOLE > 0) {
+                        if constexpr (FORM == 1) {       // (by itself: as one of an array the tile costs registers)
+                            f32x16 acc[NT];
+                            tile_mfma(acc, fr, padded);
+                            settle(acc);
+#pragma unroll
+                            for (int ct = 0; ct < NT; ++ct) {
+                                float v[1][16];
+#pragma unroll
+                                for (int r = 0; r < 16; ++r) v[0][r] = acc[ct][r];
+                                best[ct] = grid_maxima<1>(v, R[ct], C[ct]);
+                            }
+                        } else if constexpr (WHOLE > 0) {
                             f32x16 acc[WHOLE][NT];
                             if constexpr (AHEAD == 0) {
 #pragma unroll
