@@ -197,6 +197,7 @@ int fp6_record_bytes();
 bool fp6_suits(int m, int n, int K, const float *A, const float *B);
 void fp6_pack(int m, int K, const float *A, const float *B, unsigned char *Bpack, unsigned short *ATpack);
 void fp6_margins(int m, int K, const float *B, float *margin);
+bool six_bit_suits(int m, int n, int K, const float *A, const float *B);         // whether they are swept by it
 
 // The share of (candidate tile, type) pairs that a filter with margin(t) sums twice, from `pairs` (8 to 64) pairs of
 // types and rows (see sweep_mfma.hip).

@@ -27,6 +27,7 @@
 #include "bsse_internal.h"
 #include "mfma_device.h"
 #include "done_device.h"
+#include <algorithm>
 #include <cmath>
 #include <limits.h>
 #include <stdlib.h>
@@ -451,6 +452,14 @@ int fp6_code(double v)
     return code | (v < 0 ? 32 : 0);
 }
 
+// a + b, and whether that is the true sum (Knuth's two-sum leaves nothing over)
+bool sum_is_exact(double a, double b, double *s)
+{
+    *s = a + b;
+    const double back = *s - a;
+    return (a - (*s - back)) + (b - back) == 0.0;
+}
+
 // The middle of the payoffs' range over the actions for each leader action of a type (mid[m]), and the power of two that
 // brings what is left to 7.5 at most.
 double type_scale(int m, const float *B, double *mid)
@@ -490,9 +499,16 @@ bool fp6_suits(int m, int n, int K, const float *A, const float *B)
         for (int i = 0; i < m * N; ++i)
             if (!half(At[i])) return false;
         const double scale = type_scale(m, Bt, mid);
-        for (int i = 0; i < m; ++i)
+        for (int i = 0; i < m; ++i) {
+            // The codes have to be the payoffs less the middle, not what 53 bits leave of them: beside a payoff of -2^60
+            // the numbers 0 to 7 are one and the same.
+            const float *row = Bt + (size_t)i * N;
+            const auto [lo, hi] = std::minmax_element(row, row + N);
+            double rest;
+            if (!sum_is_exact(*lo, *hi, &rest)) return false;
             for (int j = 0; j < N; ++j)
-                if (fp6_code((Bt[(size_t)i * N + j] - mid[i]) * scale) < 0) return false;
+                if (!sum_is_exact(row[j], -mid[i], &rest) || fp6_code(rest * scale) < 0) return false;
+        }
     }
     return true;
 }

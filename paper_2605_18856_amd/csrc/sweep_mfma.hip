@@ -1604,6 +1604,13 @@ double twice_summed(int m, int n, int K, const float *B, const std::function<flo
     return share;
 }
 
+// Games with equal columns tie in most tiles, which three parts settle sooner (every eighth column twice, K = 64, 65536
+// rows 1820 us and 2170 on the six-bit instruction).
+bool six_bit_suits(int m, int n, int K, const float *A, const float *B)
+{
+    return fp6_suits(m, n, K, A, B) && twice_summed(m, n, K, B, [](int) { return 0.0f; }, 64, true) <= 0.25;
+}
+
 // The margins grow with the payoffs, the gaps with what tells them apart: payoffs with a large part in common
 // make the filter sum most tiles twice, at the pace of one chain.  From about a quarter of them on, six
 // products sum everything at once (m = n = 32 and n = 64, K = 16, 2^20 rows, normal payoffs plus 0, 10, 30,
@@ -1616,9 +1623,7 @@ int mfma_filter(int variant, int m, int n, int K, const float *A, const float *B
 {
     if (variant < 0 || variant >= kNumVariants || !kVariants[variant].cut) return variant;
     const Variant &v = kVariants[variant];
-    // (games with equal columns tie in most tiles, which three parts settle sooner: every eighth column twice, K = 64,
-    // 65536 rows 1820 us and 2170 on the six-bit instruction)
-    if (v.terms == 3 && v.n == 256 && fp6_suits(m, n, K, A, B) && twice_summed(m, n, K, B, [](int) { return 0.0f; }, 64, true) <= 0.25) {
+    if (v.terms == 3 && v.n == 256 && six_bit_suits(m, n, K, A, B)) {
         fp6_margins(m, K, B, margin);
         for (int i = 0; i < kNumVariants; ++i)
             if (kVariants[i].fp6) return i;

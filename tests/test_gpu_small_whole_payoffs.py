@@ -6,6 +6,7 @@ import pytest
 
 from oracle import sweep as osweep
 from paper_2605_18856_amd import bsse, workloads
+from tests import kernels
 from tests.test_gpu_parity import _full_check, _make, _run_eval
 
 pytestmark = pytest.mark.gpu
@@ -94,6 +95,21 @@ def test_whole_and_cut_launches_agree():
 def _device(X):
     import torch
     return torch.from_numpy(X).cuda(), X.shape[0]
+
+
+@pytest.mark.parametrize("forbidden", [-2.0 ** 57, -2.0 ** 60])
+def test_small_payoffs_beside_a_large_one(forbidden):
+    """Payoffs 0 to 7 and an action that nobody takes: the others are still told apart (by their own size, not by the
+    large one's)."""
+    game = _game(100, 2, 0, 7, 470)
+    X = workloads.host_candidates(100, 3001, 471, "dirichlet")
+    ref = osweep.sweep(game.A, game.B, game.prior, X, diagnostics=True)
+    game.B[:, :, 17] = forbidden
+    with _make(game) as g:
+        _, _, br = _run_eval(g, X)
+    clear = (ref.gap > 1e-6 * ref.scale) & (ref.br != 17)
+    assert clear.mean() > 0.9 and np.array_equal(br[clear], ref.br[clear])
+    assert not kernels.six_bit(game)
 
 
 def test_leader_payoffs_that_are_no_half_precision_numbers():
