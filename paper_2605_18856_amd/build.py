@@ -16,7 +16,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbsse.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["bsse_api.hip", "gen_kernels.hip", "sweep_valu.hip", "sweep_tiny.hip", "sweep_mfma.hip", "sweep_any.hip", "sweep_any_terms1.hip", "sweep_any_terms3.hip", "sweep_any_terms6.hip", "sweep_any_half.hip", "sweep_fp6.hip", "sweep_small.hip", "reduce.hip", "prior_batch.hip", "profile_lp.hip", "topk.hip", "realised.hip", "ceilings.hip"]
+SOURCES = ["bsse_api.hip", "gen_kernels.hip", "sweep_valu.hip", "sweep_tiny.hip", "sweep_mfma.hip", "sweep_any.hip", "sweep_any_terms1.hip", "sweep_any_terms3.hip", "sweep_any_terms6.hip", "sweep_any_half.hip", "sweep_fp6.hip", "sweep_small.hip", "reduce.hip", "prior_batch.hip", "profile_lp.hip", "topk.hip", "realised.hip", "ceilings.hip", "matrix_unit.hip"]
 HEADERS = [os.path.join(CSRC, "bsse_internal.h"), os.path.join(CSRC, "mfma_device.h"), os.path.join(CSRC, "sweep_any_impl.h"), os.path.join(CSRC, "gen_device.h"),
            os.path.join(CSRC, "done_device.h"), os.path.join(CSRC, "topk_device.h"),
            os.path.join(os.path.dirname(HERE), "include", "bsse.h")]

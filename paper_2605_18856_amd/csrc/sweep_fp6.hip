@@ -104,8 +104,10 @@ __device__ __forceinline__ float bf16_hi(unsigned p) { return __uint_as_float(p 
 
 // Least row part of a threshold: rows so small that squares of remainders vanish have every column summed again.
 constexpr float kLeastReach = 0x1p-30f;
-// What the instructions that go on with sums of full size drop (2^-26 of the greatest of 65 terms each) and round
-// (2^-24), two of them (the first parts' k-steps), and a sixteenth for those before; in |x|_2 |B_j|_2.
+// What the instructions that go on with sums of full size lose: 2^-26 of the greatest of 65 terms each and 2^-24 of the
+// sum are counted, two of them (the first parts' k-steps) and a sixteenth for those before; in |x|_2 |B_j|_2.  Measured
+// on terms set to lose all they can, an instruction loses 5.1 2^-24 where this counts 17.25, which leaves room for second
+// parts that come to more than a sixteenth of a row (to a third where one component of a block outweighs the others).
 constexpr float kRounding = 2.125f * (65 * 0x1p-26f + 0x1p-24f);
 
 // SLICED: workgroup row blockIdx.y walks its slice of the types and writes per-type outputs (see sweep_mfma.hip).

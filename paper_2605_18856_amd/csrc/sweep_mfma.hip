@@ -1508,11 +1508,11 @@ hipError_t launch_sweep_mfma(const GameView &g, const SweepArgs &a, hipStream_t 
 // By Cauchy and Schwarz |sum_i p_i B_ij| <= |p|_2 |B_j|_2.  For six, r bounds |p0|_2,
 // 2^9 |p1|_2 and 2^18 |p2|_2, which are about equal for rows of ordinary numbers; for three, |p0|_2 / 2 and
 // 2^18 |p2|_2, and the payoffs count from the middle of their range over the actions, which no difference
-// notices.  A matrix instruction drops what is below 2^-26 of the greatest of its seventeen terms, once
-// each, and rounds once (measured with terms set for it), 2^-21.5 of its sum together: 2^-21 of
-// |x|_2 |B_j|_2 is taken for each that goes on with the sum of the others (six).  A sum of its own (three)
-// comes to 2^-16 of that, and its addition rounds to 2^-24: 2^-23 is taken.  Both payoffs of a difference
-// move: twice all that, and 2 % for the roundings of r, of a_t and of the threshold.  Rows and payoffs so
+// notices.  Matrix instructions lose at most 8 2^-24 of the sum of their absolute products, which over all k-steps is
+// |x|_2 |B_j|_2 at most, and 6 2^-24 of the sum that they go on with, each (measured with terms set for it): 2^-21 of
+// |x|_2 |B_j|_2 is taken for each that goes on with the sum of the others (six: three a k-step, two k-steps or more).
+// A sum of its own (three) comes to 2^-16 of that, and its addition rounds to 2^-24: 2^-23 is taken.  Both payoffs of a
+// difference move: twice all that, and 2 % for the roundings of r, of a_t and of the threshold.  Rows and payoffs so
 // small that parts underflow meet the two least values.
 static void filter_margins(const Variant &v, int m, int n, int K, const float *B, float *margin)
 {
