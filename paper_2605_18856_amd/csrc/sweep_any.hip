@@ -22,11 +22,24 @@ int roundup(int v, int to) { return (v + to - 1) / to * to; }
 int payoff_parts(int terms) { return terms == 6 ? 3 : terms == 2 ? 2 : 1; }
 int products(const AnyGeo &q) { return q.terms != 2 ? q.terms : q.ks == 3 ? 4 : 3; }
 
-// Two half-precision parts leave up to 2^-25 of a number whose second part is subnormal: of components and payoffs
-// below 2^-16 of the greatest of their row or type, which is scaled to 2^14 to 2^15.  In a difference of two sums that is
-// 2^-24 sqrt(m) (|x|_2 + |B_j|_2) at most, and with both norms at least 2^14 no more than this times |x|_2 |B_j|_2.
-// 2 % for the roundings of norms and threshold.
-float half_margin(int ks) { return (float)(1.02 * 0x1p-37 * std::sqrt(16.0 * ks)); }
+// Sums of half-precision parts decide only where nothing that they leave out or round can: the margin bounds, in
+// |x|_2 |B_j|_2 of a row and a type as they are scaled, what a difference of two of them is off by, by Cauchy and Schwarz.
+//   * What two parts leave of a number is 2^-23 of it at most, of a row's component and of a payoff; three products
+//     also leave out low times low part, 2^-22.
+//   * Matrix instructions lose at most 8 2^-24 of the sum of their absolute products, over all k-steps |x|_2 |B_j|_2
+//     at most, and 6 2^-24 of the sum they go on with, each (test_gpu_matrix_terms.py); the products with a small part
+//     stand at 2^-10 of the sum when they do, which the 2 % cover.
+//   * Both sums of the difference move.  The sums in 64 bits are rounded to 32 and so may tie at a distance of
+//     2 2^-24 of their size, and the threshold is rounded: three more.
+//   * Where a part is subnormal, what is left is 2^-25 at most (of components and payoffs below 2^-16 of the greatest
+//     of their row or type, which is scaled to 2^14 to 2^15): 2^-24 sqrt(m) (|x|_2 + |B_j|_2) in a difference, and
+//     with both norms at least 2^14 no more than 2^-37 sqrt(m) |x|_2 |B_j|_2.
+// 2 % for the roundings of the norms.
+float half_margin(int ks)
+{
+    const double left_out = ks == 3 ? 4.0 : 8.0, instructions = 8.0 + 6.0 * ks;
+    return (float)(1.02 * ((2.0 * (left_out + instructions) + 3.0) * 0x1p-24 + 0x1p-37 * std::sqrt(16.0 * ks)));
+}
 // Payoffs from here on may have infinite sums, which the filter's scaled ones would not show.
 constexpr float kHalfMost = 0x1p60f;
 
@@ -240,29 +253,23 @@ static float half_margin_of(int m, int n, int ks, const float *B)
     return most < kHalfMost ? (float)(half_margin(ks) * std::sqrt(*std::max_element(sum.begin(), sum.end()))) : INFINITY;
 }
 
-// Two half-precision parts hold 22 bits of a number or more, and fewer products of them come closer to the true sum
-// than six of bf16 parts, because fewer matrix instructions round: with the small products first only the last
-// k-steps do at the sum's size.  Root mean square and greatest error against 64 bits, in 2^-24 of the sum of the
-// absolute terms, six products and these (flat rows, normal payoffs): m = 33 0.41 and 3.6, four products 0.39 and
-// 2.4 (three 0.45); m = 49 0.43 and 3.7, three products 0.39 and 2.6; m = 64 0.40 and 3.6, 0.35 and 2.1; m = 128
-// 0.43 and 4.0, 0.28 and 1.8; payoffs in 0..1 m = 48 1.21 and 5.5, 0.72 and 3.0; m = 128 2.10 and 9.3, 1.01 and 4.7.
-// Up to 32 leader actions what the parts leave counts for more (m = 24 0.34 and 2.8, four products 0.43 and 2.8).
-// Where what the parts lose outright could decide, and for ties, sums in 64 bits do (half_margin, exact_actions).
-// Sixteen follower actions or fewer take their leader payoffs off the matrix cores, which nothing watches.
-// Payoffs of very different sizes (forbidden actions at -10^6) put many values within the margin, and whole numbers
-// beyond 2^22 have ties that 22 bits may not show: six products, and so in
-// games with equal columns, which tie everywhere.
+// Two half-precision parts of a number hold 22 bits or more, and fewer products of them take fewer matrix instructions
+// that round than six of bf16 parts.  Their sums decide where the greatest stands clear of the next by all that the parts
+// leave out and the instructions round (half_margin: rigorous, some hundred times what the sums are off by as a rule);
+// elsewhere sums in 64 bits, rounded once, do (exact_column, exact_actions), so that every best response is the one of
+// the true sums rounded to 32 bits.
+// Four products where m <= 48: a third k-step costs little, and the margin is half as wide.  Up to 32 leader actions six
+// products are as fast.  Sixteen follower actions or fewer take their leader payoffs off the matrix cores, which nothing
+// watches: six products.
+// Payoffs of very different sizes (forbidden actions at -10^3 beside -2 to 2), payoffs with a large part in common and
+// equal columns put many values within the margin; from about an eighth of the tiles on six products are the faster
+// ones (normal payoffs plus 10, 30, 100, m = 60, n = 100, K = 20, 200000 rows: 287, 332, 417 us, and 350, 350, 370 with
+// six; shares 0.03, 0.09, 0.27).  Payoffs from 2^60 on may have infinite sums, which the scaled ones would not show.
 bool any_half_suits(int m, int n, int K, const float *B)
 {
     if (m <= 32 || n <= 16 || !any_supported(m, n)) return false;
-    bool whole = true, large = false;
-    for (size_t e = 0; e < (size_t)K * m * n && whole; ++e) {
-        whole = std::rint(B[e]) == B[e];
-        large |= std::fabs(B[e]) > 0x1p22f;
-    }
-    if (whole && large) return false;
     const int ks = any_geometry(m, n, K, 2).ks;
-    return twice_summed(m, n, K, B, [=](int t) { return half_margin_of(m, n, ks, B + (size_t)t * m * n); }, 16, true) <= 0.25;
+    return twice_summed(m, n, K, B, [=](int t) { return half_margin_of(m, n, ks, B + (size_t)t * m * n); }, 64, true) <= 0.125;
 }
 
 bool any_supported(int m, int n) { return m <= 128 && (long long)m * n > 64; }

@@ -724,12 +724,9 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && gmax > LEAST) & valid32[ct]);
     };
 
-    // FILTER: the best responses of the candidate columns `columns`, where values are too near the maximum for the
-    // three products, by the same rule.  These once more say which actions they are (from `floor` on, in any of the
-    // columns); their sums are taken in 64 bits and rounded once, so no further from the true ones than any sum in
-    // 32.  A column's answer does not depend on the others.  Few wavefronts come here, but a short launch ends with the
-    // last of them, and all of it is cold: little code and few loads (5 us; six products of bf16 parts over all tiles
-    // and a leader's dot product for each of a tile's rows took 13).
+    // FILTER: the best responses of the candidate columns `columns`, where several values are within the margin of the
+    // maximum, by the same rule.  The half-precision sums once more say which actions they are (from `floor` on, in any of
+    // the columns); their sums are taken in 64 bits and rounded once.  For ties, and where many columns come at once.
     auto exact_actions = [&](auto ctc, unsigned columns, int t, float gm, float floor, const u32x4 *fr, int &j_out) __attribute__((always_inline)) {
         constexpr int ct = decltype(ctc)::value;
         constexpr float LEAST = -3.402823466e38f;
@@ -780,6 +777,47 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         }
         if (mine) j_out = jbest;
         tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && cur > LEAST) & columns);
+    };
+
+    // FILTER: one candidate column by the same sums (the two halves' chains in the same order), all actions of the type
+    // side by side in the lanes: an answer if one action alone has the greatest, else -1.  A column in 250 or 100 comes
+    // here, in short launches the last wavefront of them all: little code, which is cold, and a few rounds of loads (2 to
+    // 3 us where exact_actions takes 7: m = 60, n = 100, K = 20, 20000 rows 58 -> 47 us, 1000000 rows 1098 -> 1066;
+    // m = 128, n = 255, K = 4, 30000 rows 75 -> 62).
+    auto exact_column = [&](unsigned c, int t) __attribute__((always_inline)) {
+        constexpr float LEAST = -3.402823466e38f;
+        const float *row = X + (size_t)(c < count ? c : count - 1u) * m;
+        const bool first_half = lane < HALF && lane < m, second_half = lane < HALF && HALF + lane < m;
+        const float x0 = first_half ? row[first_half ? lane : 0] : 0.0f, x1 = second_half ? row[second_half ? HALF + lane : 0] : 0.0f;
+        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + q.exact_off) + (size_t)t * n * (HALF / 2);
+        float best = -INFINITY;
+        int jbest = 0;
+        bool again = false;
+        constexpr int AT_ONCE = KS >= 6 ? 2 : 1;         // (as the registers allow)
+#pragma unroll 1
+        for (int j0 = 0; j0 < n; j0 += 64) {
+            const int j = j0 + lane;
+            const f32x4 *b = payoffs + (size_t)(j < n ? j : n - 1) * (HALF / 2);
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll AT_ONCE
+            for (int e = 0; e < HALF; e += 8) {
+                const f32x4 b0[2] = { b[e / 4], b[e / 4 + 1] }, b1[2] = { b[HALF / 4 + e / 4], b[HALF / 4 + e / 4 + 1] };
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    s0 = fma((double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x0), e + k)), (double)b0[k / 4][k % 4], s0);
+                    s1 = fma((double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x1), e + k)), (double)b1[k / 4][k % 4], s1);
+                }
+            }
+            const float u = j < n ? fmaxf((float)(s0 + s1), LEAST) : -INFINITY;
+            again = u == best || (again && u < best);
+            if (u > best) { best = u; jbest = j; }
+        }
+        float most = best;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) most = fmaxf(most, __shfl_xor(most, d, 64));
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(best == most), twice = __builtin_amdgcn_ballot_w64(best == most && again);
+        const int j = __builtin_amdgcn_readlane(jbest, (int)__builtin_ctzll(at | 1ull << 63));
+        return most > LEAST && twice == 0ull && (at & (at - 1ull)) == 0ull ? j : -1;
     };
 
     int buf = 0;
@@ -1057,7 +1095,20 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             const unsigned j = WHOLE ? grid_action<WHOLE == 3 ? 4 : WHOLE ? WHOLE : 1>(both) : grid_action<2>(both) + 32u * ((both >> 16) & kUnitTiles);
                             js[ct] = j < (unsigned)n ? (int)j : 0;
                         }
-                        if constexpr (FILTER)
+                        if constexpr (FILTER) {
+                            unsigned long long few = columns[0] | (NT == 2 ? (unsigned long long)columns[NT - 1] << 32 : 0ull);
+                            if (__builtin_popcountll(few) <= 4)
+#pragma unroll 1
+                                for (; few != 0ull; few &= few - 1ull) {
+                                    const int c = __builtin_ctzll(few), j = exact_column(first + c, t);
+                                    if (j < 0) continue;
+#pragma unroll
+                                    for (int ct = 0; ct < NT; ++ct) {
+                                        if (c / 32 != ct) continue;
+                                        columns[ct] &= ~(1u << (c % 32));
+                                        js[ct] = col == c % 32 ? j : js[ct];
+                                    }
+                                }
                             static_for<0, NT, 1>([&](auto ctc) __attribute__((always_inline)) {
                                 constexpr int ct = decltype(ctc)::value;
                                 if (columns[ct] != 0u)
@@ -1065,6 +1116,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                                                   q.nq == 1 ? fr : reinterpret_cast<const u32x4 *>(records + (size_t)t * q.rec_bytes) + lane,
                                                   js[ct]);
                             });
+                        }
                         float part[NT];
                         if (q.lead_off >= 0) {
                             const lds_byte *lb = (const lds_byte *)sb + (unsigned)(ui * q.rec_bytes + q.lead_off + h * HALF * LBYTES);

@@ -6,6 +6,7 @@ import pytest
 
 from oracle import sweep as osweep
 from paper_2605_18856_amd import bsse, workloads
+from tests import kernels
 from tests.test_gpu_parity import _full_check, _make, _run_eval
 
 pytestmark = pytest.mark.gpu
@@ -40,6 +41,81 @@ def test_exact_ties(shape):
         assert rep.br_mismatch == 0
         ref = osweep.sweep(game.A, game.B, game.prior, X, diagnostics=True)
         assert out.n_tie_evals == int((ref.gap == 0).sum()) > 0
+
+
+def _unseen(game, change):
+    """change(type) for every type that the rule for half-precision parts does not sample (it takes eight evenly), so
+    that the game keeps them."""
+    assert game.K >= 16
+    for t in range(1, game.K, 2):
+        change(t)
+    assert kernels.half_parts(game)
+    return game
+
+
+def _rounded_once(game, X):
+    """Best responses on follower sums in 64 bits that are rounded to 32, by the rule: what the kernel's own sums must
+    come to wherever they decide.  And how many evaluations tie."""
+    best, ties = np.empty((len(X), game.K), np.int32), 0
+    X = X.astype(np.float64)
+    for t in range(game.K):
+        u = (X @ game.B[t].astype(np.float64)).astype(np.float32)
+        tied = u == u.max(axis=1, keepdims=True)
+        best[:, t] = np.where(tied, X @ game.A[t].astype(np.float64), -np.inf).argmax(axis=1)
+        ties += int((tied.sum(axis=1) > 1).sum())
+    return best, ties
+
+
+@pytest.mark.parametrize("shape", [(40, 24, 16), (64, 33, 16), (64, 90, 16), (96, 20, 16), (128, 70, 16), (128, 257, 16)], ids=IDS)
+def test_ties_that_need_all_bits(shape):
+    """Rows of multiples of 2^-12 and whole numbers of twelve or thirteen bits: all sums are exact, and ties hang on
+    the product of the low parts (2049/4096 and 2047/4096 against (2049, 0) and (2, 2049))."""
+    m, n, K = shape
+    rng = np.random.default_rng(360 + m + n)
+    game = workloads.small_game(m, n, K, 361, "normal")
+    game.A = rng.integers(-4000, 4000, game.A.shape).astype(np.float32)
+    game.B = rng.integers(-4000, -1999, game.B.shape).astype(np.float32)
+    X = np.zeros((K * 40, m), np.float32)
+
+    def pairs(t):
+        i, k = rng.choice(m, 2, replace=False), 2 * int(rng.integers(1024, 1060)) + 1
+        first, second, shift = rng.choice(n, 2, replace=False), rng.choice(n, 2, replace=False), 2 * int(rng.integers(40, 300))
+        game.B[t, i] = -3999.0
+        for pair in (first, second) if not set(first) & set(second) else (first,):
+            game.B[t, i, pair[0]] = (4096 - k + shift, 0)
+            game.B[t, i, pair[1]] = (shift, k)
+        X[40 * t:40 * t + 40, i] = np.array([k, 4096 - k], np.float32) / 4096
+    _unseen(game, pairs)
+    rest = X.sum(axis=1) == 0
+    X[rest] = workloads.host_candidates(m, int(rest.sum()), 362, "dyadic")
+    rep, out = _full_check(game, X, bsse.BSSE_PATH_AUTO, "mfma_split6")
+    ref = osweep.sweep(game.A, game.B, game.prior, X, diagnostics=True)
+    assert rep.br_mismatch == 0
+    assert out.n_tie_evals == int((ref.gap == 0).sum()) >= 40 * (K // 2)
+
+
+@pytest.mark.parametrize("shape", [(40, 24, 16), (60, 90, 16), (64, 33, 16), (96, 64, 16), (128, 257, 16)], ids=IDS)
+@pytest.mark.parametrize("kind", ["sparse", "vertex", "dirichlet"])
+def test_near_ties(shape, kind):
+    """Pairs of columns a few last bits apart: the responses are those of the true sums, rounded once, whatever else is
+    in the wavefront: rows by themselves have the same."""
+    m, n, K = shape
+    rng = np.random.default_rng(370 + m)
+    game = workloads.small_game(m, n, K, 371 + m, "normal")
+
+    def pairs(t):
+        half = n // 2
+        units = np.spacing(np.abs(game.B[t, :, :half])) * rng.integers(-2, 3, (m, half))
+        game.B[t, :, half:2 * half] = game.B[t, :, :half] + units.astype(np.float32)
+    _unseen(game, pairs)
+    X = workloads.host_candidates(m, 2003, 372, kind)
+    best, ties = _rounded_once(game, X)
+    with _make(game) as g:
+        Xd, _, br = _run_eval(g, X)
+        assert np.array_equal(br, best)
+        assert bsse.bsse_sweep(g, Xd, len(X)).n_tie_evals == ties > 0
+        for c in range(0, len(X), 97):
+            assert np.array_equal(_run_eval(g, X[c:c + 1])[2][0], br[c])
 
 
 @pytest.mark.parametrize("shape", [(40, 24, 2), (50, 90, 2), (128, 70, 1)], ids=IDS)
