@@ -745,6 +745,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
             for (int r = 0; r < 16; ++r) near |= acc[r] < floor ? 0u : 1u << acc_row_base(r);
             near = mine ? near << (4 * h) : 0u;
             if (__builtin_amdgcn_ballot_w64(near != 0u) == 0ull) continue;
+            const unsigned own = pair_or(near);          // a column weighs its own, whatever is near in the others
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) near |= (unsigned)__shfl_xor((int)near, d, 64);
             if (n - tt * 32 < 32) near &= (1u << (n - tt * 32)) - 1u;
@@ -764,14 +765,15 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                     sum = fma((double)xe, (double)b[e / 4][e % 4], sum);
                 }
                 const float u = fmaxf((float)(sum + __shfl_xor(sum, 32, 64)), LEAST);      // (the same in both lanes)
-                if (u > cur) { cur = u; nmatch = 0; }
-                const bool again = u == cur && nmatch > 0;
-                bool better = u == cur && nmatch == 0;
-                if (__builtin_amdgcn_ballot_w64(again && mine) != 0ull) {
+                const bool weighs = (own >> (j & 31)) & 1u;
+                if (weighs && u > cur) { cur = u; nmatch = 0; }
+                const bool equal = weighs && u == cur, again = equal && nmatch > 0;
+                bool better = equal && nmatch == 0;
+                if (__builtin_amdgcn_ballot_w64(again) != 0ull) {
                     const float l0 = pair_total(ct, half_dot(ct, lead_global(t, jbest))), l1 = pair_total(ct, half_dot(ct, lead_global(t, j)));
                     better = better || (again && l1 > l0);
                 }
-                if (u == cur) ++nmatch;
+                if (equal) ++nmatch;
                 if (better) jbest = j;
             }
         }

@@ -94,12 +94,7 @@ def test_ties_that_need_all_bits(shape):
     assert out.n_tie_evals == int((ref.gap == 0).sum()) >= 40 * (K // 2)
 
 
-@pytest.mark.parametrize("shape", [(40, 24, 16), (60, 90, 16), (64, 33, 16), (96, 64, 16), (128, 257, 16)], ids=IDS)
-@pytest.mark.parametrize("kind", ["sparse", "vertex", "dirichlet"])
-def test_near_ties(shape, kind):
-    """Pairs of columns a few last bits apart: the responses are those of the true sums, rounded once, whatever else is
-    in the wavefront: rows by themselves have the same."""
-    m, n, K = shape
+def _near_pairs(m, n, K):
     rng = np.random.default_rng(370 + m)
     game = workloads.small_game(m, n, K, 371 + m, "normal")
 
@@ -107,15 +102,53 @@ def test_near_ties(shape, kind):
         half = n // 2
         units = np.spacing(np.abs(game.B[t, :, :half])) * rng.integers(-2, 3, (m, half))
         game.B[t, :, half:2 * half] = game.B[t, :, :half] + units.astype(np.float32)
-    _unseen(game, pairs)
+    return _unseen(game, pairs)
+
+
+@pytest.mark.parametrize("shape", [(64, 24, 16), (64, 90, 16), (128, 257, 16)], ids=IDS)
+def test_rows_alone_and_among_others(shape):
+    """Two equal columns, and two more that tie with them in one row (by the product of low parts) and with each other in
+    another: the first row has the same responses by itself, beside the other one and among many."""
+    m, n, K = shape
+    game = workloads.small_game(m, n, K, 375, "normal")
+    rng = np.random.default_rng(376)
+    game.B = rng.integers(-4000, -1999, game.B.shape).astype(np.float32)
+    one, other = np.zeros((2, m), np.float32)
+    one[:2], other[0] = (2049 / 4096, 2047 / 4096), 1.0
+
+    def columns(t):
+        game.B[t, :2, :] = -3999.0
+        game.B[t, :2, 3:5] = [[2], [2049]]
+        game.B[t, :2, n - 3:n - 1] = [[2049], [0]]
+        game.A[t, :, n - 2] = 9.0
+    _unseen(game, columns)
+    rows = np.stack([one] * 3 + [other] * 3 + [one] * 64 + [other] * 64)
+    with _make(game) as g:
+        alone = _run_eval(g, one[None])[2][0]
+        assert np.all(alone[1::2] == n - 2)
+        for X in (np.stack([one, other]), np.stack([one, other] * 3), rows):
+            br = _run_eval(g, X)[2]
+            assert np.array_equal(br[X[:, 1] > 0], np.tile(alone, (int((X[:, 1] > 0).sum()), 1)))
+    X = workloads.host_candidates(m, 4001, 373, "dirichlet")
+    with _make(_near_pairs(m, n, K)) as g:
+        br = _run_eval(g, X)[2]
+        for c in range(0, len(X) - 3, 97):
+            assert np.array_equal(_run_eval(g, X[c:c + 1])[2][0], br[c])
+            assert np.array_equal(_run_eval(g, X[c:c + 3])[2], br[c:c + 3])
+
+
+@pytest.mark.parametrize("shape", [(40, 24, 16), (60, 90, 16), (64, 33, 16), (96, 64, 16), (128, 257, 16)], ids=IDS)
+@pytest.mark.parametrize("kind", ["sparse", "vertex", "dirichlet"])
+def test_near_ties(shape, kind):
+    """Pairs of columns a few last bits apart: the responses are those of the true sums, rounded once."""
+    m, n, K = shape
+    game = _near_pairs(m, n, K)
     X = workloads.host_candidates(m, 2003, 372, kind)
     best, ties = _rounded_once(game, X)
     with _make(game) as g:
         Xd, _, br = _run_eval(g, X)
         assert np.array_equal(br, best)
         assert bsse.bsse_sweep(g, Xd, len(X)).n_tie_evals == ties > 0
-        for c in range(0, len(X), 97):
-            assert np.array_equal(_run_eval(g, X[c:c + 1])[2][0], br[c])
 
 
 @pytest.mark.parametrize("shape", [(40, 24, 2), (50, 90, 2), (128, 70, 1)], ids=IDS)
