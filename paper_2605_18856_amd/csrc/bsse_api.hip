@@ -756,6 +756,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         if (use_mfma && variant == kAnyVariant) {
             // packed on the device from the payoffs as given
             g->view.any = any_geometry(m, n, K, bf ? 1 : exact ? 3 : half ? 2 : 6);
+            if (half) g->view.any.row_end = any_half_row_end(elems, B);
             size_t bb = 0, ab = 0;
             any_pack_sizes(g->view, &bb, &ab);
             float *rawA = nullptr, *rawB = nullptr, *scale = nullptr;

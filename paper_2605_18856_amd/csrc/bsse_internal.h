@@ -9,7 +9,8 @@ namespace bsse {
 // Record geometry of the any-shape matrix-core kernel (see sweep_any_impl.h).  A unit is one type
 // (forms 1, 2, 3, 4: that many row tiles, n > 16; form 0: any number) or one row tile of several types (form 8, 16: n <= 8, n <= 16).
 struct AnyGeo {
-    int terms;            // 1, 3 or 6 part products of bf16 parts; 2: three of half-precision parts
+    int terms;            // 1, 3 or 6 part products of bf16 parts; 2: three or four of half-precision parts, and behind the
+                          // records in Bpack the payoffs as given, [type][action][16 * ks], zero padded
     int ks;               // k-steps of 16 leader actions
     int form;
     int tpg;              // row tiles per type (forms 0 to 4)
@@ -23,7 +24,7 @@ struct AnyGeo {
     int buf_bytes;        // one of the two stage buffers
     int resident;         // workgroups that a compute unit holds
     int resident_cut;     // the same of the kernel for launches cut over the types
-    size_t exact_off;     // terms 2: offset in Bpack of the payoffs as given, [type][action][16 * ks], zero padded
+    int row_end;          // terms 2: rows whose greatest component has this biased exponent or more may have infinite sums
 };
 
 // Device view of one game, passed to kernels by value.  All pointers are device memory
@@ -221,8 +222,9 @@ void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes);
 // terms 2: also the filter's margins, into margin [K], and the payoffs' scales [K] (scratch).
 hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, float *margin,
                            float *scale, hipStream_t s);
-// Whether an fp32 game of this shape is swept in half-precision parts (terms 2).
+// Whether an fp32 game of this shape is swept in half-precision parts (terms 2), and AnyGeo::row_end of one that is.
 bool any_half_suits(int m, int n, int K, const float *B);
+int any_half_row_end(size_t elems, const float *B);
 hipError_t any_prepare(const GameView &g);
 const char *any_name(const AnyGeo &q);
 long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an uncut launch

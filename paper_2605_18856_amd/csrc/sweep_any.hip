@@ -40,8 +40,17 @@ float half_margin(int ks)
     const double left_out = ks == 3 ? 4.0 : 8.0, instructions = 8.0 + 6.0 * ks;
     return (float)(1.02 * ((2.0 * (left_out + instructions) + 3.0) * 0x1p-24 + 0x1p-37 * std::sqrt(16.0 * ks)));
 }
-// Payoffs from here on may have infinite sums, which the filter's scaled ones would not show.
-constexpr float kHalfMost = 0x1p60f;
+// Payoffs from here on: rows of ordinary size might have infinite sums, which scaled ones do not show.
+constexpr float kHalfMost = 0x1p100f;
+
+float greatest_of(size_t elems, const float *B)
+{
+    float most = 0.0f;
+    for (size_t e = 0; e < elems; ++e) most = std::max(most, std::fabs(B[e]));
+    return most;
+}
+// Where the payoffs behind the records begin (terms 2).
+__host__ __device__ inline size_t exact_off(const AnyGeo &q) { return (size_t)q.units * q.rec_bytes; }
 
 any_impl::any_kernel_t kernel_for(const AnyGeo &q, bool many)
 {
@@ -94,7 +103,7 @@ any_margin_kernel(int m, int n, float relative, const float *__restrict__ B, flo
     norm = greatest(norm, 1);
     if (tid == 0) {
         scale[t] = s;
-        margin[t] = most < kHalfMost ? relative * sqrtf(norm) : INFINITY;
+        margin[t] = relative * sqrtf(norm);
     }
 }
 
@@ -114,8 +123,8 @@ any_pack_kernel(AnyGeo q, int m, int n, int K, const float *__restrict__ A, cons
     const int rec16 = q.rec_bytes / 16, frag16 = q.form >= 8 ? 2 * parts * q.ks * 64 : q.tpg * parts * q.ks * 64;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
     for (size_t p = (size_t)blockIdx.x * blockDim.x + threadIdx.x; p < pieces; p += stride) {
-        if (q.terms == 2 && p >= q.exact_off / 16) {      // terms 2: the payoffs themselves behind the records
-            const size_t o = p - q.exact_off / 16, tj = o / (4 * q.ks), t = tj / n, j = tj % n;
+        if (q.terms == 2 && p >= exact_off(q) / 16) {      // terms 2: the payoffs themselves behind the records
+            const size_t o = p - exact_off(q) / 16, tj = o / (4 * q.ks), t = tj / n, j = tj % n;
             float v[4];
             for (int k = 0; k < 4; ++k) {
                 const int i = (int)(o % (4 * q.ks)) * 4 + k;
@@ -243,14 +252,12 @@ hipError_t launch_finish_rows(const FinishRowsArgs &f, hipStream_t s)
 static float half_margin_of(int m, int n, int ks, const float *B)
 {
     std::vector<double> sum((size_t)n, 0.0);
-    float most = 0.0f;
     for (int i = 0; i < m; ++i)
         for (int j = 0; j < n; ++j) {
             const float b = B[(size_t)i * n + j];
             sum[j] += (double)b * b;
-            most = std::max(most, std::fabs(b));
         }
-    return most < kHalfMost ? (float)(half_margin(ks) * std::sqrt(*std::max_element(sum.begin(), sum.end()))) : INFINITY;
+    return (float)(half_margin(ks) * std::sqrt(*std::max_element(sum.begin(), sum.end())));
 }
 
 // Two half-precision parts of a number hold 22 bits or more, and fewer products of them take fewer matrix instructions
@@ -264,12 +271,21 @@ static float half_margin_of(int m, int n, int ks, const float *B)
 // Payoffs of very different sizes (forbidden actions at -10^3 beside -2 to 2), payoffs with a large part in common and
 // equal columns put many values within the margin; from about an eighth of the tiles on six products are the faster
 // ones (normal payoffs plus 10, 30, 100, m = 60, n = 100, K = 20, 200000 rows: 287, 332, 417 us, and 350, 350, 370 with
-// six; shares 0.03, 0.09, 0.27).  Payoffs from 2^60 on may have infinite sums, which the scaled ones would not show.
+// six; shares 0.03, 0.09, 0.27).
 bool any_half_suits(int m, int n, int K, const float *B)
 {
     if (m <= 32 || n <= 16 || !any_supported(m, n)) return false;
+    if (greatest_of((size_t)K * m * n, B) >= kHalfMost) return false;
     const int ks = any_geometry(m, n, K, 2).ks;
     return twice_summed(m, n, K, B, [=](int t) { return half_margin_of(m, n, ks, B + (size_t)t * m * n); }, 64, true) <= 0.125;
+}
+
+// m <= 128 products below 2^(e - 126) 2^(b + 1) come to 2^127 at most (e, b: exponents of the row, biased, and of the
+// greatest payoff); infinities and what is no number are never below the end.
+int any_half_row_end(size_t elems, const float *B)
+{
+    const float most = greatest_of(elems, B);
+    return most > 0.0f ? std::min(255, 246 - std::ilogb(most)) : 255;
 }
 
 bool any_supported(int m, int n) { return m <= 128 && (long long)m * n > 64; }
@@ -327,7 +343,6 @@ AnyGeo any_geometry(int m, int n, int K, int terms)
     } else {
         q.buf_bytes = q.stt * q.tile_bytes;
     }
-    if (terms == 2) q.exact_off = (size_t)q.units * q.rec_bytes;
     q.resident = std::max(2, std::min(waves, 160 * 1024 / (2 * q.buf_bytes + 1024)));
     q.resident_cut = terms == 1 ? q.resident : std::min(q.resident, any_impl::occupancy(terms, q.ks, q.form, false));
     return q;

@@ -414,17 +414,18 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         for (int ct = 0; ct < NT; ++ct) {
             valid32[ct] = (unsigned)__builtin_amdgcn_ballot_w64(first + ct * 32 + col < count);
             float scale = 1.0f;
+            [[maybe_unused]] float rest = 1.0f;
             if constexpr (FILTER) {
-                // the greatest component comes to 2^14 or more: what the parts leave of smaller ones is below
-                // 2^-39 of it.  Rows near the ends of fp32 (and rows of zeros) are not for the filter.
+                // the greatest component comes to 2^14 or more: what the parts leave of smaller ones is below 2^-39 of
+                // it.  Rows that may have infinite sums are not for the filter.
                 float most = 0.0f;
 #pragma unroll
                 for (int e = 0; e < HALF; ++e) most = fmaxf(most, fabsf(raw[ct][e]));
                 most = fmaxf(most, pair_other(most, partner_addr));
-                const unsigned e = __float_as_uint(most) >> 23;
-                const bool fits = e >= 67u && e < 187u;              // 2^-60 to 2^60
-                scale = __uint_as_float((fits ? 268u - e : 127u) << 23);
-                norm[ct] = fits ? 0.0f : INFINITY;
+                const int shift = 15 - __builtin_amdgcn_frexp_expf(most);      // (in two factors: 2^163 for the smallest)
+                rest = shift > 64 ? 0x1p64f : 1.0f;
+                scale = __builtin_ldexpf(1.0f, shift > 64 ? shift - 64 : shift);
+                norm[ct] = (int)(__float_as_uint(most) >> 23) < late()->g.any.row_end ? 0.0f : INFINITY;
                 bool zero = true;                        // (not from `most`, which passes over what is no number)
 #pragma unroll
                 for (int k = 0; k < HALF; ++k) zero = zero && !(h * HALF + k < m && raw[ct][k] != 0.0f);
@@ -446,7 +447,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                 if constexpr (XF) { xf[ct][e] = va; xf[ct][e + 1] = vb; }
                 if constexpr (XP == 3) { va *= scale; vb *= scale; }
                 if constexpr (FILTER) {
-                    va *= scale; vb *= scale;
+                    va = va * scale * rest; vb = vb * scale * rest;
                     norm[ct] = fmaf(va, va, fmaf(vb, vb, norm[ct]));
                     const unsigned p = pack_half(va, vb);
                     x[ct][0][k] = p;
@@ -724,6 +725,23 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && gmax > LEAST) & valid32[ct]);
     };
 
+    // FILTER: what the sums in 64 bits of a row with greatest component `most` are multiplied with before they are rounded:
+    // those of a row below 2^-60 do not end as subnormal numbers (the six products split such rows 2^64 times greater).
+    constexpr float kTinyRow = 0x1p-60f;
+    auto rounded_up = [](float most) __attribute__((always_inline)) { return most < kTinyRow ? 0x1p64f : 1.0f; };
+    auto wave_max = [](float v) __attribute__((always_inline)) {      // (in the last lane, then in all)
+        auto from = [&](auto lanes, auto rows) __attribute__((always_inline)) {
+            const int u = (int)__float_as_uint(v);
+            v = fmaxf(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(u, u, decltype(lanes)::value, decltype(rows)::value, 0xf, false)));
+        };
+        from(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});      // one, two, four and eight lanes before,
+        from(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+        from(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+        from(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+        from(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});      // the last lane of the row before,
+        from(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});      // lane 31
+        return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
+    };
     // FILTER: the best responses of the candidate columns `columns`, where several values are within the margin of the
     // maximum, by the same rule.  The half-precision sums once more say which actions they are (from `floor` on, in any of
     // the columns); their sums are taken in 64 bits and rounded once.  For ties, and where many columns come at once.
@@ -732,7 +750,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         constexpr float LEAST = -3.402823466e38f;
         const bool mine = (columns >> col) & 1u;
         if (!(gm > LEAST)) floor = -INFINITY;            // (nothing but minus infinity and no numbers: every action)
-        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + q.exact_off) + (size_t)t * n * (HALF / 2);
+        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + (size_t)q.units * q.rec_bytes) + (size_t)t * n * (HALF / 2);
         float cur = LEAST;
         int jbest = 0, nmatch = 0;
 #pragma unroll 1
@@ -755,6 +773,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                 const f32x4 *b = payoffs + (size_t)j * (HALF / 2);
                 b += h * (HALF / 4);
                 double sum = 0.0;
+                float most = 0.0f;
 #pragma unroll
                 for (int e = 0; e < HALF; ++e) {
                     // (laundered, and eight at a time: numbers in 64 bits kept across the loop, or all payoffs at once, would
@@ -762,9 +781,11 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                     if (e % 8 == 0) __builtin_amdgcn_sched_barrier(0);
                     float xe = xf[ct][XF ? e : 0];
                     asm volatile("" : "+v"(xe));
+                    most = fmaxf(most, fabsf(xe));
                     sum = fma((double)xe, (double)b[e / 4][e % 4], sum);
                 }
-                const float u = fmaxf((float)(sum + __shfl_xor(sum, 32, 64)), LEAST);      // (the same in both lanes)
+                const float up = rounded_up(fmaxf(most, pair_other(most, partner_addr)));
+                const float u = fmaxf((float)((sum + __shfl_xor(sum, 32, 64)) * (double)up), LEAST);      // (the same in both lanes)
                 const bool weighs = (own >> (j & 31)) & 1u;
                 if (weighs && u > cur) { cur = u; nmatch = 0; }
                 const bool equal = weighs && u == cur, again = equal && nmatch > 0;
@@ -791,7 +812,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         const float *row = X + (size_t)(c < count ? c : count - 1u) * m;
         const bool first_half = lane < HALF && lane < m, second_half = lane < HALF && HALF + lane < m;
         const float x0 = first_half ? row[first_half ? lane : 0] : 0.0f, x1 = second_half ? row[second_half ? HALF + lane : 0] : 0.0f;
-        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + q.exact_off) + (size_t)t * n * (HALF / 2);
+        const float up = rounded_up(__builtin_amdgcn_ballot_w64(fmaxf(fabsf(x0), fabsf(x1)) >= kTinyRow) != 0ull ? kTinyRow : 0.0f);
+        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + (size_t)q.units * q.rec_bytes) + (size_t)t * n * (HALF / 2);
         float best = -INFINITY;
         int jbest = 0;
         bool again = false;
@@ -810,13 +832,11 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                     s1 = fma((double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x1), e + k)), (double)b1[k / 4][k % 4], s1);
                 }
             }
-            const float u = j < n ? fmaxf((float)(s0 + s1), LEAST) : -INFINITY;
+            const float u = j < n ? fmaxf((float)((s0 + s1) * (double)up), LEAST) : -INFINITY;
             again = u == best || (again && u < best);
             if (u > best) { best = u; jbest = j; }
         }
-        float most = best;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) most = fmaxf(most, __shfl_xor(most, d, 64));
+        const float most = wave_max(best);
         const unsigned long long at = __builtin_amdgcn_ballot_w64(best == most), twice = __builtin_amdgcn_ballot_w64(best == most && again);
         const int j = __builtin_amdgcn_readlane(jbest, (int)__builtin_ctzll(at | 1ull << 63));
         return most > LEAST && twice == 0ull && (at & (at - 1ull)) == 0ull ? j : -1;
@@ -1102,7 +1122,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             if (__builtin_popcountll(few) <= 4)
 #pragma unroll 1
                                 for (; few != 0ull; few &= few - 1ull) {
-                                    const int c = __builtin_ctzll(few), j = exact_column(first + c, t);
+                                    const int c = __builtin_ctzll(few);
+                                    const int j = exact_column(first + c, t);
                                     if (j < 0) continue;
 #pragma unroll
                                     for (int ct = 0; ct < NT; ++ct) {

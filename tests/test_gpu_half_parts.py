@@ -184,6 +184,42 @@ def test_powers_of_two_change_nothing(shape):
     assert all(np.array_equal(seen[0], s) for s in seen[1:])
 
 
+@pytest.mark.parametrize("shape", [(40, 24, 16), (64, 90, 16), (128, 257, 16)], ids=IDS)
+def test_near_ties_of_rows_of_any_size(shape):
+    """Sums within the margin and exact ties of rows times powers of two, down to subnormal numbers (rows are multiples of
+    2^-9): as many ties, and the same responses while the leader's payoffs, which decide the ties, are no subnormal ones."""
+    m, n, K = shape
+    game = _near_pairs(m, n, K)
+    game.B[1, :, 5] = game.B[1, :, 4]
+    X = workloads.host_candidates(m, 1003, 381, "dirichlet")
+    X = np.ldexp(np.round(np.ldexp(X, 9)), -9).astype(np.float32)
+    with _make(game) as g:
+        Xd, _, br = _run_eval(g, X)
+        ties = bsse.bsse_sweep(g, Xd, len(X)).n_tie_evals
+        assert ties > 0
+        for power in (-140, -120, -100, -62, -58, 40, 62, 90, 110):
+            Xd, _, scaled = _run_eval(g, np.ldexp(X, power).astype(np.float32))
+            assert power < -110 or np.array_equal(br, scaled), power
+            assert bsse.bsse_sweep(g, Xd, len(X)).n_tie_evals == ties, power
+
+
+@pytest.mark.parametrize("shape", [(40, 24, 16), (64, 90, 16), (128, 257, 16)], ids=IDS)
+def test_rows_and_types_of_zeros(shape):
+    """Rows of zeros, types whose payoffs are all zero, and both at once: every action ties, the first one is reported
+    where the leader's payoffs tie too."""
+    m, n, K = shape
+    game = workloads.small_game(m, n, K, 385, "normal")
+
+    def zeros(t):
+        game.B[t] = 0.0
+    _unseen(game, zeros)
+    X = workloads.host_candidates(m, 500, 386, "dirichlet")
+    X[::3] = 0.0
+    rep, out = _full_check(game, X, bsse.BSSE_PATH_AUTO, "mfma_split6")
+    ref = osweep.sweep(game.A, game.B, game.prior, X, diagnostics=True)
+    assert rep.br_mismatch == 0 and out.n_tie_evals == int((ref.gap == 0).sum()) > 0
+
+
 def test_whole_and_cut_launches_agree():
     game = workloads.small_game(50, 60, 6, 340, "normal")
     game.B[:, :, 59] = game.B[:, :, 58]
