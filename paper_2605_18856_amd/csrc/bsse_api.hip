@@ -707,6 +707,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         g->won_x.resize((size_t)m); g->won_br.resize((size_t)K);
     } catch (...) { delete g; return fail(BSSE_ENOMEM, "host allocation failed"); }
     g->view.variant = variant;
+    if (mfma_is_six_bit(variant)) g->view.any.row_end = row_end_of(elems, B);
 
     DeviceGuard dg(dev);
     if (!dg.ok) { free_game(g); return fail(BSSE_EDEVICE, "hipSetDevice(%d) failed", dev); }
@@ -756,7 +757,7 @@ extern "C" bsse_status bsse_create_ex(int m, int n, int K, const float *A, const
         if (use_mfma && variant == kAnyVariant) {
             // packed on the device from the payoffs as given
             g->view.any = any_geometry(m, n, K, bf ? 1 : exact ? 3 : half ? 2 : 6);
-            if (half) g->view.any.row_end = any_half_row_end(elems, B);
+            if (half) g->view.any.row_end = row_end_of(elems, B);
             size_t bb = 0, ab = 0;
             any_pack_sizes(g->view, &bb, &ab);
             float *rawA = nullptr, *rawB = nullptr, *scale = nullptr;

@@ -24,7 +24,7 @@ struct AnyGeo {
     int buf_bytes;        // one of the two stage buffers
     int resident;         // workgroups that a compute unit holds
     int resident_cut;     // the same of the kernel for launches cut over the types
-    int row_end;          // terms 2: rows whose greatest component has this biased exponent or more may have infinite sums
+    int row_end;          // terms 2, and the six-bit kernel: rows whose greatest component has this biased exponent or more may have infinite sums
 };
 
 // Device view of one game, passed to kernels by value.  All pointers are device memory
@@ -195,6 +195,7 @@ int mfma_filter(int variant, int m, int n, int K, const float *A, const float *B
 typedef void (*sweep_fn_t)(GameView, SweepArgs, int);
 sweep_fn_t fp6_kernel(bool sliced);
 int fp6_record_bytes();
+bool mfma_is_six_bit(int variant);
 bool fp6_suits(int m, int n, int K, const float *A, const float *B);
 void fp6_pack(int m, int K, const float *A, const float *B, unsigned char *Bpack, unsigned short *ATpack);
 void fp6_margins(int m, int K, const float *B, float *margin);
@@ -222,9 +223,10 @@ void any_pack_sizes(const GameView &g, size_t *Bbytes, size_t *ATbytes);
 // terms 2: also the filter's margins, into margin [K], and the payoffs' scales [K] (scratch).
 hipError_t launch_any_pack(const GameView &g, const float *A, const float *B, void *Bpack, void *ATpack, float *margin,
                            float *scale, hipStream_t s);
-// Whether an fp32 game of this shape is swept in half-precision parts (terms 2), and AnyGeo::row_end of one that is.
+// Whether an fp32 game of this shape is swept in half-precision parts (terms 2).
 bool any_half_suits(int m, int n, int K, const float *B);
-int any_half_row_end(size_t elems, const float *B);
+// AnyGeo::row_end of a game (m <= 128).
+int row_end_of(size_t elems, const float *B);
 hipError_t any_prepare(const GameView &g);
 const char *any_name(const AnyGeo &q);
 long long any_num_blocks(const GameView &g, long long count);     // workgroups (= records) of an uncut launch

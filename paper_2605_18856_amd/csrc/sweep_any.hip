@@ -282,7 +282,7 @@ bool any_half_suits(int m, int n, int K, const float *B)
 
 // m <= 128 products below 2^(e - 126) 2^(b + 1) come to 2^127 at most (e, b: exponents of the row, biased, and of the
 // greatest payoff); infinities and what is no number are never below the end.
-int any_half_row_end(size_t elems, const float *B)
+int row_end_of(size_t elems, const float *B)
 {
     const float most = greatest_of(elems, B);
     return most > 0.0f ? std::min(255, 246 - std::ilogb(most)) : 255;

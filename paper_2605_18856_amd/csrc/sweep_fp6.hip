@@ -102,8 +102,6 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 __device__ __forceinline__ float bf16_lo(unsigned p) { return __uint_as_float(p << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned p) { return __uint_as_float(p & 0xFFFF0000u); }
 
-// Least row part of a threshold: rows so small that squares of remainders vanish have every column summed again.
-constexpr float kLeastReach = 0x1p-30f;
 // What the instructions that go on with sums of full size lose: 2^-26 of the greatest of 65 terms each and 2^-24 of the
 // sum are counted, two of them (the first parts' k-steps) and a sixteenth for those before; in |x|_2 |B_j|_2.  Measured
 // on terms set to lose all they can, an instruction loses 5.1 2^-24 where this counts 17.25, which leaves room for second
@@ -147,29 +145,34 @@ sweep_fp6_kernel(GameView g, SweepArgs a, int row_tiles)
     const long long c = wave_base + col;
     const bool ok = c < a.count;                         // (past the end: the last row again)
     const unsigned valid32 = (unsigned)__builtin_amdgcn_ballot_w64(ok);
-    float xf[HALF], reach;
+    float xf[HALF], reach, scale = 1.0f;                 // scale: of the row in its parts (leader payoffs take it as given)
     u32x6 x[KS][PARTS];
     int scales[KS];
     {
         load_half_row<HALF>(a.X + (ok ? c : a.count - 1) * (long long)m, h, m, xf);
+        // The greatest component comes to 1 to 2 (2^-24 for the smallest numbers), so that rows of any size are alike, but
+        // for those whose sums may be infinite, which are not for the parts.
+        float row_most = 0.0f;
+#pragma unroll
+        for (int e = 0; e < HALF; ++e) row_most = fmaxf(row_most, fabsf(xf[e]));
+        row_most = pair_max(row_most);
+        const bool fits = (int)(__float_as_uint(row_most) >> 23) < g.any.row_end;
+        const int up = 1 - __builtin_amdgcn_frexp_expf(row_most);
+        if (fits) scale = __builtin_ldexpf(1.0f, up > 126 ? 126 : up < -126 ? -126 : up);
         float left = 0.0f, square = 0.0f;
-        bool fits = true;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            float most = 0.0f;
+            float r[32], most = 0.0f;
 #pragma unroll
             for (int e = 0; e < 32; ++e) {
-                most = fmaxf(most, fabsf(xf[32 * s + e]));
-                square = fmaf(xf[32 * s + e], xf[32 * s + e], square);
+                r[e] = xf[32 * s + e] * scale;
+                most = fmaxf(most, fabsf(r[e]));
+                square = fmaf(r[e], r[e], square);
             }
-            // (blocks below 2^-90 have parts of zero and are all remainder; rows beyond 2^60 are not for the parts)
+            // (blocks below 2^-90 have parts of zero and are all remainder)
             int ex = (int)(__float_as_uint(most) >> 23) - 1;             // biased exponent of the block's unit
-            fits = fits && ex < 187;
             ex = ex < 37 ? 37 : ex > 187 ? 187 : ex;
             scales[s] = ex | (ex - 5) << 8 | (ex - 10) << 16 | (ex - 15) << 24;
-            float r[32];
-#pragma unroll
-            for (int e = 0; e < 32; ++e) r[e] = xf[32 * s + e];
 #pragma unroll
             for (int p = 0; p < PARTS; ++p) {
                 const float unit = __uint_as_float((unsigned)(ex - 5 * p) << 23);
@@ -182,8 +185,7 @@ sweep_fp6_kernel(GameView g, SweepArgs a, int row_tiles)
             for (int e = 0; e < 32; ++e) left = fmaf(r[e], r[e], left);
         }
         left = pair_sum(left); square = pair_sum(square);
-        reach = fmaxf(__builtin_amdgcn_sqrtf(left) + kRounding * __builtin_amdgcn_sqrtf(square), kLeastReach);
-        if (__builtin_amdgcn_ds_bpermute(4 * (lane ^ 32), fits) == 0 || !fits) reach = INFINITY;
+        reach = fits ? __builtin_amdgcn_sqrtf(left) + kRounding * __builtin_amdgcn_sqrtf(square) : INFINITY;
     }
 
     // The lane's half of the row against its half of a leader column: two fp32 chains.
@@ -225,6 +227,7 @@ sweep_fp6_kernel(GameView g, SweepArgs a, int row_tiles)
                     float va = xf[32 * s + 8 * k + 2 * e], vb = xf[32 * s + 8 * k + 2 * e + 1];
                     // (laundered: parts formed outside the loops would take the registers of the main path)
                     asm volatile("" : "+v"(va), "+v"(vb));
+                    va *= scale; vb *= scale;
                     p[0][e] = pack_bf16(va, vb);
                     const float ra = va - bf16_lo(p[0][e]), rb = vb - bf16_hi(p[0][e]);
                     p[1][e] = pack_bf16(ra, rb);

@@ -1360,6 +1360,7 @@ const char *mfma_variant_name(int variant)
     return (variant >= 0 && variant < kNumVariants) ? kVariants[variant].name : "";
 }
 
+bool mfma_is_six_bit(int variant) { return variant >= 0 && variant < kNumVariants && kVariants[variant].fp6; }
 bool mfma_is_small(int variant) { return variant == kSmallVariant; }
 
 long long mfma_num_blocks(int variant, long long count)

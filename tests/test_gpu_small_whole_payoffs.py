@@ -66,6 +66,28 @@ def test_powers_of_two_change_nothing(power):
         assert np.all((scaled >= 0) & (scaled < N))
 
 
+@pytest.mark.parametrize("rows, payoffs", [(-140, 0), (-60, -60), (0, -100), (120, -100), (127, -90), (100, 20)])
+def test_rows_and_payoffs_of_any_size(rows, payoffs):
+    """The same best responses and ties from rows of multiples of 2^-9 whatever the powers of two, also where rows beyond
+    2^118 meet payoffs that are scaled up (the leader's payoffs are large enough not to become subnormal)."""
+    game = _game(100, 2, 0, 7, 435)
+    X = workloads.host_candidates(100, 1003, 436, "dirichlet")
+    X = np.ldexp(np.round(np.ldexp(X, 9)), -9).astype(np.float32)
+    if rows < -100:
+        game.A = (2.0 ** 14 * np.clip(game.A, -3, 3)).astype(np.float32)
+    elif rows > 110:
+        game.A = (2.0 ** -14 * game.A).astype(np.float32)
+    with _make(game) as g:
+        Xd, _, br = _run_eval(g, X)
+        ties = bsse.bsse_sweep(g, Xd, len(X)).n_tie_evals
+    game.B = np.ldexp(game.B, payoffs).astype(np.float32)
+    assert kernels.six_bit(game)
+    with _make(game) as g:
+        Xd, _, scaled = _run_eval(g, np.ldexp(X, rows).astype(np.float32))
+        assert bsse.bsse_sweep(g, Xd, len(X)).n_tie_evals == ties > 0
+    assert np.array_equal(br, scaled)
+
+
 def test_small_components_decide():
     """Nearly all of a row on leader actions where all payoffs are equal: the remainder decides."""
     game = _game(128, 2, 0, 7, 440)
