@@ -88,6 +88,25 @@ def test_rows_and_payoffs_of_any_size(rows, payoffs):
     assert np.array_equal(br, scaled)
 
 
+@pytest.mark.parametrize("spread", [0, 3, 6, 9])
+@pytest.mark.parametrize("bits", [4, 6, 9])
+def test_rows_with_exact_sums(spread, bits):
+    """Rows of whole numbers of a few bits, blocks of 32 components up to 2^-spread smaller: with few bits two parts hold
+    them and their sums tie exactly or not at all, with more they do not.  Equal columns in the types that the rule for
+    the six-bit kernel does not sample."""
+    m, K = 120, 16
+    game = _game(m, K, 0, 7, 437)
+    game.B[1::2, :, 1::4] = game.B[1::2, :, 0::4]
+    assert kernels.six_bit(game)
+    rng = np.random.default_rng(438 + spread + bits)
+    X = rng.integers(0, 2 ** bits, (601, m)) * (rng.random((601, m)) < 0.3)
+    X = X * np.repeat(np.ldexp(1.0, -rng.integers(0, spread + 1, (601, 4))), 32, axis=1)[:, :m]
+    X = np.ldexp(X, -bits - 4).astype(np.float32)
+    rep, out = _full_check(game, X, bsse.BSSE_PATH_AUTO, "mfma_split3")
+    ref = osweep.sweep(game.A, game.B, game.prior, X, diagnostics=True)
+    assert rep.br_mismatch == 0 and out.n_tie_evals == int((ref.gap == 0).sum()) > 601
+
+
 def test_small_components_decide():
     """Nearly all of a row on leader actions where all payoffs are equal: the remainder decides."""
     game = _game(128, 2, 0, 7, 440)
