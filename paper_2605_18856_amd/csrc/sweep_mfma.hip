@@ -666,8 +666,8 @@ sweep_mfma_kernel(GameView g, SweepArgs a, int row_tiles)
     // (ties: the candidate columns without a unique maximiser, per tile)
     // READ_AHEAD: the column at the best response is requested as soon as that is known, and met after the
     // arg-max of the other candidate tile: fetch and meet.  (m = n = 32, K = 16, 2^22 rows 600 -> 590 us; n = 64, 2^20
-    // rows 267 -> 262; m = 16, n = 32 bf16 85 -> 83.  Three products spill.)
-    constexpr bool READ_AHEAD = N >= 32 && AT_LDS && TERMS != 3 && std::is_same<T, __bf16>::value;
+    // rows 267 -> 262; m = 16, n = 32 bf16 85 -> 83.  Three products spill; with one tile there is no other.)
+    constexpr bool READ_AHEAD = NT > 1 && N >= 32 && AT_LDS && TERMS != 3 && std::is_same<T, __bf16>::value;
     constexpr int COL16 = READ_AHEAD ? (LEAD_F32 ? HALF_BASE / 4 : HALF / 8) : 1;       // 16-byte pieces of a lane's half
     auto fetch = [&](int ti, int js, const lds_byte *at_lds, u32x4 (&column)[COL16]) __attribute__((always_inline)) {
         const auto *p = (const __attribute__((address_space(3))) u32x4 *)(
