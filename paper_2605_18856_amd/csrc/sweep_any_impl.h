@@ -566,7 +566,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
             if constexpr (HERE > 0) __builtin_amdgcn_sched_barrier(0);
         });
     };
-    // All row tiles of a type at once (FORM 1 to 4), in the same order.  The fragments of AHEAD k-steps are under way
+    // All row tiles of a type at once (FORM 2 to 4), in the same order.  The fragments of AHEAD k-steps are under way
     // while one is multiplied, in the order written: left to the compiler, which saves registers, every matrix
     // instruction waited for a read of LDS issued just before it (us: m = 50, n = 100, K = 24 bf16, 300000 rows 182 and
     // 173, 70001 rows 71.5 and 69.8; m = 90, n = 80, K = 10 bf16 118 and 112; m = 60, n = 40, K = 20, whole numbers,
@@ -991,19 +991,15 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             } else {
                                 whole_mfma(acc, fr);
                             }
-                            if constexpr (WHOLE == 1) {
-                                settle(acc[0]);
-                            } else {                     // (one wait for all of them)
-                                constexpr int LAST = WHOLE - 1;
-                                __builtin_amdgcn_sched_barrier(0);
-                                if constexpr (WHOLE * NT == 2) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[LAST][0]));
-                                else if constexpr (NT == 2)
-                                    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[0][NT - 1]), "+v"(acc[LAST][0]), "+v"(acc[LAST][NT - 1]));
-                                else if constexpr (WHOLE == 3)
-                                    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[LAST][0]));
-                                else
-                                    asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[LAST - 1][0]), "+v"(acc[LAST][0]));
-                            }
+                            constexpr int LAST = WHOLE - 1;      // (one wait for all of them)
+                            __builtin_amdgcn_sched_barrier(0);
+                            if constexpr (WHOLE * NT == 2) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[LAST][0]));
+                            else if constexpr (NT == 2)
+                                asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[0][NT - 1]), "+v"(acc[LAST][0]), "+v"(acc[LAST][NT - 1]));
+                            else if constexpr (WHOLE == 3)
+                                asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[LAST][0]));
+                            else
+                                asm volatile("s_nop 15\n\ts_nop 3" : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[LAST - 1][0]), "+v"(acc[LAST][0]));
 #pragma unroll
                             for (int ct = 0; ct < NT; ++ct) {
                                 float v[WHOLE][16];
