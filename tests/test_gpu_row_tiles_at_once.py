@@ -5,6 +5,7 @@ import pytest
 
 from oracle import sweep as osweep
 from paper_2605_18856_amd import bsse, workloads
+from tests import kernels
 from tests.test_gpu_parity import _full_check
 
 pytestmark = pytest.mark.gpu
@@ -38,6 +39,7 @@ def test_ties_here_and_there(shape, kind):
     game.B[:, 0, 3] = 4095.0
     game.B[:, 1:, 3] = -4001.0
     game.B[:, :, n - 1] = game.B[:, :, 3]
+    assert kernels.half_parts(game) == (m > 32)
     X = workloads.host_candidates(m, 3001, 412, kind)
     X[::7] = 0.0
     X[::7, 0] = 1.0

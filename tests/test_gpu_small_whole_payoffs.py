@@ -24,16 +24,19 @@ def _game(m, K, low, high, seed, step=1.0):
 @pytest.mark.parametrize("m", [3, 31, 64, 65, 97, 127, 128])
 @pytest.mark.parametrize("count", [1, 129, 3001, 40001])
 def test_rows_of_any_length(m, count):
-    K = 3 if count < 40000 else 1
-    rep, _ = _full_check(_game(m, K, 0, 7, 400 + m), workloads.host_candidates(m, count, 401, "dirichlet"), bsse.BSSE_PATH_AUTO, "mfma_split3")
+    game = _game(m, 3 if count < 40000 else 1, 0, 7, 400 + m)
+    assert kernels.six_bit(game)
+    rep, _ = _full_check(game, workloads.host_candidates(m, count, 401, "dirichlet"), bsse.BSSE_PATH_AUTO, "mfma_split3")
     assert rep.br_mismatch == rep.flagged
 
 
 @pytest.mark.parametrize("low, high, step", [(0, 1, 1.0), (0, 15, 1.0), (-7, 7, 0.25), (100, 107, 1.0), (-3, 12, 2.0 ** 40), (0, 16, 1.0),
                                              (0, 100, 1.0), (5, 5, 1.0)])
 def test_spans_of_payoffs(low, high, step):
-    """Spans up to fifteen steps fit (their middle is taken off), wider ones stay on bf16 parts; equal payoffs tie."""
+    """Spans up to sixteen steps fit (their middle is taken off), wider ones stay on bf16 parts, and so do equal payoffs,
+    which tie."""
     game = _game(100, 2, low, high, 410 + high, step)
+    assert kernels.six_bit(game) == (0 < high - low <= 16)
     rep, out = _full_check(game, workloads.host_candidates(100, 3001, 411, "dirichlet"), bsse.BSSE_PATH_AUTO, "mfma_split3")
     assert rep.br_mismatch == rep.flagged
     if low == high:
@@ -44,6 +47,7 @@ def test_spans_of_payoffs(low, high, step):
 def test_exact_ties(kind):
     game = _game(90, 3, 0, 7, 420)
     game.B[:, :, 1::8] = game.B[:, :, 0::8]
+    assert kernels.six_bit(game)
     X = workloads.host_candidates(90, 2003, 421, kind)
     rep, out = _full_check(game, X, bsse.BSSE_PATH_AUTO, "mfma_split3")
     assert rep.br_mismatch == 0
@@ -54,6 +58,7 @@ def test_exact_ties(kind):
 @pytest.mark.parametrize("power", [-140, -100, -70, -30, 40, 70, 110])
 def test_powers_of_two_change_nothing(power):
     game = _game(128, 2, 0, 7, 430)
+    assert kernels.six_bit(game)
     X = workloads.host_candidates(128, 1003, 431, "dirichlet")
     X = np.where(X < 2.0 ** -9, 0.0, X).astype(np.float32)
     X = np.float32(2.0 ** -9) * np.round(X * 2.0 ** 9).astype(np.float32)       # (still exact as subnormal numbers)
@@ -111,6 +116,7 @@ def test_small_components_decide():
     """Nearly all of a row on leader actions where all payoffs are equal: the remainder decides."""
     game = _game(128, 2, 0, 7, 440)
     game.B[:, :64] = 3.0
+    assert kernels.six_bit(game)
     for small in (-10, -17, -25):
         X = workloads.host_candidates(128, 2003, 441, "dirichlet").astype(np.float64)
         X[:, 64:] *= 2.0 ** small
@@ -122,6 +128,7 @@ def test_small_components_decide():
 def test_whole_and_cut_launches_agree():
     game = _game(128, 40, 0, 7, 450)
     game.B[:, :, 255] = game.B[:, :, 254]
+    assert kernels.six_bit(game)
     X = workloads.host_candidates(128, 140001, 451, "dirichlet")
     with _make(game) as g:
         whole = bsse.bsse_sweep(g, *_device(X))
@@ -157,4 +164,5 @@ def test_leader_payoffs_that_are_no_half_precision_numbers():
     """Those keep the bf16 parts of the general kernel."""
     game = _game(70, 2, 0, 7, 460)
     game.A[0, 0, 0] = 2.0 ** 17
+    assert not kernels.six_bit(game)
     _full_check(game, workloads.host_candidates(70, 1001, 461, "dirichlet"), bsse.BSSE_PATH_AUTO, "mfma_split3")

@@ -31,3 +31,23 @@ def test_spans_that_fit(low, high, step, fits):
     game = _wide(1)
     game.B = (step * np.random.default_rng(501).integers(low, high + 1, game.B.shape)).astype(np.float32)
     assert kernels.six_bit(game) == fits
+
+
+@pytest.mark.parametrize("change, fits", [(lambda B: B, True), (lambda B: B + 1000.0, False), (lambda B: np.where(np.arange(50) % 4, B, -1e6), False),
+                                          (lambda B: np.repeat(B[:, :, ::2], 2, axis=2), False), (lambda B: B * 2.0 ** 101, False),
+                                          (lambda B: np.round(B * 2.0 ** 22), True), (lambda B: 0.0 * B, False)],
+                         ids=["as drawn", "in common", "forbidden", "twice", "large", "whole numbers", "zeros"])
+def test_half_precision_parts(change, fits):
+    """The rule for half-precision parts, which knows no scale: where six products are the faster ones (many values near
+    the maximum) or the only ones (sums of ordinary rows may be infinite) they stay."""
+    game = workloads.small_game(60, 50, 3, 510, "normal")
+    game.B = change(game.B.astype(np.float64)).astype(np.float32)
+    assert kernels.half_parts(game) == fits
+    for power in (-20, -2, 2) if np.abs(game.B).max() < 2.0 ** 90 else ():
+        game.B = np.ldexp(change(workloads.small_game(60, 50, 3, 510, "normal").B.astype(np.float64)), power).astype(np.float32)
+        assert kernels.half_parts(game) == fits
+
+
+@pytest.mark.parametrize("m, n, fits", [(32, 50, False), (33, 17, True), (33, 16, False), (128, 300, True), (129, 50, False)])
+def test_shapes_of_half_precision_parts(m, n, fits):
+    assert kernels.half_parts(workloads.small_game(m, n, 2, 511, "normal")) == fits
