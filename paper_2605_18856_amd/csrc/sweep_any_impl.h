@@ -204,6 +204,17 @@ __device__ __forceinline__ void argmax8_chain(const float *u, const float *w, fl
     n_eq += c;
 }
 
+// FIRST + ... of leaves FIRST to FIRST + COUNT (a power of two, of which the first LEAVES are there), two by two.
+template <int FIRST, int COUNT, int LEAVES, class F> __device__ __forceinline__ double sum_of_eights(F &&leaf)
+{
+    if constexpr (COUNT == 1) return leaf(std::integral_constant<int, FIRST>{});
+    else if constexpr (FIRST + COUNT / 2 >= LEAVES) return sum_of_eights<FIRST, COUNT / 2, LEAVES>(leaf);
+    else {
+        const double lower = sum_of_eights<FIRST, COUNT / 2, LEAVES>(leaf);
+        return lower + sum_of_eights<FIRST + COUNT / 2, COUNT / 2, LEAVES>(leaf);
+    }
+}
+
 // Folds `n` workgroup records (greatest value, lowest index among equals); every thread of the
 // workgroup gets the result.
 __device__ __forceinline__ void fold_records(const float *v, const long long *i, int n, float &bv, long long &bi)
@@ -729,18 +740,11 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
     // those of a row below 2^-60 do not end as subnormal numbers (the six products split such rows 2^64 times greater).
     constexpr float kTinyRow = 0x1p-60f;
     auto rounded_up = [](float most) __attribute__((always_inline)) { return most < kTinyRow ? 0x1p64f : 1.0f; };
-    auto wave_max = [](float v) __attribute__((always_inline)) {      // (in the last lane, then in all)
-        auto from = [&](auto lanes, auto rows) __attribute__((always_inline)) {
-            const int u = (int)__float_as_uint(v);
-            v = fmaxf(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(u, u, decltype(lanes)::value, decltype(rows)::value, 0xf, false)));
-        };
-        from(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});      // one, two, four and eight lanes before,
-        from(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
-        from(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
-        from(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
-        from(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});      // the last lane of the row before,
-        from(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});      // lane 31
-        return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
+    auto from_lane = [](double v, auto lanes) __attribute__((always_inline)) {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)u, decltype(lanes)::value, 0xf, 0xf, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), decltype(lanes)::value, 0xf, 0xf, false);
+        return __builtin_bit_cast(double, (unsigned long long)(unsigned)hi << 32 | (unsigned)lo);
     };
     // FILTER: the best responses of the candidate columns `columns`, where several values are within the margin of the
     // maximum, by the same rule.  The half-precision sums once more say which actions they are (from `floor` on, in any of
@@ -772,18 +776,22 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                 const int j = tt * 32 + __builtin_ctz(rest);
                 const f32x4 *b = payoffs + (size_t)j * (HALF / 2);
                 b += h * (HALF / 4);
-                double sum = 0.0;
                 float most = 0.0f;
+                // (laundered, and eight at a time: numbers in 64 bits kept across the loop, or all payoffs at once, would
+                // take the main path's registers)
+                const double sum = sum_of_eights<0, HALF <= 32 ? 4 : 8, HALF / 8>([&](auto leaf) __attribute__((always_inline)) {
+                    constexpr int e = 8 * decltype(leaf)::value;
+                    __builtin_amdgcn_sched_barrier(0);
+                    double eight = 0.0;
 #pragma unroll
-                for (int e = 0; e < HALF; ++e) {
-                    // (laundered, and eight at a time: numbers in 64 bits kept across the loop, or all payoffs at once, would
-                    // take the main path's registers)
-                    if (e % 8 == 0) __builtin_amdgcn_sched_barrier(0);
-                    float xe = xf[ct][XF ? e : 0];
-                    asm volatile("" : "+v"(xe));
-                    most = fmaxf(most, fabsf(xe));
-                    sum = fma((double)xe, (double)b[e / 4][e % 4], sum);
-                }
+                    for (int k = 0; k < 8; ++k) {
+                        float xe = xf[ct][XF ? e + k : 0];
+                        asm volatile("" : "+v"(xe));
+                        most = fmaxf(most, fabsf(xe));
+                        eight = fma((double)xe, (double)b[(e + k) / 4][k % 4], eight);
+                    }
+                    return eight;
+                });
                 const float up = rounded_up(fmaxf(most, pair_other(most, partner_addr)));
                 const float u = fmaxf((float)((sum + __shfl_xor(sum, 32, 64)) * (double)up), LEAST);      // (the same in both lanes)
                 const bool weighs = (own >> (j & 31)) & 1u;
@@ -802,44 +810,78 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         tie_count += __builtin_popcount((unsigned)__builtin_amdgcn_ballot_w64(nmatch >= 2 && cur > LEAST) & columns);
     };
 
-    // FILTER: one candidate column by the same sums (the two halves' chains in the same order), all actions of the type
-    // side by side in the lanes: an answer if one action alone has the greatest, else -1.  A column in 250 or 100 comes
-    // here, in short launches the last wavefront of them all: little code, which is cold, and a few rounds of loads (2 to
-    // 3 us where exact_actions takes 7: m = 60, n = 100, K = 20, 20000 rows 58 -> 47 us, 1000000 rows 1098 -> 1066;
-    // m = 128, n = 255, K = 4, 30000 rows 75 -> 62).
-    auto exact_column = [&](unsigned c, int t) __attribute__((always_inline)) {
+    // FILTER: one candidate column by the same sums, over the actions that the maps of its two lanes leave open (FORM 0:
+    // in all row tiles where a bit of `units` says that a lane has several): an answer if one of them alone has the
+    // greatest, else -1.  A column in 250 or 100 comes here, in short launches the last wavefront of them all, so what
+    // counts is the chain of latencies and the code, which is cold: sixteen lanes hold the row and an action's payoffs,
+    // eight components each, and four actions go side by side.  (All actions of the type in the lanes, each lane along
+    // its own, were sixteen round trips where n = 255, us: m = 128, n = 255, K = 4, 1000 rows 38.2 -> 32.2, 30000 rows 71.6
+    // -> 58.7; m = 128, n = 100, K = 10, 3000 rows 29.4 -> 26.1; m = 50, n = 90, K = 2, 10000 rows 22.1 -> 20.2; m = 60,
+    // n = 100, K = 20, 30000 rows 61.6 -> 59.6; exact_actions for every column 58 where that took 49, 20000 rows.)
+    auto exact_column = [&](unsigned c, int t, unsigned map0, unsigned map1, unsigned units) __attribute__((always_inline)) {
         constexpr float LEAST = -3.402823466e38f;
+        int lane_here = lane;                            // (laundered: what follows from it is not kept across the main loop)
+        asm volatile("" : "+v"(lane_here));
+        const int lane = lane_here, leaf = lane & 7, i0 = leaf < HALF / 8 ? (lane >> 3 & 1) * HALF + 8 * leaf : 2 * HALF;
+        typedef f32x4 f32x4_dword __attribute__((aligned(4)));
         const float *row = X + (size_t)(c < count ? c : count - 1u) * m;
-        const bool first_half = lane < HALF && lane < m, second_half = lane < HALF && HALF + lane < m;
-        const float x0 = first_half ? row[first_half ? lane : 0] : 0.0f, x1 = second_half ? row[second_half ? HALF + lane : 0] : 0.0f;
-        const float up = rounded_up(__builtin_amdgcn_ballot_w64(fmaxf(fabsf(x0), fabsf(x1)) >= kTinyRow) != 0ull ? kTinyRow : 0.0f);
-        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + (size_t)q.units * q.rec_bytes) + (size_t)t * n * (HALF / 2);
-        float best = -INFINITY;
+        // (a piece that would reach past the row ends with it, and counts from where it should have begun)
+        int from[2];
+        float xe[2][4], most = 0.0f;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int i = i0 + 4 * p;
+            from[p] = i < m - 4 ? i : m - 4;
+            const f32x4 r = *reinterpret_cast<const f32x4_dword *>(row + from[p]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                xe[p][k] = from[p] + k < i ? 0.0f : r[k];
+                most = fmaxf(most, fabsf(xe[p][k]));
+            }
+        }
+        const float up = rounded_up(__builtin_amdgcn_ballot_w64(most >= kTinyRow) != 0ull ? kTinyRow : 0.0f);
+        const float *payoffs = reinterpret_cast<const float *>(records + (size_t)q.units * q.rec_bytes) + (size_t)t * n * (2 * HALF);
+        float best = -INFINITY;                          // of the actions that the sixteen lanes had
         int jbest = 0;
         bool again = false;
-        constexpr int AT_ONCE = KS >= 6 ? 2 : 1;         // (as the registers allow)
 #pragma unroll 1
         for (int j0 = 0; j0 < n; j0 += 64) {
-            const int j = j0 + lane;
-            const f32x4 *b = payoffs + (size_t)(j < n ? j : n - 1) * (HALF / 2);
-            double s0 = 0.0, s1 = 0.0;
-#pragma unroll AT_ONCE
-            for (int e = 0; e < HALF; e += 8) {
-                const f32x4 b0[2] = { b[e / 4], b[e / 4 + 1] }, b1[2] = { b[HALF / 4 + e / 4], b[HALF / 4 + e / 4 + 1] };
+            const int jl = j0 + lane;
+            const unsigned map = jl & 4 ? map1 : map0;
+            bool open;
+            if constexpr (FORM == 0) open = (map >> (jl & 15) & 1u) != 0u && ((units >> (jl >> 2 & 1) & 1u) != 0u || ((map >> 16 & kUnitTiles) == (unsigned)jl >> 5 && (map >> (31 - (jl >> 4 & 1)) & 1u) != 0u));
+            else if constexpr (FORM == 1) open = jl < 32 && (map0 >> (31 - (jl >> 3 & 31)) & map0 >> (jl & 7) & 1u) != 0u;
+            else open = (map0 >> (31 - (jl >> 4 & 31)) & map0 >> (jl & 15) & 1u) != 0u;
+            unsigned long long rest = __builtin_amdgcn_ballot_w64(open && jl < n);
+#pragma unroll 1
+            while (rest != 0ull) {
+                int j = -1;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    s0 = fma((double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x0), e + k)), (double)b0[k / 4][k % 4], s0);
-                    s1 = fma((double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x1), e + k)), (double)b1[k / 4][k % 4], s1);
+                for (int a = 0; a < 4; ++a) {
+                    const int next = rest != 0ull ? j0 + __builtin_ctzll(rest) : -1;
+                    rest &= rest - 1ull;
+                    j = lane >> 4 == a ? next : j;
                 }
+                const float *b = payoffs + (size_t)(j < 0 ? 0 : j) * (2 * HALF);
+                const f32x4 b0 = *reinterpret_cast<const f32x4_dword *>(b + from[0]), b1 = *reinterpret_cast<const f32x4_dword *>(b + from[1]);
+                double sum = 0.0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) sum = fma((double)xe[k / 4][k % 4], (double)(k < 4 ? b0 : b1)[k % 4], sum);
+                // (both partners add the same two: pairs, fours and eights of lanes by their order in the row)
+                sum += from_lane(sum, std::integral_constant<int, 0xB1>{});      // quad_perm 1 0 3 2
+                sum += from_lane(sum, std::integral_constant<int, 0x4E>{});      // quad_perm 2 3 0 1
+                sum += from_lane(sum, std::integral_constant<int, 0x141>{});     // the other four of eight
+                sum += from_lane(sum, std::integral_constant<int, 0x140>{});     // the other half of the row
+                const float u = fmaxf((float)(sum * (double)up), LEAST);
+                again = j >= 0 ? u == best || (again && u < best) : again;
+                if (j >= 0 && u > best) { best = u; jbest = j; }
             }
-            const float u = j < n ? fmaxf((float)((s0 + s1) * (double)up), LEAST) : -INFINITY;
-            again = u == best || (again && u < best);
-            if (u > best) { best = u; jbest = j; }
         }
-        const float most = wave_max(best);
-        const unsigned long long at = __builtin_amdgcn_ballot_w64(best == most), twice = __builtin_amdgcn_ballot_w64(best == most && again);
+        auto of = [&](int l) __attribute__((always_inline)) { return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(best), l)); };
+        const float greatest = fmaxf(fmaxf(of(0), of(16)), fmaxf(of(32), of(48)));
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(best == greatest), twice = __builtin_amdgcn_ballot_w64(best == greatest && again);
         const int j = __builtin_amdgcn_readlane(jbest, (int)__builtin_ctzll(at | 1ull << 63));
-        return most > LEAST && twice == 0ull && (at & (at - 1ull)) == 0ull ? j : -1;
+        return greatest > LEAST && twice == 0ull && __builtin_popcountll(at) == 16 ? j : -1;
     };
 
     int buf = 0;
@@ -1094,7 +1136,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         float l[NT];
                         int js[NT];
                         bool clean[NT];
-                        [[maybe_unused]] unsigned columns[NT];       // FILTER: those without a value that stands clear
+                        [[maybe_unused]] unsigned columns[NT], maps[NT];      // FILTER: those without a value that stands clear
 #pragma unroll
                         for (int ct = 0; ct < NT; ++ct) {
                             const unsigned both = map[ct] | map_other[ct];
@@ -1103,6 +1145,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             if constexpr (FORM == 0) multi |= FILTER ? __builtin_amdgcn_ballot_w64(second[ct] >= floor[ct]) : dup[ct];
                             columns[ct] = (unsigned)(multi | (multi >> 32)) & valid32[ct];
                             if constexpr (FILTER) {
+                                maps[ct] = FORM == 0 ? map[ct] : both;
                                 // rows of zeros: all actions tie and are worth the same, and the map says the first
                                 columns[ct] &= ~zero32[ct];
                                 tie_count += __builtin_popcount(zero32[ct]);
@@ -1114,12 +1157,21 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                             js[ct] = j < (unsigned)n ? (int)j : 0;
                         }
                         if constexpr (FILTER) {
+                            // (bit h: lane half h of the column has values from the threshold on in several units)
+                            auto units = [&](int ct, int c) __attribute__((always_inline)) {
+                                const unsigned long long several = __builtin_amdgcn_ballot_w64(second[ct] >= floor[ct]) >> c;
+                                return ((unsigned)several & 1u) | ((unsigned)(several >> 32) & 1u) << 1;
+                            };
                             unsigned long long few = columns[0] | (NT == 2 ? (unsigned long long)columns[NT - 1] << 32 : 0ull);
                             if (__builtin_popcountll(few) <= 4)
 #pragma unroll 1
                                 for (; few != 0ull; few &= few - 1ull) {
                                     const int c = __builtin_ctzll(few);
-                                    const int j = exact_column(first + c, t);
+                                    const bool other = NT == 2 && c >= 32;
+                                    const unsigned of = other ? maps[NT - 1] : maps[0];
+                                    const int j = exact_column(first + c, t, (unsigned)__builtin_amdgcn_readlane((int)of, c % 32),
+                                                               FORM == 0 ? (unsigned)__builtin_amdgcn_readlane((int)of, c % 32 + 32) : 0u,
+                                                               FORM == 0 ? units(other ? NT - 1 : 0, c % 32) : 0u);
                                     if (j < 0) continue;
 #pragma unroll
                                     for (int ct = 0; ct < NT; ++ct) {

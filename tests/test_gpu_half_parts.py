@@ -155,6 +155,22 @@ def test_near_ties(shape, kind):
         assert bsse.bsse_sweep(g, Xd, len(X)).n_tie_evals == ties > 0
 
 
+@pytest.mark.parametrize("shape", [(33, 17, 16), (45, 32, 16), (48, 64, 16), (47, 250, 16), (49, 33, 16), (62, 95, 16), (64, 128, 16),
+                                   (66, 40, 16), (95, 200, 16), (97, 63, 16), (127, 31, 16), (128, 257, 16)], ids=IDS)
+def test_single_columns(shape):
+    """One to three rows a wavefront, which go one by one: rows that do not begin or end on a multiple of four, pairs in
+    the first and the last row tile, rows below 2^-60."""
+    m, n, K = shape
+    game = _near_pairs(m, n, K)
+    X = np.concatenate([workloads.host_candidates(m, 30, 390, kind) for kind in ("sparse", "dirichlet", "vertex")])
+    X[40:50] = np.ldexp(X[40:50], -70)
+    best = _rounded_once(game, np.where(X.max(axis=1, keepdims=True) < 2.0 ** -60, np.ldexp(X, 70), X))[0]
+    with _make(game) as g:
+        for c in range(0, len(X), 3):
+            few = 1 + c % 2 + c % 4 // 2
+            assert np.array_equal(_run_eval(g, X[c:c + few])[2], best[c:c + few]), c
+
+
 @pytest.mark.parametrize("shape", [(40, 24, 2), (50, 90, 2), (128, 70, 1)], ids=IDS)
 @pytest.mark.parametrize("small", [-12, -18, -24, -30])
 def test_small_components_decide(shape, small):
