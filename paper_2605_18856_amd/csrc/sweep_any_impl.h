@@ -754,7 +754,7 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
         constexpr float LEAST = -3.402823466e38f;
         const bool mine = (columns >> col) & 1u;
         if (!(gm > LEAST)) floor = -INFINITY;            // (nothing but minus infinity and no numbers: every action)
-        const f32x4 *payoffs = reinterpret_cast<const f32x4 *>(records + (size_t)q.units * q.rec_bytes) + (size_t)t * n * (HALF / 2);
+        const float *payoffs = reinterpret_cast<const float *>(records + (size_t)q.units * q.rec_bytes) + (size_t)t * n * (2 * HALF);
         float cur = LEAST;
         int jbest = 0, nmatch = 0;
 #pragma unroll 1
@@ -774,11 +774,13 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
 #pragma unroll 1
             for (unsigned rest = (unsigned)__builtin_amdgcn_readfirstlane((int)near); rest != 0u; rest &= rest - 1u) {
                 const int j = tt * 32 + __builtin_ctz(rest);
-                const f32x4 *b = payoffs + (size_t)j * (HALF / 2);
-                b += h * (HALF / 4);
+                // (the payoffs in one request, spread over the lanes; eight after eight by every lane, a round trip each, a tie
+                // held a short launch up by another 6 us: m = 128, n = 32, K = 6, 10000 rows 35.0 -> 29.3, 25 without one)
+                const float *b = payoffs + (size_t)j * (2 * HALF);
+                const int at = lane < HALF ? lane : HALF - 1;
+                const float b0 = b[at], b1 = b[HALF + at];
                 float most = 0.0f;
-                // (laundered, and eight at a time: numbers in 64 bits kept across the loop, or all payoffs at once, would
-                // take the main path's registers)
+                // (laundered, and eight at a time: numbers in 64 bits kept across the loop would take the main path's registers)
                 const double sum = sum_of_eights<0, HALF <= 32 ? 4 : 8, HALF / 8>([&](auto leaf) __attribute__((always_inline)) {
                     constexpr int e = 8 * decltype(leaf)::value;
                     __builtin_amdgcn_sched_barrier(0);
@@ -788,7 +790,8 @@ __global__ void __launch_bounds__(THREADS, occupancy(TERMS, KS, FORM, MANY)) swe
                         float xe = xf[ct][XF ? e + k : 0];
                         asm volatile("" : "+v"(xe));
                         most = fmaxf(most, fabsf(xe));
-                        eight = fma((double)xe, (double)b[(e + k) / 4][k % 4], eight);
+                        const unsigned lower = __builtin_amdgcn_readlane(__float_as_uint(b0), e + k), upper = __builtin_amdgcn_readlane(__float_as_uint(b1), e + k);
+                        eight = fma((double)xe, (double)__uint_as_float(h ? upper : lower), eight);
                     }
                     return eight;
                 });
