@@ -4,6 +4,7 @@
 #include "sweep_any_impl.h"
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 #include "done_device.h"
 
@@ -43,11 +44,19 @@ float half_margin(int ks)
 // Payoffs from here on: rows of ordinary size might have infinite sums, which scaled ones do not show.
 constexpr float kHalfMost = 0x1p100f;
 
+// (on the bits, which are ordered as the numbers are: whole numbers are compared several at a time)
 float greatest_of(size_t elems, const float *B)
 {
-    float most = 0.0f;
-    for (size_t e = 0; e < elems; ++e) most = std::max(most, std::fabs(B[e]));
-    return most;
+    int most = 0;
+    for (size_t e = 0; e < elems; ++e) {
+        int bits;
+        memcpy(&bits, &B[e], 4);
+        bits &= 0x7FFFFFFF;
+        most = bits > most ? bits : most;
+    }
+    float v;
+    memcpy(&v, &most, 4);
+    return v;
 }
 // Where the payoffs behind the records begin (terms 2).
 __host__ __device__ inline size_t exact_off(const AnyGeo &q) { return (size_t)q.units * q.rec_bytes; }
