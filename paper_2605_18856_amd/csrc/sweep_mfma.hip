@@ -1586,10 +1586,17 @@ double twice_summed(int m, int n, int K, const float *B, const std::function<flo
         int near = 0, tied = 0;
         for (int r = 0; r < rows; ++r) {
             float first = -INFINITY, second = -INFINITY;
-            std::fill(u.begin(), u.end(), 0.0f);
-            for (int i = 0; i < m; ++i) {
-                const float *row = B + ((size_t)t * m + i) * n;
-                for (int j = 0; j < n; ++j) u[j] += x[r][i] * row[j];
+            const float *Bt = B + (size_t)t * m * n;
+            int done = 0;
+            for (; done + 16 <= n; done += 16) {                        // (sixteen sums in registers)
+                float sum[16] = {};
+                for (int i = 0; i < m; ++i)
+                    for (int k = 0; k < 16; ++k) sum[k] += x[r][i] * Bt[(size_t)i * n + done + k];
+                for (int k = 0; k < 16; ++k) u[done + k] = sum[k];
+            }
+            for (; done < n; ++done) {
+                u[done] = 0.0f;
+                for (int i = 0; i < m; ++i) u[done] += x[r][i] * Bt[(size_t)i * n + done];
             }
             for (int j = 0; j < n; ++j) {
                 second = u[j] > first ? first : u[j] > second ? u[j] : second;
