@@ -32,8 +32,11 @@ PEAK_TFLOPS = {"mfma_f32": 157.3, "mfma_bf16": 2500.0, "valu": 78.6, "valu_bf16"
                # small-game kernel 6x)
                "mfma_split3": 2500.0, "mfma_split6": 2500.0, "mfma_small_split6": 2500.0}
 # (the part products that are always summed; the others, where they may decide, add 2.5 % to the matrix
-# instructions of config 3.  Config 5's small whole numbers run on the six-bit matrix instruction instead)
+# instructions of config 3)
 EXECUTED_FLOP_FACTOR = {"mfma_split3": 2.0, "mfma_split6": 3.0, "mfma_small_split6": 6.0}
+# Peak and part products of workloads that run on another instruction than their path's: config 5's small
+# whole numbers take four six-bit parts of a row (32x32x64 in 32 cycles, on 1 024 SIMDs at 2.4 GHz)
+OTHER_UNIT = {"config5": (10066.0, 4.0)}
 
 # HBM bytes per launch of the fused sweep kernel, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
 # (profiles/sweep_kernels_hbm_traffic.md; FETCH_SIZE reads half of a known-size copy on this part,
@@ -218,9 +221,9 @@ def run_workload(name, steps, warmup, want_cpu_baseline=True):
     # 4m bytes per candidate (rows read once; the payoffs stay in cache / LDS and are not counted)
     flops = chunk * game.K * (2.0 * game.m * game.n + 2.0 * game.m)
     bytes_ = 0.0 if fused else chunk * 4.0 * game.m
-    flop_peak = PEAK_TFLOPS[path]
+    flop_peak, factor = OTHER_UNIT.get(name, (PEAK_TFLOPS[path], EXECUTED_FLOP_FACTOR.get(path, 1.0)))
     t_hbm = bytes_ / (HBM_PEAK_GBS * 1e9)
-    t_flop = flops * EXECUTED_FLOP_FACTOR.get(path, 1.0) / (flop_peak * 1e12)   # what the unit executes
+    t_flop = flops * factor / (flop_peak * 1e12)                                # what the unit executes
     if t_hbm >= t_flop:
         bound, unit, peak = "hbm", "GB/s", HBM_PEAK_GBS
         achieved = bytes_ / (k_ms * 1e-3) / 1e9
@@ -246,11 +249,11 @@ def run_workload(name, steps, warmup, want_cpu_baseline=True):
         roofline["frac_counting_every_generator_and_argmax_operation"] = ops / (k_ms * 1e-3) / 1e12 / peak
         roofline["frac_at_step_rate"] = flops / (ms_per_step * 1e-3) / 1e12 / peak
     if path in EXECUTED_FLOP_FACTOR and bound == "mfma":
-        # the split path does an fp32-accurate contraction with 2, 3 or 6 bf16 products per term:
-        # frac prices the algorithmic flops against the bf16 peak; these fields give the rate the
-        # matrix cores actually run at and the comparison with the fp32 matrix-core peak
-        roofline["executed_mfma_tflops"] = achieved * EXECUTED_FLOP_FACTOR[path]
-        roofline["executed_frac"] = achieved * EXECUTED_FLOP_FACTOR[path] / peak
+        # the split path does an fp32-accurate contraction with 2, 3 or 6 bf16 products per term (or four
+        # six-bit ones): frac prices the algorithmic flops against the peak of that instruction; these
+        # fields give the rate the matrix cores actually run at and the comparison with the fp32 peak
+        roofline["executed_mfma_tflops"] = achieved * factor
+        roofline["executed_frac"] = achieved * factor / peak
         roofline["frac_of_fp32_mfma_peak"] = achieved / PEAK_TFLOPS["mfma_f32"]
 
     cpu = cpu_baseline_leg(game, g, chunk, lattice, True) if want_cpu_baseline else None
@@ -458,7 +461,8 @@ def main():
         line["measured_ceilings"] = c
         rf = line["roofline"]
         key = {"GB/s": "stream_read_GBs", "TFLOP/s": "mfma_bf16_TFLOPs" if rf["peak"] == 2500.0 else "mfma_f32_TFLOPs"}[rf["unit"]]
-        rf["frac_of_measured_ceiling"] = rf["achieved"] / c[key]
+        if args.workload not in OTHER_UNIT:              # (no loop of that instruction is measured)
+            rf["frac_of_measured_ceiling"] = rf["achieved"] / c[key]
         if args.workload in MIXES:
             # what the bf16 matrix cores keep under this kernel's mix of matrix and vector instructions
             # with nothing else in the way (no loads, dependencies or barriers)
