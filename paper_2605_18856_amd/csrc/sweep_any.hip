@@ -279,8 +279,9 @@ static float half_margin_of(int m, int n, int ks, const float *B)
 // watches: six products.
 // Payoffs of very different sizes (forbidden actions at -10^3 beside -2 to 2), payoffs with a large part in common and
 // equal columns put many values within the margin; from about an eighth of the tiles on six products are the faster
-// ones (normal payoffs plus 10, 30, 100, m = 60, n = 100, K = 20, 200000 rows: 287, 332, 417 us, and 350, 350, 370 with
-// six; shares 0.03, 0.09, 0.27).
+// ones on the shapes with the least matrix work (200000 rows, K = 20, normal payoffs plus 30, 100, 200, 400, us, these and
+// six products: m = 60, n = 100 290, 356, 385, 476, and 350, 387, 389, 422, the second with a share of 0.27; m = 40, n = 24
+// 117, 131, 156, and 105, 111, 122 from 100 on).
 bool any_half_suits(int m, int n, int K, const float *B)
 {
     if (m <= 32 || n <= 16 || !any_supported(m, n)) return false;

@@ -45,7 +45,7 @@ typedef void __attribute__((address_space(3))) *lds_ptr;
 constexpr int WAVES = 4, THREADS = WAVES * 64;
 
 // Kernels of two kinds, for three workgroups on a compute unit (`many`) and for two: splits with two k-steps,
-// which spill 15 and 25 registers at a block's start with three wavefronts a SIMD, and long bf16 rows, which
+// which spill 15 to 29 registers at a block's start with three wavefronts a SIMD, and long bf16 rows, which
 // have one candidate tile a wavefront with three and two with two.  The others have one kernel.
 constexpr bool two_kinds(int terms, int ks, int form)
 {

@@ -10,7 +10,7 @@
 // two bf16 parts were sixteen of about the same length, and a row tile's fragments are 3 KiB instead of 8.
 //
 // Decisions.  The sums decide where the maximum stands clear of the next value by more than the row's remainder
-// and the instructions' roundings can change (fp6_pack): then it is the maximum of the true sums.  Other columns sum
+// and the instructions' roundings can change (fp6_margins): then it is the maximum of the true sums.  Other columns sum
 // three bf16 parts of the row, from the same fragments, as sweep_mfma.hip's settle does; ties go to the exact routine.
 // Rows of few bits (multiples of 1/16, say), which tie often, have exact sums as they are and go there at once (m = 128,
 // K = 32, 40000 such rows 933 us, without summing again 634, on bf16 parts alone 771).
@@ -21,7 +21,7 @@
 // L2, requested when the best response is known and met during the next type.
 // Workgroups of four wavefronts, two a compute unit, so that no barrier keeps the two wavefronts of a SIMD in step.
 //
-// Against two bf16 products (us): m = 128, n = 256, K = 256, 131072 rows 3115 and 2183; K = 100, 25000 rows 297 and 218;
+// Against two bf16 products (us): m = 128, n = 256, K = 256, 131072 rows 3225 and 2215; K = 100, 25000 rows 297 and 218;
 // m = 100, K = 100, 66000 rows 835 and 510; m = 70, K = 30, 1000 rows 31 and 24.  Matrix and vector time still add up
 // (a part less: 1788 of 2183, about 44 cycles an instruction); of the rest 4 % is the gather of leader columns and 2 %
 // the columns that are summed again (0.9 % of the tiles).  Three parts would leave 25 % of the tiles to be summed again.
